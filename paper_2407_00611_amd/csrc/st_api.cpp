@@ -501,7 +501,20 @@ st_status st_schedule_report(int32_t P, int32_t C, int64_t B, int64_t N, int64_t
 // of 256 queries on 256 compute units) is split over the visited chunks: every query tile gets several
 // workgroups, each with a contiguous share of the chunks and a partial state of its own, and one combine
 // pass folds the states (the chunks of a ring step are independent until the fold, Algorithm 1).
+//
+// fp32: a workgroup owns 32 query rows and its eight wavefronts share the keys.  Splitting pays once it saves more
+// than the combine launch costs (about 10 us): a 32-key tile is 64 D cycles of a SIMD's matrix unit, two wavefronts to a SIMD.
+int fwd_splits_f32(const st_ring_desc* d, int n_visible) {
+  const int64_t wgs = (int64_t)d->B * d->Hq * ((d->Sq + 31) / 32);
+  if (wgs < 1 || wgs >= 192 || n_visible < 2 || n_visible > st::kMaxTable) return 1;
+  int64_t n = 256 / wgs;
+  if (n > n_visible) n = n_visible;
+  if (n > 16) n = 16;
+  const double us = (double)n_visible * ((d->Sk + 31) / 32) / 8 * 2 * 64 * d->D / 2400;    // one workgroup, unsplit
+  return n > 1 && us * (1 - 1.0 / n) > 10 ? (int)n : 1;
+}
 int fwd_splits(const st_ring_desc* d, int n_visible) {
+  if (d->dtype == ST_F32) return fwd_splits_f32(d, n_visible);
   if (d->dtype != ST_BF16 || (d->D != 128 && d->D != 64) || n_visible < 2 || n_visible > st::kMaxTable) return 1;
   if (d->Sq < st::kQTileFastRows || d->Sk < st::kQTileFastKeys) return 1;
   const int64_t wgs = (int64_t)d->B * d->Hq * (d->Sq / st::kQTileFastRows);
@@ -528,7 +541,7 @@ size_t st_ring_workspace_bytes(const st_ring_desc* d, int32_t mode, int32_t back
   // the split grows with the number of visited chunks up to one launch's table, and any subset may be visited
   const int n_most = d->n_chunks < st::kMaxTable ? d->n_chunks : st::kMaxTable;
   const int splits = fwd_splits(d, n_most);
-  return (size_t)(splits > 1 ? splits + 1 : 1) * (n_o + n_l);
+  return (size_t)(splits == 1 ? 1 : d->dtype == ST_BF16 ? splits + 1 : splits) * (n_o + n_l);
 }
 
 st_status st_ring_fwd(const st_ring_desc* d, const st_tensor* q, const int32_t* order, const int32_t* member_of,
@@ -559,7 +572,9 @@ st_status st_ring_fwd(const st_ring_desc* d, const st_tensor* q, const int32_t* 
   a.q = view_of(q);
   set_table_strides(a.t, d);
   int splits = mode == ST_RING_FUSED ? fwd_splits(d, n) : 1;
-  if (splits > 1 && !st::fwd_fast_usable(a)) splits = 1;      // only the hand-scheduled kernel pair walks a split table
+  if (splits > 1 && d->dtype == ST_BF16 && !st::fwd_fast_usable(a)) splits = 1;   // only the hand-scheduled kernel pair walks a split table
+  // without a workspace the fp32 forward is one launch over the whole table
+  if (d->dtype == ST_F32 && (workspace == nullptr || workspace_bytes < st_ring_workspace_bytes(d, mode, 0))) splits = 1;
   const bool need_ws = mode == ST_RING_STEPWISE || n > st::kMaxTable || splits > 1;
   if (need_ws) {
     if (workspace == nullptr || workspace_bytes < st_ring_workspace_bytes(d, mode, 0)) return fail(ST_ERR_WORKSPACE, "forward workspace needs %zu bytes", st_ring_workspace_bytes(d, mode, 0));
@@ -584,8 +599,8 @@ st_status st_ring_fwd(const st_ring_desc* d, const st_tensor* q, const int32_t* 
     ST_HIP(launch_fwd(d->dtype, a, stream), "split forward launch");
     st::CombineArgs c;
     memset(&c, 0, sizeof(c));
-    c.n = splits + 1;                               // one state per split, and the general workgroups' own
-    for (int y = 0; y < splits + 1; ++y) {
+    c.n = splits + (d->dtype == ST_BF16 ? 1 : 0);   // one state per split, and the general workgroups' own
+    for (int y = 0; y < c.n; ++y) {
       c.o[y] = part_o + (int64_t)y * a.split_o;
       c.lse[y] = part_l + (int64_t)y * a.split_l;
     }

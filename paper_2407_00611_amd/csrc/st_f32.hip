@@ -1,38 +1,44 @@
-// fp32 reference-precision kernels: any D <= 256 (multiple of 4), any Sq / Sk.
-// Plain VALU code, one wavefront per query row (forward, dQ) or per key row (dK, dV):
-// deterministic, no atomics.  These serve the fp32 storage dtype; the bf16 MFMA
-// kernels are the throughput path.
+// fp32 kernels: any D <= 256 (multiple of 8), any Sq / Sk, on the fp32 matrix instruction v_mfma_f32_32x32x2_f32
+// (exact fp32 products and sums, 256 flop per clock and compute unit: twice what v_fma_f32 issues, and 64 cycles per
+// instruction, under which operand loads and the softmax arithmetic hide).  Deterministic, no atomics: every
+// accumulator element has one owning workgroup, whose wavefronts add up in a fixed order.
+//
+//   forward, dQ   a workgroup owns 32 query rows of one head; its wavefronts take the 32-key tiles of the walk in
+//                 turn (a 512-row shard of 8 heads has only 128 such workgroups, so the keys have to be split inside
+//                 one) and fold their states through LDS at the end.  Q and dO rows sit in LDS, shared by all.
+//                     S^T = K Q^T, dP^T = V dO^T         lane = query column, registers = 16 keys
+//                     O^T += V^T P^T, dQ^T += K^T dS^T   the S^T registers are the B operand as they stand
+//   dK / dV       a workgroup owns 32 keys; its wavefronts take the (query head of the group, 32-row tile) pairs.
+//                     S = Q K^T, dP = dO V^T             lane = key column, registers = 16 query rows
+//                     dV^T += dO^T P, dK^T += Q^T dS
+//
+// Operand layouts (lane l: r = l % 32, g = l / 32): A holds row r at k = g, B holds column r at k = g, C holds column
+// r at rows 8 (v / 4) + 4 g + v % 4, v = 0..15.  The k order is free as long as A and B agree, which gives
+//   * contractions along D: one 16-byte load of elements 8 j + 4 g .. + 3 of row r feeds four instructions,
+//   * contractions along a tile's rows: step v takes register v of a C tile as B and row 8 (v / 4) + 4 g + v % 4 as A.
+//
+// One wavefront per row with scalar fused multiply-adds, as these kernels were before, read K with every lane on a
+// row of its own and one load per four multiply-adds: 8 heads x 512 rows x 8 chunks of 512 keys at D = 128 took 2460 us
+// forward, 2640 us dQ, 3590 us dK / dV (3.2 TFLOP/s).  Now 108, 276 and 203 us (dQ has 128 workgroups for 256 compute
+units there; dK / dV executes 16 GFLOP, 105 us at the 154 TFLOP/s of a large fp32 matrix product on this card).
+#include <type_traits>
+
 #include "st_internal.h"
+#include "st_mfma.h"
 
 namespace st {
 namespace {
 
-constexpr int kWaves = 4;          // rows per workgroup
-constexpr int kMaxD = 256;
-constexpr int kDV = kMaxD / 64;    // d-values owned by a lane
+constexpr int kT = 32;             // rows of every tile
 
-__device__ __forceinline__ float wave_max(float x) {
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) x = fmaxf(x, __shfl_xor(x, o));
-  return x;
-}
-__device__ __forceinline__ float wave_sum(float x) {
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) x += __shfl_xor(x, o);
-  return x;
+__device__ __forceinline__ f32x16 mfma_f32(float a, float b, f32x16 c) {
+  return __builtin_amdgcn_mfma_f32_32x32x2f32(a, b, c, 0, 0, 0);
 }
 
-__device__ __forceinline__ float dot_row(const float* __restrict__ lds_vec, const float* __restrict__ row, int D) {
-  float acc = 0.f;
-  for (int d = 0; d < D; d += 4) {
-    const float4 x = *reinterpret_cast<const float4*>(row + d);
-    acc = fmaf(lds_vec[d], x.x, acc);
-    acc = fmaf(lds_vec[d + 1], x.y, acc);
-    acc = fmaf(lds_vec[d + 2], x.z, acc);
-    acc = fmaf(lds_vec[d + 3], x.w, acc);
-  }
-  return acc;
-}
+// wavefronts per workgroup: eight (two per SIMD, which hide each other's loads) as long as a wavefront's accumulators
+// and operands fit 256 registers
+template <int DP>
+constexpr int waves() { return DP <= 128 ? 8 : 4; }
 
 // number of leading keys of a chunk that query position qpos may see
 __device__ __forceinline__ int visible_keys(const Shape& s, int64_t qpos, int64_t k0) {
@@ -41,215 +47,573 @@ __device__ __forceinline__ int visible_keys(const Shape& s, int64_t qpos, int64_
   return n < 0 ? 0 : (n > s.Sk ? s.Sk : (int)n);
 }
 
-// ---------------------------------------------------------------- forward
-__global__ __launch_bounds__(kWaves * 64) void fwd_f32_kernel(const FwdArgs a) {
-  __shared__ float qs[kWaves][kMaxD];
-  const Shape& s = a.s;
-  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-  const int i = blockIdx.x * kWaves + w, h = blockIdx.y, b = blockIdx.z;
-  const int g = h / (s.Hq / s.Hkv);
-  const bool live = i < s.Sq;
-  if (live) {
-    const float* qrow = (const float*)a.q.ptr + b * a.q.sb + (int64_t)i * a.q.ss + h * a.q.sh;
-    for (int d = lane; d < s.D; d += 64) qs[w][d] = qrow[d];
-  }
-  __syncthreads();
-  if (!live) return;
+// row of a tile that register v of a C tile holds in half g
+__device__ __forceinline__ int c_row(int v, int g) { return 8 * (v / 4) + 4 * g + v % 4; }
 
-  const int64_t qpos = q_pos(s, i);
-  float m = -INFINITY, l = 0.f, acc[kDV] = {0.f, 0.f, 0.f, 0.f};
-  for (int c = 0; c < a.t.n; ++c) {
-    const float* kb = (const float*)a.t.k[c] + b * a.t.ksb + g * a.t.ksh;
-    const float* vb = (const float*)a.t.v[c] + b * a.t.vsb + g * a.t.vsh;
-    const int nvis = visible_keys(s, qpos, a.t.k_offset[c]);
-    for (int t0 = 0; t0 < nvis; t0 += 64) {
-      const int t = t0 + lane;
-      const bool valid = t < nvis;
-      const float sc = valid ? s.scale * dot_row(qs[w], kb + (int64_t)t * a.t.kss, s.D) : -INFINITY;
-      const float m_new = fmaxf(m, wave_max(sc));          // finite: lane 0 is always valid
-      const float p = valid ? expf(sc - m_new) : 0.f;
-      const float alpha = expf(m - m_new);                 // m = -inf on the first tile -> 0
-      l = l * alpha + wave_sum(p);
+// ---- streamed operands, in pieces of N (32 or 16) registers.  While one piece is contracted (N instructions of 64
+// cycles) the next one is on its way; two pieces and the accumulators are what fits beside a second wavefront.
+// FULL: D == DP.  Otherwise the columns at or beyond D read as zero.
+template <int N>
+struct Piece {
+  float x[N];
+};
+template <int DP, int N>
+constexpr int row_pieces() { return (DP + 2 * N - 1) / (2 * N); }           // 2 N columns each
+template <int DP, int N>
+constexpr int piece_rows() {                                                // registers v of a C tile per column piece
+  int n = 16;
+  while (n * (DP / 32) > N) n /= 2;
+  return n;
+}
+template <int DP, int N>
+constexpr int col_pieces() { return 16 / piece_rows<DP, N>(); }
+
+// Row r of a tile as the k-along-D operand: columns 2 N n + 8 j + 4 g .. + 3
+template <int DP, bool FULL, int N>
+__device__ __forceinline__ void load_rows(Piece<N>& f, const float* row, int n, int D, int g) {
 #pragma unroll
-      for (int x = 0; x < kDV; ++x) acc[x] *= alpha;
-      const int nt = min(64, nvis - t0);
-      for (int tt = 0; tt < nt; ++tt) {
-        const float pt = __shfl(p, tt);
-        const float* vrow = vb + (int64_t)(t0 + tt) * a.t.vss;
+  for (int j = 0; j < N / 4; ++j) {
+    const int d = 2 * N * n + 8 * j;
+    if (d >= DP) continue;
+    float4 x = make_float4(0.f, 0.f, 0.f, 0.f);
+    if (FULL || d < D) x = *reinterpret_cast<const float4*>(row + d + 4 * g);
+    f.x[4 * j] = x.x; f.x[4 * j + 1] = x.y; f.x[4 * j + 2] = x.z; f.x[4 * j + 3] = x.w;
+  }
+}
+
+// The transposed operand of a tile X: lane r = column 32 db + r, register v = row c_row(v, g).
+// Rows at or beyond `limit` (tile-relative, >= 1) re-read the last one.
+template <int DP, bool FULL, int N>
+__device__ __forceinline__ void load_cols(Piece<N>& f, const float* tile, int64_t stride, int limit, int n, int D, int r, int g) {
+  constexpr int DB = DP / 32;
 #pragma unroll
-        for (int x = 0; x < kDV; ++x) {
-          const int d = lane + 64 * x;
-          if (d < s.D) acc[x] = fmaf(pt, vrow[d], acc[x]);
-        }
-      }
-      m = m_new;
+  for (int u = 0; u < piece_rows<DP, N>(); ++u) {
+    const int v = n * piece_rows<DP, N>() + u, row = 8 * (v / 4) + v % 4;
+    const float* p = tile + r;
+    if (limit >= kT) p += (int64_t)(4 * g) * stride + (int64_t)row * stride;
+    else p += (int64_t)min(row + 4 * g, limit - 1) * stride;
+#pragma unroll
+    for (int db = 0; db < DB; ++db) f.x[DB * u + db] = FULL || 32 * db + r < D ? p[32 * db] : 0.f;
+  }
+}
+
+// ---- resident tile in LDS: kT rows of D floats, rows padded by 4 floats so that 16-byte reads of one column by
+// consecutive rows spread over the banks; rows at or beyond `limit` and columns at or beyond D are zero
+template <int DP>
+constexpr int lds_stride() { return DP + 4; }
+template <int DP>
+__device__ __forceinline__ void stage_tile(float* lds, const float* base, int64_t stride, int row0, int limit, int D, int tid) {
+  for (int p = tid; p < kT * (DP / 4); p += waves<DP>() * 64) {
+    const int row = p / (DP / 4), d = p % (DP / 4) * 4;
+    float4 x = make_float4(0.f, 0.f, 0.f, 0.f);
+    if (row0 + row < limit && d < D) x = *reinterpret_cast<const float4*>(base + (int64_t)(row0 + row) * stride + d);
+    *reinterpret_cast<float4*>(lds + row * lds_stride<DP>() + d) = x;
+  }
+}
+
+// C tile (rows: the streamed tile's, columns: the LDS tile's rows) += contraction along its row piece n
+template <int DP, int N>
+__device__ __forceinline__ void contract_d(f32x16& c, const Piece<N>& f, const float* lds, int n, int r, int g) {
+#pragma unroll
+  for (int j = 0; j < N / 4; ++j) {
+    const int d = 2 * N * n + 8 * j;
+    if (d >= DP) continue;
+    const float4 y = *reinterpret_cast<const float4*>(lds + r * lds_stride<DP>() + d + 4 * g);
+    c = mfma_f32(f.x[4 * j], y.x, c);
+    c = mfma_f32(f.x[4 * j + 1], y.y, c);
+    c = mfma_f32(f.x[4 * j + 2], y.z, c);
+    c = mfma_f32(f.x[4 * j + 3], y.w, c);
+  }
+}
+
+// acc^T[d][column] += sum over the rows of column piece n of X[row][d] w[row][column]
+template <int DP, int N>
+__device__ __forceinline__ void contract_rows(f32x16 (&acc)[DP / 32], const Piece<N>& f, const f32x16& w, int n) {
+  constexpr int DB = DP / 32;
+#pragma unroll
+  for (int u = 0; u < piece_rows<DP, N>(); ++u)
+#pragma unroll
+    for (int db = 0; db < DB; ++db) acc[db] = mfma_f32(f.x[DB * u + db], w[n * piece_rows<DP, N>() + u], acc[db]);
+}
+
+// ---- infinities and NaN in a tile that a mask edge crosses.  The matrix instruction multiplies a row that a column
+// does not see by a weight of zero, and 0 * inf is NaN; a row must not reach a column that it is masked from.  Such a
+// tile ("dirty", found by reading it once more: only tiles on the edge are looked at) is contracted with those values
+// taken as zero, and the workgroup adds them to the stored result of the columns that do see them.
+__device__ __forceinline__ bool finite(float x) { return fabsf(x) <= 3.402823466e38f; }
+
+__device__ __forceinline__ bool tile_dirty(const float* tile, int64_t stride, int limit, int D, int lane) {
+  bool bad = false;
+  for (int p = lane; p < limit * (D / 4); p += 64) {
+    const float4 x = *reinterpret_cast<const float4*>(tile + (int64_t)(p / (D / 4)) * stride + p % (D / 4) * 4);
+    bad = bad || !(finite(x.x) && finite(x.y) && finite(x.z) && finite(x.w));
+  }
+  return __any(bad);
+}
+
+template <int N>
+__device__ __forceinline__ void scrub(Piece<N>& f) {
+#pragma unroll
+  for (int k = 0; k < N; ++k) f.x[k] = finite(f.x[k]) ? f.x[k] : 0.f;
+}
+
+// out[d] += X[t][d] wherever that is no finite number, for the rows t in [lo, hi); as_nan: their weight may have either sign
+__device__ __forceinline__ void add_nonfinite(float* out, float* out2, const float* x0, int64_t stride, int lo, int hi, int D, int g, bool as_nan) {
+#pragma unroll 1
+  for (int t = lo; t < hi; ++t)
+#pragma unroll 1
+    for (int d = 0; d < D; ++d) {
+      const float x = x0[(int64_t)t * stride + d];
+      if (((d / 4) & 1) != g || finite(x)) continue;
+      out[d] += as_nan ? __builtin_nanf("") : x;
+      if (out2) out2[d] = out[d];
+    }
+}
+
+template <int N>
+__device__ __forceinline__ void zero_acc(f32x16 (&acc)[N]) {
+#pragma unroll
+  for (int i = 0; i < N; ++i)
+#pragma unroll
+    for (int v = 0; v < 16; ++v) acc[i][v] = 0.f;
+}
+
+// One tree step of the fold of the wavefronts' accumulators: the upper half of `n` wavefronts puts its values down.
+template <int N>
+__device__ __forceinline__ void put_acc(float* slot, const f32x16 (&acc)[N], int lane) {
+#pragma unroll
+  for (int i = 0; i < N; ++i)
+#pragma unroll
+    for (int v = 0; v < 16; ++v) slot[(16 * i + v) * 64 + lane] = acc[i][v];
+}
+template <int N>
+__device__ __forceinline__ void add_acc(const float* slot, f32x16 (&acc)[N], float own, float other, int lane) {
+#pragma unroll
+  for (int i = 0; i < N; ++i)
+#pragma unroll
+    for (int v = 0; v < 16; ++v) acc[i][v] = own * acc[i][v] + other * slot[(16 * i + v) * 64 + lane];
+}
+
+// Walk of a wavefront over the 32-key tiles of the chunk table: tile number `wave`, wave + waves, ... of the walk
+struct KeyWalk {
+  int c, t, nv;     // chunk, first key of the tile, visible keys of the chunk for the workgroup's last row
+  int skip;         // tiles still to pass over
+};
+template <int DP>
+__device__ __forceinline__ bool walk_next(KeyWalk& w, const Shape& s, const ChunkTable& tab, int c_hi, int64_t last_pos) {
+  while (w.c < c_hi) {
+    const int left = w.t < w.nv ? (w.nv - w.t + kT - 1) / kT : 0;
+    if (w.skip < left) {
+      w.t += w.skip * kT;
+      w.skip = 0;
+      return true;
+    }
+    w.skip -= left;
+    if (++w.c < c_hi) {
+      w.t = 0;
+      w.nv = visible_keys(s, last_pos, tab.k_offset[w.c]);
     }
   }
+  return false;
+}
+
+// ---------------------------------------------------------------- forward
+// Bounded by the matrix instructions: D per 32 x 32 tile pair and 64 cycles each.  Eight wavefronts share the 32 rows.
+template <int DP, bool FULL>
+__global__ __launch_bounds__(waves<DP>() * 64) void fwd_f32_kernel(const FwdArgs a) {
+  constexpr int NW = waves<DP>(), DB = DP / 32, N = 32, NR = row_pieces<DP, N>(), NC = col_pieces<DP, N>();
+  __shared__ __attribute__((aligned(16))) float qs[kT * lds_stride<DP>()];
+  __shared__ float fold[NW / 2 * DB * 16 * 64];
+  __shared__ float fold_m[NW / 2 * 64], fold_l[NW / 2 * 64];
+  __shared__ int any_dirty;
+  const Shape& s = a.s;
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int g = lane >> 5, r = lane & 31;
+  const int n_qt = (s.Sq + kT - 1) / kT;
+  int qt, hb;
+  qtile_block(blockIdx.x, gridDim.x, n_qt, s.causal, qt, hb);
+  const int h = hb % s.Hq, b = hb / s.Hq, hk = h / (s.Hq / s.Hkv);
+  const int row0 = qt * kT;
+  stage_tile<DP>(qs, (const float*)a.q.ptr + b * a.q.sb + h * a.q.sh, a.q.ss, row0, s.Sq, s.D, tid);
+  if (tid == 0) any_dirty = 0;
+  __syncthreads();
+
+  const int i = min(row0 + r, s.Sq - 1);
+  const int64_t qpos = q_pos(s, i), first_pos = q_pos(s, row0), last_pos = q_pos(s, min(row0 + kT, s.Sq) - 1);
+  float m = -INFINITY, l = 0.f;
+  f32x16 acc[DB];
+  zero_acc(acc);
+  int c_lo, c_hi;
+  split_range(a.t.n, a.n_split, blockIdx.y, c_lo, c_hi);
+  KeyWalk w{c_lo, 0, c_lo < c_hi ? visible_keys(s, last_pos, a.t.k_offset[c_lo]) : 0, wave};
+  while (walk_next<DP>(w, s, a.t, c_hi, last_pos)) {
+    const float* kb = (const float*)a.t.k[w.c] + b * a.t.ksb + hk * a.t.ksh + (int64_t)w.t * a.t.kss;
+    const float* vb = (const float*)a.t.v[w.c] + b * a.t.vsb + hk * a.t.vsh + (int64_t)w.t * a.t.vss;
+    const int limit = min(kT, w.nv - w.t);
+    const int nv_first = visible_keys(s, first_pos, a.t.k_offset[w.c]) - w.t;                  // wave-uniform
+    const int nv = nv_first < kT ? visible_keys(s, qpos, a.t.k_offset[w.c]) - w.t : kT;
+    const float* krow = kb + (int64_t)min(r, limit - 1) * a.t.kss;
+    Piece<N> f[2];
+    auto load = [&](int x) {
+      if (x < NR) load_rows<DP, FULL>(f[x & 1], krow, x, s.D, g);
+      else load_cols<DP, FULL>(f[x & 1], vb, a.t.vss, limit, x - NR, s.D, r, g);
+      __builtin_amdgcn_sched_barrier(0);
+    };
+    f32x16 p;
+#pragma unroll
+    for (int v = 0; v < 16; ++v) p[v] = 0.f;
+    load(0);
+#pragma unroll
+    for (int x = 0; x < NR; ++x) {
+      load(x + 1);
+      contract_d<DP>(p, f[x & 1], qs, x, r, g);
+    }
+    float mx = -INFINITY;
+#pragma unroll
+    for (int v = 0; v < 16; ++v) {
+      p[v] = c_row(v, g) < nv ? s.scale * p[v] : -INFINITY;
+      mx = fmaxf(mx, p[v]);
+    }
+    const float m_new = fmaxf(m, xhalf_max(mx));
+    const float m_use = m_new == -INFINITY ? 0.f : m_new;      // no key of this row yet: every p below is exp(-inf) = 0
+    float sum = 0.f;
+#pragma unroll
+    for (int v = 0; v < 16; ++v) {
+      p[v] = expf(p[v] - m_use);
+      sum += p[v];
+    }
+    const float alpha = expf(m - m_use);
+    l = l * alpha + sum;
+    m = m_new;
+    if (__any(alpha != 1.f)) {
+#pragma unroll
+      for (int db = 0; db < DB; ++db)
+#pragma unroll
+        for (int v = 0; v < 16; ++v) acc[db][v] *= alpha;
+    }
+    const bool dirty = nv_first < limit && tile_dirty(vb, a.t.vss, limit, s.D, lane);          // wave-uniform
+    if (dirty) any_dirty = 1;
+#pragma unroll
+    for (int x = NR; x < NR + NC; ++x) {
+      if (x + 1 < NR + NC) load(x + 1);
+      if (dirty) scrub(f[x & 1]);
+      contract_rows<DP>(acc, f[x & 1], p, x - NR);
+    }
+    w.skip = NW;
+  }
+
+  // fold of the wavefronts' states (m, l, O), halving their number each time
+  for (int n = NW / 2; n > 0; n /= 2) {
+    if (wave >= n && wave < 2 * n) {
+      put_acc(fold + (wave - n) * DB * 16 * 64, acc, lane);
+      fold_m[(wave - n) * 64 + lane] = m;
+      fold_l[(wave - n) * 64 + lane] = l;
+    }
+    __syncthreads();
+    if (wave < n) {
+      const float mo = fold_m[wave * 64 + lane], lo = fold_l[wave * 64 + lane];
+      const float mn = fmaxf(m, mo), mu = mn == -INFINITY ? 0.f : mn;
+      const float own = expf(m - mu), other = expf(mo - mu);
+      add_acc(fold + wave * DB * 16 * 64, acc, own, other, lane);
+      l = own * l + other * lo;
+      m = mn;
+    }
+    __syncthreads();
+  }
+  if (wave != 0 || row0 + r >= s.Sq) return;
+  l = xhalf_sum(l);
   const float inv = l > 0.f ? 1.f / l : 0.f;
-  const int64_t orow = (((int64_t)b * s.Sq + i) * s.Hq + h) * s.D;
+  float* o = a.o + (int64_t)blockIdx.y * a.split_o + (((int64_t)b * s.Sq + row0 + r) * s.Hq + h) * s.D;
+  float* ol = a.o_lowp ? (float*)a.o_lowp + (((int64_t)b * s.Sq + row0 + r) * s.Hq + h) * s.D : nullptr;   // storage dtype is fp32 here
 #pragma unroll
-  for (int x = 0; x < kDV; ++x) {
-    const int d = lane + 64 * x;
-    if (d < s.D) {
-      a.o[orow + d] = acc[x] * inv;
-      if (a.o_lowp) ((float*)a.o_lowp)[orow + d] = acc[x] * inv;   // storage dtype is fp32 here
+  for (int db = 0; db < DB; ++db)
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      const int d = 32 * db + 8 * j + 4 * g;
+      if (d >= s.D) continue;
+      const float4 x = make_float4(acc[db][4 * j] * inv, acc[db][4 * j + 1] * inv, acc[db][4 * j + 2] * inv, acc[db][4 * j + 3] * inv);
+      *reinterpret_cast<float4*>(o + d) = x;
+      if (ol) *reinterpret_cast<float4*>(ol + d) = x;
     }
-  }
-  if (lane == 0) a.lse[((int64_t)b * s.Hq + h) * s.Sq + i] = l > 0.f ? m + logf(l) : -INFINITY;
+  if (g == 0) a.lse[(int64_t)blockIdx.y * a.split_l + ((int64_t)b * s.Hq + h) * s.Sq + row0 + r] = l > 0.f ? m + logf(l) : -INFINITY;
+  if (any_dirty)
+    for (int c = c_lo; c < c_hi; ++c)
+      add_nonfinite(o, ol, (const float*)a.t.v[c] + b * a.t.vsb + hk * a.t.vsh, a.t.vss,
+                    visible_keys(s, first_pos, a.t.k_offset[c]) / kT * kT, visible_keys(s, qpos, a.t.k_offset[c]), s.D, g, false);
 }
 
 // ---------------------------------------------------------------- backward: dQ
-__global__ __launch_bounds__(kWaves * 64) void bwd_dq_f32_kernel(const BwdArgs a) {
-  __shared__ float qs[kWaves][kMaxD];
-  __shared__ float dos[kWaves][kMaxD];
+// Three contractions per tile pair (S and dP are recomputed); otherwise the forward's split.
+template <int DP, bool FULL>
+__global__ __launch_bounds__(waves<DP>() * 64) void bwd_dq_f32_kernel(const BwdArgs a) {
+  constexpr int NW = waves<DP>(), DB = DP / 32, N = 32, NR = row_pieces<DP, N>(), NC = col_pieces<DP, N>();
+  __shared__ __attribute__((aligned(16))) float qs[kT * lds_stride<DP>()];
+  __shared__ __attribute__((aligned(16))) float dos[kT * lds_stride<DP>()];
+  __shared__ float fold[NW / 2 * DB * 16 * 64];
+  __shared__ int any_dirty;
   const Shape& s = a.s;
-  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-  const int i = blockIdx.x * kWaves + w, h = blockIdx.y, b = blockIdx.z;
-  const int g = h / (s.Hq / s.Hkv);
-  const bool live = i < s.Sq;
-  if (live) {
-    const float* qrow = (const float*)a.q.ptr + b * a.q.sb + (int64_t)i * a.q.ss + h * a.q.sh;
-    const float* drow = (const float*)a.d_o.ptr + b * a.d_o.sb + (int64_t)i * a.d_o.ss + h * a.d_o.sh;
-    for (int d = lane; d < s.D; d += 64) {
-      qs[w][d] = qrow[d];
-      dos[w][d] = drow[d];
-    }
-  }
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int g = lane >> 5, r = lane & 31;
+  const int n_qt = (s.Sq + kT - 1) / kT;
+  int qt, hb;
+  qtile_block(blockIdx.x, gridDim.x, n_qt, s.causal, qt, hb);
+  const int h = hb % s.Hq, b = hb / s.Hq, hk = h / (s.Hq / s.Hkv);
+  const int row0 = qt * kT;
+  stage_tile<DP>(qs, (const float*)a.q.ptr + b * a.q.sb + h * a.q.sh, a.q.ss, row0, s.Sq, s.D, tid);
+  stage_tile<DP>(dos, (const float*)a.d_o.ptr + b * a.d_o.sb + h * a.d_o.sh, a.d_o.ss, row0, s.Sq, s.D, tid);
+  if (tid == 0) any_dirty = 0;
   __syncthreads();
-  if (!live) return;
 
+  const int i = min(row0 + r, s.Sq - 1);
   const int64_t stat = ((int64_t)b * s.Hq + h) * s.Sq + i;
   const float lse = a.lse[stat], dl = a.delta[stat];
-  if (lse == -INFINITY) return;                            // empty row: no gradient
-  const int64_t qpos = q_pos(s, i);
-  float acc[kDV] = {0.f, 0.f, 0.f, 0.f};
-  for (int c = 0; c < a.t.n; ++c) {
-    const float* kb = (const float*)a.t.k[c] + b * a.t.ksb + g * a.t.ksh;
-    const float* vb = (const float*)a.t.v[c] + b * a.t.vsb + g * a.t.vsh;
-    const int nvis = visible_keys(s, qpos, a.t.k_offset[c]);
-    for (int t0 = 0; t0 < nvis; t0 += 64) {
-      const int t = t0 + lane;
-      float ds = 0.f;
-      if (t < nvis) {
-        const float sc = s.scale * dot_row(qs[w], kb + (int64_t)t * a.t.kss, s.D);
-        const float p = expf(sc - lse);
-        const float dp = dot_row(dos[w], vb + (int64_t)t * a.t.vss, s.D);
-        ds = p * (dp - dl);
-      }
-      const int nt = min(64, nvis - t0);
-      for (int tt = 0; tt < nt; ++tt) {
-        const float dst = __shfl(ds, tt);
-        const float* krow = kb + (int64_t)(t0 + tt) * a.t.kss;
+  const bool empty = lse == -INFINITY;                       // empty row: no gradient
+  const int64_t qpos = q_pos(s, i), first_pos = q_pos(s, row0), last_pos = q_pos(s, min(row0 + kT, s.Sq) - 1);
+  f32x16 acc[DB];
+  zero_acc(acc);
+  KeyWalk w{0, 0, a.t.n > 0 ? visible_keys(s, last_pos, a.t.k_offset[0]) : 0, wave};
+  while (walk_next<DP>(w, s, a.t, a.t.n, last_pos)) {
+    const float* kb = (const float*)a.t.k[w.c] + b * a.t.ksb + hk * a.t.ksh + (int64_t)w.t * a.t.kss;
+    const float* vb = (const float*)a.t.v[w.c] + b * a.t.vsb + hk * a.t.vsh + (int64_t)w.t * a.t.vss;
+    const int limit = min(kT, w.nv - w.t);
+    const int nv_first = visible_keys(s, first_pos, a.t.k_offset[w.c]) - w.t;                  // wave-uniform
+    const int nv = empty ? 0 : nv_first < kT ? visible_keys(s, qpos, a.t.k_offset[w.c]) - w.t : kT;
+    const float* krow = kb + (int64_t)min(r, limit - 1) * a.t.kss;
+    const float* vrow = vb + (int64_t)min(r, limit - 1) * a.t.vss;
+    Piece<N> f[2];
+    auto load = [&](int x) {
+      if (x < 2 * NR) load_rows<DP, FULL>(f[x & 1], x < NR ? krow : vrow, x < NR ? x : x - NR, s.D, g);
+      else load_cols<DP, FULL>(f[x & 1], kb, a.t.kss, limit, x - 2 * NR, s.D, r, g);
+      __builtin_amdgcn_sched_barrier(0);
+    };
+    f32x16 p, ds;
 #pragma unroll
-        for (int x = 0; x < kDV; ++x) {
-          const int d = lane + 64 * x;
-          if (d < s.D) acc[x] = fmaf(dst, krow[d], acc[x]);
-        }
-      }
+    for (int v = 0; v < 16; ++v) p[v] = ds[v] = 0.f;
+    load(0);
+#pragma unroll
+    for (int x = 0; x < 2 * NR; ++x) {
+      load(x + 1);
+      if (x < NR) contract_d<DP>(p, f[x & 1], qs, x, r, g);
+      else contract_d<DP>(ds, f[x & 1], dos, x - NR, r, g);
     }
-  }
-  const int64_t orow = (((int64_t)b * s.Sq + i) * s.Hq + h) * s.D;
 #pragma unroll
-  for (int x = 0; x < kDV; ++x) {
-    const int d = lane + 64 * x;
-    if (d < s.D) a.dq[orow + d] += s.scale * acc[x];
+    for (int v = 0; v < 16; ++v) ds[v] = c_row(v, g) < nv ? expf(s.scale * p[v] - lse) * (ds[v] - dl) : 0.f;
+    const bool dirty = nv_first < limit && tile_dirty(kb, a.t.kss, limit, s.D, lane);          // wave-uniform
+    if (dirty) any_dirty = 1;
+#pragma unroll
+    for (int x = 2 * NR; x < 2 * NR + NC; ++x) {
+      if (x + 1 < 2 * NR + NC) load(x + 1);
+      if (dirty) scrub(f[x & 1]);
+      contract_rows<DP>(acc, f[x & 1], ds, x - 2 * NR);
+    }
+    w.skip = NW;
   }
+  for (int n = NW / 2; n > 0; n /= 2) {
+    if (wave >= n && wave < 2 * n) put_acc(fold + (wave - n) * DB * 16 * 64, acc, lane);
+    __syncthreads();
+    if (wave < n) add_acc(fold + wave * DB * 16 * 64, acc, 1.f, 1.f, lane);
+    __syncthreads();
+  }
+  if (wave != 0 || row0 + r >= s.Sq || empty) return;
+  float* dq = a.dq + (((int64_t)b * s.Sq + row0 + r) * s.Hq + h) * s.D;
+#pragma unroll
+  for (int db = 0; db < DB; ++db)
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      const int d = 32 * db + 8 * j + 4 * g;
+      if (d >= s.D) continue;
+      float4 x = *reinterpret_cast<float4*>(dq + d);
+      x.x += s.scale * acc[db][4 * j];
+      x.y += s.scale * acc[db][4 * j + 1];
+      x.z += s.scale * acc[db][4 * j + 2];
+      x.w += s.scale * acc[db][4 * j + 3];
+      *reinterpret_cast<float4*>(dq + d) = x;
+    }
+  if (any_dirty)
+    for (int c = 0; c < a.t.n; ++c)
+      add_nonfinite(dq, nullptr, (const float*)a.t.k[c] + b * a.t.ksb + hk * a.t.ksh, a.t.kss,
+                    visible_keys(s, first_pos, a.t.k_offset[c]) / kT * kT, visible_keys(s, qpos, a.t.k_offset[c]), s.D, g, true);
 }
 
 // ---------------------------------------------------------------- backward: dK, dV
-// grid: (ceil(Sk / kWaves), Hkv, B * n_chunks)
-__global__ __launch_bounds__(kWaves * 64) void bwd_dkv_f32_kernel(const BwdArgs a) {
-  __shared__ float ks[kWaves][kMaxD];
-  __shared__ float vs[kWaves][kMaxD];
+// grid: (ceil(Sk / 32), Hkv, B * n_chunks)
+template <int DP, bool FULL>
+__global__ __launch_bounds__(waves<DP>() * 64) void bwd_dkv_f32_kernel(const BwdArgs a) {
+  constexpr int NW = waves<DP>(), DB = DP / 32, N = DP < 128 ? 32 : 16, NR = row_pieces<DP, N>(), NC = col_pieces<DP, N>();
+  __shared__ __attribute__((aligned(16))) float ks[kT * lds_stride<DP>()];
+  __shared__ __attribute__((aligned(16))) float vs[kT * lds_stride<DP>()];
+  __shared__ float fold[NW / 2 * DB * 16 * 64];
+  __shared__ int any_dirty;
+  __shared__ __attribute__((aligned(16))) float stats[NW * 64];
   const Shape& s = a.s;
-  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-  const int t = blockIdx.x * kWaves + w, g = blockIdx.y;
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int g = lane >> 5, r = lane & 31;
+  const int key0 = blockIdx.x * kT, hk = blockIdx.y;
   const int c = blockIdx.z / s.B, b = blockIdx.z % s.B;
   const int G = s.Hq / s.Hkv;
-  const bool live = t < s.Sk;
-  if (live) {
-    const float* krow = (const float*)a.t.k[c] + b * a.t.ksb + (int64_t)t * a.t.kss + g * a.t.ksh;
-    const float* vrow = (const float*)a.t.v[c] + b * a.t.vsb + (int64_t)t * a.t.vss + g * a.t.vsh;
-    for (int d = lane; d < s.D; d += 64) {
-      ks[w][d] = krow[d];
-      vs[w][d] = vrow[d];
-    }
-  }
+  const int64_t k0 = a.t.k_offset[c];
+  // row i sees key t of the chunk iff i >= first_row(t)
+  auto first_row = [&](int t) { return s.causal ? q_row_of(s, k0 + t) : 0; };
+  const int wg_first = first_row(key0);
+  if (wg_first >= s.Sq) return;                              // uniform over the workgroup
+  const int wg_all = first_row(min(key0 + kT, s.Sk) - 1);    // from this row on every key is seen
+  stage_tile<DP>(ks, (const float*)a.t.k[c] + b * a.t.ksb + hk * a.t.ksh, a.t.kss, key0, s.Sk, s.D, tid);
+  stage_tile<DP>(vs, (const float*)a.t.v[c] + b * a.t.vsb + hk * a.t.vsh, a.t.vss, key0, s.Sk, s.D, tid);
+  if (tid == 0) any_dirty = 0;
   __syncthreads();
-  if (!live) return;
 
-  const int64_t kpos = a.t.k_offset[c] + t;
-  int i_first = 0;                                          // first query row that sees this key
-  if (s.causal) {
-    i_first = q_row_of(s, kpos);
-    if (i_first >= s.Sq) return;
-  }
-  float acc_k[kDV] = {0.f, 0.f, 0.f, 0.f}, acc_v[kDV] = {0.f, 0.f, 0.f, 0.f};
-  for (int hh = 0; hh < G; ++hh) {
-    const int h = g * G + hh;
-    const float* qb = (const float*)a.q.ptr + b * a.q.sb + h * a.q.sh;
-    const float* db = (const float*)a.d_o.ptr + b * a.d_o.sb + h * a.d_o.sh;
-    const int64_t stat = ((int64_t)b * s.Hq + h) * s.Sq;
-    for (int i0 = i_first; i0 < s.Sq; i0 += 64) {
-      const int i = i0 + lane;
-      float p = 0.f, ds = 0.f;
-      if (i < s.Sq) {
-        const float lse = a.lse[stat + i];
-        if (lse != -INFINITY) {
-          const float sc = s.scale * dot_row(ks[w], qb + (int64_t)i * a.q.ss, s.D);
-          p = expf(sc - lse);
-          const float dp = dot_row(vs[w], db + (int64_t)i * a.d_o.ss, s.D);
-          ds = p * (dp - a.delta[stat + i]);
-        }
-      }
-      const int ni = min(64, s.Sq - i0);
-      for (int ii = 0; ii < ni; ++ii) {
-        const float pi = __shfl(p, ii), dsi = __shfl(ds, ii);
-        const float* qrow = qb + (int64_t)(i0 + ii) * a.q.ss;
-        const float* drow = db + (int64_t)(i0 + ii) * a.d_o.ss;
+  const int key_first = first_row(min(key0 + r, s.Sk - 1));
+  const int t_lo = wg_first / kT, per_head = (s.Sq + kT - 1) / kT - t_lo;
+  f32x16 acc_k[DB], acc_v[DB];
+  zero_acc(acc_k);
+  zero_acc(acc_v);
+  for (int x = wave; x < G * per_head; x += NW) {
+    const int h = hk * G + x / per_head, i0 = (t_lo + x % per_head) * kT;
+    const float* qb = (const float*)a.q.ptr + b * a.q.sb + h * a.q.sh + (int64_t)i0 * a.q.ss;
+    const float* db_ = (const float*)a.d_o.ptr + b * a.d_o.sb + h * a.d_o.sh + (int64_t)i0 * a.d_o.ss;
+    const int64_t stat = ((int64_t)b * s.Hq + h) * s.Sq + i0;
+    const int limit = min(kT, s.Sq - i0), lo = key_first - i0;
+    const float* qrow = qb + (int64_t)min(r, limit - 1) * a.q.ss;
+    const float* drow = db_ + (int64_t)min(r, limit - 1) * a.d_o.ss;
+    Piece<N> f[2];
+    auto load = [&](int x) {
+      if (x < 2 * NR) load_rows<DP, FULL>(f[x & 1], x < NR ? qrow : drow, x < NR ? x : x - NR, s.D, g);
+      else if (x < 2 * NR + NC) load_cols<DP, FULL>(f[x & 1], db_, a.d_o.ss, limit, x - 2 * NR, s.D, r, g);
+      else load_cols<DP, FULL>(f[x & 1], qb, a.q.ss, limit, x - 2 * NR - NC, s.D, r, g);
+      __builtin_amdgcn_sched_barrier(0);
+    };
+    f32x16 p, ds;
 #pragma unroll
-        for (int x = 0; x < kDV; ++x) {
-          const int d = lane + 64 * x;
-          if (d < s.D) {
-            acc_k[x] = fmaf(dsi, qrow[d], acc_k[x]);
-            acc_v[x] = fmaf(pi, drow[d], acc_v[x]);
-          }
-        }
+    for (int v = 0; v < 16; ++v) p[v] = ds[v] = 0.f;
+    load(0);
+#pragma unroll
+    for (int x = 0; x < 2 * NR; ++x) {
+      load(x + 1);
+      if (x < NR) contract_d<DP>(p, f[x & 1], ks, x, r, g);
+      else contract_d<DP>(ds, f[x & 1], vs, x - NR, r, g);
+    }
+    // the tile's row statistics pass through LDS: lse in the first 32 floats of this wavefront's slot, Delta behind
+    stats[wave * 64 + lane] = (g ? a.delta : a.lse)[stat + min(r, limit - 1)];
+    __builtin_amdgcn_wave_barrier();
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      const float4 lse = *reinterpret_cast<const float4*>(stats + wave * 64 + 8 * j + 4 * g);
+      const float4 dl = *reinterpret_cast<const float4*>(stats + wave * 64 + 32 + 8 * j + 4 * g);
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const int v = 4 * j + e, row = c_row(v, g);
+        const float ls = e == 0 ? lse.x : e == 1 ? lse.y : e == 2 ? lse.z : lse.w, de = e == 0 ? dl.x : e == 1 ? dl.y : e == 2 ? dl.z : dl.w;
+        const bool live = row >= lo && row < limit && ls != -INFINITY;
+        p[v] = live ? expf(s.scale * p[v] - ls) : 0.f;
+        ds[v] = live ? p[v] * (ds[v] - de) : 0.f;
       }
+      __builtin_amdgcn_sched_barrier(0);
+    }
+    __builtin_amdgcn_wave_barrier();
+    const bool crossed = i0 < wg_all;                        // wave-uniform: some key does not see some row
+    const bool dirty = crossed && (tile_dirty(db_, a.d_o.ss, limit, s.D, lane) || tile_dirty(qb, a.q.ss, limit, s.D, lane));
+    if (dirty) any_dirty = 1;
+#pragma unroll
+    for (int x = 2 * NR; x < 2 * NR + 2 * NC; ++x) {
+      if (x + 1 < 2 * NR + 2 * NC) load(x + 1);
+      if (dirty) scrub(f[x & 1]);
+      if (x < 2 * NR + NC) contract_rows<DP>(acc_v, f[x & 1], p, x - 2 * NR);
+      else contract_rows<DP>(acc_k, f[x & 1], ds, x - 2 * NR - NC);
     }
   }
-  const int64_t orow = (((int64_t)b * s.Sk + t) * s.Hkv + g) * s.D;
-#pragma unroll
-  for (int x = 0; x < kDV; ++x) {
-    const int d = lane + 64 * x;
-    if (d < s.D) {
-      a.dk[c][orow + d] += s.scale * acc_k[x];
-      a.dv[c][orow + d] += acc_v[x];
-    }
+  for (int n = NW / 2; n > 0; n /= 2) {
+    float* slot = fold + (wave - (wave >= n ? n : 0)) * DB * 16 * 64;
+    if (wave >= n && wave < 2 * n) put_acc(slot, acc_k, lane);
+    __syncthreads();
+    if (wave < n) add_acc(slot, acc_k, 1.f, 1.f, lane);
+    __syncthreads();
+    if (wave >= n && wave < 2 * n) put_acc(slot, acc_v, lane);
+    __syncthreads();
+    if (wave < n) add_acc(slot, acc_v, 1.f, 1.f, lane);
+    __syncthreads();
   }
+  if (wave != 0 || key0 + r >= s.Sk || key_first >= s.Sq) return;
+  const int64_t orow = (((int64_t)b * s.Sk + key0 + r) * s.Hkv + hk) * s.D;
+#pragma unroll
+  for (int db = 0; db < DB; ++db)
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      const int d = 32 * db + 8 * j + 4 * g;
+      if (d >= s.D) continue;
+      float4* pk = reinterpret_cast<float4*>(a.dk[c] + orow + d);
+      float4* pv = reinterpret_cast<float4*>(a.dv[c] + orow + d);
+      float4 x = *pk, y = *pv;
+      x.x += s.scale * acc_k[db][4 * j];
+      x.y += s.scale * acc_k[db][4 * j + 1];
+      x.z += s.scale * acc_k[db][4 * j + 2];
+      x.w += s.scale * acc_k[db][4 * j + 3];
+      y.x += acc_v[db][4 * j];
+      y.y += acc_v[db][4 * j + 1];
+      y.z += acc_v[db][4 * j + 2];
+      y.w += acc_v[db][4 * j + 3];
+      *pk = x;
+      *pv = y;
+    }
+  if (any_dirty)
+    for (int h = hk * G; h < (hk + 1) * G; ++h) {
+      const int hi = min(s.Sq, (wg_all + kT - 1) / kT * kT);
+      add_nonfinite(a.dk[c] + orow, nullptr, (const float*)a.q.ptr + b * a.q.sb + h * a.q.sh, a.q.ss, key_first, hi, s.D, g, true);
+      add_nonfinite(a.dv[c] + orow, nullptr, (const float*)a.d_o.ptr + b * a.d_o.sb + h * a.d_o.sh, a.d_o.ss, key_first, hi, s.D, g, false);
+    }
+}
+
+// f(integral constant, full): the kernels are built for these D, and for smaller ones with zero-filled columns
+template <typename F>
+hipError_t with_padded_d(int D, F f) {
+  using std::integral_constant;
+  constexpr integral_constant<bool, true> full;
+  constexpr integral_constant<bool, false> padded;
+  if (D == 64) return f(integral_constant<int, 64>(), full);
+  if (D == 128) return f(integral_constant<int, 128>(), full);
+  if (D == 256) return f(integral_constant<int, 256>(), full);
+  if (D <= 32) return f(integral_constant<int, 32>(), padded);
+  if (D <= 64) return f(integral_constant<int, 64>(), padded);
+  if (D <= 96) return f(integral_constant<int, 96>(), padded);
+  if (D <= 128) return f(integral_constant<int, 128>(), padded);
+  if (D <= 192) return f(integral_constant<int, 192>(), padded);
+  if (D <= 256) return f(integral_constant<int, 256>(), padded);
+  return hipErrorInvalidValue;
 }
 
 }  // namespace
 
 hipError_t launch_fwd_f32(const FwdArgs& a, hipStream_t stream) {
-  const dim3 grid((a.s.Sq + kWaves - 1) / kWaves, a.s.Hq, a.s.B);
+  const int64_t total = (int64_t)((a.s.Sq + kT - 1) / kT) * a.s.Hq * a.s.B;
+  if (total <= 0) return hipSuccess;
+  if (total > 0x7fffffff) return hipErrorInvalidValue;
   ProfScope prof("fwd_f32", stream);
-  hipLaunchKernelGGL(fwd_f32_kernel, grid, dim3(kWaves * 64), 0, stream, a);
-  return hipGetLastError();
+  return with_padded_d(a.s.D, [&](auto dp, auto full) {
+    constexpr int DP = decltype(dp)::value;
+    constexpr bool FULL = decltype(full)::value;
+    const dim3 grid((unsigned)total, (unsigned)(a.n_split > 1 ? a.n_split : 1));
+    hipLaunchKernelGGL((fwd_f32_kernel<DP, FULL>), grid, dim3(waves<DP>() * 64), 0, stream, a);
+    return hipGetLastError();
+  });
 }
 
 hipError_t launch_bwd_f32(const BwdArgs& a, hipStream_t stream) {
-  const dim3 grid_q((a.s.Sq + kWaves - 1) / kWaves, a.s.Hq, a.s.B);
-  {
-    ProfScope prof("bwd_dq_f32", stream);
-    hipLaunchKernelGGL(bwd_dq_f32_kernel, grid_q, dim3(kWaves * 64), 0, stream, a);
-  }
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess || a.t.n == 0 || a.s.Sk == 0) return e;
-  const dim3 grid_k((a.s.Sk + kWaves - 1) / kWaves, a.s.Hkv, a.s.B * a.t.n);
-  ProfScope prof("bwd_dkv_f32", stream);
-  hipLaunchKernelGGL(bwd_dkv_f32_kernel, grid_k, dim3(kWaves * 64), 0, stream, a);
-  return hipGetLastError();
+  const int64_t total = (int64_t)((a.s.Sq + kT - 1) / kT) * a.s.Hq * a.s.B;
+  if (total <= 0 || a.t.n == 0 || a.s.Sk == 0) return hipSuccess;
+  if (total > 0x7fffffff) return hipErrorInvalidValue;
+  return with_padded_d(a.s.D, [&](auto dp, auto full) {
+    constexpr int DP = decltype(dp)::value;
+    constexpr bool FULL = decltype(full)::value;
+    {
+      ProfScope prof("bwd_dq_f32", stream);
+      hipLaunchKernelGGL((bwd_dq_f32_kernel<DP, FULL>), dim3((unsigned)total), dim3(waves<DP>() * 64), 0, stream, a);
+    }
+    hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+    ProfScope prof("bwd_dkv_f32", stream);
+    const dim3 grid((a.s.Sk + kT - 1) / kT, a.s.Hkv, a.s.B * a.t.n);
+    hipLaunchKernelGGL((bwd_dkv_f32_kernel<DP, FULL>), grid, dim3(waves<DP>() * 64), 0, stream, a);
+    return hipGetLastError();
+  });
 }
 
 }  // namespace st

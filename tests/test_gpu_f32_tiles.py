@@ -1,0 +1,112 @@
+"""fp32 kernels at the edges of their 32 x 32 tiles and of the padded head sizes, against the fp64 oracle: one row
+more or less than a tile, every padded size with and without zero-filled columns, shards in two runs, more tiles than
+wavefronts, forwards split over workgroups, and values that are no numbers behind a mask.  Tolerance: the fp32
+bounds of assert_close (1e-5 relative; sums of at most 1300 terms, each rounded at 6e-8)."""
+import numpy as np
+import pytest
+import torch
+
+import paper_2407_00611_amd as st
+import synth_inputs as si
+from oracle import attention as oa
+from util import assert_close, host, positions, upload
+
+pytestmark = pytest.mark.gpu
+
+#        D,  Hq, Hkv, Sq, Sk, n, q_offset, causal, (q_seg, q_offset2)
+CASES = [(8, 1, 1, 1, 31, 2, 40, True, (0, 0)),
+         (32, 2, 1, 33, 32, 2, 31, True, (0, 0)),
+         (40, 2, 2, 31, 33, 1, 0, False, (0, 0)),
+         (96, 3, 1, 64, 65, 3, 131, True, (0, 0)),
+         (104, 1, 1, 65, 96, 2, 0, False, (0, 0)),
+         (128, 4, 2, 70, 64, 4, 32, True, (35, 186)),
+         (136, 1, 1, 34, 66, 2, 98, True, (0, 0)),
+         (256, 2, 1, 40, 90, 2, 20, True, (9, 140)),
+         (64, 2, 1, 64, 640, 2, 1216, True, (0, 0))]
+
+
+def _share(w, mode=st.ST_RING_FUSED):
+    inp = si.make_inputs(w)
+    q, ks, vs, d_o = upload(inp)
+    koffs = [w.k_offset(j) for j in range(w.n_chunks)]
+    order = list(range(w.n_chunks))
+    o, lse, _ = st.st_ring_fwd(q, ks, vs, w.q_where, koffs, w.causal, w.scale, order, None, mode)
+    dq = torch.zeros_like(o)
+    dk = [torch.zeros_like(k) for k in ks]
+    dv = [torch.zeros_like(k) for k in ks]
+    st.st_ring_bwd(q, ks, vs, d_o, o, lse, w.q_where, koffs, w.causal, w.scale, order, dq, dk, dv, mode)
+    return inp, (o, lse, dq, dk, dv)
+
+
+@pytest.mark.parametrize("c", CASES, ids=[f"d{c[0]}_q{c[3]}_k{c[4]}" for c in CASES])
+def test_share_at_tile_edges(c):
+    D, Hq, Hkv, Sq, Sk, n, q0, causal, (seg, q2) = c
+    w = si.Workload("f32_tiles", 300 + D, "f32", 1, Hq, Hkv, D, Sq, Sk, n, q0, causal, True, q_seg=seg, q_offset2=q2)
+    print(f"[f32 tiles] {c}", flush=True)
+    inp, (o, lse, dq, dk, dv) = _share(w)
+    q_pos, k_pos = positions(w)
+    o_r, lse_r = oa.attention_forward(inp.q, inp.k, inp.v, q_pos, k_pos, causal, w.scale)
+    dq_r, dk_r, dv_r = oa.attention_backward(inp.q, inp.k, inp.v, inp.d_o, q_pos, k_pos, causal, w.scale)
+    assert_close(host(o), o_r, "f32", "o")
+    assert_close(host(lse), lse_r, "f32", "lse")
+    assert_close(host(dq), dq_r, "f32", "dq")
+    for j in range(n):
+        assert_close(host(dk[j]), dk_r[j], "f32", f"dk[{j}]")
+        assert_close(host(dv[j]), dv_r[j], "f32", f"dv[{j}]")
+
+
+def test_split_forward_and_a_workspace_too_small_for_it():
+    """A few query tiles against long chunks: the fused forward splits the table over workgroups when the workspace
+    has room for their states, and walks it in one launch when there is none."""
+    w = si.Workload("f32_split", 310, "f32", 1, 2, 2, 128, 64, 512, 4, 3 * 512, True, True)
+    inp = si.make_inputs(w)
+    q, ks, vs, _ = upload(inp)
+    args = (q, ks, vs, w.q_where, [w.k_offset(j) for j in range(4)], True, w.scale)
+    one = (q.numel() + w.Hq * w.Sq) * 4
+    assert st.st_ring_workspace_bytes(*args, st.ST_RING_FUSED, False) >= 2 * one
+    q_pos, k_pos = positions(w)
+    o_r, lse_r = oa.attention_forward(inp.q, inp.k, inp.v, q_pos, k_pos, True, w.scale)
+    for ws in (None, torch.empty(256, dtype=torch.uint8, device="cuda")):
+        o, lse, low = st.st_ring_fwd(*args, list(range(4)), workspace=ws)
+        assert_close(host(o), o_r, "f32", "o")
+        assert_close(host(lse), lse_r, "f32", "lse")
+        assert torch.equal(o, low)
+
+
+def test_values_that_are_no_numbers_stay_behind_the_mask():
+    """Rows that a causal mask hides from a query (or queries it hides from a key) may hold anything: the results of
+    every row that does not see them are the ones without them, bit for bit; a row that sees one is no number."""
+    w = si.Workload("f32_nan", 311, "f32", 1, 2, 1, 72, 70, 70, 1, 0, True, True)
+    inp = si.make_inputs(w)
+    q, ks, vs, d_o = upload(inp)
+    bad = 45                                            # a key, and the query row at the same position
+    q2, k2, v2, d2 = q.clone(), ks[0].clone(), vs[0].clone(), d_o.clone()
+    v2[:, bad, :, 3] = float("inf")
+    v2[:, bad, :, 70] = float("nan")
+
+    def run(q, k, v, d_o):
+        o, lse, _ = st.st_ring_fwd(q, [k], [v], 0, [0], True, w.scale, [0])
+        dq = torch.zeros_like(o)
+        dk, dv = torch.zeros_like(k), torch.zeros_like(v)
+        st.st_ring_bwd(q, [k], [v], d_o, clean_o, clean_lse, 0, [0], True, w.scale, [0], dq, [dk], [dv])
+        return o, lse, dq, dk, dv
+
+    clean_o, clean_lse, _ = st.st_ring_fwd(q, ks, vs, 0, [0], True, w.scale, [0])
+    ref = run(q, ks[0], vs[0], d_o)
+    o, lse, dq, _, _ = run(q, ks[0], v2, d_o)
+    assert torch.equal(o[:, :bad], ref[0][:, :bad]) and torch.equal(lse, ref[1]) and torch.equal(dq[:, :bad], ref[2][:, :bad])
+    assert torch.isposinf(o[:, bad:, :, 3]).all() and torch.isnan(o[:, bad:, :, 70]).all()
+    keep = [d for d in range(72) if d not in (3, 70)]
+    assert torch.equal(o[..., keep], ref[0][..., keep])
+    k2[:, bad, :, 5] = float("nan")
+    _, _, dq, _, _ = run(q, k2, vs[0], d_o)
+    assert torch.equal(dq[:, :bad], ref[2][:, :bad]) and torch.isnan(dq[:, bad:]).all()
+    # a query row reaches the keys up to its own position only
+    q2[:, bad, :, 0] = float("nan")
+    _, _, _, dk, dv = run(q2, ks[0], vs[0], d_o)
+    assert torch.equal(dk[:, bad + 1:], ref[3][:, bad + 1:]) and torch.equal(dv[:, bad + 1:], ref[4][:, bad + 1:])
+    assert torch.isnan(dk[:, :bad + 1]).all() and torch.isnan(dv[:, :bad + 1]).all()
+    d2[:, bad, :, 9] = float("inf")
+    _, _, _, dk, dv = run(q, ks[0], vs[0], d2)
+    assert torch.equal(dk[:, bad + 1:], ref[3][:, bad + 1:]) and torch.equal(dv[:, bad + 1:], ref[4][:, bad + 1:])
+    assert torch.isposinf(dv[:, :bad + 1, :, 9]).all()
