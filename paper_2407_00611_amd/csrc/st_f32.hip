@@ -20,7 +20,7 @@
 // One wavefront per row with scalar fused multiply-adds, as these kernels were before, read K with every lane on a
 // row of its own and one load per four multiply-adds: 8 heads x 512 rows x 8 chunks of 512 keys at D = 128 took 2460 us
 // forward, 2640 us dQ, 3590 us dK / dV (3.2 TFLOP/s).  Now 108, 276 and 203 us (dQ has 128 workgroups for 256 compute
-units there; dK / dV executes 16 GFLOP, 105 us at the 154 TFLOP/s of a large fp32 matrix product on this card).
+// units there; dK / dV executes 16 GFLOP, 105 us at the 154 TFLOP/s of a large fp32 matrix product on this card).
 #include <type_traits>
 
 #include "st_internal.h"
