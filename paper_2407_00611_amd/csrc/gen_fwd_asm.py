@@ -6,10 +6,17 @@
                                                      O^T row blocks per key block, tiles of 128-byte rows)
 
 Body of ONE `asm volatile` statement in st_fwd_fast.hip.  A workgroup (4 wavefronts) owns 256 queries of
-one head, 64 per wavefront as two 32-query blocks, and walks the 64-key tiles that every one of its rows
-sees in full; it writes the partial (O, lse) of those tiles.  Everything else (masked tiles, ragged tails,
-ragged query tiles) is done afterwards by the general kernel, which folds its own partial state into this
-one with the log-sum-exp merge.
+one head, 64 per wavefront as two 32-query blocks, and walks 64-key tiles: first the ones that every one of
+its rows sees in full, then the ones that a mask edge crosses (the causal diagonal, the ragged end of a chunk).
+It writes O = acc / l, lse and, where asked for, O rounded to bf16; query rows beyond the shard are not stored.
+
+Masked tiles are the last S_NM of the walk, so the loop only compares its count-down with that number, one
+scalar test per 32-key block; the mask itself is an out-of-line routine that overwrites the invisible exponents
+with -inf before their maximum is taken.  A tile hidden from none of its columns costs nothing more than before.
+The ragged end of a chunk is read as the chunk's last 64 rows, with the rows of the tile before it masked, so no
+load leaves the chunk.  Where no tile is visible to all rows, a row may meet its first visible key late: its
+reference starts at zero and is set to its first finite block maximum by the mask routine (its accumulators are
+still zero), since a lazy reference never moves down.
 
 MFMA C layout "lane = query column": the exponent reference r (log2 units) and the row sum are one
 register per lane and query block.  The Q fragments are multiplied by scale * log2(e) once (and rounded
@@ -59,22 +66,30 @@ XL, XH = 152, 160
 TRLO_L, TRHI_L, TRLO_H, TRHI_H = 168, 172, 176, 180
 KOFF, VOFF = 184, 188
 OOFF, LSEOFF = 192, 193
-RT = 200                                             # 200..223: temporaries of the rescale routine
+RT = 200                                             # 200..223: temporaries of the out-of-line routines
+def QREL(qb): return 198 + qb                        # the row's position relative to the tile's first row, less 4 * (lane / 32)
+def SEEN(qb): return 104 if qb == 0 else 107         # 0: the row has met no visible key yet
 # inputs (pinned by the C++ side): v[224:239]
-I_QROW0, I_QROW1, I_XBASE, I_GF16, I_TRBASE, I_LF16, I_KOFF0, I_VOFF0, I_OOFF, I_LSEOFF = (
-    224, 226, 228, 229, 230, 231, 232, 233, 234, 235)
+I_QROW0, I_QROW1, I_XBASE, I_GF16, I_TRBASE, I_LF16, I_KOFF0, I_VOFF0, I_OOFF, I_LSEOFF, I_QREL, I_LIVE = (
+    224, 226, 228, 229, 230, 231, 232, 233, 234, 235, 236, 238)       # I_LIVE: bit qb = the lane's row of block qb exists
 S_GAP = 46
 (S_LDS, S_WAVE, S_NT, S_KRS16, S_VRS16, S_SCALE, S_OPTR, S_OQB, S_TBL, S_KTILE, S_VTILE, S_LSEPTR) = (
     32, 33, 34, 35, 36, 37, 38, 40, 41, 42, 43, 44)
 # scalar temporaries
 S_CEXP, T_M0, T_REM, D_KPTR, D_VPTR, D_LEFT, D_IDX, D_TBL, T_X = 47, 64, 65, 66, 68, 70, 71, 72, 73
 T_RET, T_RARE = 76, 78                               # return address; address of rescale routine b at 78 + 2 b
+# set by the prologue, from the parameter block behind the chunk table in LDS
+S_LIVE = 48                                          # 48:49, 50:51: lanes whose row of block qb exists
+S_NM, S_NM1, S_MTBL, S_FRESH, S_OLOW = 52, 53, 54, 55, 56   # masked tiles, + 1; their first table entry; 1: no tile is visible
+                                                     # to all rows; 56:57: bf16 copy of O, or null
+M_LEFT, M_REL, M_LO, T_MRET, T_CMP, T_MASK = 58, 59, 60, 62, 82, 90   # masked walk; four compare results; mask routine kb at 90 + 2 kb
 
 # ---- LDS map
 def KT(s): return 2 * TILE * s
 def VT(s): return 2 * TILE * s + TILE
-TBL = 2 * TILE * NS
-LDS_BYTES = TBL + 2048
+TBL = 2 * TILE * NS                                  # at most three entries per chunk: whole tiles, masked tiles, ragged end
+PARAMS = 3 * 64 * 32                                 # offset of the parameter block from the table
+LDS_BYTES = TBL + PARAMS + 64
 
 LAT = int(os.environ.get("ST_GEN_FWD_LAT", 3))
 BUDGET = int(os.environ.get("ST_GEN_FWD_BUDGET", 6 if D == 128 else 13))
@@ -83,6 +98,7 @@ BRANCH_SLOT = 2 * DB + 1                             # the reference test sits b
 
 NEXT_STUBS = []                                      # (label, return label) of every switch to the next chunk
 STUBS = []                                           # (call label, return label, P buffer) of every reference test
+MASK_STUBS = []                                      # (call label, return label, score buffer) of every mask test
 
 
 class Pipe:
@@ -242,6 +258,8 @@ def gen_iter(p, cur, nxt, nxt2, par, seq, do_a=True, do_valu=True, head=None, pr
             for ln in side[k]:
                 e.raw(ln)
             units += 2
+        if do_valu and k == 3:
+            mask_test(e, S_NM1 if par else S_NM, 1 - par)
         if do_valu:
             # S(i+1) was written by the last group of the block before: first reader three MFMA issues later
             while 3 <= k <= BRANCH_SLOT and mi[0] < len(valu_m) and (units < BUDGET or k == BRANCH_SLOT):
@@ -265,6 +283,97 @@ def gen_iter(p, cur, nxt, nxt2, par, seq, do_a=True, do_valu=True, head=None, pr
         e.valu(valu_e[vi[0]][0], valu_e[vi[0]][1])
         vi[0] += 1
     return leftover if do_a else 0
+
+
+def mask_test(e, limit, buf):
+    """Call the mask routine of score buffer `buf` if its block lies in one of the last S_NM tiles (the tile in hand is
+    the T_REM-th from the end; limit = S_NM for a block of that tile, S_NM + 1 for one of the next)."""
+    l_call, l_back = e.label("mcall"), e.label("mback")
+    e.raw(f"s_cmp_le_u32 {sr(T_REM)}, {sr(limit)}")
+    e.raw(f"s_cbranch_scc1 {l_call}")
+    e.raw(l_back + ":")
+    MASK_STUBS.append((l_call, l_back, buf))
+
+
+def gen_mask_routine(e, kb):
+    """Score buffer kb holds the exponents of key block kb of a masked tile: -inf wherever the key is not the row's.
+    Key t of the tile (0 .. 63) is visible to a row iff t >= M_LO and M_REL + t <= the row's position, both relative to
+    the position of the workgroup's first row.  Block 0 moves on to the next tile of the masked walk first."""
+    n4, ninf, lim, lo = RT, RT + 1, RT + 2, RT + 4
+    if kb == 0:
+        l_step, l_go = e.label("mstep"), e.label("mgo")
+        e.raw(f"s_cmp_lg_u32 {sr(M_LEFT)}, 0")
+        e.raw(f"s_cbranch_scc1 {l_step}")
+        e.raw(f"v_mov_b32 {vr(RT)}, {sr(S_MTBL)}")
+        e.raw(f"ds_read_b128 {vr(RT + 4, 4)}, {vr(RT)} offset:16")
+        e.raw("s_waitcnt lgkmcnt(0)")
+        for i, dst in enumerate((M_LEFT, M_REL, M_LO)):
+            e.raw(f"v_readfirstlane_b32 {sr(dst)}, {vr(RT + 4 + i)}")
+        e.raw(f"s_add_u32 {sr(S_MTBL)}, {sr(S_MTBL)}, 32")
+        e.raw(f"s_branch {l_go}")
+        e.raw(l_step + ":")
+        e.raw(f"s_add_i32 {sr(M_REL)}, {sr(M_REL)}, 64")
+        e.raw(l_go + ":")
+        e.raw(f"s_sub_u32 {sr(M_LEFT)}, {sr(M_LEFT)}, 1")
+    e.raw(f"v_mbcnt_lo_u32_b32 {vr(n4)}, -1, 0")
+    e.raw(f"v_mbcnt_hi_u32_b32 {vr(n4)}, -1, {vr(n4)}")
+    e.raw(f"v_lshrrev_b32 {vr(n4)}, 5, {vr(n4)}")
+    e.raw(f"v_lshlrev_b32 {vr(n4)}, 2, {vr(n4)}")
+    e.raw(f"v_mov_b32 {vr(ninf)}, 0xff800000")
+    for qb in range(QB):
+        e.raw(f"v_subrev_u32 {vr(lim + qb)}, {sr(M_REL)}, {vr(QREL(qb))}")
+        if kb:
+            e.raw(f"v_subrev_u32 {vr(lim + qb)}, 32, {vr(lim + qb)}")
+
+    def each(cmp, bound):
+        for qb in range(QB):
+            for v0 in range(0, 16, 4):              # four compares ahead of the four selects that read them
+                for i in range(4):
+                    e.raw(f"{cmp} {sr(T_CMP + 2 * i, 2)}, {vr(bound(qb))}, {8 * (v0 // 4) + i}")
+                for i in range(4):
+                    x = vr(SBUF(kb, qb) + v0 + i)
+                    e.raw(f"v_cndmask_b32_e64 {x}, {vr(ninf)}, {x}, {sr(T_CMP + 2 * i, 2)}")
+    each("v_cmp_ge_i32_e64", lambda qb: lim + qb)
+    l_nolo = e.label("mnolo")
+    e.raw(f"s_cmp_eq_u32 {sr(M_LO)}, 0")
+    e.raw(f"s_cbranch_scc1 {l_nolo}")
+    e.raw(f"v_sub_u32 {vr(lo)}, {sr(M_LO)}, {vr(n4)}")
+    if kb:
+        e.raw(f"v_subrev_u32 {vr(lo)}, 32, {vr(lo)}")
+    each("v_cmp_le_i32_e64", lambda qb: lo)
+    e.raw(l_nolo + ":")
+    l_ret = e.label("mret")
+    e.raw(f"s_cmp_eq_u32 {sr(S_FRESH)}, 0")
+    e.raw(f"s_cbranch_scc1 {l_ret}")
+    mx, t, k = RT + 8, RT + 10, RT + 12
+    for qb in range(QB):
+        x = SBUF(kb, qb)
+        e.raw(f"v_max3_f32 {vr(mx + qb)}, {vr(x)}, {vr(x + 1)}, {vr(x + 2)}")
+        for v in range(3, 15, 2):
+            e.raw(f"v_max3_f32 {vr(mx + qb)}, {vr(mx + qb)}, {vr(x + v)}, {vr(x + v + 1)}")
+        e.raw(f"v_max_f32 {vr(mx + qb)}, {vr(mx + qb)}, {vr(x + 15)}")
+        e.raw(f"v_mov_b32 {vr(t + qb)}, {vr(mx + qb)}")
+    e.raw("s_nop 1")
+    for qb in range(QB):
+        e.raw(f"v_permlane32_swap_b32 {vr(t + qb)}, {vr(mx + qb)}")
+    e.raw("s_nop 1")
+    for qb in range(QB):
+        e.raw(f"v_max_f32 {vr(mx + qb)}, {vr(mx + qb)}, {vr(t + qb)}")
+        e.raw(f"v_ceil_f32 {vr(k + qb)}, {vr(mx + qb)}")
+        e.raw(f"v_cmp_neq_f32_e64 {sr(T_CMP, 2)}, {vr(ninf)}, {vr(mx + qb)}")
+        e.raw(f"v_cmp_eq_u32_e64 {sr(T_CMP + 2, 2)}, 0, {vr(SEEN(qb))}")
+        e.raw("s_nop 1")
+        e.raw(f"s_and_b64 {sr(T_CMP, 2)}, {sr(T_CMP, 2)}, {sr(T_CMP + 2, 2)}")
+        e.raw("s_nop 1")
+        e.raw(f"v_cndmask_b32_e64 {vr(k + qb)}, 0, {vr(k + qb)}, {sr(T_CMP, 2)}")
+        e.raw(f"v_cndmask_b32_e64 {vr(SEEN(qb))}, {vr(SEEN(qb))}, 1, {sr(T_CMP, 2)}")
+        for v in range(16):
+            e.raw(f"v_sub_f32 {vr(NL(qb) + v)}, {vr(NL(qb) + v)}, {vr(k + qb)}")
+        for v in range(16):
+            e.raw(f"v_sub_f32 {vr(SBUF(kb, qb) + v)}, {vr(SBUF(kb, qb) + v)}, {vr(k + qb)}")
+    e.raw(l_ret + ":")
+    e.raw("s_nop 1")
+    e.raw(f"s_setpc_b64 {sr(T_MRET, 2)}")
 
 
 def gen_rescale_routine(e, pbuf):
@@ -369,18 +478,32 @@ def generate():
     e = Emitter()
     p = Pipe(e)
     l_rare = [e.label("rescale0"), e.label("rescale1")]
+    l_mask = [e.label("mask0"), e.label("mask1")]
     e.comment("---- prologue")
     e.raw(f"s_lshl_b32 {sr(T_M0)}, {sr(S_WAVE)}, 10")
     e.raw(f"s_add_u32 {sr(T_M0)}, {sr(T_M0)}, {sr(S_LDS)}")
     e.raw(f"s_mov_b32 {sr(T_REM)}, {sr(S_NT)}")
     e.raw(f"s_mov_b32 {sr(D_IDX)}, 0")
     e.raw(f"s_mov_b32 {sr(D_TBL)}, {sr(S_TBL)}")
-    for b in range(2):          # addresses of the two rescale routines
+    for dst, target in [(T_RARE + 2 * b, l_rare[b]) for b in range(2)] + [(T_MASK + 2 * b, l_mask[b]) for b in range(2)]:
         l_here = e.label("here")
-        e.raw(f"s_getpc_b64 {sr(T_RARE + 2 * b, 2)}")
+        e.raw(f"s_getpc_b64 {sr(dst, 2)}")
         e.raw(l_here + ":")
-        e.raw(f"s_add_u32 {sr(T_RARE + 2 * b)}, {sr(T_RARE + 2 * b)}, {l_rare[b]}-{l_here}")
-        e.raw(f"s_addc_u32 {sr(T_RARE + 2 * b + 1)}, {sr(T_RARE + 2 * b + 1)}, 0")
+        e.raw(f"s_add_u32 {sr(dst)}, {sr(dst)}, {target}-{l_here}")
+        e.raw(f"s_addc_u32 {sr(dst + 1)}, {sr(dst + 1)}, 0")
+    e.raw(f"v_mov_b32 {vr(TMP)}, {sr(S_TBL)}")
+    e.raw(f"ds_read_b128 {vr(TMP + 4, 4)}, {vr(TMP)} offset:{PARAMS}")
+    e.raw(f"ds_read_b32 {vr(TMP + 8)}, {vr(TMP)} offset:{PARAMS + 16}")
+    e.raw("s_waitcnt lgkmcnt(0)")
+    for i, dst in enumerate((S_NM, S_MTBL, S_FRESH, S_OLOW, S_OLOW + 1)):
+        e.raw(f"v_readfirstlane_b32 {sr(dst)}, {vr(TMP + 4 + i)}")
+    e.raw(f"s_add_u32 {sr(S_NM1)}, {sr(S_NM)}, 1")
+    e.raw(f"s_mov_b32 {sr(M_LEFT)}, 0")
+    for qb in range(QB):
+        e.raw(f"v_mov_b32 {vr(QREL(qb))}, {vr(I_QREL + qb)}")
+        e.raw(f"v_mov_b32 {vr(SEEN(qb))}, 1")
+        e.raw(f"v_and_b32 {vr(TMP)}, {1 << qb}, {vr(I_LIVE)}")
+        e.raw(f"v_cmp_ne_u32_e64 {sr(S_LIVE + 2 * qb, 2)}, 0, {vr(TMP)}")
     e.raw(f"v_mov_b32 {vr(TMP)}, 0x3fb8aa3b")
     e.raw(f"v_mul_f32 {vr(TMP)}, {sr(S_SCALE)}, {vr(TMP)}")
     e.raw("s_nop 0")
@@ -449,10 +572,16 @@ def generate():
     fill_s((0, 0), 0, -2, lambda qb: "0")
     e.raw("s_nop 7")
     e.raw("s_nop 7")
+    mask_test(e, S_NM, 0)
     for ln in valu_max(0, full=True):           # with r = 0: d = row maximum of S c
         e.raw(ln)
     for qb in range(QB):                        # reference = ceil(max), whole log2 units; shift block (0,0) by hand
+        e.raw(f"v_mov_b32 {vr(TMP)}, 0xff800000")
+        e.raw(f"v_cmp_neq_f32 vcc, {vr(TMP)}, {vr(MX(qb))}")
         e.raw(f"v_ceil_f32 {vr(MX(qb))}, {vr(MX(qb))}")
+        e.raw("s_nop 1")
+        e.raw(f"v_cndmask_b32 {vr(MX(qb))}, 0, {vr(MX(qb))}, vcc")      # a row that sees no key of this block: zero
+        e.raw(f"v_cndmask_b32_e64 {vr(SEEN(qb))}, 0, 1, vcc")
         for v in range(16):
             e.raw(f"v_sub_f32 {vr(NL(qb) + v)}, 0, {vr(MX(qb))}")
         for v in range(16):
@@ -505,9 +634,15 @@ def generate():
         e.raw(l_call + ":")
         e.raw(f"s_swappc_b64 {sr(T_RET, 2)}, {sr(T_RARE + 2 * par, 2)}")
         e.raw(f"s_branch {l_back}")
+    for l_call, l_back, buf in MASK_STUBS:
+        e.raw(l_call + ":")
+        e.raw(f"s_swappc_b64 {sr(T_MRET, 2)}, {sr(T_MASK + 2 * buf, 2)}")
+        e.raw(f"s_branch {l_back}")
     for b in range(2):
         e.raw(l_rare[b] + ":")
         gen_rescale_routine(e, b)
+        e.raw(l_mask[b] + ":")
+        gen_mask_routine(e, b)
     e.raw(l_done + ":")
     e.raw("s_waitcnt vmcnt(0) lgkmcnt(0)")
 
@@ -526,12 +661,15 @@ def generate():
         e.raw(f"v_add_f32 {vr(l)}, {vr(l)}, {vr(t)}")
         e.raw(f"v_rcp_f32 {vr(TMP + 2)}, {vr(l)}")
         e.raw(f"v_log_f32 {vr(TMP + 3)}, {vr(l)}")
+        e.raw(f"v_cmp_lt_f32 vcc, 0, {vr(l)}")                     # a row without a visible key: O = 0, lse = -inf
         e.raw("s_nop 1")
+        e.raw(f"v_cndmask_b32 {vr(TMP + 2)}, 0, {vr(TMP + 2)}, vcc")
         e.raw(f"v_sub_f32 {vr(TMP + 3)}, {vr(TMP + 3)}, {vr(NL(qb))}")
         e.raw(f"v_mul_f32 {vr(TMP + 3)}, 0x3f317218, {vr(TMP + 3)}")
         if qb == 1:
             e.raw(f"v_add_u32 {vr(OOFF)}, {sr(S_OQB)}, {vr(OOFF)}")
             e.raw(f"v_add_u32 {vr(LSEOFF)}, 128, {vr(LSEOFF)}")
+        e.raw(f"s_mov_b64 exec, {sr(S_LIVE + 2 * qb, 2)}")
         for db in range(DB):
             for j in range(4):
                 t0 = 4 * (4 * db + j)
@@ -541,10 +679,21 @@ def generate():
                 for i in range(4):
                     e.raw(f"v_mul_f32 {vr(t0 + i)}, {vr(TMP + 2)}, {vr(t0 + i)}")
                 e.raw(f"global_store_dwordx4 {vr(OOFF)}, {vr(t0, 4)}, {sr(S_OPTR, 2)} offset:{128 * db + 32 * j}")
+        l_nolow = e.label("nolow")
+        e.raw(f"s_cmp_eq_u64 {sr(S_OLOW, 2)}, 0")
+        e.raw(f"s_cbranch_scc1 {l_nolow}")
+        e.raw(f"v_lshrrev_b32 {vr(TMP + 4)}, 1, {vr(OOFF)}")
+        for db in range(DB):
+            for j in range(4):
+                t0, d = 4 * (4 * db + j), 64 + 2 * (4 * db + j)
+                e.raw(f"v_cvt_pk_bf16_f32 {vr(d)}, {vr(t0)}, {vr(t0 + 1)}")
+                e.raw(f"v_cvt_pk_bf16_f32 {vr(d + 1)}, {vr(t0 + 2)}, {vr(t0 + 3)}")
+                e.raw(f"global_store_dwordx2 {vr(TMP + 4)}, {vr(d, 2)}, {sr(S_OLOW, 2)} offset:{64 * db + 16 * j}")
+        e.raw(l_nolow + ":")
         # lse: one lane per row (the lower half of the wavefront)
-        e.raw(f"s_mov_b64 exec, 0xffffffff")
+        e.raw("s_mov_b32 exec_hi, 0")
         e.raw(f"global_store_dword {vr(LSEOFF)}, {vr(TMP + 3)}, {sr(S_LSEPTR, 2)}")
-        e.raw(f"s_mov_b64 exec, -1")
+        e.raw("s_mov_b64 exec, -1")
         e.raw("s_waitcnt vmcnt(0)")
     return e, leftover
 
@@ -554,7 +703,7 @@ def main():
     if leftover:
         sys.stderr.write(f"gen_fwd_asm: {leftover} VALU instructions did not fit under the MFMAs\n")
     clob = [f"v{i}" for i in range(256) if not 224 <= i < 240] + [f"a{i}" for i in range(256)]
-    clob += [f"s{S_CEXP}"] + [f"s{i}" for i in range(64, 82)]
+    clob += [f"s{i}" for i in range(S_CEXP, 94)]
     write_inc(sys.stdout, "gen_fwd_asm.py" + (" 64" if D == 64 else ""), "ST_FWD_FAST" + ("64" if D == 64 else ""), e,
               LDS_BYTES, clob)
 

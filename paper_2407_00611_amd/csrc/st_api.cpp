@@ -497,38 +497,61 @@ st_status st_schedule_report(int32_t P, int32_t C, int64_t B, int64_t N, int64_t
   return ST_OK;
 }
 
-// A fused bf16 forward whose query tiles alone would leave most of the chip idle (fewer than 128 workgroups
-// of 256 queries on 256 compute units) is split over the visited chunks: every query tile gets several
-// workgroups, each with a contiguous share of the chunks and a partial state of its own, and one combine
-// pass folds the states (the chunks of a ring step are independent until the fold, Algorithm 1).
-//
-// fp32: a workgroup owns 32 query rows and its eight wavefronts share the keys.  Splitting pays once it saves more
-// than the combine launch costs (about 10 us): a 32-key tile is 64 D cycles of a SIMD's matrix unit, two wavefronts to a SIMD.
-int fwd_splits_f32(const st_ring_desc* d, int n_visible) {
-  const int64_t wgs = (int64_t)d->B * d->Hq * ((d->Sq + 31) / 32);
-  if (wgs < 1 || wgs >= 192 || n_visible < 2 || n_visible > st::kMaxTable) return 1;
-  int64_t n = 256 / wgs;
-  if (n > n_visible) n = n_visible;
-  if (n > 16) n = 16;
-  const double us = (double)n_visible * ((d->Sk + 31) / 32) / 8 * 2 * 64 * d->D / 2400;    // one workgroup, unsplit
-  return n > 1 && us * (1 - 1.0 / n) > 10 ? (int)n : 1;
-}
+// A fused forward whose query tiles alone would leave part of the chip idle (a workgroup per 256 rows and head in bf16, per
+// 32 rows in fp32, on 256 compute units) is split over the keys: every query tile gets several workgroups, each with a share
+// of the walk and a partial state of its own, and one combine pass folds the states (the tiles of a ring are independent
+// until the fold, Algorithm 1).  The split is the one for which rounds of workgroups x time of one + combine is least; the
+// constants are measured: a 256 x 64 bf16 tile 1.6 us at head size 128 and 0.95 us at 64, 8 us of prologue and epilogue,
+// 6 us for the launch of the combine pass, which moves 4 TB/s on states this small.  fp32: a 32-key tile is 64 D cycles of
+// a SIMD's matrix unit, and eight wavefronts on four SIMDs share the keys.
+constexpr int kMaxSplits = 16;
 int fwd_splits(const st_ring_desc* d, int n_visible) {
-  if (d->dtype == ST_F32) return fwd_splits_f32(d, n_visible);
+  const bool bf16 = d->dtype == ST_BF16;
+  if (n_visible < 1 || n_visible > st::kMaxTable || d->B < 1 || d->Sq < 1 || d->Hq < 1) return 1;
+  if (bf16 && ((d->D != 128 && d->D != 64) || d->Sk < st::kQTileFastKeys)) return 1;
+  const int rows = bf16 ? st::kQTileFastRows : 32, keys = bf16 ? st::kQTileFastKeys : 32;
+  const int64_t wgs = (int64_t)d->B * d->Hq * ((d->Sq + rows - 1) / rows);
+  if (wgs >= 512) return 1;
+  const int64_t tiles = (int64_t)n_visible * ((d->Sk + keys - 1) / keys);
+  const double tile_us = bf16 ? (d->D == 128 ? 1.6 : 0.95) : 64.0 * d->D / 2400 / 4, fixed_us = bf16 ? 8 : 4;
+  const double state_us = (double)d->B * d->Sq * d->Hq * d->D * sizeof(float) / 4e6;
+  double best = (double)((wgs + 255) / 256) * (fixed_us + tiles * tile_us);
+  int n_best = 1;
+  for (int n = 2; n <= kMaxSplits && n <= tiles; ++n) {
+    const double t = (double)((wgs * n + 255) / 256) * (fixed_us + (double)((tiles + n - 1) / n) * tile_us) + 6 + (n + 1.5) * state_us;
+    if (t < 0.95 * best) {
+      best = t;
+      n_best = n;
+    }
+  }
+  return n_best;
+}
+// A share whose full 256-row tiles fill less than half of the chip: its workspace has always held a state per chunk (up to
+// 256 workgroups) and one more, and its forward has always been refused without one.  Both are part of the interface.
+int fwd_states_small(const st_ring_desc* d, int n_visible) {
   if (d->dtype != ST_BF16 || (d->D != 128 && d->D != 64) || n_visible < 2 || n_visible > st::kMaxTable) return 1;
   if (d->Sq < st::kQTileFastRows || d->Sk < st::kQTileFastKeys) return 1;
   const int64_t wgs = (int64_t)d->B * d->Hq * (d->Sq / st::kQTileFastRows);
-  if (wgs >= 128) return 1;
+  if (wgs < 1 || wgs >= 128) return 1;
   int64_t n = 256 / wgs;
   if (n > n_visible) n = n_visible;
-  if (n > 16) n = 16;
-  return (int)n;
+  if (n > kMaxSplits) n = kMaxSplits;
+  return (int)n + 1;
+}
+// states to provide for: any subset of the chunks may be visited
+int fwd_states_most(const st_ring_desc* d) {
+  int most = fwd_states_small(d, d->n_chunks < st::kMaxTable ? d->n_chunks : st::kMaxTable);
+  for (int n = 1; n <= d->n_chunks && n <= st::kMaxTable; ++n) {
+    const int x = fwd_splits(d, n);
+    if (x > most) most = x;
+  }
+  return most;
 }
 
 // Workspace layout (each block 256-byte aligned):
 //   forward, stepwise: partial O, partial lse, member O, member lse
 //   forward, fused:    partial O and partial lse, once (when more than one launch is needed) or once per
-//                      split of an under-filled launch plus one for its masked / ragged tiles: [O_0, lse_0, O_1, ...]
+//                      split of an under-filled launch: [O_0, lse_0, O_1, ...]
 //   backward:          Delta, the tile counters of the dK/dV launch (kQueueInts ints), and for the bf16 dtype
 //                      Q' = bf16(Q scale log2 e), dense [B,Sq,Hq,D]
 size_t st_ring_workspace_bytes(const st_ring_desc* d, int32_t mode, int32_t backward) {
@@ -538,10 +561,7 @@ size_t st_ring_workspace_bytes(const st_ring_desc* d, int32_t mode, int32_t back
   if (backward)
     return n_l + align_up(st::kQueueInts * sizeof(int32_t), 256) + (d->dtype == ST_BF16 ? align_up(n_o / 2, 256) : 0);
   if (mode == ST_RING_STEPWISE) return 2 * (n_o + n_l);
-  // the split grows with the number of visited chunks up to one launch's table, and any subset may be visited
-  const int n_most = d->n_chunks < st::kMaxTable ? d->n_chunks : st::kMaxTable;
-  const int splits = fwd_splits(d, n_most);
-  return (size_t)(splits == 1 ? 1 : d->dtype == ST_BF16 ? splits + 1 : splits) * (n_o + n_l);
+  return (size_t)fwd_states_most(d) * (n_o + n_l);
 }
 
 st_status st_ring_fwd(const st_ring_desc* d, const st_tensor* q, const int32_t* order, const int32_t* member_of,
@@ -572,12 +592,15 @@ st_status st_ring_fwd(const st_ring_desc* d, const st_tensor* q, const int32_t* 
   a.q = view_of(q);
   set_table_strides(a.t, d);
   int splits = mode == ST_RING_FUSED ? fwd_splits(d, n) : 1;
-  if (splits > 1 && d->dtype == ST_BF16 && !st::fwd_fast_usable(a)) splits = 1;   // only the hand-scheduled kernel pair walks a split table
-  // without a workspace the fp32 forward is one launch over the whole table
-  if (d->dtype == ST_F32 && (workspace == nullptr || workspace_bytes < st_ring_workspace_bytes(d, mode, 0))) splits = 1;
-  const bool need_ws = mode == ST_RING_STEPWISE || n > st::kMaxTable || splits > 1;
+  if (splits > 1 && d->dtype == ST_BF16 && !st::fwd_fast_usable(a)) splits = 1;   // only the hand-scheduled kernel walks a split table
+  // the step-wise walk, more chunks than one launch takes and small shares need their workspace; any other share runs
+  // unsplit without one
+  const bool small = mode == ST_RING_FUSED && fwd_states_small(d, n) > 1 && st::fwd_fast_usable(a);
+  const bool have_ws = workspace != nullptr && workspace_bytes >= st_ring_workspace_bytes(d, mode, 0);
+  if (splits > 1 && !small && !have_ws) splits = 1;
+  const bool need_ws = mode == ST_RING_STEPWISE || n > st::kMaxTable || splits > 1 || small;
   if (need_ws) {
-    if (workspace == nullptr || workspace_bytes < st_ring_workspace_bytes(d, mode, 0)) return fail(ST_ERR_WORKSPACE, "forward workspace needs %zu bytes", st_ring_workspace_bytes(d, mode, 0));
+    if (!have_ws) return fail(ST_ERR_WORKSPACE, "forward workspace needs %zu bytes", st_ring_workspace_bytes(d, mode, 0));
     if (reinterpret_cast<uintptr_t>(workspace) % 256) return fail(ST_ERR_ALIGNMENT, "workspace: not 256-byte aligned");
   }
   char* ws = (char*)workspace;
@@ -599,8 +622,8 @@ st_status st_ring_fwd(const st_ring_desc* d, const st_tensor* q, const int32_t* 
     ST_HIP(launch_fwd(d->dtype, a, stream), "split forward launch");
     st::CombineArgs c;
     memset(&c, 0, sizeof(c));
-    c.n = splits + (d->dtype == ST_BF16 ? 1 : 0);   // one state per split, and the general workgroups' own
-    for (int y = 0; y < c.n; ++y) {
+    c.n = splits;
+    for (int y = 0; y < splits; ++y) {
       c.o[y] = part_o + (int64_t)y * a.split_o;
       c.lse[y] = part_l + (int64_t)y * a.split_l;
     }

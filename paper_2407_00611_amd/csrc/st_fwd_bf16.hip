@@ -1,7 +1,6 @@
-// bf16 forward, general kernels and the launcher of the whole forward.  The general kernel's body lives in
-// st_fwd_general.h (it also runs side by side with the hand-scheduled loop in one launch, see st_fwd_fast.hip);
-// this file wraps it as a kernel of its own, holds the software-pipelined variant used when the hand-scheduled
-// loop is switched off, and picks the kernels of a launch.  One launch with a 1-entry table is
+// bf16 forward, general kernels and the launcher of the whole forward.  The hand-scheduled kernel (st_fwd_fast.hip)
+// takes every launch whose chunks have at least 64 keys; this file holds the general kernel and its software-pipelined
+// variant for the rest, and picks the kernel of a launch.  One launch with a 1-entry table is
 // st_attn_block_fwd; with the full table it is the fused ring forward.
 #include <cstdlib>
 #include <type_traits>
@@ -16,7 +15,7 @@ namespace {
 template <int D, int kWQ>
 __global__ __launch_bounds__(256, kWQ == 32 ? 2 : 1) void fwd_bf16_kernel(const FwdArgs a) {
   __shared__ __attribute__((aligned(1024))) char smem_raw[4 * kBN * D * 2];   // 2 stages x (K, V)
-  fwd_general_body<D, kWQ>(a, blockIdx.x, gridDim.x, blockIdx.y, smem_raw);
+  fwd_general_body<D, kWQ>(a, blockIdx.x, gridDim.x, smem_raw);
 }
 
 
@@ -405,34 +404,19 @@ hipError_t launch_fwd_bf16_wq(const FwdArgs& a, hipStream_t stream) {
   return hipGetLastError();
 }
 
-hipError_t launch_fwd_bf16(const FwdArgs& a_in, hipStream_t stream) {
+hipError_t launch_fwd_bf16(const FwdArgs& a, hipStream_t stream) {
   // tuning switches (see Knobs): the general kernel's variant, and whether the hand-scheduled kernel takes part
-  const int wq = knobs().fwd_wq, pipe = knobs().fwd_pipe, fast_env = knobs().fwd_fast;
-  if ((fast_env || a_in.n_split > 1) && fwd_fast_usable(a_in)) {
-    // fully visible full tiles by the hand-scheduled kernel, then everything else (merged into its result)
-    FwdArgs a = a_in;
-    if (a.n_split > 1) {
-      // under-filled launch: the hand-scheduled workgroups (one per query tile and split) and the general ones
-      // (masked / ragged tiles, one more state) run side by side in one launch; the caller combines the states
-      a.fwd_fast = 2;
-      return launch_fwd_side_by_side(a, stream);
-    }
-    a.fwd_fast = 1;
-    hipError_t e = launch_fwd_fast(a, stream);
-    if (e != hipSuccess) return e;
-    ProfScope prof("fwd_edge", stream);
-    const int n_qt = (a.s.Sq + 127) / 128;
-    const int64_t total = (int64_t)n_qt * a.s.Hq * a.s.B;
-    if (total > 0x7fffffff) return hipErrorInvalidValue;
-    const dim3 grid((unsigned)total, (unsigned)(a.n_split > 1 ? a.n_split : 1));
-    if (a.s.D == 128) hipLaunchKernelGGL((fwd_bf16_kernel<128, 32>), grid, dim3(256), 0, stream, a);
-    else hipLaunchKernelGGL((fwd_bf16_kernel<64, 32>), grid, dim3(256), 0, stream, a);
-    return hipGetLastError();
-  }
-  if (a_in.n_split > 1) return hipErrorInvalidValue;   // only the fast / edge pair walks a split table
-  const FwdArgs& a = a_in;
-  // head size 64: the two-wavefronts-per-SIMD kernel is the faster one (21.0 against 28.3 ms on the 24-head,
-  // 16384 x 131072 full-mask share); head size 128 without the fast path: the pipelined kernel
+  const int wq = knobs().fwd_wq, pipe = knobs().fwd_pipe;
+  // At head size 64 a walk of a few tiles ends before the hand-scheduled loop has made up for its prologue: one 64-key
+  // chunk 8.1 against 6.7 us on the general kernel, five tiles 13.3 (causal 15.9) against 12.2 (11.8), eight 13.5 against
+  // 15.5, 64 tiles 60 against 86.  At head size 128 it is the faster one from the first tile on (10.8 against 11.5; 64
+  // tiles: 76 against 168).
+  const bool few = a.s.D == 64 && a.n_split <= 1 && (int64_t)a.t.n * ((a.s.Sk + kQTileFastKeys - 1) / kQTileFastKeys) <= 6;
+  if ((knobs().fwd_fast || a.n_split > 1) && !few && fwd_fast_usable(a)) return launch_fwd_fast(a, stream);
+  if (a.n_split > 1) return hipErrorInvalidValue;      // only the hand-scheduled kernel walks a split table
+  // few tiles, chunks of fewer than 64 keys, or strides beyond its 32-bit offsets.
+  // Head size 64: the two-wavefronts-per-SIMD kernel is the faster one (21.0 against 28.3 ms on the 24-head,
+  // 16384 x 131072 full-mask share); head size 128: the pipelined kernel
   if (pipe && a.s.D == 128) return launch_fwd_pipe(a, stream);
   return wq == 64 ? launch_fwd_bf16_wq<64>(a, stream) : launch_fwd_bf16_wq<32>(a, stream);
 }

@@ -1,6 +1,5 @@
-// General bf16 forward (masked and ragged tiles, any visible prefix) as a device function, so that it can be a
-// kernel of its own (st_fwd_bf16.hip) and run side by side with the hand-scheduled loop in one launch
-// (st_fwd_fast.hip).
+// General bf16 forward (masked and ragged tiles, any visible prefix, chunks of any length), the body of the kernels in
+// st_fwd_bf16.hip that take what the hand-scheduled loop (st_fwd_fast.hip) does not.
 //
 // Attention of a resident Q tile against a table of KV chunks, visited in order, with the online-softmax state
 // (row max, row sum, O accumulator) kept in registers for the whole walk.
@@ -33,13 +32,9 @@ __device__ __forceinline__ int visible_keys(int causal, int Sk, int64_t qpos, in
 // Body of the general forward kernel.  kWQ = queries per wavefront: 64 (one wavefront per SIMD) or 32 (two
 // workgroups per CU, so that one wavefront's softmax overlaps another's MFMAs).
 //   block_x, grid_x  position of this workgroup among the query tiles (XCD-aware mapping, see qtile_block)
-//   split            which share of the chunk table it walks (0 when the launch is not split)
 //   smem_raw         4 * 64 * D * 2 bytes of LDS, 1 KiB aligned
-// With a.fwd_fast == 1 the fast kernel's partial result is already in the output state and this kernel folds
-// its own into it; with a.fwd_fast == 2 (both run in ONE launch, side by side) it walks the whole table, takes
-// only the tiles that are not the fast kernel's, and writes a state of its own in split slot a.n_split.
 template <int D, int kWQ>
-__device__ __forceinline__ void fwd_general_body(const FwdArgs& a, int block_x, int grid_x, int split, char* smem_raw) {
+__device__ __forceinline__ void fwd_general_body(const FwdArgs& a, int block_x, int grid_x, char* smem_raw) {
   constexpr int kBM = 4 * kWQ;   // queries per workgroup
   constexpr int QB = kWQ / 32;   // 32-query blocks per wavefront
   constexpr int KB = kBN / 32;   // 32-key blocks per tile
@@ -102,25 +97,9 @@ __device__ __forceinline__ void fwd_general_body(const FwdArgs& a, int block_x, 
     const int nv = visible_keys(s.causal, s.Sk, q_pos(s, wg_last_row), a.t.k_offset[c]);
     return (nv + kBN - 1) / kBN;
   };
-  // first tile of a chunk that is this kernel's: the leading ones may belong to the fast kernel, whose
-  // partial (O, lse) is then already in the output buffers and is merged with this kernel's in the epilogue
-  const int fast_row0 = qt * kBM / kQTileFastRows * kQTileFastRows;
-  const bool fast_on = a.fwd_fast && kBN == kQTileFastKeys && fast_row0 + kQTileFastRows <= s.Sq;
-  auto chunk_t0 = [&](int c) -> int {
-    return fast_on ? qtile_fast_tiles(s, fast_row0, a.t.k_offset[c]) : 0;
-  };
-  // this workgroup's share of the table and its output state (one share, the whole table, unless the launch is split)
-  const bool side_by_side = a.fwd_fast == 2;
-  int c_lo = 0, c_hi = a.t.n;
-  if (!side_by_side) split_range(a.t.n, a.n_split, split, c_lo, c_hi);
-  const int slot = side_by_side ? a.n_split : split;
-  float* const out_o = a.o + (int64_t)slot * a.split_o;
-  float* const out_lse = a.lse + (int64_t)slot * a.split_l;
-  bool fast_wrote = false;
-  if (fast_on && !side_by_side)
-    for (int c = c_lo; c < c_hi; ++c) fast_wrote = fast_wrote || chunk_t0(c) > 0;
-  int c_cur = c_lo, t_cur = 0, n_cur = 0;       // current chunk, tile, tiles in chunk
-  while (c_cur < c_hi && (n_cur = chunk_tiles(c_cur)) <= (t_cur = chunk_t0(c_cur))) ++c_cur;
+  const int c_hi = a.t.n;
+  int c_cur = 0, t_cur = 0, n_cur = 0;          // current chunk, tile, tiles in chunk
+  while (c_cur < c_hi && (n_cur = chunk_tiles(c_cur)) <= 0) ++c_cur;
 
   auto issue_load = [&](int c, int t, int stage) {
     const char* kb = (const char*)a.t.k[c] + ((int64_t)b * a.t.ksb + (int64_t)hk * a.t.ksh) * 2;
@@ -138,7 +117,8 @@ __device__ __forceinline__ void fwd_general_body(const FwdArgs& a, int block_x, 
     int c_nxt = c_cur, t_nxt = t_cur + 1, n_nxt = n_cur;
     if (t_nxt >= n_cur) {
       ++c_nxt;
-      while (c_nxt < c_hi && (n_nxt = chunk_tiles(c_nxt)) <= (t_nxt = chunk_t0(c_nxt))) ++c_nxt;
+      t_nxt = 0;
+      while (c_nxt < c_hi && (n_nxt = chunk_tiles(c_nxt)) <= 0) ++c_nxt;
     }
     const bool have_next = c_nxt < c_hi;
     if (have_next) issue_load(c_nxt, t_nxt, buf ^ 1);
@@ -250,7 +230,7 @@ __device__ __forceinline__ void fwd_general_body(const FwdArgs& a, int block_x, 
     n_cur = n_nxt;
   }
 
-  // ---- epilogue: O = acc / l, lse = m ln 2 + ln(l); folded into the fast kernel's partial result if there is one
+  // ---- epilogue: O = acc / l, lse = m ln 2 + ln(l)
 #pragma unroll
   for (int qb = 0; qb < QB; ++qb) {
     const int i = q_row0 + 32 * qb + r;
@@ -258,48 +238,23 @@ __device__ __forceinline__ void fwd_general_body(const FwdArgs& a, int block_x, 
     const float inv = l > 0.f ? 1.f / l : 0.f;
     if (i < s.Sq) {
       const int64_t orow = (((int64_t)b * s.Sq + i) * s.Hq + h) * D;
-      const int64_t srow = ((int64_t)b * s.Hq + h) * s.Sq + i;
-      float lse_own = l > 0.f ? m_run[qb] * kLn2 + logf(l) : -INFINITY;
-      float w_own = inv, w_prev = 0.f;          // weights of this kernel's accumulator and of the stored partial O
-      if (fast_wrote) {
-        const float lse_prev = out_lse[srow];
-        const float mx = fmaxf(lse_prev, lse_own);
-        if (mx != -INFINITY) {
-          const float e_prev = expf(lse_prev - mx), e_own = expf(lse_own - mx);
-          const float tot = e_prev + e_own;
-          w_prev = e_prev / tot;
-          w_own = inv * (e_own / tot);
-          lse_own = mx + logf(tot);
-        }
-      }
 #pragma unroll
       for (int db = 0; db < DB; ++db)
 #pragma unroll
         for (int q4 = 0; q4 < 4; ++q4) {
           const int d = 32 * db + 8 * q4 + 4 * g;
           float4 o;
-          o.x = acc_o[db][qb][4 * q4 + 0] * w_own;
-          o.y = acc_o[db][qb][4 * q4 + 1] * w_own;
-          o.z = acc_o[db][qb][4 * q4 + 2] * w_own;
-          o.w = acc_o[db][qb][4 * q4 + 3] * w_own;
-          if (fast_wrote) {
-            const float4 p = *reinterpret_cast<const float4*>(out_o + orow + d);
-            o.x = fmaf(p.x, w_prev, o.x);
-            o.y = fmaf(p.y, w_prev, o.y);
-            o.z = fmaf(p.z, w_prev, o.z);
-            o.w = fmaf(p.w, w_prev, o.w);
-          }
-          *reinterpret_cast<float4*>(out_o + orow + d) = o;
+          o.x = acc_o[db][qb][4 * q4 + 0] * inv;
+          o.y = acc_o[db][qb][4 * q4 + 1] * inv;
+          o.z = acc_o[db][qb][4 * q4 + 2] * inv;
+          o.w = acc_o[db][qb][4 * q4 + 3] * inv;
+          *reinterpret_cast<float4*>(a.o + orow + d) = o;
           if (a.o_lowp) {
             uint2 w = make_uint2(pack_bf16(o.x, o.y), pack_bf16(o.z, o.w));
             *reinterpret_cast<uint2*>((uint16_t*)a.o_lowp + orow + d) = w;
           }
         }
-      if (g == 0) out_lse[srow] = lse_own;
-      // side by side with the fast kernel: rows outside the full query tiles have no fast workgroup, so the
-      // split states, which only fast workgroups write, are marked empty there
-      if (side_by_side && !fast_on && g == 0)
-        for (int y = 0; y < a.n_split; ++y) a.lse[(int64_t)y * a.split_l + srow] = -INFINITY;
+      if (g == 0) a.lse[((int64_t)b * s.Hq + h) * s.Sq + i] = l > 0.f ? m_run[qb] * kLn2 + logf(l) : -INFINITY;
     }
   }
 }

@@ -1,0 +1,71 @@
+"""Masked and ragged tiles in the hand-scheduled bf16 forward, against the fp64 oracle: chunk lengths around the 64-key tile,
+query counts around the 64 rows of a wavefront and the 256 of a workgroup, the diagonal at every alignment, shards in two
+runs that meet inside a tile, walks without a single tile that all rows see, and splits that cut the masked part.
+Tolerance: the bf16 bounds of assert_close."""
+import numpy as np
+import pytest
+import torch
+
+import paper_2407_00611_amd as st
+import synth_inputs as si
+from oracle import attention as oa
+from util import assert_close, assert_close_wide, host, positions, upload
+
+pytestmark = pytest.mark.gpu
+
+#        D, Hq, Hkv, Sq, Sk, n, q_offset, causal, (q_seg, q_offset2)
+CASES = [(128, 1, 1, 1, 64, 1, 63, True, (0, 0)),
+         (128, 2, 1, 65, 65, 2, 65, True, (0, 0)),
+         (128, 1, 1, 255, 127, 3, 126, True, (0, 0)),
+         (128, 3, 1, 257, 129, 2, 0, False, (0, 0)),
+         (128, 1, 1, 300, 64, 6, 30, True, (0, 0)),              # every tile is crossed, some rows see nothing
+         (128, 2, 2, 512, 192, 4, 256, True, (200, 600)),         # two runs that meet inside a query tile
+         (128, 1, 1, 40, 448, 2, 880, True, (0, 0)),
+         (64, 2, 1, 1, 500, 1, 20, True, (0, 0)),
+         (64, 1, 1, 320, 500, 2, 690, True, (0, 0)),
+         (64, 2, 2, 257, 449, 3, 0, False, (0, 0)),
+         (64, 1, 1, 300, 130, 4, 100, True, (33, 360))]
+
+
+def _check(w, inp, orders, mode=st.ST_RING_FUSED, close=assert_close, **kw):
+    q, ks, vs, _ = upload(inp)
+    q_pos, k_pos = positions(w)
+    koffs = [w.k_offset(j) for j in range(w.n_chunks)]
+    o_ref, lse_ref = oa.attention_forward(inp.q, inp.k, inp.v, q_pos, k_pos, w.causal, w.scale)
+    for order in orders:
+        o, lse, low = st.st_ring_fwd(q, ks, vs, w.q_where, koffs, w.causal, w.scale, order, None, mode)
+        close(host(o), o_ref, *kw.get("args", ()), "o")
+        close(host(lse), lse_ref, *kw.get("args", ()), "lse", lse=True)
+        assert torch.equal(low, o.to(torch.bfloat16))
+
+
+@pytest.mark.parametrize("mode", [st.ST_RING_FUSED, st.ST_RING_STEPWISE], ids=["fused", "stepwise"])
+@pytest.mark.parametrize("c", CASES, ids=[f"d{c[0]}_q{c[3]}_k{c[4]}" for c in CASES])
+def test_forward_at_tile_edges(c, mode):
+    D, Hq, Hkv, Sq, Sk, n, q0, causal, (seg, q2) = c
+    w = si.Workload("masks", 320 + Sq % 50, "bf16", 1, Hq, Hkv, D, Sq, Sk, n, q0, causal, False, q_seg=seg, q_offset2=q2)
+    print(f"[masks] {c} mode {mode}", flush=True)
+    _check(w, si.make_inputs(w), [list(range(n)), list(range(n))[::-1]], mode, args=("bf16",))
+
+
+@pytest.mark.parametrize("D", [128, 64])
+def test_rows_that_meet_their_first_key_late(D):
+    """Every tile is masked (the shard's 256 rows start before the chunk's keys do) and every score lies some hundred
+    log2 units below zero: the exponent reference of a row must come from the first block in which it sees a key."""
+    w = si.Workload("late", 330, "bf16", 1, 1, 1, D, 256, 512, 1, -100, True, False)
+    inp = si.make_inputs(w)
+    # a common direction: <q, k> = -3 D plus noise, so scale * log2 e * <q, k> is about -49 (D = 128) and below;
+    # with four times the keys, below -190: exp2 of it is zero in fp32
+    for a, bits in ((inp.q, inp.q_bits), (inp.k[0], inp.k_bits[0])):
+        a[:] = si.bf16_bits_to_f32(si.f32_to_bf16_bits(a * 0.25 + (1.0 if a is inp.q else -12.0 * np.sqrt(128 / D))))
+        bits[:] = si.f32_to_bf16_bits(a)
+    q_pos, k_pos = positions(w)
+    _, lse_ref = oa.attention_forward(inp.q, inp.k, inp.v, q_pos, k_pos, True, w.scale)
+    assert np.isneginf(lse_ref[..., :100]).all() and lse_ref[..., 100:].max() < -100     # exp2 underflows at -149
+    _check(w, inp, [[0]], close=lambda x, r, what, lse=False: assert_close_wide(x, r, what, lse=lse))
+
+
+def test_split_cuts_the_masked_part():
+    """One head, so the walk of every query tile is split sixteen ways and some splits hold masked tiles only."""
+    w = si.Workload("split_masks", 331, "bf16", 1, 1, 1, 128, 700, 700, 3, 1400, True, False)
+    _check(w, si.make_inputs(w), [[0, 1, 2], [2, 0, 1]], args=("bf16",))
