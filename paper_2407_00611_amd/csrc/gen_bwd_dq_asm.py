@@ -5,8 +5,11 @@
     python gen_bwd_dq_asm.py 64 > st_bwd_dq64_asm.inc     (head_dim 64: half the MFMAs per group, 128-byte tile rows)
 
 Body of ONE `asm volatile` statement in st_bwd_dq_fast.hip.  A workgroup (4 wavefronts) owns 256 queries
-of one head, 64 per wavefront as two 32-query blocks, and walks the 64-key tiles that every one of its
-rows sees in full (tiles that need a mask, ragged tails and ragged query tiles go to the general kernel).
+of one head, 64 per wavefront as two 32-query blocks, and walks 64-key tiles: first those that every one of its
+rows sees in full, then the S_NM that a mask edge crosses.  As in the forward, one scalar test per key block calls
+an out-of-line routine that puts -inf in place of the exponents of invisible pairs (P = 0, hence dS = 0); the
+ragged end of a chunk is read as its last 64 rows, and rows beyond the shard are neither read nor written back.
+The result is added to dq_acc, or, where the walk is split over workgroups, stored as a partial sum.
 The MFMA C layout is "lane = query column", so lse and Delta are one register per lane and block.
 Q and dO fragments stay in AGPRs (MFMA B operands may come from there), the dQ^T accumulators too.
 The Q fragments are multiplied by scale * log2(e) once (and rounded to bf16 again) and the S^T accumulators
@@ -55,17 +58,24 @@ KOFF, VOFF = 248, 252                                # per-lane global offsets o
 IN_VA, IN_VB = 160, 176                              # v[160:175], v[176:179]
 I_QROW0, I_QROW1, I_DOROW0, I_DOROW1 = 160, 162, 164, 166
 I_NL0, I_NL1, I_ND0, I_ND1, I_XBASE, I_GF16, I_TRBASE, I_LF16 = 168, 169, 170, 171, 172, 173, 174, 175
-I_KOFF0, I_VOFF0, I_DQOFF = 176, 177, 178
+I_KOFF0, I_VOFF0, I_DQOFF, I_LIVE = 176, 177, 178, 179        # I_LIVE: bit qb = the lane's row of block qb exists
 PT = 184                                             # 184..199: temporaries of the prologue
 (S_LDS, S_WAVE, S_NT, S_KRS16, S_VRS16, S_SCALE, S_DQPTR, S_DQQB, S_TBL, S_KTILE, S_VTILE) = (32, 33, 34, 35, 36, 37, 38, 40, 41, 42, 43)
 # scalar temporaries
 S_CEXP, T_M0, T_REM, D_KPTR, D_VPTR, D_LEFT, D_IDX, D_TBL, T_X = 47, 64, 65, 66, 68, 70, 71, 72, 73
+# set by the prologue, from the parameter block behind the table in LDS
+S_LIVE = 48                                          # 48:49, 50:51: lanes whose row of block qb exists
+S_NM, S_MTBL, S_PART, S_NM1 = 76, 77, 78, 79         # masked tiles; their first table entry; 1: store a partial sum; S_NM + 1
+M_LEFT, M_REL, M_LO, T_MRET, T_MASK, T_CMP = 52, 53, 54, 82, 84, 88   # masked walk; mask routine kb at 84 + 2 kb; four compare results
 
 # ---- LDS map
 def KT(s): return 2 * TILE * s
 def VT(s): return 2 * TILE * s + TILE
-TBL = 2 * TILE * NS                                     # 64 entries x 32 bytes: k lo/hi, v lo/hi, tiles, pad
-LDS_BYTES = TBL + 2048
+TBL = 2 * TILE * NS                                  # at most three entries per chunk: whole tiles, masked tiles, ragged end
+PARAMS = 3 * 64 * 32                                 # offset of the parameter block from the table
+QREL = PARAMS + 64                                   # and of the rows' positions relative to the tile's first row, less
+                                                     # 4 * (lane / 32): 8 bytes per thread (two query blocks)
+LDS_BYTES = TBL + QREL + 256 * 8
 
 LAT = int(os.environ.get("ST_GEN_DQ_LAT", 3))
 BUDGET = int(os.environ.get("ST_GEN_DQ_BUDGET", 5 if D == 128 else 7))
@@ -124,6 +134,80 @@ def read_kt(p, stage, kb, m, db, seq):
     off = imm(stage, KT(stage)) + 32 * ROW * kb + 16 * ROW * m
     p.e.ds_read(f"ds_read_b64_tr_b16 {vr(r, 2)}, {vr(lo + db)} offset:{off}", tag + "lo")
     p.e.ds_read(f"ds_read_b64_tr_b16 {vr(r + 2, 2)}, {vr(hi + db)} offset:{off}", tag)
+
+
+MASK_STUBS = []                                      # (call label, return label, score buffer) of every mask test
+
+
+def mask_test(e, limit, buf):
+    """Call the mask routine of score buffer `buf` if its block lies in one of the last S_NM tiles (the tile in hand is
+    the T_REM-th from the end; limit = S_NM for a block of that tile, S_NM + 1 for one of the next)."""
+    l_call, l_back = e.label("mcall"), e.label("mback")
+    e.raw(f"s_cmp_le_u32 {sr(T_REM)}, {sr(limit)}")
+    e.raw(f"s_cbranch_scc1 {l_call}")
+    e.raw(l_back + ":")
+    MASK_STUBS.append((l_call, l_back, buf))
+
+
+def gen_mask_routine(e, kb):
+    """Score buffer kb holds the exponents of key block kb of a masked tile: -inf wherever the key is not the row's.
+    Key t of the tile (0 .. 63) is visible to a row iff t >= M_LO and M_REL + t <= the row's position, both relative to
+    the position of the workgroup's first row.  Block 0 moves on to the next tile of the masked walk first."""
+    n4, ninf, lim, lo = TMP, TMP + 1, TMP + 2, TMP + 4       # lim: a pair at an even register
+    if kb == 0:
+        l_step, l_go = e.label("mstep"), e.label("mgo")
+        e.raw(f"s_cmp_lg_u32 {sr(M_LEFT)}, 0")
+        e.raw(f"s_cbranch_scc1 {l_step}")
+        e.raw(f"v_mov_b32 {vr(TMP)}, {sr(S_MTBL)}")
+        e.raw(f"ds_read_b64 {vr(TMP + 2, 2)}, {vr(TMP)} offset:16")
+        e.raw(f"ds_read_b32 {vr(TMP + 4)}, {vr(TMP)} offset:24")
+        e.raw("s_waitcnt lgkmcnt(0)")
+        for i, dst in enumerate((M_LEFT, M_REL, M_LO)):
+            e.raw(f"v_readfirstlane_b32 {sr(dst)}, {vr(TMP + 2 + i)}")
+        e.raw(f"s_add_u32 {sr(S_MTBL)}, {sr(S_MTBL)}, 32")
+        e.raw(f"s_branch {l_go}")
+        e.raw(l_step + ":")
+        e.raw(f"s_add_i32 {sr(M_REL)}, {sr(M_REL)}, 64")
+        e.raw(l_go + ":")
+        e.raw(f"s_sub_u32 {sr(M_LEFT)}, {sr(M_LEFT)}, 1")
+    e.raw(f"v_mbcnt_lo_u32_b32 {vr(n4)}, -1, 0")
+    e.raw(f"v_mbcnt_hi_u32_b32 {vr(n4)}, -1, {vr(n4)}")
+    e.raw(f"v_lshlrev_b32 {vr(lo)}, 3, {vr(n4)}")
+    e.raw(f"s_lshl_b32 {sr(T_CMP)}, {sr(S_WAVE)}, 9")
+    e.raw(f"s_add_u32 {sr(T_CMP)}, {sr(T_CMP)}, {sr(S_TBL)}")
+    e.raw(f"v_add_u32 {vr(lo)}, {sr(T_CMP)}, {vr(lo)}")
+    e.raw(f"ds_read_b64 {vr(lim, 2)}, {vr(lo)} offset:{QREL}")
+    e.raw(f"v_lshrrev_b32 {vr(n4)}, 5, {vr(n4)}")
+    e.raw(f"v_lshlrev_b32 {vr(n4)}, 2, {vr(n4)}")
+    e.raw(f"v_mov_b32 {vr(ninf)}, 0xff800000")
+    e.raw("s_waitcnt lgkmcnt(0)")
+    for qb in range(QB):
+        e.raw(f"v_subrev_u32 {vr(lim + qb)}, {sr(M_REL)}, {vr(lim + qb)}")
+        if kb:
+            e.raw(f"v_subrev_u32 {vr(lim + qb)}, 32, {vr(lim + qb)}")
+    e.raw("s_nop 7")                                # the newest exponents come from an MFMA issued two slots ago
+    e.raw("s_nop 7")
+    e.raw("s_nop 7")
+
+    def each(cmp, bound):
+        for qb in range(QB):
+            for v0 in range(0, 16, 4):              # four compares ahead of the four selects that read them
+                for i in range(4):
+                    e.raw(f"{cmp} {sr(T_CMP + 2 * i, 2)}, {vr(bound(qb))}, {8 * (v0 // 4) + i}")
+                for i in range(4):
+                    x = vr(SBUF(kb, qb) + v0 + i)
+                    e.raw(f"v_cndmask_b32_e64 {x}, {vr(ninf)}, {x}, {sr(T_CMP + 2 * i, 2)}")
+    each("v_cmp_ge_i32_e64", lambda qb: lim + qb)
+    l_ret = e.label("mret")
+    e.raw(f"s_cmp_eq_u32 {sr(M_LO)}, 0")
+    e.raw(f"s_cbranch_scc1 {l_ret}")
+    e.raw(f"v_sub_u32 {vr(lo)}, {sr(M_LO)}, {vr(n4)}")
+    if kb:
+        e.raw(f"v_subrev_u32 {vr(lo)}, 32, {vr(lo)}")
+    each("v_cmp_le_i32_e64", lambda qb: lo)
+    e.raw(l_ret + ":")
+    e.raw("s_nop 1")
+    e.raw(f"s_setpc_b64 {sr(T_MRET, 2)}")
 
 
 def gen_block(p, cur, nxt, nxt2, pbuf, seq, do_b=True, do_ac=True, head=None, prefetched=True, side=None):
@@ -234,6 +318,8 @@ def gen_block(p, cur, nxt, nxt2, pbuf, seq, do_b=True, do_ac=True, head=None, pr
             for ln in side[k]:
                 e.raw(ln)
             units += 2
+        if do_ac and k == early1:                        # before the first exponential of the new block
+            mask_test(e, S_NM1 if do_b and cur[1] == 1 else S_NM, nbuf)
         while vi[0] < len(valu) and valu[vi[0]][0] <= k and units + valu[vi[0]][3] <= BUDGET:
             units += emit_valu(valu[vi[0]])
             vi[0] += 1
@@ -300,6 +386,7 @@ def gen_table_entry(e):
 def generate():
     e = Emitter()
     p = Pipe(e)
+    l_mask = [e.label("mask0"), e.label("mask1")]
     e.comment("---- prologue")
     e.raw(f"s_lshl_b32 {sr(T_M0)}, {sr(S_WAVE)}, 10")
     e.raw(f"s_add_u32 {sr(T_M0)}, {sr(T_M0)}, {sr(S_LDS)}")
@@ -310,6 +397,23 @@ def generate():
     e.raw(f"v_mul_f32 {vr(TMP)}, {sr(S_SCALE)}, {vr(TMP)}")
     e.raw("s_nop 0")
     e.raw(f"v_readfirstlane_b32 {sr(S_CEXP)}, {vr(TMP)}")
+    for dst, target in [(T_MASK + 2 * b, l_mask[b]) for b in range(2)]:
+        l_here = e.label("here")
+        e.raw(f"s_getpc_b64 {sr(dst, 2)}")
+        e.raw(l_here + ":")
+        e.raw(f"s_add_u32 {sr(dst)}, {sr(dst)}, {target}-{l_here}")
+        e.raw(f"s_addc_u32 {sr(dst + 1)}, {sr(dst + 1)}, 0")
+    e.raw(f"v_mov_b32 {vr(TMP)}, {sr(S_TBL)}")
+    e.raw(f"ds_read_b64 {vr(TMP + 2, 2)}, {vr(TMP)} offset:{PARAMS}")
+    e.raw(f"ds_read_b32 {vr(TMP + 4)}, {vr(TMP)} offset:{PARAMS + 8}")
+    e.raw("s_waitcnt lgkmcnt(0)")
+    for i, dst in enumerate((S_NM, S_MTBL, S_PART)):
+        e.raw(f"v_readfirstlane_b32 {sr(dst)}, {vr(TMP + 2 + i)}")
+    e.raw(f"s_add_u32 {sr(S_NM1)}, {sr(S_NM)}, 1")
+    e.raw(f"s_mov_b32 {sr(M_LEFT)}, 0")
+    for qb in range(QB):
+        e.raw(f"v_and_b32 {vr(TMP)}, {1 << qb}, {vr(I_LIVE)}")
+        e.raw(f"v_cmp_ne_u32_e64 {sr(S_LIVE + 2 * qb, 2)}, 0, {vr(TMP)}")
     e.comment("per-lane DMA offsets: instruction 4 j + wave covers rows 16 j + 4 wave .. + 3 of a 64-row tile")
     e.raw(f"v_mov_b32 {vr(KOFF)}, {vr(I_KOFF0)}")
     e.raw(f"v_mov_b32 {vr(VOFF)}, {vr(I_VOFF0)}")
@@ -404,36 +508,59 @@ def generate():
         e.raw(l_next + ":")
         gen_table_entry(e)
         e.raw(f"s_branch {l_skip}")
+    for l_call, l_back, buf in MASK_STUBS:
+        e.raw(l_call + ":")
+        e.raw(f"s_swappc_b64 {sr(T_MRET, 2)}, {sr(T_MASK + 2 * buf, 2)}")
+        e.raw(f"s_branch {l_back}")
+    for b in range(2):
+        e.raw(l_mask[b] + ":")
+        gen_mask_routine(e, b)
     e.raw(l_done + ":")
     e.raw("s_waitcnt vmcnt(0) lgkmcnt(0)")
     e.comment("---- epilogue: dq_acc += scale * dQ; lane = query row, 4 consecutive d per 16-byte access")
     e.raw("s_nop 7")
     e.raw("s_nop 7")
-    for qb in range(QB):
-        if qb == 1:
-            e.raw(f"v_add_u32 {vr(DQOFF)}, {sr(S_DQQB)}, {vr(DQOFF)}")
-        for db in range(DB):
-            for j in range(4):
-                e.raw(f"global_load_dwordx4 {vr(4 * (4 * db + j), 4)}, {vr(DQOFF)}, {sr(S_DQPTR, 2)} offset:{128 * db + 32 * j}")
-        for db in range(DB):
-            for j in range(4):
-                t = 4 * (4 * db + j)
-                e.raw(f"s_waitcnt vmcnt({4 * DB - 1 - (4 * db + j)})")
-                for i in range(4):
-                    e.raw(f"v_accvgpr_read_b32 {vr(TMP)}, {ar(ACC(db, qb) + 4 * j + i)}")
-                    e.raw("s_nop 0")
-                    e.raw(f"v_fma_f32 {vr(t + i)}, {vr(TMP)}, {sr(S_SCALE)}, {vr(t + i)}")
-        for db in range(DB):
-            for j in range(4):
-                e.raw(f"global_store_dwordx4 {vr(DQOFF)}, {vr(4 * (4 * db + j), 4)}, {sr(S_DQPTR, 2)} offset:{128 * db + 32 * j}")
-        e.raw("s_waitcnt vmcnt(0)")
+    l_part, l_end = e.label("part"), e.label("end")
+    e.raw(f"s_cmp_lg_u32 {sr(S_PART)}, 0")
+    e.raw(f"s_cbranch_scc1 {l_part}")
+    for part in (False, True):
+        if part:
+            e.raw(l_part + ":")
+        for qb in range(QB):
+            if qb == 1:
+                e.raw(f"v_add_u32 {vr(DQOFF)}, {sr(S_DQQB)}, {vr(DQOFF)}")
+            e.raw(f"s_mov_b64 exec, {sr(S_LIVE + 2 * qb, 2)}")
+            if not part:
+                for db in range(DB):
+                    for j in range(4):
+                        e.raw(f"global_load_dwordx4 {vr(4 * (4 * db + j), 4)}, {vr(DQOFF)}, {sr(S_DQPTR, 2)} offset:{128 * db + 32 * j}")
+            for db in range(DB):
+                for j in range(4):
+                    t = 4 * (4 * db + j)
+                    if not part:
+                        e.raw(f"s_waitcnt vmcnt({4 * DB - 1 - (4 * db + j)})")
+                    for i in range(4):
+                        e.raw(f"v_accvgpr_read_b32 {vr(TMP)}, {ar(ACC(db, qb) + 4 * j + i)}")
+                        e.raw("s_nop 0")
+                        if part:
+                            e.raw(f"v_mul_f32 {vr(t + i)}, {sr(S_SCALE)}, {vr(TMP)}")
+                        else:
+                            e.raw(f"v_fma_f32 {vr(t + i)}, {vr(TMP)}, {sr(S_SCALE)}, {vr(t + i)}")
+            for db in range(DB):
+                for j in range(4):
+                    e.raw(f"global_store_dwordx4 {vr(DQOFF)}, {vr(4 * (4 * db + j), 4)}, {sr(S_DQPTR, 2)} offset:{128 * db + 32 * j}")
+            e.raw("s_mov_b64 exec, -1")
+            e.raw("s_waitcnt vmcnt(0)")
+        if not part:
+            e.raw(f"s_branch {l_end}")
+    e.raw(l_end + ":")
     return e
 
 
 def main():
     e = generate()
     clob = [f"v{i}" for i in range(256) if not 160 <= i < 180] + [f"a{i}" for i in range(256)]
-    clob += [f"s{S_CEXP}"] + [f"s{i}" for i in range(64, 76)]
+    clob += [f"s{i}" for i in range(S_CEXP, 55)] + [f"s{i}" for i in range(64, 96)]
     write_inc(sys.stdout, "gen_bwd_dq_asm.py" + (" 64" if D == 64 else ""), "ST_DQ_FAST" + ("64" if D == 64 else ""), e,
               LDS_BYTES, clob)
 

@@ -505,7 +505,7 @@ st_status st_schedule_report(int32_t P, int32_t C, int64_t B, int64_t N, int64_t
 // 6 us for the launch of the combine pass, which moves 4 TB/s on states this small.  fp32: a 32-key tile is 64 D cycles of
 // a SIMD's matrix unit, and eight wavefronts on four SIMDs share the keys.
 constexpr int kMaxSplits = 16;
-int fwd_splits(const st_ring_desc* d, int n_visible) {
+static int fwd_splits(const st_ring_desc* d, int n_visible) {
   const bool bf16 = d->dtype == ST_BF16;
   if (n_visible < 1 || n_visible > st::kMaxTable || d->B < 1 || d->Sq < 1 || d->Hq < 1) return 1;
   if (bf16 && ((d->D != 128 && d->D != 64) || d->Sk < st::kQTileFastKeys)) return 1;
@@ -528,7 +528,7 @@ int fwd_splits(const st_ring_desc* d, int n_visible) {
 }
 // A share whose full 256-row tiles fill less than half of the chip: its workspace has always held a state per chunk (up to
 // 256 workgroups) and one more, and its forward has always been refused without one.  Both are part of the interface.
-int fwd_states_small(const st_ring_desc* d, int n_visible) {
+static int fwd_states_small(const st_ring_desc* d, int n_visible) {
   if (d->dtype != ST_BF16 || (d->D != 128 && d->D != 64) || n_visible < 2 || n_visible > st::kMaxTable) return 1;
   if (d->Sq < st::kQTileFastRows || d->Sk < st::kQTileFastKeys) return 1;
   const int64_t wgs = (int64_t)d->B * d->Hq * (d->Sq / st::kQTileFastRows);
@@ -539,7 +539,7 @@ int fwd_states_small(const st_ring_desc* d, int n_visible) {
   return (int)n + 1;
 }
 // states to provide for: any subset of the chunks may be visited
-int fwd_states_most(const st_ring_desc* d) {
+static int fwd_states_most(const st_ring_desc* d) {
   int most = fwd_states_small(d, d->n_chunks < st::kMaxTable ? d->n_chunks : st::kMaxTable);
   for (int n = 1; n <= d->n_chunks && n <= st::kMaxTable; ++n) {
     const int x = fwd_splits(d, n);
@@ -552,14 +552,51 @@ int fwd_states_most(const st_ring_desc* d) {
 //   forward, stepwise: partial O, partial lse, member O, member lse
 //   forward, fused:    partial O and partial lse, once (when more than one launch is needed) or once per
 //                      split of an under-filled launch: [O_0, lse_0, O_1, ...]
-//   backward:          Delta, the tile counters of the dK/dV launch (kQueueInts ints), and for the bf16 dtype
-//                      Q' = bf16(Q scale log2 e), dense [B,Sq,Hq,D]
+//   backward:          Delta, the tile counters of the dK/dV launch (kQueueInts ints), for the bf16 dtype
+//                      Q' = bf16(Q scale log2 e), dense [B,Sq,Hq,D], and the partial sums of an under-filled dQ launch
+static size_t bwd_base_bytes(const st_ring_desc* d) {
+  const size_t n_o = align_up((size_t)d->B * d->Sq * d->Hq * d->D * sizeof(float), 256);
+  return align_up((size_t)d->B * d->Sq * d->Hq * sizeof(float), 256) + align_up(st::kQueueInts * sizeof(int32_t), 256) +
+         (d->dtype == ST_BF16 ? align_up(n_o / 2, 256) : 0);
+}
+
+// Workgroups per query tile of the dQ pass.  Same model as the forward's: a 256 x 64 tile is three contractions instead of
+// two (2.4 us at head size 128, 1.4 at 64), the pass that adds the partial sums up reads and writes dQ as well.
+// The split never asks for more than the static scratch of st_ring_bwd_noalloc has room for, so that both entry points
+// compute the same sums.
+static int dq_splits(const st_ring_desc* d, int n_visible, size_t workspace_bytes) {
+  if (d->dtype != ST_BF16 || (d->D != 128 && d->D != 64) || d->Sk < st::kQTileFastKeys || n_visible < 1 || d->B < 1 || d->Sq < 1 || d->Hq < 1) return 1;
+  const int64_t wgs = (int64_t)d->B * d->Hq * ((d->Sq + st::kQTileFastRows - 1) / st::kQTileFastRows);
+  if (wgs >= 512) return 1;
+  const int64_t tiles = (int64_t)n_visible * ((d->Sk + st::kQTileFastKeys - 1) / st::kQTileFastKeys);
+  const size_t n_o = align_up((size_t)d->B * d->Sq * d->Hq * d->D * sizeof(float), 256), base = bwd_base_bytes(d);
+  const size_t room = workspace_bytes < kScratchBytes ? workspace_bytes : kScratchBytes;
+  const double tile_us = d->D == 128 ? 2.4 : 1.4, fixed_us = 10, state_us = (double)n_o / 4e6;
+  double best = (double)((wgs + 255) / 256) * (fixed_us + tiles * tile_us);
+  int n_best = 1;
+  for (int n = 2; n <= kMaxSplits && n <= tiles && base + (size_t)n * n_o <= room; ++n) {
+    const double t = (double)((wgs * n + 255) / 256) * (fixed_us + (double)((tiles + n - 1) / n) * tile_us) + 6 + (n + 2) * state_us;
+    if (t < 0.95 * best) {
+      best = t;
+      n_best = n;
+    }
+  }
+  return n_best;
+}
+
 size_t st_ring_workspace_bytes(const st_ring_desc* d, int32_t mode, int32_t backward) {
   if (d == nullptr) return 0;
   const size_t n_o = align_up((size_t)d->B * d->Sq * d->Hq * d->D * sizeof(float), 256);
   const size_t n_l = align_up((size_t)d->B * d->Sq * d->Hq * sizeof(float), 256);
-  if (backward)
-    return n_l + align_up(st::kQueueInts * sizeof(int32_t), 256) + (d->dtype == ST_BF16 ? align_up(n_o / 2, 256) : 0);
+  if (backward) {
+    // any subset of the chunks may be visited, in one launch or in several
+    int most = 1;
+    for (int n = 1; n <= d->n_chunks && n <= st::kMaxTable; ++n) {
+      const int x = dq_splits(d, mode == ST_RING_FUSED ? n : 1, kScratchBytes);
+      if (x > most) most = x;
+    }
+    return bwd_base_bytes(d) + (most > 1 ? (size_t)most * n_o : 0);
+  }
   if (mode == ST_RING_STEPWISE) return 2 * (n_o + n_l);
   return (size_t)fwd_states_most(d) * (n_o + n_l);
 }
@@ -698,7 +735,7 @@ st_status st_ring_bwd_noalloc(const st_ring_desc* d, const st_tensor* q, const s
                               int32_t mode, float* dq_acc, float* const* dk_acc, float* const* dv_acc, void* hip_stream) {
   if (d == nullptr) return fail(ST_ERR_INVALID_ARG, "null descriptor");
   ST_TRY(check_shape(d->dtype, d->B, d->Hq, d->Hkv, d->D, d->Sq, d->Sk));
-  const size_t need = st_ring_workspace_bytes(d, mode, 1);
+  const size_t need = bwd_base_bytes(d);               // a split of the dQ pass never needs more than the scratch
   if (need > kScratchBytes)
     return fail(ST_ERR_WORKSPACE, "st_ring_bwd_noalloc: this share needs %zu bytes of scratch, the library's static scratch holds %zu; use st_ring_bwd with a workspace", need, kScratchBytes);
   void* ws = nullptr;
@@ -730,7 +767,8 @@ st_status st_ring_bwd_last(const st_ring_desc* d, const st_tensor* q, const st_t
   const bool no_rows = n_o == 0;                     // no query rows: every contribution is zero
   if (no_rows && !assign && !dk_lowp) return ST_OK;
   if (!no_rows) {
-    if (workspace == nullptr || workspace_bytes < st_ring_workspace_bytes(d, mode, 1)) return fail(ST_ERR_WORKSPACE, "backward workspace needs %zu bytes", st_ring_workspace_bytes(d, mode, 1));
+    // without room for the partial sums of the dQ pass it runs on fewer workgroups
+    if (workspace == nullptr || workspace_bytes < bwd_base_bytes(d)) return fail(ST_ERR_WORKSPACE, "backward workspace needs %zu bytes", st_ring_workspace_bytes(d, mode, 1));
     if (reinterpret_cast<uintptr_t>(workspace) % 256) return fail(ST_ERR_ALIGNMENT, "workspace: not 256-byte aligned");
   }
   hipStream_t stream = (hipStream_t)hip_stream;
@@ -782,6 +820,7 @@ st_status st_ring_bwd_last(const st_ring_desc* d, const st_tensor* q, const st_t
     ST_HIP(st::launch_scale_q(a.q, qs, d->B, d->Sq, d->Hq, d->D, d->scale, stream), "scaled-Q launch");
     a.qs = qs;
   }
+  const int64_t part_stride = (int64_t)(align_up((size_t)n_o * sizeof(float), 256) / sizeof(float));
   const int per_launch = mode == ST_RING_FUSED ? st::kMaxTable : 1;
   for (int x0 = 0; x0 < n; x0 += per_launch) {
     const int cnt = n - x0 < per_launch ? n - x0 : per_launch;
@@ -793,6 +832,9 @@ st_status st_ring_bwd_last(const st_ring_desc* d, const st_tensor* q, const st_t
       a.dk_lowp[x] = dk_lowp ? dk_lowp[j] : nullptr;
       a.dv_lowp[x] = dk_lowp ? dv_lowp[j] : nullptr;
     }
+    a.n_split = dq_splits(d, cnt, workspace_bytes);
+    a.dq_part = (float*)((char*)workspace + bwd_base_bytes(d));
+    a.part_stride = part_stride;
     a.kv_assign = assign ? ~0ull : 0ull;
     if (d->dtype != ST_BF16 && assign)              // the fp32 kernels only add
       for (int x = 0; x < cnt; ++x) {

@@ -102,14 +102,8 @@ __global__ __launch_bounds__(256, kQ_WQ == 32 ? 2 : 1) void bwd_dq_bf16_kernel(c
     const int nv = visible_keys(s.causal, s.Sk, q_pos(s, wg_last_row), a.t.k_offset[c]);
     return (nv + kQ_BN - 1) / kQ_BN;
   };
-  // first tile of a chunk that is this kernel's: the leading ones may belong to the fast kernel
-  const int fast_row0 = qt * kQ_BM / kDqFastRows * kDqFastRows;
-  const bool fast_on = a.dq_fast && kQ_BN == kDqFastKeys && fast_row0 + kDqFastRows <= s.Sq;
-  auto chunk_t0 = [&](int c) -> int {
-    return fast_on ? dq_fast_tiles(s, fast_row0, a.t.k_offset[c]) : 0;
-  };
   int c_cur = 0, t_cur = 0, n_cur = 0;
-  while (c_cur < a.t.n && (n_cur = chunk_tiles(c_cur)) <= (t_cur = chunk_t0(c_cur))) ++c_cur;
+  while (c_cur < a.t.n && (n_cur = chunk_tiles(c_cur)) <= 0) ++c_cur;
 
   auto issue_load = [&](int c, int t, int stage) {
     const char* kb = (const char*)a.t.k[c] + ((int64_t)b * a.t.ksb + (int64_t)hk * a.t.ksh) * 2;
@@ -125,7 +119,8 @@ __global__ __launch_bounds__(256, kQ_WQ == 32 ? 2 : 1) void bwd_dq_bf16_kernel(c
     int c_nxt = c_cur, t_nxt = t_cur + 1, n_nxt = n_cur;
     if (t_nxt >= n_cur) {
       ++c_nxt;
-      while (c_nxt < a.t.n && (n_nxt = chunk_tiles(c_nxt)) <= (t_nxt = chunk_t0(c_nxt))) ++c_nxt;
+      t_nxt = 0;
+      while (c_nxt < a.t.n && (n_nxt = chunk_tiles(c_nxt)) <= 0) ++c_nxt;
     }
     const bool have_next = c_nxt < a.t.n;
     if (have_next) issue_load(c_nxt, t_nxt, buf ^ 1);
@@ -546,16 +541,16 @@ hipError_t launch_bwd_bf16(const BwdArgs& a_in, hipStream_t stream) {
     if (e == hipSuccess && cast_dv[c]) e = launch_cast(a.dv[c], cast_dv[c], n_kv, ST_BF16, stream);
     if (e != hipSuccess) return e;
   }
-  a.dq_fast = (knobs().dq_fast && dq_fast_usable(a)) ? 1 : 0;
-  {
-    ProfScope prof(a.dq_fast ? "bwd_dq_edge" : "bwd_dq_bf16", stream);
-    if (a.s.D == 128) hipLaunchKernelGGL(bwd_dq_bf16_kernel<128>, dim3((unsigned)total_q), dim3(256), 0, stream, a);
-    else hipLaunchKernelGGL(bwd_dq_bf16_kernel<64>, dim3((unsigned)total_q), dim3(256), 0, stream, a);
+  if (knobs().dq_fast && dq_fast_usable(a)) {
+    e = launch_bwd_dq_fast(a, stream);
+    if (e == hipSuccess && a.n_split > 1)
+      e = launch_add_parts(a.dq, a.dq_part, a.n_split, a.part_stride, (int64_t)a.s.B * a.s.Sq * a.s.Hq * a.s.D, stream);
+    return e;
   }
-  e = hipGetLastError();
-  if (e != hipSuccess) return e;
-  if (a.dq_fast) return launch_bwd_dq_fast(a, stream);
-  return hipSuccess;
+  ProfScope prof("bwd_dq_bf16", stream);
+  if (a.s.D == 128) hipLaunchKernelGGL(bwd_dq_bf16_kernel<128>, dim3((unsigned)total_q), dim3(256), 0, stream, a);
+  else hipLaunchKernelGGL(bwd_dq_bf16_kernel<64>, dim3((unsigned)total_q), dim3(256), 0, stream, a);
+  return hipGetLastError();
 }
 
 }  // namespace st

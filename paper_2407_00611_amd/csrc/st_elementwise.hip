@@ -258,6 +258,29 @@ __global__ __launch_bounds__(256) void scale_q_kernel(View q, u32x4* __restrict_
   dst[v] = scale_bf16x8(*reinterpret_cast<const u32x4*>((const uint16_t*)q.ptr + off), c);
 }
 
+// Partial sums of an under-filled launch: bytes only, (n_parts + 2) x 4 per element.  Eight loads of a thread are in flight
+// together; the order of the additions is fixed.
+__global__ __launch_bounds__(256) void add_parts_kernel(float4* __restrict__ dst, const float4* __restrict__ parts, int n_parts,
+                                                        int64_t stride, int64_t n_vec) {
+  const int64_t v = (int64_t)blockIdx.x * 256 + threadIdx.x;
+  if (v >= n_vec) return;
+  float4 x = dst[v];
+  for (int y0 = 0; y0 < n_parts; y0 += 8) {
+    float4 p[8];
+#pragma unroll
+    for (int u = 0; u < 8; ++u) p[u] = parts[(int64_t)min(y0 + u, n_parts - 1) * stride + v];
+#pragma unroll
+    for (int u = 0; u < 8; ++u)
+      if (y0 + u < n_parts) {
+        x.x += p[u].x;
+        x.y += p[u].y;
+        x.z += p[u].z;
+        x.w += p[u].w;
+      }
+  }
+  dst[v] = x;
+}
+
 __global__ __launch_bounds__(256) void fill_state_kernel(float* __restrict__ o, float* __restrict__ lse,
                                                          int64_t n_o, int64_t n_lse) {
   const int64_t v = (int64_t)blockIdx.x * 256 + threadIdx.x;
@@ -380,6 +403,14 @@ hipError_t launch_zero(void* dst, int64_t bytes, hipStream_t s) {
   const int64_t n = bytes / 4;
   ProfScope prof("zero", s);
   hipLaunchKernelGGL(zero_kernel, dim3(blocks_for((n + 3) / 4)), dim3(256), 0, s, (uint32_t*)dst, n);
+  return hipGetLastError();
+}
+
+hipError_t launch_add_parts(float* dst, const float* parts, int n_parts, int64_t stride, int64_t n, hipStream_t s) {
+  if (n <= 0 || n_parts <= 0) return hipSuccess;
+  ProfScope prof("add_parts", s);
+  hipLaunchKernelGGL(add_parts_kernel, dim3(blocks_for(n / 4)), dim3(256), 0, s, (float4*)dst, (const float4*)parts, n_parts,
+                     stride / 4, n / 4);
   return hipGetLastError();
 }
 

@@ -85,7 +85,12 @@ struct BwdArgs {
   float* dk[kMaxTable];  // fp32 [B,Sk,Hkv,D] per table entry, +=
   float* dv[kMaxTable];
   int32_t dkv_fast;    // 1: the fast dK/dV kernel runs too and owns the blocks dkv_fast_first_block describes
-  int32_t dq_fast;     // 1: the fast dQ kernel runs too and owns the tiles dq_fast_tiles describes
+  // Under-filled dQ launches of the hand-scheduled kernel: n_split > 1 gives every query tile n_split workgroups
+  // (blockIdx.y), each storing the sum over its share of the tiles at dq_part + y * part_stride (floats, laid out as dq);
+  // the launcher then adds them to dq in order.
+  int32_t n_split;
+  float* dq_part;
+  int64_t part_stride;
   // dK / dV work of a chunk's last visit folded into the launch (bf16 path).  On entry to launch_bwd_bf16 they
   // state what the caller wants for every table entry; the launcher keeps them for the entries whose every
   // block belongs to the fast kernel (their only writer) and serves the others with fill / cast launches.
@@ -166,24 +171,11 @@ struct ProfScope {
   hipStream_t stream;
 };
 
-// Split of the query-stationary kernels (forward, dQ; head_dim 128): for every FULL tile of kQTileFastRows
-// queries the fast kernel takes, of each chunk, the leading kQTileFastKeys-key tiles that the tile's first
-// row (hence every row) sees in full.
+// Tile of the hand-scheduled query-stationary kernels (forward, dQ)
 constexpr int kQTileFastRows = 256;
 constexpr int kQTileFastKeys = 64;
 constexpr int kDqFastRows = kQTileFastRows;
 constexpr int kDqFastKeys = kQTileFastKeys;
-__host__ __device__ inline int qtile_fast_tiles(const Shape& s, int row0, int64_t k0) {
-  int64_t nv = s.Sk;
-  if (s.causal) {
-    nv = q_pos(s, row0) - k0 + 1;
-    nv = nv < 0 ? 0 : (nv > s.Sk ? s.Sk : nv);
-  }
-  return (int)(nv / kQTileFastKeys);
-}
-__host__ __device__ inline int dq_fast_tiles(const Shape& s, int row0, int64_t k0) {
-  return qtile_fast_tiles(s, row0, k0);
-}
 
 // ---- launchers (each returns hipGetLastError() after the launch) ----
 hipError_t launch_fwd_f32(const FwdArgs& a, hipStream_t s);
@@ -206,6 +198,8 @@ hipError_t launch_delta(const View& d_o, int d_o_dtype, const View& o, int o_dty
 hipError_t launch_cast(const float* src, void* dst, int64_t n, int dst_dtype, hipStream_t s);
 // dst (dense bf16 [B,Sq,Hq,D]) = bf16(q * scale * log2 e) of a bf16 view q
 hipError_t launch_scale_q(const View& q, void* dst, int32_t B, int32_t Sq, int32_t Hq, int32_t D, float scale, hipStream_t s);
+// dst += parts[0] + parts[1] + ... in that order; part y at parts + y * stride, n floats each (n % 4 == 0)
+hipError_t launch_add_parts(float* dst, const float* parts, int n_parts, int64_t stride, int64_t n, hipStream_t s);
 hipError_t launch_fill_state(float* o, float* lse, int64_t n_o, int64_t n_lse, hipStream_t s);
 hipError_t launch_zero(void* dst, int64_t bytes, hipStream_t s);   // bytes % 4 == 0, dst 4-byte aligned
 // benchmark aid: MFMA-only loop, one workgroup per compute unit (see st_probe.hip)

@@ -1,0 +1,99 @@
+// The walk of a query-stationary workgroup (256 rows of one head) over the 64-key tiles its rows see, as the hand-scheduled
+// forward and dQ loops take it: a table in LDS, whole tiles first, masked ones last.
+#pragma once
+
+#include "st_internal.h"
+#include "st_mfma.h"
+
+namespace st {
+namespace {
+
+// every value passed through sgpr() is uniform over the wavefront by construction (kernel arguments, block index)
+__device__ __forceinline__ uint32_t sgpr(uint32_t x) { return __builtin_amdgcn_readfirstlane(x); }
+__device__ __forceinline__ uint32_t lo32(const void* p) { return (uint32_t)(uintptr_t)p; }
+__device__ __forceinline__ uint32_t hi32(const void* p) { return (uint32_t)((uintptr_t)p >> 32); }
+// sum over the lanes before this one; total = sum over all lanes
+__device__ __forceinline__ int lane_scan(int x, int lane, int& total) {
+  int sum = x;
+#pragma unroll
+  for (int d = 1; d < 64; d *= 2) {
+    const int y = __shfl_up(sum, d);
+    if (lane >= d) sum += y;
+  }
+  total = __shfl(sum, 63);
+  return sum - x;
+}
+
+constexpr int kRelMin = -(1 << 30);                  // relative position of a tile that no causal mask touches
+
+// The tiles a workgroup walks, written to LDS by one wavefront, a lane per chunk of the table.  Entry (32 bytes): K and V
+// addresses, tiles, position of the first key relative to q_base, first key of the (single) tile that counts, pad.
+// Whole tiles of all chunks come first, then the masked ones; split y of n takes the tiles [T y / n, T (y + 1) / n) of the
+// T in that order.  Returns the tiles of the split; n_masked of them, the last ones, are masked; their entries start at
+// first_masked.
+__device__ __forceinline__ int build_walk(const Shape& s, const ChunkTable& t, int splits, int row0, int b, int hk, int split, ST_LDS uint32_t* tbl, int lane,
+                                          int& n_masked, int& first_masked) {
+  constexpr int BM = kQTileFastRows, BN = kQTileFastKeys;
+  const int n64 = s.Sk / BN;
+  const int64_t q_base = q_pos(s, row0), q_last = q_pos(s, min(row0 + BM, s.Sq) - 1);
+  int nf = 0, nm = 0, nr = 0;                        // whole tiles, masked tiles, ragged end (0 or 1)
+  const char *kp = nullptr, *vp = nullptr;
+  int64_t rel0 = 0;
+  if (lane < t.n) {
+    const int64_t k0 = t.k_offset[lane];
+    kp = (const char*)t.k[lane] + ((int64_t)b * t.ksb + (int64_t)hk * t.ksh) * 2;
+    vp = (const char*)t.v[lane] + ((int64_t)b * t.vsb + (int64_t)hk * t.vsh) * 2;
+    int64_t nv = s.Sk, nv_last = s.Sk;               // keys the first / last row sees
+    if (s.causal) {
+      rel0 = k0 - q_base;
+      nv = min(max(q_base - k0 + 1, (int64_t)0), (int64_t)s.Sk);
+      nv_last = min(max(q_last - k0 + 1, (int64_t)0), (int64_t)s.Sk);
+    }
+    nf = (int)nv / BN;
+    nm = max(min(((int)nv_last + BN - 1) / BN, n64) - nf, 0);
+    nr = nv_last > (int64_t)n64 * BN;
+  }
+  int total_full, total_masked;
+  const int pf = lane_scan(nf, lane, total_full);
+  const int pm = total_full + lane_scan(nm + nr, lane, total_masked);
+  const int64_t total = (int64_t)total_full + total_masked;
+  const int n_split = max(splits, 1);
+  const int lo = (int)(total * split / n_split), hi = (int)(total * (split + 1) / n_split);
+  const int f0 = max(pf, lo), cf = max(min(pf + nf, hi) - f0, 0);
+  const int m0 = max(pm, lo), cm = max(min(pm + nm, hi) - m0, 0);
+  const int cr = nr && pm + nm >= lo && pm + nm < hi;
+  const uint64_t before = ((uint64_t)1 << lane) - 1, has_f = __ballot(cf > 0), has_m = __ballot(cm > 0), has_r = __ballot(cr);
+  auto put = [&](int entry, int key0, int tiles, int lo_key) {
+    const char* k = kp + (int64_t)key0 * t.kss * 2;
+    const char* v = vp + (int64_t)key0 * t.vss * 2;
+    const int64_t rel = s.causal ? min(max(rel0 + key0, (int64_t)kRelMin), (int64_t)-kRelMin) : (int64_t)kRelMin;
+    ST_LDS uint32_t* e = tbl + 8 * entry;
+    e[0] = lo32(k); e[1] = hi32(k); e[2] = lo32(v); e[3] = hi32(v);
+    e[4] = (uint32_t)tiles; e[5] = (uint32_t)(int32_t)rel; e[6] = (uint32_t)lo_key;
+  };
+  first_masked = __popcll(has_f);
+  if (cf > 0) put(__popcll(has_f & before), (f0 - pf) * BN, cf, 0);
+  const int em = first_masked + __popcll(has_m & before) + __popcll(has_r & before);
+  if (cm > 0) put(em, (nf + m0 - pm) * BN, cm, 0);
+  if (cr) put(em + (cm > 0), s.Sk - BN, 1, n64 * BN - (s.Sk - BN));   // the chunk's last 64 rows, those of the tile before masked
+  n_masked = hi - max(lo, min(total_full, hi));
+  return hi - lo;
+}
+
+// what the loops keep in 32-bit registers fits them
+inline bool walk_usable(const Shape& s, const ChunkTable& t) {
+  if ((s.D != 128 && s.D != 64) || s.Sk < kQTileFastKeys || s.Sq < 1) return false;
+  auto fits = [](int64_t x) { return x > 0 && x < (int64_t)1 << 30; };
+  if (!(fits(kQTileFastKeys * t.kss * 2) && fits(kQTileFastKeys * t.vss * 2) && fits((int64_t)kQTileFastRows * s.Hq * s.D * 4)))
+    return false;
+  // positions inside a query tile, relative to its first row; only the tile that holds the end of a first run can be wide
+  if (s.causal && s.q_seg > 0) {
+    const int row0 = s.q_seg / kQTileFastRows * kQTileFastRows;
+    const int last = row0 + kQTileFastRows < s.Sq ? row0 + kQTileFastRows - 1 : s.Sq - 1;
+    if (last > row0 && !fits(q_pos(s, last) - q_pos(s, row0))) return false;
+  }
+  return true;
+}
+
+}  // namespace
+}  // namespace st

@@ -69,3 +69,69 @@ def test_split_cuts_the_masked_part():
     """One head, so the walk of every query tile is split sixteen ways and some splits hold masked tiles only."""
     w = si.Workload("split_masks", 331, "bf16", 1, 1, 1, 128, 700, 700, 3, 1400, True, False)
     _check(w, si.make_inputs(w), [[0, 1, 2], [2, 0, 1]], args=("bf16",))
+
+
+def _backward(w, inp, mode, assign=None):
+    q, ks, vs, d_o = upload(inp)
+    koffs = [w.k_offset(j) for j in range(w.n_chunks)]
+    order = list(range(w.n_chunks))
+    args = (w.q_where, koffs, w.causal, w.scale, order)
+    o, lse, low = st.st_ring_fwd(q, ks, vs, *args, None, mode)
+    dq = torch.full_like(o, 0.25)                       # gradients are added to what is there
+    dk = [torch.full(k.shape, float("nan") if assign else -0.5, device="cuda") for k in ks]
+    dv = [x.clone() for x in dk]
+    lows = None
+    if assign is None:
+        st.st_ring_bwd(q, ks, vs, d_o, low, lse, *args, dq, dk, dv, mode)
+    else:
+        lows = [[torch.empty_like(k) for k in ks] for _ in range(2)]
+        st.st_ring_bwd_last(q, ks, vs, d_o, low, lse, *args, dq, dk, dv, assign=assign, dk_lowp=lows[0], dv_lowp=lows[1], mode=mode)
+        for x, y in zip(dk + dv, lows[0] + lows[1]):
+            assert torch.equal(x.to(torch.bfloat16), y)
+    base = 0.0 if assign else -0.5
+    q_pos, k_pos = positions(w)
+    ref = oa.attention_backward(inp.q, inp.k, inp.v, inp.d_o, q_pos, k_pos, w.causal, w.scale)
+    assert_close(host(dq) - 0.25, ref[0], "bf16", "dq")
+    for j in range(w.n_chunks):
+        # few keys and hundreds of rows: gradients well above 1, bounded relative to the largest
+        assert_close_wide(host(dk[j]) - base, ref[1][j], f"dk[{j}]")
+        assert_close_wide(host(dv[j]) - base, ref[2][j], f"dv[{j}]")
+
+
+@pytest.mark.parametrize("how", ["add", "assign", "add_lowp", "stepwise"])
+@pytest.mark.parametrize("c", CASES, ids=[f"d{c[0]}_q{c[3]}_k{c[4]}" for c in CASES])
+def test_backward_at_tile_edges(c, how):
+    D, Hq, Hkv, Sq, Sk, n, q0, causal, (seg, q2) = c
+    w = si.Workload("masks", 320 + Sq % 50, "bf16", 1, Hq, Hkv, D, Sq, Sk, n, q0, causal, True, q_seg=seg, q_offset2=q2)
+    print(f"[masks backward] {c} {how}", flush=True)
+    _backward(w, si.make_inputs(w), st.ST_RING_STEPWISE if how == "stepwise" else st.ST_RING_FUSED,
+              {"assign": True, "add_lowp": False}.get(how))
+
+
+def test_backward_split_over_workgroups():
+    """One head against 60 tiles: the dQ pass is split, and its sums are the same from call to call and from st_ring_bwd to
+    st_ring_bwd_noalloc; with a workspace of the unsplit size it runs unsplit."""
+    w = si.Workload("split_bwd", 332, "bf16", 1, 2, 1, 128, 300, 640, 6, 6 * 640 - 300, True, True)
+    inp = si.make_inputs(w)
+    _backward(w, inp, st.ST_RING_FUSED)
+    q, ks, vs, d_o = upload(inp)
+    koffs = [w.k_offset(j) for j in range(w.n_chunks)]
+    args = (w.q_where, koffs, w.causal, w.scale)
+    order = list(range(w.n_chunks))
+    need = st.st_ring_workspace_bytes(q, ks, vs, *args, st.ST_RING_FUSED, True)
+    n_o = (q.numel() * 4 + 255) // 256 * 256
+    assert need > 2 * n_o
+    o, lse, low = st.st_ring_fwd(q, ks, vs, *args, order)
+    got = []
+    for ws in (None, None, "noalloc", need % n_o + n_o):
+        dq = torch.zeros_like(o)
+        dk = [torch.zeros(k.shape, device="cuda") for k in ks]
+        dv = [torch.zeros(k.shape, device="cuda") for k in ks]
+        if ws == "noalloc":
+            st.st_ring_bwd_noalloc(q, ks, vs, d_o, low, lse, *args, order, dq, dk, dv)
+        else:
+            buf = None if ws is None else torch.empty(ws + 256, dtype=torch.uint8, device="cuda")
+            st.st_ring_bwd(q, ks, vs, d_o, low, lse, *args, order, dq, dk, dv, workspace=buf)
+        got.append(dq)
+    assert torch.equal(got[0], got[1]) and torch.equal(got[0], got[2])
+    assert_close(host(got[3]), host(got[0]), "bf16", "dq unsplit")
