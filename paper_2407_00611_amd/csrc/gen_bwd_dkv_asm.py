@@ -11,8 +11,8 @@ registers, because the kernel needs all 512 registers of a wavefront (256 accumu
 resident K fragments and the score tiles in VGPRs) and a fixed interleave of MFMA, LDS and VALU work.
 
 Work of one workgroup (4 wavefronts): 256 keys of one KV head of one chunk (64 per wavefront), against a
-run of 32-query blocks that see every one of those keys (no masking in here; blocks that need a mask go
-to the general kernel).  Per block and wavefront, with the MFMA C layout "lane = key column":
+run of 32-query blocks, from the first one with a row that sees one of those keys to the last.  Per block and
+wavefront, with the MFMA C layout "lane = key column":
     phase 1   E   = Q' K^T - lse log2e          A: Q' rows from LDS (Q' = bf16(Q scale log2 e), made once per backward
                                                 by a pass of its own and shared with the other bf16 kernels, so that
                                                 every kernel evaluates the same scores), B: resident K fragments,
@@ -28,6 +28,12 @@ the KV group being the inner index: workgroups of one XCD that work on key tiles
 the same rows of Q' and dO at about the same time whichever block their own tile's run starts at (under a causal
 mask the runs start at different blocks and all end at the last one), so those rows are fetched into the XCD's
 L2 once per round of tiles instead of once per workgroup.
+Masked blocks sit at the two ends of the walk: a last block that reaches beyond the shard comes first, the blocks on
+the causal diagonal come last.  The loop exists twice: one copy for whole blocks, whose closing compare also notices
+that the diagonal has come, and one that calls an out-of-line routine in every block; that routine puts -inf in place of
+the exponents of invisible pairs (P = 0, hence dS = 0) and knows everything else about masks.  The rows of such a last block, and the
+keys of a last key tile that reaches beyond the chunk, re-read the last row that exists; the epilogue leaves the latter
+out with an exec mask (variants of their own, so that whole tiles pay nothing).
 Q' / dO tiles arrive by direct global->LDS loads into a 4-stage ring, three blocks ahead; the per-row
 statistics (lse, Delta) are loaded three blocks ahead into registers, transformed once and written to LDS
 by every wavefront (identical values), so that no per-element VALU work is spent on them.
@@ -73,11 +79,13 @@ X = 224                                              # x[ks]: natural-read offse
 XV = 232                                             # xv[ks]: the same inside this wavefront's V rows
 TRLO, TRHI = 240, 244                                # transpose-read offsets per d block
 QOFF, DOOFF = 248, 250                               # per-lane global offsets of the two DMA instructions
-STAT_G, STAT_L, DKV_OFF, G16 = 252, 253, 254, 255
+STAT_G, STAT_L, G16 = 252, 253, 255
+def KFIRST(nb): return 216 + nb                      # first query row that sees the lane's key
+QOFFN, DOOFFN, STATGN, MT = 218, 220, 222, 223       # QOFF, DOOFF, STAT_G of a whole block; temporary of the mask routine
 
 # inputs pinned by the C++ side
 IN_V = 176                                           # v[176:191]
-(I_KROW0, I_KROW1, I_VOFF, I_QOFF0, I_QOFF1, I_DOOFF0, I_DOOFF1, I_STAT_G, I_DKV, I_XBASE, I_GF16, I_TRBASE,
+(I_KROW0, I_KROW1, I_VCOL, I_QOFF0, I_QOFF1, I_DOOFF0, I_DOOFF1, I_STAT_G, I_SROW, I_XBASE, I_GF16, I_TRBASE,
  I_LF16, I_STAT_L) = (176, 178, 180, 181, 182, 183, 184, 185, 186, 187, 188, 189, 190, 191)
 IN_SA, IN_SB = 32, 48                                # s[32:47], s[48:63]
 S_QPTR, S_DOPTR, S_LSEPTR, S_DLPTR = 32, 34, 36, 38
@@ -85,12 +93,17 @@ S_QPTR, S_DOPTR, S_LSEPTR, S_DLPTR = 32, 34, 36, 38
 # per block, S_*IN bytes from one head to the next, S_*OUT bytes (signed, all three of one sign) from one block
 # to the next one visited.
 S_QIN, S_QOUT, S_DOIN, S_DOOUT, S_STOUT, S_NIN, S_NSTEPS, S_STIN = 40, 41, 42, 43, 44, 45, 46, 47
-S_VPTR, S_VRS16, S_LDS, S_DKPTR, S_DVPTR, S_WAVE, S_RS32, S_SCALE = 48, 50, 51, 52, 54, 56, 57, 58
+S_VPTR, S_VRS, S_LDS, S_DKPTR, S_DVPTR, S_WAVE, S_RS32, S_SCALE = 48, 50, 51, 52, 54, 56, 57, 58
 S_FLAGS, S_DKLP, S_DVLP = 59, 60, 62                # epilogue variant; bf16 copies of the dK / dV tile (if asked for)
 # scalar temporaries (clobbered)
 T_QPTR, T_QHEAD, T_DOPTR, T_DOHEAD = 64, 66, 68, 70
 T_LSEPTR, T_LSEHEAD, T_DLPTR, T_DLHEAD = 72, 74, 76, 78
 T_DBLK, T_DSTEP, T_ADV, T_WRAP, T_REM, T_M0, T_HIMASK, T_X, T_VPTR, T_INC, T_HINC = 80, 81, 82, 83, 84, 85, 86, 88, 90, 92, 93
+# parameters from LDS (see PBLK) and the mask's state
+# (in input registers that the prologue has copied, in-out operands of the statement: the C++ loop around it has no other
+# scalar registers to spare)
+S_NRAG, S_EVT, S_DIAG, S_CI0, S_SQ, S_ROWS, S_GREC, S_CI, T_MRET, T_MASK, T_MT = 32, 33, 34, 35, 36, 37, 38, 39, 48, 90, 94
+T_CMP = (82, 88, 92)                                 # three compare results, in registers that only the stream advance uses
 T_HI, T_OHI = 94, 95                                 # upper half of the outer increment: this step's, and when one is applied
 
 def ACC_K(db, nb): return 16 * (2 * db + nb)
@@ -101,7 +114,12 @@ STATS = 0                                            # stage s: nl[32] at 256 s,
 def QT(s): return 1024 + 2 * TQ * s
 def DOT(s): return 1024 + 2 * TQ * s + TQ
 VT = 1024 + 2 * TQ * NS                              # V tile of the workgroup: 256 rows
-LDS_BYTES = max(VT + 256 * ROW, 4 * 2 * 32 * (4 * D + 16))   # the tiles of the loop; the epilogue's staging rows
+# Behind the tiles of the loop and the epilogue's staging rows, written by the C++ side: 32 bytes per thread (first query
+# row that sees each of its two keys; QOFF x 2, DOOFF x 2, STAT_G of a whole block; unused), then one uniform block:
+#   0 steps of a ragged last block (its heads), or -1   1 steps on the diagonal, the last ones   2 2^32 / heads + 1
+#   3 first row of the first block walked               4 query rows                             5 keys of the tile that exist
+PBLK = max(VT + 256 * ROW, 4 * 2 * 32 * (4 * D + 16))
+LDS_BYTES = PBLK + 256 * 32 + 32
 
 LAT = int(os.environ.get("ST_GEN_DKV_LAT", 3))          # MFMA slots between the issue of an LDS read and its first use
 BUDGET = int(os.environ.get("ST_GEN_DKV_BUDGET", 6 if D == 128 else 11))       # issue units of side work per MFMA slot (an MFMA occupies the pipe for 8 quad-cycles)
@@ -136,6 +154,75 @@ def advance_code():
     for ptr, head, bs, hs in STREAMS:
         c.append(f"s_cselect_b64 {sr(ptr, 2)}, {sr(head, 2)}, {sr(ptr, 2)}")
     return c
+
+
+
+
+LEAVE_STUBS = []                                     # (label, block of the masked loop) of every way out of the whole one
+
+
+def gen_whole_offsets(e):
+    """From here on the requests read whole blocks."""
+    for j in range(NDQ):
+        e.raw(f"v_mov_b32 {vr(QOFF + j)}, {vr(QOFFN + j)}")
+        e.raw(f"v_mov_b32 {vr(DOOFF + j)}, {vr(DOOFFN + j)}")
+    e.raw(f"v_mov_b32 {vr(STAT_G)}, {vr(STATGN)}")
+
+
+def gen_mask_routine(e):
+    """S holds the exponents of the block whose first row is S_CI: -inf where the row does not see the lane's key, or does
+    not exist.  Called two MFMA issues behind the last contraction step of S."""
+    n4, low, high = TMP, TMP + 1, MT
+    for _ in range(3):
+        e.raw("s_nop 7")
+    l_one, l_still = e.label("onehead"), e.label("still")
+    e.raw(f"s_sub_u32 {sr(T_MT)}, {sr(S_NSTEPS)}, {sr(T_REM)}")             # steps done; the block is that many heads on
+    e.raw(f"s_cmp_eq_u32 {sr(S_NIN)}, 1")
+    e.raw(f"s_cbranch_scc1 {l_one}")
+    e.raw(f"s_mul_hi_u32 {sr(T_MT)}, {sr(T_MT)}, {sr(S_GREC)}")
+    e.raw(l_one + ":")
+    e.raw(f"s_lshl_b32 {sr(T_MT)}, {sr(T_MT)}, 5")
+    e.raw(f"s_sub_u32 {sr(S_CI)}, {sr(S_CI0)}, {sr(T_MT)}")
+    # the next mask: while steps of a ragged block are left, in the next step; then on the diagonal
+    e.raw(f"s_sub_u32 {sr(T_MT)}, {sr(S_NSTEPS)}, {sr(S_NRAG)}")
+    e.raw(f"s_add_u32 {sr(T_MT)}, {sr(T_MT)}, 1")
+    e.raw(f"s_cmp_gt_u32 {sr(T_REM)}, {sr(T_MT)}")
+    e.raw(f"s_cselect_b32 {sr(S_EVT)}, -1, {sr(S_DIAG)}")
+    # the tile requested in this step is the first whole block's, or a later one's
+    e.raw(f"s_cmp_lt_u32 {sr(T_DSTEP)}, {sr(S_NRAG)}")
+    e.raw(f"s_cbranch_scc1 {l_still}")
+    gen_whole_offsets(e)
+    e.raw(l_still + ":")
+    e.raw(f"v_mbcnt_lo_u32_b32 {vr(n4)}, -1, 0")
+    e.raw(f"v_mbcnt_hi_u32_b32 {vr(n4)}, -1, {vr(n4)}")
+    e.raw(f"v_lshrrev_b32 {vr(n4)}, 5, {vr(n4)}")
+    e.raw(f"v_lshlrev_b32 {vr(n4)}, 2, {vr(n4)}")
+    for nb in range(NKB):
+        e.raw(f"v_subrev_u32 {vr(low + nb)}, {sr(S_CI)}, {vr(KFIRST(nb))}")
+        e.raw(f"v_sub_u32 {vr(low + nb)}, {vr(low + nb)}, {vr(n4)}")
+
+    def each(cmp, bound):
+        for nb in range(NKB):
+            for v0 in range(0, 16, 3):              # three compares ahead of the three selects that read them
+                vs = range(v0, min(v0 + 3, 16))
+                for v in vs:
+                    e.raw(f"{cmp} {sr(T_CMP[v - v0], 2)}, {vr(bound(nb))}, {8 * (v // 4) + v % 4}")
+                if len(vs) < 3:
+                    e.raw("s_nop 1")
+                for v in vs:
+                    x = vr(S0 + 16 * nb + v)
+                    e.raw(f"v_cndmask_b32_e64 {x}, {vr(NINF)}, {x}, {sr(T_CMP[v - v0], 2)}")
+    each("v_cmp_le_i32_e64", lambda nb: low + nb)
+    l_ret = e.label("mret")
+    e.raw(f"s_add_u32 {sr(T_MT)}, {sr(S_CI)}, 32")
+    e.raw(f"s_cmp_le_u32 {sr(T_MT)}, {sr(S_SQ)}")
+    e.raw(f"s_cbranch_scc1 {l_ret}")
+    e.raw(f"s_sub_u32 {sr(T_MT)}, {sr(S_SQ)}, {sr(S_CI)}")
+    e.raw(f"v_sub_u32 {vr(high)}, {sr(T_MT)}, {vr(n4)}")
+    each("v_cmp_gt_i32_e64", lambda nb: high)
+    e.raw(l_ret + ":")
+    e.raw("s_nop 1")
+    e.raw(f"s_setpc_b64 {sr(T_MRET, 2)}")
 
 
 def request_code(stage, st_set):
@@ -238,7 +325,7 @@ SYNC_SLOT = P3 - 1        # the barrier sits behind this MFMA slot (end of phase
 PUBLISH_SLOT = P3 - 6     # wait for the next block's loads and write its statistics behind this slot
 
 
-def gen_step(e, pool, u, seq, reads, next_reads):
+def gen_step(e, pool, u, seq, reads, next_reads, masked):
     """One 32-query block on LDS stage u (the loop is unrolled NS times so that stage addresses are immediates)."""
     e.comment(f"================ block on stage {u}")
     slots = []
@@ -356,6 +443,8 @@ def gen_step(e, pool, u, seq, reads, next_reads):
         for ln in side[k]:
             e.raw(ln)
             units += 1
+        if masked and k == P2 + 1:                       # before the first exponential
+            e.raw(f"s_swappc_b64 {sr(T_MRET, 2)}, {sr(T_MASK, 2)}")
         if k == PUBLISH_SLOT:
             # tile and statistics of the next block: everything but the six newest memory operations has landed
             e.raw(f"s_waitcnt vmcnt({NREQ})")
@@ -396,8 +485,9 @@ def epilogue(e):
     32 cache lines and the epilogue is bound by the rate of cache-line lookups.  Each wavefront therefore turns
     its tile through LDS (its own region, rows padded by 16 bytes) and reads, adds and writes the fp32
     accumulators in HBM as whole rows: 64 lanes x 16 bytes = RPI complete rows per access.
-    Four passes (key block x {dK, dV}).  Four variants, chosen by S_FLAGS: bit 0 = the accumulators are assigned,
-    not added to (nothing is read from HBM); bit 1 = the final values are also written rounded to bf16.  When
+    Four passes (key block x {dK, dV}).  Eight variants, chosen by S_FLAGS: bit 0 = the accumulators are assigned,
+    not added to (nothing is read from HBM); bit 1 = the final values are also written rounded to bf16; bit 2 = the tile
+    has fewer than 256 keys.  When
     adding, the HBM reads run two passes ahead of their use; nothing waits for the stores (vmcnt counts loads
     and stores in issue order, which is why every variant has its own waits)."""
     RSL = 4 * D + 16                                   # bytes of a padded fp32 row in LDS
@@ -408,7 +498,7 @@ def epilogue(e):
     def G(p, n): return 4 * NLD * (p % 2) + 4 * n      # HBM values of pass p (two sets)
     def T(n): return 128 + 4 * n                       # the wavefront's own values, row layout
     def W(k): return 192 + 4 * (k % 4)                 # accumulator pieces on their way to LDS; later bf16 pairs
-    LR, LW, GOFF, LANE, TA, TB, GOFF2 = 208, 209, 210, 211, 212, 213, 214
+    LR, LW, GOFF, LANE, TA, TB, GOFF2, RW = 208, 209, 210, 211, 212, 213, 214, 215   # RW: row of this lane's first access
     PTL, PTS, STEP, SW, PTB, STEP2 = 64, 66, 68, 69, 70, 72   # scalar temporaries of the loop, free now
     e.comment("---- epilogue: dk_acc (+)= scale * dK, dv_acc (+)= dV, through LDS so that HBM sees whole rows")
     e.raw("s_nop 7")
@@ -422,6 +512,7 @@ def epilogue(e):
     e.raw(f"v_and_b32 {vr(TB)}, {LPR - 1}, {vr(LANE)}")
     e.raw(f"v_lshlrev_b32 {vr(TB)}, 4, {vr(TB)}")                        # byte column of this lane
     e.raw(f"v_add_u32 {vr(GOFF)}, {sr(SW)}, {vr(TA)}")
+    e.raw(f"v_mov_b32 {vr(RW)}, {vr(GOFF)}")
     e.raw(f"v_mul_lo_u32 {vr(GOFF)}, {vr(GOFF)}, {sr(STEP)}")
     e.raw(f"v_add_u32 {vr(GOFF)}, {vr(GOFF)}, {vr(TB)}")
     e.raw(f"v_lshrrev_b32 {vr(GOFF2)}, 1, {vr(GOFF)}")                   # the same in the bf16 copy
@@ -440,13 +531,27 @@ def epilogue(e):
     e.raw(f"s_lshr_b32 {sr(STEP2)}, {sr(STEP)}, 1")
 
     passes = [(nb, which) for nb in range(NKB) for which in ("k", "v")]
-    l_var = [e.label(f"epi{v}") for v in range(4)]
+    l_var = [e.label(f"epi{v}") for v in range(8)]         # 4 and up: a tile of fewer than 256 keys
     l_end = e.label("epi_end")
-    for v in (1, 2, 3):
+    e.raw(f"s_cmp_lg_u32 {sr(S_ROWS)}, 256")
+    e.raw(f"s_cselect_b32 {sr(T_MT)}, 4, 0")
+    e.raw(f"s_or_b32 {sr(S_FLAGS)}, {sr(S_FLAGS)}, {sr(T_MT)}")
+    for v in range(1, 8):
         e.raw(f"s_cmp_eq_u32 {sr(S_FLAGS)}, {v}")
         e.raw(f"s_cbranch_scc1 {l_var[v]}")
 
-    def body(assign, lowp):
+    def body(assign, lowp, ragged):
+        def rows_of(p, n):                              # only the lanes whose row of this access exists
+            if ragged:
+                e.raw(f"s_sub_i32 {sr(T_MT)}, {sr(S_ROWS)}, {32 * passes[p][0] + n * RPI}")
+                e.raw(f"v_cmp_gt_i32_e64 {sr(T_CMP[0], 2)}, {sr(T_MT)}, {vr(RW)}")
+                e.raw("s_nop 1")
+                e.raw(f"s_mov_b64 exec, {sr(T_CMP[0], 2)}")
+
+        def all_rows():
+            if ragged:
+                e.raw("s_mov_b64 exec, -1")
+
         vm, lgkm = InFlight(e, "vmcnt", 1000), InFlight(e, "lgkmcnt", 12)
 
         def pointer(ptr, p, bf16=False):
@@ -466,7 +571,9 @@ def epilogue(e):
         def loads(p):
             pointer(PTL, p)
             for n in range(NLD):
+                rows_of(p, n)
                 vm.issue(f"global_load_dwordx4 {vr(G(p, n), 4)}, {vr(GOFF)}, {sr(PTL, 2)}", ("ld", p, n))
+                all_rows()
                 step(PTL)
 
         deep = 1 if lowp else 2                         # passes the HBM reads run ahead (the wait counter holds 63)
@@ -506,6 +613,7 @@ def epilogue(e):
                 if n + ahead < NLD:
                     m = n + ahead
                     lgkm.issue(f"ds_read_b128 {vr(T(m), 4)}, {vr(LR)} offset:{region + m * RPI * RSL}", ("r", p, m))
+                rows_of(p, n)
                 vm.issue(f"global_store_dwordx4 {vr(GOFF)}, {vr(res, 4)}, {sr(PTS, 2)}", ("st", p, n))
                 step(PTS)
                 if lowp:
@@ -514,13 +622,14 @@ def epilogue(e):
                     e.raw(f"v_cvt_pk_bf16_f32 {vr(lo + 1)}, {vr(res + 2)}, {vr(res + 3)}")
                     vm.issue(f"global_store_dwordx2 {vr(GOFF2)}, {vr(lo, 2)}, {sr(PTB, 2)}", ("sb", p, n))
                     step(PTB, STEP2)
+                all_rows()
             if not assign and p + deep < len(passes):   # the registers just stored take the HBM values of a later pass
                 loads(p + deep)
 
-    for v in range(4):
+    for v in range(8):
         e.raw(l_var[v] + ":")
-        body(assign=bool(v & 1), lowp=bool(v & 2))
-        if v < 3:
+        body(assign=bool(v & 1), lowp=bool(v & 2), ragged=bool(v & 4))
+        if v < 7:
             e.raw(f"s_branch {l_end}")
     e.raw(l_end + ":")
 
@@ -528,6 +637,7 @@ def epilogue(e):
 def generate():
     e = Emitter()
     pool = Pool()
+    l_mask = e.label("mask")
     e.comment("---- prologue: stream state")
     for t, s_ in ((T_QPTR, S_QPTR), (T_QHEAD, S_QPTR), (T_DOPTR, S_DOPTR), (T_DOHEAD, S_DOPTR),
                   (T_LSEPTR, S_LSEPTR), (T_LSEHEAD, S_LSEPTR), (T_DLPTR, S_DLPTR), (T_DLHEAD, S_DLPTR),
@@ -545,14 +655,39 @@ def generate():
     for nb, krow in ((0, I_KROW0), (1, I_KROW1)):
         for ks in range(KS):
             e.raw(f"global_load_dwordx4 {vr(KF(nb, ks), 4)}, {vr(krow, 2)}, off offset:{32 * ks}")
-    e.comment("---- V tile of the workgroup (256 rows) to LDS: instruction 4 j + wave covers rows 16 j + 4 wave .. + 3")
+    e.comment("---- parameters")
+    e.raw(f"v_subrev_u32 {vr(TMP)}, {sr(S_LDS)}, {vr(I_STAT_L)}")        # 4 * lane
+    e.raw(f"v_lshlrev_b32 {vr(TMP)}, 3, {vr(TMP)}")
+    e.raw(f"s_lshl_b32 {sr(T_X)}, {sr(S_WAVE)}, 11")
+    e.raw(f"s_add_u32 {sr(T_X)}, {sr(T_X)}, {sr(S_LDS)}")
+    e.raw(f"s_add_u32 {sr(T_X)}, {sr(T_X)}, {PBLK}")
+    e.raw(f"v_add_u32 {vr(TMP)}, {sr(T_X)}, {vr(TMP)}")
+    e.raw(f"ds_read_b128 {vr(KFIRST(0), 4)}, {vr(TMP)}")
+    e.raw(f"ds_read_b96 {vr(DOOFFN, 3)}, {vr(TMP)} offset:16")
+    e.raw(f"s_add_u32 {sr(T_X)}, {sr(S_LDS)}, {PBLK + 256 * 32}")
+    e.raw(f"v_mov_b32 {vr(TMP)}, {sr(T_X)}")
+    e.raw(f"ds_read_b128 {vr(ST, 4)}, {vr(TMP)}")
+    e.raw(f"ds_read_b64 {vr(TMP, 2)}, {vr(TMP)} offset:16")
+    e.raw("s_waitcnt lgkmcnt(0)")
+    for src, dst in ((ST, S_NRAG), (ST + 1, S_DIAG), (ST + 2, S_GREC), (ST + 3, S_CI0), (TMP, S_SQ), (TMP + 1, S_ROWS)):
+        e.raw(f"v_readfirstlane_b32 {sr(dst)}, {vr(src)}")
+    e.raw(f"s_cmp_lg_u32 {sr(S_NRAG)}, -1")
+    e.raw(f"s_cselect_b32 {sr(S_EVT)}, -1, {sr(S_DIAG)}")
+    e.comment("---- V tile of the workgroup (256 rows, the last one that exists repeated) to LDS: instruction 4 j + wave covers rows 16 j + 4 wave .. + 3")
+    e.raw(f"s_sub_u32 {sr(T_X)}, {sr(S_ROWS)}, 1")
     for j in range(256 * ROW // 4096):
+        e.raw(f"v_min_u32 {vr(TMP)}, {sr(T_X)}, {vr(I_SROW)}")
+        e.raw(f"v_mul_lo_u32 {vr(TMP)}, {vr(TMP)}, {sr(S_VRS)}")
+        e.raw(f"v_add_u32 {vr(TMP)}, {vr(TMP)}, {vr(I_VCOL)}")
         e.raw(f"s_add_u32 m0, {sr(T_M0)}, {VT + 4096 * j}")
         e.raw("s_nop 0")
-        e.raw(f"global_load_lds_dwordx4 {vr(I_VOFF)}, {sr(T_VPTR, 2)}")
-        if j < 256 * ROW // 4096 - 1:
-            e.raw(f"s_add_u32 {sr(T_VPTR)}, {sr(T_VPTR)}, {sr(S_VRS16)}")
-            e.raw(f"s_addc_u32 {sr(T_VPTR + 1)}, {sr(T_VPTR + 1)}, 0")
+        e.raw(f"global_load_lds_dwordx4 {vr(TMP)}, {sr(T_VPTR, 2)}")
+        e.raw(f"v_add_u32 {vr(I_SROW)}, {4096 // ROW}, {vr(I_SROW)}")
+    l_here = e.label("here")                           # (in the registers of the V stream)
+    e.raw(f"s_getpc_b64 {sr(T_MASK, 2)}")
+    e.raw(l_here + ":")
+    e.raw(f"s_add_u32 {sr(T_MASK)}, {sr(T_MASK)}, {l_mask}-{l_here}")
+    e.raw(f"s_addc_u32 {sr(T_MASK + 1)}, {sr(T_MASK + 1)}, 0")
     e.comment("---- per-lane address registers")
     e.raw(f"v_mov_b32 {vr(QOFF)}, {vr(I_QOFF0)}")
     e.raw(f"v_mov_b32 {vr(DOOFF)}, {vr(I_DOOFF0)}")
@@ -561,7 +696,6 @@ def generate():
         e.raw(f"v_mov_b32 {vr(DOOFF + 1)}, {vr(I_DOOFF1)}")
     e.raw(f"v_mov_b32 {vr(STAT_G)}, {vr(I_STAT_G)}")
     e.raw(f"v_mov_b32 {vr(STAT_L)}, {vr(I_STAT_L)}")
-    e.raw(f"v_mov_b32 {vr(DKV_OFF)}, {vr(I_DKV)}")
     e.raw(f"v_mov_b32 {vr(NINF)}, 0xff800000")
     # g16 = lds_base + 16 * (lane / 32), from stat_l = lds_base + 4 * lane
     e.raw(f"v_subrev_u32 {vr(TMP)}, {sr(S_LDS)}, {vr(I_STAT_L)}")
@@ -583,7 +717,17 @@ def generate():
         e.raw(f"v_add_u32 {vr(TRHI + db)}, {vr(I_TRBASE)}, {vr(TMP)}")
         e.raw(f"v_add_u32 {vr(TRHI + db)}, {8 * ROW}, {vr(TRHI + db)}")
     e.comment("---- blocks 0 and 1 requested; accumulators to zero meanwhile")
+    def whole_from(blk):
+        """Requests of the prologue: block `blk` may be the first whole one behind a ragged one."""
+        l_still = e.label("still")
+        e.raw(f"s_cmp_lt_u32 {sr(T_DSTEP)}, {sr(S_NRAG)}")
+        e.raw(f"s_cbranch_scc1 {l_still}")
+        gen_whole_offsets(e)
+        e.raw(l_still + ":")
+
     for blk in range(2):
+        if blk:
+            whole_from(blk)
         for grp in request_code(blk, blk):
             for ln in grp:
                 e.raw(ln)
@@ -596,6 +740,7 @@ def generate():
     stat_publish(e, 0, 0, "stw")
     e.raw("s_waitcnt lgkmcnt(0)")
     e.ds = []
+    whole_from(2)
     for grp in request_code(2, 0):
         for ln in grp:
             e.raw(ln)
@@ -609,22 +754,45 @@ def generate():
         for fn in plans[0][k]:
             fn()
     e.need("0nd3")              # as at the end of a pass through the loop: the early statistics reads have completed
-    l_loop, l_done = e.label("loop"), e.label("done")
-    e.raw(l_loop + ":")
-    entry = list(e.ds)
-    entry_next = pool.next % NPOOL
-    for u in range(NS):
-        if u == NS - 1:
-            plans[NS] = plan_reads(e, pool, 0, NS)      # block 0 of the next pass
-        gen_step(e, pool, u, u, plans[u], plans[u + 1])
-        e.raw(f"s_sub_u32 {sr(T_REM)}, {sr(T_REM)}, 1")
-        e.raw(f"s_cmp_eq_u32 {sr(T_REM)}, 0")
-        if u < NS - 1:
-            e.raw(f"s_cbranch_scc1 {l_done}")
-        else:
-            e.raw(f"s_cbranch_scc0 {l_loop}")
+    l_done = e.label("done")
+    l_whole, l_masked = ([e.label(f"{x}{u}") for u in range(NS)] for x in ("whole", "masked"))
     strip = lambda tags: [t.lstrip("0123456789") for t in tags]
-    assert strip(e.ds) == strip(entry) and pool.next % NPOOL == entry_next, (e.ds, entry)
+    entry, entry_pool = list(e.ds), (pool.next, dict(pool.owner), dict(pool.uses_left), dict(pool.reg))
+    at = [(strip(entry), pool.next % NPOOL)]
+    e.raw(f"s_cmp_le_u32 {sr(T_REM)}, {sr(S_EVT)}")
+    e.raw(f"s_cbranch_scc1 {l_masked[0]}")
+    for masked in (False, True):
+        if masked:                                      # the same loop once more, from the same state
+            e.ds = list(entry)
+            pool.next, pool.owner, pool.uses_left, pool.reg = entry_pool[0], dict(entry_pool[1]), dict(entry_pool[2]), dict(entry_pool[3])
+        for u in range(NS):
+            e.raw((l_masked if masked else l_whole)[u] + ":")
+            assert (strip(e.ds), pool.next % NPOOL) == at[u], (e.ds, at[u])
+            if u == NS - 1:
+                plans[NS] = plan_reads(e, pool, 0, NS)  # block 0 of the next pass
+            gen_step(e, pool, u, u, plans[u], plans[u + 1], masked)
+            e.raw(f"s_sub_u32 {sr(T_REM)}, {sr(T_REM)}, 1")
+            if masked:
+                e.raw(f"s_cmp_eq_u32 {sr(T_REM)}, 0")
+                e.raw(f"s_cbranch_scc1 {l_done}")
+                e.raw(f"s_cmp_gt_u32 {sr(T_REM)}, {sr(S_EVT)}")
+                e.raw(f"s_cbranch_scc1 {l_whole[(u + 1) % NS]}")
+            else:
+                l_leave = e.label("leave")
+                LEAVE_STUBS.append((l_leave, l_masked[(u + 1) % NS]))
+                e.raw(f"s_cmp_le_u32 {sr(T_REM)}, {sr(S_EVT)}")
+                e.raw(f"s_cbranch_scc1 {l_leave}")
+            if not masked and u < NS - 1:
+                at.append((strip(e.ds), pool.next % NPOOL))
+        assert (strip(e.ds), pool.next % NPOOL) == at[0], (e.ds, at[0])
+        e.raw(f"s_branch {(l_masked if masked else l_whole)[0]}")
+    for l_leave, l_to in LEAVE_STUBS:                  # no whole block left: the end, or the diagonal
+        e.raw(l_leave + ":")
+        e.raw(f"s_cmp_lg_u32 {sr(T_REM)}, 0")
+        e.raw(f"s_cbranch_scc1 {l_to}")
+        e.raw(f"s_branch {l_done}")
+    e.raw(l_mask + ":")
+    gen_mask_routine(e)
     e.raw(l_done + ":")
     e.raw("s_waitcnt vmcnt(0) lgkmcnt(0)")
 

@@ -6,8 +6,9 @@
 
 Body of ONE `asm volatile` statement in st_bwd_dq_fast.hip.  A workgroup (4 wavefronts) owns 256 queries
 of one head, 64 per wavefront as two 32-query blocks, and walks 64-key tiles: first those that every one of its
-rows sees in full, then the S_NM that a mask edge crosses.  As in the forward, one scalar test per key block calls
-an out-of-line routine that puts -inf in place of the exponents of invisible pairs (P = 0, hence dS = 0); the
+rows sees in full, then the S_NM that a mask edge crosses.  As in the forward the loop exists twice, without and with
+a test in every key block that calls an out-of-line routine, which puts -inf in place of the exponents of invisible
+pairs (P = 0, hence dS = 0); the
 ragged end of a chunk is read as its last 64 rows, and rows beyond the shard are neither read nor written back.
 The result is added to dq_acc, or, where the walk is split over workgroups, stored as a partial sum.
 The MFMA C layout is "lane = query column", so lse and Delta are one register per lane and block.
@@ -210,7 +211,7 @@ def gen_mask_routine(e, kb):
     e.raw(f"s_setpc_b64 {sr(T_MRET, 2)}")
 
 
-def gen_block(p, cur, nxt, nxt2, pbuf, seq, do_b=True, do_ac=True, head=None, prefetched=True, side=None):
+def gen_block(p, cur, nxt, nxt2, pbuf, seq, do_b=True, do_ac=True, head=None, prefetched=True, side=None, masked=True):
     """cur / nxt / nxt2 = (stage, kb) of blocks i, i+1, i+2 (nxt2 only for the prefetch at the tail).
     pbuf = score buffer that holds P(i); S(i+1) goes to the other one.  `head` is emitted in front of the
     first MFMA (barrier and DMA of a new tile).  seq numbers the block for fragment tags: tags of block
@@ -318,7 +319,7 @@ def gen_block(p, cur, nxt, nxt2, pbuf, seq, do_b=True, do_ac=True, head=None, pr
             for ln in side[k]:
                 e.raw(ln)
             units += 2
-        if do_ac and k == early1:                        # before the first exponential of the new block
+        if do_ac and masked and k == early1:                        # before the first exponential of the new block
             mask_test(e, S_NM1 if do_b and cur[1] == 1 else S_NM, nbuf)
         while vi[0] < len(valu) and valu[vi[0]][0] <= k and units + valu[vi[0]][3] <= BUDGET:
             units += emit_valu(valu[vi[0]])
@@ -469,32 +470,55 @@ def generate():
     e.comment("pipeline fill: S^T, P and dP' of block (0, 0)")
     gen_block(p, None, (0, 0), (0, 1), 1, 0, do_b=False, prefetched=False)
 
-    l_loop, l_done = e.label("loop"), e.label("done")
-    drains = []
-    e.raw(l_loop + ":")
-    loop_entry = list(e.ds)
-    seq = 1
-    for u in range(NS):
-        un = (u + 1) % NS
+    l_done = e.label("done")
+    l_loop, l_top = e.label("loop"), e.label("masked_top")
+    l_mid = [e.label(f"masked_mid{u}") for u in range(NS)]
+    strip = lambda tags: [t.split("_", 1)[1] for t in tags]
+    state = lambda: (list(e.ds), dict(p.frag_reg), dict(p.uses_left), dict(p.owner))
 
-        def head(u=u):
+    def first_half(u, seq, masked):
+        def head():
             # tile T + 1 has landed everywhere and nobody reads tile T - 1 any more: tile T + 3 may be requested
             e.raw(f"s_waitcnt vmcnt({2 * NDMA})")
             e.raw("s_barrier")
         side = {k: grp for k, grp in enumerate(dma_groups((u + 3) % NS))}
         side[2 * NDMA] = advance_lines(e)
         # the head sits between the tail prefetch of the block before and this block's first MFMA
-        gen_block(p, (u, 0), (u, 1), (un, 0), 0, seq, head=head, side=side)
-        seq += 1
+        gen_block(p, (u, 0), (u, 1), ((u + 1) % NS, 0), 0, seq, head=head, side=side, masked=masked)
+
+    def second_half(u, seq, masked):
+        un = (u + 1) % NS
+        gen_block(p, (u, 1), (un, 0), (un, 1), 1, seq, masked=masked)
+        e.raw(f"s_sub_u32 {sr(T_REM)}, {sr(T_REM)}, 1")
+
+    drains = []
+    e.comment("---- whole tiles (the first block of a tile prepares its second one, the second one the next tile's first)")
+    e.raw(f"s_cmp_le_u32 {sr(T_REM)}, {sr(S_NM)}")
+    e.raw(f"s_cbranch_scc1 {l_top}")
+    e.raw(l_loop + ":")
+    start, at = state(), [strip(e.ds)]
+    for u in range(NS):
+        first_half(u, 1 + 2 * u, False)
+        e.raw(f"s_cmp_le_u32 {sr(T_REM)}, {sr(S_NM1)}")
+        e.raw(f"s_cbranch_scc1 {l_mid[u]}")
+        at.append(strip(e.ds))
+        second_half(u, 2 + 2 * u, False)
+    assert strip(e.ds) == at[0], (e.ds, at[0])
+    e.raw(f"s_branch {l_loop}")
+    e.comment("---- the last ones")
+    e.ds, p.frag_reg, p.uses_left, p.owner = (type(x)(x) for x in start)
+    e.raw(l_top + ":")
+    for u in range(NS):
+        first_half(u, 1 + 2 * u, True)
+        e.raw(l_mid[u] + ":")
+        assert strip(e.ds) == at[1 + u], (e.ds, at[1 + u])
         l_drain = e.label("drain")
         e.raw(f"s_cmp_eq_u32 {sr(T_REM)}, 1")
         e.raw(f"s_cbranch_scc1 {l_drain}")
-        drains.append((l_drain, u, list(e.ds), dict(p.frag_reg), dict(p.uses_left), dict(p.owner), seq))
-        gen_block(p, (u, 1), (un, 0), (un, 1), 1, seq)
-        seq += 1
-        e.raw(f"s_sub_u32 {sr(T_REM)}, {sr(T_REM)}, 1")
-    assert [t.split("_", 1)[1] for t in e.ds] == [t.split("_", 1)[1] for t in loop_entry], (e.ds, loop_entry)
-    e.raw(f"s_branch {l_loop}")
+        drains.append((l_drain, u, *state(), 2 + 2 * u))
+        second_half(u, 2 + 2 * u, True)
+    assert strip(e.ds) == at[0], (e.ds, at[0])
+    e.raw(f"s_branch {l_top}")
     for l_drain, u, ds, fr, ul, ow, sq in drains:
         e.raw(l_drain + ":")
         e.ds, p.frag_reg, p.uses_left, p.owner = list(ds), dict(fr), dict(ul), dict(ow)

@@ -10,9 +10,10 @@ one head, 64 per wavefront as two 32-query blocks, and walks 64-key tiles: first
 its rows sees in full, then the ones that a mask edge crosses (the causal diagonal, the ragged end of a chunk).
 It writes O = acc / l, lse and, where asked for, O rounded to bf16; query rows beyond the shard are not stored.
 
-Masked tiles are the last S_NM of the walk, so the loop only compares its count-down with that number, one
-scalar test per 32-key block; the mask itself is an out-of-line routine that overwrites the invisible exponents
-with -inf before their maximum is taken.  A tile hidden from none of its columns costs nothing more than before.
+Masked tiles are the last S_NM of the walk.  The loop exists twice: the first copy has no masks and leaves for the
+second where a block of a masked tile comes up (the compare that ends a loop without masks does it, so whole tiles
+pay nothing; a test of its own in every 32-key block cost 1.4 % at head size 64); the second copy tests every block
+and calls an out-of-line routine that overwrites the invisible exponents with -inf before their maximum is taken.
 The ragged end of a chunk is read as the chunk's last 64 rows, with the rows of the tile before it masked, so no
 load leaves the chunk.  Where no tile is visible to all rows, a row may meet its first visible key late: its
 reference starts at zero and is set to its first finite block maximum by the mask routine (its accumulators are
@@ -199,7 +200,7 @@ def valu_exp(sbuf, pbuf):
     return out
 
 
-def gen_iter(p, cur, nxt, nxt2, par, seq, do_a=True, do_valu=True, head=None, prefetch=True, side=None):
+def gen_iter(p, cur, nxt, nxt2, par, seq, do_a=True, do_valu=True, head=None, prefetch=True, side=None, masked=False):
     """Block i = cur, i+1 = nxt (its V^T is prefetched at the tail), i+2 = nxt2 (its K feeds group A).
     par = i % 2: P(i) sits in P buffer par, S(i+1) in score buffer 1 - par, S(i+2) goes to score buffer par."""
     e = p.e
@@ -258,7 +259,7 @@ def gen_iter(p, cur, nxt, nxt2, par, seq, do_a=True, do_valu=True, head=None, pr
             for ln in side[k]:
                 e.raw(ln)
             units += 2
-        if do_valu and k == 3:
+        if do_valu and masked and k == 3:
             mask_test(e, S_NM1 if par else S_NM, 1 - par)
         if do_valu:
             # S(i+1) was written by the last group of the block before: first reader three MFMA issues later
@@ -592,37 +593,55 @@ def generate():
     for db in range(2):
         read_vt(p, (0, 0), 0, db, 0)
 
-    l_loop, l_done = e.label("loop"), e.label("done")
-    e.raw(l_loop + ":")
-    loop_entry = list(e.ds)
-    drains = []
-    seq = 0
+    l_done = e.label("done")
+    l_loop = e.label("loop")
+    l_masked = [e.label(f"masked{u}") for u in range(NS)]
+    strip = lambda tags: [t.split("_", 1)[1] for t in tags]
     leftover = 0
-    for u in range(NS):
-        un = (u + 1) % NS
-        l_drain = e.label("drain")
-        e.raw(f"s_cmp_eq_u32 {sr(T_REM)}, 1")
-        e.raw(f"s_cbranch_scc1 {l_drain}")
-        drains.append((l_drain, u, p.snapshot(), seq))
 
-        def head(u=u):
+    def tile(u, seq, masked):
+        nonlocal leftover
+        un = (u + 1) % NS
+
+        def head():
             # tile T + 1 has landed everywhere and nobody reads tile T - 1 any more: tile T + 3 may be requested
             e.raw(f"s_waitcnt vmcnt({2 * NDMA})")
             e.raw("s_barrier")
         side = {k: grp for k, grp in enumerate(dma_groups((u + 3) % NS))}
         side[2 * NDMA] = advance_lines(e)
-        leftover += gen_iter(p, (u, 0), (u, 1), (un, 0), 0, seq, head=head, side=side)
-        seq += 1
-        leftover += gen_iter(p, (u, 1), (un, 0), (un, 1), 1, seq)
-        seq += 1
+        leftover += gen_iter(p, (u, 0), (u, 1), (un, 0), 0, seq, head=head, side=side, masked=masked)
+        leftover += gen_iter(p, (u, 1), (un, 0), (un, 1), 1, seq + 1, masked=masked)
         e.raw(f"s_sub_u32 {sr(T_REM)}, {sr(T_REM)}, 1")
-    assert [t.split("_", 1)[1] for t in e.ds] == [t.split("_", 1)[1] for t in loop_entry], (e.ds, loop_entry)
+
+    e.comment("---- tiles T with T and T + 1 whole")
+    e.raw(l_loop + ":")
+    start = p.snapshot()
+    at = []
+    for u in range(NS):
+        e.raw(f"s_cmp_le_u32 {sr(T_REM)}, {sr(S_NM1)}")
+        e.raw(f"s_cbranch_scc1 {l_masked[u]}")
+        at.append(strip(e.ds))
+        tile(u, 2 * u, False)
+    assert strip(e.ds) == at[0], (e.ds, at[0])
     e.raw(f"s_branch {l_loop}")
+    e.comment("---- the last ones")
+    p.restore(start)
+    drains = []
+    for u in range(NS):
+        e.raw(l_masked[u] + ":")
+        assert strip(e.ds) == at[u], (e.ds, at[u])
+        l_drain = e.label("drain")
+        e.raw(f"s_cmp_eq_u32 {sr(T_REM)}, 1")
+        e.raw(f"s_cbranch_scc1 {l_drain}")
+        drains.append((l_drain, u, p.snapshot(), 2 * u))
+        tile(u, 2 * u, True)
+    assert strip(e.ds) == at[0], (e.ds, at[0])
+    e.raw(f"s_branch {l_masked[0]}")
     for l_drain, u, snap, sq in drains:
         e.raw(l_drain + ":")
         p.restore(snap)
         # the last tile: its second block still needs its softmax, nothing beyond it exists
-        gen_iter(p, (u, 0), (u, 1), None, 0, sq, do_a=False)
+        gen_iter(p, (u, 0), (u, 1), None, 0, sq, do_a=False, masked=True)
         e.raw("s_nop 7")                 # the exponentials above were not hidden under a second MFMA group
         gen_iter(p, (u, 1), None, None, 1, sq + 1, do_a=False, do_valu=False, prefetch=False)
         e.raw(f"s_branch {l_done}")

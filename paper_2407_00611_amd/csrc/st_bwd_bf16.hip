@@ -1,13 +1,16 @@
-// bf16 backward of one GPU's ring-attention share, as two deterministic kernels (no atomics):
+// bf16 backward of one GPU's ring-attention share, as two deterministic kernels (no atomics), and their launcher.  The
+// hand-scheduled kernels (st_bwd_dq_fast.hip, st_bwd_dkv_fast.hip) take every launch they are built for; the general ones
+// here take the rest (calls without a workspace for Q', chunks of fewer than 64 keys in the dQ pass, strides beyond 32-bit
+// offsets) and short dQ walks.
 //
-//   dq kernel   (query-stationary, mirrors the forward):  a workgroup owns 256 queries of one head
+//   dq kernel   (query-stationary, mirrors the forward):  a workgroup owns 128 queries of one head
 //               and walks the KV chunks; per 64-key tile
 //                 S^T  = K Q^T,  dP^T = V dO^T            (K, V fragments from LDS; Q, dO in registers)
 //                 dS^T = exp(S^T - lse) o (dP^T - Delta)  (lane owns one query column)
 //                 dQ^T += K^T dS^T                        (K^T by LDS transpose reads)
-//   dkv kernel  (key-stationary): a workgroup owns 256 keys of one KV head of one chunk (64 per
+//   dkv kernel  (key-stationary): a workgroup owns 128 keys of one KV head of one chunk (32 per
 //               wavefront, K and V fragments resident in registers) and walks the query heads of
-//               the group and their 64-query tiles
+//               the group and their 32-query tiles
 //                 S  = Q K^T,  dP = dO V^T,  P = exp(S - lse),  dS = P o (dP - Delta)
 //                 dV^T += dO^T P,  dK^T += Q^T dS         (dO^T, Q^T by LDS transpose reads)
 //
@@ -256,20 +259,6 @@ __global__ __launch_bounds__(256, 1) void bwd_dkv_bf16_kernel(const BwdArgs a) {
   const int q_tile_first = wg_i0 / kK_BQ;
   const int n_q_tiles = (s.Sq + kK_BQ - 1) / kK_BQ;
   if (q_tile_first >= n_q_tiles) return;
-  // Query blocks of this workgroup: [q_tile_first, q_split) and [q_resume, n_q_tiles).  The gap, if any,
-  // belongs to the fast kernel (full blocks that see every key of the enclosing full 256-key tile).
-  int q_split = n_q_tiles, q_resume = n_q_tiles;
-  if (a.dkv_fast && kK_BQ == kDkvFastRows) {
-    const int tile_key0 = wg_key0 / kDkvFastKeys * kDkvFastKeys;
-    if (tile_key0 + kDkvFastKeys <= s.Sk) {
-      const int fb = dkv_fast_first_block(s, k0, tile_key0), n_full = s.Sq / kDkvFastRows;
-      if (fb < n_full) {
-        q_split = fb > q_tile_first ? fb : q_tile_first;
-        q_resume = n_full;
-      }
-    }
-  }
-
   // resident K, V fragments (B operands, column = key)
   const char* kbase = (const char*)a.t.k[c] + ((int64_t)b * a.t.ksb + (int64_t)hk * a.t.ksh) * 2;
   const char* vbase = (const char*)a.t.v[c] + ((int64_t)b * a.t.vsb + (int64_t)hk * a.t.vsh) * 2;
@@ -298,14 +287,9 @@ __global__ __launch_bounds__(256, 1) void bwd_dkv_bf16_kernel(const BwdArgs a) {
   constexpr float c_exp = 1.f;   // the Q operand is Q' = bf16(Q scale log2 e): the scores are exponents already
 
   // flattened (head of the group, query tile) walk
-  const int n_head_lo = q_split - q_tile_first;
-  const int tiles_per_head = n_head_lo + (n_q_tiles - q_resume);
-  if (tiles_per_head <= 0) return;
+  const int tiles_per_head = n_q_tiles - q_tile_first;
   const int n_steps = G * tiles_per_head;
-  auto tile_of = [&](int step) -> int {
-    const int j = step % tiles_per_head;
-    return j < n_head_lo ? q_tile_first + j : q_resume + (j - n_head_lo);
-  };
+  auto tile_of = [&](int step) -> int { return q_tile_first + step % tiles_per_head; };
   StageRegs<D, kK_BQ> rq, rdo;
   float stat_reg = 0.f;   // threads 0..63: lse2 of row tid; threads 64..127: delta of row tid-64
   auto issue_load = [&](int step) {
@@ -468,7 +452,7 @@ hipError_t launch_bwd_bf16(const BwdArgs& a_in, hipStream_t stream) {
   const int64_t total_k = (int64_t)n_kt * a.s.Hkv * a.s.B * a.t.n;
   if (total_q > 0x7fffffff || total_k > 0x7fffffff) return hipErrorInvalidValue;
   if (a.s.D != 128 && a.s.D != 64) return hipErrorInvalidValue;
-  a.dkv_fast = (knobs().dkv_fast && dkv_fast_usable(a)) ? 1 : 0;
+  const bool dkv_fast = knobs().dkv_fast && dkv_fast_usable(a);
   if (a.s.causal) {
     // earlier chunks first (the backward does not depend on the order of the table): their keys are seen by
     // more query rows, and workgroups are handed out in table order
@@ -485,63 +469,37 @@ hipError_t launch_bwd_bf16(const BwdArgs& a_in, hipStream_t stream) {
         a.kv_assign = (a.kv_assign & ~((1ull << j) | (1ull << (j - 1)))) | (bi << j) | (bj << (j - 1));
       }
   }
-  // Assignment and bf16 copies can be left to the fast dK/dV kernel for the chunks it alone writes: full tiles
-  // only, every query row sees every key.  Every other chunk is zeroed here first (then added to as usual) and
-  // cast by a launch of its own at the end.
-  const int64_t n_kv = (int64_t)a.s.B * a.s.Sk * a.s.Hkv * a.s.D;
-  void* cast_dk[kMaxTable];
-  void* cast_dv[kMaxTable];
-  for (int c = 0; c < a.t.n; ++c) {
-    cast_dk[c] = cast_dv[c] = nullptr;
-    const bool fast_only = a.dkv_fast && dkv_chunk_fast_only(a.s, a.t.k_offset[c]);
-    if (fast_only && ((a.dk_lowp[c] == nullptr) == (a.dv_lowp[c] == nullptr))) continue;
-    if ((a.kv_assign >> c) & 1) {
-      hipError_t ez = launch_zero(a.dk[c], n_kv * (int64_t)sizeof(float), stream);
-      if (ez == hipSuccess) ez = launch_zero(a.dv[c], n_kv * (int64_t)sizeof(float), stream);
-      if (ez != hipSuccess) return ez;
-      a.kv_assign &= ~(1ull << c);
-    }
-    cast_dk[c] = a.dk_lowp[c];
-    cast_dv[c] = a.dv_lowp[c];
-    a.dk_lowp[c] = a.dv_lowp[c] = nullptr;
-  }
   hipError_t e = hipSuccess;
-  {
-    // With the fast kernel on, the general one only has the masked and ragged blocks left: chunks whose every
-    // block is the fast kernel's (dkv_chunk_fast_only) are left out of its grid, which would otherwise consist
-    // mostly of workgroups that find nothing to do.
-    BwdArgs g = a;
-    if (a.dkv_fast) {
-      g.t.n = 0;
-      for (int c = 0; c < a.t.n; ++c) {
-        if (dkv_chunk_fast_only(a.s, a.t.k_offset[c])) continue;
-        g.t.k[g.t.n] = a.t.k[c];
-        g.t.v[g.t.n] = a.t.v[c];
-        g.t.k_offset[g.t.n] = a.t.k_offset[c];
-        g.dk[g.t.n] = a.dk[c];
-        g.dv[g.t.n] = a.dv[c];
-        ++g.t.n;
-      }
-    }
-    if (g.t.n > 0) {
-      ProfScope prof(a.dkv_fast ? "bwd_dkv_edge" : "bwd_dkv_bf16", stream);
-      const unsigned grid = (unsigned)((int64_t)n_kt * a.s.Hkv * a.s.B * g.t.n);
-      if (a.s.D == 128) hipLaunchKernelGGL(bwd_dkv_bf16_kernel<128>, dim3(grid), dim3(256), 0, stream, g);
-      else hipLaunchKernelGGL(bwd_dkv_bf16_kernel<64>, dim3(grid), dim3(256), 0, stream, g);
-      e = hipGetLastError();
-    }
-  }
-  if (e != hipSuccess) return e;
-  if (a.dkv_fast) {
+  if (dkv_fast) {
     e = launch_bwd_dkv_fast(a, stream);
     if (e != hipSuccess) return e;
-  }
-  for (int c = 0; c < a.t.n; ++c) {
-    if (cast_dk[c]) e = launch_cast(a.dk[c], cast_dk[c], n_kv, ST_BF16, stream);
-    if (e == hipSuccess && cast_dv[c]) e = launch_cast(a.dv[c], cast_dv[c], n_kv, ST_BF16, stream);
+  } else {
+    // the general kernel only adds: chunks to be assigned are zeroed first, bf16 copies are launches of their own
+    const int64_t n_kv = (int64_t)a.s.B * a.s.Sk * a.s.Hkv * a.s.D;
+    for (int c = 0; c < a.t.n && e == hipSuccess; ++c)
+      if ((a.kv_assign >> c) & 1) {
+        e = launch_zero(a.dk[c], n_kv * (int64_t)sizeof(float), stream);
+        if (e == hipSuccess) e = launch_zero(a.dv[c], n_kv * (int64_t)sizeof(float), stream);
+      }
+    if (e != hipSuccess) return e;
+    {
+      ProfScope prof("bwd_dkv_bf16", stream);
+      if (a.s.D == 128) hipLaunchKernelGGL(bwd_dkv_bf16_kernel<128>, dim3((unsigned)total_k), dim3(256), 0, stream, a);
+      else hipLaunchKernelGGL(bwd_dkv_bf16_kernel<64>, dim3((unsigned)total_k), dim3(256), 0, stream, a);
+      e = hipGetLastError();
+    }
+    for (int c = 0; c < a.t.n && e == hipSuccess; ++c) {
+      if (a.dk_lowp[c]) e = launch_cast(a.dk[c], a.dk_lowp[c], n_kv, ST_BF16, stream);
+      if (e == hipSuccess && a.dv_lowp[c]) e = launch_cast(a.dv[c], a.dv_lowp[c], n_kv, ST_BF16, stream);
+    }
     if (e != hipSuccess) return e;
   }
-  if (knobs().dq_fast && dq_fast_usable(a)) {
+  // A walk of a few tiles ends before the hand-scheduled loop has made up for its prologue (head size 128: one 64-key tile
+  // 14.1 against 10.5 us on the general kernel, five 26.9 against 20.9, eight 23.2 against 23.7, 64 tiles 106 against 137;
+  // head size 64: 11.2 against 8.7, 17.7 against 15.3, 15.6 against 17.7, 61 against 94).  The dK/dV loop is the faster one
+  // from the first block on.
+  const bool few = a.n_split <= 1 && (int64_t)a.t.n * ((a.s.Sk + kDqFastKeys - 1) / kDqFastKeys) <= 6;
+  if (knobs().dq_fast && !few && dq_fast_usable(a)) {
     e = launch_bwd_dq_fast(a, stream);
     if (e == hipSuccess && a.n_split > 1)
       e = launch_add_parts(a.dq, a.dq_part, a.n_split, a.part_stride, (int64_t)a.s.B * a.s.Sq * a.s.Hq * a.s.D, stream);

@@ -84,16 +84,14 @@ struct BwdArgs {
   float* dq;           // fp32 [B,Sq,Hq,D], +=
   float* dk[kMaxTable];  // fp32 [B,Sk,Hkv,D] per table entry, +=
   float* dv[kMaxTable];
-  int32_t dkv_fast;    // 1: the fast dK/dV kernel runs too and owns the blocks dkv_fast_first_block describes
   // Under-filled dQ launches of the hand-scheduled kernel: n_split > 1 gives every query tile n_split workgroups
   // (blockIdx.y), each storing the sum over its share of the tiles at dq_part + y * part_stride (floats, laid out as dq);
   // the launcher then adds them to dq in order.
   int32_t n_split;
   float* dq_part;
   int64_t part_stride;
-  // dK / dV work of a chunk's last visit folded into the launch (bf16 path).  On entry to launch_bwd_bf16 they
-  // state what the caller wants for every table entry; the launcher keeps them for the entries whose every
-  // block belongs to the fast kernel (their only writer) and serves the others with fill / cast launches.
+  // dK / dV work of a chunk's last visit folded into the launch (bf16 path): the hand-scheduled kernel's epilogue does it,
+  // beside the general kernel the launcher runs fill and cast launches
   uint64_t kv_assign;          // bit c: dk[c] / dv[c] are overwritten, not added to
   void* dk_lowp[kMaxTable];    // nullable per entry: the final dk[c] / dv[c] rounded to bf16, dense [B,Sk,Hkv,D]
   void* dv_lowp[kMaxTable];
@@ -117,27 +115,9 @@ struct CombineArgs {
   void* o_lowp;      // nullable, [B,Sq_out,Hq,D]
 };
 
-// Split of the dK/dV work between the general kernel and the fast one (head_dim 128): the fast kernel
-// takes, for every FULL tile of kDkvFastKeys keys, the full kDkvFastRows-query blocks from the first one
-// whose rows all see the tile's last key; everything else (masked blocks, ragged tails) stays general.
+// Tile of the hand-scheduled dK/dV kernel
 constexpr int kDkvFastKeys = 256;
 constexpr int kDkvFastRows = 32;
-__host__ __device__ inline int dkv_fast_first_block(const Shape& s, int64_t k0, int tile_key0) {
-  if (!s.causal) return 0;
-  const int d = q_row_of(s, k0 + tile_key0 + kDkvFastKeys - 1);     // first row index that sees the last key
-  return (d + kDkvFastRows - 1) / kDkvFastRows;
-}
-
-// True when the fast dK/dV kernel alone works on a chunk of full tiles: every query row sees either all of the
-// chunk's keys or none of them, and the rows that see it start at a block boundary, so no block needs a mask.
-// (With one run of rows these are the chunks that end before the shard begins; with two runs also the chunks
-// that lie between the two.)
-__host__ __device__ inline bool dkv_chunk_fast_only(const Shape& s, int64_t k0) {
-  if (s.Sk % kDkvFastKeys != 0 || s.Sq % kDkvFastRows != 0) return false;
-  if (!s.causal) return true;
-  const int r_any = q_row_of(s, k0), r_all = q_row_of(s, k0 + s.Sk - 1);
-  return r_any == r_all && r_all % kDkvFastRows == 0 && r_all < s.Sq;
-}
 
 // Tuning and testing switches of the launchers.  The defaults are the product.  They are read from the
 // environment ONCE, when the library is loaded (ST_FWD_FAST, ST_DQ_FAST, ST_DKV_FAST, ST_DKV_QUEUE, ST_FWD_WQ,
