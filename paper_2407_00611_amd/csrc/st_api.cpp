@@ -168,6 +168,60 @@ st_status check_ring(const st_ring_desc* d, const st_tensor* q, const int32_t* o
   return check_tensor("q", q, d->dtype, (int64_t)d->B * d->Sq * d->Hq * d->D);
 }
 
+constexpr int kMaxSplits = 16;
+
+// Workgroups per tile of a backward launch over n chunks that have rows to see them, and the bytes of partial sums that
+// takes (the two passes run one after the other and share them).
+struct BwdSplit {
+  int dq = 1, kv = 1;
+  size_t bytes = 0;
+};
+// dQ: the forward's model (rounds of workgroups x time of one + the pass that adds up); a 256 x 64 tile is three
+// contractions instead of two: 2.4 us at head size 128, 1.4 at 64.
+// dK/dV: a step (256 keys x 32 rows of one head) is 1.2 us at head size 128 and 0.75 at 64, prologue and epilogue 20 and 14;
+// grouped heads make the walk long and the key tiles few (4096 x 4096, 32/8 heads: 128 workgroups of 512 steps on 256
+// compute units, 570 us; 310 us as two shares of 256 steps and a 25 us pass).  512 tiles and more go through the queue.
+BwdSplit bwd_splits(const st::Shape& s, int dtype, int n, size_t room, bool split_dq = true) {
+  BwdSplit r;
+  if (dtype != ST_BF16 || (s.D != 128 && s.D != 64) || n < 1 || n > st::kMaxTable || s.B < 1 || s.Sq < 1 || s.Sk < 1 || s.Hq < 1 || s.Hkv < 1) return r;
+  const bool d128 = s.D == 128;
+  const int64_t wgs = (int64_t)s.B * s.Hq * ((s.Sq + st::kQTileFastRows - 1) / st::kQTileFastRows);
+  if (split_dq && wgs < 512 && s.Sk >= st::kQTileFastKeys) {
+    const int64_t tiles = (int64_t)n * ((s.Sk + st::kQTileFastKeys - 1) / st::kQTileFastKeys);
+    const size_t n_o = (size_t)st::dq_part_floats(s) * sizeof(float);
+    const double tile_us = d128 ? 2.4 : 1.4, fixed_us = 10, state_us = (double)n_o / 4e6;
+    double best = (double)((wgs + 255) / 256) * (fixed_us + tiles * tile_us);
+    for (int x = 2; x <= kMaxSplits && x <= tiles && (size_t)x * n_o <= room; ++x) {
+      const double t = (double)((wgs * x + 255) / 256) * (fixed_us + (double)((tiles + x - 1) / x) * tile_us) + 6 + (x + 2) * state_us;
+      if (t < 0.95 * best) {
+        best = t;
+        r.dq = x;
+        r.bytes = (size_t)x * n_o;
+      }
+    }
+  }
+  const int64_t key_tiles = (int64_t)s.B * s.Hkv * n * ((s.Sk + st::kDkvFastKeys - 1) / st::kDkvFastKeys);
+  if (key_tiles < 512) {
+    const int64_t blocks = (s.Sq + st::kDkvFastRows - 1) / st::kDkvFastRows, G = s.Hq / s.Hkv;
+    const size_t kv = 2 * (size_t)n * st::kv_part_floats(s) * sizeof(float);
+    const double step_us = d128 ? 1.2 : 0.75, fixed_us = d128 ? 20 : 14;
+    double best = (double)((key_tiles + 255) / 256) * (fixed_us + blocks * G * step_us);
+    for (int x = 2; x <= kMaxSplits && x <= blocks && (size_t)(x - 1) * kv <= room; ++x) {
+      const double t = (double)((key_tiles * x + 255) / 256) * (fixed_us + (double)((blocks + x - 1) / x) * G * step_us) + 6 + 2 * x * (double)kv / 4e6;
+      if (t < 0.95 * best) {
+        best = t;
+        r.kv = x;
+        if ((size_t)(x - 1) * kv > r.bytes) r.bytes = (size_t)(x - 1) * kv;
+      }
+    }
+  }
+  return r;
+}
+void set_splits(st::BwdArgs& a, const BwdSplit& x, void* parts) {
+  a.n_split = x.dq;
+  a.kv_split = x.kv;
+  a.parts = (float*)parts;
+}
 void set_table_strides(st::ChunkTable& t, const st_ring_desc* d) {
   t.ksb = d->k_stride_b; t.kss = d->k_stride_s; t.ksh = d->k_stride_h;
   t.vsb = d->v_stride_b; t.vss = d->v_stride_s; t.vsh = d->v_stride_h;
@@ -380,9 +434,14 @@ st_status st_attn_delta(const st_block_desc* d, const st_tensor* d_o, const st_t
   return ST_OK;
 }
 
+// Q' = bf16(Q scale log2 e), then room for the partial sums of an under-filled dK/dV launch (which runs unsplit without it).
+// The dQ of this call is the same with and without a workspace, bit for bit, so that pass is never split here.
+static size_t block_base_bytes(const st_block_desc* d) { return align_up((size_t)d->B * d->Sq * d->Hq * d->D * 2, 256); }
+constexpr size_t kBlockPartsMost = (size_t)64 << 20;
+
 size_t st_attn_block_bwd_workspace_bytes(const st_block_desc* d) {
   if (d == nullptr || d->dtype != ST_BF16 || d->B <= 0 || d->Sq <= 0 || d->Hq <= 0 || d->D <= 0) return 0;
-  return align_up((size_t)d->B * d->Sq * d->Hq * d->D * 2, 256);     // Q' = bf16(Q scale log2 e)
+  return block_base_bytes(d) + bwd_splits(shape_of(d), d->dtype, 1, kBlockPartsMost, false).bytes;
 }
 
 st_status st_attn_block_bwd(const st_block_desc* d, const st_tensor* q, const st_tensor* k, const st_tensor* v,
@@ -415,10 +474,12 @@ st_status st_attn_block_bwd(const st_block_desc* d, const st_tensor* q, const st
   a.t.vsb = v->stride_b; a.t.vss = v->stride_s; a.t.vsh = v->stride_h;
   a.lse = lse_final; a.delta = delta; a.dq = dq_acc; a.dk[0] = dk_acc; a.dv[0] = dv_acc;
   if (d->dtype == ST_BF16 && workspace != nullptr) {
-    if (workspace_bytes < st_attn_block_bwd_workspace_bytes(d)) return fail(ST_ERR_WORKSPACE, "block backward workspace needs %zu bytes", st_attn_block_bwd_workspace_bytes(d));
+    if (workspace_bytes < block_base_bytes(d)) return fail(ST_ERR_WORKSPACE, "block backward workspace needs %zu bytes", st_attn_block_bwd_workspace_bytes(d));
     if (reinterpret_cast<uintptr_t>(workspace) % 256) return fail(ST_ERR_ALIGNMENT, "workspace: not 256-byte aligned");
     ST_HIP(st::launch_scale_q(a.q, workspace, d->B, d->Sq, d->Hq, d->D, d->scale, (hipStream_t)hip_stream), "scaled-Q launch");
     a.qs = workspace;
+    const size_t left = workspace_bytes - block_base_bytes(d);
+    set_splits(a, bwd_splits(a.s, d->dtype, 1, left < kBlockPartsMost ? left : kBlockPartsMost, false), (char*)workspace + block_base_bytes(d));
   }
   ST_HIP(launch_bwd(d->dtype, a, (hipStream_t)hip_stream), "st_attn_block_bwd launch");
   return ST_OK;
@@ -504,7 +565,6 @@ st_status st_schedule_report(int32_t P, int32_t C, int64_t B, int64_t N, int64_t
 // constants are measured: a 256 x 64 bf16 tile 1.6 us at head size 128 and 0.95 us at 64, 8 us of prologue and epilogue,
 // 6 us for the launch of the combine pass, which moves 4 TB/s on states this small.  fp32: a 32-key tile is 64 D cycles of
 // a SIMD's matrix unit, and eight wavefronts on four SIMDs share the keys.
-constexpr int kMaxSplits = 16;
 static int fwd_splits(const st_ring_desc* d, int n_visible) {
   const bool bf16 = d->dtype == ST_BF16;
   if (n_visible < 1 || n_visible > st::kMaxTable || d->B < 1 || d->Sq < 1 || d->Hq < 1) return 1;
@@ -560,28 +620,11 @@ static size_t bwd_base_bytes(const st_ring_desc* d) {
          (d->dtype == ST_BF16 ? align_up(n_o / 2, 256) : 0);
 }
 
-// Workgroups per query tile of the dQ pass.  Same model as the forward's: a 256 x 64 tile is three contractions instead of
-// two (2.4 us at head size 128, 1.4 at 64), the pass that adds the partial sums up reads and writes dQ as well.
-// The split never asks for more than the static scratch of st_ring_bwd_noalloc has room for, so that both entry points
-// compute the same sums.
-static int dq_splits(const st_ring_desc* d, int n_visible, size_t workspace_bytes) {
-  if (d->dtype != ST_BF16 || (d->D != 128 && d->D != 64) || d->Sk < st::kQTileFastKeys || n_visible < 1 || d->B < 1 || d->Sq < 1 || d->Hq < 1) return 1;
-  const int64_t wgs = (int64_t)d->B * d->Hq * ((d->Sq + st::kQTileFastRows - 1) / st::kQTileFastRows);
-  if (wgs >= 512) return 1;
-  const int64_t tiles = (int64_t)n_visible * ((d->Sk + st::kQTileFastKeys - 1) / st::kQTileFastKeys);
-  const size_t n_o = align_up((size_t)d->B * d->Sq * d->Hq * d->D * sizeof(float), 256), base = bwd_base_bytes(d);
-  const size_t room = workspace_bytes < kScratchBytes ? workspace_bytes : kScratchBytes;
-  const double tile_us = d->D == 128 ? 2.4 : 1.4, fixed_us = 10, state_us = (double)n_o / 4e6;
-  double best = (double)((wgs + 255) / 256) * (fixed_us + tiles * tile_us);
-  int n_best = 1;
-  for (int n = 2; n <= kMaxSplits && n <= tiles && base + (size_t)n * n_o <= room; ++n) {
-    const double t = (double)((wgs * n + 255) / 256) * (fixed_us + (double)((tiles + n - 1) / n) * tile_us) + 6 + (n + 2) * state_us;
-    if (t < 0.95 * best) {
-      best = t;
-      n_best = n;
-    }
-  }
-  return n_best;
+// room for partial sums of a ring backward: never more than the static scratch of st_ring_bwd_noalloc has, so that both
+// entry points compute the same sums
+static size_t ring_room(const st_ring_desc* d, size_t workspace_bytes) {
+  const size_t have = workspace_bytes < kScratchBytes ? workspace_bytes : kScratchBytes, base = bwd_base_bytes(d);
+  return have > base ? have - base : 0;
 }
 
 size_t st_ring_workspace_bytes(const st_ring_desc* d, int32_t mode, int32_t backward) {
@@ -590,12 +633,12 @@ size_t st_ring_workspace_bytes(const st_ring_desc* d, int32_t mode, int32_t back
   const size_t n_l = align_up((size_t)d->B * d->Sq * d->Hq * sizeof(float), 256);
   if (backward) {
     // any subset of the chunks may be visited, in one launch or in several
-    int most = 1;
-    for (int n = 1; n <= d->n_chunks && n <= st::kMaxTable; ++n) {
-      const int x = dq_splits(d, mode == ST_RING_FUSED ? n : 1, kScratchBytes);
+    size_t most = 0;
+    for (int n = 1; n <= (mode == ST_RING_FUSED ? d->n_chunks : 1) && n <= st::kMaxTable; ++n) {
+      const size_t x = bwd_splits(shape_of(d), d->dtype, n, ring_room(d, kScratchBytes)).bytes;
       if (x > most) most = x;
     }
-    return bwd_base_bytes(d) + (most > 1 ? (size_t)most * n_o : 0);
+    return bwd_base_bytes(d) + most;
   }
   if (mode == ST_RING_STEPWISE) return 2 * (n_o + n_l);
   return (size_t)fwd_states_most(d) * (n_o + n_l);
@@ -820,7 +863,6 @@ st_status st_ring_bwd_last(const st_ring_desc* d, const st_tensor* q, const st_t
     ST_HIP(st::launch_scale_q(a.q, qs, d->B, d->Sq, d->Hq, d->D, d->scale, stream), "scaled-Q launch");
     a.qs = qs;
   }
-  const int64_t part_stride = (int64_t)(align_up((size_t)n_o * sizeof(float), 256) / sizeof(float));
   const int per_launch = mode == ST_RING_FUSED ? st::kMaxTable : 1;
   for (int x0 = 0; x0 < n; x0 += per_launch) {
     const int cnt = n - x0 < per_launch ? n - x0 : per_launch;
@@ -832,9 +874,7 @@ st_status st_ring_bwd_last(const st_ring_desc* d, const st_tensor* q, const st_t
       a.dk_lowp[x] = dk_lowp ? dk_lowp[j] : nullptr;
       a.dv_lowp[x] = dk_lowp ? dv_lowp[j] : nullptr;
     }
-    a.n_split = dq_splits(d, cnt, workspace_bytes);
-    a.dq_part = (float*)((char*)workspace + bwd_base_bytes(d));
-    a.part_stride = part_stride;
+    set_splits(a, bwd_splits(a.s, d->dtype, cnt, ring_room(d, workspace_bytes)), (char*)workspace + bwd_base_bytes(d));
     a.kv_assign = assign ? ~0ull : 0ull;
     if (d->dtype != ST_BF16 && assign)              // the fp32 kernels only add
       for (int x = 0; x < cnt; ++x) {

@@ -472,6 +472,7 @@ hipError_t launch_bwd_bf16(const BwdArgs& a_in, hipStream_t stream) {
   hipError_t e = hipSuccess;
   if (dkv_fast) {
     e = launch_bwd_dkv_fast(a, stream);
+    if (e == hipSuccess && a.kv_split > 1) e = launch_add_kv_parts(a, stream);
     if (e != hipSuccess) return e;
   } else {
     // the general kernel only adds: chunks to be assigned are zeroed first, bf16 copies are launches of their own
@@ -502,7 +503,7 @@ hipError_t launch_bwd_bf16(const BwdArgs& a_in, hipStream_t stream) {
   if (knobs().dq_fast && !few && dq_fast_usable(a)) {
     e = launch_bwd_dq_fast(a, stream);
     if (e == hipSuccess && a.n_split > 1)
-      e = launch_add_parts(a.dq, a.dq_part, a.n_split, a.part_stride, (int64_t)a.s.B * a.s.Sq * a.s.Hq * a.s.D, stream);
+      e = launch_add_parts(a.dq, a.parts, a.n_split, dq_part_floats(a.s), (int64_t)a.s.B * a.s.Sq * a.s.Hq * a.s.D, stream);
     return e;
   }
   ProfScope prof("bwd_dq_bf16", stream);

@@ -281,6 +281,24 @@ __global__ __launch_bounds__(256) void add_parts_kernel(float4* __restrict__ dst
   dst[v] = x;
 }
 
+__global__ __launch_bounds__(256) void add_kv_parts_kernel(const BwdArgs a, int64_t n_vec) {
+  const int64_t v = (int64_t)blockIdx.x * 256 + threadIdx.x;
+  const int c = blockIdx.y >> 1, w = blockIdx.y & 1;
+  if (v >= n_vec) return;
+  float4* dst = reinterpret_cast<float4*>(w ? a.dv[c] : a.dk[c]);
+  float4 x = dst[v];
+  for (int y = 1; y < a.kv_split; ++y) {
+    const float4 p = reinterpret_cast<const float4*>(a.parts + ((int64_t)(2 * (y - 1) + w) * a.t.n + c) * kv_part_floats(a.s))[v];
+    x.x += p.x;
+    x.y += p.y;
+    x.z += p.z;
+    x.w += p.w;
+  }
+  dst[v] = x;
+  uint2* low = reinterpret_cast<uint2*>(w ? a.dv_lowp[c] : a.dk_lowp[c]);
+  if (low) low[v] = make_uint2(pack_bf16x2(x.x, x.y), pack_bf16x2(x.z, x.w));
+}
+
 __global__ __launch_bounds__(256) void fill_state_kernel(float* __restrict__ o, float* __restrict__ lse,
                                                          int64_t n_o, int64_t n_lse) {
   const int64_t v = (int64_t)blockIdx.x * 256 + threadIdx.x;
@@ -411,6 +429,14 @@ hipError_t launch_add_parts(float* dst, const float* parts, int n_parts, int64_t
   ProfScope prof("add_parts", s);
   hipLaunchKernelGGL(add_parts_kernel, dim3(blocks_for(n / 4)), dim3(256), 0, s, (float4*)dst, (const float4*)parts, n_parts,
                      stride / 4, n / 4);
+  return hipGetLastError();
+}
+
+hipError_t launch_add_kv_parts(const BwdArgs& a, hipStream_t s) {
+  const int64_t n_vec = (int64_t)a.s.B * a.s.Sk * a.s.Hkv * a.s.D / 4;
+  if (n_vec <= 0 || a.t.n <= 0) return hipSuccess;
+  ProfScope prof("add_parts", s);
+  hipLaunchKernelGGL(add_kv_parts_kernel, dim3(blocks_for(n_vec), 2 * a.t.n), dim3(256), 0, s, a, n_vec);
   return hipGetLastError();
 }
 

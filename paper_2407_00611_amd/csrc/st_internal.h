@@ -85,11 +85,14 @@ struct BwdArgs {
   float* dk[kMaxTable];  // fp32 [B,Sk,Hkv,D] per table entry, +=
   float* dv[kMaxTable];
   // Under-filled dQ launches of the hand-scheduled kernel: n_split > 1 gives every query tile n_split workgroups
-  // (blockIdx.y), each storing the sum over its share of the tiles at dq_part + y * part_stride (floats, laid out as dq);
-  // the launcher then adds them to dq in order.
+  // (blockIdx.y), each storing the sum over its share of the tiles at parts + y * part_floats(dq) (laid out as dq); the
+  // launcher then adds them to dq in order.
   int32_t n_split;
-  float* dq_part;
-  int64_t part_stride;
+  // Under-filled dK/dV launches likewise: kv_split > 1 gives every key tile kv_split workgroups, each with a share of the
+  // query blocks.  The first one writes dk[c] / dv[c]; number y stores its sums at parts + ((2 (y - 1) + (0: dK, 1: dV)) *
+  // t.n + c) * part_floats(dk[c]) (laid out as dk[c]), and the launcher adds them up (and rounds) in order.
+  int32_t kv_split;
+  float* parts;        // the two passes use it one after the other
   // dK / dV work of a chunk's last visit folded into the launch (bf16 path): the hand-scheduled kernel's epilogue does it,
   // beside the general kernel the launcher runs fill and cast launches
   uint64_t kv_assign;          // bit c: dk[c] / dv[c] are overwritten, not added to
@@ -99,6 +102,10 @@ struct BwdArgs {
                        // through it (one counter per XCD), so that XCDs that run faster take more of them
   int32_t queue_xcds;  // counters in use (the device's XCD count, 1 .. 8); set by the launcher
 };
+// distance between partial sums of n floats each (256-byte steps)
+__host__ __device__ inline int64_t part_floats(int64_t n) { return (n + 63) / 64 * 64; }
+__host__ __device__ inline int64_t dq_part_floats(const Shape& s) { return part_floats((int64_t)s.B * s.Sq * s.Hq * s.D); }
+__host__ __device__ inline int64_t kv_part_floats(const Shape& s) { return part_floats((int64_t)s.B * s.Sk * s.Hkv * s.D); }
 constexpr int kQueueInts = 8 * 32;   // at most 8 counters, 128 bytes apart
 // passed by value: the kernel-argument segment holds 4096 bytes, 256 of them the implicit arguments
 static_assert(sizeof(BwdArgs) <= 4096 - 256 && sizeof(FwdArgs) <= 4096 - 256, "argument structs must fit the kernel-argument segment");
@@ -178,6 +185,8 @@ hipError_t launch_delta(const View& d_o, int d_o_dtype, const View& o, int o_dty
 hipError_t launch_cast(const float* src, void* dst, int64_t n, int dst_dtype, hipStream_t s);
 // dst (dense bf16 [B,Sq,Hq,D]) = bf16(q * scale * log2 e) of a bf16 view q
 hipError_t launch_scale_q(const View& q, void* dst, int32_t B, int32_t Sq, int32_t Hq, int32_t D, float scale, hipStream_t s);
+// dk[c] += its parts (see BwdArgs::kv_split) in order, likewise dv[c]; rounded to dk_lowp[c] / dv_lowp[c] where given
+hipError_t launch_add_kv_parts(const BwdArgs& a, hipStream_t s);
 // dst += parts[0] + parts[1] + ... in that order; part y at parts + y * stride, n floats each (n % 4 == 0)
 hipError_t launch_add_parts(float* dst, const float* parts, int n_parts, int64_t stride, int64_t n, hipStream_t s);
 hipError_t launch_fill_state(float* o, float* lse, int64_t n_o, int64_t n_lse, hipStream_t s);

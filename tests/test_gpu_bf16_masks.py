@@ -135,3 +135,34 @@ def test_backward_split_over_workgroups():
         got.append(dq)
     assert torch.equal(got[0], got[1]) and torch.equal(got[0], got[2])
     assert_close(host(got[3]), host(got[0]), "bf16", "dq unsplit")
+
+
+@pytest.mark.parametrize("how", ["add", "assign", "add_lowp", "stepwise"])
+@pytest.mark.parametrize("D", [128, 64])
+def test_key_tiles_split_over_workgroups(D, how):
+    """Grouped heads against two short chunks: four key tiles, each walked by several workgroups whose sums are added up;
+    the causal shard leaves some shares of some tiles without a block, and a chunk in the future without any."""
+    w = si.Workload("split_kv", 333, "bf16", 1, 4, 1, D, 1070, 300, 3, -200, True, True)
+    print(f"[key tile split] D={D} {how}", flush=True)
+    _backward(w, si.make_inputs(w), st.ST_RING_STEPWISE if how == "stepwise" else st.ST_RING_FUSED,
+              {"assign": True, "add_lowp": False}.get(how))
+
+
+def test_block_backward_with_and_without_room_for_partial_sums():
+    w = si.Workload("split_block", 334, "bf16", 1, 8, 1, 128, 1024, 256, 1, 0, True, True)
+    inp = si.make_inputs(w)
+    q, ks, vs, d_o = upload(inp)
+    q_pos, k_pos = positions(w)
+    need = st.st_attn_block_bwd_workspace_bytes(q, ks[0], 0, 0, True, w.scale)
+    small = q.numel() * 2
+    assert need > small
+    o, lse = st.st_attn_block_fwd(q, ks[0], vs[0], 0, 0, True, w.scale)
+    delta = st.st_attn_delta(d_o, o)
+    ref = oa.attention_backward(inp.q, inp.k, inp.v, inp.d_o, q_pos, k_pos, True, w.scale)
+    for size in (need, small):
+        dq, dk, dv = torch.zeros_like(o), torch.zeros(ks[0].shape, device="cuda"), torch.zeros(ks[0].shape, device="cuda")
+        st.st_attn_block_bwd(q, ks[0], vs[0], d_o, lse, delta, 0, 0, True, w.scale, dq, dk, dv,
+                             workspace=torch.empty(size + 256, dtype=torch.uint8, device="cuda"))
+        assert_close(host(dq), ref[0], "bf16", "dq")
+        assert_close_wide(host(dk), ref[1][0], "dk")
+        assert_close_wide(host(dv), ref[2][0], "dv")
