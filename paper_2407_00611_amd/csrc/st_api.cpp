@@ -170,7 +170,7 @@ st_status check_ring(const st_ring_desc* d, const st_tensor* q, const int32_t* o
 
 constexpr int kMaxSplits = 16;
 
-// Workgroups per tile of a backward launch over n chunks that have rows to see them, and the bytes of partial sums that
+// Workgroups per tile of a backward launch over n chunks, and the bytes of partial sums that
 // takes (the two passes run one after the other and share them).
 struct BwdSplit {
   int dq = 1, kv = 1;
@@ -817,6 +817,10 @@ st_status st_ring_bwd_last(const st_ring_desc* d, const st_tensor* q, const st_t
   hipStream_t stream = (hipStream_t)hip_stream;
   auto unseen = [&](int j) { return no_rows || chunk_invisible(d, j); };
 
+  // Listed chunks that nobody sees contribute zero, but may have to be assigned or rounded: in one launch with the others
+  // (their key tiles find no query block), or by launches of their own where every chunk has its own (step-wise), and where
+  // there are no query rows at all.
+  const bool hidden_too = mode == ST_RING_FUSED && d->dtype == ST_BF16 && !no_rows && n_kv > 0;
   int vis[ST_MAX_CHUNKS], n = 0;
   for (int x = 0; x < n_visit; ++x) {
     const int j = order[x];
@@ -830,12 +834,11 @@ st_status st_ring_bwd_last(const st_ring_desc* d, const st_tensor* q, const st_t
       ST_TRY(check_f32("dk_acc[j]", dk_acc[j], n_kv));
       ST_TRY(check_f32("dv_acc[j]", dv_acc[j], n_kv));
     }
-    if (!hidden) vis[n++] = j;
+    if (!hidden || (hidden_too && (assign || lk))) vis[n++] = j;
   }
-  // a listed chunk nobody sees: its contribution is zero
   for (int x = 0; x < n_visit; ++x) {
     const int j = order[x];
-    if (!unseen(j) || n_kv == 0) continue;
+    if (!unseen(j) || n_kv == 0 || hidden_too) continue;
     if (assign) {
       ST_HIP(st::launch_zero(dk_acc[j], n_kv * (int64_t)sizeof(float), stream), "dk_acc fill");
       ST_HIP(st::launch_zero(dv_acc[j], n_kv * (int64_t)sizeof(float), stream), "dv_acc fill");
@@ -848,8 +851,6 @@ st_status st_ring_bwd_last(const st_ring_desc* d, const st_tensor* q, const st_t
   if (no_rows) return ST_OK;
 
   float* delta = (float*)workspace;
-  ST_HIP(st::launch_delta(view_of(d_o), d->dtype, view_of(o), o_dtype, delta, d->B, d->Sq, d->Hq, d->D, stream), "delta launch");
-
   st::BwdArgs a;
   memset(&a, 0, sizeof(a));
   a.s = shape_of(d);
@@ -860,13 +861,16 @@ st_status st_ring_bwd_last(const st_ring_desc* d, const st_tensor* q, const st_t
   a.queue = (int32_t*)((char*)workspace + align_up((size_t)d->B * d->Sq * d->Hq * sizeof(float), 256));
   if (d->dtype == ST_BF16) {
     void* qs = (char*)a.queue + align_up(st::kQueueInts * sizeof(int32_t), 256);
-    ST_HIP(st::launch_scale_q(a.q, qs, d->B, d->Sq, d->Hq, d->D, d->scale, stream), "scaled-Q launch");
+    ST_HIP(st::launch_bwd_prep(a.d_o, view_of(o), o_dtype, a.q, delta, qs, a.queue, d->B, d->Sq, d->Hq, d->D, d->scale, stream), "backward preparation launch");
     a.qs = qs;
+  } else {
+    ST_HIP(st::launch_delta(a.d_o, d->dtype, view_of(o), o_dtype, delta, d->B, d->Sq, d->Hq, d->D, stream), "delta launch");
   }
   const int per_launch = mode == ST_RING_FUSED ? st::kMaxTable : 1;
   for (int x0 = 0; x0 < n; x0 += per_launch) {
     const int cnt = n - x0 < per_launch ? n - x0 : per_launch;
     a.t.n = cnt;
+    a.queue_clean = d->dtype == ST_BF16 && x0 == 0;
     for (int x = 0; x < cnt; ++x) {
       const int j = vis[x0 + x];
       a.t.k[x] = d->k_ptr[j]; a.t.v[x] = d->v_ptr[j]; a.t.k_offset[x] = d->k_offset[j];

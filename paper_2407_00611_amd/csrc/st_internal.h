@@ -100,6 +100,7 @@ struct BwdArgs {
   void* dv_lowp[kMaxTable];
   int32_t* queue;      // nullable, kQueueInts ints of device memory: the fast dK/dV kernel hands its key tiles out
                        // through it (one counter per XCD), so that XCDs that run faster take more of them
+  int32_t queue_clean; // 1: the counters are zero already (the first launch behind launch_bwd_prep)
   int32_t queue_xcds;  // counters in use (the device's XCD count, 1 .. 8); set by the launcher
 };
 // distance between partial sums of n floats each (256-byte steps)
@@ -182,6 +183,9 @@ hipError_t launch_merge(float* o_acc, float* lse_acc, const float* o_part, const
 hipError_t launch_combine(const CombineArgs& a, int lowp_dtype, hipStream_t s);
 hipError_t launch_delta(const View& d_o, int d_o_dtype, const View& o, int o_dtype, float* delta,
                         int32_t B, int32_t Sq, int32_t Hq, int32_t D, hipStream_t s);
+// bf16 backward, head size 64 or 128: delta = rowsum(dO o O), qs as launch_scale_q, queue (kQueueInts ints) to zero
+hipError_t launch_bwd_prep(const View& d_o, const View& o, int o_dtype, const View& q, float* delta, void* qs, int32_t* queue,
+                           int32_t B, int32_t Sq, int32_t Hq, int32_t D, float scale, hipStream_t s);
 hipError_t launch_cast(const float* src, void* dst, int64_t n, int dst_dtype, hipStream_t s);
 // dst (dense bf16 [B,Sq,Hq,D]) = bf16(q * scale * log2 e) of a bf16 view q
 hipError_t launch_scale_q(const View& q, void* dst, int32_t B, int32_t Sq, int32_t Hq, int32_t D, float scale, hipStream_t s);

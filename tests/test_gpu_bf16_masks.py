@@ -166,3 +166,30 @@ def test_block_backward_with_and_without_room_for_partial_sums():
         assert_close(host(dq), ref[0], "bf16", "dq")
         assert_close_wide(host(dk), ref[1][0], "dk")
         assert_close_wide(host(dv), ref[2][0], "dv")
+
+
+@pytest.mark.parametrize("assign", [True, False])
+def test_listed_chunks_that_nobody_sees(assign):
+    """Chunks in the shard's future, first, last and between the others in visit order: assigned to zero, or left as they
+    are, and rounded, in the same launch as the chunks that have rows."""
+    w = si.Workload("future", 335, "bf16", 1, 2, 1, 64, 130, 130, 5, 130, True, True)
+    inp = si.make_inputs(w)
+    q, ks, vs, d_o = upload(inp)
+    koffs = [w.k_offset(j) for j in range(5)]
+    order = [3, 0, 4, 1, 2]
+    o, lse, low = st.st_ring_fwd(q, ks, vs, w.q_where, koffs, True, w.scale, order)
+    dq = torch.zeros_like(o)
+    dk = [torch.full(k.shape, float("nan") if assign else 1.25, device="cuda") for k in ks]
+    dv = [x.clone() for x in dk]
+    lk, lv = [torch.empty_like(k) for k in ks], [torch.empty_like(k) for k in ks]
+    st.st_ring_bwd_last(q, ks, vs, d_o, low, lse, w.q_where, koffs, True, w.scale, order, dq, dk, dv, assign=assign,
+                        dk_lowp=lk, dv_lowp=lv)
+    q_pos, k_pos = positions(w)
+    ref = oa.attention_backward(inp.q, inp.k, inp.v, inp.d_o, q_pos, k_pos, True, w.scale)
+    assert_close(host(dq), ref[0], "bf16", "dq")
+    for j in range(5):
+        for x, y, r in ((dk[j], lk[j], ref[1][j]), (dv[j], lv[j], ref[2][j])):
+            assert torch.equal(x.to(torch.bfloat16), y)
+            assert_close_wide(host(x) - (0.0 if assign else 1.25), r, f"chunk {j}")
+            if j > 1:
+                assert (x == (0.0 if assign else 1.25)).all()
