@@ -181,7 +181,19 @@ struct BwdSplit {
 // dK/dV: a step (256 keys x 32 rows of one head) is 1.2 us at head size 128 and 0.75 at 64, prologue and epilogue 20 and 14;
 // grouped heads make the walk long and the key tiles few (4096 x 4096, 32/8 heads: 128 workgroups of 512 steps on 256
 // compute units, 570 us; 310 us as two shares of 256 steps and a 25 us pass).  512 tiles and more go through the queue.
-BwdSplit bwd_splits(const st::Shape& s, int dtype, int n, size_t room, bool split_dq = true) {
+// A causal launch whose key tiles meet less than three quarters of the query blocks on average (the diagonal chunk alone
+// meets half of them) is planned as one of half the work: not rounds of equal workgroups, but the longest one, or all of
+// them spread evenly, whichever takes longer.
+bool bwd_half(const st::Shape& s, const int64_t* k_offset, int n) {
+  const int64_t blocks = (s.Sq + st::kDkvFastRows - 1) / st::kDkvFastRows;
+  const int64_t tiles = (s.Sk + st::kDkvFastKeys - 1) / st::kDkvFastKeys;
+  if (!s.causal || (int64_t)s.B * s.Hkv * n * tiles >= 512) return false;
+  int64_t sum = 0;
+  for (int c = 0; c < n; ++c)
+    for (int64_t t = 0; t < tiles; ++t) sum += blocks - st::q_row_of(s, k_offset[c] + t * st::kDkvFastKeys) / st::kDkvFastRows;
+  return 4 * sum < 3 * (int64_t)n * tiles * blocks;
+}
+BwdSplit bwd_splits(const st::Shape& s, int dtype, int n, bool half, size_t room, bool split_dq = true) {
   BwdSplit r;
   if (dtype != ST_BF16 || (s.D != 128 && s.D != 64) || n < 1 || n > st::kMaxTable || s.B < 1 || s.Sq < 1 || s.Sk < 1 || s.Hq < 1 || s.Hkv < 1) return r;
   const bool d128 = s.D == 128;
@@ -205,9 +217,15 @@ BwdSplit bwd_splits(const st::Shape& s, int dtype, int n, size_t room, bool spli
     const int64_t blocks = (s.Sq + st::kDkvFastRows - 1) / st::kDkvFastRows, G = s.Hq / s.Hkv;
     const size_t kv = 2 * (size_t)n * st::kv_part_floats(s) * sizeof(float);
     const double step_us = d128 ? 1.2 : 0.75, fixed_us = d128 ? 20 : 14;
-    double best = (double)((key_tiles + 255) / 256) * (fixed_us + blocks * G * step_us);
+    auto launch_us = [&](int x) {
+      const double one = fixed_us + (double)((blocks + x - 1) / x) * G * step_us;
+      if (!half) return (double)((key_tiles * x + 255) / 256) * one;
+      const double even = (double)key_tiles * (x * fixed_us + 0.5 * blocks * G * step_us) / 256;
+      return one > even ? one : even;
+    };
+    double best = launch_us(1);
     for (int x = 2; x <= kMaxSplits && x <= blocks && (size_t)(x - 1) * kv <= room; ++x) {
-      const double t = (double)((key_tiles * x + 255) / 256) * (fixed_us + (double)((blocks + x - 1) / x) * G * step_us) + 6 + 2 * x * (double)kv / 4e6;
+      const double t = launch_us(x) + 6 + 2 * x * (double)kv / 4e6;
       if (t < 0.95 * best) {
         best = t;
         r.kv = x;
@@ -217,6 +235,7 @@ BwdSplit bwd_splits(const st::Shape& s, int dtype, int n, size_t room, bool spli
   }
   return r;
 }
+size_t most_bytes(const BwdSplit& x, const BwdSplit& y) { return x.bytes > y.bytes ? x.bytes : y.bytes; }
 void set_splits(st::BwdArgs& a, const BwdSplit& x, void* parts) {
   a.n_split = x.dq;
   a.kv_split = x.kv;
@@ -441,7 +460,7 @@ constexpr size_t kBlockPartsMost = (size_t)64 << 20;
 
 size_t st_attn_block_bwd_workspace_bytes(const st_block_desc* d) {
   if (d == nullptr || d->dtype != ST_BF16 || d->B <= 0 || d->Sq <= 0 || d->Hq <= 0 || d->D <= 0) return 0;
-  return block_base_bytes(d) + bwd_splits(shape_of(d), d->dtype, 1, kBlockPartsMost, false).bytes;
+  return block_base_bytes(d) + most_bytes(bwd_splits(shape_of(d), d->dtype, 1, false, kBlockPartsMost, false), bwd_splits(shape_of(d), d->dtype, 1, true, kBlockPartsMost, false));
 }
 
 st_status st_attn_block_bwd(const st_block_desc* d, const st_tensor* q, const st_tensor* k, const st_tensor* v,
@@ -479,7 +498,7 @@ st_status st_attn_block_bwd(const st_block_desc* d, const st_tensor* q, const st
     ST_HIP(st::launch_scale_q(a.q, workspace, d->B, d->Sq, d->Hq, d->D, d->scale, (hipStream_t)hip_stream), "scaled-Q launch");
     a.qs = workspace;
     const size_t left = workspace_bytes - block_base_bytes(d);
-    set_splits(a, bwd_splits(a.s, d->dtype, 1, left < kBlockPartsMost ? left : kBlockPartsMost, false), (char*)workspace + block_base_bytes(d));
+    set_splits(a, bwd_splits(a.s, d->dtype, 1, bwd_half(a.s, a.t.k_offset, 1), left < kBlockPartsMost ? left : kBlockPartsMost, false), (char*)workspace + block_base_bytes(d));
   }
   ST_HIP(launch_bwd(d->dtype, a, (hipStream_t)hip_stream), "st_attn_block_bwd launch");
   return ST_OK;
@@ -635,7 +654,8 @@ size_t st_ring_workspace_bytes(const st_ring_desc* d, int32_t mode, int32_t back
     // any subset of the chunks may be visited, in one launch or in several
     size_t most = 0;
     for (int n = 1; n <= (mode == ST_RING_FUSED ? d->n_chunks : 1) && n <= st::kMaxTable; ++n) {
-      const size_t x = bwd_splits(shape_of(d), d->dtype, n, ring_room(d, kScratchBytes)).bytes;
+      const size_t room = ring_room(d, kScratchBytes);
+      const size_t x = most_bytes(bwd_splits(shape_of(d), d->dtype, n, false, room), bwd_splits(shape_of(d), d->dtype, n, true, room));
       if (x > most) most = x;
     }
     return bwd_base_bytes(d) + most;
@@ -878,7 +898,7 @@ st_status st_ring_bwd_last(const st_ring_desc* d, const st_tensor* q, const st_t
       a.dk_lowp[x] = dk_lowp ? dk_lowp[j] : nullptr;
       a.dv_lowp[x] = dk_lowp ? dv_lowp[j] : nullptr;
     }
-    set_splits(a, bwd_splits(a.s, d->dtype, cnt, ring_room(d, workspace_bytes)), (char*)workspace + bwd_base_bytes(d));
+    set_splits(a, bwd_splits(a.s, d->dtype, cnt, bwd_half(a.s, a.t.k_offset, cnt), ring_room(d, workspace_bytes)), (char*)workspace + bwd_base_bytes(d));
     a.kv_assign = assign ? ~0ull : 0ull;
     if (d->dtype != ST_BF16 && assign)              // the fp32 kernels only add
       for (int x = 0; x < cnt; ++x) {
