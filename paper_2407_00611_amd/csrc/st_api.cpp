@@ -177,7 +177,10 @@ struct BwdSplit {
   size_t bytes = 0;
 };
 // dQ: the forward's model (rounds of workgroups x time of one + the pass that adds up); a 256 x 64 tile is three
-// contractions instead of two: 2.4 us at head size 128, 1.4 at 64.
+// contractions instead of two: 2.4 us at head size 128, 1.4 at 64.  fp32: the eight (four beyond head size 128) wavefronts
+// of a workgroup take a 32-key tile each in 16 us at head size 128, 9 at 64, 5.5 at 32, and 16 at 256 (8 heads x 512 rows x
+// 8 chunks of 512 keys at head size 128: 128 workgroups, 270 us; 157 us as two shares each and the adding pass); 10 us for
+// the adding pass, as walks of two turns gain less than its launch takes.
 // dK/dV: a step (256 keys x 32 rows of one head) is 1.2 us at head size 128 and 0.75 at 64, prologue and epilogue 20 and 14;
 // grouped heads make the walk long and the key tiles few (4096 x 4096, 32/8 heads: 128 workgroups of 512 steps on 256
 // compute units, 570 us; 310 us as two shares of 256 steps and a 25 us pass).  512 tiles and more go through the queue.
@@ -195,16 +198,18 @@ bool bwd_half(const st::Shape& s, const int64_t* k_offset, int n) {
 }
 BwdSplit bwd_splits(const st::Shape& s, int dtype, int n, bool half, size_t room, bool split_dq = true) {
   BwdSplit r;
-  if (dtype != ST_BF16 || (s.D != 128 && s.D != 64) || n < 1 || n > st::kMaxTable || s.B < 1 || s.Sq < 1 || s.Sk < 1 || s.Hq < 1 || s.Hkv < 1) return r;
+  const bool bf16 = dtype == ST_BF16;
+  if ((bf16 && s.D != 128 && s.D != 64) || n < 1 || n > st::kMaxTable || s.B < 1 || s.Sq < 1 || s.Sk < 1 || s.Hq < 1 || s.Hkv < 1) return r;
   const bool d128 = s.D == 128;
-  const int64_t wgs = (int64_t)s.B * s.Hq * ((s.Sq + st::kQTileFastRows - 1) / st::kQTileFastRows);
-  if (split_dq && wgs < 512 && s.Sk >= st::kQTileFastKeys) {
-    const int64_t tiles = (int64_t)n * ((s.Sk + st::kQTileFastKeys - 1) / st::kQTileFastKeys);
+  const int rows = bf16 ? st::kQTileFastRows : 32, keys = bf16 ? st::kQTileFastKeys : s.D <= 128 ? 256 : 128;
+  const int64_t wgs = (int64_t)s.B * s.Hq * ((s.Sq + rows - 1) / rows);
+  if (split_dq && wgs < 512 && (!bf16 || s.Sk >= keys)) {
+    const int64_t tiles = bf16 ? (int64_t)n * ((s.Sk + keys - 1) / keys) : ((int64_t)n * ((s.Sk + 31) / 32) * 32 + keys - 1) / keys;
     const size_t n_o = (size_t)st::dq_part_floats(s) * sizeof(float);
-    const double tile_us = d128 ? 2.4 : 1.4, fixed_us = 10, state_us = (double)n_o / 4e6;
+    const double tile_us = bf16 ? (d128 ? 2.4 : 1.4) : 2 + (s.D <= 128 ? 0.11 : 0.055) * s.D, fixed_us = 10, state_us = (double)n_o / 4e6, add_us = bf16 ? 6 : 10;
     double best = (double)((wgs + 255) / 256) * (fixed_us + tiles * tile_us);
     for (int x = 2; x <= kMaxSplits && x <= tiles && (size_t)x * n_o <= room; ++x) {
-      const double t = (double)((wgs * x + 255) / 256) * (fixed_us + (double)((tiles + x - 1) / x) * tile_us) + 6 + (x + 2) * state_us;
+      const double t = (double)((wgs * x + 255) / 256) * (fixed_us + (double)((tiles + x - 1) / x) * tile_us) + add_us + (x + 2) * state_us;
       if (t < 0.95 * best) {
         best = t;
         r.dq = x;
@@ -213,7 +218,7 @@ BwdSplit bwd_splits(const st::Shape& s, int dtype, int n, bool half, size_t room
     }
   }
   const int64_t key_tiles = (int64_t)s.B * s.Hkv * n * ((s.Sk + st::kDkvFastKeys - 1) / st::kDkvFastKeys);
-  if (key_tiles < 512) {
+  if (bf16 && key_tiles < 512) {
     const int64_t blocks = (s.Sq + st::kDkvFastRows - 1) / st::kDkvFastRows, G = s.Hq / s.Hkv;
     const size_t kv = 2 * (size_t)n * st::kv_part_floats(s) * sizeof(float);
     const double step_us = d128 ? 1.2 : 0.75, fixed_us = d128 ? 20 : 14;

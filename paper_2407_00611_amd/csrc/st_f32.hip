@@ -19,8 +19,9 @@
 //
 // One wavefront per row with scalar fused multiply-adds, as these kernels were before, read K with every lane on a
 // row of its own and one load per four multiply-adds: 8 heads x 512 rows x 8 chunks of 512 keys at D = 128 took 2460 us
-// forward, 2640 us dQ, 3590 us dK / dV (3.2 TFLOP/s).  Now 108, 276 and 203 us (dQ has 128 workgroups for 256 compute
-// units there; dK / dV executes 16 GFLOP, 105 us at the 154 TFLOP/s of a large fp32 matrix product on this card).
+// forward, 2640 us dQ, 3590 us dK / dV (3.2 TFLOP/s).  Now 108, 157 and 200 us with the split launches (dQ on one workgroup
+// per query tile, 128 for 256 compute units: 270 us).  Prologue, first loads and fold are about 20 us of each; long walks
+// run at 100 TFLOP/s of the 154 of a large fp32 matrix product on this card.
 #include <type_traits>
 
 #include "st_internal.h"
@@ -343,7 +344,9 @@ __global__ __launch_bounds__(waves<DP>() * 64) void fwd_f32_kernel(const FwdArgs
 }
 
 // ---------------------------------------------------------------- backward: dQ
-// Three contractions per tile pair (S and dP are recomputed); otherwise the forward's split.
+// Three contractions per tile pair (S and dP are recomputed); otherwise the forward's layout.  An under-filled launch
+// (n_split > 1) gives every query tile n_split workgroups, blockIdx.y of them, which take NW tiles of the walk in turn, so
+// that their shares differ by one turn at most whatever the mask and however few chunks there are.
 template <int DP, bool FULL>
 __global__ __launch_bounds__(waves<DP>() * 64) void bwd_dq_f32_kernel(const BwdArgs a) {
   constexpr int NW = waves<DP>(), DB = DP / 32, N = 32, NR = row_pieces<DP, N>(), NC = col_pieces<DP, N>();
@@ -371,7 +374,8 @@ __global__ __launch_bounds__(waves<DP>() * 64) void bwd_dq_f32_kernel(const BwdA
   const int64_t qpos = q_pos(s, i), first_pos = q_pos(s, row0), last_pos = q_pos(s, min(row0 + kT, s.Sq) - 1);
   f32x16 acc[DB];
   zero_acc(acc);
-  KeyWalk w{0, 0, a.t.n > 0 ? visible_keys(s, last_pos, a.t.k_offset[0]) : 0, wave};
+  const int n_split = max(a.n_split, 1);
+  KeyWalk w{0, 0, a.t.n > 0 ? visible_keys(s, last_pos, a.t.k_offset[0]) : 0, (int)blockIdx.y * NW + wave};
   while (walk_next<DP>(w, s, a.t, a.t.n, last_pos)) {
     const float* kb = (const float*)a.t.k[w.c] + b * a.t.ksb + hk * a.t.ksh + (int64_t)w.t * a.t.kss;
     const float* vb = (const float*)a.t.v[w.c] + b * a.t.vsb + hk * a.t.vsh + (int64_t)w.t * a.t.vss;
@@ -406,7 +410,7 @@ __global__ __launch_bounds__(waves<DP>() * 64) void bwd_dq_f32_kernel(const BwdA
       if (dirty) scrub(f[x & 1]);
       contract_rows<DP>(acc, f[x & 1], ds, x - 2 * NR);
     }
-    w.skip = NW;
+    w.skip = n_split * NW;
   }
   for (int n = NW / 2; n > 0; n /= 2) {
     if (wave >= n && wave < 2 * n) put_acc(fold + (wave - n) * DB * 16 * 64, acc, lane);
@@ -414,22 +418,24 @@ __global__ __launch_bounds__(waves<DP>() * 64) void bwd_dq_f32_kernel(const BwdA
     if (wave < n) add_acc(fold + wave * DB * 16 * 64, acc, 1.f, 1.f, lane);
     __syncthreads();
   }
-  if (wave != 0 || row0 + r >= s.Sq || empty) return;
-  float* dq = a.dq + (((int64_t)b * s.Sq + row0 + r) * s.Hq + h) * s.D;
+  if (wave != 0 || row0 + r >= s.Sq) return;
+  const bool part = n_split > 1;                              // a partial sum (its memory holds nothing yet), not dq itself
+  if (empty && !part) return;
+  float* dq = (part ? a.parts + blockIdx.y * dq_part_floats(s) : a.dq) + (((int64_t)b * s.Sq + row0 + r) * s.Hq + h) * s.D;
 #pragma unroll
   for (int db = 0; db < DB; ++db)
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
       const int d = 32 * db + 8 * j + 4 * g;
       if (d >= s.D) continue;
-      float4 x = *reinterpret_cast<float4*>(dq + d);
+      float4 x = part ? make_float4(0.f, 0.f, 0.f, 0.f) : *reinterpret_cast<float4*>(dq + d);
       x.x += s.scale * acc[db][4 * j];
       x.y += s.scale * acc[db][4 * j + 1];
       x.z += s.scale * acc[db][4 * j + 2];
       x.w += s.scale * acc[db][4 * j + 3];
       *reinterpret_cast<float4*>(dq + d) = x;
     }
-  if (any_dirty)
+  if (any_dirty && !empty)
     for (int c = 0; c < a.t.n; ++c)
       add_nonfinite(dq, nullptr, (const float*)a.t.k[c] + b * a.t.ksb + hk * a.t.ksh, a.t.kss,
                     visible_keys(s, first_pos, a.t.k_offset[c]) / kT * kT, visible_keys(s, qpos, a.t.k_offset[c]), s.D, g, true);
@@ -605,9 +611,12 @@ hipError_t launch_bwd_f32(const BwdArgs& a, hipStream_t stream) {
     constexpr bool FULL = decltype(full)::value;
     {
       ProfScope prof("bwd_dq_f32", stream);
-      hipLaunchKernelGGL((bwd_dq_f32_kernel<DP, FULL>), dim3((unsigned)total), dim3(waves<DP>() * 64), 0, stream, a);
+      const dim3 grid((unsigned)total, (unsigned)(a.n_split > 1 ? a.n_split : 1));
+      hipLaunchKernelGGL((bwd_dq_f32_kernel<DP, FULL>), grid, dim3(waves<DP>() * 64), 0, stream, a);
     }
     hipError_t e = hipGetLastError();
+    if (e == hipSuccess && a.n_split > 1)
+      e = launch_add_parts(a.dq, a.parts, a.n_split, dq_part_floats(a.s), (int64_t)a.s.B * a.s.Sq * a.s.Hq * a.s.D, stream);
     if (e != hipSuccess) return e;
     ProfScope prof("bwd_dkv_f32", stream);
     const dim3 grid((a.s.Sk + kT - 1) / kT, a.s.Hkv, a.s.B * a.t.n);

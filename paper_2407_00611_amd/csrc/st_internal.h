@@ -84,7 +84,7 @@ struct BwdArgs {
   float* dq;           // fp32 [B,Sq,Hq,D], +=
   float* dk[kMaxTable];  // fp32 [B,Sk,Hkv,D] per table entry, +=
   float* dv[kMaxTable];
-  // Under-filled dQ launches of the hand-scheduled kernel: n_split > 1 gives every query tile n_split workgroups
+  // Under-filled dQ launches of the hand-scheduled and of the fp32 kernel: n_split > 1 gives every query tile n_split workgroups
   // (blockIdx.y), each storing the sum over its share of the tiles at parts + y * part_floats(dq) (laid out as dq); the
   // launcher then adds them to dq in order.
   int32_t n_split;

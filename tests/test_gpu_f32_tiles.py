@@ -110,3 +110,44 @@ def test_values_that_are_no_numbers_stay_behind_the_mask():
     _, _, _, dk, dv = run(q, ks[0], vs[0], d2)
     assert torch.equal(dk[:, bad + 1:], ref[3][:, bad + 1:]) and torch.equal(dv[:, bad + 1:], ref[4][:, bad + 1:])
     assert torch.isposinf(dv[:, :bad + 1, :, 9]).all()
+
+
+#           D,  Sq,  Sk, n, q_offset, causal, (q_seg, q_offset2)
+DQ_SPLIT = [(128, 64, 300, 4, 3 * 300, True, (0, 0)),       # a few query tiles against long chunks
+            (64, 33, 1000, 1, 0, True, (0, 0)),             # one chunk; all but its first turn is hidden
+            (40, 65, 520, 2, 100, True, (33, 900)),         # two runs of query rows
+            (256, 31, 260, 3, 0, False, (0, 0)),            # four wavefronts per workgroup, ragged last tiles
+            (96, 40, 700, 2, 20, True, (0, 0))]             # a chunk whose first rows see nothing of it
+
+
+@pytest.mark.parametrize("c", DQ_SPLIT, ids=[f"d{c[0]}_q{c[1]}_k{c[2]}" for c in DQ_SPLIT])
+def test_split_dq_and_a_workspace_without_room_for_it(c):
+    """An under-filled dQ launch is split over the keys when the workspace has room for the partial sums, and not
+    otherwise; both add to what dq holds, and st_ring_bwd_noalloc adds up as the split launch does."""
+    D, Sq, Sk, n, q0, causal, (seg, q2) = c
+    w = si.Workload("f32_dq_split", 320 + D, "f32", 1, 2, 1, D, Sq, Sk, n, q0, causal, True, q_seg=seg, q_offset2=q2)
+    print(f"[f32 dq split] {c}", flush=True)
+    inp = si.make_inputs(w)
+    q, ks, vs, d_o = upload(inp)
+    koffs, order = [w.k_offset(j) for j in range(n)], list(range(n))
+    args = (q, ks, vs, w.q_where, koffs, causal, w.scale)
+    o, lse, _ = st.st_ring_fwd(*args, order)
+    q_pos, k_pos = positions(w)
+    dq_r, _, _ = oa.attention_backward(inp.q, inp.k, inp.v, inp.d_o, q_pos, k_pos, causal, w.scale)
+    full = st.st_ring_workspace_bytes(*args, st.ST_RING_FUSED, True)
+    base = (w.Hq * Sq * 4 + 255) // 256 * 256 + 1024          # Delta and the counters, without partial sums
+    assert full - base >= 2 * q.numel() * 4, "this share was meant to split"
+
+    def run(workspace=None):
+        dq = torch.full_like(o, 1 / 64)
+        grads = (dq, [torch.zeros_like(k) for k in ks], [torch.zeros_like(v) for v in vs])
+        if workspace is None:
+            st.st_ring_bwd_noalloc(q, ks, vs, d_o, o, lse, *args[3:], order, *grads)
+        else:
+            st.st_ring_bwd(q, ks, vs, d_o, o, lse, *args[3:], order, *grads, workspace=workspace)
+        return dq
+
+    split, whole = (run(torch.full((n,), 0xff, dtype=torch.uint8, device="cuda")) for n in (full, base))   # 0xff..: NaN
+    for dq in (split, whole):
+        assert_close(host(dq) - 1 / 64, dq_r, "f32", "dq")    # the start costs 1e-9 per element
+    assert torch.equal(run(), split)
