@@ -28,8 +28,12 @@ constexpr int kRelMin = -(1 << 30);                  // relative position of a t
 
 // The tiles a workgroup walks, written to LDS by one wavefront, a lane per chunk of the table.  Entry (32 bytes): K and V
 // addresses, tiles, position of the first key relative to q_base, first key of the (single) tile that counts, pad.
-// Whole tiles of all chunks come first, then the masked ones; split y of n takes the tiles [T y / n, T (y + 1) / n) of the
-// T in that order.  Returns the tiles of the split; n_masked of them, the last ones, are masked; their entries start at
+// Whole tiles of all chunks come first, then the masked ones.  In that order split y of n takes an equal share of the work,
+// a masked tile counted as two whole ones: all of them are in the last splits, where they cost 0.5 to 1 us more each than a
+// whole tile's 1.4 (in the mask routine and in the second copy of the loop, which is fetched for them).  Shares of equal
+// tiles made the launch wait for the last split: 12 heads x 2 x 1000 rows in 3 splits 82 us, so 78.7 (dQ 105 and 102.5); 16 x
+// 2 x 512 rows at head size 64 30.7 and 29.0 (31.8 and 30.5); three units for a masked tile are as far off on the other side
+// (82.4, 107.5).  Returns the tiles of the split; n_masked of them, the last ones, are masked; their entries start at
 // first_masked.
 __device__ __forceinline__ int build_walk(const Shape& s, const ChunkTable& t, int splits, int row0, int b, int hk, int split, ST_LDS uint32_t* tbl, int lane,
                                           int& n_masked, int& first_masked) {
@@ -56,9 +60,13 @@ __device__ __forceinline__ int build_walk(const Shape& s, const ChunkTable& t, i
   int total_full, total_masked;
   const int pf = lane_scan(nf, lane, total_full);
   const int pm = total_full + lane_scan(nm + nr, lane, total_masked);
-  const int64_t total = (int64_t)total_full + total_masked;
   const int n_split = max(splits, 1);
-  const int lo = (int)(total * split / n_split), hi = (int)(total * (split + 1) / n_split);
+  const int64_t units = total_full + 2 * (int64_t)total_masked;
+  auto edge = [&](int y) {                           // tiles before unit [units y / n]
+    const int64_t u = units * y / n_split;
+    return (int)(u <= total_full ? u : total_full + (u - total_full) / 2);
+  };
+  const int lo = edge(split), hi = edge(split + 1);
   const int f0 = max(pf, lo), cf = max(min(pf + nf, hi) - f0, 0);
   const int m0 = max(pm, lo), cm = max(min(pm + nm, hi) - m0, 0);
   const int cr = nr && pm + nm >= lo && pm + nm < hi;
