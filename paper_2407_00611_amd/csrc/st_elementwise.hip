@@ -19,6 +19,21 @@ __device__ __forceinline__ uint32_t pack_bf16x2(float lo, float hi) {
 __device__ __forceinline__ float bf16_lo(uint32_t w) { return __uint_as_float(w << 16); }
 __device__ __forceinline__ float bf16_hi(uint32_t w) { return __uint_as_float(w & 0xffff0000u); }
 
+// (b, i, h) of row (b * S + i) * H + h of `rows`.  Two 64-bit divisions are some 300 instructions per lane, which
+// launches of a few megabytes do not hide; the rows of a tensor fit 32 bits but for the largest.
+struct RowOf {
+  int64_t b;
+  int32_t i, h;
+};
+__device__ __forceinline__ RowOf row_of(int64_t row, int64_t rows, int32_t S, int32_t H) {
+  if (rows <= 0x7fffffff) {
+    const uint32_t x = (uint32_t)row, bi = x / (uint32_t)H, b = bi / (uint32_t)S;
+    return RowOf{(int64_t)b, (int32_t)(bi - b * (uint32_t)S), (int32_t)(x - bi * (uint32_t)H)};
+  }
+  const int64_t bi = row / H;
+  return RowOf{bi / S, (int32_t)(bi % S), (int32_t)(row % H)};
+}
+
 // ---- merge: thread = up to U float4 of one (b, i, h) row ---------------------------------------
 // A row occupies a power-of-two group of lanes; lane `sub` of the group takes the vectors sub, sub + lanes, ...
 // of the row, so consecutive lanes read consecutive 16-byte pieces (whole 128-byte lines once the group has
@@ -37,9 +52,8 @@ __global__ __launch_bounds__(256) void merge_kernel(float* __restrict__ o_acc, f
   const int64_t row = tid >> lane_shift;               // (b * Sq + i) * Hq + h
   const int32_t sub = (int32_t)(tid & ((1 << lane_shift) - 1));
   if (row >= n_rows) return;
-  const int32_t h = (int32_t)(row % Hq);
-  const int64_t bi = row / Hq;
-  const int64_t sidx = ((bi / Sq) * Hq + h) * Sq + (bi % Sq);
+  const RowOf at = row_of(row, n_rows, Sq, Hq);
+  const int64_t sidx = (at.b * Hq + at.h) * Sq + at.i;
   const float la = lse_acc[sidx], lp = lse_part[sidx];
   int64_t v[U];
   bool live[U];
@@ -86,21 +100,21 @@ __global__ __launch_bounds__(256) void merge_kernel(float* __restrict__ o_acc, f
 // Thread = one float4 of one kept (b, i, h) row, lanes per row as in the merge.  The weights are
 // w_x = exp(lse_x - m) / sum_y exp(lse_y - m) with m the largest lse, so an empty state (lse = -inf)
 // weighs 0 and (-inf) - (-inf) is never formed; a row empty in every state gives O = 0, lse = -inf.
-// The O loads of kCombineUnroll states are in flight together.
+// kFew: at most that many states, each lse of which is read once and kept (0: any number, lse read three times, one wait
+// after the other).  O loads in flight together: all for up to 4 and 9 to 16 states, otherwise kCombineUnroll (8 states of
+// 8 x 1024 rows of 128: 12.0 us, 12.4 with all eight at once).  16 states of 4 x 256 rows, the split of a short shard: 17.5
+// us without their number known, 9.3 with it; of 8 x 1024 rows 21.7 and 18.5.
 constexpr int kCombineUnroll = 4;
-constexpr int kCombineFew = 2 * kCombineUnroll;
-
-template <bool kLowp, bool kFew>
+template <bool kLowp, int kFew>
 __global__ __launch_bounds__(256) void combine_kernel(const CombineArgs a, int32_t vec_per_row, int32_t lane_shift) {
   const int64_t tid = (int64_t)blockIdx.x * 256 + threadIdx.x;
   const int64_t row = tid >> lane_shift;               // (b * Sq_out + i) * Hq + h
   const int32_t sub = (int32_t)(tid & ((1 << lane_shift) - 1));
   const int64_t n_rows = (int64_t)a.B * a.Sq_out * a.Hq;
   if (row >= n_rows || sub >= vec_per_row) return;
-  const int32_t h = (int32_t)(row % a.Hq);
-  const int64_t bi = row / a.Hq;
-  const int64_t b = bi / a.Sq_out;
-  const int32_t i = (int32_t)(bi % a.Sq_out);
+  const RowOf at = row_of(row, n_rows, a.Sq_out, a.Hq);
+  const int64_t b = at.b;
+  const int32_t i = at.i, h = at.h;
   const int64_t l_in = (b * a.Hq + h) * a.Sq_in + a.row0 + i;
   const int64_t v_in = ((b * a.Sq_in + a.row0 + i) * a.Hq + h) * vec_per_row + sub;
 
@@ -120,33 +134,35 @@ __global__ __launch_bounds__(256) void combine_kernel(const CombineArgs a, int32
   };
   float4 r = make_float4(0.f, 0.f, 0.f, 0.f);
   float lnew = -INFINITY;
-  if (kFew) {
-    // up to kCombineFew states (a team): every lse is read once and kept, and the first O loads do not wait for them
-    float l[kCombineFew];
-    float4 p[kCombineUnroll];
+  if (kFew > 0) {
+    // every lse is read once and kept, and the first O loads do not wait for them
+    constexpr int N = kFew > 0 ? kFew : 1, U = N == 8 ? kCombineUnroll : N;
+    float l[N];
+    float4 p[U];
 #pragma unroll
-    for (int x = 0; x < kCombineFew; ++x) l[x] = x < a.n ? a.lse[x][l_in] : -INFINITY;
+    for (int x = 0; x < N; ++x) l[x] = x < a.n ? a.lse[x][l_in] : -INFINITY;
 #pragma unroll
-    for (int u = 0; u < kCombineUnroll; ++u) p[u] = load_o(u < a.n ? u : a.n - 1);
+    for (int u = 0; u < U; ++u) p[u] = load_o(u < a.n ? u : a.n - 1);
     float m = -INFINITY;
 #pragma unroll
-    for (int x = 0; x < kCombineFew; ++x) m = fmaxf(m, l[x]);
+    for (int x = 0; x < N; ++x) m = fmaxf(m, l[x]);
     if (m != -INFINITY) {
       float sum = 0.f;
 #pragma unroll
-      for (int x = 0; x < kCombineFew; ++x) {
+      for (int x = 0; x < N; ++x) {
         l[x] = expf(l[x] - m);                           // exp(-inf) = 0 for an empty state and for x >= n
         sum += l[x];
       }
       lnew = m + logf(sum);
       const float inv = 1.f / sum;
 #pragma unroll
-      for (int u = 0; u < kCombineUnroll; ++u) add(r, u < a.n ? l[u] * inv : 0.f, p[u]);
-      if (a.n > kCombineUnroll) {
+      for (int x0 = 0; x0 < N; x0 += U) {
 #pragma unroll
-        for (int u = 0; u < kCombineUnroll; ++u) p[u] = load_o(kCombineUnroll + u < a.n ? kCombineUnroll + u : a.n - 1);
+        for (int u = 0; u < U; ++u) {
+          if (x0 > 0) p[u] = load_o(x0 + u < a.n ? x0 + u : a.n - 1);
+        }
 #pragma unroll
-        for (int u = 0; u < kCombineUnroll; ++u) add(r, kCombineUnroll + u < a.n ? l[kCombineUnroll + u] * inv : 0.f, p[u]);
+        for (int u = 0; u < U; ++u) add(r, x0 + u < a.n ? l[x0 + u] * inv : 0.f, p[u]);
       }
     }
   } else {
@@ -191,12 +207,11 @@ __global__ __launch_bounds__(256) void delta_kernel(View d_o, View o, float* __r
   const int64_t row = ((int64_t)blockIdx.x * 256 + threadIdx.x) >> 4;
   const int sub = threadIdx.x & 15;
   const int64_t n_rows = (int64_t)B * Sq * Hq;
+  const RowOf at = row_of(row, n_rows, Sq, Hq);
+  const int64_t b = at.b;
+  const int32_t i = at.i, h = at.h;
   float acc = 0.f;
   if (row < n_rows) {
-    const int32_t h = (int32_t)(row % Hq);
-    const int64_t bi = row / Hq;
-    const int32_t i = (int32_t)(bi % Sq);
-    const int64_t b = bi / Sq;
     const int64_t off_d = b * d_o.sb + (int64_t)i * d_o.ss + (int64_t)h * d_o.sh;
     const int64_t off_o = b * o.sb + (int64_t)i * o.ss + (int64_t)h * o.sh;
     for (int d = sub * 8; d < D; d += 128) {           // 8 elements per lane per step
@@ -225,11 +240,7 @@ __global__ __launch_bounds__(256) void delta_kernel(View d_o, View o, float* __r
   }
 #pragma unroll
   for (int s = 8; s > 0; s >>= 1) acc += __shfl_xor(acc, s);
-  if (row < n_rows && sub == 0) {
-    const int32_t h = (int32_t)(row % Hq);
-    const int64_t bi = row / Hq;
-    delta[((bi / Sq) * Hq + h) * Sq + (bi % Sq)] = acc;
-  }
+  if (row < n_rows && sub == 0) delta[(b * Hq + h) * Sq + i] = acc;
 }
 
 // ---- backward preparation of a bf16 share in one pass: Delta, Q' = bf16(Q c), the tile counters of the dK/dV launch to zero.
@@ -242,11 +253,11 @@ __global__ __launch_bounds__(256) void bwd_prep_kernel(View d_o, View o, View q,
   const int64_t v = (int64_t)blockIdx.x * 256 + threadIdx.x;
   const int64_t row = v / LPR;
   const int d = (int)(v % LPR) * 8;
-  const bool live = row < (int64_t)B * Sq * Hq;
-  const int32_t h = (int32_t)(row % Hq);
-  const int64_t bi = row / Hq;
-  const int32_t i = (int32_t)(bi % Sq);
-  const int64_t b = bi / Sq;
+  const int64_t n_rows = (int64_t)B * Sq * Hq;
+  const bool live = row < n_rows;
+  const RowOf at = row_of(row, n_rows, Sq, Hq);
+  const int64_t b = at.b;
+  const int32_t i = at.i, h = at.h;
   float acc = 0.f;
   if (live) {
     const uint4 x = *reinterpret_cast<const uint4*>((const uint16_t*)d_o.ptr + b * d_o.sb + (int64_t)i * d_o.ss + (int64_t)h * d_o.sh + d);
@@ -290,12 +301,12 @@ __global__ __launch_bounds__(256) void scale_q_kernel(View q, u32x4* __restrict_
                                                       int32_t Hq, int32_t D, float c) {
   const int64_t v = (int64_t)blockIdx.x * 256 + threadIdx.x;
   const int32_t per_row = D / 8;
-  const int64_t row = v / per_row;
-  if (row >= (int64_t)B * Sq * Hq) return;
-  const int32_t chunk = (int32_t)(v % per_row);
-  const int32_t h = (int32_t)(row % Hq);
-  const int64_t bi = row / Hq;
-  const int64_t off = (bi / Sq) * q.sb + (bi % Sq) * q.ss + (int64_t)h * q.sh + chunk * 8;
+  const int64_t n_rows = (int64_t)B * Sq * Hq;
+  if (v >= n_rows * per_row) return;
+  const int64_t row = n_rows * per_row <= 0x7fffffff ? (int64_t)((uint32_t)v / (uint32_t)per_row) : v / per_row;
+  const int32_t chunk = (int32_t)(v - row * per_row);
+  const RowOf at = row_of(row, n_rows, Sq, Hq);
+  const int64_t off = at.b * q.sb + at.i * q.ss + at.h * q.sh + chunk * 8;
   dst[v] = scale_bf16x8(*reinterpret_cast<const u32x4*>((const uint16_t*)q.ptr + off), c);
 }
 
@@ -404,17 +415,26 @@ hipError_t launch_combine(const CombineArgs& a, int lowp_dtype, hipStream_t s) {
   if (n_vec == 0) return hipSuccess;
   int lane_shift = 0;
   while ((1 << lane_shift) < a.D / 4) ++lane_shift;
-  const unsigned blocks = blocks_for(n_rows << lane_shift);
+  const dim3 grid(blocks_for(n_rows << lane_shift)), block(256);
+  const bool lowp = a.o_lowp != nullptr && lowp_dtype == ST_BF16;
   ProfScope prof("combine", s);
-  if (a.o_lowp != nullptr && lowp_dtype == ST_BF16) {
-    if (a.n <= kCombineFew) hipLaunchKernelGGL((combine_kernel<true, true>), dim3(blocks), dim3(256), 0, s, a, a.D / 4, lane_shift);
-    else hipLaunchKernelGGL((combine_kernel<true, false>), dim3(blocks), dim3(256), 0, s, a, a.D / 4, lane_shift);
-    return hipGetLastError();
+#define ST_LAUNCH_COMBINE(LOWP, FEW) hipLaunchKernelGGL((combine_kernel<LOWP, FEW>), grid, block, 0, s, a, a.D / 4, lane_shift)
+  if (a.n <= 4) {
+    if (lowp) ST_LAUNCH_COMBINE(true, 4);
+    else ST_LAUNCH_COMBINE(false, 4);
+  } else if (a.n <= 8) {
+    if (lowp) ST_LAUNCH_COMBINE(true, 8);
+    else ST_LAUNCH_COMBINE(false, 8);
+  } else if (a.n <= 16) {
+    if (lowp) ST_LAUNCH_COMBINE(true, 16);
+    else ST_LAUNCH_COMBINE(false, 16);
+  } else {
+    if (lowp) ST_LAUNCH_COMBINE(true, 0);
+    else ST_LAUNCH_COMBINE(false, 0);
   }
-  if (a.n <= kCombineFew) hipLaunchKernelGGL((combine_kernel<false, true>), dim3(blocks), dim3(256), 0, s, a, a.D / 4, lane_shift);
-  else hipLaunchKernelGGL((combine_kernel<false, false>), dim3(blocks), dim3(256), 0, s, a, a.D / 4, lane_shift);
+#undef ST_LAUNCH_COMBINE
   hipError_t e = hipGetLastError();
-  if (e == hipSuccess && a.o_lowp != nullptr) {
+  if (e == hipSuccess && a.o_lowp != nullptr && !lowp) {
     hipLaunchKernelGGL(copy_f32_kernel, dim3(blocks_for(n_vec)), dim3(256), 0, s, (const float4*)a.o_out,
                        (float4*)a.o_lowp, n_vec);
     e = hipGetLastError();
