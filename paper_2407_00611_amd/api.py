@@ -139,15 +139,18 @@ def _torch_dtype(code: int):
 
 
 def _view(t: torch.Tensor) -> st_tensor:
-    if t.dim() != 4:
+    stride = t.stride()
+    if len(stride) != 4:
         raise ValueError("expected a [B, S, heads, D] tensor")
-    if t.shape[3] > 1 and t.stride(3) != 1:
+    if stride[3] != 1 and t.shape[3] > 1:
         raise ValueError("the D dimension must be contiguous")
-    return st_tensor(t.data_ptr() if t.numel() else None, t.stride(0), t.stride(1), t.stride(2))
+    return st_tensor(t.data_ptr() if t.numel() else None, stride[0], stride[1], stride[2])
 
 
 def _stream(stream) -> C.c_void_p:
     if stream is None:
+        if torch.cuda.is_initialized():          # the handle alone, without a Stream object around it
+            return C.c_void_p(torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice()))
         stream = torch.cuda.current_stream()
     return C.c_void_p(stream.cuda_stream if hasattr(stream, "cuda_stream") else int(stream))
 
@@ -163,7 +166,7 @@ def _aligned(buf: torch.Tensor, a: int) -> Tuple[int, int]:
 
 
 def _f32_dense(t: torch.Tensor, shape, name: str) -> torch.Tensor:
-    if t.dtype != torch.float32 or tuple(t.shape) != tuple(shape) or not t.is_contiguous():
+    if t.dtype != torch.float32 or t.shape != shape or not t.is_contiguous():
         raise ValueError(f"{name} must be a contiguous fp32 tensor of shape {tuple(shape)}")
     return t
 
@@ -313,9 +316,10 @@ def st_attn_block_bwd(q, k, v, d_o, lse_final, delta, q_offset: int, k_offset: i
     _f32_dense(dk_acc, (B, Sk, Hkv, D), "dk_acc"); _f32_dense(dv_acc, (B, Sk, Hkv, D), "dv_acc")
     d = _block_desc(q, k, q_offset, k_offset, causal, scale)
     tq, tk, tv, td = _view(q), _view(k), _view(v), _view(d_o)
-    need = int(_lib.st_attn_block_bwd_workspace_bytes(C.byref(d)))
-    if workspace is None and need > 0:
-        workspace = torch.empty(need + 256, dtype=torch.uint8, device=q.device)
+    if workspace is None:
+        need = int(_lib.st_attn_block_bwd_workspace_bytes(C.byref(d)))
+        if need > 0:
+            workspace = torch.empty(need + 256, dtype=torch.uint8, device=q.device)
     ws_ptr, ws_bytes = (None, 0) if workspace is None or workspace is False else _aligned(workspace, 256)
     _check(_lib.st_attn_block_bwd(C.byref(d), C.byref(tq), C.byref(tk), C.byref(tv), C.byref(td), _ptr(lse_final),
                                   _ptr(delta), _ptr(dq_acc), _ptr(dk_acc), _ptr(dv_acc), C.c_void_p(ws_ptr), ws_bytes,
@@ -365,20 +369,20 @@ class _Ring:
             raise ValueError("need one K, one V and one offset per chunk")
         B, Sq, Hq, D = q.shape
         k0, v0 = k_chunks[0], v_chunks[0]
+        shape, k_stride, v_stride, dtype = k0.shape, k0.stride(), v0.stride(), q.dtype
         for k, v in zip(k_chunks, v_chunks):
-            if k.shape != k0.shape or v.shape != k0.shape or k.stride() != k0.stride() or v.stride() != v0.stride() \
-                    or k.dtype != q.dtype or v.dtype != q.dtype:
+            if k.shape != shape or v.shape != shape or k.stride() != k_stride or v.stride() != v_stride \
+                    or k.dtype != dtype or v.dtype != dtype:
                 raise ValueError("all chunks must share shape, strides and dtype")
-            _view(k), _view(v)
+            if k is k0:
+                _view(k), _view(v)                # the others have the shape and the strides of these
         self.k_ptr = (C.c_void_p * n)(*[k.data_ptr() for k in k_chunks])
         self.v_ptr = (C.c_void_p * n)(*[v.data_ptr() for v in v_chunks])
         self.k_off = (C.c_int64 * n)(*[int(x) for x in k_offsets])
         off, seg, off2 = _q_runs(q_offset)
-        self.desc = st_ring_desc(_dtype_code(q), B, Hq, k0.shape[2], D, Sq, k0.shape[1], off,
-                                 1 if causal else 0, float(scale), n,
-                                 C.cast(self.k_ptr, C.POINTER(C.c_void_p)), C.cast(self.v_ptr, C.POINTER(C.c_void_p)),
-                                 k0.stride(0), k0.stride(1), k0.stride(2), v0.stride(0), v0.stride(1), v0.stride(2),
-                                 C.cast(self.k_off, C.POINTER(C.c_int64)), seg, off2)
+        self.desc = st_ring_desc(_dtype_code(q), B, Hq, shape[2], D, Sq, shape[1], off, 1 if causal else 0, float(scale), n,
+                                 self.k_ptr, self.v_ptr, k_stride[0], k_stride[1], k_stride[2], v_stride[0], v_stride[1],
+                                 v_stride[2], self.k_off, seg, off2)
 
 
 def st_ring_workspace_bytes(q, k_chunks, v_chunks, q_offset, k_offsets, causal, scale, mode: int,
@@ -405,8 +409,8 @@ def st_ring_fwd(q, k_chunks, v_chunks, q_offset: int, k_offsets: Sequence[int], 
         _f32_dense(lse, (B, Hq, Sq), "lse")
     if o_lowp is None and want_lowp:
         o_lowp = torch.empty((B, Sq, Hq, D), dtype=q.dtype, device=q.device)
-    need = int(_lib.st_ring_workspace_bytes(C.byref(r.desc), mode, 0))
     if workspace is None:
+        need = int(_lib.st_ring_workspace_bytes(C.byref(r.desc), mode, 0))
         workspace = torch.empty(need + 256, dtype=torch.uint8, device=q.device)
     ws_ptr = (workspace.data_ptr() + 255) // 256 * 256
     ws_bytes = workspace.numel() * workspace.element_size() - (ws_ptr - workspace.data_ptr())
@@ -431,15 +435,15 @@ def st_ring_bwd(q, k_chunks, v_chunks, d_o, o, lse_final, q_offset: int, k_offse
             _f32_dense(t, kv_shape, "dk_acc/dv_acc entry")
     dk_ptr = (C.c_void_p * n)(*[(t.data_ptr() if t is not None else None) for t in dk_acc])
     dv_ptr = (C.c_void_p * n)(*[(t.data_ptr() if t is not None else None) for t in dv_acc])
-    need = int(_lib.st_ring_workspace_bytes(C.byref(r.desc), mode, 1))
     if workspace is None:
+        need = int(_lib.st_ring_workspace_bytes(C.byref(r.desc), mode, 1))
         workspace = torch.empty(need + 256, dtype=torch.uint8, device=q.device)
     ws_ptr = (workspace.data_ptr() + 255) // 256 * 256
     ws_bytes = workspace.numel() * workspace.element_size() - (ws_ptr - workspace.data_ptr())
     tq, td, to = _view(q), _view(d_o), _view(o)
     _check(_lib.st_ring_bwd(C.byref(r.desc), C.byref(tq), C.byref(td), C.byref(to), _dtype_code(o), _ptr(lse_final),
                             _i32_array(order), len(order), mode, _ptr(dq_acc),
-                            C.cast(dk_ptr, C.POINTER(C.c_void_p)), C.cast(dv_ptr, C.POINTER(C.c_void_p)),
+                            dk_ptr, dv_ptr,
                             C.c_void_p(ws_ptr), ws_bytes, _stream(stream)), "st_ring_bwd")
 
 
@@ -464,7 +468,7 @@ def st_ring_bwd_noalloc(q, k_chunks, v_chunks, d_o, o, lse_final, q_offset: int,
     tq, td, to = _view(q), _view(d_o), _view(o)
     _check(_lib.st_ring_bwd_noalloc(C.byref(r.desc), C.byref(tq), C.byref(td), C.byref(to), _dtype_code(o),
                                     _ptr(lse_final), _i32_array(order), len(order), mode, _ptr(dq_acc),
-                                    C.cast(dk_ptr, C.POINTER(C.c_void_p)), C.cast(dv_ptr, C.POINTER(C.c_void_p)),
+                                    dk_ptr, dv_ptr,
                                     _stream(stream)), "st_ring_bwd_noalloc")
 
 
@@ -487,24 +491,22 @@ def st_ring_bwd_last(q, k_chunks, v_chunks, d_o, o, lse_final, q_offset: int, k_
         if ts is None:
             return None
         for t in ts:
-            if t is not None and not (t.is_cuda and t.is_contiguous() and t.dtype == q.dtype and tuple(t.shape) == kv_shape):
+            if t is not None and not (t.is_cuda and t.is_contiguous() and t.dtype == q.dtype and t.shape == kv_shape):
                 raise ValueError("dk_lowp/dv_lowp entry: expected a dense device tensor shaped like a chunk, in the dtype of q")
         return (C.c_void_p * n)(*[(t.data_ptr() if t is not None else None) for t in ts])
 
     dk_ptr, dv_ptr = _ptr_table(dk_acc, n), _ptr_table(dv_acc, n)
     lk, lv = table(dk_lowp), table(dv_lowp)
-    need = int(_lib.st_ring_workspace_bytes(C.byref(r.desc), mode, 1))
     if workspace is None:
+        need = int(_lib.st_ring_workspace_bytes(C.byref(r.desc), mode, 1))
         workspace = torch.empty(need + 256, dtype=torch.uint8, device=q.device)
     ws_ptr = (workspace.data_ptr() + 255) // 256 * 256
     ws_bytes = workspace.numel() * workspace.element_size() - (ws_ptr - workspace.data_ptr())
     tq, td, to = _view(q), _view(d_o), _view(o)
-    vpp = C.POINTER(C.c_void_p)
     _check(_lib.st_ring_bwd_last(C.byref(r.desc), C.byref(tq), C.byref(td), C.byref(to), _dtype_code(o), _ptr(lse_final),
-                                 _i32_array(order), len(order), mode, _ptr(dq_acc), C.cast(dk_ptr, vpp), C.cast(dv_ptr, vpp),
-                                 ST_KV_ASSIGN if assign else 0, C.cast(lk, vpp) if lk is not None else None,
-                                 C.cast(lv, vpp) if lv is not None else None,
-                                 C.c_void_p(ws_ptr), ws_bytes, _stream(stream)), "st_ring_bwd_last")
+                                 _i32_array(order), len(order), mode, _ptr(dq_acc), dk_ptr, dv_ptr,
+                                 ST_KV_ASSIGN if assign else 0, lk, lv, C.c_void_p(ws_ptr), ws_bytes, _stream(stream)),
+           "st_ring_bwd_last")
 
 
 def _ptr_table(ts, n):
