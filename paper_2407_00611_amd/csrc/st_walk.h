@@ -12,21 +12,25 @@ namespace {
 __device__ __forceinline__ uint32_t sgpr(uint32_t x) { return __builtin_amdgcn_readfirstlane(x); }
 __device__ __forceinline__ uint32_t lo32(const void* p) { return (uint32_t)(uintptr_t)p; }
 __device__ __forceinline__ uint32_t hi32(const void* p) { return (uint32_t)((uintptr_t)p >> 32); }
-// sum over the lanes before this one; total = sum over all lanes
-__device__ __forceinline__ int lane_scan(int x, int lane, int& total) {
+// sum over the lanes before this one; total = sum over all 64 (all of them active).  Data parallel primitives: a scan by
+// shuffles waits for LDS six times, which is time no other wavefront of the workgroup has work for.
+__device__ __forceinline__ int lane_scan(int x, int& total) {
   int sum = x;
-#pragma unroll
-  for (int d = 1; d < 64; d *= 2) {
-    const int y = __shfl_up(sum, d);
-    if (lane >= d) sum += y;
-  }
-  total = __shfl(sum, 63);
+  sum += __builtin_amdgcn_update_dpp(0, sum, 0x111, 0xf, 0xf, false);      // row_shr:1, inside the rows of 16
+  sum += __builtin_amdgcn_update_dpp(0, sum, 0x112, 0xf, 0xf, false);
+  sum += __builtin_amdgcn_update_dpp(0, sum, 0x114, 0xf, 0xf, false);
+  sum += __builtin_amdgcn_update_dpp(0, sum, 0x118, 0xf, 0xf, false);
+  sum += __builtin_amdgcn_update_dpp(0, sum, 0x142, 0xa, 0xf, false);      // row_bcast:15 into rows 1 and 3
+  sum += __builtin_amdgcn_update_dpp(0, sum, 0x143, 0xc, 0xf, false);      // row_bcast:31 into rows 2 and 3
+  total = __builtin_amdgcn_readlane(sum, 63);
   return sum - x;
 }
 
 constexpr int kRelMin = -(1 << 30);                  // relative position of a tile that no causal mask touches
 
-// The tiles a workgroup walks, written to LDS by one wavefront, a lane per chunk of the table.  Entry (32 bytes): K and V
+// The tiles a workgroup walks, written to LDS by one wavefront, a lane per chunk of the table, while the others wait: a chain
+// of latencies at the start of every workgroup (2.8 us of a 25 us launch with shuffles, 64-bit divisions and loads behind
+// the table's length; 2.1 us so).  Entry (32 bytes): K and V
 // addresses, tiles, position of the first key relative to q_base, first key of the (single) tile that counts, pad.
 // Whole tiles of all chunks come first, then the masked ones.  In that order split y of n takes an equal share of the work,
 // a masked tile counted as two whole ones: all of them are in the last splits, where they cost 0.5 to 1 us more each than a
@@ -39,34 +43,30 @@ __device__ __forceinline__ int build_walk(const Shape& s, const ChunkTable& t, i
                                           int& n_masked, int& first_masked) {
   constexpr int BM = kQTileFastRows, BN = kQTileFastKeys;
   const int n64 = s.Sk / BN;
-  const int64_t q_base = q_pos(s, row0), q_last = q_pos(s, min(row0 + BM, s.Sq) - 1);
-  int nf = 0, nm = 0, nr = 0;                        // whole tiles, masked tiles, ragged end (0 or 1)
-  const char *kp = nullptr, *vp = nullptr;
-  int64_t rel0 = 0;
-  if (lane < t.n) {
-    const int64_t k0 = t.k_offset[lane];
-    kp = (const char*)t.k[lane] + ((int64_t)b * t.ksb + (int64_t)hk * t.ksh) * 2;
-    vp = (const char*)t.v[lane] + ((int64_t)b * t.vsb + (int64_t)hk * t.vsh) * 2;
-    int64_t nv = s.Sk, nv_last = s.Sk;               // keys the first / last row sees
-    if (s.causal) {
-      rel0 = k0 - q_base;
-      nv = min(max(q_base - k0 + 1, (int64_t)0), (int64_t)s.Sk);
-      nv_last = min(max(q_last - k0 + 1, (int64_t)0), (int64_t)s.Sk);
-    }
-    nf = (int)nv / BN;
-    nm = max(min(((int)nv_last + BN - 1) / BN, n64) - nf, 0);
-    nr = nv_last > (int64_t)n64 * BN;
-  }
+  static_assert(kMaxTable == 64, "a lane per chunk");
+  // the whole table is read, so that the loads need not wait for its length (arguments come from host memory)
+  const int64_t k0 = t.k_offset[lane];
+  const char* kp = (const char*)t.k[lane] + ((int64_t)b * t.ksb + (int64_t)hk * t.ksh) * 2;
+  const char* vp = (const char*)t.v[lane] + ((int64_t)b * t.vsb + (int64_t)hk * t.vsh) * 2;
+  const int64_t q_base = q_pos(s, row0), q_last = q_pos(s, min(row0 + BM, s.Sq) - 1), rel0 = k0 - q_base;
+  const int64_t nv = s.causal ? min(max(q_base - k0 + 1, (int64_t)0), (int64_t)s.Sk) : s.Sk;       // keys the first row sees
+  const int64_t nv_last = s.causal ? min(max(q_last - k0 + 1, (int64_t)0), (int64_t)s.Sk) : s.Sk;  // and the last one
+  const bool listed = lane < t.n;
+  const int nf = listed ? (int)nv / BN : 0;                                                        // whole tiles
+  const int nm = listed ? max(min(((int)nv_last + BN - 1) / BN, n64) - nf, 0) : 0;                 // masked tiles
+  const int nr = listed && nv_last > (int64_t)n64 * BN;                                            // ragged end (0 or 1)
   int total_full, total_masked;
-  const int pf = lane_scan(nf, lane, total_full);
-  const int pm = total_full + lane_scan(nm + nr, lane, total_masked);
-  const int n_split = max(splits, 1);
-  const int64_t units = total_full + 2 * (int64_t)total_masked;
-  auto edge = [&](int y) {                           // tiles before unit [units y / n]
-    const int64_t u = units * y / n_split;
-    return (int)(u <= total_full ? u : total_full + (u - total_full) / 2);
-  };
-  const int lo = edge(split), hi = edge(split + 1);
+  const int pf = lane_scan(nf, total_full);
+  const int pm = total_full + lane_scan(nm + nr, total_masked);
+  int lo = 0, hi = total_full + total_masked;
+  if (splits > 1) {
+    const uint32_t units = (uint32_t)total_full + 2 * (uint32_t)total_masked, each = units / splits, rest = units % splits;
+    auto edge = [&](uint32_t y) {                    // tiles before unit [units y / splits]
+      const uint32_t u = each * y + rest * y / (uint32_t)splits;
+      return (int)(u <= (uint32_t)total_full ? u : total_full + (u - total_full) / 2);
+    };
+    lo = edge(split), hi = edge(split + 1);
+  }
   const int f0 = max(pf, lo), cf = max(min(pf + nf, hi) - f0, 0);
   const int m0 = max(pm, lo), cm = max(min(pm + nm, hi) - m0, 0);
   const int cr = nr && pm + nm >= lo && pm + nm < hi;
