@@ -1,6 +1,7 @@
 // C-ABI layer: argument validation, dtype dispatch, the visit-order generator and the
 // driver that walks a chunk-visit order.  No arithmetic of the method lives here; every
 // step of the path runs in the HIP kernels behind the launch_* functions.
+#include <algorithm>
 #include <cstdarg>
 #include <cstdio>
 #include <cstring>
@@ -174,6 +175,8 @@ constexpr int kMaxSplits = 16;
 // takes (the two passes run one after the other and share them).
 struct BwdSplit {
   int dq = 1, kv = 1;
+  int parts = 0;         // dQ shares whose sums are stored, see BwdArgs
+  bool pair = false;
   size_t bytes = 0;
 };
 // dQ: the forward's model (rounds of workgroups x time of one + the pass that adds up); a 256 x 64 tile is three
@@ -199,23 +202,31 @@ bool bwd_half(const st::Shape& s, const int64_t* k_offset, int n) {
 BwdSplit bwd_splits(const st::Shape& s, int dtype, int n, bool half, size_t room, bool split_dq = true) {
   BwdSplit r;
   const bool bf16 = dtype == ST_BF16;
+  int64_t dq_tiles = 0;
+  double dq_us = 0, dq_tile_us = 0, part_us = 0;
   if ((bf16 && s.D != 128 && s.D != 64) || n < 1 || n > st::kMaxTable || s.B < 1 || s.Sq < 1 || s.Sk < 1 || s.Hq < 1 || s.Hkv < 1) return r;
   const bool d128 = s.D == 128;
   const int rows = bf16 ? st::kQTileFastRows : 32, keys = bf16 ? st::kQTileFastKeys : s.D <= 128 ? 256 : 128;
   const int64_t wgs = (int64_t)s.B * s.Hq * ((s.Sq + rows - 1) / rows);
+  const size_t n_o = (size_t)st::dq_part_floats(s) * sizeof(float);
+  auto set_dq = [&](int x) {
+    r.dq = x;
+    r.parts = x == 1 ? 0 : (size_t)x * n_o > room ? x - 1 : x;
+    r.bytes = (size_t)r.parts * n_o;
+  };
   if (split_dq && wgs < 512 && (!bf16 || s.Sk >= keys)) {
     const int64_t tiles = bf16 ? (int64_t)n * ((s.Sk + keys - 1) / keys) : ((int64_t)n * ((s.Sk + 31) / 32) * 32 + keys - 1) / keys;
-    const size_t n_o = (size_t)st::dq_part_floats(s) * sizeof(float);
     const double tile_us = bf16 ? (d128 ? 2.4 : 1.4) : 2 + (s.D <= 128 ? 0.11 : 0.055) * s.D, fixed_us = 10, state_us = (double)n_o / 4e6, add_us = bf16 ? 6 : 10;
+    dq_tiles = tiles, dq_tile_us = tile_us, part_us = state_us;
     double best = (double)((wgs + 255) / 256) * (fixed_us + tiles * tile_us);
-    for (int x = 2; x <= kMaxSplits && x <= tiles && (size_t)x * n_o <= room; ++x) {
+    for (int x = 2; x <= kMaxSplits && x <= tiles && (size_t)(x - 1) * n_o <= room; ++x) {
       const double t = (double)((wgs * x + 255) / 256) * (fixed_us + (double)((tiles + x - 1) / x) * tile_us) + add_us + (x + 2) * state_us;
       if (t < 0.95 * best) {
         best = t;
-        r.dq = x;
-        r.bytes = (size_t)x * n_o;
+        set_dq(x);
       }
     }
+    dq_us = best;
   }
   const int64_t key_tiles = (int64_t)s.B * s.Hkv * n * ((s.Sk + st::kDkvFastKeys - 1) / st::kDkvFastKeys);
   if (bf16 && key_tiles < 512) {
@@ -237,13 +248,38 @@ BwdSplit bwd_splits(const st::Shape& s, int dtype, int n, bool half, size_t room
         if ((size_t)(x - 1) * kv > r.bytes) r.bytes = (size_t)(x - 1) * kv;
       }
     }
+    // Both passes in one launch: the compute units that have no key tile, or one less than others, take shares of the dQ
+    // pass meanwhile.  The launch ends at the first time by which all shares fit in; only multiples of a share's time from
+    // where a compute unit is done with its key tiles come into question.  Forward and backward, apart and together: 4 heads x
+    // 700 rows x 4 chunks 99 and 77 us, 12 heads of 64 x 800 rows x 4 chunks 96 and 88 us, 6 heads x 1500 rows x 4 chunks 146
+    // and 116 us.  Launches of 512 key tiles and more (the queue) and split key tiles fill the chip by themselves.
+    if (r.kv == 1 && dq_tiles > 6) {
+      const double one = fixed_us + (double)(blocks * G) * step_us;
+      const int64_t late_cus = key_tiles % 256;            // have a key tile more than the others
+      const double early = (double)(key_tiles / 256) * one, late = early + one, end = late_cus ? late : early;
+      double least = 0.95 * (best + 4 + dq_us);
+      for (int x = 1; x <= kMaxSplits && x <= dq_tiles && (size_t)(x - 1) * n_o <= room; ++x) {
+        const double share = 10 + (double)((dq_tiles + x - 1) / x) * dq_tile_us, add = x > 1 ? 6 + (x + 2) * part_us : 0;
+        for (int j = 1; early + j * share + add < least; ++j)
+          for (const double from : {early, late}) {
+            const double t = std::max(end, from + j * share);
+            const int64_t fit = (256 - late_cus) * (int64_t)((t - early) / share + 1e-6) + late_cus * (int64_t)(std::max(t - late, 0.0) / share + 1e-6);
+            if (t + add >= least || fit < wgs * x) continue;
+            least = t + add;
+            r.pair = true;
+            set_dq(x);
+          }
+      }
+    }
   }
   return r;
 }
 size_t most_bytes(const BwdSplit& x, const BwdSplit& y) { return x.bytes > y.bytes ? x.bytes : y.bytes; }
 void set_splits(st::BwdArgs& a, const BwdSplit& x, void* parts) {
   a.n_split = x.dq;
+  a.n_parts = x.parts;
   a.kv_split = x.kv;
+  a.pair = x.pair;
   a.parts = (float*)parts;
 }
 void set_table_strides(st::ChunkTable& t, const st_ring_desc* d) {

@@ -419,9 +419,10 @@ __global__ __launch_bounds__(waves<DP>() * 64) void bwd_dq_f32_kernel(const BwdA
     __syncthreads();
   }
   if (wave != 0 || row0 + r >= s.Sq) return;
-  const bool part = n_split > 1;                              // a partial sum (its memory holds nothing yet), not dq itself
+  const int first_part = n_split - a.n_parts;
+  const bool part = (int)blockIdx.y >= first_part;                            // a partial sum (its memory holds nothing yet), not dq itself
   if (empty && !part) return;
-  float* dq = (part ? a.parts + blockIdx.y * dq_part_floats(s) : a.dq) + (((int64_t)b * s.Sq + row0 + r) * s.Hq + h) * s.D;
+  float* dq = (part ? a.parts + (int64_t)((int)blockIdx.y - first_part) * dq_part_floats(s) : a.dq) + (((int64_t)b * s.Sq + row0 + r) * s.Hq + h) * s.D;
 #pragma unroll
   for (int db = 0; db < DB; ++db)
 #pragma unroll
@@ -615,8 +616,8 @@ hipError_t launch_bwd_f32(const BwdArgs& a, hipStream_t stream) {
       hipLaunchKernelGGL((bwd_dq_f32_kernel<DP, FULL>), grid, dim3(waves<DP>() * 64), 0, stream, a);
     }
     hipError_t e = hipGetLastError();
-    if (e == hipSuccess && a.n_split > 1)
-      e = launch_add_parts(a.dq, a.parts, a.n_split, dq_part_floats(a.s), (int64_t)a.s.B * a.s.Sq * a.s.Hq * a.s.D, stream);
+    if (e == hipSuccess && a.n_parts > 0)
+      e = launch_add_parts(a.dq, a.parts, a.n_parts, dq_part_floats(a.s), (int64_t)a.s.B * a.s.Sq * a.s.Hq * a.s.D, stream);
     if (e != hipSuccess) return e;
     ProfScope prof("bwd_dkv_f32", stream);
     const dim3 grid((a.s.Sk + kT - 1) / kT, a.s.Hkv, a.s.B * a.t.n);

@@ -85,13 +85,16 @@ struct BwdArgs {
   float* dk[kMaxTable];  // fp32 [B,Sk,Hkv,D] per table entry, +=
   float* dv[kMaxTable];
   // Under-filled dQ launches of the hand-scheduled and of the fp32 kernel: n_split > 1 gives every query tile n_split workgroups
-  // (blockIdx.y), each storing the sum over its share of the tiles at parts + y * part_floats(dq) (laid out as dq); the
-  // launcher then adds them to dq in order.
-  int32_t n_split;
+  // (blockIdx.y), each with a share of the tiles.  The last n_parts of them store their sums at parts + (0, 1, ...) *
+  // part_floats(dq) (laid out as dq), and the launcher then adds these to dq in order.  n_parts is 0 unsplit and n_split
+  // otherwise, or n_split - 1 where the workspace has no room for one more: then number 0 adds to dq itself, and its reads
+  // end the launch 2 us later.
+  int32_t n_split, n_parts;
   // Under-filled dK/dV launches likewise: kv_split > 1 gives every key tile kv_split workgroups, each with a share of the
   // query blocks.  The first one writes dk[c] / dv[c]; number y stores its sums at parts + ((2 (y - 1) + (0: dK, 1: dV)) *
   // t.n + c) * part_floats(dk[c]) (laid out as dk[c]), and the launcher adds them up (and rounds) in order.
   int32_t kv_split;
+  int32_t pair;        // 1: both passes in one launch, where the hand-scheduled kernels take both (kv_split <= 1)
   float* parts;        // the two passes use it one after the other
   // dK / dV work of a chunk's last visit folded into the launch (bf16 path): the hand-scheduled kernel's epilogue does it,
   // beside the general kernel the launcher runs fill and cast launches
@@ -174,6 +177,7 @@ hipError_t launch_fwd_fast(const FwdArgs& a, hipStream_t s);
 hipError_t launch_bwd_bf16(const BwdArgs& a, hipStream_t s);
 bool dkv_fast_usable(const BwdArgs& a);
 hipError_t launch_bwd_dkv_fast(const BwdArgs& a, hipStream_t s);
+hipError_t launch_bwd_pair_fast(const BwdArgs& a, hipStream_t s);   // both, kv_split <= 1
 bool dq_fast_usable(const BwdArgs& a);
 hipError_t launch_bwd_dq_fast(const BwdArgs& a, hipStream_t s);
 

@@ -110,7 +110,8 @@ def test_backward_at_tile_edges(c, how):
 
 def test_backward_split_over_workgroups():
     """One head against 60 tiles: the dQ pass is split, and its sums are the same from call to call and from st_ring_bwd to
-    st_ring_bwd_noalloc; with a workspace of the unsplit size it runs unsplit."""
+    st_ring_bwd_noalloc; with a workspace of the unsplit size it runs unsplit, with room for one partial sum its first
+    share adds to dq itself."""
     w = si.Workload("split_bwd", 332, "bf16", 1, 2, 1, 128, 300, 640, 6, 6 * 640 - 300, True, True)
     inp = si.make_inputs(w)
     _backward(w, inp, st.ST_RING_FUSED)
@@ -120,10 +121,11 @@ def test_backward_split_over_workgroups():
     order = list(range(w.n_chunks))
     need = st.st_ring_workspace_bytes(q, ks, vs, *args, st.ST_RING_FUSED, True)
     n_o = (q.numel() * 4 + 255) // 256 * 256
-    assert need > 2 * n_o
+    base = (w.Hq * w.Sq * 4 + 255) // 256 * 256 + 1024 + n_o // 2       # Delta, the counters, the scaled copy of Q
+    assert need > base + n_o
     o, lse, low = st.st_ring_fwd(q, ks, vs, *args, order)
     got = []
-    for ws in (None, None, "noalloc", need % n_o + n_o):
+    for ws in (None, None, "noalloc", base, base + n_o):
         dq = torch.zeros_like(o)
         dk = [torch.zeros(k.shape, device="cuda") for k in ks]
         dv = [torch.zeros(k.shape, device="cuda") for k in ks]
@@ -135,6 +137,7 @@ def test_backward_split_over_workgroups():
         got.append(dq)
     assert torch.equal(got[0], got[1]) and torch.equal(got[0], got[2])
     assert_close(host(got[3]), host(got[0]), "bf16", "dq unsplit")
+    assert_close(host(got[4]), host(got[0]), "bf16", "dq of two shares and one partial sum")
 
 
 @pytest.mark.parametrize("how", ["add", "assign", "add_lowp", "stepwise"])
@@ -193,3 +196,32 @@ def test_listed_chunks_that_nobody_sees(assign):
             assert_close_wide(host(x) - (0.0 if assign else 1.25), r, f"chunk {j}")
             if j > 1:
                 assert (x == (0.0 if assign else 1.25)).all()
+
+
+@pytest.mark.parametrize("D,n,Sk", [(128, 64, 70), (64, 33, 64), (128, 17, 130)])
+def test_walk_of_many_chunks(D, n, Sk):
+    """A lane per chunk builds the walk: sums over all 64 lanes, over a row of 16 and one lane more, over two rows and one;
+    the shard sits where the first chunks are seen whole, the middle ones in part and the last ones not at all."""
+    w = si.Workload("many_chunks", 340, "bf16", 1, 1, 1, D, 300, Sk, n, (n // 2) * Sk + 13, True, False)
+    print(f"[many chunks] D={D} n={n} Sk={Sk}", flush=True)
+    rng = np.random.default_rng(n)
+    _check(w, si.make_inputs(w), [list(range(n)), [int(x) for x in rng.permutation(n)]], args=("bf16",))
+
+
+#       D, Hq, Hkv, Sq, Sk, n, q_offset, causal, (q_seg, q_offset2)
+PAIRS = [(128, 4, 4, 300, 700, 4, 3 * 700 + 400, True, (0, 0)),
+         (128, 6, 2, 200, 513, 6, 0, False, (0, 0)),
+         (64, 4, 4, 333, 500, 6, 1700, True, (0, 0)),               # the last chunks are hidden
+         (64, 8, 8, 260, 600, 4, 500, True, (130, 1500))]           # two runs of rows
+
+
+@pytest.mark.parametrize("how", ["add", "assign", "add_lowp"])
+@pytest.mark.parametrize("c", PAIRS, ids=[f"d{c[0]}_q{c[3]}_k{c[4]}" for c in PAIRS])
+def test_both_backward_passes_in_one_launch(c, how):
+    """Few key tiles with short walks leave compute units for the dQ pass beside them: one launch holds both."""
+    D, Hq, Hkv, Sq, Sk, n, q0, causal, (seg, q2) = c
+    w = si.Workload("pair", 341, "bf16", 1, Hq, Hkv, D, Sq, Sk, n, q0, causal, True, q_seg=seg, q_offset2=q2)
+    print(f"[pair] {c} {how}", flush=True)
+    st.st_profile_begin()
+    _backward(w, si.make_inputs(w), st.ST_RING_FUSED, {"assign": True, "add_lowp": False}.get(how))
+    assert "bwd_bf16" in st.st_profile_end(), "this share was meant to take the common launch"

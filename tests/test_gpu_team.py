@@ -159,3 +159,9 @@ def test_team_gathered_forward_and_backward(case, mode):
     for j in range(w.n_chunks):
         assert_close(host(dk[j]), dk_ref[j], dtype, f"dk buffer {j} (summed over all teams)")
         assert_close(host(dv[j]), dv_ref[j], dtype, f"dv buffer {j} (summed over all teams)")
+
+
+@pytest.mark.parametrize("n", [3, 8, 9, 16, 17])
+def test_combine_at_the_edges_of_its_variants(n):
+    """Up to 4, 8 and 16 states have kernels of their own; the bounds are those of any other number."""
+    test_combine_matches_oracle((n, 1, 37, 3, 128, 4, 30))
