@@ -341,7 +341,7 @@ def main() -> int:
             per_kernel[name]["algorithmic_tflops"] = round(algo[name] / (avg * 1e-3) / 1e12, 1)
     dom = max((n for n in kernels if n in algo), key=lambda n: kernels[n][1], default=None)
     # HIP-event time of the forward and of the backward kernels of a step (the sums of the per-kernel times above)
-    fwd_names = {"fwd_bf16", "fwd_edge", "fwd_f32", "combine", "merge"}
+    fwd_names = {"fwd_bf16", "fwd_f32", "combine", "merge"}
     ms_fwd = sum(t for n, (_, t) in kernels.items() if n in fwd_names) / prof_steps
     ms_bwd = sum(t for n, (_, t) in kernels.items() if n not in fwd_names) / prof_steps
     facts = st.st_device_facts()

@@ -166,10 +166,12 @@ st_status st_attn_block_bwd(const st_block_desc* desc, const st_tensor* q, const
                             const st_tensor* v, const st_tensor* d_o, const float* lse_final,
                             const float* delta, float* dq_acc, float* dk_acc, float* dv_acc,
                             void* workspace, size_t workspace_bytes, void* hip_stream);
-/* workspace (nullable): device, 256-byte aligned, at least st_attn_block_bwd_workspace_bytes(desc) bytes (0 for
- * ST_F32).  With it the ST_BF16 path keeps a scaled copy of Q there and its hand-scheduled dK/dV kernel takes
- * part; without it the same values are computed by the general kernel, at a lower rate.  Contents mean nothing
- * between calls; calls that share a workspace must be ordered on one stream. */
+/* workspace (nullable): device, 256-byte aligned, best st_attn_block_bwd_workspace_bytes(desc) bytes (0 for
+ * ST_F32).  With it the ST_BF16 path keeps a scaled copy of Q there, which is what its hand-scheduled dK/dV kernel
+ * reads (B Sq Hq D 2 bytes, rounded up to 256: the least that is accepted), and behind it the partial sums of a
+ * launch with few key tiles; with less room it runs on fewer workgroups.  Without a workspace the same values are
+ * computed by the general kernel, at a lower rate.  Contents mean nothing between calls; calls that share a
+ * workspace must be ordered on one stream. */
 size_t st_attn_block_bwd_workspace_bytes(const st_block_desc* desc);
 
 /* ---- fp32 -> storage dtype (round to nearest even), n contiguous elements ---- */
@@ -232,8 +234,8 @@ st_status st_schedule_report(int32_t P, int32_t C, int64_t B, int64_t N, int64_t
  * Forward outputs: o_acc fp32 [B,Sq,Hq,D], lse fp32 [B,Hq,Sq] (overwritten); o_lowp nullable,
  *   [B,Sq,Hq,D] in desc->dtype.
  * workspace: device, >= st_ring_workspace_bytes(desc, mode, backward) bytes, 256-byte aligned.  Its contents
- *   are the library's (partial states, Delta, the tile counters of the dK/dV launch, the scaled copy of Q) and
- *   mean nothing between calls; calls that share a workspace must be ordered on one stream. */
+ *   are the library's (partial states, Delta, the tile counters of the dK/dV launch, the scaled copy of Q, partial
+ *   sums of backward launches that would leave part of the chip idle) and mean nothing between calls; calls that share a workspace must be ordered on one stream. */
 size_t st_ring_workspace_bytes(const st_ring_desc* desc, int32_t mode, int32_t backward);
 
 st_status st_ring_fwd(const st_ring_desc* desc, const st_tensor* q, const int32_t* order,
@@ -256,8 +258,8 @@ st_status st_ring_bwd(const st_ring_desc* desc, const st_tensor* q, const st_ten
  * copy of Q live in a static device array of st_ring_bwd_noalloc_max_bytes() = 40 MiB that every GPU the library
  * runs on holds until the process ends.  The call allocates and frees nothing (no hipMalloc / hipFree, no
  * allocating library routine); the array's device address is looked up once per device, on the first call.
- * A share whose st_ring_workspace_bytes(desc, mode, 1) exceeds the array returns ST_ERR_WORKSPACE and enqueues
- * nothing.  Every call on a GPU uses that GPU's one array (what must start at zero is cleared by the call
+ * A share whose Delta, counters and copy of Q exceed the array returns ST_ERR_WORKSPACE and enqueues nothing;
+ * partial sums take no more than the room that is left in it, here and in st_ring_bwd alike.  Every call on a GPU uses that GPU's one array (what must start at zero is cleared by the call
  * itself): calls that overlap on one GPU, on different streams or from different threads, race; order them. */
 st_status st_ring_bwd_noalloc(const st_ring_desc* desc, const st_tensor* q, const st_tensor* d_o,
                               const st_tensor* o, int32_t o_dtype, const float* lse_final,
