@@ -52,11 +52,10 @@ __device__ __forceinline__ void dq_fast_body(const BwdArgs& a, int block_x, int 
   const int q_row = row0 + 64 * wave + r;            // this lane's row of query block 0; block 1: + 32
   const int i0 = min(q_row, s.Sq - 1), i1 = min(q_row + 32, s.Sq - 1);
   ST_LDS uint32_t* params = (ST_LDS uint32_t*)(smem + kParams);
-  {  // positions relative to the workgroup's first row, for the mask (walk_usable sees to it that they fit)
-    const int64_t q_base = q_pos(s, row0);
+  {  // for the mask
     ST_LDS int32_t* qrel = (ST_LDS int32_t*)(smem + kQrel) + 2 * tid;
-    qrel[0] = (int)(q_pos(s, i0) - q_base) - 4 * g;
-    qrel[1] = (int)(q_pos(s, i1) - q_base) - 4 * g;
+    qrel[0] = walk_row_pos(s, i0, row0) - 4 * g;
+    qrel[1] = walk_row_pos(s, i1, row0) - 4 * g;
   }
   const int first_part = max(a.n_split, 1) - a.n_parts;
   if (wave == 0) {

@@ -28,6 +28,14 @@ __device__ __forceinline__ int lane_scan(int x, int& total) {
 
 constexpr int kRelMin = -(1 << 30);                  // relative position of a tile that no causal mask touches
 
+// Position of row i relative to the workgroup's first row, as the mask routines compare it with a tile's: the sum of the two
+// has to stay inside 32 bits.  Under a causal mask walk_usable sees to that.  Without one the routines still run, for the
+// ragged end of a chunk, and two runs of rows may lie any distance apart, so there a row has no position: all of them see
+// every key of a tile at kRelMin.
+__device__ __forceinline__ int walk_row_pos(const Shape& s, int i, int row0) {
+  return s.causal ? (int)(q_pos(s, i) - q_pos(s, row0)) : 0;
+}
+
 // The tiles a workgroup walks, written to LDS by one wavefront, a lane per chunk of the table, while the others wait: a chain
 // of latencies at the start of every workgroup (2.8 us of a 25 us launch with shuffles, 64-bit divisions and loads behind
 // the table's length; 2.1 us so).  Entry (32 bytes): K and V
@@ -94,7 +102,7 @@ inline bool walk_usable(const Shape& s, const ChunkTable& t) {
   auto fits = [](int64_t x) { return x > 0 && x < (int64_t)1 << 30; };
   if (!(fits(kQTileFastKeys * t.kss * 2) && fits(kQTileFastKeys * t.vss * 2) && fits((int64_t)kQTileFastRows * s.Hq * s.D * 4)))
     return false;
-  // positions inside a query tile, relative to its first row; only the tile that holds the end of a first run can be wide
+  // walk_row_pos; only the tile that holds the end of a first run can be wide
   if (s.causal && s.q_seg > 0) {
     const int row0 = s.q_seg / kQTileFastRows * kQTileFastRows;
     const int last = row0 + kQTileFastRows < s.Sq ? row0 + kQTileFastRows - 1 : s.Sq - 1;

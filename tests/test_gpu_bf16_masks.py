@@ -24,7 +24,10 @@ CASES = [(128, 1, 1, 1, 64, 1, 63, True, (0, 0)),
          (64, 2, 1, 1, 500, 1, 20, True, (0, 0)),
          (64, 1, 1, 320, 500, 2, 690, True, (0, 0)),
          (64, 2, 2, 257, 449, 3, 0, False, (0, 0)),
-         (64, 1, 1, 300, 130, 4, 100, True, (33, 360))]
+         (64, 1, 1, 300, 130, 4, 100, True, (33, 360)),
+         # no causal mask: ragged chunks, and two runs inside a query tile whose distance does not fit 30 bits
+         (128, 1, 1, 256, 129, 4, 0, False, (100, 3 << 29)),
+         (64, 2, 1, 200, 129, 4, 0, False, (70, 1 << 31))]
 
 
 def _check(w, inp, orders, mode=st.ST_RING_FUSED, close=assert_close, **kw):
