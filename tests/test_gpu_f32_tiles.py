@@ -112,6 +112,33 @@ def test_values_that_are_no_numbers_stay_behind_the_mask():
     assert torch.isposinf(dv[:, :bad + 1, :, 9]).all()
 
 
+@pytest.mark.parametrize("D,Sq,Sk", [(72, 45, 70), (128, 33, 33), (256, 63, 40), (64, 1, 1)])
+def test_infinities_in_the_last_row_of_a_ragged_tile(D, Sq, Sk):
+    """Every query sees the last key and every key the last query; rows that a ragged tile lacks must not multiply what they
+    hold by zero: an infinity arrives as one, and the other columns are what they are without it, bit for bit."""
+    w = si.Workload("f32_inf", 312, "f32", 1, 2, 1, D, Sq, Sk, 2, 0, False, True)
+    inp = si.make_inputs(w)
+    q, ks, vs, d_o = upload(inp)
+    koffs = [w.k_offset(j) for j in range(2)]
+    args = (0, koffs, False, w.scale, [0, 1])
+    v2, d2 = [v.clone() for v in vs], d_o.clone()
+    v2[0][:, -1, :, 3], v2[1][:, -1, :, D - 1] = float("inf"), float("-inf")
+    d2[:, -1, :, 5] = float("inf")
+    o, lse, _ = st.st_ring_fwd(q, ks, vs, *args)
+    o2, lse2, _ = st.st_ring_fwd(q, ks, v2, *args)
+    assert torch.isposinf(o2[..., 3]).all() and torch.isneginf(o2[..., D - 1]).all() and torch.equal(lse, lse2)
+    keep = [d for d in range(D) if d not in (3, D - 1)]
+    assert torch.equal(o[..., keep], o2[..., keep])
+    dvs = []
+    for x in (d_o, d2):
+        dq, dk, dv = torch.zeros_like(o), [torch.zeros_like(k) for k in ks], [torch.zeros_like(v) for v in vs]
+        st.st_ring_bwd(q, ks, vs, x, o, lse, *args, dq, dk, dv)
+        dvs.append(dv)
+    keep = [d for d in range(D) if d != 5]
+    for a, b in zip(*dvs):
+        assert torch.isposinf(b[..., 5]).all() and torch.equal(a[..., keep], b[..., keep])
+
+
 #           D,  Sq,  Sk, n, q_offset, causal, (q_seg, q_offset2)
 DQ_SPLIT = [(128, 64, 300, 4, 3 * 300, True, (0, 0)),       # a few query tiles against long chunks
             (64, 33, 1000, 1, 0, True, (0, 0)),             # one chunk; all but its first turn is hidden
