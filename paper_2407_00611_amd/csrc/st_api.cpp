@@ -625,7 +625,7 @@ st_status st_schedule_report(int32_t P, int32_t C, int64_t B, int64_t N, int64_t
 // constants are measured: a 256 x 64 bf16 tile 1.6 us at head size 128 and 0.95 us at 64, 8 us of prologue and epilogue,
 // 6 us for the launch of the combine pass, which moves 4 TB/s on states this small.  fp32: a 32-key tile is 64 D cycles of
 // a SIMD's matrix unit, and eight wavefronts on four SIMDs share the keys.
-static int fwd_splits(const st_ring_desc* d, int n_visible) {
+static int fwd_splits(const st_ring_desc* d, int n_visible, int most = kMaxSplits) {
   const bool bf16 = d->dtype == ST_BF16;
   if (n_visible < 1 || n_visible > st::kMaxTable || d->B < 1 || d->Sq < 1 || d->Hq < 1) return 1;
   if (bf16 && ((d->D != 128 && d->D != 64) || d->Sk < st::kQTileFastKeys)) return 1;
@@ -637,7 +637,7 @@ static int fwd_splits(const st_ring_desc* d, int n_visible) {
   const double state_us = (double)d->B * d->Sq * d->Hq * d->D * sizeof(float) / 4e6;
   double best = (double)((wgs + 255) / 256) * (fixed_us + tiles * tile_us);
   int n_best = 1;
-  for (int n = 2; n <= kMaxSplits && n <= tiles; ++n) {
+  for (int n = 2; n <= most && n <= tiles; ++n) {
     const double t = (double)((wgs * n + 255) / 256) * (fixed_us + (double)((tiles + n - 1) / n) * tile_us) + 6 + (n + 1.5) * state_us;
     if (t < 0.95 * best) {
       best = t;
@@ -732,18 +732,22 @@ st_status st_ring_fwd(const st_ring_desc* d, const st_tensor* q, const int32_t* 
   a.s = shape_of(d);
   a.q = view_of(q);
   set_table_strides(a.t, d);
-  int splits = mode == ST_RING_FUSED ? fwd_splits(d, n) : 1;
-  if (splits > 1 && d->dtype == ST_BF16 && !st::fwd_fast_usable(a)) splits = 1;   // only the hand-scheduled kernel walks a split table
-  // the step-wise walk, more chunks than one launch takes and small shares need their workspace; any other share runs
-  // unsplit without one
-  const bool small = mode == ST_RING_FUSED && fwd_states_small(d, n) > 1 && st::fwd_fast_usable(a);
-  const bool have_ws = workspace != nullptr && workspace_bytes >= st_ring_workspace_bytes(d, mode, 0);
-  if (splits > 1 && !small && !have_ws) splits = 1;
-  const bool need_ws = mode == ST_RING_STEPWISE || n > st::kMaxTable || splits > 1 || small;
-  if (need_ws) {
-    if (!have_ws) return fail(ST_ERR_WORKSPACE, "forward workspace needs %zu bytes", st_ring_workspace_bytes(d, mode, 0));
-    if (reinterpret_cast<uintptr_t>(workspace) % 256) return fail(ST_ERR_ALIGNMENT, "workspace: not 256-byte aligned");
+  const bool fused = mode == ST_RING_FUSED, fast = d->dtype == ST_BF16 && st::fwd_fast_usable(a);
+  const size_t state = b_o + b_l;
+  // The step-wise walk, more chunks than one launch takes and small shares need a workspace: the least of it is what they
+  // have always asked for.  What is there beyond that, or for any other share, only decides how many states a split may have:
+  // one that is missing, short or off the boundary costs workgroups, not the call.
+  const int n_most = d->n_chunks < st::kMaxTable ? d->n_chunks : st::kMaxTable;
+  const bool small = fused && fast && fwd_states_small(d, n) > 1;
+  const size_t least = !fused ? 2 * state : small || n > st::kMaxTable ? fwd_states_small(d, n_most) * state : 0;
+  const bool on_boundary = reinterpret_cast<uintptr_t>(workspace) % 256 == 0;
+  if (least > 0) {
+    if (workspace == nullptr || workspace_bytes < least) return fail(ST_ERR_WORKSPACE, "forward workspace needs %zu bytes", st_ring_workspace_bytes(d, mode, 0));
+    if (!on_boundary) return fail(ST_ERR_ALIGNMENT, "workspace: not 256-byte aligned");
   }
+  const size_t room = fused && workspace != nullptr && on_boundary ? workspace_bytes / state : 0;
+  int splits = room > 1 ? fwd_splits(d, n, room < (size_t)kMaxSplits ? (int)room : kMaxSplits) : 1;
+  if (d->dtype == ST_BF16 && !fast) splits = 1;        // only the hand-scheduled kernel walks a split table
   char* ws = (char*)workspace;
   float* part_o = (float*)ws;
   float* part_l = (float*)(ws + b_o);
