@@ -171,6 +171,13 @@ st_status check_ring(const st_ring_desc* d, const st_tensor* q, const int32_t* o
 
 constexpr int kMaxSplits = 16;
 
+// fp32: the turns a query tile's workgroup takes over n chunks; in one its wavefronts (eight, four beyond head size 128) take
+// a 32-key tile each
+int64_t f32_turns(int D, int Sk, int64_t n) {
+  const int waves = D <= 128 ? 8 : 4;
+  return (n * ((Sk + 31) / 32) + waves - 1) / waves;
+}
+
 // Workgroups per tile of a backward launch over n chunks, and the bytes of partial sums that
 // takes (the two passes run one after the other and share them).
 struct BwdSplit {
@@ -206,7 +213,7 @@ BwdSplit bwd_splits(const st::Shape& s, int dtype, int n, bool half, size_t room
   double dq_us = 0, dq_tile_us = 0, part_us = 0;
   if ((bf16 && s.D != 128 && s.D != 64) || n < 1 || n > st::kMaxTable || s.B < 1 || s.Sq < 1 || s.Sk < 1 || s.Hq < 1 || s.Hkv < 1) return r;
   const bool d128 = s.D == 128;
-  const int rows = bf16 ? st::kQTileFastRows : 32, keys = bf16 ? st::kQTileFastKeys : s.D <= 128 ? 256 : 128;
+  const int rows = bf16 ? st::kQTileFastRows : 32, keys = st::kQTileFastKeys;
   const int64_t wgs = (int64_t)s.B * s.Hq * ((s.Sq + rows - 1) / rows);
   const size_t n_o = (size_t)st::dq_part_floats(s) * sizeof(float);
   auto set_dq = [&](int x) {
@@ -215,7 +222,7 @@ BwdSplit bwd_splits(const st::Shape& s, int dtype, int n, bool half, size_t room
     r.bytes = (size_t)r.parts * n_o;
   };
   if (split_dq && wgs < 512 && (!bf16 || s.Sk >= keys)) {
-    const int64_t tiles = bf16 ? (int64_t)n * ((s.Sk + keys - 1) / keys) : ((int64_t)n * ((s.Sk + 31) / 32) * 32 + keys - 1) / keys;
+    const int64_t tiles = bf16 ? (int64_t)n * ((s.Sk + keys - 1) / keys) : f32_turns(s.D, s.Sk, n);
     const double tile_us = bf16 ? (d128 ? 2.4 : 1.4) : 2 + (s.D <= 128 ? 0.11 : 0.055) * s.D, fixed_us = 10, state_us = (double)n_o / 4e6, add_us = bf16 ? 6 : 10;
     dq_tiles = tiles, dq_tile_us = tile_us, part_us = state_us;
     double best = (double)((wgs + 255) / 256) * (fixed_us + tiles * tile_us);
@@ -623,17 +630,21 @@ st_status st_schedule_report(int32_t P, int32_t C, int64_t B, int64_t N, int64_t
 // of the walk and a partial state of its own, and one combine pass folds the states (the tiles of a ring are independent
 // until the fold, Algorithm 1).  The split is the one for which rounds of workgroups x time of one + combine is least; the
 // constants are measured: a 256 x 64 bf16 tile 1.6 us at head size 128 and 0.95 us at 64, 8 us of prologue and epilogue,
-// 6 us for the launch of the combine pass, which moves 4 TB/s on states this small.  fp32: a 32-key tile is 64 D cycles of
-// a SIMD's matrix unit, and eight wavefronts on four SIMDs share the keys.
+// 6 us for the launch of the combine pass, which moves 4 TB/s on states this small.  fp32: a turn (see f32_turns) takes 4.1,
+// 6.1 and 10.4 us at head sizes 32, 64 and 128 and 10.7 at 256 (with half the wavefronts), what stands around the turns 5, 7,
+// 10 and 13 us.  At head size 128, unsplit and as planned: 4 heads x 128 rows x 512 keys 30.3 and 22.9 us (two shares of a
+// turn each), x 2048 keys 92.6 and 25.0 (eight), 8 heads x 512 rows x 8 chunks of 512 keys 181 and 105 (two shares on 128
+// query tiles; four, which are two rounds of workgroups, 113).
 static int fwd_splits(const st_ring_desc* d, int n_visible, int most = kMaxSplits) {
   const bool bf16 = d->dtype == ST_BF16;
   if (n_visible < 1 || n_visible > st::kMaxTable || d->B < 1 || d->Sq < 1 || d->Hq < 1) return 1;
   if (bf16 && ((d->D != 128 && d->D != 64) || d->Sk < st::kQTileFastKeys)) return 1;
-  const int rows = bf16 ? st::kQTileFastRows : 32, keys = bf16 ? st::kQTileFastKeys : 32;
+  const int rows = bf16 ? st::kQTileFastRows : 32, keys = st::kQTileFastKeys;
   const int64_t wgs = (int64_t)d->B * d->Hq * ((d->Sq + rows - 1) / rows);
   if (wgs >= 512) return 1;
-  const int64_t tiles = (int64_t)n_visible * ((d->Sk + keys - 1) / keys);
-  const double tile_us = bf16 ? (d->D == 128 ? 1.6 : 0.95) : 64.0 * d->D / 2400 / 4, fixed_us = bf16 ? 8 : 4;
+  const int64_t tiles = bf16 ? (int64_t)n_visible * ((d->Sk + keys - 1) / keys) : f32_turns(d->D, d->Sk, n_visible);
+  const double tile_us = bf16 ? (d->D == 128 ? 1.6 : 0.95) : 2 + (d->D <= 128 ? 0.065 : 0.034) * d->D;
+  const double fixed_us = bf16 ? 8 : 5 + 0.035 * d->D;
   const double state_us = (double)d->B * d->Sq * d->Hq * d->D * sizeof(float) / 4e6;
   double best = (double)((wgs + 255) / 256) * (fixed_us + tiles * tile_us);
   int n_best = 1;

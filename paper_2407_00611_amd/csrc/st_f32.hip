@@ -214,8 +214,8 @@ struct KeyWalk {
   int skip;         // tiles still to pass over
 };
 template <int DP>
-__device__ __forceinline__ bool walk_next(KeyWalk& w, const Shape& s, const ChunkTable& tab, int c_hi, int64_t last_pos) {
-  while (w.c < c_hi) {
+__device__ __forceinline__ bool walk_next(KeyWalk& w, const Shape& s, const ChunkTable& tab, int64_t last_pos) {
+  while (w.c < tab.n) {
     const int left = w.t < w.nv ? (w.nv - w.t + kT - 1) / kT : 0;
     if (w.skip < left) {
       w.t += w.skip * kT;
@@ -223,7 +223,7 @@ __device__ __forceinline__ bool walk_next(KeyWalk& w, const Shape& s, const Chun
       return true;
     }
     w.skip -= left;
-    if (++w.c < c_hi) {
+    if (++w.c < tab.n) {
       w.t = 0;
       w.nv = visible_keys(s, last_pos, tab.k_offset[w.c]);
     }
@@ -232,7 +232,9 @@ __device__ __forceinline__ bool walk_next(KeyWalk& w, const Shape& s, const Chun
 }
 
 // ---------------------------------------------------------------- forward
-// Bounded by the matrix instructions: D per 32 x 32 tile pair and 64 cycles each.  Eight wavefronts share the 32 rows.
+// Bounded by the matrix instructions: D per 32 x 32 tile pair and 64 cycles each.  Eight wavefronts share the 32 rows.  An
+// under-filled launch (n_split > 1) gives every query tile n_split workgroups, blockIdx.y of them, which take NW tiles of the
+// walk in turn, so that their shares differ by one turn at most whatever the mask and however few chunks there are.
 template <int DP, bool FULL>
 __global__ __launch_bounds__(waves<DP>() * 64) void fwd_f32_kernel(const FwdArgs a) {
   constexpr int NW = waves<DP>(), DB = DP / 32, N = 32, NR = row_pieces<DP, N>(), NC = col_pieces<DP, N>();
@@ -257,10 +259,8 @@ __global__ __launch_bounds__(waves<DP>() * 64) void fwd_f32_kernel(const FwdArgs
   float m = -INFINITY, l = 0.f;
   f32x16 acc[DB];
   zero_acc(acc);
-  int c_lo, c_hi;
-  split_range(a.t.n, a.n_split, blockIdx.y, c_lo, c_hi);
-  KeyWalk w{c_lo, 0, c_lo < c_hi ? visible_keys(s, last_pos, a.t.k_offset[c_lo]) : 0, wave};
-  while (walk_next<DP>(w, s, a.t, c_hi, last_pos)) {
+  KeyWalk w{0, 0, a.t.n > 0 ? visible_keys(s, last_pos, a.t.k_offset[0]) : 0, (int)blockIdx.y * NW + wave};
+  while (walk_next<DP>(w, s, a.t, last_pos)) {
     const float* kb = (const float*)a.t.k[w.c] + b * a.t.ksb + hk * a.t.ksh + (int64_t)w.t * a.t.kss;
     const float* vb = (const float*)a.t.v[w.c] + b * a.t.vsb + hk * a.t.vsh + (int64_t)w.t * a.t.vss;
     const int limit = min(kT, w.nv - w.t);
@@ -314,7 +314,7 @@ __global__ __launch_bounds__(waves<DP>() * 64) void fwd_f32_kernel(const FwdArgs
       if (limit < kT) drop_rows<DP>(f[x & 1], limit, x - NR, g);
       contract_rows<DP>(acc, f[x & 1], p, x - NR);
     }
-    w.skip = NW;
+    w.skip = max(a.n_split, 1) * NW;
   }
 
   // fold of the wavefronts' states (m, l, O), halving their number each time
@@ -351,16 +351,14 @@ __global__ __launch_bounds__(waves<DP>() * 64) void fwd_f32_kernel(const FwdArgs
       if (ol) *reinterpret_cast<float4*>(ol + d) = x;
     }
   if (g == 0) a.lse[(int64_t)blockIdx.y * a.split_l + ((int64_t)b * s.Hq + h) * s.Sq + row0 + r] = l > 0.f ? m + logf(l) : -INFINITY;
-  if (any_dirty)
-    for (int c = c_lo; c < c_hi; ++c)
+  if (any_dirty)                                             // (a value that several shares add is the same infinity or NaN)
+    for (int c = 0; c < a.t.n; ++c)
       add_nonfinite(o, ol, (const float*)a.t.v[c] + b * a.t.vsb + hk * a.t.vsh, a.t.vss,
                     visible_keys(s, first_pos, a.t.k_offset[c]) / kT * kT, visible_keys(s, qpos, a.t.k_offset[c]), s.D, g, false);
 }
 
 // ---------------------------------------------------------------- backward: dQ
-// Three contractions per tile pair (S and dP are recomputed); otherwise the forward's layout.  An under-filled launch
-// (n_split > 1) gives every query tile n_split workgroups, blockIdx.y of them, which take NW tiles of the walk in turn, so
-// that their shares differ by one turn at most whatever the mask and however few chunks there are.
+// Three contractions per tile pair (S and dP are recomputed); otherwise the forward's layout and its shares.
 template <int DP, bool FULL>
 __global__ __launch_bounds__(waves<DP>() * 64) void bwd_dq_f32_kernel(const BwdArgs a) {
   constexpr int NW = waves<DP>(), DB = DP / 32, N = 32, NR = row_pieces<DP, N>(), NC = col_pieces<DP, N>();
@@ -390,7 +388,7 @@ __global__ __launch_bounds__(waves<DP>() * 64) void bwd_dq_f32_kernel(const BwdA
   zero_acc(acc);
   const int n_split = max(a.n_split, 1);
   KeyWalk w{0, 0, a.t.n > 0 ? visible_keys(s, last_pos, a.t.k_offset[0]) : 0, (int)blockIdx.y * NW + wave};
-  while (walk_next<DP>(w, s, a.t, a.t.n, last_pos)) {
+  while (walk_next<DP>(w, s, a.t, last_pos)) {
     const float* kb = (const float*)a.t.k[w.c] + b * a.t.ksb + hk * a.t.ksh + (int64_t)w.t * a.t.kss;
     const float* vb = (const float*)a.t.v[w.c] + b * a.t.vsb + hk * a.t.vsh + (int64_t)w.t * a.t.vss;
     const int limit = min(kT, w.nv - w.t);

@@ -58,19 +58,13 @@ struct FwdArgs {
   float* lse;      // fp32 [B,Hq,Sq]
   void* o_lowp;    // nullable, [B,Sq,Hq,D] in the storage dtype
   // Under-filled launches: n_split > 1 gives every query tile n_split workgroups (blockIdx.y), each walking a
-  // contiguous share of the tiles and writing its own partial state at o + y * split_o, lse + y * split_l
-  // (floats); the states are combined afterwards.  0 or 1: one workgroup walks the whole table.
+  // share of the tiles (contiguous in bf16, every n_split-th turn in fp32) and writing its own partial state at
+  // o + y * split_o, lse + y * split_l (floats); the states are combined afterwards.  0 or 1: one workgroup walks
+  // the whole table.
   int32_t n_split;
   int64_t split_o, split_l;
   float gap;         // fast kernel: log2 units a block maximum may exceed the lazy exponent reference by (set by its launcher)
 };
-
-// table entries [lo, hi) of split y
-__host__ __device__ inline void split_range(int n, int n_split, int y, int& lo, int& hi) {
-  if (n_split <= 1) { lo = 0; hi = n; return; }
-  lo = (int)((int64_t)n * y / n_split);
-  hi = (int)((int64_t)n * (y + 1) / n_split);
-}
 
 struct BwdArgs {
   Shape s;

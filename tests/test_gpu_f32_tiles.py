@@ -73,6 +73,50 @@ def test_split_forward_and_a_workspace_too_small_for_it():
         assert torch.equal(o, low)
 
 
+#           D,  Sq, Sk, n, q_offset, causal, shares
+FWD_SPLIT = [(128, 64, 512, 4, 4 * 512 - 64, True, 8), # eight turns, four chunks
+             (128, 100, 512, 1, 412, True, 2),         # one chunk
+             (64, 33, 1000, 2, 0, False, 8),           # turns that reach over two chunks, ragged last tiles
+             (256, 40, 300, 3, 860, True, 8)]          # four wavefronts per workgroup
+
+
+@pytest.mark.parametrize("c", FWD_SPLIT, ids=[f"d{c[0]}_q{c[1]}_k{c[2]}" for c in FWD_SPLIT])
+def test_every_share_of_a_split_forward_has_work(c):
+    """The plan counts turns of tiles and the launch hands them out: no partial state is empty, whatever the number of
+    chunks, and an infinity behind a mask edge reaches exactly the rows that see it, whichever share met it."""
+    D, Sq, Sk, n, q0, causal, shares = c
+    w = si.Workload("f32_shares", 313, "f32", 1, 2, 1, D, Sq, Sk, n, q0, causal, False)
+    inp = si.make_inputs(w)
+    q, ks, vs, _ = upload(inp)
+    args = (q0, [w.k_offset(j) for j in range(n)], causal, w.scale)
+    up = lambda x: (x + 255) // 256 * 256
+    b_o, b_l = up(q.numel() * 4), up(w.Hq * Sq * 4)
+    need = st.st_ring_workspace_bytes(q, ks, vs, *args, st.ST_RING_FUSED, False)
+    assert need == shares * (b_o + b_l)
+    ws = torch.full((need + 256,), 0xff, dtype=torch.uint8, device="cuda")                   # NaN
+    o, lse, _ = st.st_ring_fwd(q, ks, vs, *args, list(range(n)), workspace=ws)
+    o_r, lse_r = oa.attention_forward(inp.q, inp.k, inp.v, *positions(w), causal, w.scale)
+    assert_close(host(o), o_r, "f32", "o")
+    assert_close(host(lse), lse_r, "f32", "lse")
+    first = (-ws.data_ptr()) % 256
+    for y in range(shares):
+        at = first + y * (b_o + b_l) + b_o
+        part = ws[at:at + w.Hq * Sq * 4].view(torch.float32)
+        assert torch.isfinite(part).any(), f"share {y} met no key"
+    if not causal:
+        return
+    bad = q0 + Sq // 2                                  # the position of a query row in the middle
+    v2 = [v.clone() for v in vs]
+    v2[bad // Sk][:, bad % Sk, :, 3] = float("inf")
+    v2[(bad + 1) // Sk][:, (bad + 1) % Sk, :, 4] = float("nan")
+    o2, lse2, _ = st.st_ring_fwd(q, ks, v2, *args, list(range(n)))
+    i = bad - q0
+    assert torch.equal(lse, lse2) and torch.equal(o[:, :i], o2[:, :i])
+    assert torch.isposinf(o2[:, i:, :, 3]).all() and torch.isnan(o2[:, i + 1:, :, 4]).all()
+    keep = [d for d in range(D) if d not in (3, 4)]
+    assert torch.equal(o[..., keep], o2[..., keep]) and torch.equal(o[:, i, :, 4], o2[:, i, :, 4])
+
+
 def test_values_that_are_no_numbers_stay_behind_the_mask():
     """Rows that a causal mask hides from a query (or queries it hides from a key) may hold anything: the results of
     every row that does not see them are the ones without them, bit for bit; a row that sees one is no number."""
