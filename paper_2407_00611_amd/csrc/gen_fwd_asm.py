@@ -22,9 +22,12 @@ still zero), since a lazy reference never moves down.
 MFMA C layout "lane = query column": the exponent reference r (log2 units) and the row sum are one
 register per lane and query block.  The Q fragments are multiplied by scale * log2(e) once (and rounded
 to bf16 again), and every S^T accumulator starts from -r instead of zero, so the MFMAs deliver the
-exponent S c - r directly and no VALU instruction is spent on it.  The reference is lazy: it only moves, by a whole number of log2 units,
-when a block's maximum exceeds it by more than GAP, so the rescale factor is an exact power of two and the
-common path never touches the accumulators.
+exponent S c - r directly and no VALU instruction is spent on it.  The reference starts as the row's maximum over the
+first tile, so that the P of that key is 1 and carries no rounding: a row that sees few keys (the first ones of a causal
+sequence) is mostly that key.  Rounded up to whole log2 units it made O of the first rows of a sequence 1.6e-3 wrong where
+one key is seen and the result is exact, of rows 1 to 31 2.0e-3 instead of 1.5e-3, of 2000 rows together 2.19e-3 instead of
+1.91e-3.  From there it is lazy: it only moves, by a whole number of log2 units, when a block's maximum exceeds it by more
+than GAP, so the rescale factor is an exact power of two and the common path never touches the accumulators.
 
 Per 32-key block i and wavefront two groups of 16 MFMAs, software-pipelined two blocks deep:
     group B   O^T += V^T P^T(i)          A: V^T of block i by LDS transpose reads, B: packed P(i)
@@ -152,10 +155,9 @@ def read_vt(p, blk, m, db, seq):
     p.e.ds_read(f"ds_read_b64_tr_b16 {vr(r + 2, 2)}, {vr(hi + db)} offset:{off}", tag)
 
 
-def valu_max(buf, full=False):
-    """d = maximum of the exponents S c - r in buffer `buf` over this lane's key rows (full: over both halves of the
-    wavefront, i.e. the whole block), per query block.  The test against GAP is a wavefront-wide vote, so the
-    common path does not need the halves combined."""
+def valu_max(buf):
+    """d = maximum of the exponents S c - r in buffer `buf` over this lane's key rows, per query block.  The test against
+    GAP is a wavefront-wide vote, so the common path does not need the halves of the wavefront combined."""
     out = []
     for qb in range(QB):
         s0 = SBUF(buf, qb)
@@ -163,8 +165,6 @@ def valu_max(buf, full=False):
         for v in range(3, 15, 2):
             out.append(f"v_max3_f32 {vr(MX(qb))}, {vr(MX(qb))}, {vr(s0 + v)}, {vr(s0 + v + 1)}")
         out.append(f"v_max_f32 {vr(MX(qb))}, {vr(MX(qb))}, {vr(s0 + 15)}")
-    if full:
-        out += valu_exchange()
     out.append(f"v_max_f32 {vr(DMAX)}, {vr(MX(0))}, {vr(MX(1))}")
     return out
 
@@ -360,13 +360,12 @@ def gen_mask_routine(e, kb):
     e.raw("s_nop 1")
     for qb in range(QB):
         e.raw(f"v_max_f32 {vr(mx + qb)}, {vr(mx + qb)}, {vr(t + qb)}")
-        e.raw(f"v_ceil_f32 {vr(k + qb)}, {vr(mx + qb)}")
         e.raw(f"v_cmp_neq_f32_e64 {sr(T_CMP, 2)}, {vr(ninf)}, {vr(mx + qb)}")
         e.raw(f"v_cmp_eq_u32_e64 {sr(T_CMP + 2, 2)}, 0, {vr(SEEN(qb))}")
         e.raw("s_nop 1")
         e.raw(f"s_and_b64 {sr(T_CMP, 2)}, {sr(T_CMP, 2)}, {sr(T_CMP + 2, 2)}")
         e.raw("s_nop 1")
-        e.raw(f"v_cndmask_b32_e64 {vr(k + qb)}, 0, {vr(k + qb)}, {sr(T_CMP, 2)}")
+        e.raw(f"v_cndmask_b32_e64 {vr(k + qb)}, 0, {vr(mx + qb)}, {sr(T_CMP, 2)}")
         e.raw(f"v_cndmask_b32_e64 {vr(SEEN(qb))}, {vr(SEEN(qb))}, 1, {sr(T_CMP, 2)}")
         for v in range(16):
             e.raw(f"v_sub_f32 {vr(NL(qb) + v)}, {vr(NL(qb) + v)}, {vr(k + qb)}")
@@ -558,7 +557,7 @@ def generate():
         e.raw(f"v_accvgpr_write_b32 {ar(128 + i)}, {vr(i)}")
     e.raw("s_barrier")
 
-    e.comment("---- pipeline fill: exponents of block (0,0) from zero, reference, P and row sums; then block (0,1) from -r")
+    e.comment("---- pipeline fill: exponents of tile 0 from zero, reference; P and row sums of its first block")
 
     def fill_s(blk, buf, seq, c_init):
         for ks in range(KS):
@@ -570,24 +569,30 @@ def generate():
                         d = vr(SBUF(buf, qb), 16)
                         e.mfma(d, vr(p.use(f"k{seq}_{k2}"), 4), ar(QF(qb, k2), 4), c_init(qb) if k2 == 0 else d)
 
-    fill_s((0, 0), 0, -2, lambda qb: "0")
+    for kb in range(2):
+        fill_s((0, kb), kb, kb - 2, lambda qb: "0")
     e.raw("s_nop 7")
     e.raw("s_nop 7")
-    mask_test(e, S_NM, 0)
-    for ln in valu_max(0, full=True):           # with r = 0: d = row maximum of S c
+    for kb in range(2):
+        mask_test(e, S_NM, kb)
+    for qb in range(QB):                        # with r = 0: d = row maximum of S c
+        x = [SBUF(kb, qb) + v for kb in range(2) for v in range(16)]
+        e.raw(f"v_max_f32 {vr(MX(qb))}, {vr(x[0])}, {vr(x[1])}")
+        for v in range(2, 32, 2):
+            e.raw(f"v_max3_f32 {vr(MX(qb))}, {vr(MX(qb))}, {vr(x[v])}, {vr(x[v + 1])}")
+    for ln in valu_exchange():
         e.raw(ln)
-    for qb in range(QB):                        # reference = ceil(max), whole log2 units; shift block (0,0) by hand
+    for qb in range(QB):                        # reference = the maximum (its P is 1, exactly); shift the tile by hand
         e.raw(f"v_mov_b32 {vr(TMP)}, 0xff800000")
         e.raw(f"v_cmp_neq_f32 vcc, {vr(TMP)}, {vr(MX(qb))}")
-        e.raw(f"v_ceil_f32 {vr(MX(qb))}, {vr(MX(qb))}")
         e.raw("s_nop 1")
-        e.raw(f"v_cndmask_b32 {vr(MX(qb))}, 0, {vr(MX(qb))}, vcc")      # a row that sees no key of this block: zero
+        e.raw(f"v_cndmask_b32 {vr(MX(qb))}, 0, {vr(MX(qb))}, vcc")      # a row that sees no key of this tile: zero
         e.raw(f"v_cndmask_b32_e64 {vr(SEEN(qb))}, 0, 1, vcc")
         for v in range(16):
             e.raw(f"v_sub_f32 {vr(NL(qb) + v)}, 0, {vr(MX(qb))}")
-        for v in range(16):
-            e.raw(f"v_sub_f32 {vr(SBUF(0, qb) + v)}, {vr(SBUF(0, qb) + v)}, {vr(MX(qb))}")
-    fill_s((0, 1), 1, -1, lambda qb: vr(NL(qb), 16))
+        for kb in range(2):
+            for v in range(16):
+                e.raw(f"v_sub_f32 {vr(SBUF(kb, qb) + v)}, {vr(SBUF(kb, qb) + v)}, {vr(MX(qb))}")
     for text, writes, _ in valu_exp(0, 0):
         e.valu(text, writes)
     for db in range(2):
@@ -614,6 +619,11 @@ def generate():
         e.raw(f"s_sub_u32 {sr(T_REM)}, {sr(T_REM)}, 1")
 
     e.comment("---- tiles T with T and T + 1 whole")
+    if D == 64:
+        # Where the loop lies among the 64-byte lines of the instruction cache is 1 to 3 % at this head size: 24 heads x 16384
+        # rows x 131072 keys 12.3 ms from byte 4 of a line, 12.4 from 16, 32 or 48, 12.5 to 12.6 from 0 or 8.  At 128 it is nothing.
+        e.raw(".p2align 6")
+        e.raw("s_nop 0")
     e.raw(l_loop + ":")
     start = p.snapshot()
     at = []

@@ -68,6 +68,31 @@ def test_rows_that_meet_their_first_key_late(D):
     _check(w, inp, [[0]], close=lambda x, r, what, lse=False: assert_close_wide(x, r, what, lse=lse))
 
 
+#        D, Sq, Sk, n, q_offset, causal
+EQUAL = [(128, 300, 300, 1, 0, True), (64, 520, 520, 2, 0, True), (128, 200, 130, 3, 0, False), (64, 270, 500, 2, 700, True)]
+
+
+@pytest.mark.parametrize("mode", [st.ST_RING_FUSED, st.ST_RING_STEPWISE], ids=["fused", "stepwise"])
+@pytest.mark.parametrize("c", EQUAL, ids=[f"d{c[0]}_q{c[1]}_k{c[2]}" for c in EQUAL])
+def test_the_largest_probability_carries_no_rounding(c, mode):
+    """A row's exponent reference is its maximum, so a key that holds it has P = 1 in bf16.  A row that sees one key returns
+    its V bit for bit; where all keys are alike O is the mean of the visible V to fp32 accuracy: every P is 1, and the row
+    sum is off by the rounding of scores of at most 32 log2 units summed in 8 steps, 8 * 32 * 2^-24 * ln 2 = 1.1e-5."""
+    D, Sq, Sk, n, q0, causal = c
+    w = si.Workload("equal", 342, "bf16", 1, 2, 1, D, Sq, Sk, n, q0, causal, False)
+    print(f"[equal keys] {c} {mode}", flush=True)
+    inp = si.make_inputs(w)
+    for k, bits in zip(inp.k, inp.k_bits):
+        k[:], bits[:] = inp.k[0][:, :1], inp.k_bits[0][:, :1]
+    q, ks, vs, _ = upload(inp)
+    q_pos, k_pos = positions(w)
+    o_ref, _ = oa.attention_forward(inp.q, inp.k, inp.v, q_pos, k_pos, causal, w.scale)
+    o, _, _ = st.st_ring_fwd(q, ks, vs, q0, [w.k_offset(j) for j in range(n)], causal, w.scale, list(range(n)), None, mode)
+    assert np.abs(host(o) - o_ref).max() <= 2e-5 * np.abs(o_ref).max()
+    if causal and q0 == 0:
+        assert torch.equal(o[:, 0], vs[0][:, 0].float().expand(1, 2, D))
+
+
 def test_split_cuts_the_masked_part():
     """One head, so the walk of every query tile is split sixteen ways and some splits hold masked tiles only."""
     w = si.Workload("split_masks", 331, "bf16", 1, 1, 1, 128, 700, 700, 3, 1400, True, False)
