@@ -82,32 +82,25 @@ __device__ __forceinline__ void load_rows(Piece<N>& f, const float* row, int n, 
   }
 }
 
+// a pointer said to be global, where the compiler does not see it (it would load with flat loads, which wait for LDS too)
+typedef const __attribute__((address_space(1))) float* GlobalFloats;
+__device__ const float zero_row[256] = {};
 // The transposed operand of a tile X: lane r = column 32 db + r, register v = row c_row(v, g).
-// Rows at or beyond `limit` (tile-relative, >= 1) re-read the last one; drop_rows before the contraction.
+// Rows at or beyond `limit` (tile-relative, >= 1) are zero: their weight is, but a row that exists, read in their place, may
+// hold an infinity, and 0 * inf is NaN.
 template <int DP, bool FULL, int N>
 __device__ __forceinline__ void load_cols(Piece<N>& f, const float* tile, int64_t stride, int limit, int n, int D, int r, int g) {
   constexpr int DB = DP / 32;
+  int mine = limit - 4 * g;
+  asm volatile("" : "+v"(mine));                     // compared anew for every piece: kept, the masks of all rows spill
 #pragma unroll
   for (int u = 0; u < piece_rows<DP, N>(); ++u) {
     const int v = n * piece_rows<DP, N>() + u, row = 8 * (v / 4) + v % 4;
-    const float* p = tile + r;
-    if (limit >= kT) p += (int64_t)(4 * g) * stride + (int64_t)row * stride;
-    else p += (int64_t)min(row + 4 * g, limit - 1) * stride;
+    GlobalFloats p = (GlobalFloats)tile + (int64_t)(4 * g) * stride + (int64_t)row * stride;
+    if (limit < kT) p = row < mine ? p : (GlobalFloats)zero_row;
+    p += r;
 #pragma unroll
     for (int db = 0; db < DB; ++db) f.x[DB * u + db] = FULL || 32 * db + r < D ? p[32 * db] : 0.f;
-  }
-}
-
-// Rows at or beyond `limit` to zero.  Their weight is zero, but a value re-read from a row that exists may be an infinity,
-// and 0 * inf is NaN.  Not done in load_cols, where it would wait for the loads.
-template <int DP, int N>
-__device__ __forceinline__ void drop_rows(Piece<N>& f, int limit, int n, int g) {
-#pragma unroll
-  for (int u = 0; u < piece_rows<DP, N>(); ++u) {
-    const int v = n * piece_rows<DP, N>() + u;
-    const bool there = 8 * (v / 4) + 4 * g + v % 4 < limit;
-#pragma unroll
-    for (int db = 0; db < DP / 32; ++db) f.x[DP / 32 * u + db] = there ? f.x[DP / 32 * u + db] : 0.f;
   }
 }
 
@@ -311,7 +304,6 @@ __global__ __launch_bounds__(waves<DP>() * 64) void fwd_f32_kernel(const FwdArgs
     for (int x = NR; x < NR + NC; ++x) {
       if (x + 1 < NR + NC) load(x + 1);
       if (dirty) scrub(f[x & 1]);
-      if (limit < kT) drop_rows<DP>(f[x & 1], limit, x - NR, g);
       contract_rows<DP>(acc, f[x & 1], p, x - NR);
     }
     w.skip = max(a.n_split, 1) * NW;
@@ -420,7 +412,6 @@ __global__ __launch_bounds__(waves<DP>() * 64) void bwd_dq_f32_kernel(const BwdA
     for (int x = 2 * NR; x < 2 * NR + NC; ++x) {
       if (x + 1 < 2 * NR + NC) load(x + 1);
       if (dirty) scrub(f[x & 1]);
-      if (limit < kT) drop_rows<DP>(f[x & 1], limit, x - 2 * NR, g);
       contract_rows<DP>(acc, f[x & 1], ds, x - 2 * NR);
     }
     w.skip = n_split * NW;
@@ -537,7 +528,6 @@ __global__ __launch_bounds__(waves<DP>() * 64) void bwd_dkv_f32_kernel(const Bwd
     for (int x = 2 * NR; x < 2 * NR + 2 * NC; ++x) {
       if (x + 1 < 2 * NR + 2 * NC) load(x + 1);
       if (dirty) scrub(f[x & 1]);
-      if (limit < kT) drop_rows<DP>(f[x & 1], limit, (x - 2 * NR) % NC, g);
       if (x < 2 * NR + NC) contract_rows<DP>(acc_v, f[x & 1], p, x - 2 * NR);
       else contract_rows<DP>(acc_k, f[x & 1], ds, x - 2 * NR - NC);
     }
