@@ -632,9 +632,10 @@ st_status st_schedule_report(int32_t P, int32_t C, int64_t B, int64_t N, int64_t
 // constants are measured: a 256 x 64 bf16 tile 1.6 us at head size 128 and 0.95 us at 64, 8 us of prologue and epilogue,
 // 6 us for the launch of the combine pass, which moves 4 TB/s on states this small.  fp32: a turn (see f32_turns) takes 4.1,
 // 6.1 and 10.4 us at head sizes 32, 64 and 128 and 10.7 at 256 (with half the wavefronts), what stands around the turns 5, 7,
-// 10 and 13 us.  At head size 128, unsplit and as planned: 4 heads x 128 rows x 512 keys 30.3 and 22.9 us (two shares of a
-// turn each), x 2048 keys 92.6 and 25.0 (eight), 8 heads x 512 rows x 8 chunks of 512 keys 181 and 105 (two shares on 128
-// query tiles; four, which are two rounds of workgroups, 113).
+// 10 and 13 us; 8 us for the combine pass, as a caller that waits for launches (small fp32 shares are such calls: 67 us for
+// 45 us of kernels) loses 5 us by one more.  At head size 128, unsplit and as planned: 4 heads x 128 rows x 2048 keys 92.6 and
+// 24.9 us (eight shares of a turn), 8 heads x 512 rows x 8 chunks of 512 keys 181 and 105 (two shares on 128 query tiles; four,
+// which are two rounds of workgroups, 113).
 static int fwd_splits(const st_ring_desc* d, int n_visible, int most = kMaxSplits) {
   const bool bf16 = d->dtype == ST_BF16;
   if (n_visible < 1 || n_visible > st::kMaxTable || d->B < 1 || d->Sq < 1 || d->Hq < 1) return 1;
@@ -644,12 +645,12 @@ static int fwd_splits(const st_ring_desc* d, int n_visible, int most = kMaxSplit
   if (wgs >= 512) return 1;
   const int64_t tiles = bf16 ? (int64_t)n_visible * ((d->Sk + keys - 1) / keys) : f32_turns(d->D, d->Sk, n_visible);
   const double tile_us = bf16 ? (d->D == 128 ? 1.6 : 0.95) : 2 + (d->D <= 128 ? 0.065 : 0.034) * d->D;
-  const double fixed_us = bf16 ? 8 : 5 + 0.035 * d->D;
+  const double fixed_us = bf16 ? 8 : 5 + 0.035 * d->D, combine_us = bf16 ? 6 : 8;
   const double state_us = (double)d->B * d->Sq * d->Hq * d->D * sizeof(float) / 4e6;
   double best = (double)((wgs + 255) / 256) * (fixed_us + tiles * tile_us);
   int n_best = 1;
   for (int n = 2; n <= most && n <= tiles; ++n) {
-    const double t = (double)((wgs * n + 255) / 256) * (fixed_us + (double)((tiles + n - 1) / n) * tile_us) + 6 + (n + 1.5) * state_us;
+    const double t = (double)((wgs * n + 255) / 256) * (fixed_us + (double)((tiles + n - 1) / n) * tile_us) + combine_us + (n + 1.5) * state_us;
     if (t < 0.95 * best) {
       best = t;
       n_best = n;

@@ -19,13 +19,14 @@
 //
 // One wavefront per row with scalar fused multiply-adds, as these kernels were before, read K with every lane on a
 // row of its own and one load per four multiply-adds: 8 heads x 512 rows x 8 chunks of 512 keys at D = 128 took 2460 us
-// forward, 2640 us dQ, 3590 us dK / dV (3.2 TFLOP/s).  Now 108, 157 and 200 us with the split launches (dQ on one workgroup
-// per query tile, 128 for 256 compute units: 270 us).  Prologue, first loads and fold are about 20 us of each; long walks
-// run at 100 TFLOP/s of the 154 of a large fp32 matrix product on this card.
+// forward, 2640 us dQ, 3590 us dK / dV (3.2 TFLOP/s).  Now 104, 151 and 202 us with the split launches (on one workgroup per
+// query tile, 128 for 256 compute units: 181 us forward, 270 us dQ).  Prologue, first loads and fold are 10 to 20 us of each;
+// long walks run at 100 TFLOP/s of the 154 of a large fp32 matrix product on this card.
 #include <type_traits>
 
 #include "st_internal.h"
 #include "st_mfma.h"
+#include "st_walk.h"
 
 namespace st {
 namespace {
@@ -201,39 +202,66 @@ __device__ __forceinline__ void add_acc(const float* slot, f32x16 (&acc)[N], flo
     for (int v = 0; v < 16; ++v) acc[i][v] = own * acc[i][v] + other * slot[(16 * i + v) * 64 + lane];
 }
 
-// Walk of a wavefront over the 32-key tiles of the chunk table: tile number `wave`, wave + waves, ... of the walk
-struct KeyWalk {
-  int c, t, nv;     // chunk, first key of the tile, visible keys of the chunk for the workgroup's last row
-  int skip;         // tiles still to pass over
+// The 32-key tiles a query tile's workgroups walk, numbered through the chunks.  A share is a run of them, and the workgroup's
+// wavefronts take the tiles of the run in turn: shares differ by one tile at most, whatever the mask and the chunks (dealt out
+// in turns of eight, 104 tiles make four shares of 32 and 24: 4 heads x 400 rows x 8 chunks of 400 keys at head size 128 59 us,
+// 51 so).  The table is in LDS because arguments come from host memory: a read of them is 0.7 us, and every chunk that the
+// walk comes to would need some.
+struct KeyTable {
+  int32_t end[kMaxTable];                            // tiles up to and with this chunk that the workgroup's last row sees
+  int64_t k_offset[kMaxTable];
+  const float* k[kMaxTable];                         // of this head and batch entry
+  const float* v[kMaxTable];
 };
-template <int DP>
-__device__ __forceinline__ bool walk_next(KeyWalk& w, const Shape& s, const ChunkTable& tab, int64_t last_pos) {
-  while (w.c < tab.n) {
-    const int left = w.t < w.nv ? (w.nv - w.t + kT - 1) / kT : 0;
-    if (w.skip < left) {
-      w.t += w.skip * kT;
-      w.skip = 0;
-      return true;
-    }
-    w.skip -= left;
-    if (++w.c < tab.n) {
-      w.t = 0;
-      w.nv = visible_keys(s, last_pos, tab.k_offset[w.c]);
-    }
-  }
-  return false;
+// by one wavefront, a lane per chunk; a barrier has to follow
+__device__ __forceinline__ void build_key_table(KeyTable& tab, const Shape& s, const ChunkTable& t, int64_t last_pos, int b, int hk, int lane) {
+  static_assert(kMaxTable == 64, "a lane per chunk");
+  const int64_t k0 = t.k_offset[lane];               // the whole table is read: the loads need not wait for its length
+  const float* k = (const float*)t.k[lane] + (int64_t)b * t.ksb + (int64_t)hk * t.ksh;
+  const float* v = (const float*)t.v[lane] + (int64_t)b * t.vsb + (int64_t)hk * t.vsh;
+  const int n = lane < t.n ? (visible_keys(s, last_pos, k0) + kT - 1) / kT : 0;
+  int total;
+  tab.end[lane] = lane_scan(n, total) + n;
+  tab.k_offset[lane] = k0;
+  tab.k[lane] = k;
+  tab.v[lane] = v;
+}
+// tiles [lo, hi) of share y
+__device__ __forceinline__ void key_share(int end, int n_split, int y, int& lo, int& hi) {
+  const uint32_t total = (uint32_t)__builtin_amdgcn_readlane(end, 63), n = (uint32_t)max(n_split, 1), each = total / n, rest = total % n;
+  lo = (int)(each * y + rest * y / n);
+  hi = (int)(each * (y + 1) + rest * (y + 1) / n);
+}
+// Tile x of the walk, x below the last `end`; end = this lane's entry of the table
+struct KeyTile {
+  int key0;                                          // first key in its chunk
+  int64_t k_offset;
+  const float *k, *v;                                // at that key
+};
+__device__ __forceinline__ uint64_t uniform64(uint64_t x) { return (uint64_t)sgpr((uint32_t)x) | (uint64_t)sgpr((uint32_t)(x >> 32)) << 32; }
+__device__ __forceinline__ const float* uniform_ptr(const float* p) { return (const float*)(GlobalFloats)uniform64((uint64_t)p); }
+__device__ __forceinline__ KeyTile key_tile(const KeyTable& tab, const ChunkTable& t, int end, int x) {
+  const int c = __popcll(__ballot(end <= x));
+  const int first = c > 0 ? __builtin_amdgcn_readlane(end, c - 1) : 0;
+  KeyTile y;
+  y.key0 = (x - first) * kT;
+  y.k_offset = (int64_t)uniform64((uint64_t)tab.k_offset[c]);
+  y.k = uniform_ptr(tab.k[c]) + (int64_t)y.key0 * t.kss;
+  y.v = uniform_ptr(tab.v[c]) + (int64_t)y.key0 * t.vss;
+  return y;
 }
 
 // ---------------------------------------------------------------- forward
 // Bounded by the matrix instructions: D per 32 x 32 tile pair and 64 cycles each.  Eight wavefronts share the 32 rows.  An
-// under-filled launch (n_split > 1) gives every query tile n_split workgroups, blockIdx.y of them, which take NW tiles of the
-// walk in turn, so that their shares differ by one turn at most whatever the mask and however few chunks there are.
+// under-filled launch (n_split > 1) gives every query tile n_split workgroups, blockIdx.y of them, each with a share of the
+// walk (see KeyTable).
 template <int DP, bool FULL>
 __global__ __launch_bounds__(waves<DP>() * 64) void fwd_f32_kernel(const FwdArgs a) {
   constexpr int NW = waves<DP>(), DB = DP / 32, N = 32, NR = row_pieces<DP, N>(), NC = col_pieces<DP, N>();
   __shared__ __attribute__((aligned(16))) float qs[kT * lds_stride<DP>()];
   __shared__ float fold[NW / 2 * DB * 16 * 64];
   __shared__ float fold_m[NW / 2 * 64], fold_l[NW / 2 * 64];
+  __shared__ KeyTable tab;
   __shared__ int any_dirty;
   const Shape& s = a.s;
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -243,22 +271,26 @@ __global__ __launch_bounds__(waves<DP>() * 64) void fwd_f32_kernel(const FwdArgs
   qtile_block(blockIdx.x, gridDim.x, n_qt, s.causal, qt, hb);
   const int h = hb % s.Hq, b = hb / s.Hq, hk = h / (s.Hq / s.Hkv);
   const int row0 = qt * kT;
+  const int64_t first_pos = q_pos(s, row0), last_pos = q_pos(s, min(row0 + kT, s.Sq) - 1);
+  if (wave == 0) build_key_table(tab, s, a.t, last_pos, b, hk, lane);
   stage_tile<DP>(qs, (const float*)a.q.ptr + b * a.q.sb + h * a.q.sh, a.q.ss, row0, s.Sq, s.D, tid);
   if (tid == 0) any_dirty = 0;
   __syncthreads();
 
   const int i = min(row0 + r, s.Sq - 1);
-  const int64_t qpos = q_pos(s, i), first_pos = q_pos(s, row0), last_pos = q_pos(s, min(row0 + kT, s.Sq) - 1);
+  const int64_t qpos = q_pos(s, i);
   float m = -INFINITY, l = 0.f;
   f32x16 acc[DB];
   zero_acc(acc);
-  KeyWalk w{0, 0, a.t.n > 0 ? visible_keys(s, last_pos, a.t.k_offset[0]) : 0, (int)blockIdx.y * NW + wave};
-  while (walk_next<DP>(w, s, a.t, last_pos)) {
-    const float* kb = (const float*)a.t.k[w.c] + b * a.t.ksb + hk * a.t.ksh + (int64_t)w.t * a.t.kss;
-    const float* vb = (const float*)a.t.v[w.c] + b * a.t.vsb + hk * a.t.vsh + (int64_t)w.t * a.t.vss;
-    const int limit = min(kT, w.nv - w.t);
-    const int nv_first = visible_keys(s, first_pos, a.t.k_offset[w.c]) - w.t;                  // wave-uniform
-    const int nv = nv_first < kT ? visible_keys(s, qpos, a.t.k_offset[w.c]) - w.t : kT;
+  const int end = tab.end[lane];
+  int lo, hi;
+  key_share(end, a.n_split, blockIdx.y, lo, hi);
+  for (int x = lo + wave; x < hi; x += NW) {
+    const KeyTile w = key_tile(tab, a.t, end, x);
+    const float *kb = w.k, *vb = w.v;
+    const int limit = min(kT, visible_keys(s, last_pos, w.k_offset) - w.key0);
+    const int nv_first = visible_keys(s, first_pos, w.k_offset) - w.key0;                      // wave-uniform
+    const int nv = nv_first < kT ? visible_keys(s, qpos, w.k_offset) - w.key0 : kT;
     const float* krow = kb + (int64_t)min(r, limit - 1) * a.t.kss;
     Piece<N> f[2];
     auto load = [&](int x) {
@@ -306,7 +338,6 @@ __global__ __launch_bounds__(waves<DP>() * 64) void fwd_f32_kernel(const FwdArgs
       if (dirty) scrub(f[x & 1]);
       contract_rows<DP>(acc, f[x & 1], p, x - NR);
     }
-    w.skip = max(a.n_split, 1) * NW;
   }
 
   // fold of the wavefronts' states (m, l, O), halving their number each time
@@ -357,6 +388,7 @@ __global__ __launch_bounds__(waves<DP>() * 64) void bwd_dq_f32_kernel(const BwdA
   __shared__ __attribute__((aligned(16))) float qs[kT * lds_stride<DP>()];
   __shared__ __attribute__((aligned(16))) float dos[kT * lds_stride<DP>()];
   __shared__ float fold[NW / 2 * DB * 16 * 64];
+  __shared__ KeyTable tab;
   __shared__ int any_dirty;
   const Shape& s = a.s;
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -366,6 +398,8 @@ __global__ __launch_bounds__(waves<DP>() * 64) void bwd_dq_f32_kernel(const BwdA
   qtile_block(blockIdx.x, gridDim.x, n_qt, s.causal, qt, hb);
   const int h = hb % s.Hq, b = hb / s.Hq, hk = h / (s.Hq / s.Hkv);
   const int row0 = qt * kT;
+  const int64_t first_pos = q_pos(s, row0), last_pos = q_pos(s, min(row0 + kT, s.Sq) - 1);
+  if (wave == 0) build_key_table(tab, s, a.t, last_pos, b, hk, lane);
   stage_tile<DP>(qs, (const float*)a.q.ptr + b * a.q.sb + h * a.q.sh, a.q.ss, row0, s.Sq, s.D, tid);
   stage_tile<DP>(dos, (const float*)a.d_o.ptr + b * a.d_o.sb + h * a.d_o.sh, a.d_o.ss, row0, s.Sq, s.D, tid);
   if (tid == 0) any_dirty = 0;
@@ -375,17 +409,19 @@ __global__ __launch_bounds__(waves<DP>() * 64) void bwd_dq_f32_kernel(const BwdA
   const int64_t stat = ((int64_t)b * s.Hq + h) * s.Sq + i;
   const float lse = a.lse[stat], dl = a.delta[stat];
   const bool empty = lse == -INFINITY;                       // empty row: no gradient
-  const int64_t qpos = q_pos(s, i), first_pos = q_pos(s, row0), last_pos = q_pos(s, min(row0 + kT, s.Sq) - 1);
+  const int64_t qpos = q_pos(s, i);
   f32x16 acc[DB];
   zero_acc(acc);
   const int n_split = max(a.n_split, 1);
-  KeyWalk w{0, 0, a.t.n > 0 ? visible_keys(s, last_pos, a.t.k_offset[0]) : 0, (int)blockIdx.y * NW + wave};
-  while (walk_next<DP>(w, s, a.t, last_pos)) {
-    const float* kb = (const float*)a.t.k[w.c] + b * a.t.ksb + hk * a.t.ksh + (int64_t)w.t * a.t.kss;
-    const float* vb = (const float*)a.t.v[w.c] + b * a.t.vsb + hk * a.t.vsh + (int64_t)w.t * a.t.vss;
-    const int limit = min(kT, w.nv - w.t);
-    const int nv_first = visible_keys(s, first_pos, a.t.k_offset[w.c]) - w.t;                  // wave-uniform
-    const int nv = empty ? 0 : nv_first < kT ? visible_keys(s, qpos, a.t.k_offset[w.c]) - w.t : kT;
+  const int end = tab.end[lane];
+  int lo, hi;
+  key_share(end, n_split, blockIdx.y, lo, hi);
+  for (int x = lo + wave; x < hi; x += NW) {
+    const KeyTile w = key_tile(tab, a.t, end, x);
+    const float *kb = w.k, *vb = w.v;
+    const int limit = min(kT, visible_keys(s, last_pos, w.k_offset) - w.key0);
+    const int nv_first = visible_keys(s, first_pos, w.k_offset) - w.key0;                      // wave-uniform
+    const int nv = empty ? 0 : nv_first < kT ? visible_keys(s, qpos, w.k_offset) - w.key0 : kT;
     const float* krow = kb + (int64_t)min(r, limit - 1) * a.t.kss;
     const float* vrow = vb + (int64_t)min(r, limit - 1) * a.t.vss;
     Piece<N> f[2];
@@ -414,7 +450,6 @@ __global__ __launch_bounds__(waves<DP>() * 64) void bwd_dq_f32_kernel(const BwdA
       if (dirty) scrub(f[x & 1]);
       contract_rows<DP>(acc, f[x & 1], ds, x - 2 * NR);
     }
-    w.skip = n_split * NW;
   }
   for (int n = NW / 2; n > 0; n /= 2) {
     if (wave >= n && wave < 2 * n) put_acc(fold + (wave - n) * DB * 16 * 64, acc, lane);

@@ -58,9 +58,8 @@ struct FwdArgs {
   float* lse;      // fp32 [B,Hq,Sq]
   void* o_lowp;    // nullable, [B,Sq,Hq,D] in the storage dtype
   // Under-filled launches: n_split > 1 gives every query tile n_split workgroups (blockIdx.y), each walking a
-  // share of the tiles (contiguous in bf16, every n_split-th turn in fp32) and writing its own partial state at
-  // o + y * split_o, lse + y * split_l (floats); the states are combined afterwards.  0 or 1: one workgroup walks
-  // the whole table.
+  // share of the tiles and writing its own partial state at o + y * split_o, lse + y * split_l (floats); the states
+  // are combined afterwards.  0 or 1: one workgroup walks the whole table.
   int32_t n_split;
   int64_t split_o, split_l;
   float gap;         // fast kernel: log2 units a block maximum may exceed the lazy exponent reference by (set by its launcher)

@@ -75,7 +75,7 @@ def test_split_forward_and_a_workspace_too_small_for_it():
 
 #           D,  Sq, Sk, n, q_offset, causal, shares
 FWD_SPLIT = [(128, 64, 512, 4, 4 * 512 - 64, True, 8), # eight turns, four chunks
-             (128, 100, 512, 1, 412, True, 2),         # one chunk
+             (128, 100, 1024, 1, 924, True, 4),        # one chunk
              (64, 33, 1000, 2, 0, False, 8),           # turns that reach over two chunks, ragged last tiles
              (256, 40, 300, 3, 860, True, 8)]          # four wavefronts per workgroup
 
