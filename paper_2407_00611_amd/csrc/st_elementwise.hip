@@ -123,7 +123,8 @@ __global__ __launch_bounds__(256) void combine_kernel(const CombineArgs a, int32
     const f32x4_t t = __builtin_nontemporal_load(reinterpret_cast<const f32x4_t*>(a.o[x]) + v_in);   // read once
     return make_float4(t.x, t.y, t.z, t.w);
   };
-  // a weight of exactly 0 must not turn a non-finite value of an empty state into NaN
+  // The O of an empty state may never have been written (the split forward leaves it out): it is loaded like the others, and a
+  // weight of exactly 0 keeps it, NaN or not, out of the sum.
   auto add = [](float4& r, float w, const float4& p) {
     if (w != 0.f) {
       r.x = fmaf(w, p.x, r.x);
@@ -518,7 +519,7 @@ hipError_t launch_add_parts(float* dst, const float* parts, int n_parts, int64_t
 hipError_t launch_add_kv_parts(const BwdArgs& a, hipStream_t s) {
   const int64_t n_vec = (int64_t)a.s.B * a.s.Sk * a.s.Hkv * a.s.D / 4;
   if (n_vec <= 0 || a.t.n <= 0) return hipSuccess;
-  ProfScope prof("add_parts", s);
+  ProfScope prof("add_kv_parts", s);
   hipLaunchKernelGGL(add_kv_parts_kernel, dim3(blocks_for(n_vec), 2 * a.t.n), dim3(256), 0, s, a, n_vec);
   return hipGetLastError();
 }

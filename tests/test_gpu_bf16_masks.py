@@ -96,7 +96,35 @@ def test_the_largest_probability_carries_no_rounding(c, mode):
 def test_split_cuts_the_masked_part():
     """One head, so the walk of every query tile is split sixteen ways and some splits hold masked tiles only."""
     w = si.Workload("split_masks", 331, "bf16", 1, 1, 1, 128, 700, 700, 3, 1400, True, False)
+    st.st_profile_begin()
     _check(w, si.make_inputs(w), [[0, 1, 2], [2, 0, 1]], args=("bf16",))
+    assert "combine" in st.st_profile_end(), "this share was meant to be split"
+
+
+@pytest.mark.parametrize("D", [128, 64])
+def test_the_state_of_an_empty_share_stays_out(D):
+    """First rank of a causal ring: the plan counts the tiles of the last rows, so some shares of the first query tile have
+    none.  They leave their O unwritten, here NaN, behind an lse of -inf."""
+    w = si.Workload("empty_shares", 343, "bf16", 1, 1, 1, D, 1024, 1024, 1, 0, True, False)
+    inp = si.make_inputs(w)
+    q, ks, vs, _ = upload(inp)
+    b_o, b_l = q.numel() * 4, 1024 * 4
+    need = st.st_ring_workspace_bytes(q, ks, vs, 0, [0], True, w.scale, st.ST_RING_FUSED, False)
+    shares = need // (b_o + b_l)
+    assert shares > 1, "this share was meant to be split"
+    ws = torch.full((need + 256,), 0xff, dtype=torch.uint8, device="cuda")
+    o, lse, low = st.st_ring_fwd(q, ks, vs, 0, [0], True, w.scale, [0], workspace=ws)
+    first, empty = (-ws.data_ptr()) % 256, 0
+    for y in range(shares):
+        state = ws[first + y * (b_o + b_l):first + (y + 1) * (b_o + b_l)].view(torch.float32)
+        if torch.isneginf(state[b_o // 4:b_o // 4 + 256]).all():
+            assert torch.isnan(state[:256 * D]).all()
+            empty += 1
+    assert empty > 0, "every share of the first query tile had a tile"
+    o_ref, lse_ref = oa.attention_forward(inp.q, inp.k, inp.v, *positions(w), True, w.scale)
+    assert_close(host(o), o_ref, "bf16", "o")
+    assert_close(host(lse), lse_ref, "bf16", "lse", lse=True)
+    assert torch.equal(low, o.to(torch.bfloat16))
 
 
 def _backward(w, inp, mode, assign=None):
@@ -152,8 +180,9 @@ def test_backward_split_over_workgroups():
     base = (w.Hq * w.Sq * 4 + 255) // 256 * 256 + 1024 + n_o // 2       # Delta, the counters, the scaled copy of Q
     assert need > base + n_o
     o, lse, low = st.st_ring_fwd(q, ks, vs, *args, order)
-    got = []
+    got, launches = [], []
     for ws in (None, None, "noalloc", base, base + n_o):
+        st.st_profile_begin()
         dq = torch.zeros_like(o)
         dk = [torch.zeros(k.shape, device="cuda") for k in ks]
         dv = [torch.zeros(k.shape, device="cuda") for k in ks]
@@ -162,7 +191,9 @@ def test_backward_split_over_workgroups():
         else:
             buf = None if ws is None else torch.empty(ws + 256, dtype=torch.uint8, device="cuda")
             st.st_ring_bwd(q, ks, vs, d_o, low, lse, *args, order, dq, dk, dv, workspace=buf)
+        launches.append(st.st_profile_end())
         got.append(dq)
+    assert ["add_parts" in x for x in launches] == [True, True, True, False, True]
     assert torch.equal(got[0], got[1]) and torch.equal(got[0], got[2])
     assert_close(host(got[3]), host(got[0]), "bf16", "dq unsplit")
     assert_close(host(got[4]), host(got[0]), "bf16", "dq of two shares and one partial sum")
@@ -175,8 +206,10 @@ def test_key_tiles_split_over_workgroups(D, how):
     the causal shard leaves some shares of some tiles without a block, and a chunk in the future without any."""
     w = si.Workload("split_kv", 333, "bf16", 1, 4, 1, D, 1070, 300, 3, -200, True, True)
     print(f"[key tile split] D={D} {how}", flush=True)
+    st.st_profile_begin()
     _backward(w, si.make_inputs(w), st.ST_RING_STEPWISE if how == "stepwise" else st.ST_RING_FUSED,
               {"assign": True, "add_lowp": False}.get(how))
+    assert "add_kv_parts" in st.st_profile_end(), "the key tiles of this share were meant to be split"
 
 
 def test_block_backward_with_and_without_room_for_partial_sums():
@@ -192,8 +225,10 @@ def test_block_backward_with_and_without_room_for_partial_sums():
     ref = oa.attention_backward(inp.q, inp.k, inp.v, inp.d_o, q_pos, k_pos, True, w.scale)
     for size in (need, small):
         dq, dk, dv = torch.zeros_like(o), torch.zeros(ks[0].shape, device="cuda"), torch.zeros(ks[0].shape, device="cuda")
+        st.st_profile_begin()
         st.st_attn_block_bwd(q, ks[0], vs[0], d_o, lse, delta, 0, 0, True, w.scale, dq, dk, dv,
                              workspace=torch.empty(size + 256, dtype=torch.uint8, device="cuda"))
+        assert ("add_kv_parts" in st.st_profile_end()) == (size == need)
         assert_close(host(dq), ref[0], "bf16", "dq")
         assert_close_wide(host(dk), ref[1][0], "dk")
         assert_close_wide(host(dv), ref[2][0], "dv")

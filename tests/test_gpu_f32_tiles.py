@@ -67,7 +67,9 @@ def test_split_forward_and_a_workspace_too_small_for_it():
     q_pos, k_pos = positions(w)
     o_r, lse_r = oa.attention_forward(inp.q, inp.k, inp.v, q_pos, k_pos, True, w.scale)
     for ws in (None, torch.empty(256, dtype=torch.uint8, device="cuda")):
+        st.st_profile_begin()
         o, lse, low = st.st_ring_fwd(*args, list(range(4)), workspace=ws)
+        assert ("combine" in st.st_profile_end()) == (ws is None)
         assert_close(host(o), o_r, "f32", "o")
         assert_close(host(lse), lse_r, "f32", "lse")
         assert torch.equal(o, low)
