@@ -11,14 +11,7 @@
 namespace st {
 namespace {
 
-typedef __attribute__((__vector_size__(16 * sizeof(uint32_t)))) uint32_t u32x16;
 typedef __attribute__((__vector_size__(4 * sizeof(uint32_t)))) uint32_t u32x4v;
-
-// XOR swizzle of the LDS tiles (the f of swz<D> in st_mfma.h)
-template <int D>
-__device__ __forceinline__ int swz_f(int row) {
-  return D == 128 ? (((row & 3) << 2) | ((row >> 2) & 3)) : ((((row >> 1) & 1) << 2) | ((row >> 2) & 3));
-}
 
 constexpr float kLog2e = 1.4426950408889634f;
 

@@ -8,6 +8,14 @@
 namespace st {
 namespace {
 
+typedef __attribute__((__vector_size__(16 * sizeof(uint32_t)))) uint32_t u32x16;
+
+// XOR swizzle of the LDS tiles (the f of swz<D> in st_mfma.h)
+template <int D>
+__device__ __forceinline__ int swz_f(int row) {
+  return D == 128 ? (((row & 3) << 2) | ((row >> 2) & 3)) : ((((row >> 1) & 1) << 2) | ((row >> 2) & 3));
+}
+
 // every value passed through sgpr() is uniform over the wavefront by construction (kernel arguments, block index)
 __device__ __forceinline__ uint32_t sgpr(uint32_t x) { return __builtin_amdgcn_readfirstlane(x); }
 __device__ __forceinline__ uint32_t lo32(const void* p) { return (uint32_t)(uintptr_t)p; }
