@@ -29,9 +29,9 @@
  *     k_offset + t <= q_offset + i.  lse is the natural-log log-sum-exp of
  *     scale * <q, k> over visible keys; a row with no visible key has O = 0
  *     and lse = -inf.
- *   - Supported: ST_F32 with D <= 256 (plain kernels), ST_BF16 with D == 128
- *     or D == 64 (MFMA kernels, fp32 accumulation).  Anything else returns
- *     ST_ERR_UNSUPPORTED.
+ *   - Supported: ST_F32 with D <= 256 and D % 8 == 0 (fp32 MFMA kernels), ST_BF16
+ *     with D == 128 or D == 64 (bf16 MFMA kernels, fp32 accumulation).  Anything
+ *     else returns ST_ERR_UNSUPPORTED.
  *   - Precision of the ST_BF16 path: P and dS are rounded to bf16 before the
  *     second contractions, and every kernel, forward and backward, evaluates
  *     the scores from the same operand Q' = bf16(Q * scale * log2 e), so that
@@ -235,7 +235,8 @@ st_status st_schedule_report(int32_t P, int32_t C, int64_t B, int64_t N, int64_t
  *   [B,Sq,Hq,D] in desc->dtype.
  * workspace: device, >= st_ring_workspace_bytes(desc, mode, backward) bytes, 256-byte aligned.  Its contents
  *   are the library's (partial states, Delta, the tile counters of the dK/dV launch, the scaled copy of Q, partial
- *   sums of backward launches that would leave part of the chip idle) and mean nothing between calls; calls that share a workspace must be ordered on one stream. */
+ *   sums of backward launches that would leave part of the chip idle) and mean nothing between calls; calls that share a
+ *   workspace must be ordered on one stream. */
 size_t st_ring_workspace_bytes(const st_ring_desc* desc, int32_t mode, int32_t backward);
 
 st_status st_ring_fwd(const st_ring_desc* desc, const st_tensor* q, const int32_t* order,
@@ -259,8 +260,8 @@ st_status st_ring_bwd(const st_ring_desc* desc, const st_tensor* q, const st_ten
  * runs on holds until the process ends.  The call allocates and frees nothing (no hipMalloc / hipFree, no
  * allocating library routine); the array's device address is looked up once per device, on the first call.
  * A share whose Delta, counters and copy of Q exceed the array returns ST_ERR_WORKSPACE and enqueues nothing;
- * partial sums take no more than the room that is left in it, here and in st_ring_bwd alike.  Every call on a GPU uses that GPU's one array (what must start at zero is cleared by the call
- * itself): calls that overlap on one GPU, on different streams or from different threads, race; order them. */
+ * partial sums take no more than the room that is left in it, here and in st_ring_bwd alike.  Every call on a GPU uses
+ * that GPU's one array (what must start at zero is cleared by the call itself): calls that overlap on one GPU, on different streams or from different threads, race; order them. */
 st_status st_ring_bwd_noalloc(const st_ring_desc* desc, const st_tensor* q, const st_tensor* d_o,
                               const st_tensor* o, int32_t o_dtype, const float* lse_final,
                               const int32_t* order, int32_t n_visit, int32_t mode,

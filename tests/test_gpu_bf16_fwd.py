@@ -19,7 +19,7 @@ STEP_CASES = [
     ("ragged_causal_d64", 2, 3, 1, 64, 260, 150, 2, 40, True),
     ("noncausal_d64", 1, 4, 4, 64, 515, 64, 3, 0, False),
     ("one_row_one_key", 1, 1, 1, 128, 1, 1, 1, 0, True),
-    # full 256-query tiles: the hand-scheduled loop takes the fully visible 64-key tiles, the general kernel the rest
+    # the hand-scheduled loop: one tile, two, switches of the chunk, whole and masked tiles
     ("fast_one_tile", 1, 1, 1, 128, 256, 64, 1, 0, False),
     ("fast_two_tiles", 1, 1, 1, 128, 256, 128, 1, 0, False),
     ("fast_chunk_switches", 2, 4, 2, 128, 300, 320, 3, 0, False),
@@ -200,10 +200,9 @@ def _tight_reference_case(D, gap):
 @pytest.mark.parametrize("D", [128, 64])
 @pytest.mark.parametrize("Sq,causal", [(512, True), (300, True), (600, False), (256, True)])
 def test_split_forward_on_a_poisoned_workspace(D, Sq, causal):
-    """Under-filled fused forward: the query tiles are split over the chunks, hand-scheduled and general
-    workgroups run side by side in one launch and the partial states (one per split, one for the masked and
-    ragged tiles) are combined.  The workspace starts out full of NaN, so a state row nobody wrote, or one that
-    is read although it is empty, shows; ragged row counts leave rows that only the general workgroups cover."""
+    """Under-filled fused forward: the walk of every query tile is split over workgroups and the partial states (one per
+    share) are combined.  The workspace starts out full of NaN, so a state row nobody wrote, or one that is used although
+    it is empty, shows; ragged row counts leave query tiles with rows that do not exist."""
     n, Sk = 7, 320
     w = si.Workload(f"split_sq{Sq}", 88, "bf16", 1, 2, 1, D, Sq, Sk, n, (n - 2) * Sk - Sq + 100 if causal else 0, causal, False)
     inp = si.make_inputs(w)

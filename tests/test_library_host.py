@@ -119,7 +119,7 @@ def test_empty_problems_are_ok_without_a_gpu():
 
 
 def test_forward_workspace_covers_every_visited_subset():
-    """An under-filled fused forward is split over the visited chunks; the workspace the library asks for must be
+    """An under-filled fused forward is split over workgroups; the workspace the library asks for must be
     enough for any subset of the table the caller may then visit (host logic only: no launch)."""
     import torch
 
@@ -129,7 +129,7 @@ def test_forward_workspace_covers_every_visited_subset():
         return st.st_ring_workspace_bytes(q, ks, ks, 0, [Sk * j for j in range(n_chunks)], True, 0.1, st.ST_RING_FUSED, False)
 
     one = need(1)
-    assert one > 0 and need(2) == 3 * one                    # two chunks: a state per split and the general workgroups' own
+    assert one > 0 and need(2) == 3 * one                    # two chunks: what a small share has always asked for
     sizes = [need(n) for n in (1, 2, 5, 16, 50, 64)]
     assert sizes == sorted(sizes)                             # grows with the table ...
     assert need(150) == need(64) == need(256)                 # ... up to one launch's table, and stays there
