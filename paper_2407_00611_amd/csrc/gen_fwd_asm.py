@@ -27,13 +27,17 @@ first tile, so that the P of that key is 1 and carries no rounding: a row that s
 sequence) is mostly that key.  Rounded up to whole log2 units it made O of the first rows of a sequence 1.6e-3 wrong where
 one key is seen and the result is exact, of rows 1 to 31 2.0e-3 instead of 1.5e-3, of 2000 rows together 2.19e-3 instead of
 1.91e-3.  From there it is lazy: it only moves, by a whole number of log2 units, when a block's maximum exceeds it by more
-than GAP, so the rescale factor is an exact power of two and the common path never touches the accumulators.
+than GAP, so the rescale factor is an exact power of two and the common path never touches the accumulators.  That is
+noticed by the block's row sums, which are there anyway: while they stay below a limit no exponent was too large, and
+beyond it, infinities included, nothing of the block has been used yet and its exponents still stand where the MFMAs put
+them.  A maximum of its own, 17 of 97 VALU instructions per block, cost the loop 2 % at head size 128 (6.03 ms, now 5.90)
+and 5 % at 64 (11.7 ms, now 11.1), where it waits for VALU issue.
 
 Per 32-key block i and wavefront two groups of 16 MFMAs, software-pipelined two blocks deep:
     group B   O^T += V^T P^T(i)          A: V^T of block i by LDS transpose reads, B: packed P(i)
     group A   S^T(i+2) = K Q^T           A: K rows of block i+2 from LDS,          B: Q fragments (AGPRs)
-    VALU      slots 3..9: row maximum of S(i+1), both halves, and the test against the reference
-              (rare: call the rescale routine);  slots 10..31: P(i+1) = exp2(S c - r), bf16 pack, row sums
+    VALU      slots 3..30: P(i+1) = exp2(S c - r), bf16 pack, row sums of the block; behind slot 30 the test of the sums
+              (rare: call the rescale routine), then their addition to the running ones
 K / V tiles (64 keys) arrive by direct global->LDS loads into a 4-stage ring, three tiles ahead; one
 barrier per tile.  The chunk table (base pointers, tiles per chunk) sits in LDS, written by the C++ side.
 """
@@ -49,7 +53,7 @@ TILE = 64 * ROW                                      # one 64-key tile
 NDMA = TILE // 4096                                  # direct-to-LDS loads per wavefront and tile (4 wavefronts x 1 KiB each)
 NSLOT = 4 * DB + 2 * KS                              # MFMAs per key block and wavefront
 SPLIT = 4 * 2 * TILE > 65536                         # ring beyond the 16-bit offset field: second set of base registers
-                                                     # (GAP, log2 units a block maximum may exceed the reference by, arrives in s46)
+                                                     # (the limit of a block sum, 2^(GAP + 4), arrives in s46)
 
 # ---- AGPRs
 def ACC(db, qb): return 16 * (2 * db + qb)
@@ -61,22 +65,24 @@ def P16(buf, qb, m): return 64 + 16 * buf + 8 * qb + 4 * m
 def NL(qb): return 240 - 16 * qb                     # sixteen copies of -r (minus the exponent reference, log2 units):
                                                      # the C operand that starts every S^T accumulator
                                                      # (NL(1) reuses the input registers once the prologue has read them)
-def LSUM(qb, m, c=0): return (98 if c == 0 else 194) + 2 * qb + m   # partial row sums (this lane's key rows), two chains each
-def MX(qb): return 102 + qb                         # block maximum, then d = max * c - r
-GAPR, DMAX = 105, 106                                # GAP; max over both query blocks of d
+def LSUM(qb): return 98 + qb                        # row sum over the blocks before (this lane's key rows)
+def BSUM(qb, c): return 100 + 2 * qb + c             # of the block in hand, two chains
+LIMR, SMAX = 105, 106                                # what a block sum may be; largest block sum of both query blocks
+def MX(qb): return 194 + qb                         # row maximum (prologue, rescale routine)
 TMP = 108                                            # 108..119
 POOL0 = 120                                          # 2 rings x 4 fragments x 4 registers
 XL, XH = 152, 160
 TRLO_L, TRHI_L, TRLO_H, TRHI_H = 168, 172, 176, 180
 KOFF, VOFF = 184, 188
 OOFF, LSEOFF = 192, 193
-RT = 200                                             # 200..223: temporaries of the out-of-line routines
+RT = 200                                             # 200..223: probabilities on their way to the pack; temporaries of the
+                                                     # out-of-line routines, which are called when none is
 def QREL(qb): return 198 + qb                        # the row's position relative to the tile's first row, less 4 * (lane / 32)
 def SEEN(qb): return 104 if qb == 0 else 107         # 0: the row has met no visible key yet
 # inputs (pinned by the C++ side): v[224:239]
 I_QROW0, I_QROW1, I_XBASE, I_GF16, I_TRBASE, I_LF16, I_KOFF0, I_VOFF0, I_OOFF, I_LSEOFF, I_QREL, I_LIVE = (
     224, 226, 228, 229, 230, 231, 232, 233, 234, 235, 236, 238)       # I_LIVE: bit qb = the lane's row of block qb exists
-S_GAP = 46
+S_LIMIT = 46
 (S_LDS, S_WAVE, S_NT, S_KRS16, S_VRS16, S_SCALE, S_OPTR, S_OQB, S_TBL, S_KTILE, S_VTILE, S_LSEPTR) = (
     32, 33, 34, 35, 36, 37, 38, 40, 41, 42, 43, 44)
 # scalar temporaries
@@ -96,8 +102,11 @@ PARAMS = 3 * 64 * 32                                 # offset of the parameter b
 LDS_BYTES = TBL + PARAMS + 64
 
 LAT = int(os.environ.get("ST_GEN_FWD_LAT", 3))
-BUDGET = int(os.environ.get("ST_GEN_FWD_BUDGET", 6 if D == 128 else 13))
-BRANCH_SLOT = 2 * DB + 1                             # the reference test sits behind this MFMA slot (m = 1, db = 0 issued)
+# issue units of side work per MFMA slot: 0 = spread evenly; otherwise as many as fit, from the first slot on, the rest in one lump
+# ahead of the test.  24 heads of 64 x 16384 rows x 131072 keys: 11.30 ms evenly, 11.10 by sixes, 11.15 by sevens, 11.4 by nines and
+# more; 32/8 heads of 128 x 4096 rows x 32 chunks of 4096: 5.90 ms evenly, 5.93 by sixes, 6.0 and 6.1 by sevens and eights.
+BUDGET = int(os.environ.get("ST_GEN_FWD_BUDGET", 0 if D == 128 else 6))
+BRANCH_SLOT = NSLOT - 2                              # the test of the row sums sits behind this MFMA slot
 
 
 NEXT_STUBS = []                                      # (label, return label) of every switch to the next chunk
@@ -155,49 +164,50 @@ def read_vt(p, blk, m, db, seq):
     p.e.ds_read(f"ds_read_b64_tr_b16 {vr(r + 2, 2)}, {vr(hi + db)} offset:{off}", tag)
 
 
-def valu_max(buf):
-    """d = maximum of the exponents S c - r in buffer `buf` over this lane's key rows, per query block.  The test against
-    GAP is a wavefront-wide vote, so the common path does not need the halves of the wavefront combined."""
+def valu_exchange(reg=MX, op="v_max_f32"):
+    """The two halves of the wavefront hold different key rows of the same query column: combine them in both."""
     out = []
     for qb in range(QB):
-        s0 = SBUF(buf, qb)
-        out.append(f"v_max3_f32 {vr(MX(qb))}, {vr(s0)}, {vr(s0 + 1)}, {vr(s0 + 2)}")
-        for v in range(3, 15, 2):
-            out.append(f"v_max3_f32 {vr(MX(qb))}, {vr(MX(qb))}, {vr(s0 + v)}, {vr(s0 + v + 1)}")
-        out.append(f"v_max_f32 {vr(MX(qb))}, {vr(MX(qb))}, {vr(s0 + 15)}")
-    out.append(f"v_max_f32 {vr(DMAX)}, {vr(MX(0))}, {vr(MX(1))}")
-    return out
-
-
-def valu_exchange():
-    """The two halves of the wavefront hold different key rows of the same query column: make MX the maximum of both."""
-    out = []
-    for qb in range(QB):
-        out.append(f"v_mov_b32 {vr(TMP + qb)}, {vr(MX(qb))}")
+        out.append(f"v_mov_b32 {vr(TMP + qb)}, {vr(reg(qb))}")
     out.append("s_nop 1")
     for qb in range(QB):
-        out.append(f"v_permlane32_swap_b32 {vr(TMP + qb)}, {vr(MX(qb))}")
+        out.append(f"v_permlane32_swap_b32 {vr(TMP + qb)}, {vr(reg(qb))}")
     out.append("s_nop 1")
     for qb in range(QB):
-        out.append(f"v_max_f32 {vr(MX(qb))}, {vr(MX(qb))}, {vr(TMP + qb)}")
+        out.append(f"{op} {vr(reg(qb))}, {vr(reg(qb))}, {vr(TMP + qb)}")
     return out
 
 
 def valu_exp(sbuf, pbuf):
-    """P = exp2(exponent) in place, packed to bf16 into P buffer `pbuf`, row sums of the fp32 values (plain adds
-    in two chains per group: measured cheaper than v_dot2c_f32_bf16 on the packed values against ones)."""
+    """P = exp2(exponent), packed to bf16 into P buffer `pbuf`, and the block's row sums of the fp32 values (plain adds
+    in two chains per query block: measured cheaper than v_dot2c_f32_bf16 on the packed values against ones).  The
+    exponents stay where they are: the rescale routine starts from them again."""
     out = []
     for qb in range(QB):
         for m in range(2):
-            rs = [SBUF(sbuf, qb) + 8 * m + i for i in range(8)]
-            for r in rs:
-                out.append((f"v_exp_f32 {vr(r)}, {vr(r)}", (), 2))
+            es = [SBUF(sbuf, qb) + 8 * m + i for i in range(8)]
+            rs = [RT + 8 * ((2 * qb + m) % 3) + i for i in range(8)]
+            for x, r in zip(es, rs):
+                out.append((f"v_exp_f32 {vr(r)}, {vr(x)}", (), 2))
             for i in range(4):
                 d = P16(pbuf, qb, m) + i
                 out.append((f"v_cvt_pk_bf16_f32 {vr(d)}, {vr(rs[2 * i])}, {vr(rs[2 * i + 1])}", (d,), 1))
-            for i in range(8):
-                out.append((f"v_add_f32 {vr(LSUM(qb, m, i % 2))}, {vr(LSUM(qb, m, i % 2))}, {vr(rs[i])}", (), 1))
+            for c in range(2):
+                s = BSUM(qb, c)
+                out.append((f"v_add_f32 {vr(s)}, {vr(rs[c])}, {vr(rs[2 + c])}" if m == 0 else f"v_add_f32 {vr(s)}, {vr(s)}, {vr(rs[c])}", (), 1))
+                if m:
+                    out.append((f"v_add_f32 {vr(s)}, {vr(s)}, {vr(rs[2 + c])}", (), 1))
+            for i in range(4, 8):
+                s = BSUM(qb, i % 2)
+                out.append((f"v_add_f32 {vr(s)}, {vr(s)}, {vr(rs[i])}", (), 1))
+    for qb in range(QB):
+        out.append((f"v_add_f32 {vr(BSUM(qb, 0))}, {vr(BSUM(qb, 0))}, {vr(BSUM(qb, 1))}", (), 1))
     return out
+
+
+def valu_take():
+    """The block's row sums into the running ones."""
+    return [f"v_add_f32 {vr(LSUM(qb))}, {vr(LSUM(qb))}, {vr(BSUM(qb, 0))}" for qb in range(QB)]
 
 
 def gen_iter(p, cur, nxt, nxt2, par, seq, do_a=True, do_valu=True, head=None, prefetch=True, side=None, masked=False):
@@ -207,35 +217,38 @@ def gen_iter(p, cur, nxt, nxt2, par, seq, do_a=True, do_valu=True, head=None, pr
     e.comment(f"======== block {cur}: O^T += V^T P^T{cur} | S^T{nxt2} -> buffer {par} | softmax of {nxt}")
     reads = {k: [] for k in range(-1, NSLOT)}
 
-    def plan(first_use, fn):
-        reads[max(first_use - LAT, -1)].append(fn)
+    def plan(first_use, fn, n):                           # n LDS reads, LAT slots ahead
+        reads[max(first_use - LAT, -1)].append((fn, n))
 
     slots = []
     for m in range(2):
         for db in range(DB):
             k = 2 * (DB * m + db)
             if not (m == 0 and db < 2):                   # requested at the tail of the block before
-                plan(k, (lambda m=m, db=db: read_vt(p, cur, m, db, seq)))
+                plan(k, (lambda m=m, db=db: read_vt(p, cur, m, db, seq)), 2)
             for qb in range(QB):
                 slots.append(("B", m, db, qb))
     if do_a:
         for ks in range(KS):
-            plan(4 * DB + 2 * ks, (lambda ks=ks: read_k(p, nxt2, ks, seq)))
+            plan(4 * DB + 2 * ks, (lambda ks=ks: read_k(p, nxt2, ks, seq)), 1)
             for qb in range(QB):
                 slots.append(("A", ks, qb))
     else:
         slots += [None] * (2 * KS)
     if prefetch and nxt is not None:
         for db in range(2):
-            reads[NSLOT - 3 + db].append(lambda db=db: read_vt(p, nxt, 0, db, seq + 1))
+            reads[NSLOT - 3 + db].append(((lambda db=db: read_vt(p, nxt, 0, db, seq + 1)), 2))
 
-    valu_m = valu_max(1 - par) if do_valu else []
     valu_e = valu_exp(1 - par, 1 - par) if do_valu else []
-    mi, vi = [0], [0]
+    vi = [0]
+    left = 0
+
+    def side_units(k):                                   # what stands beside the softmax behind MFMA slot k
+        return sum(n for _, n in reads[k]) + (2 if side and k in side else 0)
 
     if head is not None:
         head()
-    for fn in reads[-1]:
+    for fn, _ in reads[-1]:
         fn()
     for k, sl in enumerate(slots):
         if sl is not None and sl[0] == "B":
@@ -250,40 +263,36 @@ def gen_iter(p, cur, nxt, nxt2, par, seq, do_a=True, do_valu=True, head=None, pr
             e.need(tag)
             d = vr(SBUF(par, qb), 16)
             e.mfma(d, vr(p.use(tag), 4), ar(QF(qb, ks), 4), vr(NL(qb), 16) if ks == 0 else d)
-        units = 0
-        for fn in reads[k]:
-            n0 = len(e.ds)
+        units = side_units(k)
+        for fn, _ in reads[k]:
             fn()
-            units += len(e.ds) - n0
         if side and k in side:                           # tile request / stream bookkeeping spread under the MFMAs
             for ln in side[k]:
                 e.raw(ln)
-            units += 2
         if do_valu and masked and k == 3:
             mask_test(e, S_NM1 if par else S_NM, 1 - par)
         if do_valu:
             # S(i+1) was written by the last group of the block before: first reader three MFMA issues later
-            while 3 <= k <= BRANCH_SLOT and mi[0] < len(valu_m) and (units < BUDGET or k == BRANCH_SLOT):
-                e.raw(valu_m[mi[0]])
-                mi[0] += 1
-                units += 1
+            budget = BUDGET or -(-(sum(x[2] for x in valu_e[vi[0]:]) + sum(side_units(j) for j in range(k, BRANCH_SLOT))) // max(BRANCH_SLOT - k, 1))
+            while 3 <= k < BRANCH_SLOT and vi[0] < len(valu_e) and units + valu_e[vi[0]][2] <= budget:
+                e.valu(valu_e[vi[0]][0], valu_e[vi[0]][1])
+                units += valu_e[vi[0]][2]
+                vi[0] += 1
             if k == BRANCH_SLOT:
+                left = len(valu_e) - vi[0]
+                for text, writes, _ in valu_e[vi[0]:]:       # what did not fit under the MFMAs (the pipeline stalls on it)
+                    e.valu(text, writes)
                 # the common path falls through; the call sits out of line behind the loop (a taken branch costs a refetch)
                 l_call, l_back = e.label("call"), e.label("back")
-                e.raw(f"v_cmp_gt_f32 vcc, {vr(DMAX)}, {vr(GAPR)}")
+                e.raw(f"v_max_f32 {vr(SMAX)}, {vr(BSUM(0, 0))}, {vr(BSUM(1, 0))}")
+                e.raw(f"v_cmp_gt_f32 vcc, {vr(SMAX)}, {vr(LIMR)}")
                 e.raw("s_cmp_lg_u64 vcc, 0")
                 e.raw(f"s_cbranch_scc1 {l_call}")
                 e.raw(l_back + ":")
                 STUBS.append((l_call, l_back, par))
-            while k > BRANCH_SLOT and vi[0] < len(valu_e) and units + valu_e[vi[0]][2] <= BUDGET:
-                e.valu(valu_e[vi[0]][0], valu_e[vi[0]][1])
-                units += valu_e[vi[0]][2]
-                vi[0] += 1
-    leftover = len(valu_e) - vi[0]
-    while vi[0] < len(valu_e):           # what did not fit under the MFMAs (the pipeline stalls on it)
-        e.valu(valu_e[vi[0]][0], valu_e[vi[0]][1])
-        vi[0] += 1
-    return leftover if do_a else 0
+                for ln in valu_take():
+                    e.raw(ln)
+    return left if do_a else 0
 
 
 def mask_test(e, limit, buf):
@@ -376,34 +385,40 @@ def gen_mask_routine(e, kb):
     e.raw(f"s_setpc_b64 {sr(T_MRET, 2)}")
 
 
-def gen_rescale_routine(e, pbuf):
-    """Called when some row's block maximum exceeds its reference by more than GAP.  MFMA slots 0..BRANCH_SLOT of
-    the calling block have been issued (all of m = 0 and db = 0 of m = 1); the rest of m = 1 still reads P buffer
-    `pbuf`; the exponents in score buffer 1 - pbuf wait for their softmax.  Moves the reference of the jumping rows
-    up by k = ceil(d) log2 units: accumulators, row sums and the pending packed P values are multiplied by 2^-k
-    (exact), k is taken off the waiting exponents and off the start values of the S^T accumulators."""
+def gen_rescale_routine(e, par):
+    """Called when some row's sum over the block whose softmax has just been done exceeds the limit 2^(GAP + 4): its
+    largest exponent exceeds GAP then (a lane's sum has 16 terms), or was too large for exp2.  Nothing of that block has
+    been used: its exponents still sit in score buffer 1 - par, its P in P buffer 1 - par and its sums apart.  Moves the
+    reference of these rows up by k = ceil(maximum) log2 units: accumulators and running sums are multiplied by 2^-k
+    (exact), k is taken off the exponents of this block, off those of the next one (score buffer par; an MFMA or two that
+    add to them are still to come) and off the start values of the S^T accumulators; then the softmax is done again."""
     e.raw("s_nop 7")
     e.raw("s_nop 7")
     e.raw("s_nop 7")
+    for qb in range(QB):
+        x = SBUF(1 - par, qb)
+        e.raw(f"v_max3_f32 {vr(MX(qb))}, {vr(x)}, {vr(x + 1)}, {vr(x + 2)}")
+        for v in range(3, 15, 2):
+            e.raw(f"v_max3_f32 {vr(MX(qb))}, {vr(MX(qb))}, {vr(x + v)}, {vr(x + v + 1)}")
+        e.raw(f"v_max_f32 {vr(MX(qb))}, {vr(MX(qb))}, {vr(x + 15)}")
     for ln in valu_exchange():          # both halves of a query column must move their reference by the same amount
+        e.raw(ln)
+    for ln in valu_exchange(lambda qb: BSUM(qb, 0)):
         e.raw(ln)
     alpha = [RT, RT + 1]
     for qb in range(QB):
         k, ki = RT + 2 + qb, RT + 4 + qb
         e.raw(f"v_ceil_f32 {vr(k)}, {vr(MX(qb))}")
-        e.raw(f"v_cmp_gt_f32 vcc, {vr(MX(qb))}, {vr(GAPR)}")
+        e.raw(f"v_cmp_gt_f32 vcc, {vr(BSUM(qb, 0))}, {vr(LIMR)}")
         e.raw("s_nop 1")
         e.raw(f"v_cndmask_b32 {vr(k)}, 0, {vr(k)}, vcc")
-        for v in range(16):
-            e.raw(f"v_sub_f32 {vr(NL(qb) + v)}, {vr(NL(qb) + v)}, {vr(k)}")
-        for v in range(16):             # exponents of the block whose softmax comes next: they carry the old reference
-            e.raw(f"v_sub_f32 {vr(SBUF(1 - pbuf, qb) + v)}, {vr(SBUF(1 - pbuf, qb) + v)}, {vr(k)}")
+        for reg in (NL(qb), SBUF(0, qb), SBUF(1, qb)):
+            for v in range(16):
+                e.raw(f"v_sub_f32 {vr(reg + v)}, {vr(reg + v)}, {vr(k)}")
         e.raw(f"v_cvt_i32_f32 {vr(ki)}, {vr(k)}")
         e.raw(f"v_sub_u32 {vr(ki)}, 0, {vr(ki)}")
         e.raw(f"v_ldexp_f32 {vr(alpha[qb])}, 1.0, {vr(ki)}")
-        for m in range(2):
-            for c in range(2):
-                e.raw(f"v_mul_f32 {vr(LSUM(qb, m, c))}, {vr(alpha[qb])}, {vr(LSUM(qb, m, c))}")
+        e.raw(f"v_mul_f32 {vr(LSUM(qb))}, {vr(alpha[qb])}, {vr(LSUM(qb))}")
     t = RT + 8
     for qb in range(QB):
         for db in range(DB):
@@ -414,13 +429,8 @@ def gen_rescale_routine(e, pbuf):
                     e.raw(f"v_mul_f32 {vr(t + i)}, {vr(alpha[qb])}, {vr(t + i)}")
                 for i in range(8):
                     e.raw(f"v_accvgpr_write_b32 {ar(ACC(db, qb) + v0 + i)}, {vr(t + i)}")
-        for i in range(4):                                   # pending packed P values: m = 1
-            pr = P16(pbuf, qb, 1) + i
-            e.raw(f"v_lshlrev_b32 {vr(t)}, 16, {vr(pr)}")
-            e.raw(f"v_and_b32 {vr(t + 1)}, 0xffff0000, {vr(pr)}")
-            e.raw(f"v_mul_f32 {vr(t)}, {vr(alpha[qb])}, {vr(t)}")
-            e.raw(f"v_mul_f32 {vr(t + 1)}, {vr(alpha[qb])}, {vr(t + 1)}")
-            e.raw(f"v_cvt_pk_bf16_f32 {vr(pr)}, {vr(t)}, {vr(t + 1)}")
+    for text, _, _ in valu_exp(1 - par, 1 - par):
+        e.raw(text)
     e.raw("s_nop 3")
     e.raw(f"s_setpc_b64 {sr(T_RET, 2)}")
 
@@ -508,7 +518,7 @@ def generate():
     e.raw(f"v_mul_f32 {vr(TMP)}, {sr(S_SCALE)}, {vr(TMP)}")
     e.raw("s_nop 0")
     e.raw(f"v_readfirstlane_b32 {sr(S_CEXP)}, {vr(TMP)}")
-    e.raw(f"v_mov_b32 {vr(GAPR)}, {sr(S_GAP)}")
+    e.raw(f"v_mov_b32 {vr(LIMR)}, {sr(S_LIMIT)}")
     e.raw(f"v_mov_b32 {vr(KOFF)}, {vr(I_KOFF0)}")
     e.raw(f"v_mov_b32 {vr(VOFF)}, {vr(I_VOFF0)}")
     e.raw(f"v_mov_b32 {vr(OOFF)}, {vr(I_OOFF)}")
@@ -540,9 +550,7 @@ def generate():
     for i in range(32 * DB):
         e.raw(f"v_accvgpr_write_b32 {ar(i)}, 0")
     for qb in range(QB):
-        for m in range(2):
-            for c in range(2):
-                e.raw(f"v_mov_b32 {vr(LSUM(qb, m, c))}, 0")
+        e.raw(f"v_mov_b32 {vr(LSUM(qb))}, 0")
     e.raw("s_waitcnt vmcnt(0)")
     e.comment("Q <- bf16(Q * scale * log2(e)): the MFMAs then deliver exponents in log2 units")
     for i in range(0, 8 * KS, 4):
@@ -595,6 +603,8 @@ def generate():
                 e.raw(f"v_sub_f32 {vr(SBUF(kb, qb) + v)}, {vr(SBUF(kb, qb) + v)}, {vr(MX(qb))}")
     for text, writes, _ in valu_exp(0, 0):
         e.valu(text, writes)
+    for ln in valu_take():
+        e.raw(ln)
     for db in range(2):
         read_vt(p, (0, 0), 0, db, 0)
 
@@ -680,10 +690,8 @@ def generate():
     e.raw("s_nop 7")
     for qb in range(QB):
         l, t = TMP, TMP + 1
-        e.raw(f"v_add_f32 {vr(l)}, {vr(LSUM(qb, 0))}, {vr(LSUM(qb, 1))}")
-        e.raw(f"v_add_f32 {vr(t)}, {vr(LSUM(qb, 0, 1))}, {vr(LSUM(qb, 1, 1))}")
-        e.raw(f"v_add_f32 {vr(l)}, {vr(l)}, {vr(t)}")
-        e.raw(f"v_mov_b32 {vr(t)}, {vr(l)}")
+        e.raw(f"v_mov_b32 {vr(l)}, {vr(LSUM(qb))}")
+        e.raw(f"v_mov_b32 {vr(t)}, {vr(LSUM(qb))}")
         e.raw("s_nop 1")
         e.raw(f"v_permlane32_swap_b32 {vr(t)}, {vr(l)}")
         e.raw("s_nop 1")

@@ -62,7 +62,7 @@ struct FwdArgs {
   // are combined afterwards.  0 or 1: one workgroup walks the whole table.
   int32_t n_split;
   int64_t split_o, split_l;
-  float gap;         // fast kernel: log2 units a block maximum may exceed the lazy exponent reference by (set by its launcher)
+  float sum_limit;   // fast kernel: sum over a block's probabilities beyond which the lazy exponent reference moves (set by its launcher)
 };
 
 struct BwdArgs {
@@ -134,7 +134,7 @@ struct Knobs {
   int dkv_queue = 1;   // 0: every dK/dV key tile is a workgroup of its own (no tile queue)
   int fwd_wq = 32;     // general forward without the fast path: queries per wavefront (32 or 64)
   int fwd_pipe = 1;    // general forward without the fast path, head size 128: the pipelined variant
-  float fwd_gap = 8.f; // fast forward: log2 units a block maximum may exceed the lazy exponent reference by (0 .. 64)
+  float fwd_gap = 8.f; // fast forward: log2 units every block maximum may exceed the lazy exponent reference by (0 .. 64)
 };
 Knobs& knobs();
 

@@ -197,6 +197,45 @@ def _tight_reference_case(D, gap):
         assert_close(host(lse), l_r, "bf16", f"lse, order {order}", lse=True)
 
 
+@pytest.mark.parametrize("causal", [False, True])
+@pytest.mark.parametrize("D", [128, 64])
+def test_forward_past_the_range_of_the_exponential(D, causal):
+    """Single keys in later blocks raise the exponent of every other row by 200 log2 units each, beyond what exp2 can
+    deliver against the old reference: the loop notices the infinity in the block's row sums and does that softmax again.
+    The spikes sit in both 32-key blocks of whole tiles, in the first tile of a chunk and in a masked tile; the rows
+    between see none of them.  A raised row is its last visible spike's V row (all others weigh 2^-200).  Its lse is a single
+    product of some hundreds whose factor Q' is rounded to bf16 once: relative 2^-8, and nothing averages it out."""
+    rng = np.random.default_rng(17 + D)
+    B, H, Sq, Sk, n = 1, 2, 320, 320, 3
+    q0 = 2 * Sk if causal else 0
+    bf = lambda x: torch.from_numpy(x.astype(np.float32)).to(torch.bfloat16)
+    q, k, v = (rng.standard_normal((B, s, H, D)) for s in (Sq, n * Sk, n * Sk))
+    scale = D ** -0.5
+    q[..., 0] = 0.0
+    q[:, ::2, :, 0] = 8.0
+    for i, key in enumerate((70, 130, 165, Sk + 1, Sk + 97, 2 * Sk + 5, 2 * Sk + 64 + 40, 3 * Sk - 1)):
+        k[:, key] *= 0.01
+        k[:, key, :, 0] = 200.0 * (i + 1) / (8.0 * scale * 1.4427)
+    qb, kb, vb = bf(q), bf(k), bf(v)
+    parts = lambda x: [x[:, j * Sk:(j + 1) * Sk].contiguous() for j in range(n)]
+    f64 = lambda x: x.float().numpy().astype(np.float64)
+    pos = np.arange(n * Sk, dtype=np.int64)
+    o_ref, lse_ref = oa.attention_forward(f64(qb), [f64(x) for x in parts(kb)], [f64(x) for x in parts(vb)], q0 + np.arange(Sq),
+                                          [pos[j * Sk:(j + 1) * Sk] for j in range(n)], causal, scale)
+    args = (qb.cuda(), [x.cuda() for x in parts(kb)], [x.cuda() for x in parts(vb)], q0, [j * Sk for j in range(n)], causal, scale)
+    def check(o, lse):
+        assert_close_wide(host(o), o_ref, "o")
+        err = np.abs(host(lse) - lse_ref)
+        assert (err <= 2e-2 + 2.0 ** -8 * np.abs(lse_ref)).all(), err.max()
+    for order in ([0, 1, 2], [2, 1, 0]):
+        print(f"[past the exponential D={D}] causal {causal} order {order}", flush=True)
+        check(*st.st_ring_fwd(*args, order, None, st.ST_RING_FUSED)[:2])
+    print(f"[past the exponential D={D}] causal {causal} one walk", flush=True)
+    o, lse = torch.empty((B, Sq, H, D), device="cuda"), torch.empty((B, H, Sq), device="cuda")
+    st.st_attn_block_fwd(qb.cuda(), kb.cuda(), vb.cuda(), q0, 0, causal, scale, o, lse)
+    check(o, lse)
+
+
 @pytest.mark.parametrize("D", [128, 64])
 @pytest.mark.parametrize("Sq,causal", [(512, True), (300, True), (600, False), (256, True)])
 def test_split_forward_on_a_poisoned_workspace(D, Sq, causal):
