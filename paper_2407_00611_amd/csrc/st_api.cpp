@@ -170,6 +170,7 @@ st_status check_ring(const st_ring_desc* d, const st_tensor* q, const int32_t* o
 }
 
 constexpr int kMaxSplits = 16;
+constexpr int kPlanCus = 256;
 
 // fp32: the turns a query tile's workgroup takes over n chunks; in one its wavefronts (eight, four beyond head size 128) take
 // a 32-key tile each
@@ -178,19 +179,147 @@ int64_t f32_turns(int D, int Sk, int64_t n) {
   return (n * ((Sk + 31) / 32) + waves - 1) / waves;
 }
 
+// What the query tiles of a launch have to walk, in the units their kernels deal out: 64-key tiles in bf16, a masked one
+// counted twice (see build_walk), and turns in fp32.
+struct QueryWalk {
+  int64_t heads = 0;     // B Hq
+  st::QueryTiles q = {};
+  int tiles = 0;         // per head
+  int n = 0;             // entries of units: one per tile, or a single one where all tiles have the same
+  int units[st::kShareTiles];
+  int64_t wgs() const { return heads * tiles; }
+  int most() const { return *std::max_element(units, units + n); }
+};
+QueryWalk query_walk(const st::Shape& s, int dtype, const int64_t* k_offset, int n) {
+  const bool bf16 = dtype == ST_BF16;
+  QueryWalk w;
+  w.q = st::query_tiles(s, bf16 ? st::kQTileFastRows : 32);
+  w.tiles = w.q.count();
+  w.heads = (int64_t)s.B * s.Hq;
+  w.n = s.causal && k_offset && w.tiles > 1 && w.tiles <= st::kShareTiles ? w.tiles : 1;
+  if (w.n == 1) {
+    w.units[0] = (int)std::min<int64_t>(bf16 ? (int64_t)n * ((s.Sk + st::kQTileFastKeys - 1) / st::kQTileFastKeys) : f32_turns(s.D, s.Sk, n), 1 << 28);
+    return w;
+  }
+  const int n64 = s.Sk / st::kQTileFastKeys, waves = s.D <= 128 ? 8 : 4;
+  for (int qt = 0; qt < w.tiles; ++qt) {
+    const int64_t first = st::q_pos(s, w.q.row0(qt)), last = st::q_pos(s, w.q.row0(qt) + w.q.rows_of(qt) - 1);
+    int64_t units = 0;
+    for (int c = 0; c < n; ++c) {
+      const int64_t nv_last = std::min<int64_t>(std::max<int64_t>(last - k_offset[c] + 1, 0), s.Sk);
+      if (!bf16) {
+        units += (nv_last + 31) / 32;
+        continue;
+      }
+      const int64_t nf = std::min<int64_t>(std::max<int64_t>(first - k_offset[c] + 1, 0), s.Sk) / st::kQTileFastKeys;
+      const int64_t seen = std::min<int64_t>((nv_last + st::kQTileFastKeys - 1) / st::kQTileFastKeys, n64);
+      units += nf + 2 * (std::max<int64_t>(seen - nf, 0) + (nv_last > (int64_t)n64 * st::kQTileFastKeys));
+    }
+    w.units[qt] = (int)std::min<int64_t>(bf16 ? units : (units + waves - 1) / waves, 1 << 28);
+  }
+  return w;
+}
+
+// A way to split the tiles of a walk into shares of at most `each` units.
+struct Split {
+  const QueryWalk* w;
+  int each;
+  int n = 1;                    // most shares of a tile
+  int total = 0;                // shares of a head
+  int64_t rows = 0, rows_own0 = 0;   // rows of partial results per batch entry and head: all shares of split tiles, all but the first ones
+  int shares(int i) const { return std::min(std::max((w->units[i] + each - 1) / each, 1), kMaxSplits); }
+  Split(const QueryWalk& walk, int units) : w(&walk), each(std::max(units, 1)) {
+    for (int i = 0; i < w->n; ++i) {
+      const int x = shares(i), tiles = w->n == 1 ? w->tiles : 1;
+      n = std::max(n, x);
+      total += x * tiles;
+      if (x == 1) continue;
+      const int64_t rows_i = w->n == 1 ? w->q.Sq : w->q.rows_of(i);
+      rows += x * rows_i;
+      rows_own0 += (x - 1) * rows_i;
+    }
+  }
+  int64_t workgroups() const { return w->heads * total; }
+  int longest() const {         // units of the longest share
+    int most = 0;
+    for (int i = 0; i < w->n; ++i) most = std::max(most, (w->units[i] + shares(i) - 1) / shares(i));
+    return most;
+  }
+  // Time of the launch: workgroups handed out longest first, each to the compute unit that is free first (one holds one).
+  double launch_us(double fixed_us, double unit_us) const {
+    if (workgroups() <= kPlanCus) return fixed_us + longest() * unit_us;
+    if (w->n == 1) return (double)((workgroups() + kPlanCus - 1) / kPlanCus) * (fixed_us + longest() * unit_us);
+    struct Group { double us; int64_t n; };
+    Group job[st::kShareTiles], cu[2 * st::kShareTiles + 8];
+    for (int i = 0; i < w->n; ++i) job[i] = Group{fixed_us + (double)((w->units[i] + shares(i) - 1) / shares(i)) * unit_us, w->heads * shares(i)};
+    std::sort(job, job + w->n, [](const Group& x, const Group& y) { return x.us > y.us; });
+    int groups = 1;
+    cu[0] = Group{0, kPlanCus};
+    double end = 0;
+    for (int i = 0; i < w->n; ++i) {
+      for (int64_t left = job[i].n; left > 0;) {
+        const int64_t take = std::min(left, cu[0].n);
+        const double us = cu[0].us + job[i].us;
+        end = std::max(end, us);
+        left -= take;
+        if (take == cu[0].n) std::copy(cu + 1, cu + groups--, cu);
+        else cu[0].n -= take;
+        int at = groups;
+        while (at > 0 && cu[at - 1].us >= us) --at;
+        if (at < groups && cu[at].us == us) {
+          cu[at].n += take;
+          continue;
+        }
+        if (groups == (int)(sizeof(cu) / sizeof(cu[0]))) return end + job[i].us;      // (not reached: a job splits one group)
+        std::copy_backward(cu + at, cu + groups, cu + groups + 1);
+        cu[at] = Group{us, take};
+        ++groups;
+      }
+    }
+    return end;
+  }
+  st::TileShares table(bool own0) const {
+    st::TileShares t;
+    memset(&t, 0, sizeof(t));
+    t.n = (int16_t)n;
+    t.own0 = n > 1 && own0;
+    bool same = true;
+    for (int i = 1; i < w->n; ++i) same = same && shares(i) == shares(0);
+    if (w->n == 1 || same) return t;
+    t.total = (int16_t)total;
+    for (int i = 0; i < w->n; ++i) t.less1[i >> 4] |= (uint64_t)(shares(i) - 1) << (4 * (i & 15));
+    return t;
+  }
+};
+// the passes that fold the shares have eight loads in flight; more are a second wait
+double more_than_8_us(const Split& s) { return s.n > 8 ? 1.5 : 0; }
+// f(split) for the splits that give the longest walk 2, 3, ... shares
+template <typename F>
+void each_split(const QueryWalk& w, int most, F f) {
+  const int top = w.most();
+  for (int k = 2, before = top; k <= most && k <= top; ++k) {
+    const int each = (top + k - 1) / k;
+    if (each == before) continue;
+    before = each;
+    const Split s(w, each);
+    if (s.workgroups() > 8 * kPlanCus) return;
+    f(s);
+  }
+}
+
 // Workgroups per tile of a backward launch over n chunks, and the bytes of partial sums that
 // takes (the two passes run one after the other and share them).
 struct BwdSplit {
-  int dq = 1, kv = 1;
-  int parts = 0;         // dQ shares whose sums are stored, see BwdArgs
+  st::TileShares dq = {};
+  int kv = 1;
   bool pair = false;
   size_t bytes = 0;
 };
-// dQ: the forward's model (rounds of workgroups x time of one + the pass that adds up); a 256 x 64 tile is three
-// contractions instead of two: 2.4 us at head size 128, 1.4 at 64.  fp32: the eight (four beyond head size 128) wavefronts
-// of a workgroup take a 32-key tile each in 16 us at head size 128, 9 at 64, 5.5 at 32, and 16 at 256 (8 heads x 512 rows x
-// 8 chunks of 512 keys at head size 128: 128 workgroups, 270 us; 157 us as two shares each and the adding pass); 10 us for
-// the adding pass, as walks of two turns gain less than its launch takes.
+// dQ: the forward's model (the launch + the pass that adds up); a 256 x 64 tile is three contractions instead of two: 1.7 us at
+// head size 128, 1.05 at 64, behind 14 and 11 us.  fp32: the eight (four beyond head size 128) wavefronts of a workgroup take a
+// 32-key tile each in 16 us at head size 128, 9 at 64, 5.5 at 32, and 16 at 256 (8 heads x 512 rows x 8 chunks of 512 keys at
+// head size 128: 128 workgroups, 270 us; 157 us as two shares each and the adding pass); 10 us for the adding pass, as walks
+// of two turns gain less than its launch takes.
 // dK/dV: a step (256 keys x 32 rows of one head) is 1.2 us at head size 128 and 0.75 at 64, prologue and epilogue 20 and 14;
 // grouped heads make the walk long and the key tiles few (4096 x 4096, 32/8 heads: 128 workgroups of 512 steps on 256
 // compute units, 570 us; 310 us as two shares of 256 steps and a 25 us pass).  512 tiles and more go through the queue.
@@ -206,33 +335,39 @@ bool bwd_half(const st::Shape& s, const int64_t* k_offset, int n) {
     for (int64_t t = 0; t < tiles; ++t) sum += blocks - st::q_row_of(s, k_offset[c] + t * st::kDkvFastKeys) / st::kDkvFastRows;
   return 4 * sum < 3 * (int64_t)n * tiles * blocks;
 }
-BwdSplit bwd_splits(const st::Shape& s, int dtype, int n, bool half, size_t room, bool split_dq = true) {
+BwdSplit bwd_splits(const st::Shape& s, int dtype, const int64_t* k_offset, int n, bool half, size_t room, bool split_dq = true) {
   BwdSplit r;
   const bool bf16 = dtype == ST_BF16;
-  int64_t dq_tiles = 0;
-  double dq_us = 0, dq_tile_us = 0, part_us = 0;
   if ((bf16 && s.D != 128 && s.D != 64) || n < 1 || n > st::kMaxTable || s.B < 1 || s.Sq < 1 || s.Sk < 1 || s.Hq < 1 || s.Hkv < 1) return r;
   const bool d128 = s.D == 128;
-  const int rows = bf16 ? st::kQTileFastRows : 32, keys = st::kQTileFastKeys;
-  const int64_t wgs = (int64_t)s.B * s.Hq * ((s.Sq + rows - 1) / rows);
-  const size_t n_o = (size_t)st::dq_part_floats(s) * sizeof(float);
-  auto set_dq = [&](int x) {
-    r.dq = x;
-    r.parts = x == 1 ? 0 : (size_t)x * n_o > room ? x - 1 : x;
-    r.bytes = (size_t)r.parts * n_o;
+  QueryWalk walk;
+  const int64_t wgs = (int64_t)s.B * s.Hq * st::query_tiles(s, bf16 ? st::kQTileFastRows : 32).count();
+  const bool plan_dq = split_dq && wgs < 512 && (!bf16 || s.Sk >= st::kQTileFastKeys);
+  const double unit_us = bf16 ? (d128 ? 1.7 : 1.05) : 2 + (s.D <= 128 ? 0.11 : 0.055) * s.D, dq_fixed_us = bf16 ? (d128 ? 14 : 11) : 10, add_us = bf16 ? 6 : 10;
+  const size_t row_bytes = (size_t)s.B * s.Hq * s.D * sizeof(float);
+  auto part_us = [&](int64_t rows) { return (double)(row_bytes * rows) / 4e6; };
+  auto fits = [&](const Split& x) { return (size_t)x.rows_own0 * row_bytes <= room; };
+  auto set_dq = [&](const Split& x) {
+    const bool own0 = (size_t)x.rows * row_bytes > room;
+    r.dq = x.table(own0);
+    r.bytes = (size_t)(own0 ? x.rows_own0 : x.rows) * row_bytes;
   };
-  if (split_dq && wgs < 512 && (!bf16 || s.Sk >= keys)) {
-    const int64_t tiles = bf16 ? (int64_t)n * ((s.Sk + keys - 1) / keys) : f32_turns(s.D, s.Sk, n);
-    const double tile_us = bf16 ? (d128 ? 2.4 : 1.4) : 2 + (s.D <= 128 ? 0.11 : 0.055) * s.D, fixed_us = 10, state_us = (double)n_o / 4e6, add_us = bf16 ? 6 : 10;
-    dq_tiles = tiles, dq_tile_us = tile_us, part_us = state_us;
-    double best = (double)((wgs + 255) / 256) * (fixed_us + tiles * tile_us);
-    for (int x = 2; x <= kMaxSplits && x <= tiles && (size_t)(x - 1) * n_o <= room; ++x) {
-      const double t = (double)((wgs * x + 255) / 256) * (fixed_us + (double)((tiles + x - 1) / x) * tile_us) + add_us + (x + 2) * state_us;
+  double dq_us = 0;
+  int dq_units = 0;
+  if (plan_dq) {
+    walk = query_walk(s, dtype, k_offset, n);
+    dq_units = walk.most();
+    double best = Split(walk, dq_units).launch_us(dq_fixed_us, unit_us);
+    each_split(walk, kMaxSplits, [&](const Split& x) {
+      if (!fits(x)) return;
+      const double add = add_us + more_than_8_us(x) + part_us(x.rows + 2 * s.Sq);
+      if (dq_fixed_us + x.longest() * unit_us + add >= 0.95 * best) return;
+      const double t = x.launch_us(dq_fixed_us, unit_us) + add;
       if (t < 0.95 * best) {
         best = t;
         set_dq(x);
       }
-    }
+    });
     dq_us = best;
   }
   const int64_t key_tiles = (int64_t)s.B * s.Hkv * n * ((s.Sk + st::kDkvFastKeys - 1) / st::kDkvFastKeys);
@@ -260,32 +395,34 @@ BwdSplit bwd_splits(const st::Shape& s, int dtype, int n, bool half, size_t room
     // where a compute unit is done with its key tiles come into question.  Forward and backward, apart and together: 4 heads x
     // 700 rows x 4 chunks 99 and 77 us, 12 heads of 64 x 800 rows x 4 chunks 96 and 88 us, 6 heads x 1500 rows x 4 chunks 146
     // and 116 us.  Launches of 512 key tiles and more (the queue) and split key tiles fill the chip by themselves.
-    if (r.kv == 1 && dq_tiles > 6) {
+    if (r.kv == 1 && dq_units > 6) {
       const double one = fixed_us + (double)(blocks * G) * step_us;
       const int64_t late_cus = key_tiles % 256;            // have a key tile more than the others
       const double early = (double)(key_tiles / 256) * one, late = early + one, end = late_cus ? late : early;
       double least = 0.95 * (best + 4 + dq_us);
-      for (int x = 1; x <= kMaxSplits && x <= dq_tiles && (size_t)(x - 1) * n_o <= room; ++x) {
-        const double share = 10 + (double)((dq_tiles + x - 1) / x) * dq_tile_us, add = x > 1 ? 6 + (x + 2) * part_us : 0;
+      auto together = [&](const Split& x) {
+        if (!fits(x)) return;
+        const double share = dq_fixed_us + (double)x.longest() * unit_us, add = x.n > 1 ? add_us + more_than_8_us(x) + part_us(x.rows + 2 * s.Sq) : 0;
         for (int j = 1; early + j * share + add < least; ++j)
           for (const double from : {early, late}) {
             const double t = std::max(end, from + j * share);
             const int64_t fit = (256 - late_cus) * (int64_t)((t - early) / share + 1e-6) + late_cus * (int64_t)(std::max(t - late, 0.0) / share + 1e-6);
-            if (t + add >= least || fit < wgs * x) continue;
+            if (t + add >= least || fit < x.workgroups()) continue;
             least = t + add;
             r.pair = true;
             set_dq(x);
           }
-      }
+      };
+      together(Split(walk, dq_units));
+      each_split(walk, kMaxSplits, together);
     }
   }
   return r;
 }
 size_t most_bytes(const BwdSplit& x, const BwdSplit& y) { return x.bytes > y.bytes ? x.bytes : y.bytes; }
 void set_splits(st::BwdArgs& a, const BwdSplit& x, void* parts) {
-  a.n_split = x.dq;
-  a.n_parts = x.parts;
-  a.kv_split = x.kv;
+  a.shares = x.dq;
+  a.kv_split = (int16_t)x.kv;
   a.pair = x.pair;
   a.parts = (float*)parts;
 }
@@ -508,7 +645,8 @@ constexpr size_t kBlockPartsMost = (size_t)64 << 20;
 
 size_t st_attn_block_bwd_workspace_bytes(const st_block_desc* d) {
   if (d == nullptr || d->dtype != ST_BF16 || d->B <= 0 || d->Sq <= 0 || d->Hq <= 0 || d->D <= 0) return 0;
-  return block_base_bytes(d) + most_bytes(bwd_splits(shape_of(d), d->dtype, 1, false, kBlockPartsMost, false), bwd_splits(shape_of(d), d->dtype, 1, true, kBlockPartsMost, false));
+  const st::Shape s = shape_of(d);
+  return block_base_bytes(d) + most_bytes(bwd_splits(s, d->dtype, nullptr, 1, false, kBlockPartsMost, false), bwd_splits(s, d->dtype, nullptr, 1, true, kBlockPartsMost, false));
 }
 
 st_status st_attn_block_bwd(const st_block_desc* d, const st_tensor* q, const st_tensor* k, const st_tensor* v,
@@ -546,7 +684,7 @@ st_status st_attn_block_bwd(const st_block_desc* d, const st_tensor* q, const st
     ST_HIP(st::launch_scale_q(a.q, workspace, d->B, d->Sq, d->Hq, d->D, d->scale, (hipStream_t)hip_stream), "scaled-Q launch");
     a.qs = workspace;
     const size_t left = workspace_bytes - block_base_bytes(d);
-    set_splits(a, bwd_splits(a.s, d->dtype, 1, bwd_half(a.s, a.t.k_offset, 1), left < kBlockPartsMost ? left : kBlockPartsMost, false), (char*)workspace + block_base_bytes(d));
+    set_splits(a, bwd_splits(a.s, d->dtype, a.t.k_offset, 1, bwd_half(a.s, a.t.k_offset, 1), left < kBlockPartsMost ? left : kBlockPartsMost, false), (char*)workspace + block_base_bytes(d));
   }
   ST_HIP(launch_bwd(d->dtype, a, (hipStream_t)hip_stream), "st_attn_block_bwd launch");
   return ST_OK;
@@ -626,37 +764,43 @@ st_status st_schedule_report(int32_t P, int32_t C, int64_t B, int64_t N, int64_t
 }
 
 // A fused forward whose query tiles alone would leave part of the chip idle (a workgroup per 256 rows and head in bf16, per
-// 32 rows in fp32, on 256 compute units) is split over the keys: every query tile gets several workgroups, each with a share
-// of the walk and a partial state of its own, and one combine pass folds the states (the tiles of a ring are independent
-// until the fold, Algorithm 1).  The split is the one for which rounds of workgroups x time of one + combine is least; the
-// constants are measured: a 256 x 64 bf16 tile 1.6 us at head size 128 and 0.95 us at 64, 8 us of prologue and epilogue,
-// 6 us for the launch of the combine pass, which moves 4 TB/s on states this small.  fp32: a turn (see f32_turns) takes 4.1,
-// 6.1 and 10.4 us at head sizes 32, 64 and 128 and 10.7 at 256 (with half the wavefronts), what stands around the turns 5, 7,
-// 10 and 13 us; 8 us for the combine pass, as a caller that waits for launches (small fp32 shares are such calls: 67 us for
-// 45 us of kernels) loses 5 us by one more.  At head size 128, unsplit and as planned: 4 heads x 128 rows x 2048 keys 92.6 and
-// 24.9 us (eight shares of a turn), 8 heads x 512 rows x 8 chunks of 512 keys 181 and 105 (two shares on 128 query tiles; four,
-// which are two rounds of workgroups, 113).
-static int fwd_splits(const st_ring_desc* d, int n_visible, int most = kMaxSplits) {
+// 32 rows in fp32, on 256 compute units) is split over the keys: a query tile gets several workgroups, each with a share of
+// the walk and a partial state of its own, and one combine pass folds the states (the tiles of a ring are independent
+// until the fold, Algorithm 1).  The split is the one for which launch + combine is least (Split::launch_us), with measured
+// constants: a 256 x 64 bf16 tile 1.25 us at head size 128 and 0.8 us at 64 behind 12 and 9 us of walk, prologue and epilogue
+// (short launches: below some 100 us the chip does not reach its power limit), 6 us for the launch of the combine pass, which
+// moves 4 TB/s on states this small.  fp32: a turn (see f32_turns) takes 4.1, 6.1 and 10.4 us at head sizes 32, 64 and 128 and
+// 10.7 at 256 (with half the wavefronts), what stands around the turns 5, 7, 10 and 13 us; 8 us for the combine pass, as a
+// caller that waits for launches loses 5 us by one more.
+// Under a causal mask the tiles differ, and shares of one size are what fills the chip: 48 heads x two runs of 736 rows,
+// walks of 230 and 610 tiles, 885 us with one number of shares for all tiles and 674 so (dQ 1254 and 1024); 3 heads x two
+// runs of 2112 rows 254 and 185 (342 and 253).
+static bool fwd_splittable(const st_ring_desc* d, int n_visible) {
   const bool bf16 = d->dtype == ST_BF16;
-  if (n_visible < 1 || n_visible > st::kMaxTable || d->B < 1 || d->Sq < 1 || d->Hq < 1) return 1;
-  if (bf16 && ((d->D != 128 && d->D != 64) || d->Sk < st::kQTileFastKeys)) return 1;
-  const int rows = bf16 ? st::kQTileFastRows : 32, keys = st::kQTileFastKeys;
-  const int64_t wgs = (int64_t)d->B * d->Hq * ((d->Sq + rows - 1) / rows);
-  if (wgs >= 512) return 1;
-  const int64_t tiles = bf16 ? (int64_t)n_visible * ((d->Sk + keys - 1) / keys) : f32_turns(d->D, d->Sk, n_visible);
-  const double tile_us = bf16 ? (d->D == 128 ? 1.6 : 0.95) : 2 + (d->D <= 128 ? 0.065 : 0.034) * d->D;
-  const double fixed_us = bf16 ? 8 : 5 + 0.035 * d->D, combine_us = bf16 ? 6 : 8;
-  const double state_us = (double)d->B * d->Sq * d->Hq * d->D * sizeof(float) / 4e6;
-  double best = (double)((wgs + 255) / 256) * (fixed_us + tiles * tile_us);
-  int n_best = 1;
-  for (int n = 2; n <= most && n <= tiles; ++n) {
-    const double t = (double)((wgs * n + 255) / 256) * (fixed_us + (double)((tiles + n - 1) / n) * tile_us) + combine_us + (n + 1.5) * state_us;
+  if (n_visible < 1 || n_visible > st::kMaxTable || d->B < 1 || d->Sq < 1 || d->Hq < 1) return false;
+  if (bf16 && ((d->D != 128 && d->D != 64) || d->Sk < st::kQTileFastKeys)) return false;
+  return (int64_t)d->B * d->Hq * st::query_tiles(shape_of(d), bf16 ? st::kQTileFastRows : 32).count() < 512;
+}
+// k_offset of the visible chunks; nullptr: of chunks that every row sees
+static st::TileShares fwd_shares(const st_ring_desc* d, const int64_t* k_offset, int n_visible, int most = kMaxSplits) {
+  st::TileShares r = {};
+  if (!fwd_splittable(d, n_visible)) return r;
+  const bool bf16 = d->dtype == ST_BF16;
+  const QueryWalk walk = query_walk(shape_of(d), d->dtype, k_offset, n_visible);
+  const double unit_us = bf16 ? (d->D == 128 ? 1.25 : 0.8) : 2 + (d->D <= 128 ? 0.065 : 0.034) * d->D;
+  const double fixed_us = bf16 ? (d->D == 128 ? 12 : 9) : 5 + 0.035 * d->D, combine_us = bf16 ? 6 : 8;
+  const double row_us = (double)d->B * d->Hq * d->D * sizeof(float) / 4e6;
+  double best = Split(walk, walk.most()).launch_us(fixed_us, unit_us);
+  each_split(walk, most, [&](const Split& x) {
+    const double add = combine_us + more_than_8_us(x) + (x.rows + 1.5 * d->Sq) * row_us;
+    if (fixed_us + x.longest() * unit_us + add >= 0.95 * best) return;
+    const double t = x.launch_us(fixed_us, unit_us) + add;
     if (t < 0.95 * best) {
       best = t;
-      n_best = n;
+      r = x.table(false);
     }
-  }
-  return n_best;
+  });
+  return r;
 }
 // A share whose full 256-row tiles fill less than half of the chip: its workspace has always held a state per chunk (up to
 // 256 workgroups) and one more, and its forward has always been refused without one.  Both are part of the interface.
@@ -670,12 +814,15 @@ static int fwd_states_small(const st_ring_desc* d, int n_visible) {
   if (n > kMaxSplits) n = kMaxSplits;
   return (int)n + 1;
 }
-// states to provide for: any subset of the chunks may be visited
+// States to provide for: any subset of the chunks may be visited.  Under a causal mask the tiles with the longest walks may
+// be split where one number for all of them would not be: they have about twice the average.
 static int fwd_states_most(const st_ring_desc* d) {
-  int most = fwd_states_small(d, d->n_chunks < st::kMaxTable ? d->n_chunks : st::kMaxTable);
-  for (int n = 1; n <= d->n_chunks && n <= st::kMaxTable; ++n) {
-    const int x = fwd_splits(d, n);
-    if (x > most) most = x;
+  const int n_most = d->n_chunks < st::kMaxTable ? d->n_chunks : st::kMaxTable;
+  int most = fwd_states_small(d, n_most);
+  for (int n = 1; n <= n_most; ++n) most = std::max(most, (int)fwd_shares(d, nullptr, n).n);
+  if (d->causal && fwd_splittable(d, n_most)) {
+    const QueryWalk w = query_walk(shape_of(d), d->dtype, nullptr, n_most);
+    most = std::max(most, (int)std::min<int64_t>({(int64_t)kMaxSplits, (int64_t)w.units[0], (2 * kPlanCus + w.wgs() - 1) / w.wgs()}));
   }
   return most;
 }
@@ -705,12 +852,11 @@ size_t st_ring_workspace_bytes(const st_ring_desc* d, int32_t mode, int32_t back
   const size_t n_l = align_up((size_t)d->B * d->Sq * d->Hq * sizeof(float), 256);
   if (backward) {
     // any subset of the chunks may be visited, in one launch or in several
+    const size_t room = ring_room(d, kScratchBytes);
+    if (d->causal) return bwd_base_bytes(d) + room;    // the plan depends on where the chunks lie
     size_t most = 0;
-    for (int n = 1; n <= (mode == ST_RING_FUSED ? d->n_chunks : 1) && n <= st::kMaxTable; ++n) {
-      const size_t room = ring_room(d, kScratchBytes);
-      const size_t x = most_bytes(bwd_splits(shape_of(d), d->dtype, n, false, room), bwd_splits(shape_of(d), d->dtype, n, true, room));
-      if (x > most) most = x;
-    }
+    for (int n = 1; n <= (mode == ST_RING_FUSED ? d->n_chunks : 1) && n <= st::kMaxTable; ++n)
+      most = std::max(most, bwd_splits(shape_of(d), d->dtype, nullptr, n, false, room).bytes);
     return bwd_base_bytes(d) + most;
   }
   if (mode == ST_RING_STEPWISE) return 2 * (n_o + n_l);
@@ -758,31 +904,39 @@ st_status st_ring_fwd(const st_ring_desc* d, const st_tensor* q, const int32_t* 
     if (!on_boundary) return fail(ST_ERR_ALIGNMENT, "workspace: not 256-byte aligned");
   }
   const size_t room = fused && workspace != nullptr && on_boundary ? workspace_bytes / state : 0;
-  int splits = room > 1 ? fwd_splits(d, n, room < (size_t)kMaxSplits ? (int)room : kMaxSplits) : 1;
-  if (d->dtype == ST_BF16 && !fast) splits = 1;        // only the hand-scheduled kernel walks a split table
+  st::TileShares shares = {};
+  if (room > 1 && n > 0 && n <= st::kMaxTable && (fast || d->dtype != ST_BF16)) {        // only the hand-scheduled kernel walks a split table
+    int64_t k_offset[st::kMaxTable];
+    for (int x = 0; x < n; ++x) k_offset[x] = d->k_offset[vis[x]];
+    shares = fwd_shares(d, k_offset, n, room < (size_t)kMaxSplits ? (int)room : kMaxSplits);
+  }
   char* ws = (char*)workspace;
   float* part_o = (float*)ws;
   float* part_l = (float*)(ws + b_o);
 
-  if (mode == ST_RING_FUSED && splits > 1) {
+  if (shares.n > 1) {
     a.t.n = n;
     for (int x = 0; x < n; ++x) {
       a.t.k[x] = d->k_ptr[vis[x]];
       a.t.v[x] = d->v_ptr[vis[x]];
       a.t.k_offset[x] = d->k_offset[vis[x]];
     }
-    a.o = part_o;
-    a.lse = part_l;
-    a.o_lowp = nullptr;
-    a.n_split = splits;
-    a.split_o = a.split_l = (int64_t)((b_o + b_l) / sizeof(float));
+    a.o = o_acc;
+    a.lse = lse;
+    a.o_lowp = o_lowp;
+    a.shares = shares;
+    a.part_o = part_o;
+    a.part_lse = part_l;
+    a.part_stride = (int64_t)(state / sizeof(float));
     ST_HIP(launch_fwd(d->dtype, a, stream), "split forward launch");
     st::CombineArgs c;
     memset(&c, 0, sizeof(c));
-    c.n = splits;
-    for (int y = 0; y < splits; ++y) {
-      c.o[y] = part_o + (int64_t)y * a.split_o;
-      c.lse[y] = part_l + (int64_t)y * a.split_l;
+    c.n = shares.n;
+    c.shares = shares;
+    c.tiles = st::query_tiles(a.s, d->dtype == ST_BF16 ? st::kQTileFastRows : 32);
+    for (int y = 0; y < c.n; ++y) {
+      c.o[y] = part_o + y * a.part_stride;
+      c.lse[y] = part_l + y * a.part_stride;
     }
     c.B = d->B; c.Sq_in = d->Sq; c.Hq = d->Hq; c.D = d->D; c.row0 = 0; c.Sq_out = d->Sq;
     c.o_out = o_acc; c.lse_out = lse; c.o_lowp = o_lowp;
@@ -955,7 +1109,7 @@ st_status st_ring_bwd_last(const st_ring_desc* d, const st_tensor* q, const st_t
       a.dk_lowp[x] = dk_lowp ? dk_lowp[j] : nullptr;
       a.dv_lowp[x] = dk_lowp ? dv_lowp[j] : nullptr;
     }
-    set_splits(a, bwd_splits(a.s, d->dtype, cnt, bwd_half(a.s, a.t.k_offset, cnt), ring_room(d, workspace_bytes)), (char*)workspace + bwd_base_bytes(d));
+    set_splits(a, bwd_splits(a.s, d->dtype, a.t.k_offset, cnt, bwd_half(a.s, a.t.k_offset, cnt), ring_room(d, workspace_bytes)), (char*)workspace + bwd_base_bytes(d));
     a.kv_assign = assign ? ~0ull : 0ull;
     if (d->dtype != ST_BF16 && assign)              // the fp32 kernels only add
       for (int x = 0; x < cnt; ++x) {

@@ -473,7 +473,7 @@ hipError_t launch_bwd_bf16(const BwdArgs& a_in, hipStream_t stream) {
   // 14.1 against 10.5 us on the general kernel, five 26.9 against 20.9, eight 23.2 against 23.7, 64 tiles 106 against 137;
   // head size 64: 11.2 against 8.7, 17.7 against 15.3, 15.6 against 17.7, 61 against 94).  The dK/dV loop is the faster one
   // from the first block on.
-  const bool few = a.n_split <= 1 && (int64_t)a.t.n * ((a.s.Sk + kDqFastKeys - 1) / kDqFastKeys) <= 6;
+  const bool few = a.shares.n <= 1 && (int64_t)a.t.n * ((a.s.Sk + kDqFastKeys - 1) / kDqFastKeys) <= 6;
   const bool dq_fast = knobs().dq_fast && !few && dq_fast_usable(a), pair = a.pair && dkv_fast && dq_fast && a.kv_split <= 1;
   hipError_t e = hipSuccess;
   if (pair) {
@@ -506,8 +506,7 @@ hipError_t launch_bwd_bf16(const BwdArgs& a_in, hipStream_t stream) {
   }
   if (dq_fast) {
     if (!pair) e = launch_bwd_dq_fast(a, stream);
-    if (e == hipSuccess && a.n_parts > 0)
-      e = launch_add_parts(a.dq, a.parts, a.n_parts, dq_part_floats(a.s), (int64_t)a.s.B * a.s.Sq * a.s.Hq * a.s.D, stream);
+    if (e == hipSuccess && a.shares.n > 1) e = launch_add_parts(a, kDqFastRows, stream);
     return e;
   }
   ProfScope prof("bwd_dq_bf16", stream);

@@ -18,9 +18,9 @@ constexpr float kLog2e = 1.4426950408889634f;
 template <int D>
 constexpr int dq_lds_bytes() { return D == 128 ? ST_DQ_FAST_LDS_BYTES : ST_DQ_FAST64_LDS_BYTES; }
 
-// One workgroup: query tile block_x of grid_x (XCD-aware mapping), share `split` of its walk.
+// One workgroup: a share of a query tile's walk (share_block).
 template <int D>
-__device__ __forceinline__ void dq_fast_body(const BwdArgs& a, int block_x, int grid_x, int split, char* smem_raw) {
+__device__ __forceinline__ void dq_fast_body(const BwdArgs& a, int block_x, int grid_x, int block_y, char* smem_raw) {
   constexpr int BM = kDqFastRows, BN = kDqFastKeys;
   constexpr int kLdsBytes = dq_lds_bytes<D>();
   constexpr int kQrel = kLdsBytes - 256 * 8;         // behind the tile ring: table, parameter block, row positions
@@ -35,37 +35,38 @@ __device__ __forceinline__ void dq_fast_body(const BwdArgs& a, int block_x, int 
   const Shape& s = a.s;
   const int tid = threadIdx.x, lane = tid & 63, wave = (int)sgpr(tid >> 6);
   const int g = lane >> 5, r = lane & 31;
-  const int n_qt = (s.Sq + BM - 1) / BM;
-  int qt, hb;
-  qtile_block(block_x, grid_x, n_qt, s.causal, qt, hb);
+  const QueryTiles tiles = query_tiles(s, BM);
+  int qt, hb, split;
+  share_block(a.shares, block_x, grid_x, block_y, tiles.count(), s.causal, qt, hb, split);
+  const int n_split = max(shares_of(a.shares, qt), 1);
   // divisions run on the vector unit; their results are uniform, and so are the addresses made of them
   const int h = (int)sgpr(hb % s.Hq), b = (int)sgpr(hb / s.Hq), hk = (int)sgpr(h / (s.Hq / s.Hkv));
-  const int row0 = (int)sgpr(qt * BM), rows = min(BM, s.Sq - row0);
+  const int row0 = (int)sgpr(tiles.row0(qt)), rows = (int)sgpr(tiles.rows_of(qt)), row_end = row0 + rows;
 
   const int q_row = row0 + 64 * wave + r;            // this lane's row of query block 0; block 1: + 32
-  const int i0 = min(q_row, s.Sq - 1), i1 = min(q_row + 32, s.Sq - 1);
+  const int i0 = min(q_row, row_end - 1), i1 = min(q_row + 32, row_end - 1);
   ST_LDS uint32_t* params = (ST_LDS uint32_t*)(smem + kParams);
   {  // for the mask
     ST_LDS int32_t* qrel = (ST_LDS int32_t*)(smem + kQrel) + 2 * tid;
     qrel[0] = walk_row_pos(s, i0, row0) - 4 * g;
     qrel[1] = walk_row_pos(s, i1, row0) - 4 * g;
   }
-  const int first_part = max(a.n_split, 1) - a.n_parts;
+  const bool part = n_split > 1 && split >= a.shares.own0;      // a sum of its own, not dq itself
   if (wave == 0) {
     int n_masked, first_masked;
-    const int n = build_walk(s, a.t, a.n_split, row0, b, hk, split, (ST_LDS uint32_t*)(smem + kTblOffset), lane, n_masked, first_masked);
+    const int n = build_walk(s, a.t, n_split, row0, row_end, b, hk, split, (ST_LDS uint32_t*)(smem + kTblOffset), lane, n_masked, first_masked);
     if (lane == 0) {
       params[0] = (uint32_t)n_masked;
       params[1] = lds_base + kTblOffset + 32 * first_masked;
-      params[2] = split >= first_part ? 1 : 0;
+      params[2] = part ? 1 : 0;
       params[3] = (uint32_t)n;
     }
   }
   __syncthreads();
   const int total_tiles = (int)params[3];
-  float* dq0 = (split >= first_part ? a.parts + (int64_t)(split - first_part) * dq_part_floats(s) : a.dq) + (((int64_t)b * s.Sq + row0) * s.Hq + h) * D;
+  float* dq0 = (part ? dq_part(a.parts, s, tiles, a.shares, b, qt, split - a.shares.own0) : a.dq + ((int64_t)b * s.Sq + row0) * s.Hq * D) + h * D;
   if (total_tiles <= 0) {                            // uniform over the workgroup
-    if (split >= first_part)
+    if (part)
       for (int p = tid; p < rows * (D / 4); p += 256)
         *reinterpret_cast<float4*>(dq0 + (int64_t)(p / (D / 4)) * s.Hq * D + p % (D / 4) * 4) = make_float4(0.f, 0.f, 0.f, 0.f);
     return;
@@ -120,7 +121,7 @@ __device__ __forceinline__ void dq_fast_body(const BwdArgs& a, int block_x, int 
   vb[0] = (uint32_t)(srow * a.t.kss * 2 + spc * 16);
   vb[1] = (uint32_t)(srow * a.t.vss * 2 + spc * 16);
   vb[2] = (uint32_t)((64 * wave + r) * s.Hq * D * 4 + g * 16);       // dQ row of this lane
-  vb[3] = (q_row < s.Sq ? 1u : 0u) | (q_row + 32 < s.Sq ? 2u : 0u);
+  vb[3] = (q_row < row_end ? 1u : 0u) | (q_row + 32 < row_end ? 2u : 0u);
 
   if constexpr (D == 128) {
     asm volatile(ST_DQ_FAST_ASM

@@ -115,6 +115,8 @@ __global__ __launch_bounds__(256) void combine_kernel(const CombineArgs a, int32
   const RowOf at = row_of(row, n_rows, a.Sq_out, a.Hq);
   const int64_t b = at.b;
   const int32_t i = at.i, h = at.h;
+  const int n = a.shares.n > 1 ? shares_of(a.shares, a.tiles.tile_of(i)) : a.n;     // states that hold this row
+  if (a.shares.n > 1 && n <= 1) return;
   const int64_t l_in = (b * a.Hq + h) * a.Sq_in + a.row0 + i;
   const int64_t v_in = ((b * a.Sq_in + a.row0 + i) * a.Hq + h) * vec_per_row + sub;
 
@@ -123,6 +125,7 @@ __global__ __launch_bounds__(256) void combine_kernel(const CombineArgs a, int32
     const f32x4_t t = __builtin_nontemporal_load(reinterpret_cast<const f32x4_t*>(a.o[x]) + v_in);   // read once
     return make_float4(t.x, t.y, t.z, t.w);
   };
+  auto load_few = [&](int x) { return x < n ? load_o(x) : make_float4(0.f, 0.f, 0.f, 0.f); };
   // The O of an empty state may never have been written (the split forward leaves it out): it is loaded like the others, and a
   // weight of exactly 0 keeps it, NaN or not, out of the sum.
   auto add = [](float4& r, float w, const float4& p) {
@@ -141,9 +144,9 @@ __global__ __launch_bounds__(256) void combine_kernel(const CombineArgs a, int32
     float l[N];
     float4 p[U];
 #pragma unroll
-    for (int x = 0; x < N; ++x) l[x] = x < a.n ? a.lse[x][l_in] : -INFINITY;
+    for (int x = 0; x < N; ++x) l[x] = x < n ? a.lse[x][l_in] : -INFINITY;
 #pragma unroll
-    for (int u = 0; u < U; ++u) p[u] = load_o(u < a.n ? u : a.n - 1);
+    for (int u = 0; u < U; ++u) p[u] = load_few(u);
     float m = -INFINITY;
 #pragma unroll
     for (int x = 0; x < N; ++x) m = fmaxf(m, l[x]);
@@ -160,10 +163,10 @@ __global__ __launch_bounds__(256) void combine_kernel(const CombineArgs a, int32
       for (int x0 = 0; x0 < N; x0 += U) {
 #pragma unroll
         for (int u = 0; u < U; ++u) {
-          if (x0 > 0) p[u] = load_o(x0 + u < a.n ? x0 + u : a.n - 1);
+          if (x0 > 0) p[u] = load_few(x0 + u);
         }
 #pragma unroll
-        for (int u = 0; u < U; ++u) add(r, x0 + u < a.n ? l[x0 + u] * inv : 0.f, p[u]);
+        for (int u = 0; u < U; ++u) add(r, x0 + u < n ? l[x0 + u] * inv : 0.f, p[u]);
       }
     }
   } else {
@@ -311,27 +314,31 @@ __global__ __launch_bounds__(256) void scale_q_kernel(View q, u32x4* __restrict_
   dst[v] = scale_bf16x8(*reinterpret_cast<const u32x4*>((const uint16_t*)q.ptr + off), c);
 }
 
-// Partial sums of an under-filled launch: bytes only, (n_parts + 2) x 4 per element.  Eight loads of a thread are in flight
-// together; the order of the additions is fixed.
-__global__ __launch_bounds__(256) void add_parts_kernel(float4* __restrict__ dst, const float4* __restrict__ parts, int n_parts,
-                                                        int64_t stride, int64_t n_vec) {
-  const int64_t v = (int64_t)blockIdx.x * 256 + threadIdx.x;
+// Partial sums of an under-filled launch: bytes only, (sums + 2) x 4 per element.  blockIdx.y is a query tile of a batch
+// entry, whose rows are one run of memory in dq and in each sum.  Eight loads of a thread are in flight together; the order of
+// the additions is fixed.
+__global__ __launch_bounds__(256) void add_parts_kernel(float* dq, float* sums, Shape s, QueryTiles tiles, TileShares shares, int n_qt) {
+  const int b = blockIdx.y / n_qt, qt = blockIdx.y % n_qt, n = shares_of(shares, qt) - shares.own0;
+  if (n + shares.own0 <= 1) return;
+  const int64_t n_vec = (int64_t)tiles.rows_of(qt) * s.Hq * s.D / 4, v = (int64_t)blockIdx.x * 256 + threadIdx.x;
   if (v >= n_vec) return;
-  float4 x = dst[v];
-  for (int y0 = 0; y0 < n_parts; y0 += 8) {
+  const float4* parts = reinterpret_cast<const float4*>(dq_part(sums, s, tiles, shares, b, qt, 0)) + v;
+  float4* dst = reinterpret_cast<float4*>(dq + ((int64_t)b * s.Sq + tiles.row0(qt)) * s.Hq * s.D) + v;
+  float4 x = *dst;
+  for (int y0 = 0; y0 < n; y0 += 8) {
     float4 p[8];
 #pragma unroll
-    for (int u = 0; u < 8; ++u) p[u] = parts[(int64_t)min(y0 + u, n_parts - 1) * stride + v];
+    for (int u = 0; u < 8; ++u) p[u] = parts[min(y0 + u, n - 1) * n_vec];
 #pragma unroll
     for (int u = 0; u < 8; ++u)
-      if (y0 + u < n_parts) {
+      if (y0 + u < n) {
         x.x += p[u].x;
         x.y += p[u].y;
         x.z += p[u].z;
         x.w += p[u].w;
       }
   }
-  dst[v] = x;
+  *dst = x;
 }
 
 __global__ __launch_bounds__(256) void add_kv_parts_kernel(const BwdArgs a, int64_t n_vec) {
@@ -508,11 +515,13 @@ hipError_t launch_zero(void* dst, int64_t bytes, hipStream_t s) {
   return hipGetLastError();
 }
 
-hipError_t launch_add_parts(float* dst, const float* parts, int n_parts, int64_t stride, int64_t n, hipStream_t s) {
-  if (n <= 0 || n_parts <= 0) return hipSuccess;
+hipError_t launch_add_parts(const BwdArgs& a, int rows, hipStream_t s) {
+  const QueryTiles tiles = query_tiles(a.s, rows);
+  const int n_qt = tiles.count();
+  if (n_qt <= 0 || a.s.B <= 0) return hipSuccess;
+  if ((int64_t)n_qt * a.s.B > 65535) return hipErrorInvalidValue;     // split launches have fewer than 512 tiles
   ProfScope prof("add_parts", s);
-  hipLaunchKernelGGL(add_parts_kernel, dim3(blocks_for(n / 4)), dim3(256), 0, s, (float4*)dst, (const float4*)parts, n_parts,
-                     stride / 4, n / 4);
+  hipLaunchKernelGGL(add_parts_kernel, dim3(blocks_for((int64_t)min(rows, a.s.Sq) * a.s.Hq * a.s.D / 4), n_qt * a.s.B), dim3(256), 0, s, a.dq, a.parts, a.s, tiles, a.shares, n_qt);
   return hipGetLastError();
 }
 

@@ -253,8 +253,7 @@ __device__ __forceinline__ KeyTile key_tile(const KeyTable& tab, const ChunkTabl
 
 // ---------------------------------------------------------------- forward
 // Bounded by the matrix instructions: D per 32 x 32 tile pair and 64 cycles each.  Eight wavefronts share the 32 rows.  An
-// under-filled launch (n_split > 1) gives every query tile n_split workgroups, blockIdx.y of them, each with a share of the
-// walk (see KeyTable).
+// under-filled launch gives a query tile several workgroups, each with a share of the walk (see KeyTable, TileShares).
 template <int DP, bool FULL>
 __global__ __launch_bounds__(waves<DP>() * 64) void fwd_f32_kernel(const FwdArgs a) {
   constexpr int NW = waves<DP>(), DB = DP / 32, N = 32, NR = row_pieces<DP, N>(), NC = col_pieces<DP, N>();
@@ -267,8 +266,9 @@ __global__ __launch_bounds__(waves<DP>() * 64) void fwd_f32_kernel(const FwdArgs
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int g = lane >> 5, r = lane & 31;
   const int n_qt = (s.Sq + kT - 1) / kT;
-  int qt, hb;
-  qtile_block(blockIdx.x, gridDim.x, n_qt, s.causal, qt, hb);
+  int qt, hb, split;
+  share_block(a.shares, blockIdx.x, gridDim.x, blockIdx.y, n_qt, s.causal, qt, hb, split);
+  const int n_split = max(shares_of(a.shares, qt), 1);
   const int h = hb % s.Hq, b = hb / s.Hq, hk = h / (s.Hq / s.Hkv);
   const int row0 = qt * kT;
   const int64_t first_pos = q_pos(s, row0), last_pos = q_pos(s, min(row0 + kT, s.Sq) - 1);
@@ -284,7 +284,7 @@ __global__ __launch_bounds__(waves<DP>() * 64) void fwd_f32_kernel(const FwdArgs
   zero_acc(acc);
   const int end = tab.end[lane];
   int lo, hi;
-  key_share(end, a.n_split, blockIdx.y, lo, hi);
+  key_share(end, n_split, split, lo, hi);
   for (int x = lo + wave; x < hi; x += NW) {
     const KeyTile w = key_tile(tab, a.t, end, x);
     const float *kb = w.k, *vb = w.v;
@@ -361,8 +361,8 @@ __global__ __launch_bounds__(waves<DP>() * 64) void fwd_f32_kernel(const FwdArgs
   if (wave != 0 || row0 + r >= s.Sq) return;
   l = xhalf_sum(l);
   const float inv = l > 0.f ? 1.f / l : 0.f;
-  float* o = a.o + (int64_t)blockIdx.y * a.split_o + (((int64_t)b * s.Sq + row0 + r) * s.Hq + h) * s.D;
-  float* ol = a.o_lowp ? (float*)a.o_lowp + (((int64_t)b * s.Sq + row0 + r) * s.Hq + h) * s.D : nullptr;   // storage dtype is fp32 here
+  float* o = (n_split > 1 ? a.part_o + split * a.part_stride : a.o) + (((int64_t)b * s.Sq + row0 + r) * s.Hq + h) * s.D;
+  float* ol = a.o_lowp && n_split <= 1 ? (float*)a.o_lowp + (((int64_t)b * s.Sq + row0 + r) * s.Hq + h) * s.D : nullptr;   // storage dtype is fp32 here
 #pragma unroll
   for (int db = 0; db < DB; ++db)
 #pragma unroll
@@ -373,7 +373,10 @@ __global__ __launch_bounds__(waves<DP>() * 64) void fwd_f32_kernel(const FwdArgs
       *reinterpret_cast<float4*>(o + d) = x;
       if (ol) *reinterpret_cast<float4*>(ol + d) = x;
     }
-  if (g == 0) a.lse[(int64_t)blockIdx.y * a.split_l + ((int64_t)b * s.Hq + h) * s.Sq + row0 + r] = l > 0.f ? m + logf(l) : -INFINITY;
+  const int64_t stat = ((int64_t)b * s.Hq + h) * s.Sq + row0 + r;
+  if (g == 0) (n_split > 1 ? a.part_lse + split * a.part_stride : a.lse)[stat] = l > 0.f ? m + logf(l) : -INFINITY;
+  if (g == 0 && split == 0)                                  // states of shares that other tiles have: empty
+    for (int y = n_split > 1 ? n_split : 0; y < a.shares.n && a.shares.n > 1; ++y) a.part_lse[y * a.part_stride + stat] = -INFINITY;
   if (any_dirty)                                             // (a value that several shares add is the same infinity or NaN)
     for (int c = 0; c < a.t.n; ++c)
       add_nonfinite(o, ol, (const float*)a.t.v[c] + b * a.t.vsb + hk * a.t.vsh, a.t.vss,
@@ -394,8 +397,9 @@ __global__ __launch_bounds__(waves<DP>() * 64) void bwd_dq_f32_kernel(const BwdA
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int g = lane >> 5, r = lane & 31;
   const int n_qt = (s.Sq + kT - 1) / kT;
-  int qt, hb;
-  qtile_block(blockIdx.x, gridDim.x, n_qt, s.causal, qt, hb);
+  int qt, hb, split;
+  share_block(a.shares, blockIdx.x, gridDim.x, blockIdx.y, n_qt, s.causal, qt, hb, split);
+  const int n_split = max(shares_of(a.shares, qt), 1);
   const int h = hb % s.Hq, b = hb / s.Hq, hk = h / (s.Hq / s.Hkv);
   const int row0 = qt * kT;
   const int64_t first_pos = q_pos(s, row0), last_pos = q_pos(s, min(row0 + kT, s.Sq) - 1);
@@ -412,10 +416,9 @@ __global__ __launch_bounds__(waves<DP>() * 64) void bwd_dq_f32_kernel(const BwdA
   const int64_t qpos = q_pos(s, i);
   f32x16 acc[DB];
   zero_acc(acc);
-  const int n_split = max(a.n_split, 1);
   const int end = tab.end[lane];
   int lo, hi;
-  key_share(end, n_split, blockIdx.y, lo, hi);
+  key_share(end, n_split, split, lo, hi);
   for (int x = lo + wave; x < hi; x += NW) {
     const KeyTile w = key_tile(tab, a.t, end, x);
     const float *kb = w.k, *vb = w.v;
@@ -458,10 +461,9 @@ __global__ __launch_bounds__(waves<DP>() * 64) void bwd_dq_f32_kernel(const BwdA
     __syncthreads();
   }
   if (wave != 0 || row0 + r >= s.Sq) return;
-  const int first_part = n_split - a.n_parts;
-  const bool part = (int)blockIdx.y >= first_part;                            // a partial sum (its memory holds nothing yet), not dq itself
+  const bool part = n_split > 1 && split >= a.shares.own0;   // a sum of its own (its memory holds nothing yet), not dq itself
   if (empty && !part) return;
-  float* dq = (part ? a.parts + (int64_t)((int)blockIdx.y - first_part) * dq_part_floats(s) : a.dq) + (((int64_t)b * s.Sq + row0 + r) * s.Hq + h) * s.D;
+  float* dq = (part ? dq_part(a.parts, s, query_tiles(s, kT), a.shares, b, qt, split - a.shares.own0) : a.dq + ((int64_t)b * s.Sq + row0) * s.Hq * s.D) + ((int64_t)r * s.Hq + h) * s.D;
 #pragma unroll
   for (int db = 0; db < DB; ++db)
 #pragma unroll
@@ -636,7 +638,7 @@ hipError_t launch_fwd_f32(const FwdArgs& a, hipStream_t stream) {
   return with_padded_d(a.s.D, [&](auto dp, auto full) {
     constexpr int DP = decltype(dp)::value;
     constexpr bool FULL = decltype(full)::value;
-    const dim3 grid((unsigned)total, (unsigned)(a.n_split > 1 ? a.n_split : 1));
+    const dim3 grid = share_grid(a.shares, total, (a.s.Sq + kT - 1) / kT);
     hipLaunchKernelGGL((fwd_f32_kernel<DP, FULL>), grid, dim3(waves<DP>() * 64), 0, stream, a);
     return hipGetLastError();
   });
@@ -651,12 +653,11 @@ hipError_t launch_bwd_f32(const BwdArgs& a, hipStream_t stream) {
     constexpr bool FULL = decltype(full)::value;
     {
       ProfScope prof("bwd_dq_f32", stream);
-      const dim3 grid((unsigned)total, (unsigned)(a.n_split > 1 ? a.n_split : 1));
+      const dim3 grid = share_grid(a.shares, total, (a.s.Sq + kT - 1) / kT);
       hipLaunchKernelGGL((bwd_dq_f32_kernel<DP, FULL>), grid, dim3(waves<DP>() * 64), 0, stream, a);
     }
     hipError_t e = hipGetLastError();
-    if (e == hipSuccess && a.n_parts > 0)
-      e = launch_add_parts(a.dq, a.parts, a.n_parts, dq_part_floats(a.s), (int64_t)a.s.B * a.s.Sq * a.s.Hq * a.s.D, stream);
+    if (e == hipSuccess && a.shares.n > 1) e = launch_add_parts(a, kT, stream);
     if (e != hipSuccess) return e;
     ProfScope prof("bwd_dkv_f32", stream);
     const dim3 grid((a.s.Sk + kT - 1) / kT, a.s.Hkv, a.s.B * a.t.n);

@@ -411,9 +411,9 @@ hipError_t launch_fwd_bf16(const FwdArgs& a, hipStream_t stream) {
   // chunk 8.1 against 6.7 us on the general kernel, five tiles 13.3 (causal 15.9) against 12.2 (11.8), eight 13.5 against
   // 15.5, 64 tiles 60 against 86.  At head size 128 it is the faster one from the first tile on (10.8 against 11.5; 64
   // tiles: 76 against 168).
-  const bool few = a.s.D == 64 && a.n_split <= 1 && (int64_t)a.t.n * ((a.s.Sk + kQTileFastKeys - 1) / kQTileFastKeys) <= 6;
-  if ((knobs().fwd_fast || a.n_split > 1) && !few && fwd_fast_usable(a)) return launch_fwd_fast(a, stream);
-  if (a.n_split > 1) return hipErrorInvalidValue;      // only the hand-scheduled kernel walks a split table
+  const bool few = a.s.D == 64 && a.shares.n <= 1 && (int64_t)a.t.n * ((a.s.Sk + kQTileFastKeys - 1) / kQTileFastKeys) <= 6;
+  if ((knobs().fwd_fast || a.shares.n > 1) && !few && fwd_fast_usable(a)) return launch_fwd_fast(a, stream);
+  if (a.shares.n > 1) return hipErrorInvalidValue;      // only the hand-scheduled kernel walks a split table
   // few tiles, chunks of fewer than 64 keys, or strides beyond its 32-bit offsets.
   // Head size 64: the two-wavefronts-per-SIMD kernel is the faster one (21.0 against 28.3 ms on the 24-head,
   // 16384 x 131072 full-mask share); head size 128: the pipelined kernel

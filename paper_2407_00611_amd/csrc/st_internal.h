@@ -50,6 +50,58 @@ struct ChunkTable {
   int64_t ksb, kss, ksh, vsb, vss, vsh;
 };
 
+// The query tiles of a head, `rows` rows each but for the last one; where n_lo > 0 the two runs of rows have tiles of their own,
+// n_lo of them the first run.
+struct QueryTiles {
+  int32_t rows, Sq, seg, n_lo;
+  __host__ __device__ int count() const { return n_lo > 0 ? n_lo + (Sq - seg + rows - 1) / rows : (Sq + rows - 1) / rows; }
+  __host__ __device__ int row0(int qt) const { return n_lo > 0 && qt >= n_lo ? seg + (qt - n_lo) * rows : qt * rows; }
+  __host__ __device__ int rows_of(int qt) const {
+    const int left = (n_lo > 0 && qt < n_lo ? seg : Sq) - row0(qt);
+    return left < rows ? left : rows;
+  }
+  __host__ __device__ int tile_of(int row) const { return n_lo > 0 && row >= seg ? n_lo + (row - seg) / rows : row / rows; }
+};
+// of the hand-scheduled kernels (kQTileFastRows) and the fp32 ones (32 rows).  Under a causal mask a 256-row tile with rows of
+// both runs would walk what the second run sees with masks all the way: a masked tile takes 1.4 (dQ) to 2 times a whole one (64
+// workgroups of 128 tiles, head size 128: forward 142 us whole and 266 masked, dQ 198 and 275).
+constexpr int kQTileFastRows = 256;
+__host__ __device__ inline QueryTiles query_tiles(const Shape& s, int rows) {
+  return QueryTiles{rows, s.Sq, s.q_seg, s.causal && s.q_seg % rows && rows == kQTileFastRows ? (s.q_seg + rows - 1) / rows : 0};
+}
+
+// Under-filled launches of the query-stationary kernels: workgroups per query tile, each with a share of the tile's walk.
+// Every tile has n of them (total == 0; grid (tiles, n)), or, where a causal mask makes the walks of the tiles differ, tile qt
+// has its own number, at most n (total > 0: their sum over the tiles of a head; grid (heads * total)).  n <= 1: no tile is split.
+constexpr int kShareTiles = 64;      // tiles per head such a table has room for
+struct TileShares {
+  int16_t n, total;
+  int16_t own0;        // dQ only, 1: the first share of a split tile adds to dq itself instead of storing a partial sum
+  uint64_t less1[kShareTiles / 16];   // shares less one of tile qt: bits 4 (qt % 16) of word qt / 16
+};
+// (the words are picked by selects, so that a kernel reads all of them at once with its other arguments, which come from host
+// memory, and not one after the other)
+__host__ __device__ inline int shares_of(const TileShares& t, int qt) {
+  if (t.total <= 0) return t.n;
+  uint64_t w = t.less1[0];
+  for (int x = 1; x < kShareTiles / 16; ++x) w = (qt >> 4) == x ? t.less1[x] : w;
+  return (int)(w >> (4 * (qt & 15)) & 15) + 1;
+}
+// partial sums the tiles before qt store (see BwdArgs::shares): n - own0 each for n > 1 shares
+__host__ __device__ inline int parts_before(const TileShares& t, int qt) {
+  if (t.n <= 1) return 0;
+  if (t.total <= 0) return qt * (t.n - t.own0);
+  int sum = 0;
+  for (int x = 0; x < kShareTiles / 16; ++x) {
+    const int k = qt - 16 * x;                         // tiles of this word
+    const uint64_t m = k <= 0 ? 0 : k >= 16 ? t.less1[x] : t.less1[x] & (((uint64_t)1 << (4 * k)) - 1);
+    const uint64_t low = 0x0f0f0f0f0f0f0f0full, pairs = (m & low) + (m >> 4 & low);      // at most 8 x 30 together
+    const uint64_t split = (m | m >> 1 | m >> 2 | m >> 3) & 0x1111111111111111ull;
+    sum += (int)(pairs * 0x0101010101010101ull >> 56) + (1 - t.own0) * __builtin_popcountll(split);
+  }
+  return sum;
+}
+
 struct FwdArgs {
   Shape s;
   View q;
@@ -57,11 +109,11 @@ struct FwdArgs {
   float* o;        // fp32 [B,Sq,Hq,D]
   float* lse;      // fp32 [B,Hq,Sq]
   void* o_lowp;    // nullable, [B,Sq,Hq,D] in the storage dtype
-  // Under-filled launches: n_split > 1 gives every query tile n_split workgroups (blockIdx.y), each walking a
-  // share of the tiles and writing its own partial state at o + y * split_o, lse + y * split_l (floats); the states
-  // are combined afterwards.  0 or 1: one workgroup walks the whole table.
-  int32_t n_split;
-  int64_t split_o, split_l;
+  // A split launch (shares.n > 1): share y of a split tile writes a partial state of its own at part_o + y * part_stride,
+  // part_lse + y * part_stride (floats), the states are combined afterwards; tiles with one share write o, lse and o_lowp.
+  TileShares shares;
+  float *part_o, *part_lse;
+  int64_t part_stride;
   float sum_limit;   // fast kernel: sum over a block's probabilities beyond which the lazy exponent reference moves (set by its launcher)
 };
 
@@ -77,17 +129,16 @@ struct BwdArgs {
   float* dq;           // fp32 [B,Sq,Hq,D], +=
   float* dk[kMaxTable];  // fp32 [B,Sk,Hkv,D] per table entry, +=
   float* dv[kMaxTable];
-  // Under-filled dQ launches of the hand-scheduled and of the fp32 kernel: n_split > 1 gives every query tile n_split workgroups
-  // (blockIdx.y), each with a share of the tiles.  The last n_parts of them store their sums at parts + (0, 1, ...) *
-  // part_floats(dq) (laid out as dq), and the launcher then adds these to dq in order.  n_parts is 0 unsplit and n_split
-  // otherwise, or n_split - 1 where the workspace has no room for one more: then number 0 adds to dq itself, and its reads
-  // end the launch 2 us later.
-  int32_t n_split, n_parts;
+  // Under-filled dQ launches of the hand-scheduled and of the fp32 kernel: a share of a split tile stores its sum, and the
+  // launcher then adds the sums to dq in order.  Sum y of tile qt holds the tile's rows, dense as dq has them, behind those of
+  // the tiles before it and of the shares before it (see dq_part).  Where the workspace has no room for all of them
+  // (shares.own0) the first share adds to dq itself, and its reads end the launch 2 us later.
+  TileShares shares;
   // Under-filled dK/dV launches likewise: kv_split > 1 gives every key tile kv_split workgroups, each with a share of the
   // query blocks.  The first one writes dk[c] / dv[c]; number y stores its sums at parts + ((2 (y - 1) + (0: dK, 1: dV)) *
   // t.n + c) * part_floats(dk[c]) (laid out as dk[c]), and the launcher adds them up (and rounds) in order.
-  int32_t kv_split;
-  int32_t pair;        // 1: both passes in one launch, where the hand-scheduled kernels take both (kv_split <= 1)
+  int16_t kv_split;
+  int16_t pair;        // 1: both passes in one launch, where the hand-scheduled kernels take both (kv_split <= 1)
   float* parts;        // the two passes use it one after the other
   // dK / dV work of a chunk's last visit folded into the launch (bf16 path): the hand-scheduled kernel's epilogue does it,
   // beside the general kernel the launcher runs fill and cast launches
@@ -96,16 +147,33 @@ struct BwdArgs {
   void* dv_lowp[kMaxTable];
   int32_t* queue;      // nullable, kQueueInts ints of device memory: the fast dK/dV kernel hands its key tiles out
                        // through it (one counter per XCD), so that XCDs that run faster take more of them
-  int32_t queue_clean; // 1: the counters are zero already (the first launch behind launch_bwd_prep)
-  int32_t queue_xcds;  // counters in use (the device's XCD count, 1 .. 8); set by the launcher
+  int16_t queue_clean; // 1: the counters are zero already (the first launch behind launch_bwd_prep)
+  int16_t queue_xcds;  // counters in use (the device's XCD count, 1 .. 8); set by the launcher
 };
 // distance between partial sums of n floats each (256-byte steps)
 __host__ __device__ inline int64_t part_floats(int64_t n) { return (n + 63) / 64 * 64; }
-__host__ __device__ inline int64_t dq_part_floats(const Shape& s) { return part_floats((int64_t)s.B * s.Sq * s.Hq * s.D); }
+// Partial sum y of query tile qt of batch entry b: [row, head, element] floats from here on.  The sums of a batch entry lie one
+// behind the other; dq_part_rows are the rows before that of tile qt.
+__host__ __device__ inline int64_t dq_part_rows(const QueryTiles& q, const TileShares& t, int qt) {
+  // every tile before qt as a full one, less what the last tile of the first run lacks
+  int64_t rows = (int64_t)parts_before(t, qt) * q.rows;
+  if (q.n_lo > 0 && qt >= q.n_lo) {
+    const int n = shares_of(t, q.n_lo - 1);
+    rows -= (int64_t)(n > 1 ? n - t.own0 : 0) * (q.n_lo * q.rows - q.seg);
+  }
+  return rows;
+}
+__host__ __device__ inline int64_t dq_part_rows_all(const QueryTiles& q, const TileShares& t) {
+  const int last = q.count() - 1, n = shares_of(t, last);
+  return dq_part_rows(q, t, last) + (int64_t)(t.n > 1 && n > 1 ? n - t.own0 : 0) * q.rows_of(last);
+}
+__host__ __device__ inline float* dq_part(float* parts, const Shape& s, const QueryTiles& q, const TileShares& t, int b, int qt, int y) {
+  return parts + (b * dq_part_rows_all(q, t) + dq_part_rows(q, t, qt) + (int64_t)y * q.rows_of(qt)) * s.Hq * s.D;
+}
 __host__ __device__ inline int64_t kv_part_floats(const Shape& s) { return part_floats((int64_t)s.B * s.Sk * s.Hkv * s.D); }
 constexpr int kQueueInts = 8 * 32;   // at most 8 counters, 128 bytes apart
-// passed by value: the kernel-argument segment holds 4096 bytes, 256 of them the implicit arguments
-static_assert(sizeof(BwdArgs) <= 4096 - 256 && sizeof(FwdArgs) <= 4096 - 256, "argument structs must fit the kernel-argument segment");
+// passed by value: a kernel takes 4096 bytes of arguments
+static_assert(sizeof(BwdArgs) <= 4096 - 64 && sizeof(FwdArgs) <= 4096 - 64, "argument structs must fit the kernel arguments");
 
 // n partial states of the same query rows (each O fp32 [B,Sq_in,Hq,D], lse fp32 [B,Hq,Sq_in]) and the run of
 // rows [row0, row0 + Sq_out) the combined state keeps.
@@ -117,6 +185,10 @@ struct CombineArgs {
   float* o_out;      // fp32 [B,Sq_out,Hq,D]
   float* lse_out;    // fp32 [B,Hq,Sq_out]
   void* o_lowp;      // nullable, [B,Sq_out,Hq,D]
+  // The states of a split forward (shares.n > 1; row0 = 0, Sq_out = Sq_in): only the first shares_of(tile) of them hold rows of
+  // a tile, and the rows of a tile with one share are not combined.
+  TileShares shares;
+  QueryTiles tiles;
 };
 
 // Tile of the hand-scheduled dK/dV kernel
@@ -155,8 +227,7 @@ struct ProfScope {
   hipStream_t stream;
 };
 
-// Tile of the hand-scheduled query-stationary kernels (forward, dQ)
-constexpr int kQTileFastRows = 256;
+// Keys of a tile of the hand-scheduled query-stationary kernels (forward, dQ); its rows are kQTileFastRows
 constexpr int kQTileFastKeys = 64;
 constexpr int kDqFastRows = kQTileFastRows;
 constexpr int kDqFastKeys = kQTileFastKeys;
@@ -188,8 +259,8 @@ hipError_t launch_cast(const float* src, void* dst, int64_t n, int dst_dtype, hi
 hipError_t launch_scale_q(const View& q, void* dst, int32_t B, int32_t Sq, int32_t Hq, int32_t D, float scale, hipStream_t s);
 // dk[c] += its parts (see BwdArgs::kv_split) in order, likewise dv[c]; rounded to dk_lowp[c] / dv_lowp[c] where given
 hipError_t launch_add_kv_parts(const BwdArgs& a, hipStream_t s);
-// dst += parts[0] + parts[1] + ... in that order; part y at parts + y * stride, n floats each (n % 4 == 0)
-hipError_t launch_add_parts(float* dst, const float* parts, int n_parts, int64_t stride, int64_t n, hipStream_t s);
+// dq += its partial sums (see BwdArgs::shares) in order; `rows` rows per query tile
+hipError_t launch_add_parts(const BwdArgs& a, int rows, hipStream_t s);
 hipError_t launch_fill_state(float* o, float* lse, int64_t n_o, int64_t n_lse, hipStream_t s);
 hipError_t launch_zero(void* dst, int64_t bytes, hipStream_t s);   // bytes % 4 == 0, dst 4-byte aligned
 // benchmark aid: MFMA-only loop, one workgroup per compute unit (see st_probe.hip)

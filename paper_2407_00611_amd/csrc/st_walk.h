@@ -34,10 +34,28 @@ __device__ __forceinline__ int lane_scan(int x, int& total) {
   return sum - x;
 }
 
+// Block of a query-stationary launch -> query tile, head-and-batch index and share (see TileShares).  Where the tiles have
+// numbers of their own, the shares of a head are numbered from its last tile down and handed out in that order, all heads'
+// first ones first (qtile_block): the longest ones are the last tiles'.
+__device__ __forceinline__ void share_block(const TileShares& t, int block_x, int grid_x, int block_y, int n_qt, int causal, int& qt, int& hb, int& split) {
+  if (t.total <= 0) {
+    qtile_block(block_x, grid_x, n_qt, causal, qt, hb);
+    split = block_y;
+    return;
+  }
+  qtile_block(block_x, grid_x, t.total, 0, split, hb);
+  split = (int)sgpr(split);
+  for (qt = n_qt - 1; qt > 0; --qt) {
+    const int n = shares_of(t, qt);
+    if (split < n) break;
+    split -= n;
+  }
+}
+
 constexpr int kRelMin = -(1 << 30);                  // relative position of a tile that no causal mask touches
 
 // Position of row i relative to the workgroup's first row, as the mask routines compare it with a tile's: the sum of the two
-// has to stay inside 32 bits.  Under a causal mask walk_usable sees to that.  Without one the routines still run, for the
+// has to stay inside 32 bits.  Under a causal mask it does, as no tile has rows of two runs.  Without one the routines still run, for the
 // ragged end of a chunk, and two runs of rows may lie any distance apart, so there a row has no position: all of them see
 // every key of a tile at kRelMin.
 __device__ __forceinline__ int walk_row_pos(const Shape& s, int i, int row0) {
@@ -55,16 +73,16 @@ __device__ __forceinline__ int walk_row_pos(const Shape& s, int i, int row0) {
 // 2 x 512 rows at head size 64 30.7 and 29.0 (31.8 and 30.5); three units for a masked tile are as far off on the other side
 // (82.4, 107.5).  Returns the tiles of the split; n_masked of them, the last ones, are masked; their entries start at
 // first_masked.
-__device__ __forceinline__ int build_walk(const Shape& s, const ChunkTable& t, int splits, int row0, int b, int hk, int split, ST_LDS uint32_t* tbl, int lane,
+__device__ __forceinline__ int build_walk(const Shape& s, const ChunkTable& t, int splits, int row0, int row_end, int b, int hk, int split, ST_LDS uint32_t* tbl, int lane,
                                           int& n_masked, int& first_masked) {
-  constexpr int BM = kQTileFastRows, BN = kQTileFastKeys;
+  constexpr int BN = kQTileFastKeys;
   const int n64 = s.Sk / BN;
   static_assert(kMaxTable == 64, "a lane per chunk");
   // the whole table is read, so that the loads need not wait for its length (arguments come from host memory)
   const int64_t k0 = t.k_offset[lane];
   const char* kp = (const char*)t.k[lane] + ((int64_t)b * t.ksb + (int64_t)hk * t.ksh) * 2;
   const char* vp = (const char*)t.v[lane] + ((int64_t)b * t.vsb + (int64_t)hk * t.vsh) * 2;
-  const int64_t q_base = q_pos(s, row0), q_last = q_pos(s, min(row0 + BM, s.Sq) - 1), rel0 = k0 - q_base;
+  const int64_t q_base = q_pos(s, row0), q_last = q_pos(s, row_end - 1), rel0 = k0 - q_base;
   const int64_t nv = s.causal ? min(max(q_base - k0 + 1, (int64_t)0), (int64_t)s.Sk) : s.Sk;       // keys the first row sees
   const int64_t nv_last = s.causal ? min(max(q_last - k0 + 1, (int64_t)0), (int64_t)s.Sk) : s.Sk;  // and the last one
   const bool listed = lane < t.n;
@@ -104,18 +122,18 @@ __device__ __forceinline__ int build_walk(const Shape& s, const ChunkTable& t, i
   return hi - lo;
 }
 
+// grid of a launch whose `total` query tiles, n_qt of each head, have these shares
+inline dim3 share_grid(const TileShares& t, int64_t total, int n_qt) {
+  if (t.total > 0) return dim3((unsigned)(total / n_qt * t.total));
+  return dim3((unsigned)total, (unsigned)(t.n > 1 ? t.n : 1));
+}
+
 // what the loops keep in 32-bit registers fits them
 inline bool walk_usable(const Shape& s, const ChunkTable& t) {
   if ((s.D != 128 && s.D != 64) || s.Sk < kQTileFastKeys || s.Sq < 1) return false;
   auto fits = [](int64_t x) { return x > 0 && x < (int64_t)1 << 30; };
   if (!(fits(kQTileFastKeys * t.kss * 2) && fits(kQTileFastKeys * t.vss * 2) && fits((int64_t)kQTileFastRows * s.Hq * s.D * 4)))
     return false;
-  // walk_row_pos; only the tile that holds the end of a first run can be wide
-  if (s.causal && s.q_seg > 0) {
-    const int row0 = s.q_seg / kQTileFastRows * kQTileFastRows;
-    const int last = row0 + kQTileFastRows < s.Sq ? row0 + kQTileFastRows - 1 : s.Sq - 1;
-    if (last > row0 && !fits(q_pos(s, last) - q_pos(s, row0))) return false;
-  }
   return true;
 }
 

@@ -1,0 +1,67 @@
+"""Launches whose query tiles have unlike walks (a causal mask, two runs of rows): each tile has a number of workgroups of its
+own, and the two runs have tiles of their own.  Forward and dQ against the fp64 oracle, on workspaces full of NaN, and
+against the launch that a workspace without room for partial results leaves whole."""
+import pytest
+import torch
+
+import paper_2407_00611_amd as st
+import synth_inputs as si
+from oracle import attention as oa
+from util import assert_close, assert_close_wide, host, positions, upload
+
+pytestmark = pytest.mark.gpu
+
+#          dtype, B, Hq, Hkv, D, Sq, Sk, n, q_offset, (q_seg, q_offset2)
+CASES = [("bf16", 1, 2, 1, 128, 1500, 1500, 1, 0, (0, 0)),                # the diagonal alone: 1 to 6 tiles' worth
+         ("bf16", 2, 2, 2, 64, 1300, 700, 3, 650, (0, 0)),
+         ("bf16", 1, 2, 1, 128, 200, 100, 8, 100, (100, 600)),            # a tile per run
+         ("bf16", 2, 1, 1, 128, 1030, 515, 6, 0, (515, 2575)),            # three tiles per run, ragged ends of three rows
+         ("bf16", 1, 3, 1, 64, 1026, 513, 6, 1026, (513, 1539)),          # the runs touch; ragged ends of one row
+         ("bf16", 1, 1, 1, 128, 700, 350, 5, 0, (257, 1300)),             # runs of unlike length
+         ("bf16", 1, 1, 1, 64, 16384, 320, 8, -9000, (0, 0)),             # 64 tiles, the first half of them sees nothing
+         ("bf16", 1, 1, 1, 64, 16400, 320, 8, -9000, (0, 0)),             # 65: one number for all
+         ("f32", 1, 1, 1, 64, 1210, 1210, 1, 0, (0, 0)),
+         ("f32", 2, 1, 1, 128, 140, 70, 12, 70, (70, 700)),
+         ("f32", 1, 1, 1, 256, 2048, 256, 3, -100, (0, 0))]
+
+
+@pytest.mark.parametrize("c", CASES, ids=[f"{c[0]}_d{c[4]}_q{c[5]}_seg{c[9][0]}" for c in CASES])
+def test_tiles_with_shares_of_their_own(c):
+    dtype, B, Hq, Hkv, D, Sq, Sk, n, q0, (seg, q2) = c
+    w = si.Workload("shares", 360 + Sq % 100, dtype, B, Hq, Hkv, D, Sq, Sk, n, q0, True, True, q_seg=seg, q_offset2=q2)
+    print(f"[shares] {c}", flush=True)
+    inp = si.make_inputs(w)
+    q, ks, vs, d_o = upload(inp)
+    args = (w.q_where, [w.k_offset(j) for j in range(n)], True, w.scale)
+    order = list(range(n))
+    pos = positions(w)
+    o_r, lse_r = oa.attention_forward(inp.q, inp.k, inp.v, *pos, True, w.scale)
+    dq_r, dk_r, dv_r = oa.attention_backward(inp.q, inp.k, inp.v, inp.d_o, *pos, True, w.scale)
+    full = [st.st_ring_workspace_bytes(q, ks, vs, *args, st.ST_RING_FUSED, back) for back in (False, True)]
+    up = lambda x: (x + 255) // 256 * 256
+    base = up(B * Hq * Sq * 4) + 1024 + (up(q.numel() * 2) if dtype == "bf16" else 0)      # Delta, counters, scaled Q
+    ws = lambda size: torch.full((size + 256,), 0xff, dtype=torch.uint8, device="cuda")
+    st.st_profile_begin()
+    o, lse, low = st.st_ring_fwd(q, ks, vs, *args, order, workspace=ws(full[0]))
+    assert "combine" in st.st_profile_end(), "this share was meant to be split"
+    assert_close(host(o), o_r, dtype, "o")
+    assert_close(host(lse), lse_r, dtype, "lse", lse=dtype == "bf16")
+    assert torch.equal(low, o.to(low.dtype))
+    got = []
+    for size in (full[1], base + up(q.numel() * 4), base):                # all sums, first shares add themselves, unsplit
+        dq = torch.full_like(o, 1 / 64)
+        dk, dv = ([torch.zeros(k.shape, device="cuda") for k in ks] for _ in range(2))
+        st.st_ring_bwd(q, ks, vs, d_o, low, lse, *args, order, dq, dk, dv, workspace=ws(size))
+        assert_close(host(dq) - 1 / 64, dq_r, dtype, "dq")                # the start costs 1e-9 per element
+        for j in range(n):
+            if dtype == "f32":
+                assert_close(host(dk[j]), dk_r[j], dtype, f"dk[{j}]")
+                assert_close(host(dv[j]), dv_r[j], dtype, f"dv[{j}]")
+            else:                                                          # hundreds of rows add into few keys
+                assert_close_wide(host(dk[j]), dk_r[j], f"dk[{j}]")
+                assert_close_wide(host(dv[j]), dv_r[j], f"dv[{j}]")
+        got.append(dq)
+    dq = torch.full_like(o, 1 / 64)
+    st.st_ring_bwd_noalloc(q, ks, vs, d_o, low, lse, *args, order, dq, [torch.zeros(k.shape, device="cuda") for k in ks],
+                           [torch.zeros(k.shape, device="cuda") for k in ks])
+    assert torch.equal(dq, got[0])
