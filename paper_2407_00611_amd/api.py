@@ -3,6 +3,10 @@
 Argument marshalling only: tensors are torch tensors on the GPU ([B, S, heads, D] with D
 contiguous, fp32 or bf16), outputs are allocated with torch when not supplied, and every
 call is enqueued on torch's current stream.  A non-zero status raises StarTrailError.
+
+The calls that a training step makes many times try the native half first (``csrc/st_binding.cpp``),
+which reads plain tensors, lists and numbers in a tenth of the time; what it does not take (it then
+answers None, and has called nothing) goes through ctypes below, which also raises the errors.
 """
 from __future__ import annotations
 
@@ -115,6 +119,8 @@ def _load() -> C.CDLL:
 
 
 _lib = _load()
+from . import _binding  # noqa: E402  (linked against the library that has just been loaded)
+
 EXPORTS = ["st_attn_block_fwd", "st_attn_merge", "st_attn_combine", "st_attn_delta", "st_attn_block_bwd", "st_attn_block_bwd_workspace_bytes", "st_cast_from_f32",
            "st_visit_order", "st_team_visit_order", "st_schedule_report", "st_ring_workspace_bytes", "st_ring_fwd", "st_ring_bwd", "st_ring_bwd_noalloc", "st_ring_bwd_noalloc_max_bytes", "st_ring_bwd_last", "st_device_facts", "st_mfma_probe", "st_mfma_probe_mixes", "st_mfma_probe_mix_name", "st_profile_begin",
            "st_profile_end", "st_status_str",
@@ -153,6 +159,20 @@ def _stream(stream) -> C.c_void_p:
             return C.c_void_p(torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice()))
         stream = torch.cuda.current_stream()
     return C.c_void_p(stream.cuda_stream if hasattr(stream, "cuda_stream") else int(stream))
+
+
+def _raw_stream(stream):
+    """The stream's handle as a number, or None where only _stream knows how to get it."""
+    if stream is None:
+        return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice()) if torch.cuda.is_initialized() else None
+    return getattr(stream, "cuda_stream", None)
+
+
+def _done(status: Optional[int], where: str) -> bool:
+    """Whether the native half has made the call (its status is checked)."""
+    if status:
+        _check(status, where)
+    return status is not None
 
 
 def _ptr(t: Optional[torch.Tensor]) -> C.c_void_p:
@@ -240,6 +260,9 @@ def st_profile_end() -> dict:
 
 def st_attn_block_fwd(q, k, v, q_offset: int, k_offset: int, causal: bool, scale: float,
                       o_part=None, lse_part=None, stream=None) -> Tuple[torch.Tensor, torch.Tensor]:
+    if o_part is not None and lse_part is not None and \
+            _done(_binding.block_fwd(q, k, v, q_offset, k_offset, causal, scale, o_part, lse_part, _raw_stream(stream)), "st_attn_block_fwd"):
+        return o_part, lse_part
     B, Sq, Hq, D = q.shape
     o_part = torch.empty((B, Sq, Hq, D), dtype=torch.float32, device=q.device) if o_part is None else \
         _f32_dense(o_part, (B, Sq, Hq, D), "o_part")
@@ -253,6 +276,8 @@ def st_attn_block_fwd(q, k, v, q_offset: int, k_offset: int, causal: bool, scale
 
 
 def st_attn_merge(o_acc, lse_acc, o_part, lse_part, out_dtype: int = ST_F32, o_out_lowp=None, stream=None) -> None:
+    if _done(_binding.merge(o_acc, lse_acc, o_part, lse_part, out_dtype, o_out_lowp, _raw_stream(stream)), "st_attn_merge"):
+        return
     B, Sq, Hq, D = o_acc.shape
     _f32_dense(o_acc, (B, Sq, Hq, D), "o_acc"); _f32_dense(o_part, (B, Sq, Hq, D), "o_part")
     _f32_dense(lse_acc, (B, Hq, Sq), "lse_acc"); _f32_dense(lse_part, (B, Hq, Sq), "lse_part")
@@ -266,6 +291,9 @@ def st_attn_merge(o_acc, lse_acc, o_part, lse_part, out_dtype: int = ST_F32, o_o
 def st_attn_combine(o_parts, lse_parts, row0: int = 0, Sq_out: int = None, out_dtype: int = ST_F32, o_out=None,
                     lse_out=None, o_out_lowp=None, stream=None):
     """n partial states of the same rows -> (o_out, lse_out) of rows [row0, row0 + Sq_out)."""
+    if o_out is not None and lse_out is not None and \
+            _done(_binding.combine(o_parts, lse_parts, row0, Sq_out, out_dtype, o_out, lse_out, o_out_lowp, _raw_stream(stream)), "st_attn_combine"):
+        return o_out, lse_out
     n = len(o_parts)
     if n == 0 or len(lse_parts) != n:
         raise ValueError("need as many lse_parts as o_parts, at least one")
@@ -290,6 +318,8 @@ def st_attn_combine(o_parts, lse_parts, row0: int = 0, Sq_out: int = None, out_d
 
 
 def st_attn_delta(d_o, o, delta=None, stream=None) -> torch.Tensor:
+    if delta is not None and _done(_binding.delta(d_o, o, delta, _raw_stream(stream)), "st_attn_delta"):
+        return delta
     B, Sq, Hq, D = d_o.shape
     delta = torch.empty((B, Hq, Sq), dtype=torch.float32, device=d_o.device) if delta is None else \
         _f32_dense(delta, (B, Hq, Sq), "delta")
@@ -309,6 +339,10 @@ def st_attn_block_bwd(q, k, v, d_o, lse_final, delta, q_offset: int, k_offset: i
                       dq_acc, dk_acc, dv_acc, stream=None, workspace=None) -> None:
     """workspace: a uint8 tensor of st_attn_block_bwd_workspace_bytes(...) bytes, None to have one allocated, or
     False to pass none (the C call then keeps the dK/dV work in its general kernel)."""
+    if workspace is not None and workspace is not False and \
+            _done(_binding.block_bwd(q, k, v, d_o, lse_final, delta, q_offset, k_offset, causal, scale, dq_acc, dk_acc, dv_acc, workspace,
+                                     _raw_stream(stream)), "st_attn_block_bwd"):
+        return
     B, Sq, Hq, D = q.shape
     Sk, Hkv = k.shape[1], k.shape[2]
     _f32_dense(lse_final, (B, Hq, Sq), "lse_final"); _f32_dense(delta, (B, Hq, Sq), "delta")
@@ -328,6 +362,8 @@ def st_attn_block_bwd(q, k, v, d_o, lse_final, delta, q_offset: int, k_offset: i
 
 
 def st_cast_from_f32(src, dst_dtype: int, dst=None, stream=None) -> torch.Tensor:
+    if dst is not None and _done(_binding.cast(src, dst, dst_dtype, _raw_stream(stream)), "st_cast_from_f32"):
+        return dst
     if src.dtype != torch.float32 or not src.is_contiguous():
         raise ValueError("src must be contiguous fp32")
     dst = torch.empty(src.shape, dtype=_torch_dtype(dst_dtype), device=src.device) if dst is None else dst
@@ -401,6 +437,10 @@ def st_ring_fwd(q, k_chunks, v_chunks, q_offset: int, k_offsets: Sequence[int], 
                 order: Sequence[int], member_of: Optional[Sequence[int]] = None, mode: int = ST_RING_FUSED,
                 o_acc=None, lse=None, o_lowp=None, want_lowp: bool = True, workspace=None, stream=None):
     """Returns (o_acc fp32, lse fp32, o_lowp or None)."""
+    if o_acc is not None and lse is not None and workspace is not None and (o_lowp is not None or not want_lowp) and \
+            _done(_binding.ring_fwd(q, k_chunks, v_chunks, q_offset, k_offsets, causal, scale, order, member_of, mode, o_acc, lse, o_lowp,
+                                    workspace, _raw_stream(stream)), "st_ring_fwd"):
+        return o_acc, lse, o_lowp
     B, Sq, Hq, D = q.shape
     r = _Ring(q, k_chunks, v_chunks, q_offset, k_offsets, causal, scale)
     o_acc = torch.empty((B, Sq, Hq, D), dtype=torch.float32, device=q.device) if o_acc is None else \
@@ -425,6 +465,10 @@ def st_ring_bwd(q, k_chunks, v_chunks, d_o, o, lse_final, q_offset: int, k_offse
                 scale: float, order: Sequence[int], dq_acc, dk_acc: Sequence[Optional[torch.Tensor]],
                 dv_acc: Sequence[Optional[torch.Tensor]], mode: int = ST_RING_FUSED, workspace=None,
                 stream=None) -> None:
+    if workspace is not None and \
+            _done(_binding.ring_bwd(q, k_chunks, v_chunks, d_o, o, lse_final, q_offset, k_offsets, causal, scale, order, dq_acc, dk_acc,
+                                    dv_acc, False, None, None, mode, workspace, _raw_stream(stream)), "st_ring_bwd"):
+        return
     B, Sq, Hq, D = q.shape
     r = _Ring(q, k_chunks, v_chunks, q_offset, k_offsets, causal, scale)
     n = len(k_chunks)
@@ -455,6 +499,9 @@ def st_ring_bwd_noalloc(q, k_chunks, v_chunks, d_o, o, lse_final, q_offset: int,
                         scale: float, order: Sequence[int], dq_acc, dk_acc: Sequence[Optional[torch.Tensor]],
                         dv_acc: Sequence[Optional[torch.Tensor]], mode: int = ST_RING_FUSED, stream=None) -> None:
     """st_ring_bwd on the library's static scratch: this wrapper allocates no device memory either."""
+    if _done(_binding.ring_bwd(q, k_chunks, v_chunks, d_o, o, lse_final, q_offset, k_offsets, causal, scale, order, dq_acc, dk_acc, dv_acc,
+                               False, None, None, mode, None, _raw_stream(stream)), "st_ring_bwd_noalloc"):
+        return
     B, Sq, Hq, D = q.shape
     r = _Ring(q, k_chunks, v_chunks, q_offset, k_offsets, causal, scale)
     n = len(k_chunks)
@@ -478,6 +525,10 @@ def st_ring_bwd_last(q, k_chunks, v_chunks, d_o, o, lse_final, q_offset: int, k_
                      dk_lowp: Optional[Sequence[Optional[torch.Tensor]]] = None,
                      dv_lowp: Optional[Sequence[Optional[torch.Tensor]]] = None, mode: int = ST_RING_FUSED,
                      workspace=None, stream=None) -> None:
+    if workspace is not None and \
+            _done(_binding.ring_bwd(q, k_chunks, v_chunks, d_o, o, lse_final, q_offset, k_offsets, causal, scale, order, dq_acc, dk_acc,
+                                    dv_acc, assign, dk_lowp, dv_lowp, mode, workspace, _raw_stream(stream)), "st_ring_bwd_last"):
+        return
     B, Sq, Hq, D = q.shape
     r = _Ring(q, k_chunks, v_chunks, q_offset, k_offsets, causal, scale)
     n = len(k_chunks)

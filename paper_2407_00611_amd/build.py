@@ -1,4 +1,4 @@
-"""Builds libstartrail.so (gfx950) in-tree with hipcc.
+"""Builds libstartrail.so (gfx950) in-tree with hipcc, and _binding.so, the native half of the Python wrapper, with g++.
 
     python paper_2407_00611_amd/build.py      (run as a script: importing the package needs the built library)
 
@@ -9,11 +9,13 @@ from __future__ import annotations
 import os
 import subprocess
 import sys
+import sysconfig
 from concurrent.futures import ThreadPoolExecutor
 
 PKG = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(PKG, "csrc")
 OUT = os.path.join(PKG, "libstartrail.so")
+BINDING = os.path.join(PKG, "_binding.so")
 OBJ_DIR = os.path.join(PKG, "_build")
 
 SOURCES = ["st_api.cpp", "st_runtime.cpp", "st_f32.hip", "st_elementwise.hip", "st_fwd_bf16.hip", "st_bwd_bf16.hip", "st_bwd_dkv_fast.hip", "st_bwd_dq_fast.hip", "st_fwd_fast.hip", "st_probe.hip"]
@@ -43,6 +45,19 @@ def _compile(src: str) -> str:
     return obj
 
 
+def _build_binding() -> None:
+    """Host code only: torch's and Python's headers, and the C ABI of the library next to it."""
+    import torch
+    root = os.path.dirname(torch.__file__)
+    cmd = ["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-fvisibility=hidden", f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}",
+           "-isystem", os.path.join(root, "include"), "-isystem", os.path.join(root, "include", "torch", "csrc", "api", "include"),
+           "-isystem", sysconfig.get_paths()["include"], os.path.join(CSRC, "st_binding.cpp"), "-o", BINDING, "-L" + PKG, "-lstartrail",
+           "-L" + os.path.join(root, "lib"), "-ltorch_python", "-ltorch_cpu", "-lc10", "-Wl,-rpath,$ORIGIN"]
+    r = subprocess.run(cmd, capture_output=True, text=True)
+    if r.returncode != 0:
+        raise RuntimeError(f"g++ failed for st_binding.cpp:\n{r.stdout}\n{r.stderr}")
+
+
 def build(verbose: bool = True) -> str:
     os.makedirs(OBJ_DIR, exist_ok=True)
     for script, out in GENERATED:
@@ -58,6 +73,7 @@ def build(verbose: bool = True) -> str:
     r = subprocess.run(cmd, capture_output=True, text=True)
     if r.returncode != 0:
         raise RuntimeError(f"link failed:\n{r.stdout}\n{r.stderr}")
+    _build_binding()
     if verbose:
         print(f"built {OUT}")
     return OUT
