@@ -28,11 +28,14 @@ thread_local char g_err[512] = "";
 // ---- scratch of st_ring_bwd_noalloc: device memory every loaded GPU holds until the process ends ----
 // In host code the array's name is only a handle: its device address differs from GPU to GPU and is looked up
 // once per device with hipGetSymbolAddress (scratch_of_current_device); kernels only ever see that pointer.
-constexpr size_t kScratchBytes = (size_t)40 << 20;
+// Partial sums of under-filled launches have an array of their own, as large as a ring backward ever uses (kPartsMost): what a
+// call gets beside it must not depend on how much of the 40 MiB its Delta and Q' leave.
+constexpr size_t kScratchBytes = (size_t)40 << 20, kPartsMost = (size_t)64 << 20;
 static __device__ __align__(256) unsigned char scratch[kScratchBytes];
+static __device__ __align__(256) unsigned char scratch_parts[kPartsMost];
 constexpr int kScratchDevices = 64;
 std::mutex g_scratch_mu;
-void* g_scratch_ptr[kScratchDevices];
+void* g_scratch_ptr[kScratchDevices][2];
 
 st_status fail(st_status s, const char* fmt, ...) {
   va_list ap;
@@ -46,21 +49,25 @@ st_status hip_fail(hipError_t e, const char* what) {
   return fail(ST_ERR_HIP, "%s: %s", what, hipGetErrorString(e));
 }
 
-// Device address of `scratch` on the current device (looked up on the first call per device, then cached).
-st_status scratch_of_current_device(void** out) {
+// Device addresses of `scratch` and `scratch_parts` on the current device (looked up on the first call per device, then cached).
+st_status scratch_of_current_device(void** out, void** parts) {
   int dev = 0;
   hipError_t e = hipGetDevice(&dev);
   if (e != hipSuccess) return hip_fail(e, "hipGetDevice");
   if (dev < 0 || dev >= kScratchDevices) return fail(ST_ERR_UNSUPPORTED, "device index %d beyond %d", dev, kScratchDevices - 1);
   std::lock_guard<std::mutex> lk(g_scratch_mu);
-  if (g_scratch_ptr[dev] == nullptr) {
-    void* p = nullptr;
+  if (g_scratch_ptr[dev][0] == nullptr) {
+    void *p = nullptr, *q = nullptr;
     e = hipGetSymbolAddress(&p, HIP_SYMBOL(scratch));
+    if (e == hipSuccess) e = hipGetSymbolAddress(&q, HIP_SYMBOL(scratch_parts));
     if (e != hipSuccess) return hip_fail(e, "hipGetSymbolAddress(scratch)");
-    if (p == nullptr || reinterpret_cast<uintptr_t>(p) % 256) return fail(ST_ERR_HIP, "scratch symbol has no aligned device address");
-    g_scratch_ptr[dev] = p;
+    for (void* x : {p, q})
+      if (x == nullptr || reinterpret_cast<uintptr_t>(x) % 256) return fail(ST_ERR_HIP, "scratch symbol has no aligned device address");
+    g_scratch_ptr[dev][0] = p;
+    g_scratch_ptr[dev][1] = q;
   }
-  *out = g_scratch_ptr[dev];
+  *out = g_scratch_ptr[dev][0];
+  *parts = g_scratch_ptr[dev][1];
   return ST_OK;
 }
 
@@ -220,6 +227,62 @@ QueryWalk query_walk(const st::Shape& s, int dtype, const int64_t* k_offset, int
   return w;
 }
 
+// Time of a workgroup: what stands around its walk, and a unit of it.  Both grow with the workgroups that run beside it: they
+// share the memory that results are written to, and the more of the chip works, the lower its clock.
+struct Cost {
+  double fixed_us, unit_us, fixed_full, unit_full;     // of one alone, and what is added on a full chip
+  double us(double units, int64_t workgroups) const {
+    const double f = (double)std::min<int64_t>(workgroups, kPlanCus) / kPlanCus;
+    return fixed_us + f * fixed_full + units * (unit_us + f * unit_full);
+  }
+};
+// Measured on 32 to 256 workgroups with walks of 4 to 128 units, kernels back to back.  Forward, a 256 x 64 tile; dQ, the same (three contractions
+// instead of two); dK/dV, 256 keys x 32 rows of one head.  fp32: a turn (see f32_turns).
+Cost fwd_cost(int dtype, int D) {
+  if (dtype != ST_BF16) return Cost{5 + 0.035 * D, 2 + (D <= 128 ? 0.065 : 0.034) * D, 0, 0};
+  return D == 128 ? Cost{16, 1.05, 0, 0.45} : Cost{11, 0.75, 0, 0.2};
+}
+Cost dq_cost(int dtype, int D) {
+  if (dtype != ST_BF16) return Cost{10, 2 + (D <= 128 ? 0.11 : 0.055) * D, 0, 0};
+  return D == 128 ? Cost{20, 1.45, 0, 0.35} : Cost{14, 0.95, 0, 0.25};
+}
+Cost dkv_cost(int D) { return D == 128 ? Cost{17, 0.9, 5, 0.25} : Cost{14, 0.68, 3, 0.2}; }
+
+// Time of a launch of so many workgroups each: handed out in this order, each to the compute unit that is free first (one holds
+// one).  Stops where it is beyond `most`.
+struct Job {
+  double us;
+  int64_t n;
+};
+double jobs_us(const Job* job, int n, double most = 1e30) {
+  struct Group { double us; int64_t n; };
+  constexpr int kGroups = 64;
+  Group cu[kGroups];                                  // free first, free last
+  int groups = 1;
+  cu[0] = Group{0, kPlanCus};
+  double end = 0;
+  for (int i = 0; i < n; ++i)
+    for (int64_t left = job[i].n; left > 0;) {
+      const int64_t take = std::min(left, cu[0].n);
+      const double us = cu[0].us + job[i].us;
+      end = std::max(end, us);
+      if (end >= most) return end;
+      left -= take;
+      if (take == cu[0].n) std::copy(cu + 1, cu + groups--, cu);
+      else cu[0].n -= take;
+      int at = groups;
+      while (at > 0 && cu[at - 1].us >= us) --at;
+      if ((at < groups && cu[at].us < us + 0.5) || groups == kGroups) {
+        cu[std::min(at, groups - 1)].n += take;       // as good as at the same time
+        continue;
+      }
+      std::copy_backward(cu + at, cu + groups, cu + groups + 1);
+      cu[at] = Group{us, take};
+      ++groups;
+    }
+  return end;
+}
+
 // A way to split the tiles of a walk into shares of at most `each` units.
 struct Split {
   const QueryWalk* w;
@@ -245,38 +308,18 @@ struct Split {
     for (int i = 0; i < w->n; ++i) most = std::max(most, (w->units[i] + shares(i) - 1) / shares(i));
     return most;
   }
-  // Time of the launch: workgroups handed out longest first, each to the compute unit that is free first (one holds one).
-  double launch_us(double fixed_us, double unit_us) const {
-    if (workgroups() <= kPlanCus) return fixed_us + longest() * unit_us;
-    if (w->n == 1) return (double)((workgroups() + kPlanCus - 1) / kPlanCus) * (fixed_us + longest() * unit_us);
-    struct Group { double us; int64_t n; };
-    Group job[st::kShareTiles], cu[2 * st::kShareTiles + 8];
-    for (int i = 0; i < w->n; ++i) job[i] = Group{fixed_us + (double)((w->units[i] + shares(i) - 1) / shares(i)) * unit_us, w->heads * shares(i)};
-    std::sort(job, job + w->n, [](const Group& x, const Group& y) { return x.us > y.us; });
-    int groups = 1;
-    cu[0] = Group{0, kPlanCus};
-    double end = 0;
-    for (int i = 0; i < w->n; ++i) {
-      for (int64_t left = job[i].n; left > 0;) {
-        const int64_t take = std::min(left, cu[0].n);
-        const double us = cu[0].us + job[i].us;
-        end = std::max(end, us);
-        left -= take;
-        if (take == cu[0].n) std::copy(cu + 1, cu + groups--, cu);
-        else cu[0].n -= take;
-        int at = groups;
-        while (at > 0 && cu[at - 1].us >= us) --at;
-        if (at < groups && cu[at].us == us) {
-          cu[at].n += take;
-          continue;
-        }
-        if (groups == (int)(sizeof(cu) / sizeof(cu[0]))) return end + job[i].us;      // (not reached: a job splits one group)
-        std::copy_backward(cu + at, cu + groups, cu + groups + 1);
-        cu[at] = Group{us, take};
-        ++groups;
-      }
-    }
-    return end;
+  // its workgroups as jobs, longest first, beside `others`; returns their number
+  int jobs(Job* to, const Cost& cost, int64_t others = 0) const {
+    for (int i = 0; i < w->n; ++i)
+      to[i] = Job{cost.us((w->units[i] + shares(i) - 1) / shares(i), others + workgroups()), w->heads * shares(i) * (w->n == 1 ? w->tiles : 1)};
+    std::sort(to, to + w->n, [](const Job& x, const Job& y) { return x.us > y.us; });
+    return w->n;
+  }
+  double longest_us(const Cost& cost, int64_t others = 0) const { return cost.us(longest(), others + workgroups()); }
+  double launch_us(const Cost& cost) const {
+    if (workgroups() <= kPlanCus) return longest_us(cost);
+    Job job[st::kShareTiles];
+    return jobs_us(job, jobs(job, cost));
   }
   st::TileShares table(bool own0) const {
     st::TileShares t;
@@ -311,41 +354,93 @@ void each_split(const QueryWalk& w, int most, F f) {
 // takes (the two passes run one after the other and share them).
 struct BwdSplit {
   st::TileShares dq = {};
-  int kv = 1;
+  int kv_each = 0, kv_items = 0;
   bool pair = false;
-  size_t bytes = 0;
+  size_t dq_bytes = 0, bytes = 0;
 };
 // dQ: the forward's model (the launch + the pass that adds up); a 256 x 64 tile is three contractions instead of two: 1.7 us at
 // head size 128, 1.05 at 64, behind 14 and 11 us.  fp32: the eight (four beyond head size 128) wavefronts of a workgroup take a
 // 32-key tile each in 16 us at head size 128, 9 at 64, 5.5 at 32, and 16 at 256 (8 heads x 512 rows x 8 chunks of 512 keys at
 // head size 128: 128 workgroups, 270 us; 157 us as two shares each and the adding pass); 10 us for the adding pass, as walks
 // of two turns gain less than its launch takes.
-// dK/dV: a step (256 keys x 32 rows of one head) is 1.2 us at head size 128 and 0.75 at 64, prologue and epilogue 20 and 14;
-// grouped heads make the walk long and the key tiles few (4096 x 4096, 32/8 heads: 128 workgroups of 512 steps on 256
-// compute units, 570 us; 310 us as two shares of 256 steps and a 25 us pass).  512 tiles and more go through the queue.
-// A causal launch whose key tiles meet less than three quarters of the query blocks on average (the diagonal chunk alone
-// meets half of them) is planned as one of half the work: not rounds of equal workgroups, but the longest one, or all of
-// them spread evenly, whichever takes longer.
-bool bwd_half(const st::Shape& s, const int64_t* k_offset, int n) {
-  const int64_t blocks = (s.Sq + st::kDkvFastRows - 1) / st::kDkvFastRows;
-  const int64_t tiles = (s.Sk + st::kDkvFastKeys - 1) / st::kDkvFastKeys;
-  if (!s.causal || (int64_t)s.B * s.Hkv * n * tiles >= 512) return false;
-  int64_t sum = 0;
-  for (int c = 0; c < n; ++c)
-    for (int64_t t = 0; t < tiles; ++t) sum += blocks - st::q_row_of(s, k_offset[c] + t * st::kDkvFastKeys) / st::kDkvFastRows;
-  return 4 * sum < 3 * (int64_t)n * tiles * blocks;
+// dK/dV: the key tiles that some row sees, by the query blocks they meet (under a causal mask the diagonal chunk's meet half of
+// them, two runs of rows have chunks that only one run sees).  Few and long walks are split into shares of one size, so the
+// launch does not wait for the longest; a tile that no row sees is written or skipped in 4 us.  24/3 heads x 1601 rows, first
+// of two chunks: 21 tiles of up to 51 blocks x 8 heads, 130 us in equal numbers of shares and 61 of dQ; now 98 together.
+// From 512 tiles on that some row sees, they go through the queue.
+struct KeyWalk {
+  int64_t heads = 0;     // B Hkv
+  int tiles = 0;         // per head, over all chunks
+  int G = 1, top = 0, seen = 0;     // heads per group, most blocks of a tile, tiles that meet some
+  int n = 0;
+  struct Class { int blocks, tiles; } c[512];   // tiles by the blocks they meet
+};
+void key_walk(KeyWalk& w, const st::Shape& s, const int64_t* k_offset, int n) {
+  const int n_kt = (s.Sk + st::kDkvFastKeys - 1) / st::kDkvFastKeys, all = (s.Sq + st::kDkvFastRows - 1) / st::kDkvFastRows;
+  w.heads = (int64_t)s.B * s.Hkv;
+  w.tiles = n_kt * n;
+  w.G = s.Hq / s.Hkv;
+  w.n = 0;
+  auto add = [&](int blocks, int tiles) {
+    w.top = std::max(w.top, blocks);
+    if (blocks > 0) w.seen += tiles;
+    for (int i = 0; i < w.n; ++i)
+      if (w.c[i].blocks == blocks) {
+        w.c[i].tiles += tiles;
+        return;
+      }
+    if (w.n < (int)(sizeof(w.c) / sizeof(w.c[0]))) w.c[w.n++] = KeyWalk::Class{blocks, tiles};
+    else w.c[w.n - 1].tiles += tiles;
+  };
+  const int64_t first = st::q_pos(s, 0), last = st::q_pos(s, s.Sq - 1);
+  for (int c = 0; c < n; ++c) {
+    if (!s.causal || k_offset == nullptr || k_offset[c] + s.Sk - 1 <= first) add(all, n_kt);
+    else if (k_offset[c] > last) add(0, n_kt);
+    else
+      for (int kt = 0; kt < n_kt; ++kt) add(st::kv_blocks(s, k_offset[c], kt), 1);
+  }
+  std::sort(w.c, w.c + w.n, [](const KeyWalk::Class& x, const KeyWalk::Class& y) { return x.blocks > y.blocks; });
 }
-BwdSplit bwd_splits(const st::Shape& s, int dtype, const int64_t* k_offset, int n, bool half, size_t room, bool split_dq = true) {
+// shares of at most `each` blocks (0: unsplit)
+struct KeySplit {
+  const KeyWalk* w;
+  int each, longest = 0;        // blocks of the longest share
+  int64_t items = 0, slots = 0, split_tiles = 0;   // of a head: shares, shares that store partial sums, tiles with some
+  KeySplit(const KeyWalk& walk, int blocks) : w(&walk), each(blocks) {
+    for (int i = 0; i < w->n; ++i) {
+      const int x = st::kv_shares(w->c[i].blocks, each);
+      items += (int64_t)x * w->c[i].tiles;
+      slots += (int64_t)(x - 1) * w->c[i].tiles;
+      if (x > 1) split_tiles += w->c[i].tiles;
+      longest = std::max(longest, (w->c[i].blocks + x - 1) / x);
+    }
+  }
+  int64_t workgroups() const { return w->heads * (items - (w->tiles - w->seen)); }       // that have something to do
+  double longest_us(const Cost& cost, int64_t others = 0) const { return cost.us(longest * w->G, others + workgroups()); }
+  int jobs(Job* to, const Cost& cost, int64_t others = 0) const {
+    for (int i = 0; i < w->n; ++i) {
+      const int x = st::kv_shares(w->c[i].blocks, each);
+      to[i] = Job{w->c[i].blocks > 0 ? cost.us((w->c[i].blocks + x - 1) / x * w->G, others + workgroups()) : 4.0, w->heads * w->c[i].tiles * x};
+    }
+    return w->n;
+  }
+};
+// Both passes in one launch: the compute units that have no key tile, or are done with theirs, take shares of the dQ pass
+// meanwhile, and the launch ends with the last of them (jobs_us, key tiles first).  Forward and backward, apart and together:
+// 4 heads x 700 rows x 4 chunks 99 and 77 us, 12 heads of 64 x 800 rows x 4 chunks 96 and 88 us, 6 heads x 1500 rows x 4
+// chunks 146 and 116 us.
+BwdSplit bwd_splits(const st::Shape& s, int dtype, const int64_t* k_offset, int n, size_t room, bool split_dq = true) {
   BwdSplit r;
   const bool bf16 = dtype == ST_BF16;
   if ((bf16 && s.D != 128 && s.D != 64) || n < 1 || n > st::kMaxTable || s.B < 1 || s.Sq < 1 || s.Sk < 1 || s.Hq < 1 || s.Hkv < 1) return r;
-  const bool d128 = s.D == 128;
   QueryWalk walk;
   const int64_t wgs = (int64_t)s.B * s.Hq * st::query_tiles(s, bf16 ? st::kQTileFastRows : 32).count();
-  const bool plan_dq = split_dq && wgs < 512 && (!bf16 || s.Sk >= st::kQTileFastKeys);
-  const double unit_us = bf16 ? (d128 ? 1.7 : 1.05) : 2 + (s.D <= 128 ? 0.11 : 0.055) * s.D, dq_fixed_us = bf16 ? (d128 ? 14 : 11) : 10, add_us = bf16 ? 6 : 10;
+  const bool plan_dq = wgs < 1024 && (!bf16 || s.Sk >= st::kQTileFastKeys);
+  split_dq = split_dq && wgs < 512;
+  const Cost cost = dq_cost(dtype, s.D);
+  const double add_us = bf16 ? 6 : 10;
   const size_t row_bytes = (size_t)s.B * s.Hq * s.D * sizeof(float);
-  auto part_us = [&](int64_t rows) { return (double)(row_bytes * rows) / 4e6; };
+  auto part_us = [&](int64_t rows) { return (double)(row_bytes * rows) / 8e6; };
   auto fits = [&](const Split& x) { return (size_t)x.rows_own0 * row_bytes <= room; };
   auto set_dq = [&](const Split& x) {
     const bool own0 = (size_t)x.rows * row_bytes > room;
@@ -357,12 +452,12 @@ BwdSplit bwd_splits(const st::Shape& s, int dtype, const int64_t* k_offset, int 
   if (plan_dq) {
     walk = query_walk(s, dtype, k_offset, n);
     dq_units = walk.most();
-    double best = Split(walk, dq_units).launch_us(dq_fixed_us, unit_us);
-    each_split(walk, kMaxSplits, [&](const Split& x) {
+    double best = Split(walk, dq_units).launch_us(cost);
+    if (split_dq) each_split(walk, kMaxSplits, [&](const Split& x) {
       if (!fits(x)) return;
       const double add = add_us + more_than_8_us(x) + part_us(x.rows + 2 * s.Sq);
-      if (dq_fixed_us + x.longest() * unit_us + add >= 0.95 * best) return;
-      const double t = x.launch_us(dq_fixed_us, unit_us) + add;
+      if (x.longest_us(cost) + add >= 0.95 * best) return;
+      const double t = x.launch_us(cost) + add;
       if (t < 0.95 * best) {
         best = t;
         set_dq(x);
@@ -370,61 +465,84 @@ BwdSplit bwd_splits(const st::Shape& s, int dtype, const int64_t* k_offset, int 
     });
     dq_us = best;
   }
-  const int64_t key_tiles = (int64_t)s.B * s.Hkv * n * ((s.Sk + st::kDkvFastKeys - 1) / st::kDkvFastKeys);
-  if (bf16 && key_tiles < 512) {
-    const int64_t blocks = (s.Sq + st::kDkvFastRows - 1) / st::kDkvFastRows, G = s.Hq / s.Hkv;
-    const size_t kv = 2 * (size_t)n * st::kv_part_floats(s) * sizeof(float);
-    const double step_us = d128 ? 1.2 : 0.75, fixed_us = d128 ? 20 : 14;
-    auto launch_us = [&](int x) {
-      const double one = fixed_us + (double)((blocks + x - 1) / x) * G * step_us;
-      if (!half) return (double)((key_tiles * x + 255) / 256) * one;
-      const double even = (double)key_tiles * (x * fixed_us + 0.5 * blocks * G * step_us) / 256;
-      return one > even ? one : even;
-    };
-    double best = launch_us(1);
-    for (int x = 2; x <= kMaxSplits && x <= blocks && (size_t)(x - 1) * kv <= room; ++x) {
-      const double t = launch_us(x) + 6 + 2 * x * (double)kv / 4e6;
-      if (t < 0.95 * best) {
-        best = t;
-        r.kv = x;
-        if ((size_t)(x - 1) * kv > r.bytes) r.bytes = (size_t)(x - 1) * kv;
-      }
-    }
-    // Both passes in one launch: the compute units that have no key tile, or one less than others, take shares of the dQ
-    // pass meanwhile.  The launch ends at the first time by which all shares fit in; only multiples of a share's time from
-    // where a compute unit is done with its key tiles come into question.  Forward and backward, apart and together: 4 heads x
-    // 700 rows x 4 chunks 99 and 77 us, 12 heads of 64 x 800 rows x 4 chunks 96 and 88 us, 6 heads x 1500 rows x 4 chunks 146
-    // and 116 us.  Launches of 512 key tiles and more (the queue) and split key tiles fill the chip by themselves.
-    if (r.kv == 1 && dq_units > 6) {
-      const double one = fixed_us + (double)(blocks * G) * step_us;
-      const int64_t late_cus = key_tiles % 256;            // have a key tile more than the others
-      const double early = (double)(key_tiles / 256) * one, late = early + one, end = late_cus ? late : early;
-      double least = 0.95 * (best + 4 + dq_us);
-      auto together = [&](const Split& x) {
-        if (!fits(x)) return;
-        const double share = dq_fixed_us + (double)x.longest() * unit_us, add = x.n > 1 ? add_us + more_than_8_us(x) + part_us(x.rows + 2 * s.Sq) : 0;
-        for (int j = 1; early + j * share + add < least; ++j)
-          for (const double from : {early, late}) {
-            const double t = std::max(end, from + j * share);
-            const int64_t fit = (256 - late_cus) * (int64_t)((t - early) / share + 1e-6) + late_cus * (int64_t)(std::max(t - late, 0.0) / share + 1e-6);
-            if (t + add >= least || fit < x.workgroups()) continue;
-            least = t + add;
-            r.pair = true;
-            set_dq(x);
-          }
-      };
-      together(Split(walk, dq_units));
-      each_split(walk, kMaxSplits, together);
+  if (!bf16) return r;
+  KeyWalk keys;
+  key_walk(keys, s, k_offset, n);
+  if (keys.seen < 1 || keys.heads * keys.seen >= 512 || keys.tiles > 32767) return r;
+  const Cost kv_cost = dkv_cost(s.D);
+  auto slot_bytes = [&](const KeySplit& x) { return (size_t)(keys.heads * x.slots * st::kv_slot_floats(s)) * sizeof(float); };
+  // the adding pass reads the sums and reads and writes the gradients; only the keys a tile has are there, of the last tile of a
+  // chunk often few.  What fits the L2 caches comes at some 16 TB/s, the rest at 5.
+  const double tile_bytes = (double)keys.heads * 2 * s.Sk / ((s.Sk + st::kDkvFastKeys - 1) / st::kDkvFastKeys) * s.D * sizeof(float);
+  auto add_kv_us = [&](const KeySplit& x) {
+    const double bytes = tile_bytes * (x.slots + 2 * x.split_tiles), in_l2 = std::min(bytes, 16e6);
+    return x.slots > 0 ? 6 + in_l2 / 16e6 + (bytes - in_l2) / 5e6 : 0.0;
+  };
+  Job job[512 + st::kShareTiles];
+  const KeySplit whole(keys, 0);
+  KeySplit kv = whole;
+  double kv_us = jobs_us(job, whole.jobs(job, kv_cost));
+  for (int k = 2, before = keys.top; k <= st::kKvSharesMost && k <= keys.top; ++k) {
+    const int each = (keys.top + k - 1) / k;
+    if (each == before) continue;
+    before = each;
+    const KeySplit x(keys, each);
+    if (slot_bytes(x) > room || keys.heads * x.items > 4 * kPlanCus) break;
+    const double add = add_kv_us(x);
+    const double less = (kv.each > 0 ? 0.97 : 0.95) * kv_us;     // more workgroups have to be worth it
+    if (x.longest_us(kv_cost) + add >= less) continue;
+    const double us = add + jobs_us(job, x.jobs(job, kv_cost), less - add);
+    if (us < less) {
+      kv_us = us;
+      kv = x;
     }
   }
+  size_t dq_bytes = r.bytes;
+  if (plan_dq && dq_units > 6) {
+    double least = 0.95 * (kv_us + 4 + dq_us);
+    KeySplit pair_kv = kv;
+    auto together = [&](const KeySplit& y, const Split& x) {
+      const size_t left = room - slot_bytes(y);
+      if (x.n > 1 && (size_t)x.rows_own0 * row_bytes > left) return;
+      const double add = (x.n > 1 ? add_us + more_than_8_us(x) + part_us(x.rows + 2 * s.Sq) : 0) + add_kv_us(y);
+      if (x.longest_us(cost, y.workgroups()) + add >= least) return;
+      const int m = y.jobs(job, kv_cost, x.workgroups());
+      const double us = add + jobs_us(job, m + x.jobs(job + m, cost, y.workgroups()), least - add);
+      if (us >= least) return;
+      least = us;
+      const bool own0 = x.n > 1 && (size_t)x.rows * row_bytes > left;
+      r.dq = x.table(own0);
+      dq_bytes = x.n > 1 ? (size_t)(own0 ? x.rows_own0 : x.rows) * row_bytes : 0;
+      r.pair = true;
+      pair_kv = y;
+    };
+    for (int split_kv = 0; split_kv <= (kv.each > 0); ++split_kv) {
+      const KeySplit y = split_kv ? KeySplit(keys, kv.each) : whole;
+      together(y, Split(walk, dq_units));
+      if (split_dq) each_split(walk, kMaxSplits, [&](const Split& x) { together(y, x); });
+    }
+    if (r.pair) kv = pair_kv;
+  }
+  r.kv_each = kv.each;
+  r.kv_items = (int)kv.items;
+  r.dq_bytes = dq_bytes;
+  r.bytes = r.pair ? dq_bytes + slot_bytes(kv) : std::max(dq_bytes, slot_bytes(kv));
   return r;
 }
-size_t most_bytes(const BwdSplit& x, const BwdSplit& y) { return x.bytes > y.bytes ? x.bytes : y.bytes; }
+// whether some launch of such a share has too few workgroups (see bwd_splits)
+bool bwd_splittable(const st::Shape& s, int dtype) {
+  if (s.B < 1 || s.Sq < 1 || s.Sk < 1) return false;
+  const bool bf16 = dtype == ST_BF16;
+  const int64_t wgs = (int64_t)s.B * s.Hq * st::query_tiles(s, bf16 ? st::kQTileFastRows : 32).count();
+  return wgs < 512 || (bf16 && (int64_t)s.B * s.Hkv * ((s.Sk + st::kDkvFastKeys - 1) / st::kDkvFastKeys) < 512);
+}
 void set_splits(st::BwdArgs& a, const BwdSplit& x, void* parts) {
   a.shares = x.dq;
-  a.kv_split = (int16_t)x.kv;
+  a.kv_each = x.kv_each;
+  a.kv_items = x.kv_items;
   a.pair = x.pair;
   a.parts = (float*)parts;
+  a.kv_parts = (float*)((char*)parts + (x.pair ? x.dq_bytes : 0));
 }
 void set_table_strides(st::ChunkTable& t, const st_ring_desc* d) {
   t.ksb = d->k_stride_b; t.kss = d->k_stride_s; t.ksh = d->k_stride_h;
@@ -641,12 +759,12 @@ st_status st_attn_delta(const st_block_desc* d, const st_tensor* d_o, const st_t
 // Q' = bf16(Q scale log2 e), then room for the partial sums of an under-filled dK/dV launch (which runs unsplit without it).
 // The dQ of this call is the same with and without a workspace, bit for bit, so that pass is never split here.
 static size_t block_base_bytes(const st_block_desc* d) { return align_up((size_t)d->B * d->Sq * d->Hq * d->D * 2, 256); }
-constexpr size_t kBlockPartsMost = (size_t)64 << 20;
 
 size_t st_attn_block_bwd_workspace_bytes(const st_block_desc* d) {
   if (d == nullptr || d->dtype != ST_BF16 || d->B <= 0 || d->Sq <= 0 || d->Hq <= 0 || d->D <= 0) return 0;
+  // one workspace serves every chunk of a ring: under a causal mask the plan depends on where the chunk lies
   const st::Shape s = shape_of(d);
-  return block_base_bytes(d) + most_bytes(bwd_splits(s, d->dtype, nullptr, 1, false, kBlockPartsMost, false), bwd_splits(s, d->dtype, nullptr, 1, true, kBlockPartsMost, false));
+  return block_base_bytes(d) + (!d->causal ? bwd_splits(s, d->dtype, nullptr, 1, kPartsMost, false).bytes : bwd_splittable(s, d->dtype) ? kPartsMost : 0);
 }
 
 st_status st_attn_block_bwd(const st_block_desc* d, const st_tensor* q, const st_tensor* k, const st_tensor* v,
@@ -684,7 +802,7 @@ st_status st_attn_block_bwd(const st_block_desc* d, const st_tensor* q, const st
     ST_HIP(st::launch_scale_q(a.q, workspace, d->B, d->Sq, d->Hq, d->D, d->scale, (hipStream_t)hip_stream), "scaled-Q launch");
     a.qs = workspace;
     const size_t left = workspace_bytes - block_base_bytes(d);
-    set_splits(a, bwd_splits(a.s, d->dtype, a.t.k_offset, 1, bwd_half(a.s, a.t.k_offset, 1), left < kBlockPartsMost ? left : kBlockPartsMost, false), (char*)workspace + block_base_bytes(d));
+    set_splits(a, bwd_splits(a.s, d->dtype, a.t.k_offset, 1, left < kPartsMost ? left : kPartsMost, false), (char*)workspace + block_base_bytes(d));
   }
   ST_HIP(launch_bwd(d->dtype, a, (hipStream_t)hip_stream), "st_attn_block_bwd launch");
   return ST_OK;
@@ -787,14 +905,14 @@ static st::TileShares fwd_shares(const st_ring_desc* d, const int64_t* k_offset,
   if (!fwd_splittable(d, n_visible)) return r;
   const bool bf16 = d->dtype == ST_BF16;
   const QueryWalk walk = query_walk(shape_of(d), d->dtype, k_offset, n_visible);
-  const double unit_us = bf16 ? (d->D == 128 ? 1.25 : 0.8) : 2 + (d->D <= 128 ? 0.065 : 0.034) * d->D;
-  const double fixed_us = bf16 ? (d->D == 128 ? 12 : 9) : 5 + 0.035 * d->D, combine_us = bf16 ? 6 : 8;
-  const double row_us = (double)d->B * d->Hq * d->D * sizeof(float) / 4e6;
-  double best = Split(walk, walk.most()).launch_us(fixed_us, unit_us);
+  const Cost cost = fwd_cost(d->dtype, d->D);
+  const double combine_us = bf16 ? 6 : 8;
+  const double row_us = (double)d->B * d->Hq * d->D * sizeof(float) / 8e6;
+  double best = Split(walk, walk.most()).launch_us(cost);
   each_split(walk, most, [&](const Split& x) {
     const double add = combine_us + more_than_8_us(x) + (x.rows + 1.5 * d->Sq) * row_us;
-    if (fixed_us + x.longest() * unit_us + add >= 0.95 * best) return;
-    const double t = x.launch_us(fixed_us, unit_us) + add;
+    if (x.longest_us(cost) + add >= 0.95 * best) return;
+    const double t = x.launch_us(cost) + add;
     if (t < 0.95 * best) {
       best = t;
       r = x.table(false);
@@ -839,11 +957,11 @@ static size_t bwd_base_bytes(const st_ring_desc* d) {
          (d->dtype == ST_BF16 ? align_up(n_o / 2, 256) : 0);
 }
 
-// room for partial sums of a ring backward: never more than the static scratch of st_ring_bwd_noalloc has, so that both
-// entry points compute the same sums
+// room for partial sums of a ring backward: never more than st_ring_bwd_noalloc has, so that both entry points compute the
+// same sums
 static size_t ring_room(const st_ring_desc* d, size_t workspace_bytes) {
-  const size_t have = workspace_bytes < kScratchBytes ? workspace_bytes : kScratchBytes, base = bwd_base_bytes(d);
-  return have > base ? have - base : 0;
+  const size_t base = bwd_base_bytes(d);
+  return workspace_bytes > base ? std::min(workspace_bytes - base, kPartsMost) : 0;
 }
 
 size_t st_ring_workspace_bytes(const st_ring_desc* d, int32_t mode, int32_t backward) {
@@ -851,12 +969,12 @@ size_t st_ring_workspace_bytes(const st_ring_desc* d, int32_t mode, int32_t back
   const size_t n_o = align_up((size_t)d->B * d->Sq * d->Hq * d->D * sizeof(float), 256);
   const size_t n_l = align_up((size_t)d->B * d->Sq * d->Hq * sizeof(float), 256);
   if (backward) {
-    // any subset of the chunks may be visited, in one launch or in several
-    const size_t room = ring_room(d, kScratchBytes);
-    if (d->causal) return bwd_base_bytes(d) + room;    // the plan depends on where the chunks lie
+    // any subset of the chunks may be visited, in one launch or in several; under a causal mask the plan depends on where they lie
     size_t most = 0;
-    for (int n = 1; n <= (mode == ST_RING_FUSED ? d->n_chunks : 1) && n <= st::kMaxTable; ++n)
-      most = std::max(most, bwd_splits(shape_of(d), d->dtype, nullptr, n, false, room).bytes);
+    if (d->causal && bwd_splittable(shape_of(d), d->dtype)) most = kPartsMost;
+    else if (!d->causal)
+      for (int n = 1; n <= (mode == ST_RING_FUSED ? d->n_chunks : 1) && n <= st::kMaxTable; ++n)
+        most = std::max(most, bwd_splits(shape_of(d), d->dtype, nullptr, n, kPartsMost).bytes);
     return bwd_base_bytes(d) + most;
   }
   if (mode == ST_RING_STEPWISE) return 2 * (n_o + n_l);
@@ -996,6 +1114,12 @@ st_status st_ring_fwd(const st_ring_desc* d, const st_tensor* q, const int32_t* 
   return ST_OK;
 }
 
+// partial sums in parts_bytes bytes at `parts`
+static st_status ring_bwd(const st_ring_desc* d, const st_tensor* q, const st_tensor* d_o, const st_tensor* o, int32_t o_dtype,
+                          const float* lse_final, const int32_t* order, int32_t n_visit, int32_t mode, float* dq_acc, float* const* dk_acc,
+                          float* const* dv_acc, int32_t kv_flags, void* const* dk_lowp, void* const* dv_lowp, void* workspace,
+                          size_t workspace_bytes, void* parts, size_t parts_bytes, void* hip_stream);
+
 st_status st_ring_bwd(const st_ring_desc* d, const st_tensor* q, const st_tensor* d_o, const st_tensor* o,
                       int32_t o_dtype, const float* lse_final, const int32_t* order, int32_t n_visit, int32_t mode,
                       float* dq_acc, float* const* dk_acc, float* const* dv_acc, void* workspace,
@@ -1012,10 +1136,10 @@ st_status st_ring_bwd_noalloc(const st_ring_desc* d, const st_tensor* q, const s
   const size_t need = bwd_base_bytes(d);               // a split of the dQ pass never needs more than the scratch
   if (need > kScratchBytes)
     return fail(ST_ERR_WORKSPACE, "st_ring_bwd_noalloc: this share needs %zu bytes of scratch, the library's static scratch holds %zu; use st_ring_bwd with a workspace", need, kScratchBytes);
-  void* ws = nullptr;
-  ST_TRY(scratch_of_current_device(&ws));
-  return st_ring_bwd_last(d, q, d_o, o, o_dtype, lse_final, order, n_visit, mode, dq_acc, dk_acc, dv_acc, 0, nullptr,
-                          nullptr, ws, kScratchBytes, hip_stream);
+  void *ws = nullptr, *parts = nullptr;
+  ST_TRY(scratch_of_current_device(&ws, &parts));
+  return ring_bwd(d, q, d_o, o, o_dtype, lse_final, order, n_visit, mode, dq_acc, dk_acc, dv_acc, 0, nullptr, nullptr, ws, kScratchBytes,
+                  parts, kPartsMost, hip_stream);
 }
 
 size_t st_ring_bwd_noalloc_max_bytes(void) { return kScratchBytes; }
@@ -1025,6 +1149,18 @@ st_status st_ring_bwd_last(const st_ring_desc* d, const st_tensor* q, const st_t
                            int32_t mode, float* dq_acc, float* const* dk_acc, float* const* dv_acc, int32_t kv_flags,
                            void* const* dk_lowp, void* const* dv_lowp, void* workspace, size_t workspace_bytes,
                            void* hip_stream) {
+  // partial sums: what the workspace has beyond the rest
+  const size_t room = d == nullptr || workspace == nullptr ? 0 : ring_room(d, workspace_bytes);
+  return ring_bwd(d, q, d_o, o, o_dtype, lse_final, order, n_visit, mode, dq_acc, dk_acc, dv_acc, kv_flags, dk_lowp, dv_lowp, workspace,
+                  workspace_bytes, room > 0 ? (char*)workspace + bwd_base_bytes(d) : nullptr, room, hip_stream);
+}
+
+}  // extern "C"
+
+static st_status ring_bwd(const st_ring_desc* d, const st_tensor* q, const st_tensor* d_o, const st_tensor* o, int32_t o_dtype,
+                          const float* lse_final, const int32_t* order, int32_t n_visit, int32_t mode, float* dq_acc, float* const* dk_acc,
+                          float* const* dv_acc, int32_t kv_flags, void* const* dk_lowp, void* const* dv_lowp, void* workspace,
+                          size_t workspace_bytes, void* parts, size_t parts_bytes, void* hip_stream) {
   ST_TRY(check_ring(d, q, order, n_visit));
   if (mode != ST_RING_STEPWISE && mode != ST_RING_FUSED) return fail(ST_ERR_INVALID_ARG, "unknown mode %d", mode);
   if (o_dtype != ST_F32 && o_dtype != d->dtype) return fail(ST_ERR_INVALID_ARG, "o_dtype must be ST_F32 or the storage dtype");
@@ -1109,7 +1245,7 @@ st_status st_ring_bwd_last(const st_ring_desc* d, const st_tensor* q, const st_t
       a.dk_lowp[x] = dk_lowp ? dk_lowp[j] : nullptr;
       a.dv_lowp[x] = dk_lowp ? dv_lowp[j] : nullptr;
     }
-    set_splits(a, bwd_splits(a.s, d->dtype, a.t.k_offset, cnt, bwd_half(a.s, a.t.k_offset, cnt), ring_room(d, workspace_bytes)), (char*)workspace + bwd_base_bytes(d));
+    set_splits(a, bwd_splits(a.s, d->dtype, a.t.k_offset, cnt, parts_bytes), parts);
     a.kv_assign = assign ? ~0ull : 0ull;
     if (d->dtype != ST_BF16 && assign)              // the fp32 kernels only add
       for (int x = 0; x < cnt; ++x) {
@@ -1120,5 +1256,3 @@ st_status st_ring_bwd_last(const st_ring_desc* d, const st_tensor* q, const st_t
   }
   return ST_OK;
 }
-
-}  // extern "C"

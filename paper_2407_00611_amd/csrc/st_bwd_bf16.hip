@@ -474,15 +474,12 @@ hipError_t launch_bwd_bf16(const BwdArgs& a_in, hipStream_t stream) {
   // head size 64: 11.2 against 8.7, 17.7 against 15.3, 15.6 against 17.7, 61 against 94).  The dK/dV loop is the faster one
   // from the first block on.
   const bool few = a.shares.n <= 1 && (int64_t)a.t.n * ((a.s.Sk + kDqFastKeys - 1) / kDqFastKeys) <= 6;
-  const bool dq_fast = knobs().dq_fast && !few && dq_fast_usable(a), pair = a.pair && dkv_fast && dq_fast && a.kv_split <= 1;
+  const bool dq_fast = knobs().dq_fast && !few && dq_fast_usable(a), pair = a.pair && dkv_fast && dq_fast;
   hipError_t e = hipSuccess;
   if (pair) {
     e = launch_bwd_pair_fast(a, stream);
-    if (e != hipSuccess) return e;
   } else if (dkv_fast) {
     e = launch_bwd_dkv_fast(a, stream);
-    if (e == hipSuccess && a.kv_split > 1) e = launch_add_kv_parts(a, stream);
-    if (e != hipSuccess) return e;
   } else {
     // the general kernel only adds: chunks to be assigned are zeroed first, bf16 copies are launches of their own
     const int64_t n_kv = (int64_t)a.s.B * a.s.Sk * a.s.Hkv * a.s.D;
@@ -502,8 +499,9 @@ hipError_t launch_bwd_bf16(const BwdArgs& a_in, hipStream_t stream) {
       if (a.dk_lowp[c]) e = launch_cast(a.dk[c], a.dk_lowp[c], n_kv, ST_BF16, stream);
       if (e == hipSuccess && a.dv_lowp[c]) e = launch_cast(a.dv[c], a.dv_lowp[c], n_kv, ST_BF16, stream);
     }
-    if (e != hipSuccess) return e;
   }
+  if (e == hipSuccess && dkv_fast && a.kv_each > 0) e = launch_add_kv_parts(a, stream);
+  if (e != hipSuccess) return e;
   if (dq_fast) {
     if (!pair) e = launch_bwd_dq_fast(a, stream);
     if (e == hipSuccess && a.shares.n > 1) e = launch_add_parts(a, kDqFastRows, stream);

@@ -4,6 +4,7 @@
 // One 16-byte vector per lane, rows never straddle a lane; grid sized to the data.
 #include "st_internal.h"
 #include "st_mfma.h"
+#include "st_walk.h"
 
 namespace st {
 namespace {
@@ -341,22 +342,37 @@ __global__ __launch_bounds__(256) void add_parts_kernel(float* dq, float* sums, 
   *dst = x;
 }
 
-__global__ __launch_bounds__(256) void add_kv_parts_kernel(const BwdArgs a, int64_t n_vec) {
-  const int64_t v = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  const int c = blockIdx.y >> 1, w = blockIdx.y & 1;
-  if (v >= n_vec) return;
-  float4* dst = reinterpret_cast<float4*>(w ? a.dv[c] : a.dk[c]);
-  float4 x = dst[v];
-  for (int y = 1; y < a.kv_split; ++y) {
-    const float4 p = reinterpret_cast<const float4*>(a.parts + ((int64_t)(2 * (y - 1) + w) * a.t.n + c) * kv_part_floats(a.s))[v];
-    x.x += p.x;
-    x.y += p.y;
-    x.z += p.z;
-    x.w += p.w;
+// The same for key tiles: blockIdx.y is a key tile of the table (kt fastest), blockIdx.z a head (kv_job's hb), the first half of
+// the blocks in x dK and the other half dV.
+__global__ __launch_bounds__(256) void add_kv_parts_kernel(const BwdArgs a) {
+  const Shape& s = a.s;
+  const int n_kt = (s.Sk + kDkvFastKeys - 1) / kDkvFastKeys, tile = blockIdx.y, c = tile / n_kt, kt = tile - c * n_kt;
+  const KvPlace place = kv_place(s, a.kv_sec, a.kv_each, n_kt, tile, true, threadIdx.x & 63, [&](int x) { return a.t.k_offset[x]; });
+  const int n = place.n_share, slot = blockIdx.z * (a.kv_items - n_kt * a.t.n) + place.slot;
+  if (n <= 1) return;
+  const int vec = s.D / 4, half = gridDim.x / 2, w = (int)blockIdx.x >= half, v = (blockIdx.x - w * half) * 256 + threadIdx.x, row = v / vec;
+  if (row >= min(kDkvFastKeys, s.Sk - kt * kDkvFastKeys)) return;
+  const int hk = blockIdx.z / s.B, b = blockIdx.z % s.B;
+  const int64_t at = ((((int64_t)b * s.Sk + kt * kDkvFastKeys + row) * s.Hkv + hk) * s.D) / 4 + v % vec, slot_vec = kv_slot_floats(s) / 4;
+  const float4* parts = reinterpret_cast<const float4*>(a.kv_parts) + slot * slot_vec + w * kDkvFastKeys * vec + v;
+  float4* dst = reinterpret_cast<float4*>(w ? a.dv[c] : a.dk[c]) + at;
+  float4 x = *dst;
+  for (int y0 = 0; y0 < n - 1; y0 += 8) {
+    float4 p[8];
+#pragma unroll
+    for (int u = 0; u < 8; ++u) p[u] = parts[min(y0 + u, n - 2) * slot_vec];
+#pragma unroll
+    for (int u = 0; u < 8; ++u)
+      if (y0 + u < n - 1) {
+        x.x += p[u].x;
+        x.y += p[u].y;
+        x.z += p[u].z;
+        x.w += p[u].w;
+      }
   }
-  dst[v] = x;
+  *dst = x;
   uint2* low = reinterpret_cast<uint2*>(w ? a.dv_lowp[c] : a.dk_lowp[c]);
-  if (low) low[v] = make_uint2(pack_bf16x2(x.x, x.y), pack_bf16x2(x.z, x.w));
+  if (low) low[at] = make_uint2(pack_bf16x2(x.x, x.y), pack_bf16x2(x.z, x.w));
 }
 
 __global__ __launch_bounds__(256) void fill_state_kernel(float* __restrict__ o, float* __restrict__ lse,
@@ -525,11 +541,14 @@ hipError_t launch_add_parts(const BwdArgs& a, int rows, hipStream_t s) {
   return hipGetLastError();
 }
 
-hipError_t launch_add_kv_parts(const BwdArgs& a, hipStream_t s) {
-  const int64_t n_vec = (int64_t)a.s.B * a.s.Sk * a.s.Hkv * a.s.D / 4;
-  if (n_vec <= 0 || a.t.n <= 0) return hipSuccess;
+hipError_t launch_add_kv_parts(const BwdArgs& a_in, hipStream_t s) {
+  BwdArgs a = a_in;
+  kv_sections(a);
+  const int tiles = (a.s.Sk + kDkvFastKeys - 1) / kDkvFastKeys * a.t.n, heads = a.s.Hkv * a.s.B;
+  if (tiles <= 0 || heads <= 0) return hipSuccess;
+  if (tiles > 65535 || heads > 65535) return hipErrorInvalidValue;    // split launches have fewer than 512 tiles that see rows
   ProfScope prof("add_kv_parts", s);
-  hipLaunchKernelGGL(add_kv_parts_kernel, dim3(blocks_for(n_vec), 2 * a.t.n), dim3(256), 0, s, a, n_vec);
+  hipLaunchKernelGGL(add_kv_parts_kernel, dim3(2 * blocks_for(kDkvFastKeys * a.s.D / 4), tiles, heads), dim3(256), 0, s, a);
   return hipGetLastError();
 }
 

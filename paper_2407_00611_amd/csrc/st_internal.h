@@ -117,6 +117,31 @@ struct FwdArgs {
   float sum_limit;   // fast kernel: sum over a block's probabilities beyond which the lazy exponent reference moves (set by its launcher)
 };
 
+// Tile of the hand-scheduled dK/dV kernel
+constexpr int kDkvFastKeys = 256;
+constexpr int kDkvFastRows = 32;
+// 32-row query blocks with a row that sees some key of key tile kt of a chunk at position k0: the last so many of the shard
+__host__ __device__ inline int kv_blocks(const Shape& s, int64_t k0, int kt) {
+  const int all = (s.Sq + kDkvFastRows - 1) / kDkvFastRows;
+  const int first = s.causal ? q_row_of(s, k0 + (int64_t)kt * kDkvFastKeys) : 0;
+  return first >= s.Sq ? 0 : all - first / kDkvFastRows;
+}
+constexpr int kKvSharesMost = 16;
+// shares of a key tile that meets so many blocks (see BwdArgs::kv_each)
+__host__ __device__ inline int kv_shares(int blocks, int each) {
+  const int n = each > 0 ? (blocks + each - 1) / each : 1;
+  return n < 1 ? 1 : n > kKvSharesMost ? kKvSharesMost : n;
+}
+
+// Runs of key tiles, in table order, that a workgroup finds its tile through without reading the chunks' positions (arguments are
+// in host memory, and a load of them per lane takes 2 us of a launch that may be 20): all tiles of a run have the same
+// number of shares, unless it is `mixed`.  The last run may hold anything.
+struct KvSection {
+  uint16_t tiles, items;       // items: shares
+  uint16_t mixed;
+};
+constexpr int kKvSections = 5;
+
 struct BwdArgs {
   Shape s;
   View q, d_o;
@@ -134,12 +159,14 @@ struct BwdArgs {
   // the tiles before it and of the shares before it (see dq_part).  Where the workspace has no room for all of them
   // (shares.own0) the first share adds to dq itself, and its reads end the launch 2 us later.
   TileShares shares;
-  // Under-filled dK/dV launches likewise: kv_split > 1 gives every key tile kv_split workgroups, each with a share of the
-  // query blocks.  The first one writes dk[c] / dv[c]; number y stores its sums at parts + ((2 (y - 1) + (0: dK, 1: dV)) *
-  // t.n + c) * part_floats(dk[c]) (laid out as dk[c]), and the launcher adds them up (and rounds) in order.
-  int16_t kv_split;
-  int16_t pair;        // 1: both passes in one launch, where the hand-scheduled kernels take both (kv_split <= 1)
-  float* parts;        // the two passes use it one after the other
+  // Under-filled dK/dV launches likewise: kv_each > 0 splits the query blocks a key tile meets into shares of at most that many
+  // (kv_shares).  The first share writes dk[c] / dv[c]; each other one stores its sums, dK and then dV of kDkvFastKeys rows of D
+  // floats, in a slot of kv_parts: slots are numbered through the tiles of a head (kt fastest), a head's behind another's; the
+  // launcher adds them up (and rounds) in order.  kv_items: shares of a head, kv_sec: where they are (both set by the launcher).
+  int32_t kv_each, kv_items;
+  KvSection kv_sec[kKvSections];
+  int32_t pair;        // 1: both passes in one launch, where the hand-scheduled kernels take both
+  float *parts, *kv_parts;   // of launches that run one after the other they may be the same memory
   // dK / dV work of a chunk's last visit folded into the launch (bf16 path): the hand-scheduled kernel's epilogue does it,
   // beside the general kernel the launcher runs fill and cast launches
   uint64_t kv_assign;          // bit c: dk[c] / dv[c] are overwritten, not added to
@@ -150,8 +177,6 @@ struct BwdArgs {
   int16_t queue_clean; // 1: the counters are zero already (the first launch behind launch_bwd_prep)
   int16_t queue_xcds;  // counters in use (the device's XCD count, 1 .. 8); set by the launcher
 };
-// distance between partial sums of n floats each (256-byte steps)
-__host__ __device__ inline int64_t part_floats(int64_t n) { return (n + 63) / 64 * 64; }
 // Partial sum y of query tile qt of batch entry b: [row, head, element] floats from here on.  The sums of a batch entry lie one
 // behind the other; dq_part_rows are the rows before that of tile qt.
 __host__ __device__ inline int64_t dq_part_rows(const QueryTiles& q, const TileShares& t, int qt) {
@@ -170,7 +195,8 @@ __host__ __device__ inline int64_t dq_part_rows_all(const QueryTiles& q, const T
 __host__ __device__ inline float* dq_part(float* parts, const Shape& s, const QueryTiles& q, const TileShares& t, int b, int qt, int y) {
   return parts + (b * dq_part_rows_all(q, t) + dq_part_rows(q, t, qt) + (int64_t)y * q.rows_of(qt)) * s.Hq * s.D;
 }
-__host__ __device__ inline int64_t kv_part_floats(const Shape& s) { return part_floats((int64_t)s.B * s.Sk * s.Hkv * s.D); }
+// (not a multiple of a large power of two: workgroups in step would write to the same memory channels)
+__host__ __device__ inline int64_t kv_slot_floats(const Shape& s) { return (int64_t)2 * kDkvFastKeys * s.D + 17 * 64; }
 constexpr int kQueueInts = 8 * 32;   // at most 8 counters, 128 bytes apart
 // passed by value: a kernel takes 4096 bytes of arguments
 static_assert(sizeof(BwdArgs) <= 4096 - 64 && sizeof(FwdArgs) <= 4096 - 64, "argument structs must fit the kernel arguments");
@@ -190,10 +216,6 @@ struct CombineArgs {
   TileShares shares;
   QueryTiles tiles;
 };
-
-// Tile of the hand-scheduled dK/dV kernel
-constexpr int kDkvFastKeys = 256;
-constexpr int kDkvFastRows = 32;
 
 // Tuning and testing switches of the launchers.  The defaults are the product.  They are read from the
 // environment ONCE, when the library is loaded (ST_FWD_FAST, ST_DQ_FAST, ST_DKV_FAST, ST_DKV_QUEUE, ST_FWD_WQ,
@@ -240,8 +262,9 @@ bool fwd_fast_usable(const FwdArgs& a);
 hipError_t launch_fwd_fast(const FwdArgs& a, hipStream_t s);
 hipError_t launch_bwd_bf16(const BwdArgs& a, hipStream_t s);
 bool dkv_fast_usable(const BwdArgs& a);
+void kv_sections(BwdArgs& a);    // sets kv_items and kv_sec from the table and kv_each
 hipError_t launch_bwd_dkv_fast(const BwdArgs& a, hipStream_t s);
-hipError_t launch_bwd_pair_fast(const BwdArgs& a, hipStream_t s);   // both, kv_split <= 1
+hipError_t launch_bwd_pair_fast(const BwdArgs& a, hipStream_t s);   // both
 bool dq_fast_usable(const BwdArgs& a);
 hipError_t launch_bwd_dq_fast(const BwdArgs& a, hipStream_t s);
 
@@ -257,7 +280,7 @@ hipError_t launch_bwd_prep(const View& d_o, const View& o, int o_dtype, const Vi
 hipError_t launch_cast(const float* src, void* dst, int64_t n, int dst_dtype, hipStream_t s);
 // dst (dense bf16 [B,Sq,Hq,D]) = bf16(q * scale * log2 e) of a bf16 view q
 hipError_t launch_scale_q(const View& q, void* dst, int32_t B, int32_t Sq, int32_t Hq, int32_t D, float scale, hipStream_t s);
-// dk[c] += its parts (see BwdArgs::kv_split) in order, likewise dv[c]; rounded to dk_lowp[c] / dv_lowp[c] where given
+// dk[c] += its partial sums (see BwdArgs::kv_each) in order, likewise dv[c]; rounded to dk_lowp[c] / dv_lowp[c] where given
 hipError_t launch_add_kv_parts(const BwdArgs& a, hipStream_t s);
 // dq += its partial sums (see BwdArgs::shares) in order; `rows` rows per query tile
 hipError_t launch_add_parts(const BwdArgs& a, int rows, hipStream_t s);

@@ -34,6 +34,50 @@ __device__ __forceinline__ int lane_scan(int x, int& total) {
   return sum - x;
 }
 
+// The shares of the key tiles of a head (see BwdArgs::kv_each).  `offsets`: a function that gives the position of chunk c.
+struct KvPlace {
+  int tile, share, n_share, slot;                    // slot: of the tile's share 1, within the head
+};
+// of share `w`, or (by_tile) the first one of tile w
+template <typename F>
+__device__ __forceinline__ KvPlace kv_place(const Shape& s, const KvSection (&sec)[kKvSections], int each, int n_kt, int w, bool by_tile, int lane, F offsets) {
+  int t0 = 0, i0 = 0, x = 0;                         // tiles and shares before the section that w is in
+  for (; x < kKvSections - 1; ++x) {
+    if (w < (by_tile ? t0 + sec[x].tiles : i0 + sec[x].items)) break;
+    t0 += sec[x].tiles;
+    i0 += sec[x].items;
+  }
+  const int tiles = sec[x].tiles;
+  KvPlace p;
+  if (!sec[x].mixed) {
+    p.n_share = sec[x].items / max(tiles, 1);
+    const int k = by_tile ? w - t0 : (w - i0) / p.n_share;
+    p.tile = t0 + k;
+    p.share = by_tile ? 0 : w - i0 - k * p.n_share;
+    p.slot = i0 - t0 + k * (p.n_share - 1);
+    return p;
+  }
+  p.tile = t0;
+  p.share = p.slot = 0;
+  p.n_share = 1;
+  for (int at = t0; at < t0 + tiles; at += 64) {     // a lane per tile
+    const int t = at + lane, n = t < t0 + tiles ? kv_shares(kv_blocks(s, offsets(min(t, t0 + tiles - 1) / n_kt), t % n_kt), each) : 0;
+    int total;
+    const int first = i0 + lane_scan(n, total);
+    const uint64_t here = __ballot(by_tile ? t == w : w >= first && w < first + n);
+    if (here) {
+      const int l = (int)__builtin_ctzll(here), f = __builtin_amdgcn_readlane(first, l);
+      p.tile = at + l;
+      p.share = by_tile ? 0 : w - f;
+      p.n_share = __builtin_amdgcn_readlane(n, l);
+      p.slot = f - p.tile;
+      break;
+    }
+    i0 += total;
+  }
+  return p;
+}
+
 // Block of a query-stationary launch -> query tile, head-and-batch index and share (see TileShares).  Where the tiles have
 // numbers of their own, the shares of a head are numbered from its last tile down and handed out in that order, all heads'
 // first ones first (qtile_block): the longest ones are the last tiles'.

@@ -20,6 +20,12 @@ CASES = [("bf16", 1, 2, 1, 128, 1500, 1500, 1, 0, (0, 0)),                # the 
          ("bf16", 1, 1, 1, 128, 700, 350, 5, 0, (257, 1300)),             # runs of unlike length
          ("bf16", 1, 1, 1, 64, 16384, 320, 8, -9000, (0, 0)),             # 64 tiles, the first half of them sees nothing
          ("bf16", 1, 1, 1, 64, 16400, 320, 8, -9000, (0, 0)),             # 65: one number for all
+         # few key tiles with unlike walks: split into shares of one size, found through runs of tiles (of which there are
+         # more than five in the first case: the last one is mixed), beside hidden chunks, with dQ in the same launch
+         ("bf16", 1, 4, 1, 128, 1500, 100, 18, 0, (0, 0)),
+         ("bf16", 1, 8, 1, 64, 900, 450, 8, 450, (450, 2700)),
+         ("bf16", 2, 4, 2, 128, 1280, 640, 4, 0, (0, 0)),
+         ("bf16", 1, 8, 1, 128, 300, 2000, 2, 1800, (0, 0)),
          ("f32", 1, 1, 1, 64, 1210, 1210, 1, 0, (0, 0)),
          ("f32", 2, 1, 1, 128, 140, 70, 12, 70, (70, 700)),
          ("f32", 1, 1, 1, 256, 2048, 256, 3, -100, (0, 0))]
@@ -61,6 +67,16 @@ def test_tiles_with_shares_of_their_own(c):
                 assert_close_wide(host(dk[j]), dk_r[j], f"dk[{j}]")
                 assert_close_wide(host(dv[j]), dv_r[j], f"dv[{j}]")
         got.append(dq)
+    if dtype == "bf16":                                                    # assigned and rounded, hidden chunks too
+        dq = torch.full_like(o, 1 / 64)
+        dk, dv = ([torch.full(k.shape, float("nan"), device="cuda") for k in ks] for _ in range(2))
+        lows = [[torch.empty_like(k) for k in ks] for _ in range(2)]
+        st.st_ring_bwd_last(q, ks, vs, d_o, low, lse, *args, order, dq, dk, dv, assign=True, dk_lowp=lows[0], dv_lowp=lows[1], workspace=ws(full[1]))
+        assert torch.equal(dq, got[0])
+        for j in range(n):
+            assert torch.equal(dk[j].to(torch.bfloat16), lows[0][j]) and torch.equal(dv[j].to(torch.bfloat16), lows[1][j])
+            assert_close_wide(host(dk[j]), dk_r[j], f"assigned dk[{j}]")
+            assert_close_wide(host(dv[j]), dv_r[j], f"assigned dv[{j}]")
     dq = torch.full_like(o, 1 / 64)
     st.st_ring_bwd_noalloc(q, ks, vs, d_o, low, lse, *args, order, dq, [torch.zeros(k.shape, device="cuda") for k in ks],
                            [torch.zeros(k.shape, device="cuda") for k in ks])
