@@ -198,11 +198,12 @@ __global__ __launch_bounds__(256) void combine_kernel(const CombineArgs a, int32
   if (sub == 0) a.lse_out[(b * a.Hq + h) * a.Sq_out + i] = lnew;
 }
 
-// fp32 "lowp" copy for the fp32 storage dtype
-__global__ __launch_bounds__(256) void copy_f32_kernel(const float4* __restrict__ src, float4* __restrict__ dst,
-                                                       int64_t n_vec) {
+// fp32 "lowp" copy for the fp32 storage dtype; the last n % 4 values one by one
+__global__ __launch_bounds__(256) void copy_f32_kernel(const float4* src, float4* dst, int64_t n) {
   const int64_t v = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  if (v < n_vec) dst[v] = src[v];
+  if (4 * v + 4 <= n) dst[v] = src[v];
+  else
+    for (int64_t i = 4 * v; i < n; ++i) reinterpret_cast<float*>(dst)[i] = reinterpret_cast<const float*>(src)[i];
 }
 
 // ---- delta: 16 lanes per row, 16-byte loads, shuffle reduction inside the 16-lane group -------
@@ -427,7 +428,7 @@ hipError_t launch_merge(float* o_acc, float* lse_acc, const float* o_part, const
   hipError_t e = hipGetLastError();
   if (e == hipSuccess && o_lowp != nullptr) {
     hipLaunchKernelGGL(copy_f32_kernel, dim3(blocks_for(n_vec)), dim3(256), 0, s, (const float4*)o_acc,
-                       (float4*)o_lowp, n_vec);
+                       (float4*)o_lowp, 4 * n_vec);
     e = hipGetLastError();
   }
   return e;
@@ -460,7 +461,7 @@ hipError_t launch_combine(const CombineArgs& a, int lowp_dtype, hipStream_t s) {
   hipError_t e = hipGetLastError();
   if (e == hipSuccess && a.o_lowp != nullptr && !lowp) {
     hipLaunchKernelGGL(copy_f32_kernel, dim3(blocks_for(n_vec)), dim3(256), 0, s, (const float4*)a.o_out,
-                       (float4*)a.o_lowp, n_vec);
+                       (float4*)a.o_lowp, 4 * n_vec);
     e = hipGetLastError();
   }
   return e;
@@ -504,10 +505,13 @@ hipError_t launch_bwd_prep(const View& d_o, const View& o, int o_dtype, const Vi
 
 hipError_t launch_cast(const float* src, void* dst, int64_t n, int dst_dtype, hipStream_t s) {
   if (n == 0) return hipSuccess;
-  if (dst_dtype == ST_F32) return hipMemcpyAsync(dst, src, n * sizeof(float), hipMemcpyDeviceToDevice, s);
   const int64_t n_vec = n / 4;
   const int tail = (int)(n - n_vec * 4);
   ProfScope prof("cast", s);
+  if (dst_dtype == ST_F32) {                           // as a copy of the runtime it held the stream for 5 us more
+    hipLaunchKernelGGL(copy_f32_kernel, dim3(blocks_for((n + 3) / 4)), dim3(256), 0, s, (const float4*)src, (float4*)dst, n);
+    return hipGetLastError();
+  }
   hipLaunchKernelGGL(cast_bf16_kernel, dim3(blocks_for(n_vec + tail)), dim3(256), 0, s, (const float4*)src,
                      (uint2*)dst, n_vec, src + n_vec * 4, (uint16_t*)dst + n_vec * 4, tail);
   return hipGetLastError();

@@ -385,20 +385,25 @@ __global__ __launch_bounds__(waves<DP>() * 64) void fwd_f32_kernel(const FwdArgs
 
 // ---------------------------------------------------------------- backward: dQ
 // Three contractions per tile pair (S and dP are recomputed); otherwise the forward's layout and its shares.
+template <int DP>
+struct alignas(16) DqShared {
+  float qs[kT * lds_stride<DP>()], dos[kT * lds_stride<DP>()];
+  float fold[waves<DP>() / 2 * (DP / 32) * 16 * 64];
+  KeyTable tab;
+  int any_dirty;
+};
 template <int DP, bool FULL>
-__global__ __launch_bounds__(waves<DP>() * 64) void bwd_dq_f32_kernel(const BwdArgs a) {
+__device__ __forceinline__ void bwd_dq_f32(const BwdArgs& a, DqShared<DP>& sm, int block_x, int grid_x, int block_y) {
   constexpr int NW = waves<DP>(), DB = DP / 32, N = 32, NR = row_pieces<DP, N>(), NC = col_pieces<DP, N>();
-  __shared__ __attribute__((aligned(16))) float qs[kT * lds_stride<DP>()];
-  __shared__ __attribute__((aligned(16))) float dos[kT * lds_stride<DP>()];
-  __shared__ float fold[NW / 2 * DB * 16 * 64];
-  __shared__ KeyTable tab;
-  __shared__ int any_dirty;
+  float *qs = sm.qs, *dos = sm.dos, *fold = sm.fold;
+  KeyTable& tab = sm.tab;
+  int& any_dirty = sm.any_dirty;
   const Shape& s = a.s;
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int g = lane >> 5, r = lane & 31;
   const int n_qt = (s.Sq + kT - 1) / kT;
   int qt, hb, split;
-  share_block(a.shares, blockIdx.x, gridDim.x, blockIdx.y, n_qt, s.causal, qt, hb, split);
+  share_block(a.shares, block_x, grid_x, block_y, n_qt, s.causal, qt, hb, split);
   const int n_split = max(shares_of(a.shares, qt), 1);
   const int h = hb % s.Hq, b = hb / s.Hq, hk = h / (s.Hq / s.Hkv);
   const int row0 = qt * kT;
@@ -484,20 +489,24 @@ __global__ __launch_bounds__(waves<DP>() * 64) void bwd_dq_f32_kernel(const BwdA
 }
 
 // ---------------------------------------------------------------- backward: dK, dV
-// grid: (ceil(Sk / 32), Hkv, B * n_chunks)
+// block = key tile + ceil(Sk / 32) (KV head + Hkv (batch entry + B chunk))
+template <int DP>
+struct alignas(16) DkvShared {
+  float ks[kT * lds_stride<DP>()], vs[kT * lds_stride<DP>()];
+  float stats[waves<DP>() * 64];
+  float fold[waves<DP>() / 2 * (DP / 32) * 16 * 64];
+  int any_dirty;
+};
 template <int DP, bool FULL>
-__global__ __launch_bounds__(waves<DP>() * 64) void bwd_dkv_f32_kernel(const BwdArgs a) {
+__device__ __forceinline__ void bwd_dkv_f32(const BwdArgs& a, DkvShared<DP>& sm, int block) {
   constexpr int NW = waves<DP>(), DB = DP / 32, N = DP < 128 ? 32 : 16, NR = row_pieces<DP, N>(), NC = col_pieces<DP, N>();
-  __shared__ __attribute__((aligned(16))) float ks[kT * lds_stride<DP>()];
-  __shared__ __attribute__((aligned(16))) float vs[kT * lds_stride<DP>()];
-  __shared__ float fold[NW / 2 * DB * 16 * 64];
-  __shared__ int any_dirty;
-  __shared__ __attribute__((aligned(16))) float stats[NW * 64];
+  float *ks = sm.ks, *vs = sm.vs, *fold = sm.fold, *stats = sm.stats;
+  int& any_dirty = sm.any_dirty;
   const Shape& s = a.s;
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int g = lane >> 5, r = lane & 31;
-  const int key0 = blockIdx.x * kT, hk = blockIdx.y;
-  const int c = blockIdx.z / s.B, b = blockIdx.z % s.B;
+  const int n_kt = (s.Sk + kT - 1) / kT, outer = block / n_kt, bc = outer / s.Hkv;
+  const int key0 = (int)sgpr((block - outer * n_kt) * kT), hk = (int)sgpr(outer - bc * s.Hkv), c = (int)sgpr(bc / s.B), b = (int)sgpr(bc % s.B);
   const int G = s.Hq / s.Hkv;
   const int64_t k0 = a.t.k_offset[c];
   // row i sees key t of the chunk iff i >= first_row(t)
@@ -610,6 +619,24 @@ __global__ __launch_bounds__(waves<DP>() * 64) void bwd_dkv_f32_kernel(const Bwd
     }
 }
 
+// Both passes in one launch: the first n_kv workgroups are key tiles, the others the dQ launch's blocks.  Neither needs the other's
+// results, each is a chain of latencies at its start and its end, and a causal shard's key tiles do unlike amounts of work:
+// one head x 128 rows x 4 chunks of 128 keys 16 and 24 us apart and a gap between them, 8/2 heads x 512 rows x 8 chunks of
+// 512 keys 206 and 152.
+template <int DP, bool FULL>
+__global__ __launch_bounds__(waves<DP>() * 64) void bwd_f32_kernel(const BwdArgs a, int n_kv, int q_blocks) {
+  __shared__ union Both {
+    DqShared<DP> dq;
+    DkvShared<DP> dkv;
+  } sm;
+  if ((int)blockIdx.x < n_kv) {
+    bwd_dkv_f32<DP, FULL>(a, sm.dkv, blockIdx.x);
+  } else {
+    const int x = blockIdx.x - n_kv;
+    bwd_dq_f32<DP, FULL>(a, sm.dq, (int)sgpr(x % q_blocks), q_blocks, (int)sgpr(x / q_blocks));
+  }
+}
+
 // f(integral constant, full): the kernels are built for these D, and for smaller ones with zero-filled columns
 template <typename F>
 hipError_t with_padded_d(int D, F f) {
@@ -645,25 +672,21 @@ hipError_t launch_fwd_f32(const FwdArgs& a, hipStream_t stream) {
 }
 
 hipError_t launch_bwd_f32(const BwdArgs& a, hipStream_t stream) {
-  const int64_t total = (int64_t)((a.s.Sq + kT - 1) / kT) * a.s.Hq * a.s.B;
+  const int n_qt = (a.s.Sq + kT - 1) / kT;
+  const int64_t total = (int64_t)n_qt * a.s.Hq * a.s.B;
   if (total <= 0 || a.t.n == 0 || a.s.Sk == 0) return hipSuccess;
-  if (total > 0x7fffffff) return hipErrorInvalidValue;
-  return with_padded_d(a.s.D, [&](auto dp, auto full) {
+  const dim3 q_grid = share_grid(a.shares, total, n_qt);
+  const int64_t n_kv = (int64_t)((a.s.Sk + kT - 1) / kT) * a.s.Hkv * a.s.B * a.t.n, blocks = n_kv + (int64_t)q_grid.x * q_grid.y;
+  if (total > 0x7fffffff || blocks > 0x7fffffff) return hipErrorInvalidValue;
+  hipError_t e = with_padded_d(a.s.D, [&](auto dp, auto full) {
     constexpr int DP = decltype(dp)::value;
     constexpr bool FULL = decltype(full)::value;
-    {
-      ProfScope prof("bwd_dq_f32", stream);
-      const dim3 grid = share_grid(a.shares, total, (a.s.Sq + kT - 1) / kT);
-      hipLaunchKernelGGL((bwd_dq_f32_kernel<DP, FULL>), grid, dim3(waves<DP>() * 64), 0, stream, a);
-    }
-    hipError_t e = hipGetLastError();
-    if (e == hipSuccess && a.shares.n > 1) e = launch_add_parts(a, kT, stream);
-    if (e != hipSuccess) return e;
-    ProfScope prof("bwd_dkv_f32", stream);
-    const dim3 grid((a.s.Sk + kT - 1) / kT, a.s.Hkv, a.s.B * a.t.n);
-    hipLaunchKernelGGL((bwd_dkv_f32_kernel<DP, FULL>), grid, dim3(waves<DP>() * 64), 0, stream, a);
+    ProfScope prof("bwd_f32", stream);
+    hipLaunchKernelGGL((bwd_f32_kernel<DP, FULL>), dim3((unsigned)blocks), dim3(waves<DP>() * 64), 0, stream, a, (int)n_kv, (int)q_grid.x);
     return hipGetLastError();
   });
+  if (e == hipSuccess && a.shares.n > 1) e = launch_add_parts(a, kT, stream);
+  return e;
 }
 
 }  // namespace st
