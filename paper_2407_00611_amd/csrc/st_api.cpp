@@ -425,6 +425,66 @@ struct KeySplit {
     return w->n;
   }
 };
+// fp32: both passes are always one launch.  A key tile is 32 keys, its wavefronts take a (head, 32-row tile) pair each in a turn of
+// 23 us at head size 128, 12.6 at 64 and 21.5 at 256 (half the wavefronts), behind 15 us; dQ's are above.
+void f32_bwd_split(BwdSplit& r, const st::Shape& s, const QueryWalk& walk, const int64_t* k_offset, int n, size_t room, bool split_dq) {
+  const int n_kt = (s.Sk + 31) / 32, waves = s.D <= 128 ? 8 : 4, G = s.Hq / s.Hkv, rows = (s.Sq + 31) / 32;
+  const Cost kv_cost{15, 3 + (s.D <= 128 ? 0.15 : 0.072) * s.D, 0, 0}, cost = dq_cost(ST_F32, s.D);
+  // key tiles by the pairs they meet, at most 64 kinds
+  struct Kind { int pairs; int64_t tiles; } kind[64];
+  int kinds = 0;
+  auto add = [&](int row_tiles, int64_t tiles) {
+    const int pairs = row_tiles * G;
+    for (int i = 0; i < kinds; ++i)
+      if (kind[i].pairs == pairs || (kinds == 64 && i == 63)) {
+        kind[i].tiles += tiles;
+        return;
+      }
+    if (pairs > 0) kind[kinds++] = Kind{pairs, tiles};
+  };
+  const int64_t heads = (int64_t)s.B * s.Hkv, first = st::q_pos(s, 0);
+  for (int c = 0; c < n; ++c) {
+    if (!s.causal || k_offset == nullptr || k_offset[c] + s.Sk - 1 <= first) add(rows, heads * n_kt);
+    else
+      for (int kt = 0; kt < n_kt; ++kt) {
+        const int row = st::q_row_of(s, k_offset[c] + kt * 32);
+        add(row >= s.Sq ? 0 : rows - row / 32, heads);
+      }
+  }
+  std::sort(kind, kind + kinds, [](const Kind& x, const Kind& y) { return x.pairs > y.pairs; });
+  int64_t tiles = 0;
+  for (int i = 0; i < kinds; ++i) tiles += kind[i].tiles;
+  if (kinds == 0 || tiles >= 1024) return;
+  const size_t kv_bytes = 2 * (size_t)n * st::f32_kv_floats(s) * sizeof(float), row_bytes = (size_t)s.B * s.Hq * s.D * sizeof(float);
+  Job job[64 + st::kShareTiles];
+  double best = 1e30;
+  const BwdSplit none = {};
+  auto look = [&](int x, const Split& q) {
+    const size_t kv = (size_t)(x - 1) * kv_bytes;
+    auto dq_bytes = [&](int64_t part_rows) { return q.n > 1 ? align_up((size_t)part_rows * row_bytes, 256) : 0; };
+    if (kv + dq_bytes(q.rows_own0) > room) return;
+    const double add = (x > 1 ? 7 + (double)kv_bytes * (x + 1) / 8e6 : 0) + (q.n > 1 ? 7 + (double)row_bytes * (q.rows + 2 * s.Sq) / 8e6 : 0);
+    const double less = best < 1e30 ? (x > 1 || q.n > 1 ? 0.97 : 1) * best : best;
+    for (int i = 0; i < kinds; ++i) job[i] = Job{kv_cost.us((kind[i].pairs + x * waves - 1) / (x * waves), 0), kind[i].tiles * x};
+    if (job[0].us + add >= less || q.longest_us(cost) + add >= less) return;
+    const double us = add + jobs_us(job, kinds + q.jobs(job + kinds, cost), less - add);
+    if (us >= less) return;
+    best = us;
+    const bool own0 = kv + dq_bytes(q.rows) > room;
+    r = none;
+    r.dq = q.table(own0);
+    r.dq_bytes = dq_bytes(own0 ? q.rows_own0 : q.rows);
+    r.kv_items = x;
+    r.pair = true;
+    r.bytes = r.dq_bytes + kv;
+  };
+  const Split whole(walk, walk.most());
+  for (int x = 1; x <= kMaxSplits && x <= (kind[0].pairs + waves - 1) / waves; x = x < 4 ? x + 1 : x + x / 2) {
+    if (x > 1 && tiles * x > 4 * kPlanCus) break;
+    look(x, whole);
+    if (split_dq) each_split(walk, kMaxSplits, [&](const Split& q) { look(x, q); });
+  }
+}
 // Both passes in one launch: the compute units that have no key tile, or are done with theirs, take shares of the dQ pass
 // meanwhile, and the launch ends with the last of them (jobs_us, key tiles first).  Forward and backward, apart and together:
 // 4 heads x 700 rows x 4 chunks 99 and 77 us, 12 heads of 64 x 800 rows x 4 chunks 96 and 88 us, 6 heads x 1500 rows x 4
@@ -465,7 +525,10 @@ BwdSplit bwd_splits(const st::Shape& s, int dtype, const int64_t* k_offset, int 
     });
     dq_us = best;
   }
-  if (!bf16) return r;
+  if (!bf16) {
+    if (plan_dq) f32_bwd_split(r, s, walk, k_offset, n, room, split_dq);
+    return r;
+  }
   KeyWalk keys;
   key_walk(keys, s, k_offset, n);
   if (keys.seen < 1 || keys.heads * keys.seen >= 512 || keys.tiles > 32767) return r;
@@ -525,7 +588,7 @@ BwdSplit bwd_splits(const st::Shape& s, int dtype, const int64_t* k_offset, int 
   }
   r.kv_each = kv.each;
   r.kv_items = (int)kv.items;
-  r.dq_bytes = dq_bytes;
+  r.dq_bytes = dq_bytes;                               // whole rows of 64 or 128 floats: kv_parts stays on its boundary
   r.bytes = r.pair ? dq_bytes + slot_bytes(kv) : std::max(dq_bytes, slot_bytes(kv));
   return r;
 }

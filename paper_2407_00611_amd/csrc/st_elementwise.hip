@@ -376,6 +376,32 @@ __global__ __launch_bounds__(256) void add_kv_parts_kernel(const BwdArgs a) {
   if (low) low[at] = make_uint2(pack_bf16x2(x.x, x.y), pack_bf16x2(x.z, x.w));
 }
 
+// fp32 key tiles: blockIdx.y is a chunk, dK and then dV.  Keys that no row sees have no sums.
+__global__ __launch_bounds__(256) void add_kv_parts_f32_kernel(const BwdArgs a, int64_t n_vec) {
+  const Shape& s = a.s;
+  const int64_t v = (int64_t)blockIdx.x * 256 + threadIdx.x;
+  const int c = blockIdx.y >> 1, w = blockIdx.y & 1, n = a.kv_items;
+  if (v >= n_vec) return;
+  const int64_t row = v / (s.Hkv * s.D / 4);
+  if (s.causal && q_row_of(s, a.t.k_offset[c] + row % s.Sk) >= s.Sq) return;
+  float4* dst = reinterpret_cast<float4*>(w ? a.dv[c] : a.dk[c]) + v;
+  float4 x = *dst;
+  for (int y0 = 1; y0 < n; y0 += 4) {
+    float4 p[4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) p[u] = reinterpret_cast<const float4*>(f32_kv_part(a.kv_parts, s, a.t.n, min(y0 + u, n - 1), c, w))[v];
+#pragma unroll
+    for (int u = 0; u < 4; ++u)
+      if (y0 + u < n) {
+        x.x += p[u].x;
+        x.y += p[u].y;
+        x.z += p[u].z;
+        x.w += p[u].w;
+      }
+  }
+  *dst = x;
+}
+
 __global__ __launch_bounds__(256) void fill_state_kernel(float* __restrict__ o, float* __restrict__ lse,
                                                          int64_t n_o, int64_t n_lse) {
   const int64_t v = (int64_t)blockIdx.x * 256 + threadIdx.x;
@@ -553,6 +579,14 @@ hipError_t launch_add_kv_parts(const BwdArgs& a_in, hipStream_t s) {
   if (tiles > 65535 || heads > 65535) return hipErrorInvalidValue;    // split launches have fewer than 512 tiles that see rows
   ProfScope prof("add_kv_parts", s);
   hipLaunchKernelGGL(add_kv_parts_kernel, dim3(2 * blocks_for(kDkvFastKeys * a.s.D / 4), tiles, heads), dim3(256), 0, s, a);
+  return hipGetLastError();
+}
+
+hipError_t launch_add_kv_parts_f32(const BwdArgs& a, hipStream_t s) {
+  const int64_t n_vec = (int64_t)a.s.B * a.s.Sk * a.s.Hkv * a.s.D / 4;
+  if (n_vec <= 0 || a.t.n <= 0) return hipSuccess;
+  ProfScope prof("add_kv_parts", s);
+  hipLaunchKernelGGL(add_kv_parts_f32_kernel, dim3(blocks_for(n_vec), 2 * a.t.n), dim3(256), 0, s, a, n_vec);
   return hipGetLastError();
 }
 

@@ -22,6 +22,7 @@
 // forward, 2640 us dQ, 3590 us dK / dV (3.2 TFLOP/s).  Now 104, 151 and 202 us with the split launches (on one workgroup per
 // query tile, 128 for 256 compute units: 181 us forward, 270 us dQ).  Prologue, first loads and fold are 10 to 20 us of each;
 // long walks run at 100 TFLOP/s of the 154 of a large fp32 matrix product on this card.
+#include <algorithm>
 #include <type_traits>
 
 #include "st_internal.h"
@@ -489,7 +490,9 @@ __device__ __forceinline__ void bwd_dq_f32(const BwdArgs& a, DqShared<DP>& sm, i
 }
 
 // ---------------------------------------------------------------- backward: dK, dV
-// block = key tile + ceil(Sk / 32) (KV head + Hkv (batch entry + B chunk))
+// block = key tile + ceil(Sk / 32) (KV head + Hkv (batch entry + B (chunk + n share))).  An under-filled launch gives every key
+// tile kv_items workgroups, each with a run of its (head, row tile) pairs: 4/1 heads of 256 x 534 rows are 17 key tiles of up to
+// 68 pairs, 379 us on 17 workgroups; with dQ (53 us) and the pass that adds up 91 + 7 now.
 template <int DP>
 struct alignas(16) DkvShared {
   float ks[kT * lds_stride<DP>()], vs[kT * lds_stride<DP>()];
@@ -505,8 +508,9 @@ __device__ __forceinline__ void bwd_dkv_f32(const BwdArgs& a, DkvShared<DP>& sm,
   const Shape& s = a.s;
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int g = lane >> 5, r = lane & 31;
-  const int n_kt = (s.Sk + kT - 1) / kT, outer = block / n_kt, bc = outer / s.Hkv;
-  const int key0 = (int)sgpr((block - outer * n_kt) * kT), hk = (int)sgpr(outer - bc * s.Hkv), c = (int)sgpr(bc / s.B), b = (int)sgpr(bc % s.B);
+  const int n_kt = (s.Sk + kT - 1) / kT, outer = block / n_kt, bc = outer / s.Hkv, cs = bc / s.B;
+  const int key0 = (int)sgpr((block - outer * n_kt) * kT), hk = (int)sgpr(outer - bc * s.Hkv), b = (int)sgpr(bc - cs * s.B);
+  const int share = (int)sgpr(cs / a.t.n), c = (int)sgpr(cs - share * a.t.n);
   const int G = s.Hq / s.Hkv;
   const int64_t k0 = a.t.k_offset[c];
   // row i sees key t of the chunk iff i >= first_row(t)
@@ -524,7 +528,8 @@ __device__ __forceinline__ void bwd_dkv_f32(const BwdArgs& a, DkvShared<DP>& sm,
   f32x16 acc_k[DB], acc_v[DB];
   zero_acc(acc_k);
   zero_acc(acc_v);
-  for (int x = wave; x < G * per_head; x += NW) {
+  const int pairs = G * per_head, n_share = max(a.kv_items, 1);
+  for (int x = pairs * share / n_share + wave, x1 = pairs * (share + 1) / n_share; x < x1; x += NW) {
     const int h = hk * G + x / per_head, i0 = (t_lo + x % per_head) * kT;
     const float* qb = (const float*)a.q.ptr + b * a.q.sb + h * a.q.sh + (int64_t)i0 * a.q.ss;
     const float* db_ = (const float*)a.d_o.ptr + b * a.d_o.sb + h * a.d_o.sh + (int64_t)i0 * a.d_o.ss;
@@ -591,15 +596,18 @@ __device__ __forceinline__ void bwd_dkv_f32(const BwdArgs& a, DkvShared<DP>& sm,
   }
   if (wave != 0 || key0 + r >= s.Sk || key_first >= s.Sq) return;
   const int64_t orow = (((int64_t)b * s.Sk + key0 + r) * s.Hkv + hk) * s.D;
+  float* out_k = (share ? f32_kv_part(a.kv_parts, s, a.t.n, share, c, 0) : a.dk[c]) + orow;
+  float* out_v = (share ? f32_kv_part(a.kv_parts, s, a.t.n, share, c, 1) : a.dv[c]) + orow;
 #pragma unroll
   for (int db = 0; db < DB; ++db)
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
       const int d = 32 * db + 8 * j + 4 * g;
       if (d >= s.D) continue;
-      float4* pk = reinterpret_cast<float4*>(a.dk[c] + orow + d);
-      float4* pv = reinterpret_cast<float4*>(a.dv[c] + orow + d);
-      float4 x = *pk, y = *pv;
+      float4* pk = reinterpret_cast<float4*>(out_k + d);
+      float4* pv = reinterpret_cast<float4*>(out_v + d);
+      float4 x = make_float4(0.f, 0.f, 0.f, 0.f), y = x;      // the memory of a partial sum holds nothing yet
+      if (share == 0) x = *pk, y = *pv;
       x.x += s.scale * acc_k[db][4 * j];
       x.y += s.scale * acc_k[db][4 * j + 1];
       x.z += s.scale * acc_k[db][4 * j + 2];
@@ -614,8 +622,8 @@ __device__ __forceinline__ void bwd_dkv_f32(const BwdArgs& a, DkvShared<DP>& sm,
   if (any_dirty)
     for (int h = hk * G; h < (hk + 1) * G; ++h) {
       const int hi = min(s.Sq, (wg_all + kT - 1) / kT * kT);
-      add_nonfinite(a.dk[c] + orow, nullptr, (const float*)a.q.ptr + b * a.q.sb + h * a.q.sh, a.q.ss, key_first, hi, s.D, g, true);
-      add_nonfinite(a.dv[c] + orow, nullptr, (const float*)a.d_o.ptr + b * a.d_o.sb + h * a.d_o.sh, a.d_o.ss, key_first, hi, s.D, g, false);
+      add_nonfinite(out_k, nullptr, (const float*)a.q.ptr + b * a.q.sb + h * a.q.sh, a.q.ss, key_first, hi, s.D, g, true);
+      add_nonfinite(out_v, nullptr, (const float*)a.d_o.ptr + b * a.d_o.sb + h * a.d_o.sh, a.d_o.ss, key_first, hi, s.D, g, false);
     }
 }
 
@@ -676,7 +684,7 @@ hipError_t launch_bwd_f32(const BwdArgs& a, hipStream_t stream) {
   const int64_t total = (int64_t)n_qt * a.s.Hq * a.s.B;
   if (total <= 0 || a.t.n == 0 || a.s.Sk == 0) return hipSuccess;
   const dim3 q_grid = share_grid(a.shares, total, n_qt);
-  const int64_t n_kv = (int64_t)((a.s.Sk + kT - 1) / kT) * a.s.Hkv * a.s.B * a.t.n, blocks = n_kv + (int64_t)q_grid.x * q_grid.y;
+  const int64_t n_kv = (int64_t)((a.s.Sk + kT - 1) / kT) * a.s.Hkv * a.s.B * a.t.n * std::max(a.kv_items, 1), blocks = n_kv + (int64_t)q_grid.x * q_grid.y;
   if (total > 0x7fffffff || blocks > 0x7fffffff) return hipErrorInvalidValue;
   hipError_t e = with_padded_d(a.s.D, [&](auto dp, auto full) {
     constexpr int DP = decltype(dp)::value;
@@ -685,6 +693,7 @@ hipError_t launch_bwd_f32(const BwdArgs& a, hipStream_t stream) {
     hipLaunchKernelGGL((bwd_f32_kernel<DP, FULL>), dim3((unsigned)blocks), dim3(waves<DP>() * 64), 0, stream, a, (int)n_kv, (int)q_grid.x);
     return hipGetLastError();
   });
+  if (e == hipSuccess && a.kv_items > 1) e = launch_add_kv_parts_f32(a, stream);
   if (e == hipSuccess && a.shares.n > 1) e = launch_add_parts(a, kT, stream);
   return e;
 }

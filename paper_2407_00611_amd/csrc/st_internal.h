@@ -163,6 +163,7 @@ struct BwdArgs {
   // (kv_shares).  The first share writes dk[c] / dv[c]; each other one stores its sums, dK and then dV of kDkvFastKeys rows of D
   // floats, in a slot of kv_parts: slots are numbered through the tiles of a head (kt fastest), a head's behind another's; the
   // launcher adds them up (and rounds) in order.  kv_items: shares of a head, kv_sec: where they are (both set by the launcher).
+  // The fp32 kernels: kv_items shares of every key tile (0: one), sums as f32_kv_part says.
   int32_t kv_each, kv_items;
   KvSection kv_sec[kKvSections];
   int32_t pair;        // 1: both passes in one launch, where the hand-scheduled kernels take both
@@ -196,6 +197,11 @@ __host__ __device__ inline float* dq_part(float* parts, const Shape& s, const Qu
   return parts + (b * dq_part_rows_all(q, t) + dq_part_rows(q, t, qt) + (int64_t)y * q.rows_of(qt)) * s.Hq * s.D;
 }
 // (not a multiple of a large power of two: workgroups in step would write to the same memory channels)
+// fp32: sum of share `y` >= 1 of chunk c, laid out as dk[c] (w = 0) and dv[c] (1)
+__host__ __device__ inline int64_t f32_kv_floats(const Shape& s) { return ((int64_t)s.B * s.Sk * s.Hkv * s.D + 63) / 64 * 64; }
+__host__ __device__ inline float* f32_kv_part(float* parts, const Shape& s, int n_chunks, int y, int c, int w) {
+  return parts + ((int64_t)(y - 1) * n_chunks + c) * 2 * f32_kv_floats(s) + w * f32_kv_floats(s);
+}
 __host__ __device__ inline int64_t kv_slot_floats(const Shape& s) { return (int64_t)2 * kDkvFastKeys * s.D + 17 * 64; }
 constexpr int kQueueInts = 8 * 32;   // at most 8 counters, 128 bytes apart
 // passed by value: a kernel takes 4096 bytes of arguments
@@ -282,6 +288,7 @@ hipError_t launch_cast(const float* src, void* dst, int64_t n, int dst_dtype, hi
 hipError_t launch_scale_q(const View& q, void* dst, int32_t B, int32_t Sq, int32_t Hq, int32_t D, float scale, hipStream_t s);
 // dk[c] += its partial sums (see BwdArgs::kv_each) in order, likewise dv[c]; rounded to dk_lowp[c] / dv_lowp[c] where given
 hipError_t launch_add_kv_parts(const BwdArgs& a, hipStream_t s);
+hipError_t launch_add_kv_parts_f32(const BwdArgs& a, hipStream_t s);
 // dq += its partial sums (see BwdArgs::shares) in order; `rows` rows per query tile
 hipError_t launch_add_parts(const BwdArgs& a, int rows, hipStream_t s);
 hipError_t launch_fill_state(float* o, float* lse, int64_t n_o, int64_t n_lse, hipStream_t s);
