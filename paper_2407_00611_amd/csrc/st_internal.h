@@ -291,6 +291,12 @@ hipError_t launch_add_kv_parts(const BwdArgs& a, hipStream_t s);
 hipError_t launch_add_kv_parts_f32(const BwdArgs& a, hipStream_t s);
 // dq += its partial sums (see BwdArgs::shares) in order; `rows` rows per query tile
 hipError_t launch_add_parts(const BwdArgs& a, int rows, hipStream_t s);
+// gradients of chunks that no row sees: set to zero (assign), and rounded to bf16 where a copy is asked for
+struct KvTables {
+  float *dk[kMaxTable], *dv[kMaxTable];
+  void *dk_lowp[kMaxTable], *dv_lowp[kMaxTable];
+};
+hipError_t launch_hidden_kv(const KvTables& t, int n, bool assign, int64_t n_kv, hipStream_t s);
 hipError_t launch_fill_state(float* o, float* lse, int64_t n_o, int64_t n_lse, hipStream_t s);
 hipError_t launch_zero(void* dst, int64_t bytes, hipStream_t s);   // bytes % 4 == 0, dst 4-byte aligned
 // benchmark aid: MFMA-only loop, one workgroup per compute unit (see st_probe.hip)
