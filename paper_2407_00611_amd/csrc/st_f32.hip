@@ -19,9 +19,11 @@
 //
 // One wavefront per row with scalar fused multiply-adds, as these kernels were before, read K with every lane on a
 // row of its own and one load per four multiply-adds: 8 heads x 512 rows x 8 chunks of 512 keys at D = 128 took 2460 us
-// forward, 2640 us dQ, 3590 us dK / dV (3.2 TFLOP/s).  Now 104, 151 and 202 us with the split launches (on one workgroup per
-// query tile, 128 for 256 compute units: 181 us forward, 270 us dQ).  Prologue, first loads and fold are 10 to 20 us of each;
-// long walks run at 100 TFLOP/s of the 154 of a large fp32 matrix product on this card.
+// forward, 2640 us dQ, 3590 us dK / dV (3.2 TFLOP/s).  Now 102 us forward with the split launch (on one workgroup per query
+// tile, 128 for 256 compute units: 181) and 312 to 322 us both backward passes in one launch (206 and 152 us, and a gap, in two).
+// Long walks run at 100 TFLOP/s of the 154 of a large fp32 matrix product on this card.  Bursts of 60 to 130 us of nothing but
+// this instruction on random data run at 129 to 136; of the forward's 103 us the loads cost 17 (without any 85), the exponential
+// 4, masks, addresses and rescaling nothing that shows.  A tile's columns in one load a row in place of DB took 2 to 3 % off both.
 #include <algorithm>
 #include <type_traits>
 
@@ -86,8 +88,11 @@ __device__ __forceinline__ void load_rows(Piece<N>& f, const float* row, int n, 
 
 // a pointer said to be global, where the compiler does not see it (it would load with flat loads, which wait for LDS too)
 typedef const __attribute__((address_space(1))) float* GlobalFloats;
-__device__ const float zero_row[256] = {};
-// The transposed operand of a tile X: lane r = column 32 db + r, register v = row c_row(v, g).
+__device__ const __attribute__((aligned(16))) float zero_row[256] = {};
+typedef float f32x2v __attribute__((ext_vector_type(2)));
+typedef float f32x4v __attribute__((ext_vector_type(4)));
+// The transposed operand of a tile X: lane r = columns DB r + db, register v = row c_row(v, g).  A lane's columns are neighbours
+// (which d an A row stands for is free as long as the results are stored so, see acc_block): one load of DB floats a row, not DB of one.
 // Rows at or beyond `limit` (tile-relative, >= 1) are zero: their weight is, but a row that exists, read in their place, may
 // hold an infinity, and 0 * inf is NaN.
 template <int DP, bool FULL, int N>
@@ -100,9 +105,22 @@ __device__ __forceinline__ void load_cols(Piece<N>& f, const float* tile, int64_
     const int v = n * piece_rows<DP, N>() + u, row = 8 * (v / 4) + v % 4;
     GlobalFloats p = (GlobalFloats)tile + (int64_t)(4 * g) * stride + (int64_t)row * stride;
     if (limit < kT) p = row < mine ? p : (GlobalFloats)zero_row;
-    p += r;
+    p += DB * r;
+    float* x = f.x + DB * u;
+    if constexpr (DB % 2 == 0) {
+      constexpr int W = DB % 4 == 0 ? 4 : 2;
+      typedef typename std::conditional<W == 4, f32x4v, f32x2v>::type Vec;
 #pragma unroll
-    for (int db = 0; db < DB; ++db) f.x[DB * u + db] = FULL || 32 * db + r < D ? p[32 * db] : 0.f;
+      for (int q = 0; q < DB; q += W) {
+        Vec y = {};
+        if (FULL || DB * r + q < D) y = *reinterpret_cast<const __attribute__((address_space(1))) Vec*>(p + q);   // D is a multiple of 8
+#pragma unroll
+        for (int e = 0; e < W; ++e) x[q + e] = y[e];
+      }
+    } else {
+#pragma unroll
+      for (int db = 0; db < DB; ++db) x[db] = FULL || DB * r + db < D ? p[db] : 0.f;
+    }
   }
 }
 
@@ -167,13 +185,14 @@ __device__ __forceinline__ void scrub(Piece<N>& f) {
 }
 
 // out[d] += X[t][d] wherever that is no finite number, for the rows t in [lo, hi); as_nan: their weight may have either sign
+template <int DB>
 __device__ __forceinline__ void add_nonfinite(float* out, float* out2, const float* x0, int64_t stride, int lo, int hi, int D, int g, bool as_nan) {
 #pragma unroll 1
   for (int t = lo; t < hi; ++t)
 #pragma unroll 1
     for (int d = 0; d < D; ++d) {
       const float x = x0[(int64_t)t * stride + d];
-      if (((d / 4) & 1) != g || finite(x)) continue;
+      if (((d / DB / 4) & 1) != g || finite(x)) continue;                // acc_block's half
       out[d] += as_nan ? __builtin_nanf("") : x;
       if (out2) out2[d] = out[d];
     }
@@ -186,6 +205,17 @@ __device__ __forceinline__ void zero_acc(f32x16 (&acc)[N]) {
 #pragma unroll
     for (int v = 0; v < 16; ++v) acc[i][v] = 0.f;
 }
+
+// Four neighbouring results of a lane: columns 4 (DB (2 j + g) + q) .. + 3 of the 4 DB that block j of its accumulators holds
+template <int DB>
+__device__ __forceinline__ float4 acc_block(const f32x16 (&acc)[DB], int j, int q, float c) {
+  float x[4];
+#pragma unroll
+  for (int e = 0; e < 4; ++e) x[e] = c * acc[(4 * q + e) % DB][4 * j + (4 * q + e) / DB];
+  return make_float4(x[0], x[1], x[2], x[3]);
+}
+
+__device__ __forceinline__ float4 add(float4 x, float4 y) { return make_float4(x.x + y.x, x.y + y.y, x.z + y.z, x.w + y.w); }
 
 // One tree step of the fold of the wavefronts' accumulators: the upper half of `n` wavefronts puts its values down.
 template <int N>
@@ -365,12 +395,12 @@ __global__ __launch_bounds__(waves<DP>() * 64) void fwd_f32_kernel(const FwdArgs
   float* o = (n_split > 1 ? a.part_o + split * a.part_stride : a.o) + (((int64_t)b * s.Sq + row0 + r) * s.Hq + h) * s.D;
   float* ol = a.o_lowp && n_split <= 1 ? (float*)a.o_lowp + (((int64_t)b * s.Sq + row0 + r) * s.Hq + h) * s.D : nullptr;   // storage dtype is fp32 here
 #pragma unroll
-  for (int db = 0; db < DB; ++db)
+  for (int j = 0; j < 4; ++j)
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      const int d = 32 * db + 8 * j + 4 * g;
+    for (int q = 0; q < DB; ++q) {
+      const int d = 4 * (DB * (2 * j + g) + q);
       if (d >= s.D) continue;
-      const float4 x = make_float4(acc[db][4 * j] * inv, acc[db][4 * j + 1] * inv, acc[db][4 * j + 2] * inv, acc[db][4 * j + 3] * inv);
+      const float4 x = acc_block(acc, j, q, inv);
       *reinterpret_cast<float4*>(o + d) = x;
       if (ol) *reinterpret_cast<float4*>(ol + d) = x;
     }
@@ -380,7 +410,7 @@ __global__ __launch_bounds__(waves<DP>() * 64) void fwd_f32_kernel(const FwdArgs
     for (int y = n_split > 1 ? n_split : 0; y < a.shares.n && a.shares.n > 1; ++y) a.part_lse[y * a.part_stride + stat] = -INFINITY;
   if (any_dirty)                                             // (a value that several shares add is the same infinity or NaN)
     for (int c = 0; c < a.t.n; ++c)
-      add_nonfinite(o, ol, (const float*)a.t.v[c] + b * a.t.vsb + hk * a.t.vsh, a.t.vss,
+      add_nonfinite<DB>(o, ol, (const float*)a.t.v[c] + b * a.t.vsb + hk * a.t.vsh, a.t.vss,
                     visible_keys(s, first_pos, a.t.k_offset[c]) / kT * kT, visible_keys(s, qpos, a.t.k_offset[c]), s.D, g, false);
 }
 
@@ -471,21 +501,18 @@ __device__ __forceinline__ void bwd_dq_f32(const BwdArgs& a, DqShared<DP>& sm, i
   if (empty && !part) return;
   float* dq = (part ? dq_part(a.parts, s, query_tiles(s, kT), a.shares, b, qt, split - a.shares.own0) : a.dq + ((int64_t)b * s.Sq + row0) * s.Hq * s.D) + ((int64_t)r * s.Hq + h) * s.D;
 #pragma unroll
-  for (int db = 0; db < DB; ++db)
+  for (int j = 0; j < 4; ++j)
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      const int d = 32 * db + 8 * j + 4 * g;
+    for (int q = 0; q < DB; ++q) {
+      const int d = 4 * (DB * (2 * j + g) + q);
       if (d >= s.D) continue;
       float4 x = part ? make_float4(0.f, 0.f, 0.f, 0.f) : *reinterpret_cast<float4*>(dq + d);
-      x.x += s.scale * acc[db][4 * j];
-      x.y += s.scale * acc[db][4 * j + 1];
-      x.z += s.scale * acc[db][4 * j + 2];
-      x.w += s.scale * acc[db][4 * j + 3];
+      x = add(x, acc_block(acc, j, q, s.scale));
       *reinterpret_cast<float4*>(dq + d) = x;
     }
   if (any_dirty && !empty)
     for (int c = 0; c < a.t.n; ++c)
-      add_nonfinite(dq, nullptr, (const float*)a.t.k[c] + b * a.t.ksb + hk * a.t.ksh, a.t.kss,
+      add_nonfinite<DB>(dq, nullptr, (const float*)a.t.k[c] + b * a.t.ksb + hk * a.t.ksh, a.t.kss,
                     visible_keys(s, first_pos, a.t.k_offset[c]) / kT * kT, visible_keys(s, qpos, a.t.k_offset[c]), s.D, g, true);
 }
 
@@ -599,31 +626,25 @@ __device__ __forceinline__ void bwd_dkv_f32(const BwdArgs& a, DkvShared<DP>& sm,
   float* out_k = (share ? f32_kv_part(a.kv_parts, s, a.t.n, share, c, 0) : a.dk[c]) + orow;
   float* out_v = (share ? f32_kv_part(a.kv_parts, s, a.t.n, share, c, 1) : a.dv[c]) + orow;
 #pragma unroll
-  for (int db = 0; db < DB; ++db)
+  for (int j = 0; j < 4; ++j)
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      const int d = 32 * db + 8 * j + 4 * g;
+    for (int q = 0; q < DB; ++q) {
+      const int d = 4 * (DB * (2 * j + g) + q);
       if (d >= s.D) continue;
       float4* pk = reinterpret_cast<float4*>(out_k + d);
       float4* pv = reinterpret_cast<float4*>(out_v + d);
       float4 x = make_float4(0.f, 0.f, 0.f, 0.f), y = x;      // the memory of a partial sum holds nothing yet
       if (share == 0) x = *pk, y = *pv;
-      x.x += s.scale * acc_k[db][4 * j];
-      x.y += s.scale * acc_k[db][4 * j + 1];
-      x.z += s.scale * acc_k[db][4 * j + 2];
-      x.w += s.scale * acc_k[db][4 * j + 3];
-      y.x += acc_v[db][4 * j];
-      y.y += acc_v[db][4 * j + 1];
-      y.z += acc_v[db][4 * j + 2];
-      y.w += acc_v[db][4 * j + 3];
+      x = add(x, acc_block(acc_k, j, q, s.scale));
+      y = add(y, acc_block(acc_v, j, q, 1.f));
       *pk = x;
       *pv = y;
     }
   if (any_dirty)
     for (int h = hk * G; h < (hk + 1) * G; ++h) {
       const int hi = min(s.Sq, (wg_all + kT - 1) / kT * kT);
-      add_nonfinite(out_k, nullptr, (const float*)a.q.ptr + b * a.q.sb + h * a.q.sh, a.q.ss, key_first, hi, s.D, g, true);
-      add_nonfinite(out_v, nullptr, (const float*)a.d_o.ptr + b * a.d_o.sb + h * a.d_o.sh, a.d_o.ss, key_first, hi, s.D, g, false);
+      add_nonfinite<DB>(out_k, nullptr, (const float*)a.q.ptr + b * a.q.sb + h * a.q.sh, a.q.ss, key_first, hi, s.D, g, true);
+      add_nonfinite<DB>(out_v, nullptr, (const float*)a.d_o.ptr + b * a.d_o.sb + h * a.d_o.sh, a.d_o.ss, key_first, hi, s.D, g, false);
     }
 }
 

@@ -158,6 +158,30 @@ def test_values_that_are_no_numbers_stay_behind_the_mask():
     assert torch.isposinf(dv[:, :bad + 1, :, 9]).all()
 
 
+@pytest.mark.parametrize("D", [32, 64, 88, 128, 136, 192, 256])
+def test_no_numbers_behind_the_mask_in_every_block_of_columns(D):
+    """A lane owns blocks of neighbouring columns, as many as the padded head size has multiples of 32: an infinity in any of them
+    reaches the rows that see it, once, and no other column."""
+    w = si.Workload("f32_cols", 313, "f32", 1, 1, 1, D, 40, 40, 1, 0, True, True)
+    q, ks, vs, d_o = upload(si.make_inputs(w))
+    bad, cols = 21, sorted({c for b in range(0, D, 16) for c in (b, b + 7, min(b + 13, D - 1)) if c < D})
+    rest = [d for d in range(D) if d not in cols]
+    v2, d2 = vs[0].clone(), d_o.clone()
+    v2[:, bad, :, cols] = float("inf")
+    d2[:, bad, :, cols] = float("-inf")
+    o, lse, _ = st.st_ring_fwd(q, ks, vs, 0, [0], True, w.scale, [0])
+    o2, _, low = st.st_ring_fwd(q, ks, [v2], 0, [0], True, w.scale, [0])
+    assert torch.equal(o2[:, :bad], o[:, :bad]) and torch.equal(o2[..., rest], o[..., rest]) and torch.equal(low, o2)
+    assert torch.isposinf(o2[:, bad:][..., cols]).all()
+    out = []
+    for x in (d_o, d2):
+        g = [torch.zeros_like(o), torch.zeros_like(ks[0]), torch.zeros_like(vs[0])]
+        st.st_ring_bwd(q, ks, vs, x, o, lse, 0, [0], True, w.scale, [0], g[0], [g[1]], [g[2]])
+        out.append(g[2])
+    assert torch.equal(out[0][:, bad + 1:], out[1][:, bad + 1:]) and torch.equal(out[0][..., rest], out[1][..., rest])
+    assert torch.isneginf(out[1][:, :bad + 1][..., cols]).all()
+
+
 @pytest.mark.parametrize("D,Sq,Sk", [(72, 45, 70), (128, 33, 33), (256, 63, 40), (64, 1, 1)])
 def test_infinities_in_the_last_row_of_a_ragged_tile(D, Sq, Sk):
     """Every query sees the last key and every key the last query; rows that a ragged tile lacks must not multiply what they
