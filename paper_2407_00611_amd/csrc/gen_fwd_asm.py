@@ -13,7 +13,7 @@ It writes O = acc / l, lse and, where asked for, O rounded to bf16; query rows b
 Masked tiles are the last S_NM of the walk.  The loop exists twice: the first copy has no masks and leaves for the
 second where a block of a masked tile comes up (the compare that ends a loop without masks does it, so whole tiles
 pay nothing; a test of its own in every 32-key block cost 1.4 % at head size 64); the second copy tests every block
-and calls an out-of-line routine that overwrites the invisible exponents with -inf before their maximum is taken.
+and calls an out-of-line routine that overwrites the invisible exponents with -inf before their exponentials are.
 The ragged end of a chunk is read as the chunk's last 64 rows, with the rows of the tile before it masked, so no
 load leaves the chunk.  Where no tile is visible to all rows, a row may meet its first visible key late: its
 reference starts at zero and is set to its first finite block maximum by the mask routine (its accumulators are

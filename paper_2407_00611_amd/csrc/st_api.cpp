@@ -1013,7 +1013,8 @@ static int fwd_states_most(const st_ring_desc* d) {
 //   forward, fused:    partial O and partial lse, once (when more than one launch is needed) or once per
 //                      split of an under-filled launch: [O_0, lse_0, O_1, ...]
 //   backward:          Delta, the tile counters of the dK/dV launch (kQueueInts ints), for the bf16 dtype
-//                      Q' = bf16(Q scale log2 e), dense [B,Sq,Hq,D], and the partial sums of an under-filled dQ launch
+//                      Q' = bf16(Q scale log2 e), dense [B,Sq,Hq,D], and the partial sums of
+//                      under-filled dQ and dK/dV launches (at most kPartsMost)
 static size_t bwd_base_bytes(const st_ring_desc* d) {
   const size_t n_o = align_up((size_t)d->B * d->Sq * d->Hq * d->D * sizeof(float), 256);
   return align_up((size_t)d->B * d->Sq * d->Hq * sizeof(float), 256) + align_up(st::kQueueInts * sizeof(int32_t), 256) +
