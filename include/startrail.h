@@ -236,7 +236,9 @@ st_status st_schedule_report(int32_t P, int32_t C, int64_t B, int64_t N, int64_t
  * workspace: device, >= st_ring_workspace_bytes(desc, mode, backward) bytes, 256-byte aligned.  Its contents
  *   are the library's (partial states, Delta, the tile counters of the dK/dV launch, the scaled copy of Q, partial
  *   sums of backward launches that would leave part of the chip idle) and mean nothing between calls; calls that share a
- *   workspace must be ordered on one stream. */
+ *   workspace must be ordered on one stream.  Sizes depend on the whole descriptor, under a causal mask on the positions
+ *   too.  What is there beyond that size changes nothing; with less room a backward runs on fewer workgroups, down to the
+ *   room its Delta, counters and copy of Q need. */
 size_t st_ring_workspace_bytes(const st_ring_desc* desc, int32_t mode, int32_t backward);
 
 st_status st_ring_fwd(const st_ring_desc* desc, const st_tensor* q, const int32_t* order,
@@ -255,10 +257,10 @@ st_status st_ring_bwd(const st_ring_desc* desc, const st_tensor* q, const st_ten
 
 /* st_ring_bwd for callers that cannot allocate device memory or hand over a workspace: code under HIP graph
  * capture, tight serving or training loops, harnesses that forbid hipMalloc.  Same arguments and results as
- * st_ring_bwd (bit for bit) without the workspace: Delta, the tile counters of the dK/dV launch and the scaled
- * copy of Q live in a static device array of st_ring_bwd_noalloc_max_bytes() = 40 MiB that every GPU the library
- * runs on holds until the process ends.  The call allocates and frees nothing (no hipMalloc / hipFree, no
- * allocating library routine); the array's device address is looked up once per device, on the first call.
+ * st_ring_bwd with a workspace of st_ring_workspace_bytes() (bit for bit) without one: Delta, the tile counters of the
+ * dK/dV launch and the scaled copy of Q live in a static device array of st_ring_bwd_noalloc_max_bytes() = 40 MiB that
+ * every GPU the library runs on holds until the process ends.  The call allocates and frees nothing (no hipMalloc /
+ * hipFree, no allocating library routine); the array's device address is looked up once per device, on the first call.
  * A share whose Delta, counters and copy of Q exceed the array returns ST_ERR_WORKSPACE and enqueues nothing;
  * partial sums of launches that are split over more workgroups have a second static array of 64 MiB, which is also the most
  * that st_ring_bwd uses of its workspace for them.  Every call on a GPU uses

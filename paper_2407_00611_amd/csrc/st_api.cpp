@@ -10,6 +10,7 @@
 #include <vector>
 
 #include "st_internal.h"
+#include "st_testing.h"
 
 namespace {
 
@@ -493,6 +494,12 @@ BwdSplit bwd_splits(const st::Shape& s, int dtype, const int64_t* k_offset, int 
   BwdSplit r;
   const bool bf16 = dtype == ST_BF16;
   if ((bf16 && s.D != 128 && s.D != 64) || n < 1 || n > st::kMaxTable || s.B < 1 || s.Sq < 1 || s.Sk < 1 || s.Hq < 1 || s.Hkv < 1) return r;
+  int64_t sorted[st::kMaxTable];                       // the plan does not depend on the order of the table
+  if (s.causal && k_offset != nullptr) {
+    std::copy(k_offset, k_offset + n, sorted);
+    std::sort(sorted, sorted + n);
+    k_offset = sorted;
+  }
   QueryWalk walk;
   const int64_t wgs = (int64_t)s.B * s.Hq * st::query_tiles(s, bf16 ? st::kQTileFastRows : 32).count();
   const bool plan_dq = wgs < 1024 && (!bf16 || s.Sk >= st::kQTileFastKeys);
@@ -1021,26 +1028,77 @@ static size_t bwd_base_bytes(const st_ring_desc* d) {
          (d->dtype == ST_BF16 ? align_up(n_o / 2, 256) : 0);
 }
 
-// room for partial sums of a ring backward: never more than st_ring_bwd_noalloc has, so that both entry points compute the
-// same sums
+// What a workspace has beyond the rest, for the partial sums of a ring backward
 static size_t ring_room(const st_ring_desc* d, size_t workspace_bytes) {
   const size_t base = bwd_base_bytes(d);
   return workspace_bytes > base ? std::min(workspace_bytes - base, kPartsMost) : 0;
+}
+
+// Partial sums to provide for.  Under a causal mask the plan depends on where the chunks lie: as a caller visits them who lists
+// all of them, in one launch or a launch each, and where every row sees them, so that what was sized for one shard does for
+// its neighbours.  Without one it depends on their number, and any subset may be visited.
+static size_t ring_parts_bytes(const st_ring_desc* d, int mode) {
+  const st::Shape s = shape_of(d);
+  const bool fused = mode == ST_RING_FUSED;
+  const int n_chunks = std::min(d->n_chunks, ST_MAX_CHUNKS), per_launch = std::min(n_chunks, fused ? st::kMaxTable : 1);
+  size_t most = 0;
+  auto look = [&](const int64_t* k_offset, int n) { most = std::max(most, bwd_splits(s, d->dtype, k_offset, n, kPartsMost).bytes); };
+  if (!d->causal || d->k_offset == nullptr) {
+    for (int n = 1; n <= per_launch; ++n) look(nullptr, n);
+    return most;
+  }
+  look(nullptr, per_launch);
+  for (int hidden = 0; hidden <= (fused && d->dtype == ST_BF16); ++hidden) {       // without and with the chunks that nobody sees
+    int64_t k_offset[st::kMaxTable];
+    int n = 0;
+    bool whole = false;                                // one that every row sees has been looked at
+    for (int j = 0; j < n_chunks; ++j) {
+      if (!hidden && chunk_invisible(d, j)) continue;
+      if (!fused && d->k_offset[j] + d->Sk - 1 <= d->q_offset) {
+        if (whole) continue;
+        whole = true;
+      }
+      k_offset[n++] = d->k_offset[j];
+      if (n == per_launch) {
+        look(k_offset, n);
+        n = 0;
+      }
+    }
+    if (n > 0) look(k_offset, n);
+  }
+  return most;
+}
+
+// The chunks of a backward launch and whether ring_parts_bytes has looked at such a one
+struct RingVisit {
+  int chunk[ST_MAX_CHUNKS], n = 0, hidden = 0;
+  void add(const st_ring_desc* d, int j) {
+    chunk[n++] = j;
+    hidden += chunk_invisible(d, j);
+  }
+  bool provided(const st_ring_desc* d, int mode) const {
+    if (mode != ST_RING_FUSED || !d->causal) return true;
+    if (n > st::kMaxTable) return false;
+    int seen = 0;
+    for (int j = 0; j < d->n_chunks; ++j) seen += !chunk_invisible(d, j);
+    return n - hidden == seen && (hidden == 0 || n == d->n_chunks);
+  }
+};
+
+// The plan of a launch over n chunks.  It does not depend on the room beyond what st_ring_workspace_bytes provides for, so that
+// st_ring_bwd with that much and st_ring_bwd_noalloc compute the same sums; with less it is the best one that fits.
+static BwdSplit ring_plan(const st_ring_desc* d, int mode, const int64_t* k_offset, int n, bool provided, size_t room) {
+  const st::Shape s = shape_of(d);
+  BwdSplit r = bwd_splits(s, d->dtype, k_offset, n, kPartsMost);
+  if (!provided && r.bytes > 0) room = std::min(room, ring_parts_bytes(d, mode));
+  return r.bytes <= room ? r : bwd_splits(s, d->dtype, k_offset, n, room);
 }
 
 size_t st_ring_workspace_bytes(const st_ring_desc* d, int32_t mode, int32_t backward) {
   if (d == nullptr) return 0;
   const size_t n_o = align_up((size_t)d->B * d->Sq * d->Hq * d->D * sizeof(float), 256);
   const size_t n_l = align_up((size_t)d->B * d->Sq * d->Hq * sizeof(float), 256);
-  if (backward) {
-    // any subset of the chunks may be visited, in one launch or in several; under a causal mask the plan depends on where they lie
-    size_t most = 0;
-    if (d->causal && bwd_splittable(shape_of(d), d->dtype)) most = kPartsMost;
-    else if (!d->causal)
-      for (int n = 1; n <= (mode == ST_RING_FUSED ? d->n_chunks : 1) && n <= st::kMaxTable; ++n)
-        most = std::max(most, bwd_splits(shape_of(d), d->dtype, nullptr, n, kPartsMost).bytes);
-    return bwd_base_bytes(d) + most;
-  }
+  if (backward) return bwd_base_bytes(d) + ring_parts_bytes(d, mode);
   if (mode == ST_RING_STEPWISE) return 2 * (n_o + n_l);
   return (size_t)fwd_states_most(d) * (n_o + n_l);
 }
@@ -1205,7 +1263,7 @@ st_status st_ring_bwd_noalloc(const st_ring_desc* d, const st_tensor* q, const s
                               int32_t mode, float* dq_acc, float* const* dk_acc, float* const* dv_acc, void* hip_stream) {
   if (d == nullptr) return fail(ST_ERR_INVALID_ARG, "null descriptor");
   ST_TRY(check_shape(d->dtype, d->B, d->Hq, d->Hkv, d->D, d->Sq, d->Sk));
-  const size_t need = bwd_base_bytes(d);               // a split of the dQ pass never needs more than the scratch
+  const size_t need = bwd_base_bytes(d);               // partial sums have their own array
   if (need > kScratchBytes)
     return fail(ST_ERR_WORKSPACE, "st_ring_bwd_noalloc: this share needs %zu bytes of scratch, the library's static scratch holds %zu; use st_ring_bwd with a workspace", need, kScratchBytes);
   void *ws = nullptr, *parts = nullptr;
@@ -1260,7 +1318,7 @@ static st_status ring_bwd(const st_ring_desc* d, const st_tensor* q, const st_te
   // (their key tiles find no query block), or by launches of their own where every chunk has its own (step-wise), and where
   // there are no query rows at all.
   const bool hidden_too = mode == ST_RING_FUSED && d->dtype == ST_BF16 && !no_rows && n_kv > 0;
-  int vis[ST_MAX_CHUNKS], n = 0;
+  RingVisit vis;
   for (int x = 0; x < n_visit; ++x) {
     const int j = order[x];
     void* lk = dk_lowp ? dk_lowp[j] : nullptr;
@@ -1273,7 +1331,7 @@ static st_status ring_bwd(const st_ring_desc* d, const st_tensor* q, const st_te
       ST_TRY(check_f32("dk_acc[j]", dk_acc[j], n_kv));
       ST_TRY(check_f32("dv_acc[j]", dv_acc[j], n_kv));
     }
-    if (!hidden || (hidden_too && (assign || lk))) vis[n++] = j;
+    if (!hidden || (hidden_too && (assign || lk))) vis.add(d, j);
   }
   if (!hidden_too && n_kv > 0 && (assign || dk_lowp)) {
     st::KvTables h;                                  // of the hidden chunks, as many as one launch takes
@@ -1310,18 +1368,19 @@ static st_status ring_bwd(const st_ring_desc* d, const st_tensor* q, const st_te
     ST_HIP(st::launch_delta(a.d_o, d->dtype, view_of(o), o_dtype, delta, d->B, d->Sq, d->Hq, d->D, stream), "delta launch");
   }
   const int per_launch = mode == ST_RING_FUSED ? st::kMaxTable : 1;
-  for (int x0 = 0; x0 < n; x0 += per_launch) {
-    const int cnt = n - x0 < per_launch ? n - x0 : per_launch;
+  const bool provided = vis.provided(d, mode);
+  for (int x0 = 0; x0 < vis.n; x0 += per_launch) {
+    const int cnt = std::min(vis.n - x0, per_launch);
     a.t.n = cnt;
     a.queue_clean = d->dtype == ST_BF16 && x0 == 0;
     for (int x = 0; x < cnt; ++x) {
-      const int j = vis[x0 + x];
+      const int j = vis.chunk[x0 + x];
       a.t.k[x] = d->k_ptr[j]; a.t.v[x] = d->v_ptr[j]; a.t.k_offset[x] = d->k_offset[j];
       a.dk[x] = dk_acc[j]; a.dv[x] = dv_acc[j];
       a.dk_lowp[x] = dk_lowp ? dk_lowp[j] : nullptr;
       a.dv_lowp[x] = dk_lowp ? dv_lowp[j] : nullptr;
     }
-    set_splits(a, bwd_splits(a.s, d->dtype, a.t.k_offset, cnt, parts_bytes), parts);
+    set_splits(a, ring_plan(d, mode, a.t.k_offset, cnt, provided, parts_bytes), parts);
     a.kv_assign = assign ? ~0ull : 0ull;
     if (d->dtype != ST_BF16 && assign)              // the fp32 kernels only add
       for (int x = 0; x < cnt; ++x) {
@@ -1331,4 +1390,28 @@ static st_status ring_bwd(const st_ring_desc* d, const st_tensor* q, const st_te
     ST_HIP(launch_bwd(d->dtype, a, stream), "backward launch");
   }
   return ST_OK;
+}
+
+extern "C" int st_testing_bwd_plan(const st_ring_desc* d, const int32_t* order, int32_t n_visit, int32_t mode, int32_t assign,
+                                   int64_t workspace_bytes, int64_t* out, int32_t max_out) {
+  if (check_shape(d->dtype, d->B, d->Hq, d->Hkv, d->D, d->Sq, d->Sk) != ST_OK || d->n_chunks < 1 || d->n_chunks > ST_MAX_CHUNKS) return -1;
+  RingVisit vis;
+  for (int x = 0; x < n_visit; ++x)
+    if (!chunk_invisible(d, order[x]) || (assign && mode == ST_RING_FUSED && d->dtype == ST_BF16)) vis.add(d, order[x]);
+  const size_t room = workspace_bytes < 0 ? kPartsMost : ring_room(d, (size_t)workspace_bytes);
+  const int per_launch = mode == ST_RING_FUSED ? st::kMaxTable : 1;
+  int written = 0;
+  for (int x0 = 0; x0 < vis.n; x0 += per_launch) {
+    int64_t k_offset[st::kMaxTable];
+    const int cnt = std::min(vis.n - x0, per_launch);
+    for (int x = 0; x < cnt; ++x) k_offset[x] = d->k_offset[vis.chunk[x0 + x]];
+    const BwdSplit p = ring_plan(d, mode, k_offset, cnt, vis.provided(d, mode), room);
+    const int64_t v[] = {cnt, p.dq.n, p.dq.total, p.dq.own0, (int64_t)p.dq.less1[0], (int64_t)p.dq.less1[1], (int64_t)p.dq.less1[2],
+                         (int64_t)p.dq.less1[3], p.kv_each, p.kv_items, p.pair, (int64_t)p.bytes};
+    for (int64_t y : v) {
+      if (written >= max_out) return -1;
+      out[written++] = y;
+    }
+  }
+  return written;
 }

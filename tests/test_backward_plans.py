@@ -1,0 +1,92 @@
+"""How ring backwards are split over workgroups (host logic, no launch): st_ring_bwd with the workspace the library asks for and
+st_ring_bwd_noalloc promise the same bits, so both have to make the same plan, for every dtype, mask, mode and visited subset;
+and what the plan stores has to fit what was asked for, which is no more than some plan of the share can use."""
+import ctypes as C
+import random
+
+import pytest
+
+from paper_2407_00611_amd import api
+
+F32, BF16, STEPWISE, FUSED = 0, 1, 0, 1
+I64, I32 = C.c_int64, C.c_int32
+_plan = C.CDLL(api.library_path()).st_testing_bwd_plan
+_plan.restype, _plan.argtypes = C.c_int, [C.POINTER(api.st_ring_desc), C.POINTER(I32), I32, I32, I32, I64, C.POINTER(I64), I32]
+PER_LAUNCH = 12                                                # values per launch, the last one the bytes of partial sums
+
+
+class Share:
+    def __init__(self, dtype, B, Hq, Hkv, D, Sq, Sk, offsets, q_offset=0, causal=True, seg=0, q2=0):
+        n = len(offsets)
+        self.offsets = (I64 * n)(*offsets)
+        self.tables = (C.c_void_p * n)(*[0x10000] * n)
+        self.d = api.st_ring_desc(dtype, B, Hq, Hkv, D, Sq, Sk, q_offset, int(causal), 0.1, n, self.tables, self.tables,
+                                  Sk * Hkv * D, Hkv * D, D, Sk * Hkv * D, Hkv * D, D, self.offsets, seg, q2)
+        up = lambda x: (x + 255) // 256 * 256
+        self.base = up(B * Sq * Hq * 4) + 1024 + (up(B * Sq * Hq * D * 2) if dtype == BF16 else 0)     # Delta, counters, scaled Q
+        self.text = f"{('f32', 'bf16')[dtype]} {B} x {Hq}/{Hkv} x {D}, {Sq} rows at {q_offset} ({seg}, {q2}), {n} x {Sk}, causal {causal}"
+
+    def size(self, mode):
+        return int(api._lib.st_ring_workspace_bytes(C.byref(self.d), mode, 1))
+
+    def plan(self, order, mode, assign, workspace):
+        out = (I64 * (PER_LAUNCH * 256))()
+        n = _plan(C.byref(self.d), (I32 * max(len(order), 1))(*order), len(order), mode, int(assign), workspace, out, len(out))
+        assert n >= 0
+        return [tuple(out[i:i + PER_LAUNCH]) for i in range(0, n, PER_LAUNCH)]
+
+
+def _check(share, rng):
+    n = len(share.offsets)
+    some = rng.sample(range(n), rng.randint(1, n))
+    for mode in (FUSED, STEPWISE):
+        size = share.size(mode)
+        for order in (list(range(n)), list(reversed(range(n))), some):
+            for assign in (False, True):
+                asked = share.plan(order, mode, assign, size)
+                assert asked == share.plan(order, mode, assign, -1), f"noalloc plans otherwise: {share.text}, order {order}, mode {mode}"
+                assert asked == share.plan(order, mode, assign, size + (200 << 20)), f"more room, another plan: {share.text}"
+                assert all(x[-1] <= size - share.base for x in asked), share.text
+                less = share.base + max([x[-1] for x in asked], default=0) // 2     # short of it: fewer workgroups, not more memory
+                assert all(x[-1] <= less - share.base for x in share.plan(order, mode, assign, less)), share.text
+
+
+def _ring(dtype, B, Hq, Hkv, D, S, n, rank, causal=True):
+    return Share(dtype, B, Hq, Hkv, D, S, S, [S * j for j in range(n)], S * rank, causal)
+
+
+@pytest.mark.parametrize("share", [
+    _ring(F32, 1, 24, 3, 64, 678, 3, 0), _ring(F32, 2, 16, 2, 128, 512, 8, 0),        # 512 to 1023 query tiles, few key tiles
+    Share(BF16, 1, 32, 4, 64, 4096, 32768, [0]),                                       # many keys, few of them seen
+    _ring(BF16, 1, 1, 1, 128, 694, 8, 0, False), _ring(BF16, 1, 4, 4, 64, 2408, 2, 0, False)],  # no mask
+    ids=lambda s: s.text)
+def test_shares_whose_two_plans_differed(share):
+    assert any(x[8] > 0 or x[9] > 1 or x[1] > 1 for x in share.plan(list(range(len(share.offsets))), FUSED, False, -1)), "meant to be split"
+    _check(share, random.Random(1))
+
+
+def test_random_shares():
+    rng = random.Random(2407)
+    split = 0
+    for _ in range(400):
+        dtype = rng.choice([F32, BF16])
+        D = rng.choice([32, 64, 80, 128, 256]) if dtype == F32 else rng.choice([64, 128])
+        hkv, g, B = rng.choice([1, 1, 2, 3, 8]), rng.choice([1, 1, 2, 4, 8]), rng.choice([1, 1, 2])
+        S, n = int(2 ** rng.uniform(4, 10 if dtype == F32 else 13)), rng.choice([1, 2, 3, 4, 8, 16, 70])
+        rank, causal = rng.randrange(n), rng.random() < 0.7
+        if rng.random() < 0.25:                                # two runs of rows
+            m = max(S // 2, 1)
+            share = Share(dtype, B, hkv * g, hkv, D, 2 * m, m, [m * j for j in range(2 * n)], rank * m, causal, m, (2 * n - 1 - rank) * m)
+        elif rng.random() < 0.3:                               # chunks of another length, anywhere
+            share = Share(dtype, B, hkv * g, hkv, D, S, max(1, int(S * rng.uniform(0.1, 4))), [rng.randint(-S, 4 * S) for _ in range(n)], rng.randint(0, 2 * S), causal)
+        else:
+            share = _ring(dtype, B, hkv * g, hkv, D, S, n, rank, causal)
+        split += any(x[-1] > 0 for x in share.plan(list(range(len(share.offsets))), FUSED, False, -1))
+        _check(share, rng)
+    assert split > 100
+
+
+def test_small_shares_ask_for_little():
+    assert _ring(F32, 1, 1, 1, 64, 128, 4, 3).size(FUSED) <= 1 << 20              # 40 KB of it Delta and what surrounds it
+    assert _ring(F32, 1, 8, 2, 128, 512, 8, 7).size(FUSED) <= 48 << 20
+    assert _ring(BF16, 1, 4, 4, 64, 69, 8, 7).size(FUSED) <= 2 << 20
