@@ -599,13 +599,6 @@ BwdSplit bwd_splits(const st::Shape& s, int dtype, const int64_t* k_offset, int 
   r.bytes = r.pair ? dq_bytes + slot_bytes(kv) : std::max(dq_bytes, slot_bytes(kv));
   return r;
 }
-// whether some launch of such a share has too few workgroups (see bwd_splits)
-bool bwd_splittable(const st::Shape& s, int dtype) {
-  if (s.B < 1 || s.Sq < 1 || s.Sk < 1) return false;
-  const bool bf16 = dtype == ST_BF16;
-  const int64_t wgs = (int64_t)s.B * s.Hq * st::query_tiles(s, bf16 ? st::kQTileFastRows : 32).count();
-  return wgs < 512 || (bf16 && (int64_t)s.B * s.Hkv * ((s.Sk + st::kDkvFastKeys - 1) / st::kDkvFastKeys) < 512);
-}
 void set_splits(st::BwdArgs& a, const BwdSplit& x, void* parts) {
   a.shares = x.dq;
   a.kv_each = x.kv_each;
@@ -830,11 +823,22 @@ st_status st_attn_delta(const st_block_desc* d, const st_tensor* d_o, const st_t
 // The dQ of this call is the same with and without a workspace, bit for bit, so that pass is never split here.
 static size_t block_base_bytes(const st_block_desc* d) { return align_up((size_t)d->B * d->Sq * d->Hq * d->D * 2, 256); }
 
+// as with a ring's (ring_plan): one plan whatever the room, unless that is short
+static BwdSplit block_plan(const st::Shape& s, int dtype, int64_t k_offset, size_t room) {
+  const BwdSplit r = bwd_splits(s, dtype, &k_offset, 1, kPartsMost, false);
+  return r.bytes <= room ? r : bwd_splits(s, dtype, &k_offset, 1, room, false);
+}
+
 size_t st_attn_block_bwd_workspace_bytes(const st_block_desc* d) {
   if (d == nullptr || d->dtype != ST_BF16 || d->B <= 0 || d->Sq <= 0 || d->Hq <= 0 || d->D <= 0) return 0;
-  // one workspace serves every chunk of a ring: under a causal mask the plan depends on where the chunk lies
   const st::Shape s = shape_of(d);
-  return block_base_bytes(d) + (!d->causal ? bwd_splits(s, d->dtype, nullptr, 1, kPartsMost, false).bytes : bwd_splittable(s, d->dtype) ? kPartsMost : 0);
+  size_t most = bwd_splits(s, d->dtype, nullptr, 1, kPartsMost, false).bytes;
+  if (d->causal)
+    // one workspace serves every chunk of a ring, and under a mask the plan depends on where the chunk lies: seen whole (above),
+    // here, on the diagonal of either run of rows, and seen by the second run only
+    for (const int64_t k_offset : {d->k_offset, d->q_offset, d->q_offset2, d->q_offset + d->q_seg})
+      most = std::max(most, bwd_splits(s, d->dtype, &k_offset, 1, kPartsMost, false).bytes);
+  return block_base_bytes(d) + most;
 }
 
 st_status st_attn_block_bwd(const st_block_desc* d, const st_tensor* q, const st_tensor* k, const st_tensor* v,
@@ -872,7 +876,7 @@ st_status st_attn_block_bwd(const st_block_desc* d, const st_tensor* q, const st
     ST_HIP(st::launch_scale_q(a.q, workspace, d->B, d->Sq, d->Hq, d->D, d->scale, (hipStream_t)hip_stream), "scaled-Q launch");
     a.qs = workspace;
     const size_t left = workspace_bytes - block_base_bytes(d);
-    set_splits(a, bwd_splits(a.s, d->dtype, a.t.k_offset, 1, left < kPartsMost ? left : kPartsMost, false), (char*)workspace + block_base_bytes(d));
+    set_splits(a, block_plan(a.s, d->dtype, d->k_offset, std::min(left, kPartsMost)), (char*)workspace + block_base_bytes(d));
   }
   ST_HIP(launch_bwd(d->dtype, a, (hipStream_t)hip_stream), "st_attn_block_bwd launch");
   return ST_OK;
@@ -1398,14 +1402,15 @@ extern "C" int st_testing_bwd_plan(const st_ring_desc* d, const int32_t* order, 
   RingVisit vis;
   for (int x = 0; x < n_visit; ++x)
     if (!chunk_invisible(d, order[x]) || (assign && mode == ST_RING_FUSED && d->dtype == ST_BF16)) vis.add(d, order[x]);
-  const size_t room = workspace_bytes < 0 ? kPartsMost : ring_room(d, (size_t)workspace_bytes);
+  const size_t base = mode < 0 ? align_up((size_t)d->B * d->Sq * d->Hq * d->D * 2, 256) : bwd_base_bytes(d);
+  const size_t room = workspace_bytes < 0 ? kPartsMost : (size_t)workspace_bytes > base ? std::min((size_t)workspace_bytes - base, kPartsMost) : 0;
   const int per_launch = mode == ST_RING_FUSED ? st::kMaxTable : 1;
   int written = 0;
   for (int x0 = 0; x0 < vis.n; x0 += per_launch) {
     int64_t k_offset[st::kMaxTable];
     const int cnt = std::min(vis.n - x0, per_launch);
     for (int x = 0; x < cnt; ++x) k_offset[x] = d->k_offset[vis.chunk[x0 + x]];
-    const BwdSplit p = ring_plan(d, mode, k_offset, cnt, vis.provided(d, mode), room);
+    const BwdSplit p = mode < 0 ? block_plan(shape_of(d), d->dtype, k_offset[0], room) : ring_plan(d, mode, k_offset, cnt, vis.provided(d, mode), room);
     const int64_t v[] = {cnt, p.dq.n, p.dq.total, p.dq.own0, (int64_t)p.dq.less1[0], (int64_t)p.dq.less1[1], (int64_t)p.dq.less1[2],
                          (int64_t)p.dq.less1[3], p.kv_each, p.kv_items, p.pair, (int64_t)p.bytes};
     for (int64_t y : v) {

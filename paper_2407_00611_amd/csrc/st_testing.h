@@ -17,7 +17,7 @@ extern "C" {
 int st_testing_set(const char* name, double value);
 
 /* How a ring backward over the listed chunks would be split, without launching anything (host only): st_ring_bwd(_last) with a
- * workspace of so many bytes, or st_ring_bwd_noalloc (workspace_bytes < 0).  Writes 12 values per launch to out (host): chunks;
+ * workspace of so many bytes, or st_ring_bwd_noalloc (workspace_bytes < 0); mode -1: st_attn_block_bwd of each.  Writes 12 values per launch to out (host): chunks;
  * dQ: most shares of a query tile, shares of a head where the tiles differ, first shares that add themselves, shares per tile
  * (4 words); dK/dV: blocks per share, shares; both passes in one launch; bytes of partial sums.  Returns the number of values,
  * or -1 if max_out are too few or the descriptor has no kernel. */

@@ -90,3 +90,29 @@ def test_small_shares_ask_for_little():
     assert _ring(F32, 1, 1, 1, 64, 128, 4, 3).size(FUSED) <= 1 << 20              # 40 KB of it Delta and what surrounds it
     assert _ring(F32, 1, 8, 2, 128, 512, 8, 7).size(FUSED) <= 48 << 20
     assert _ring(BF16, 1, 4, 4, 64, 69, 8, 7).size(FUSED) <= 2 << 20
+
+
+def _block_size(share, k_offset):
+    d = share.d
+    b = api.st_block_desc(d.dtype, d.B, d.Hq, d.Hkv, d.D, d.Sq, d.Sk, d.q_offset, k_offset, d.causal, d.scale, d.q_seg, d.q_offset2)
+    return int(api._lib.st_attn_block_bwd_workspace_bytes(C.byref(b)))
+
+
+def test_block_backwards():
+    """One workspace, sized for any chunk of the ring, holds the plan of every other one; and it is no larger than some plan uses."""
+    rng = random.Random(611)
+    for _ in range(300):
+        D, hkv, g, B = rng.choice([64, 128]), rng.choice([1, 1, 2, 3, 8]), rng.choice([1, 1, 2, 4, 8]), rng.choice([1, 1, 2])
+        S, n = int(2 ** rng.uniform(4, 13)), rng.choice([1, 2, 3, 8])
+        rank, causal, m = rng.randrange(n), rng.random() < 0.7, max(S // 2, 1)
+        share = _ring(BF16, B, hkv * g, hkv, D, S, n, rank, causal) if rng.random() < 0.7 else \
+            Share(BF16, B, hkv * g, hkv, D, 2 * m, m, [m * j for j in range(2 * n)], rank * m, causal, m, (2 * n - 1 - rank) * m)
+        order = list(range(len(share.offsets)))
+        best = share.plan(order, -1, False, -1)
+        base = (B * share.d.Sq * hkv * g * D * 2 + 255) // 256 * 256
+        for j in order:
+            size = _block_size(share, share.offsets[j])
+            assert share.plan(order, -1, False, size) == best == share.plan(order, -1, False, size + (200 << 20)), share.text
+            assert causal or size - base == max(x[-1] for x in best), share.text
+    assert _block_size(_ring(BF16, 1, 2, 2, 128, 320, 2, 1), 0) <= 1 << 20
+    assert _block_size(_ring(BF16, 2, 16, 16, 64, 512, 8, 5), 0) <= 4 << 20
