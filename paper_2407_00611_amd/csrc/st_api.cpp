@@ -1007,16 +1007,21 @@ static int fwd_states_small(const st_ring_desc* d, int n_visible) {
   return (int)n + 1;
 }
 // States to provide for: any subset of the chunks may be visited.  Under a causal mask the tiles with the longest walks may
-// be split where one number for all of them would not be: they have about twice the average.
+// be split where one number for all of them would not be, as the chunks that this shard sees lie; they have about twice the
+// average, so more than twice the chip's workgroups are not provided for.
 static int fwd_states_most(const st_ring_desc* d) {
   const int n_most = d->n_chunks < st::kMaxTable ? d->n_chunks : st::kMaxTable;
   int most = fwd_states_small(d, n_most);
   for (int n = 1; n <= n_most; ++n) most = std::max(most, (int)fwd_shares(d, nullptr, n).n);
-  if (d->causal && fwd_splittable(d, n_most)) {
-    const QueryWalk w = query_walk(shape_of(d), d->dtype, nullptr, n_most);
-    most = std::max(most, (int)std::min<int64_t>({(int64_t)kMaxSplits, (int64_t)w.units[0], (2 * kPlanCus + w.wgs() - 1) / w.wgs()}));
-  }
-  return most;
+  if (!d->causal || d->k_offset == nullptr || !fwd_splittable(d, n_most)) return most;
+  int64_t k_offset[st::kMaxTable];
+  int n = 0;
+  for (int j = 0; j < std::min(d->n_chunks, ST_MAX_CHUNKS) && n <= st::kMaxTable; ++j)
+    if (!chunk_invisible(d, j) && n++ < st::kMaxTable) k_offset[n - 1] = d->k_offset[j];
+  if (n > st::kMaxTable) return most;                  // are never split
+  const int64_t wgs = query_walk(shape_of(d), d->dtype, nullptr, n_most).wgs();
+  const int provided = (int)std::min<int64_t>(kMaxSplits, (2 * kPlanCus + wgs - 1) / wgs);
+  return std::max(most, (int)fwd_shares(d, k_offset, n, std::max(most, provided)).n);
 }
 
 // Workspace layout (each block 256-byte aligned):

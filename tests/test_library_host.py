@@ -136,6 +136,22 @@ def test_forward_workspace_covers_every_visited_subset():
     assert need(64, Sq=4096, Hq=32) == need(1, Sq=4096, Hq=32)  # enough query tiles to fill the chip: never split
 
 
+def test_forward_workspace_of_a_causal_share_holds_what_its_plan_uses():
+    """Tiles with long walks get more workgroups than one number for all of them would give, where that pays; elsewhere no room
+    is asked for it (32 heads x 3801 rows and 16 x 3737 asked for two states and never used them)."""
+    def states(B, Hq, Hkv, D, S, n, rank):
+        off = (C.c_int64 * n)(*[S * j for j in range(n)])
+        ptr = (C.c_void_p * n)(*[0x10000] * n)
+        d = api.st_ring_desc(1, B, Hq, Hkv, D, S, S, S * rank, 1, 0.1, n, ptr, ptr, S * Hkv * D, Hkv * D, D, S * Hkv * D, Hkv * D, D, off, 0, 0)
+        up = lambda x: (x + 255) // 256 * 256
+        size, state = api._lib.st_ring_workspace_bytes(C.byref(d), 1, 0), up(B * S * Hq * D * 4) + up(B * S * Hq * 4)
+        assert size % state == 0
+        return size // state
+
+    assert states(1, 32, 8, 128, 3801, 1, 0) == 1 and states(2, 16, 8, 128, 3737, 2, 0) == 1
+    assert states(1, 8, 2, 128, 7375, 16, 0) == 3          # the tiles at the end of the diagonal chunk
+
+
 def test_ring_bwd_last_validation_fails_before_any_launch():
     """Fake device pointers: the arguments st_ring_bwd_last adds are checked on the host."""
     lib = api._lib
