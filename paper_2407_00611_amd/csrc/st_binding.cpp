@@ -191,13 +191,28 @@ bool tables(PyObject* o, const Ring& r, bool low, void** to) {
   return true;
 }
 
+struct Unlocked {                              // other Python threads run meanwhile
+  PyThreadState* state = PyEval_SaveThread();
+  ~Unlocked() { PyEval_RestoreThread(state); }
+};
 template <typename F>
 PyObject* call(F f) {
   st_status s;
-  Py_BEGIN_ALLOW_THREADS
-  s = f();
-  Py_END_ALLOW_THREADS
+  {
+    Unlocked u;
+    s = f();
+  }
   return PyLong_FromLong(s);
+}
+// Python calls in through C: an exception of a tensor's accessors (memory that may not be touched, a copy on write that does not
+// fit) must not leave here.  Nothing has been called yet then; the general way meets the same exception and raises it.
+template <PyObject* (*F)(PyObject*, PyObject* const*, Py_ssize_t)>
+PyObject* guarded(PyObject* self, PyObject* const* a, Py_ssize_t n) {
+  try {
+    return F(self, a, n);
+  } catch (...) {
+    Py_RETURN_NONE;
+  }
 }
 #define ST_SHORT(cond) \
   if (!(cond)) Py_RETURN_NONE
@@ -368,7 +383,7 @@ PyObject* cast(PyObject*, PyObject* const* a, Py_ssize_t n) {
   return call([&] { return st_cast_from_f32(from, to, count, out, stream); });
 }
 
-#define ST_METHOD(f) {#f, (PyCFunction)(void*)f, METH_FASTCALL, nullptr}
+#define ST_METHOD(f) {#f, (PyCFunction)(void*)guarded<f>, METH_FASTCALL, nullptr}
 PyMethodDef methods[] = {ST_METHOD(ring_fwd), ST_METHOD(ring_bwd), ST_METHOD(block_fwd), ST_METHOD(block_bwd), ST_METHOD(merge),
                          ST_METHOD(combine),  ST_METHOD(delta),    ST_METHOD(cast),      {nullptr, nullptr, 0, nullptr}};
 PyModuleDef module = {PyModuleDef_HEAD_INIT, "_binding", nullptr, -1, methods, nullptr, nullptr, nullptr, nullptr};

@@ -106,3 +106,22 @@ def test_what_is_refused():
         fwd(where=(100, 100, 0))                     # the second run before the first
     with pytest.raises(ValueError):
         st.st_cast_from_f32(o, st.ST_BF16, low[:, :100])
+
+
+def test_a_tensor_whose_memory_may_not_be_touched_raises():
+    """Its accessors throw inside the native half, which is called through C: the error reaches Python as one."""
+    w, q, ks, vs, d_o = _share()
+    src, dst = torch.ones(64, device="cuda"), torch.zeros(64, dtype=torch.bfloat16, device="cuda")
+    barred = torch.ones(64, device="cuda")
+    torch._C._set_throw_on_mutable_data_ptr(barred)
+    with pytest.raises(RuntimeError, match="data pointer"):
+        st.st_cast_from_f32(barred, st.ST_BF16, dst)
+    k = ks[1].clone()
+    torch._C._set_throw_on_mutable_data_ptr(k)
+    o, lse, low = torch.empty(q.shape, device="cuda"), torch.empty((w.B, w.Hq, w.Sq), device="cuda"), torch.empty_like(q)
+    ws = torch.empty(64 << 20, dtype=torch.uint8, device="cuda")
+    with pytest.raises(RuntimeError, match="data pointer"):
+        st.st_ring_fwd(q, [ks[0], k, ks[2]], vs, w.q_where, [w.k_offset(j) for j in range(3)], True, w.scale, [0, 1, 2], o_acc=o, lse=lse,
+                       o_lowp=low, workspace=ws)
+    st.st_cast_from_f32(src, st.ST_BF16, dst)           # and the library goes on
+    assert float(dst.float().sum()) == 64
