@@ -7,11 +7,14 @@ call is enqueued on torch's current stream.  A non-zero status raises StarTrailE
 The calls that a training step makes many times try the native half first (``csrc/st_binding.cpp``),
 which reads plain tensors, lists and numbers in a tenth of the time; what it does not take (it then
 answers None, and has called nothing) goes through ctypes below, which also raises the errors.
+Without it, or with another torch or Python than it was built for, everything goes through ctypes.
 """
 from __future__ import annotations
 
 import ctypes as C
 import os
+import sys
+import warnings
 from typing import List, Optional, Sequence, Tuple
 
 import torch
@@ -119,7 +122,33 @@ def _load() -> C.CDLL:
 
 
 _lib = _load()
-from . import _binding  # noqa: E402  (linked against the library that has just been loaded)
+
+
+class _Declines:
+    """In the place of a native half that is not there or not for this process: leaves every call to ctypes."""
+    built_for = None
+
+    def __getattr__(self, name):
+        return lambda *args: None
+
+
+def _native_half():
+    """csrc/st_binding.cpp, linked against the library that has just been loaded.  It reads torch's and Python's objects as their
+    headers laid them out, so it is taken only where it was built for this torch and this Python."""
+    try:
+        from . import _binding
+    except ImportError as e:
+        warnings.warn(f"calls are marshalled by ctypes, at several times the host time: {e}", RuntimeWarning)
+        return _Declines()
+    here = f"torch {torch.__version__}, Python {sys.version_info.major}.{sys.version_info.minor}"
+    if _binding.built_for != here:
+        warnings.warn(f"calls are marshalled by ctypes, at several times the host time: the native half was built for {_binding.built_for}, "
+                      f"this is {here}", RuntimeWarning)
+        return _Declines()
+    return _binding
+
+
+_binding = _native_half()
 
 EXPORTS = ["st_attn_block_fwd", "st_attn_merge", "st_attn_combine", "st_attn_delta", "st_attn_block_bwd", "st_attn_block_bwd_workspace_bytes", "st_cast_from_f32",
            "st_visit_order", "st_team_visit_order", "st_schedule_report", "st_ring_workspace_bytes", "st_ring_fwd", "st_ring_bwd", "st_ring_bwd_noalloc", "st_ring_bwd_noalloc_max_bytes", "st_ring_bwd_last", "st_device_facts", "st_mfma_probe", "st_mfma_probe_mixes", "st_mfma_probe_mix_name", "st_profile_begin",

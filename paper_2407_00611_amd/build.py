@@ -48,8 +48,12 @@ def _compile(src: str) -> str:
 def _build_binding() -> None:
     """Host code only: torch's and Python's headers, and the C ABI of the library next to it."""
     import torch
+    if not os.path.exists(os.path.join(sysconfig.get_paths()["include"], "Python.h")):
+        print("no Python headers: the wrapper will marshal its calls by ctypes")
+        return
     root = os.path.dirname(torch.__file__)
-    cmd = ["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-fvisibility=hidden", f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}",
+    built_for = f"torch {torch.__version__}, Python {sys.version_info.major}.{sys.version_info.minor}"
+    cmd = ["g++", f'-DST_BUILT_FOR="{built_for}"', "-O2", "-std=c++17", "-fPIC", "-shared", "-fvisibility=hidden", f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}",
            "-isystem", os.path.join(root, "include"), "-isystem", os.path.join(root, "include", "torch", "csrc", "api", "include"),
            "-isystem", sysconfig.get_paths()["include"], os.path.join(CSRC, "st_binding.cpp"), "-o", BINDING, "-L" + PKG, "-lstartrail",
            "-L" + os.path.join(root, "lib"), "-ltorch_python", "-ltorch_cpu", "-lc10", "-Wl,-rpath,$ORIGIN"]

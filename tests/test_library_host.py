@@ -3,6 +3,8 @@ host logic (visit order, validation that fails before any launch) behaves."""
 import ctypes as C
 import os
 import re
+import subprocess
+import sys
 
 import pytest
 
@@ -206,3 +208,29 @@ def test_mfma_probe_mixes_and_validation():
     assert call(mix=-1) == 1 and call(mix=n + 1) == 1
     assert call(nsink=16) == 1                          # the sink holds one float per thread of the launch
     assert flop.value == -1.0
+
+
+def test_the_package_works_without_its_native_half():
+    """Not there, or built for another torch or Python: a warning, and ctypes for every call."""
+    assert api._binding.built_for is not None, "the build makes one for this torch and this Python"
+    code = """
+import sys, types, warnings
+if sys.argv[1] == "absent":
+    sys.modules["paper_2407_00611_amd._binding"] = None
+else:
+    m = sys.modules["paper_2407_00611_amd._binding"] = types.ModuleType("_binding")
+    m.built_for = "torch 1.0, Python 3.0"
+    m.cast = lambda *a: 1 / 0
+with warnings.catch_warnings(record=True) as seen:
+    warnings.simplefilter("always")
+    import paper_2407_00611_amd as st
+assert any("ctypes" in str(w.message) for w in seen), seen
+import torch
+try:
+    st.st_cast_from_f32(torch.zeros(8), st.ST_F32, torch.zeros(7))
+except ValueError:
+    print("general way")
+"""
+    for how in ("absent", "another"):
+        r = subprocess.run([sys.executable, "-c", code, how], cwd=ROOT, capture_output=True, text=True)
+        assert r.returncode == 0 and "general way" in r.stdout, r.stdout + r.stderr
