@@ -651,17 +651,20 @@ __device__ __forceinline__ void bwd_dkv_f32(const BwdArgs& a, DkvShared<DP>& sm,
 // Both passes in one launch: the first n_kv workgroups are key tiles, the others the dQ launch's blocks.  Neither needs the other's
 // results, each is a chain of latencies at its start and its end, and a causal shard's key tiles do unlike amounts of work:
 // one head x 128 rows x 4 chunks of 128 keys 16 and 24 us apart and a gap between them, 8/2 heads x 512 rows x 8 chunks of
-// 512 keys 206 and 152.
+// 512 keys 206 and 152.  The workgroups are numbered through rows of `row`: a dimension of a grid holds fewer than 2^32 threads,
+// and one that is wider loses the rest without an error.
 template <int DP, bool FULL>
-__global__ __launch_bounds__(waves<DP>() * 64) void bwd_f32_kernel(const BwdArgs a, int n_kv, int q_blocks) {
+__global__ __launch_bounds__(waves<DP>() * 64) void bwd_f32_kernel(const BwdArgs a, uint32_t n_kv, int q_blocks, uint32_t row, uint32_t blocks) {
   __shared__ union Both {
     DqShared<DP> dq;
     DkvShared<DP> dkv;
   } sm;
-  if ((int)blockIdx.x < n_kv) {
-    bwd_dkv_f32<DP, FULL>(a, sm.dkv, blockIdx.x);
+  const uint32_t block = blockIdx.y * row + blockIdx.x;
+  if (block >= blocks) return;
+  if (block < n_kv) {
+    bwd_dkv_f32<DP, FULL>(a, sm.dkv, (int)block);
   } else {
-    const int x = blockIdx.x - n_kv;
+    const int x = (int)(block - n_kv);
     bwd_dq_f32<DP, FULL>(a, sm.dq, (int)sgpr(x % q_blocks), q_blocks, (int)sgpr(x / q_blocks));
   }
 }
@@ -711,7 +714,9 @@ hipError_t launch_bwd_f32(const BwdArgs& a, hipStream_t stream) {
     constexpr int DP = decltype(dp)::value;
     constexpr bool FULL = decltype(full)::value;
     ProfScope prof("bwd_f32", stream);
-    hipLaunchKernelGGL((bwd_f32_kernel<DP, FULL>), dim3((unsigned)blocks), dim3(waves<DP>() * 64), 0, stream, a, (int)n_kv, (int)q_grid.x);
+    const uint32_t row = (uint32_t)std::min<int64_t>(blocks, 1 << 22);
+    hipLaunchKernelGGL((bwd_f32_kernel<DP, FULL>), dim3(row, (unsigned)((blocks + row - 1) / row)), dim3(waves<DP>() * 64), 0, stream, a, (uint32_t)n_kv,
+                       (int)q_grid.x, row, (uint32_t)blocks);
     return hipGetLastError();
   });
   if (e == hipSuccess && a.kv_items > 1) e = launch_add_kv_parts_f32(a, stream);

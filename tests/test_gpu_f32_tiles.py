@@ -249,3 +249,32 @@ def test_split_dq_and_a_workspace_without_room_for_it(c):
     for dq in (split, two, whole):
         assert_close(host(dq) - 1 / 64, dq_r, "f32", "dq")    # the start costs 1e-9 per element
     assert torch.equal(run(), split)
+
+
+def test_backward_of_more_key_tiles_than_one_grid_dimension_takes():
+    """4.2 million key tiles of two heads: more workgroups than the 2^32 threads of one dimension of a grid hold.  Only the first
+    64 keys are seen, the results are those of a chunk of these 64, bit for bit, and nothing else is written."""
+    Sk, Sq, H, D = 32 * ((1 << 22) + 5), 40, 2, 8
+    if torch.cuda.mem_get_info()[0] < 48 << 30:
+        pytest.skip("needs 35 GB of device memory")
+    gen = torch.Generator(device="cuda").manual_seed(91)
+    rand = lambda *shape: torch.randn(shape, generator=gen, device="cuda")
+    q, d_o = rand(1, Sq, H, D), rand(1, Sq, H, D)
+    k, v, dk, dv = (torch.empty((1, Sk, H, D), device="cuda") for _ in range(4))
+    for t in (k, v):
+        t[:, :64] = rand(1, 64, H, D)
+    o, lse = st.st_attn_block_fwd(q, k[:, :64], v[:, :64], 0, 0, True, 0.3)
+    delta = st.st_attn_delta(d_o, o)
+    got = []
+    for n in (64, Sk):
+        dq = torch.zeros_like(q)
+        g = [dk, dv] if n == Sk else [torch.empty((1, n, H, D), device="cuda") for _ in range(2)]
+        for x in g:
+            x[:, :64] = 0.0
+            x[:, -1] = 7.0 if n == Sk else 0.0
+        st.st_attn_block_bwd(q, k[:, :n], v[:, :n], d_o, lse, delta, 0, 0, True, 0.3, dq, *g)
+        got.append([dq] + [x[:, :64].clone() for x in g])
+    assert float(dk[:, -1].min()) == float(dv[:, -1].max()) == 7.0
+    for name, x, y in zip(("dq", "dk", "dv"), *got):
+        same, live = torch.equal(x, y), bool(x.abs().max() > 0)
+        assert live and same, name
