@@ -435,6 +435,19 @@ __global__ __launch_bounds__(256) void zero_kernel(uint32_t* __restrict__ dst, i
 
 inline unsigned blocks_for(int64_t n) { return (unsigned)((n + 255) / 256); }
 
+// In launches of at most 2^30 vectors: a dimension of a grid holds fewer than 2^32 threads, and one that is wider loses the rest
+// without an error.
+hipError_t copy_f32(const float* src, float* dst, int64_t n, hipStream_t s) {
+  constexpr int64_t kMost = (int64_t)1 << 32;
+  for (int64_t at = 0; at < n; at += kMost) {
+    const int64_t here = n - at < kMost ? n - at : kMost;
+    hipLaunchKernelGGL(copy_f32_kernel, dim3(blocks_for((here + 3) / 4)), dim3(256), 0, s, (const float4*)(src + at), (float4*)(dst + at), here);
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+  }
+  return hipSuccess;
+}
+
 }  // namespace
 
 hipError_t launch_merge(float* o_acc, float* lse_acc, const float* o_part, const float* lse_part, int32_t B,
@@ -466,11 +479,7 @@ hipError_t launch_merge(float* o_acc, float* lse_acc, const float* o_part, const
   else ST_LAUNCH_MERGE(false, 4);
 #undef ST_LAUNCH_MERGE
   hipError_t e = hipGetLastError();
-  if (e == hipSuccess && o_lowp != nullptr) {
-    hipLaunchKernelGGL(copy_f32_kernel, dim3(blocks_for(n_vec)), dim3(256), 0, s, (const float4*)o_acc,
-                       (float4*)o_lowp, 4 * n_vec);
-    e = hipGetLastError();
-  }
+  if (e == hipSuccess && o_lowp != nullptr) e = copy_f32(o_acc, (float*)o_lowp, 4 * n_vec, s);
   return e;
 }
 
@@ -499,11 +508,7 @@ hipError_t launch_combine(const CombineArgs& a, int lowp_dtype, hipStream_t s) {
   }
 #undef ST_LAUNCH_COMBINE
   hipError_t e = hipGetLastError();
-  if (e == hipSuccess && a.o_lowp != nullptr && !lowp) {
-    hipLaunchKernelGGL(copy_f32_kernel, dim3(blocks_for(n_vec)), dim3(256), 0, s, (const float4*)a.o_out,
-                       (float4*)a.o_lowp, 4 * n_vec);
-    e = hipGetLastError();
-  }
+  if (e == hipSuccess && a.o_lowp != nullptr && !lowp) e = copy_f32(a.o_out, (float*)a.o_lowp, 4 * n_vec, s);
   return e;
 }
 
@@ -548,10 +553,7 @@ hipError_t launch_cast(const float* src, void* dst, int64_t n, int dst_dtype, hi
   const int64_t n_vec = n / 4;
   const int tail = (int)(n - n_vec * 4);
   ProfScope prof("cast", s);
-  if (dst_dtype == ST_F32) {                           // as a copy of the runtime it held the stream for 5 us more
-    hipLaunchKernelGGL(copy_f32_kernel, dim3(blocks_for((n + 3) / 4)), dim3(256), 0, s, (const float4*)src, (float4*)dst, n);
-    return hipGetLastError();
-  }
+  if (dst_dtype == ST_F32) return copy_f32(src, (float*)dst, n, s);      // as a copy of the runtime it held the stream for 5 us more
   hipLaunchKernelGGL(cast_bf16_kernel, dim3(blocks_for(n_vec + tail)), dim3(256), 0, s, (const float4*)src,
                      (uint2*)dst, n_vec, src + n_vec * 4, (uint16_t*)dst + n_vec * 4, tail);
   return hipGetLastError();

@@ -168,3 +168,18 @@ def test_merge_ignores_the_o_of_an_empty_state():
     assert_close(host(l_a), ref_l, "f32", "merge lse")
     assert not o_a[1, 30:, 1].any()      # empty on both sides: O = 0
     assert torch.equal(low, o_a.to(torch.bfloat16))
+
+
+def test_copy_of_more_than_one_grid_dimension_holds():
+    """fp32 to fp32, 2^34 values and some: a thread takes four, and a dimension of a grid holds fewer than 2^32 threads."""
+    n, run = (1 << 34) + 1027, 2000
+    if torch.cuda.mem_get_info()[0] < 150 << 30:
+        pytest.skip("needs 138 GB of device memory")
+    src, dst = torch.empty(n, device="cuda"), torch.empty(n, device="cuda")
+    marks = [0, 12345, (1 << 32) - 3, (1 << 33) - 1000, n - run]           # both sides of where a launch ends, and the odd end
+    for at in marks:
+        src[at:at + run] = torch.arange(run, device="cuda") + at % 1009
+        dst[at:at + run] = -1.0
+    st.st_cast_from_f32(src, st.ST_F32, dst)
+    for at in marks:
+        assert torch.equal(src[at:at + run], dst[at:at + run]), at
