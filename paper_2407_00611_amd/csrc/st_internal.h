@@ -137,8 +137,8 @@ __host__ __device__ inline int kv_shares(int blocks, int each) {
 // in host memory, and a load of them per lane takes 2 us of a launch that may be 20): all tiles of a run have the same
 // number of shares, unless it is `mixed`.  The last run may hold anything.
 struct KvSection {
-  uint16_t tiles, items;       // items: shares
-  uint16_t mixed;
+  int32_t tiles, items;        // items: shares
+  int32_t mixed;
 };
 constexpr int kKvSections = 5;
 

@@ -41,16 +41,24 @@ struct KvPlace {
 // of share `w`, or (by_tile) the first one of tile w
 template <typename F>
 __device__ __forceinline__ KvPlace kv_place(const Shape& s, const KvSection (&sec)[kKvSections], int each, int n_kt, int w, bool by_tile, int lane, F offsets) {
-  int t0 = 0, i0 = 0, x = 0;                         // tiles and shares before the section that w is in
-  for (; x < kKvSections - 1; ++x) {
-    if (w < (by_tile ? t0 + sec[x].tiles : i0 + sec[x].items)) break;
-    t0 += sec[x].tiles;
-    i0 += sec[x].items;
+  // the section that w is in, and the tiles and shares before it; picked by selects: an index that is only known at run time would
+  // put the sections into scratch memory, a chain of stores and loads at the start of every workgroup
+  int t0 = 0, i0 = 0, tiles = sec[0].tiles, items = sec[0].items, mixed = sec[0].mixed;
+  int t1 = tiles, i1 = items;
+#pragma unroll
+  for (int x = 1; x < kKvSections; ++x) {
+    const bool beyond = w >= (by_tile ? t1 : i1);
+    t0 = beyond ? t1 : t0;
+    i0 = beyond ? i1 : i0;
+    tiles = beyond ? sec[x].tiles : tiles;
+    items = beyond ? sec[x].items : items;
+    mixed = beyond ? sec[x].mixed : mixed;
+    t1 += sec[x].tiles;
+    i1 += sec[x].items;
   }
-  const int tiles = sec[x].tiles;
   KvPlace p;
-  if (!sec[x].mixed) {
-    p.n_share = sec[x].items / max(tiles, 1);
+  if (!mixed) {
+    p.n_share = items / max(tiles, 1);
     const int k = by_tile ? w - t0 : (w - i0) / p.n_share;
     p.tile = t0 + k;
     p.share = by_tile ? 0 : w - i0 - k * p.n_share;
