@@ -568,7 +568,7 @@ BwdSplit bwd_splits(const st::Shape& s, int dtype, const int64_t* k_offset, int 
     }
   }
   size_t dq_bytes = r.bytes;
-  if (plan_dq && dq_units > 6) {
+  if (plan_dq && !st::dq_few(s, n)) {
     double least = 0.95 * (kv_us + 4 + dq_us);
     KeySplit pair_kv = kv;
     auto together = [&](const KeySplit& y, const Split& x) {

@@ -469,11 +469,8 @@ hipError_t launch_bwd_bf16(const BwdArgs& a_in, hipStream_t stream) {
         a.kv_assign = (a.kv_assign & ~((1ull << j) | (1ull << (j - 1)))) | (bi << j) | (bj << (j - 1));
       }
   }
-  // A walk of a few tiles ends before the hand-scheduled loop has made up for its prologue (head size 128: one 64-key tile
-  // 14.1 against 10.5 us on the general kernel, five 26.9 against 20.9, eight 23.2 against 23.7, 64 tiles 106 against 137;
-  // head size 64: 11.2 against 8.7, 17.7 against 15.3, 15.6 against 17.7, 61 against 94).  The dK/dV loop is the faster one
-  // from the first block on.
-  const bool few = a.shares.n <= 1 && (int64_t)a.t.n * ((a.s.Sk + kDqFastKeys - 1) / kDqFastKeys) <= 6;
+  // the dK/dV loop is the faster one from the first block on
+  const bool few = a.shares.n <= 1 && dq_few(a.s, a.t.n);
   const bool dq_fast = knobs().dq_fast && !few && dq_fast_usable(a), pair = a.pair && dkv_fast && dq_fast;
   hipError_t e = hipSuccess;
   if (pair) {

@@ -260,6 +260,12 @@ constexpr int kQTileFastKeys = 64;
 constexpr int kDqFastRows = kQTileFastRows;
 constexpr int kDqFastKeys = kQTileFastKeys;
 
+// A dQ walk of a few tiles ends before the hand-scheduled loop has made up for its prologue (head size 128: one 64-key tile
+// 14.1 against 10.5 us on the general kernel, five 26.9 against 20.9, eight 23.2 against 23.7, 64 tiles 106 against 137;
+// head size 64: 11.2 against 8.7, 17.7 against 15.3, 15.6 against 17.7, 61 against 94): unless it is split it stays there, and
+// out of the launch that holds both passes.
+inline bool dq_few(const Shape& s, int n) { return (int64_t)n * ((s.Sk + kDqFastKeys - 1) / kDqFastKeys) <= 6; }
+
 // ---- launchers (each returns hipGetLastError() after the launch) ----
 hipError_t launch_fwd_f32(const FwdArgs& a, hipStream_t s);
 hipError_t launch_bwd_f32(const BwdArgs& a, hipStream_t s);
