@@ -406,8 +406,6 @@ __global__ __launch_bounds__(waves<DP>() * 64) void fwd_f32_kernel(const FwdArgs
     }
   const int64_t stat = ((int64_t)b * s.Hq + h) * s.Sq + row0 + r;
   if (g == 0) (n_split > 1 ? a.part_lse + split * a.part_stride : a.lse)[stat] = l > 0.f ? m + logf(l) : -INFINITY;
-  if (g == 0 && split == 0)                                  // states of shares that other tiles have: empty
-    for (int y = n_split > 1 ? n_split : 0; y < a.shares.n && a.shares.n > 1; ++y) a.part_lse[y * a.part_stride + stat] = -INFINITY;
   if (any_dirty)                                             // (a value that several shares add is the same infinity or NaN)
     for (int c = 0; c < a.t.n; ++c)
       add_nonfinite<DB>(o, ol, (const float*)a.t.v[c] + b * a.t.vsb + hk * a.t.vsh, a.t.vss,

@@ -83,3 +83,24 @@ def test_tiles_with_shares_of_their_own(c):
     st.st_ring_bwd_noalloc(q, ks, vs, d_o, low, lse, *args, order, dq, [torch.zeros(k.shape, device="cuda") for k in ks],
                            [torch.zeros(k.shape, device="cuda") for k in ks])
     assert torch.equal(dq, got[0])
+
+
+@pytest.mark.parametrize("dtype,Sq", [("bf16", 1500), ("f32", 1210)])
+def test_states_a_tile_does_not_have_are_left_alone(dtype, Sq):
+    """Tiles of a causal shard have unlike numbers of shares; the pass that folds them reads only those a tile has, so nothing is
+    written in the place of the others."""
+    B, Hq, Hkv, D = 1, 2, 1, 128 if dtype == "bf16" else 64
+    w = si.Workload("shares", 361, dtype, B, Hq, Hkv, D, Sq, Sq, 1, 0, True, True)
+    q, ks, vs, _ = upload(si.make_inputs(w))
+    args = (q, ks, vs, 0, [0], True, w.scale)
+    size = st.st_ring_workspace_bytes(*args, st.ST_RING_FUSED, False)
+    up = lambda x: (x + 255) // 256 * 256
+    o_bytes, state = up(q.numel() * 4), up(q.numel() * 4) + up(B * Hq * Sq * 4)
+    buf = torch.full((size + 256,), 0xff, dtype=torch.uint8, device="cuda")
+    st.st_ring_fwd(*args, [0], workspace=buf)
+    at = -buf.data_ptr() % 256
+    n = size // state
+    assert n >= 3
+    lse = [buf[at + y * state + o_bytes:at + y * state + o_bytes + 4 * B * Hq * Sq].view(torch.float32).view(B, Hq, Sq) for y in range(n)]
+    written = [int((~x.isnan()).sum()) for x in lse]                    # rows of the tiles that have a share y
+    assert written[0] > written[n - 1] and all(x >= y for x, y in zip(written, written[1:])), written
