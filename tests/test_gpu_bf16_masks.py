@@ -103,17 +103,19 @@ def test_split_cuts_the_masked_part():
 
 @pytest.mark.parametrize("D", [128, 64])
 def test_the_state_of_an_empty_share_stays_out(D):
-    """First rank of a causal ring: the plan counts the tiles of the last rows, so some shares of the first query tile have
-    none.  They leave their O unwritten, here NaN, behind an lse of -inf."""
-    w = si.Workload("empty_shares", 343, "bf16", 1, 1, 1, D, 1024, 1024, 1, 0, True, False)
+    """65 query tiles, more than have numbers of shares of their own: the plan counts the tiles of the last rows, and of the
+    first query tile, which sees one key tile, some shares have none.  They leave their O unwritten, here NaN, behind an lse of
+    -inf."""
+    Sq = 65 * 256
+    w = si.Workload("empty_shares", 343, "bf16", 1, 1, 1, D, Sq, 4096, 1, -200, True, False)
     inp = si.make_inputs(w)
     q, ks, vs, _ = upload(inp)
-    b_o, b_l = q.numel() * 4, 1024 * 4
-    need = st.st_ring_workspace_bytes(q, ks, vs, 0, [0], True, w.scale, st.ST_RING_FUSED, False)
+    b_o, b_l = q.numel() * 4, Sq * 4
+    need = st.st_ring_workspace_bytes(q, ks, vs, w.q_offset, [0], True, w.scale, st.ST_RING_FUSED, False)
     shares = need // (b_o + b_l)
     assert shares > 1, "this share was meant to be split"
     ws = torch.full((need + 256,), 0xff, dtype=torch.uint8, device="cuda")
-    o, lse, low = st.st_ring_fwd(q, ks, vs, 0, [0], True, w.scale, [0], workspace=ws)
+    o, lse, low = st.st_ring_fwd(q, ks, vs, w.q_offset, [0], True, w.scale, [0], workspace=ws)
     first, empty = (-ws.data_ptr()) % 256, 0
     for y in range(shares):
         state = ws[first + y * (b_o + b_l):first + (y + 1) * (b_o + b_l)].view(torch.float32)
