@@ -2,6 +2,8 @@
 // Delta = rowsum(dO * O),
 // fp32 -> storage-dtype casts and the (O = 0, lse = -inf) state fill.
 // One 16-byte vector per lane, rows never straddle a lane; grid sized to the data.
+#include <type_traits>
+
 #include "st_internal.h"
 #include "st_mfma.h"
 #include "st_walk.h"
@@ -348,8 +350,14 @@ __global__ __launch_bounds__(256) void add_parts_kernel(float* dq, float* sums, 
 __global__ __launch_bounds__(256) void add_kv_parts_kernel(const BwdArgs a) {
   const Shape& s = a.s;
   const int n_kt = (s.Sk + kDkvFastKeys - 1) / kDkvFastKeys, tile = blockIdx.y, c = tile / n_kt, kt = tile - c * n_kt;
-  const KvPlace place = kv_place(s, a.kv_sec, a.kv_each, n_kt, tile, true, threadIdx.x & 63, [&](int x) { return a.t.k_offset[x]; });
-  const int n = place.n_share, slot = blockIdx.z * (a.kv_items - n_kt * a.t.n) + place.slot;
+  KvPlace place;
+  if (a.kv_same > 0) {
+    place.n_share = a.kv_same;
+    place.slot = tile * (a.kv_same - 1);
+  } else {
+    place = kv_place(s, a.kv_sec, a.kv_each, n_kt, tile, true, threadIdx.x & 63, [&](int x) { return a.t.k_offset[x]; });
+  }
+  const int n = (int)sgpr(place.n_share), slot = blockIdx.z * (a.kv_items - n_kt * a.t.n) + (int)sgpr(place.slot);
   if (n <= 1) return;
   const int vec = s.D / 4, half = gridDim.x / 2, w = (int)blockIdx.x >= half, v = (blockIdx.x - w * half) * 256 + threadIdx.x, row = v / vec;
   if (row >= min(kDkvFastKeys, s.Sk - kt * kDkvFastKeys)) return;
@@ -358,18 +366,32 @@ __global__ __launch_bounds__(256) void add_kv_parts_kernel(const BwdArgs a) {
   const float4* parts = reinterpret_cast<const float4*>(a.kv_parts) + slot * slot_vec + w * kDkvFastKeys * vec + v;
   float4* dst = reinterpret_cast<float4*>(w ? a.dv[c] : a.dk[c]) + at;
   float4 x = *dst;
-  for (int y0 = 0; y0 < n - 1; y0 += 8) {
-    float4 p[8];
+  // eight loads in flight together, and no load twice: n is the same for the workgroup
+  int y0 = 0;
+  auto some = [&](auto count) {
+    constexpr int N = decltype(count)::value;
+    float4 p[N];
 #pragma unroll
-    for (int u = 0; u < 8; ++u) p[u] = parts[min(y0 + u, n - 2) * slot_vec];
+    for (int u = 0; u < N; ++u) p[u] = parts[(y0 + u) * slot_vec];
 #pragma unroll
-    for (int u = 0; u < 8; ++u)
-      if (y0 + u < n - 1) {
-        x.x += p[u].x;
-        x.y += p[u].y;
-        x.z += p[u].z;
-        x.w += p[u].w;
-      }
+    for (int u = 0; u < N; ++u) {
+      x.x += p[u].x;
+      x.y += p[u].y;
+      x.z += p[u].z;
+      x.w += p[u].w;
+    }
+    y0 += N;
+  };
+  using std::integral_constant;
+  while (n - 1 - y0 >= 8) some(integral_constant<int, 8>());
+  switch (n - 1 - y0) {
+    case 7: some(integral_constant<int, 7>()); break;
+    case 6: some(integral_constant<int, 6>()); break;
+    case 5: some(integral_constant<int, 5>()); break;
+    case 4: some(integral_constant<int, 4>()); break;
+    case 3: some(integral_constant<int, 3>()); break;
+    case 2: some(integral_constant<int, 2>()); break;
+    case 1: some(integral_constant<int, 1>()); break;
   }
   *dst = x;
   uint2* low = reinterpret_cast<uint2*>(w ? a.dv_lowp[c] : a.dk_lowp[c]);

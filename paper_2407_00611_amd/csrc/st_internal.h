@@ -166,6 +166,7 @@ struct BwdArgs {
   // The fp32 kernels: kv_items shares of every key tile (0: one), sums as f32_kv_part says.
   int32_t kv_each, kv_items;
   KvSection kv_sec[kKvSections];
+  int32_t kv_same;     // shares of every tile where all have the same number (then nothing is looked up), else 0; set by the launcher
   int32_t pair;        // 1: both passes in one launch, where the hand-scheduled kernels take both
   float *parts, *kv_parts;   // of launches that run one after the other they may be the same memory
   // dK / dV work of a chunk's last visit folded into the launch (bf16 path): the hand-scheduled kernel's epilogue does it,
