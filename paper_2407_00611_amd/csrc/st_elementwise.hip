@@ -107,8 +107,12 @@ __global__ __launch_bounds__(256) void merge_kernel(float* __restrict__ o_acc, f
 // after the other).  O loads in flight together: all for up to 4 and 9 to 16 states, otherwise kCombineUnroll (8 states of
 // 8 x 1024 rows of 128: 12.0 us, 12.4 with all eight at once).  16 states of 4 x 256 rows, the split of a short shard: 17.5
 // us without their number known, 9.3 with it; of 8 x 1024 rows 21.7 and 18.5.
+// kOwn: the states of a split forward whose tiles have numbers of their own.  Where all have the same it stays uniform: one head
+// x 3000 rows 7.6 us, 7.9 with a number per lane.  (Numbers of their own: the last state read again in the place of the ones a
+// row lacks, so that no load hangs on a mask, 8.0 for 7.5 us at 8 heads x 1024 rows; a uniform path for wavefronts whose rows
+// agree 7.2 for 6.4 at 12 x 448: twice the code, and launches this short fetch all of it.)
 constexpr int kCombineUnroll = 4;
-template <bool kLowp, int kFew>
+template <bool kLowp, int kFew, bool kOwn = false>
 __global__ __launch_bounds__(256) void combine_kernel(const CombineArgs a, int32_t vec_per_row, int32_t lane_shift) {
   const int64_t tid = (int64_t)blockIdx.x * 256 + threadIdx.x;
   const int64_t row = tid >> lane_shift;               // (b * Sq_out + i) * Hq + h
@@ -118,8 +122,6 @@ __global__ __launch_bounds__(256) void combine_kernel(const CombineArgs a, int32
   const RowOf at = row_of(row, n_rows, a.Sq_out, a.Hq);
   const int64_t b = at.b;
   const int32_t i = at.i, h = at.h;
-  const int n = a.shares.n > 1 ? shares_of(a.shares, a.tiles.tile_of(i)) : a.n;     // states that hold this row
-  if (a.shares.n > 1 && n <= 1) return;
   const int64_t l_in = (b * a.Hq + h) * a.Sq_in + a.row0 + i;
   const int64_t v_in = ((b * a.Sq_in + a.row0 + i) * a.Hq + h) * vec_per_row + sub;
 
@@ -128,7 +130,6 @@ __global__ __launch_bounds__(256) void combine_kernel(const CombineArgs a, int32
     const f32x4_t t = __builtin_nontemporal_load(reinterpret_cast<const f32x4_t*>(a.o[x]) + v_in);   // read once
     return make_float4(t.x, t.y, t.z, t.w);
   };
-  auto load_few = [&](int x) { return x < n ? load_o(x) : make_float4(0.f, 0.f, 0.f, 0.f); };
   // The O of an empty state may never have been written (the split forward leaves it out): it is loaded like the others, and a
   // weight of exactly 0 keeps it, NaN or not, out of the sum.
   auto add = [](float4& r, float w, const float4& p) {
@@ -141,9 +142,15 @@ __global__ __launch_bounds__(256) void combine_kernel(const CombineArgs a, int32
   };
   float4 r = make_float4(0.f, 0.f, 0.f, 0.f);
   float lnew = -INFINITY;
-  if (kFew > 0) {
+  if constexpr (kFew > 0) {
     // every lse is read once and kept, and the first O loads do not wait for them
-    constexpr int N = kFew > 0 ? kFew : 1, U = N == 8 ? kCombineUnroll : N;
+    constexpr int N = kFew, U = N == 8 ? kCombineUnroll : N;
+    int n = a.n;                                         // states that hold this row
+    if constexpr (kOwn) {
+      n = shares_of(a.shares, a.tiles.tile_of(i));
+      if (n <= 1) return;
+    }
+    auto load_few = [&](int x) { return x < n ? load_o(x) : make_float4(0.f, 0.f, 0.f, 0.f); };
     float l[N];
     float4 p[U];
 #pragma unroll
@@ -514,19 +521,35 @@ hipError_t launch_combine(const CombineArgs& a, int lowp_dtype, hipStream_t s) {
   const dim3 grid(blocks_for(n_rows << lane_shift)), block(256);
   const bool lowp = a.o_lowp != nullptr && lowp_dtype == ST_BF16;
   ProfScope prof("combine", s);
-#define ST_LAUNCH_COMBINE(LOWP, FEW) hipLaunchKernelGGL((combine_kernel<LOWP, FEW>), grid, block, 0, s, a, a.D / 4, lane_shift)
+#define ST_LAUNCH_COMBINE(LOWP, FEW)                                                                                         \
+  if (a.shares.n > 1 && a.shares.total > 0)                                                                                 \
+    hipLaunchKernelGGL((combine_kernel<LOWP, FEW, (FEW > 0)>), grid, block, 0, s, a, a.D / 4, lane_shift);                   \
+  else                                                                                                                      \
+    hipLaunchKernelGGL((combine_kernel<LOWP, FEW>), grid, block, 0, s, a, a.D / 4, lane_shift)
   if (a.n <= 4) {
-    if (lowp) ST_LAUNCH_COMBINE(true, 4);
-    else ST_LAUNCH_COMBINE(false, 4);
+    if (lowp) {
+      ST_LAUNCH_COMBINE(true, 4);
+    } else {
+      ST_LAUNCH_COMBINE(false, 4);
+    }
   } else if (a.n <= 8) {
-    if (lowp) ST_LAUNCH_COMBINE(true, 8);
-    else ST_LAUNCH_COMBINE(false, 8);
-  } else if (a.n <= 16) {
-    if (lowp) ST_LAUNCH_COMBINE(true, 16);
-    else ST_LAUNCH_COMBINE(false, 16);
+    if (lowp) {
+      ST_LAUNCH_COMBINE(true, 8);
+    } else {
+      ST_LAUNCH_COMBINE(false, 8);
+    }
+  } else if (a.n <= 16) {                              // the most shares a tile can have
+    if (lowp) {
+      ST_LAUNCH_COMBINE(true, 16);
+    } else {
+      ST_LAUNCH_COMBINE(false, 16);
+    }
   } else {
-    if (lowp) ST_LAUNCH_COMBINE(true, 0);
-    else ST_LAUNCH_COMBINE(false, 0);
+    if (lowp) {
+      ST_LAUNCH_COMBINE(true, 0);
+    } else {
+      ST_LAUNCH_COMBINE(false, 0);
+    }
   }
 #undef ST_LAUNCH_COMBINE
   hipError_t e = hipGetLastError();

@@ -60,7 +60,10 @@ struct QueryTiles {
     const int left = (n_lo > 0 && qt < n_lo ? seg : Sq) - row0(qt);
     return left < rows ? left : rows;
   }
-  __host__ __device__ int tile_of(int row) const { return n_lo > 0 && row >= seg ? n_lo + (row - seg) / rows : row / rows; }
+  __host__ __device__ int tile_of(int row) const {     // rows is a power of two
+    const int shift = 31 - __builtin_clz((unsigned)rows);
+    return n_lo > 0 && row >= seg ? n_lo + ((row - seg) >> shift) : row >> shift;
+  }
 };
 // of the hand-scheduled kernels (kQTileFastRows) and the fp32 ones (32 rows).  Under a causal mask a 256-row tile with rows of
 // both runs would walk what the second run sees with masks all the way: a masked tile takes 1.4 (dQ) to 2 times a whole one (64
