@@ -559,7 +559,7 @@ BwdSplit bwd_splits(const st::Shape& s, int dtype, const int64_t* k_offset, int 
     const KeySplit x(keys, each);
     if (slot_bytes(x) > room || keys.heads * x.items > 4 * kPlanCus) break;
     const double add = add_kv_us(x);
-    const double less = (kv.each > 0 ? 0.97 : 0.95) * kv_us;     // more workgroups have to be worth it
+    const double less = 0.95 * kv_us;                   // more workgroups have to be worth it
     if (x.longest_us(kv_cost) + add >= less) continue;
     const double us = add + jobs_us(job, x.jobs(job, kv_cost), less - add);
     if (us < less) {
@@ -569,7 +569,7 @@ BwdSplit bwd_splits(const st::Shape& s, int dtype, const int64_t* k_offset, int 
   }
   size_t dq_bytes = r.bytes;
   if (plan_dq && !st::dq_few(s, n)) {
-    double least = 0.95 * (kv_us + 4 + dq_us);
+    double least = kv_us + 4 + dq_us;
     KeySplit pair_kv = kv;
     auto together = [&](const KeySplit& y, const Split& x) {
       const size_t left = room - slot_bytes(y);
