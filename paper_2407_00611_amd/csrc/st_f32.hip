@@ -91,8 +91,12 @@ typedef const __attribute__((address_space(1))) float* GlobalFloats;
 __device__ const __attribute__((aligned(16))) float zero_row[256] = {};
 typedef float f32x2v __attribute__((ext_vector_type(2)));
 typedef float f32x4v __attribute__((ext_vector_type(4)));
-// The transposed operand of a tile X: lane r = columns DB r + db, register v = row c_row(v, g).  A lane's columns are neighbours
-// (which d an A row stands for is free as long as the results are stored so, see acc_block): one load of DB floats a row, not DB of one.
+// The column that row m of accumulator db stands for, which is free as long as the results are stored so (acc_block).  A lane's
+// columns are neighbours, one load of up to four floats a row, where their number is even.  Three would be three loads again, at
+// strides of three floats: head size 96 has them 32 apart, a row's loads of a wavefront in one piece.
+template <int DB>
+__device__ __forceinline__ constexpr int column(int m, int db) { return DB % 2 == 0 ? DB * m + db : 32 * db + m; }
+// The transposed operand of a tile X: lane r = columns column(r, 0 .. DB - 1), register v = row c_row(v, g).
 // Rows at or beyond `limit` (tile-relative, >= 1) are zero: their weight is, but a row that exists, read in their place, may
 // hold an infinity, and 0 * inf is NaN.
 template <int DP, bool FULL, int N>
@@ -105,7 +109,7 @@ __device__ __forceinline__ void load_cols(Piece<N>& f, const float* tile, int64_
     const int v = n * piece_rows<DP, N>() + u, row = 8 * (v / 4) + v % 4;
     GlobalFloats p = (GlobalFloats)tile + (int64_t)(4 * g) * stride + (int64_t)row * stride;
     if (limit < kT) p = row < mine ? p : (GlobalFloats)zero_row;
-    p += DB * r;
+    p += column<DB>(r, 0);
     float* x = f.x + DB * u;
     if constexpr (DB % 2 == 0) {
       constexpr int W = DB % 4 == 0 ? 4 : 2;
@@ -119,7 +123,7 @@ __device__ __forceinline__ void load_cols(Piece<N>& f, const float* tile, int64_
       }
     } else {
 #pragma unroll
-      for (int db = 0; db < DB; ++db) x[db] = FULL || DB * r + db < D ? p[db] : 0.f;
+      for (int db = 0; db < DB; ++db) x[db] = FULL || column<DB>(r, db) < D ? p[32 * db] : 0.f;
     }
   }
 }
@@ -192,7 +196,7 @@ __device__ __forceinline__ void add_nonfinite(float* out, float* out2, const flo
 #pragma unroll 1
     for (int d = 0; d < D; ++d) {
       const float x = x0[(int64_t)t * stride + d];
-      if (((d / DB / 4) & 1) != g || finite(x)) continue;                // acc_block's half
+      if (((DB % 2 == 0 ? d / DB / 4 : d / 4) & 1) != g || finite(x)) continue;       // acc_block's half
       out[d] += as_nan ? __builtin_nanf("") : x;
       if (out2) out2[d] = out[d];
     }
@@ -206,12 +210,14 @@ __device__ __forceinline__ void zero_acc(f32x16 (&acc)[N]) {
     for (int v = 0; v < 16; ++v) acc[i][v] = 0.f;
 }
 
-// Four neighbouring results of a lane: columns 4 (DB (2 j + g) + q) .. + 3 of the 4 DB that block j of its accumulators holds
+// Four neighbouring results of a lane, the columns from block_column on: number q of the DB that block j of its accumulators holds
+template <int DB>
+__device__ __forceinline__ int block_column(int j, int q, int g) { return DB % 2 == 0 ? 4 * (DB * (2 * j + g) + q) : 32 * q + 8 * j + 4 * g; }
 template <int DB>
 __device__ __forceinline__ float4 acc_block(const f32x16 (&acc)[DB], int j, int q, float c) {
   float x[4];
 #pragma unroll
-  for (int e = 0; e < 4; ++e) x[e] = c * acc[(4 * q + e) % DB][4 * j + (4 * q + e) / DB];
+  for (int e = 0; e < 4; ++e) x[e] = c * (DB % 2 == 0 ? acc[(4 * q + e) % DB][4 * j + (4 * q + e) / DB] : acc[q][4 * j + e]);
   return make_float4(x[0], x[1], x[2], x[3]);
 }
 
@@ -398,7 +404,7 @@ __global__ __launch_bounds__(waves<DP>() * 64) void fwd_f32_kernel(const FwdArgs
   for (int j = 0; j < 4; ++j)
 #pragma unroll
     for (int q = 0; q < DB; ++q) {
-      const int d = 4 * (DB * (2 * j + g) + q);
+      const int d = block_column<DB>(j, q, g);
       if (d >= s.D) continue;
       const float4 x = acc_block(acc, j, q, inv);
       *reinterpret_cast<float4*>(o + d) = x;
@@ -502,7 +508,7 @@ __device__ __forceinline__ void bwd_dq_f32(const BwdArgs& a, DqShared<DP>& sm, i
   for (int j = 0; j < 4; ++j)
 #pragma unroll
     for (int q = 0; q < DB; ++q) {
-      const int d = 4 * (DB * (2 * j + g) + q);
+      const int d = block_column<DB>(j, q, g);
       if (d >= s.D) continue;
       float4 x = part ? make_float4(0.f, 0.f, 0.f, 0.f) : *reinterpret_cast<float4*>(dq + d);
       x = add(x, acc_block(acc, j, q, s.scale));
@@ -627,7 +633,7 @@ __device__ __forceinline__ void bwd_dkv_f32(const BwdArgs& a, DkvShared<DP>& sm,
   for (int j = 0; j < 4; ++j)
 #pragma unroll
     for (int q = 0; q < DB; ++q) {
-      const int d = 4 * (DB * (2 * j + g) + q);
+      const int d = block_column<DB>(j, q, g);
       if (d >= s.D) continue;
       float4* pk = reinterpret_cast<float4*>(out_k + d);
       float4* pv = reinterpret_cast<float4*>(out_v + d);
