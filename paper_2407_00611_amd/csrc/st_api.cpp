@@ -204,8 +204,9 @@ QueryWalk query_walk(const st::Shape& s, int dtype, const int64_t* k_offset, int
   w.q = st::query_tiles(s, bf16 ? st::kQTileFastRows : 32);
   w.tiles = w.q.count();
   w.heads = (int64_t)s.B * s.Hq;
-  w.n = s.causal && k_offset && w.tiles > 1 && w.tiles <= st::kShareTiles ? w.tiles : 1;
-  if (w.n == 1) {
+  const bool apart = s.causal && k_offset && w.tiles >= 1 && w.tiles <= st::kShareTiles;
+  w.n = apart ? w.tiles : 1;
+  if (!apart) {
     w.units[0] = (int)std::min<int64_t>(bf16 ? (int64_t)n * ((s.Sk + st::kQTileFastKeys - 1) / st::kQTileFastKeys) : f32_turns(s.D, s.Sk, n), 1 << 28);
     return w;
   }

@@ -152,6 +152,7 @@ def test_forward_workspace_of_a_causal_share_holds_what_its_plan_uses():
 
     assert states(1, 32, 8, 128, 3801, 1, 0) == 1 and states(2, 16, 8, 128, 3737, 2, 0) == 1
     assert states(1, 8, 2, 128, 7375, 16, 0) == 3          # the tiles at the end of the diagonal chunk
+    assert states(1, 2, 1, 128, 228, 2, 1) > 1              # one query tile a head: its masked key tiles count twice as well
 
 
 def test_ring_bwd_last_validation_fails_before_any_launch():
