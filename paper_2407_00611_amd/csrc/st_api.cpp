@@ -240,9 +240,13 @@ struct Cost {
 };
 // Measured on 32 to 256 workgroups with walks of 4 to 128 units, kernels back to back.  Forward, a 256 x 64 tile; dQ, the same (three contractions
 // instead of two); dK/dV, 256 keys x 32 rows of one head.  fp32: a turn (see f32_turns).
+// The forward alone, launches of whole tiles in a graph, 1 / 64 / 128 / 192 / 256 workgroups: head size 128 4 tiles 15.3 / 16.7 / 19.4 / 21.8 / 24.2
+// us, 16 tiles 26.8 / 29.8 / 33.0 / 36.3 / 42.9, 64 tiles 73 / 76 / 85 / 110 / 129; head size 64 16 tiles 19.2 / 20.5 / 22.8 / 24.4 / 27.5, 64 tiles
+// 53 / 55 / 58 / 64 / 81; a masked tile is two.  In a share fewer workgroups cost somewhat more than that and splits somewhat less:
+// constants that follow the table to the letter choose too few shares (100 under-filled shares 0.6 % slower than with these).
 Cost fwd_cost(int dtype, int D) {
   if (dtype != ST_BF16) return Cost{5 + 0.035 * D, 2 + (D <= 128 ? 0.065 : 0.034) * D, 0, 0};
-  return D == 128 ? Cost{16, 1.05, 0, 0.45} : Cost{11, 0.75, 0, 0.2};
+  return D == 128 ? Cost{13.5, 1.05, 2.5, 0.45} : Cost{9.5, 0.75, 1.5, 0.2};
 }
 Cost dq_cost(int dtype, int D) {
   if (dtype != ST_BF16) return Cost{10, 2 + (D <= 128 ? 0.11 : 0.055) * D, 0, 0};
@@ -959,12 +963,10 @@ st_status st_schedule_report(int32_t P, int32_t C, int64_t B, int64_t N, int64_t
 // A fused forward whose query tiles alone would leave part of the chip idle (a workgroup per 256 rows and head in bf16, per
 // 32 rows in fp32, on 256 compute units) is split over the keys: a query tile gets several workgroups, each with a share of
 // the walk and a partial state of its own, and one combine pass folds the states (the tiles of a ring are independent
-// until the fold, Algorithm 1).  The split is the one for which launch + combine is least (Split::launch_us), with measured
-// constants: a 256 x 64 bf16 tile 1.25 us at head size 128 and 0.8 us at 64 behind 12 and 9 us of walk, prologue and epilogue
-// (short launches: below some 100 us the chip does not reach its power limit), 6 us for the launch of the combine pass, which
-// moves 4 TB/s on states this small.  fp32: a turn (see f32_turns) takes 4.1, 6.1 and 10.4 us at head sizes 32, 64 and 128 and
-// 10.7 at 256 (with half the wavefronts), what stands around the turns 5, 7, 10 and 13 us; 8 us for the combine pass, as a
-// caller that waits for launches loses 5 us by one more.
+// until the fold, Algorithm 1).  The split is the one for which launch + combine is least (Split::launch_us) with the
+// constants of fwd_cost, 5 us for the combine pass and what its bytes take, 8 TB/s from the caches; fp32 8 us, as a caller that
+// waits for launches loses some by one more.  To be split at all has to be worth 5 %; a split of more workgroups 3 % (100
+// under-filled shares 0.7 % faster than with 5; with 1 some that are 3 to 10 % slower, and more states).
 // Under a causal mask the tiles differ, and shares of one size are what fills the chip: 48 heads x two runs of 736 rows,
 // walks of 230 and 610 tiles, 885 us with one number of shares for all tiles and 674 so (dQ 1254 and 1024); 3 heads x two
 // runs of 2112 rows 254 and 185 (342 and 253).
@@ -981,14 +983,15 @@ static st::TileShares fwd_shares(const st_ring_desc* d, const int64_t* k_offset,
   const bool bf16 = d->dtype == ST_BF16;
   const QueryWalk walk = query_walk(shape_of(d), d->dtype, k_offset, n_visible);
   const Cost cost = fwd_cost(d->dtype, d->D);
-  const double combine_us = bf16 ? 6 : 8;
+  const double combine_us = bf16 ? 5 : 8;
   const double row_us = (double)d->B * d->Hq * d->D * sizeof(float) / 8e6;
   double best = Split(walk, walk.most()).launch_us(cost);
   each_split(walk, most, [&](const Split& x) {
     const double add = combine_us + more_than_8_us(x) + (x.rows + 1.5 * d->Sq) * row_us;
-    if (x.longest_us(cost) + add >= 0.95 * best) return;
+    const double less = (r.n > 1 ? 0.97 : 0.95) * best;      // to be split at all has to be worth it; of two splits the better one
+    if (x.longest_us(cost) + add >= less) return;
     const double t = x.launch_us(cost) + add;
-    if (t < 0.95 * best) {
+    if (t < less) {
       best = t;
       r = x.table(false);
     }

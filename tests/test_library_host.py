@@ -152,6 +152,7 @@ def test_forward_workspace_of_a_causal_share_holds_what_its_plan_uses():
 
     assert states(1, 32, 8, 128, 3801, 1, 0) == 1 and states(2, 16, 8, 128, 3737, 2, 0) == 1
     assert states(1, 8, 2, 128, 7375, 16, 0) == 3          # the tiles at the end of the diagonal chunk
+    assert states(1, 1, 1, 128, 384, 1, 0) > 1              # few workgroups, short walks: 18.0 us split, 22.8 whole
     assert states(1, 2, 1, 128, 228, 2, 1) > 1              # one query tile a head: its masked key tiles count twice as well
 
 
