@@ -26,6 +26,10 @@ class Share:
         self.base = up(B * Sq * Hq * 4) + 1024 + (up(B * Sq * Hq * D * 2) if dtype == BF16 else 0)     # Delta, counters, scaled Q
         self.text = f"{('f32', 'bf16')[dtype]} {B} x {Hq}/{Hkv} x {D}, {Sq} rows at {q_offset} ({seg}, {q2}), {n} x {Sk}, causal {causal}"
 
+    def last_position(self):
+        d = self.d
+        return d.q_offset2 + d.Sq - d.q_seg - 1 if d.q_seg else d.q_offset + d.Sq - 1
+
     def size(self, mode):
         return int(api._lib.st_ring_workspace_bytes(C.byref(self.d), mode, 1))
 

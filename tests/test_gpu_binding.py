@@ -12,6 +12,21 @@ from util import upload
 pytestmark = pytest.mark.gpu
 
 
+class Watched:
+    """the native half, and what it answered: a status, or None where it left the call to ctypes"""
+    NAMES = {"ring_fwd", "ring_bwd", "block_fwd", "block_bwd", "merge", "combine", "delta", "cast"}
+
+    def __init__(self, half):
+        self.half, self.took, self.left = half, set(), set()
+
+    def __getattr__(self, name):
+        def call(*args):
+            status = getattr(self.half, name)(*args)
+            (self.left if status is None else self.took).add(name)
+            return status
+        return call
+
+
 class Wrapped(torch.Tensor):
     """a subclass: the native half does not look into it"""
 
@@ -57,17 +72,26 @@ def _run(w, q, ks, vs, d_o, offsets, where, scale, causal, order, stream=None):
 def test_both_halves_make_the_same_call(monkeypatch):
     w, q, ks, vs, d_o = _share()
     offsets, order = [w.k_offset(j) for j in range(3)], [2, 0, 1]
+    watched = lambda: monkeypatch.setattr(api, "_binding", Watched(native)) or api._binding
+    native = api._binding
+    seen = watched()
     plain = _run(w, q, ks, vs, d_o, offsets, w.q_where, w.scale, True, order)
-    forms = {"tuples and a parameter": (torch.nn.Parameter(q), tuple(ks), tuple(vs), d_o, tuple(offsets), tuple(w.q_where), w.scale, True, tuple(order)),
-             "numpy numbers, a list, an int": (q, ks, vs, d_o, list(np.array(offsets)), list(w.q_where), np.float64(w.scale), 1, list(np.array(order))),
-             "a subclass": (q.as_subclass(Wrapped), ks, vs, d_o.as_subclass(Wrapped), offsets, w.q_where, w.scale, True, order)}
+    assert seen.took == Watched.NAMES and not seen.left, "plain arguments go the short way"
+    uses_q = {"ring_fwd", "ring_bwd", "block_fwd", "block_bwd"}
+    # the calls that each form leaves to ctypes
+    forms = {"tuples and a parameter": (set(), (torch.nn.Parameter(q), tuple(ks), tuple(vs), d_o, tuple(offsets), tuple(w.q_where), w.scale, True, tuple(order))),
+             "numpy numbers, a list, an int": (uses_q, (q, ks, vs, d_o, list(np.array(offsets)), list(w.q_where), np.float64(w.scale), 1, list(np.array(order)))),
+             "a subclass": (uses_q | {"delta"}, (q.as_subclass(Wrapped), ks, vs, d_o.as_subclass(Wrapped), offsets, w.q_where, w.scale, True, order))}
     side = torch.cuda.Stream()
     side.wait_stream(torch.cuda.current_stream())
-    for name, form in forms.items():
+    for name, (left, form) in forms.items():
         for stream in (None, side, side.cuda_stream):
             print(f"[binding] {name}", flush=True)
+            seen = watched()
             with torch.cuda.stream(side if stream is not None else torch.cuda.current_stream()):      # tensors are made there too
                 got = _run(w, *form, stream=stream)
+            left_now = Watched.NAMES if isinstance(stream, int) else left          # a bare handle is ctypes' as well
+            assert seen.left == left_now and seen.took == Watched.NAMES - left_now, name
             for x, y in zip(plain, got):
                 assert torch.equal(x, y), name
 
