@@ -554,17 +554,21 @@ BwdSplit bwd_splits(const st::Shape& s, int dtype, const int64_t* k_offset, int 
     return x.slots > 0 ? 6 + in_l2 / 16e6 + (bytes - in_l2) / 5e6 : 0.0;
   };
   Job job[512 + st::kShareTiles];
-  const KeySplit whole(keys, 0);
-  KeySplit kv = whole;
-  double kv_us = jobs_us(job, whole.jobs(job, kv_cost));
+  int each_of[st::kKvSharesMost], ways = 1;            // unsplit, and the splits that have room
+  each_of[0] = 0;
   for (int k = 2, before = keys.top; k <= st::kKvSharesMost && k <= keys.top; ++k) {
     const int each = (keys.top + k - 1) / k;
     if (each == before) continue;
     before = each;
     const KeySplit x(keys, each);
     if (slot_bytes(x) > room || keys.heads * x.items > 4 * kPlanCus) break;
-    const double add = add_kv_us(x);
-    const double less = 0.95 * kv_us;                   // more workgroups have to be worth it
+    each_of[ways++] = each;
+  }
+  KeySplit kv(keys, 0);
+  double kv_us = jobs_us(job, kv.jobs(job, kv_cost));
+  for (int i = 1; i < ways; ++i) {
+    const KeySplit x(keys, each_of[i]);
+    const double add = add_kv_us(x), less = 0.95 * kv_us;     // more workgroups have to be worth it
     if (x.longest_us(kv_cost) + add >= less) continue;
     const double us = add + jobs_us(job, x.jobs(job, kv_cost), less - add);
     if (us < less) {
@@ -574,29 +578,41 @@ BwdSplit bwd_splits(const st::Shape& s, int dtype, const int64_t* k_offset, int 
   }
   size_t dq_bytes = r.bytes;
   if (plan_dq && !st::dq_few(s, n)) {
-    double least = kv_us + 4 + dq_us;
-    KeySplit pair_kv = kv;
+    // Whole key tiles and the split that is best by itself first; any other one has to be better by 10 %, as the model does not know
+    // that a share with the blocks of the diagonal takes longer (12/3 heads x 1408 rows: shares of 9 blocks a few per cent
+    // better than of 4 in the model, 81 and 74 us).  Where the one that is best by itself fills the chip, few workgroups beside
+    // dQ's may be far better: 2 x 8/4 heads x 1728 rows x 573 keys, three blocks 172 us and 224 in launches of their own.
+    double least = kv_us + 4 + dq_us, dq_work = 0, kv_work = 0;
+    for (int i = 0; i < walk.n; ++i) dq_work += (double)walk.heads * (walk.n == 1 ? walk.tiles : 1) * walk.units[i];
+    for (int i = 0; i < keys.n; ++i) kv_work += (double)keys.heads * keys.G * keys.c[i].tiles * keys.c[i].blocks;
+    const int by_itself = kv.each;
     auto together = [&](const KeySplit& y, const Split& x) {
       const size_t left = room - slot_bytes(y);
       if (x.n > 1 && (size_t)x.rows_own0 * row_bytes > left) return;
-      const double add = (x.n > 1 ? add_us + more_than_8_us(x) + part_us(x.rows + 2 * s.Sq) : 0) + add_kv_us(y);
-      if (x.longest_us(cost, y.workgroups()) + add >= least) return;
+      const double less = (y.each == 0 || y.each == by_itself ? 1 : 0.9) * least, add = (x.n > 1 ? add_us + more_than_8_us(x) + part_us(x.rows + 2 * s.Sq) : 0) + add_kv_us(y);
+      if (x.longest_us(cost, y.workgroups()) + add >= less || y.longest_us(kv_cost, x.workgroups()) + add >= less) return;
+      // not before all of the work is done, evenly spread
+      const int64_t beside = x.workgroups() + y.workgroups();
+      const double fixed = x.workgroups() * cost.us(0, beside) + y.workgroups() * kv_cost.us(0, beside);
+      const double work = dq_work * (cost.us(1, beside) - cost.us(0, beside)) + kv_work * (kv_cost.us(1, beside) - kv_cost.us(0, beside));
+      if ((fixed + work) / kPlanCus + add >= less) return;
       const int m = y.jobs(job, kv_cost, x.workgroups());
-      const double us = add + jobs_us(job, m + x.jobs(job + m, cost, y.workgroups()), least - add);
-      if (us >= least) return;
+      const double us = add + jobs_us(job, m + x.jobs(job + m, cost, y.workgroups()), less - add);
+      if (us >= less) return;
       least = us;
       const bool own0 = x.n > 1 && (size_t)x.rows * row_bytes > left;
       r.dq = x.table(own0);
       dq_bytes = x.n > 1 ? (size_t)(own0 ? x.rows_own0 : x.rows) * row_bytes : 0;
       r.pair = true;
-      pair_kv = y;
+      kv = y;
     };
-    for (int split_kv = 0; split_kv <= (kv.each > 0); ++split_kv) {
-      const KeySplit y = split_kv ? KeySplit(keys, kv.each) : whole;
-      together(y, Split(walk, dq_units));
-      if (split_dq) each_split(walk, kMaxSplits, [&](const Split& x) { together(y, x); });
-    }
-    if (r.pair) kv = pair_kv;
+    for (const bool others : {false, true})
+      for (int i = 0; i < ways; ++i) {
+        if (others == (i == 0 || each_of[i] == by_itself)) continue;
+        const KeySplit y(keys, each_of[i]);
+        together(y, Split(walk, dq_units));
+        if (split_dq) each_split(walk, kMaxSplits, [&](const Split& x) { together(y, x); });
+      }
   }
   r.kv_each = kv.each;
   r.kv_items = (int)kv.items;

@@ -114,6 +114,13 @@ def test_a_tie_goes_to_the_common_launch():
     assert all(x[10] for x in share.plan(list(range(16)), FUSED, False, -1))
 
 
+def test_key_tiles_that_fill_the_chip_by_themselves():
+    """The common launch is looked for with every way to split them: 2 x 8/4 heads x 1728 rows x 573 keys, three blocks 172 us
+    together and 224 in launches of their own."""
+    share = Share(BF16, 2, 8, 4, 128, 1728, 573, [0, 573, 1146], 1146)
+    assert all(x[10] and x[8] for x in share.plan([0, 1, 2], -1, False, -1))
+
+
 def test_small_shares_ask_for_little():
     assert _ring(F32, 1, 1, 1, 64, 128, 4, 3).size(FUSED) <= 1 << 20              # 40 KB of it Delta and what surrounds it
     assert _ring(F32, 1, 8, 2, 128, 512, 8, 7).size(FUSED) <= 48 << 20
