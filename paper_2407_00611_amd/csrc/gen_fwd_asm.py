@@ -630,8 +630,9 @@ def generate():
 
     e.comment("---- tiles T with T and T + 1 whole")
     if D == 64:
-        # Where the loop lies among the 64-byte lines of the instruction cache is 1 to 3 % at this head size: 24 heads x 16384
-        # rows x 131072 keys 12.3 ms from byte 4 of a line, 12.4 from 16, 32 or 48, 12.5 to 12.6 from 0 or 8.  At 128 it is nothing.
+        # Where the loop lies among the 64-byte lines of the instruction cache was 1 to 3 % at this head size when the loop still
+        # kept a row maximum (24 heads x 16384 rows x 131072 keys 12.3 ms from byte 4 of a line, 12.4 from 16, 32 or 48, 12.5
+        # to 12.6 from 0 or 8; 11.1 today from byte 4, the others not measured again).  At 128 it is nothing.
         e.raw(".p2align 6")
         e.raw("s_nop 0")
     e.raw(l_loop + ":")

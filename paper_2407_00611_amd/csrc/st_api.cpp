@@ -364,8 +364,7 @@ struct BwdSplit {
   bool pair = false;
   size_t dq_bytes = 0, bytes = 0;
 };
-// dQ: the forward's model (the launch + the pass that adds up); a 256 x 64 tile is three contractions instead of two: 1.7 us at
-// head size 128, 1.05 at 64, behind 14 and 11 us.  fp32: the eight (four beyond head size 128) wavefronts of a workgroup take a
+// dQ: the forward's model (the launch + the pass that adds up) with the constants of dq_cost.  fp32: the eight (four beyond head size 128) wavefronts of a workgroup take a
 // 32-key tile each in 16 us at head size 128, 9 at 64, 5.5 at 32, and 16 at 256 (8 heads x 512 rows x 8 chunks of 512 keys at
 // head size 128: 128 workgroups, 270 us; 157 us as two shares each and the adding pass); 10 us for the adding pass, as walks
 // of two turns gain less than its launch takes.

@@ -200,12 +200,13 @@ __host__ __device__ inline int64_t dq_part_rows_all(const QueryTiles& q, const T
 __host__ __device__ inline float* dq_part(float* parts, const Shape& s, const QueryTiles& q, const TileShares& t, int b, int qt, int y) {
   return parts + (b * dq_part_rows_all(q, t) + dq_part_rows(q, t, qt) + (int64_t)y * q.rows_of(qt)) * s.Hq * s.D;
 }
-// (not a multiple of a large power of two: workgroups in step would write to the same memory channels)
 // fp32: sum of share `y` >= 1 of chunk c, laid out as dk[c] (w = 0) and dv[c] (1)
 __host__ __device__ inline int64_t f32_kv_floats(const Shape& s) { return ((int64_t)s.B * s.Sk * s.Hkv * s.D + 63) / 64 * 64; }
 __host__ __device__ inline float* f32_kv_part(float* parts, const Shape& s, int n_chunks, int y, int c, int w) {
   return parts + ((int64_t)(y - 1) * n_chunks + c) * 2 * f32_kv_floats(s) + w * f32_kv_floats(s);
 }
+// bf16: a slot of a key tile's sums, dk behind dv (not a multiple of a large power of two: workgroups in step would write to the
+// same memory channels)
 __host__ __device__ inline int64_t kv_slot_floats(const Shape& s) { return (int64_t)2 * kDkvFastKeys * s.D + 17 * 64; }
 constexpr int kQueueInts = 8 * 32;   // at most 8 counters, 128 bytes apart
 // passed by value: a kernel takes 4096 bytes of arguments
