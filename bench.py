@@ -330,9 +330,9 @@ def main() -> int:
     pairs = si.visible_pairs(w, met) * w.Hq * w.B
     # algorithmic work of each MFMA kernel per launch: forward = QK^T and PV; the dK/dV kernel owns
     # S, dP, dV, dK (four of the five backward contractions); the dQ kernel owns dQ (its recomputed
-    # S and dP earn nothing); the fp32 backward is one kernel
+    # S and dP earn nothing); in one walk they are one kernel, as the fp32 backward is
     algo = {"fwd_bf16": 4 * w.D * pairs, "bwd_dkv_bf16": 8 * w.D * pairs, "bwd_dq_bf16": 2 * w.D * pairs,
-            "fwd_f32": 4 * w.D * pairs, "bwd_f32": 10 * w.D * pairs}
+            "bwd_one_bf16": 10 * w.D * pairs, "fwd_f32": 4 * w.D * pairs, "bwd_f32": 10 * w.D * pairs}
     per_kernel = {}
     for name, (launches, total_ms) in kernels.items():
         avg = total_ms / max(launches, 1)

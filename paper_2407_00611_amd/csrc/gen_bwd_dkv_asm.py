@@ -236,7 +236,7 @@ def request_code(stage, st_set):
     return c
 
 
-def stat_publish(e, st_set, stage, tag):
+def stat_publish_to(e, stat_l, st_set, stage, tag):
     """-lse log2(e) (or -inf for an empty row, whose P must be 0) and -Delta of the 32 rows to the stage's statistics slot."""
     rs = ST + 2 * st_set
     e.raw(f"v_mul_f32 {vr(TMP)}, 0xbfb8aa3b, {vr(rs)}")
@@ -245,7 +245,11 @@ def stat_publish(e, st_set, stage, tag):
     e.raw("s_nop 1")
     e.raw(f"v_cndmask_b32 {vr(TMP)}, {vr(TMP)}, {vr(NINF)}, vcc")
     e.raw(f"v_cndmask_b32_e64 {vr(TMP)}, {vr(TMP)}, {vr(TMP + 1)}, {sr(T_HIMASK, 2)}")
-    e.ds_read(f"ds_write_b32 {vr(STAT_L)}, {vr(TMP)} offset:{STATS + 256 * stage}", tag)
+    e.ds_read(f"ds_write_b32 {vr(stat_l)}, {vr(TMP)} offset:{STATS + 256 * stage}", tag)
+
+
+def stat_publish(e, st_set, stage, tag):
+    stat_publish_to(e, STAT_L, st_set, stage, tag)
 
 
 class Pool:
@@ -479,7 +483,7 @@ class InFlight:
             self.e.raw(f"s_waitcnt {self.counter}({len(self.q)})")
 
 
-def epilogue(e):
+def epilogue(e, ragged_tiles=True):
     """dk_acc (+)= scale * dK, dv_acc (+)= dV.  The accumulators hold dK^T / dV^T with lane = key, so a lane owns
     16-byte pieces of 32 different rows of the output: written like that, every access of a wavefront touches
     32 cache lines and the epilogue is bound by the rate of cache-line lookups.  Each wavefront therefore turns
@@ -531,12 +535,14 @@ def epilogue(e):
     e.raw(f"s_lshr_b32 {sr(STEP2)}, {sr(STEP)}, 1")
 
     passes = [(nb, which) for nb in range(NKB) for which in ("k", "v")]
-    l_var = [e.label(f"epi{v}") for v in range(8)]         # 4 and up: a tile of fewer than 256 keys
+    n_var = 8 if ragged_tiles else 4
+    l_var = [e.label(f"epi{v}") for v in range(n_var)]     # 4 and up: a tile of fewer than 256 keys
     l_end = e.label("epi_end")
-    e.raw(f"s_cmp_lg_u32 {sr(S_ROWS)}, 256")
-    e.raw(f"s_cselect_b32 {sr(T_MT)}, 4, 0")
-    e.raw(f"s_or_b32 {sr(S_FLAGS)}, {sr(S_FLAGS)}, {sr(T_MT)}")
-    for v in range(1, 8):
+    if ragged_tiles:
+        e.raw(f"s_cmp_lg_u32 {sr(S_ROWS)}, 256")
+        e.raw(f"s_cselect_b32 {sr(T_MT)}, 4, 0")
+        e.raw(f"s_or_b32 {sr(S_FLAGS)}, {sr(S_FLAGS)}, {sr(T_MT)}")
+    for v in range(1, n_var):
         e.raw(f"s_cmp_eq_u32 {sr(S_FLAGS)}, {v}")
         e.raw(f"s_cbranch_scc1 {l_var[v]}")
 
@@ -626,10 +632,10 @@ def epilogue(e):
             if not assign and p + deep < len(passes):   # the registers just stored take the HBM values of a later pass
                 loads(p + deep)
 
-    for v in range(8):
+    for v in range(n_var):
         e.raw(l_var[v] + ":")
         body(assign=bool(v & 1), lowp=bool(v & 2), ragged=bool(v & 4))
-        if v < 7:
+        if v < n_var - 1:
             e.raw(f"s_branch {l_end}")
     e.raw(l_end + ":")
 

@@ -1,0 +1,686 @@
+#!/usr/bin/env python3
+"""Generates the gfx950 assembly of the loop that makes dK, dV and dQ in one walk (head_dim 128) as a C string literal.
+
+    python gen_bwd_one_asm.py > st_bwd_one_asm.inc          (build.py does this before compiling)
+
+The walk, the masks, the statistics and the epilogue are those of gen_bwd_dkv_asm.py; what is said there holds here.  Five contractions
+a pair in place of the seven that the loop there and the one of gen_bwd_dq_asm.py execute: S and dP are not made again for dQ.
+
+  * The packed dS of a block goes to LDS as [key][row] (two buffers; rows padded to 72 bytes, so that the 8-byte writes and the
+    transposing reads meet few bank conflicts).  From the barrier of the next block on, wavefront w contracts all 256 keys of it with
+    columns 32 w .. 32 w + 31 of K: dQ^T[32 x 32] += K^T dS^T, sixteen MFMAs spread to the barrier after that.  K lies in LDS for
+    this, as the tile that S reads; V is resident instead.
+  * dQ of a (head, block) pair, 16 KiB, travels from key tile to key tile of its KV head through a workspace in the order of the walk
+    (and of the accumulator registers: 1 KiB an access; read and written where dQ lies, in rows of 16 KiB, the exchange cost more than
+    the two contractions).  A wavefront reads what the tile before has left, adds its own and stores it; key tile i may read a pair
+    when wavefront w of tile i - 1 has counted it done.  All of them run on one XCD, whose L2 the loads (sc1: past
+    the L1) and stores meet in.  The first tile reads zeros.  Every sum has a fixed order; a pass behind the launch multiplies them by
+    the softmax scale and adds them to dQ.
+  * Under way two pairs behind the block in hand: pair x is contracted behind the barrier of block x + 1, read in block x + 2
+    (into the registers that the exponents' start values have just left), added and stored before its barrier, and counted
+    when the stores are acknowledged.  Pairs -2 and -1 do not exist; the workspace has room for them.
+  * LDS rows of Q', dO and K tiles: groups of four rows (1 KiB, what one direct-to-LDS load fills), 16 bytes between groups; the
+    16-byte chunk c of row r lies at c ^ 4 (r % 4).  Conflict-free like the swizzle of the other loops, and all but two bits of an
+    offset are immediates, which leaves the sixteen registers that dQ's accumulator takes.
+  * Three stages of tiles, two blocks ahead; with the two buffers of dS six copies of the block make the loop.
+
+What bounds it: the matrix cores at the chip's power limit, as with the two loops it replaces.  A loop of this instruction mix
+without dependences (80 MFMAs, 44 16-byte and 96 transposing LDS reads, 96 VALU instructions, the exchange of a pair and the tile loads per
+block and wavefront) takes 2085 ns on random data, those of the two loops 1547 + 1115.  Backward of 32/8 heads x 4096 rows x 32 chunks
+20.0 -> 16.8 ms, 32 heads x 2048 rows x 16 chunks 2.75 -> 2.39 (64 blocks a tile: 25 us of its 150 are before and behind the loop).
+Where the MFMAs of a pair lie in the block, how far ahead their operands are read and how much side work a slot gets moved that by less than
+1 % each; half of them under the first phase, whose reads are the densest, cost 3 %.
+"""
+import os
+import sys
+
+import gen_bwd_dkv_asm as kv
+from gen_bwd_dkv_asm import (ACC_K, ACC_V, DB, DP0, KS, ND, NDQ, NINF, NKB, NL, NSLOT, P16, P2, P3, P4, POOL0, S0, ST, TMP,
+                             S_CI, S_CI0, S_DIAG, S_EVT, S_FLAGS, S_GREC, S_LDS, S_NIN, S_NRAG, S_NSTEPS, S_QOUT, S_ROWS, S_SQ, S_VRS, S_WAVE, T_CMP,
+                             T_DBLK, T_DLHEAD, T_DLPTR, T_DOHEAD, T_DOPTR, T_DSTEP, T_HIMASK, T_LSEHEAD, T_LSEPTR, T_M0, T_MASK, T_MRET, T_MT,
+                             T_OHI, T_QHEAD, T_QPTR, T_REM, T_VPTR, T_X)
+from st_asmgen import Emitter, ar, sr, vr, write_inc
+
+assert kv.D == 128
+NS, PF, COPIES = 3, 2, 6
+GRP = 1024 + 16                                      # bytes from one group of four rows to the next
+TQ = 8 * GRP                                         # a 32-row tile
+def QT(s): return 1024 + 2 * TQ * s
+def DOT(s): return 1024 + 2 * TQ * s + TQ
+KT = 1024 + 2 * TQ * NS                              # K tile: 256 rows
+DSR_ROW = 72                                         # bytes of a key's 32 dS
+DS_BYTES = 256 * DSR_ROW
+DS0 = KT + 64 * GRP
+PBLK = DS0 + 2 * DS_BYTES                            # as in gen_bwd_dkv_asm.py; it stays, the mask routine reads it
+NUNI = 20                                            # words of the uniform block behind it
+LDS_BYTES = PBLK + 256 * 32 + 4 * NUNI
+assert LDS_BYTES <= 163840 and PBLK >= 4 * 2 * 32 * (4 * 128 + 16)
+# words of the uniform block behind the six of gen_bwd_dkv_asm.py: what only the epilogue needs
+U_DKPTR, U_DVPTR, U_RS32, U_SCALE, U_FLAGS, U_DKLP, U_DVLP = 8, 10, 12, 13, 14, 16, 18
+SLICE = 4096                                         # a wavefront's part of a pair in the workspace
+PAIR = 4 * SLICE
+
+# registers
+VF = kv.KF                                           # resident V fragments
+X, XK, TR, KTR, DSW, DSR, DQO, FLG = 216, 220, 224, 228, 229, 230, 231, 232
+QOFF, DOOFF, STAT_G, STAT_L, G16, ACC_Q = 233, 235, 237, 238, 239, 240
+OLD = NL                                             # what the tile before left, from slot 3 to the stores
+# scalars in the places of the epilogue's inputs
+S_DQL, S_DQW, S_DQINC, S_CNT, S_PRED, S_OWN = 52, 54, 57, 59, 60, 62
+SPINS = int(os.environ.get("ST_GEN_ONE_SPINS", 1 << 21))     # most polls of a wait: seconds; then it goes on, so that every launch ends
+
+LAT = int(os.environ.get("ST_GEN_ONE_LAT", 3))
+LATQ = int(os.environ.get("ST_GEN_ONE_LATQ", 3))
+BUDGET = int(os.environ.get("ST_GEN_ONE_BUDGET", 6))
+BUDGET_Q = int(os.environ.get("ST_GEN_ONE_BUDGETQ", 4))
+EARLY = 12
+SYNC_SLOT, PUBLISH_SLOT = P3 - 1, P3 - 6
+# slots behind which the MFMAs of a pair are issued, from the barrier of one block (slot 32 on) to that of the next (64 + 26)
+DQ_AT = [int(x) for x in os.environ.get("ST_GEN_ONE_AT", "35,37,39,41,43,45,47,49,52,55,58,61,80,82,84,86").split(",")]
+assert len(DQ_AT) == 16 and DQ_AT == sorted(DQ_AT) and DQ_AT[0] - LATQ > SYNC_SLOT and DQ_AT[-1] <= NSLOT + P3 - 6
+N_A = sum(1 for p in DQ_AT if p < NSLOT)             # of them in the block behind the pair's own
+SUM_SLOT = P3 - 3                                    # the sums behind this slot, the stores behind the next
+NREQ = 2 + 2 * NDQ
+assert NREQ == 6
+
+
+class Pool(kv.Pool):
+    pass
+
+
+class OneEmitter(Emitter):
+    def ds_read(self, text, tag):
+        if len(self.ds) >= 15:                          # the counter has four bits
+            self.need(self.ds[2])
+        super().ds_read(text, tag)
+
+
+def request_code(stage, st_set):
+    c = [[f"global_load_dword {vr(ST + 2 * st_set)}, {vr(STAT_G)}, {sr(T_LSEPTR, 2)}",
+          f"global_load_dword {vr(ST + 2 * st_set + 1)}, {vr(STAT_G)}, {sr(T_DLPTR, 2)}"]]
+    for ptr, off, tbase in ((T_QPTR, QOFF, QT(stage)), (T_DOPTR, DOOFF, DOT(stage))):
+        for j in range(NDQ):
+            c.append([f"s_add_u32 m0, {sr(T_M0)}, {tbase + 4 * GRP * j}", "s_nop 0",
+                      f"global_load_lds_dwordx4 {vr(off + j)}, {sr(ptr, 2)}"])
+    return c
+
+
+def flag_load(e):
+    e.raw(f"v_mov_b32 {vr(TMP + 2)}, 0")
+    e.raw(f"global_load_dword {vr(FLG)}, {vr(TMP + 2)}, {sr(S_PRED, 2)} sc1")
+
+
+def flag_wait(e, newer):
+    """Until the tile before has counted the pair; `newer` memory operations were issued behind the load of its count."""
+    l_spin, l_ok = e.label("spin"), e.label("counted")
+    if newer is not None:
+        e.raw(f"s_waitcnt vmcnt({newer})")
+        e.raw(f"v_readfirstlane_b32 {sr(T_MT)}, {vr(FLG)}")
+        e.raw(f"s_cmp_ge_i32 {sr(T_MT)}, {sr(S_CNT)}")
+        e.raw(f"s_cbranch_scc1 {l_ok}")
+    e.raw(f"s_mov_b32 {sr(T_X)}, {SPINS}")
+    e.raw(l_spin + ":")
+    flag_load(e)
+    e.raw("s_waitcnt vmcnt(0)")
+    e.raw(f"v_readfirstlane_b32 {sr(T_MT)}, {vr(FLG)}")
+    e.raw(f"s_cmp_ge_i32 {sr(T_MT)}, {sr(S_CNT)}")
+    e.raw(f"s_cbranch_scc1 {l_ok}")
+    e.raw("s_sleep 1")
+    e.raw(f"s_sub_u32 {sr(T_X)}, {sr(T_X)}, 1")
+    e.raw(f"s_cmp_lg_u32 {sr(T_X)}, 0")
+    e.raw(f"s_cbranch_scc1 {l_spin}")
+    e.raw(l_ok + ":")
+
+
+def flag_store(e):
+    e.raw(f"v_mov_b32 {vr(TMP + 2)}, 0")
+    e.raw(f"v_mov_b32 {vr(TMP + 1)}, {sr(S_CNT)}")
+    e.raw("s_mov_b64 exec, 1")
+    e.raw(f"global_store_dword {vr(TMP + 2)}, {vr(TMP + 1)}, {sr(S_OWN, 2)}")
+    e.raw("s_mov_b64 exec, -1")
+
+
+def old_load(e, j):
+    e.raw(f"global_load_dwordx4 {vr(OLD + 4 * j, 4)}, {vr(DQO)}, {sr(S_DQL, 2)} offset:{1024 * j} sc1")
+
+
+def sum_store(e, j):
+    e.raw(f"global_store_dwordx4 {vr(DQO)}, {vr(OLD + 4 * j, 4)}, {sr(S_DQW, 2)} offset:{1024 * j}")
+
+
+def next_pair():
+    return [f"s_add_u32 {sr(S_DQL)}, {sr(S_DQL)}, {sr(S_DQINC)}", f"s_addc_u32 {sr(S_DQL + 1)}, {sr(S_DQL + 1)}, 0",
+            f"s_add_u32 {sr(S_DQW)}, {sr(S_DQW)}, {PAIR}", f"s_addc_u32 {sr(S_DQW + 1)}, {sr(S_DQW + 1)}, 0"]
+
+
+def rd_dq(e, pool, tag, t, buf):
+    """The two operands of MFMA t of a pair: keys 16 t .. + 15 of K^T and of dS^T."""
+    r = pool.alloc(tag + "k", 1)
+    e.ds_read(f"ds_read_b64_tr_b16 {vr(r, 2)}, {vr(KTR)} offset:{4 * GRP * t}", tag + "klo")
+    e.ds_read(f"ds_read_b64_tr_b16 {vr(r + 2, 2)}, {vr(KTR)} offset:{4 * GRP * t + 2 * GRP}", tag + "k")
+    r = pool.alloc(tag + "s", 1)
+    e.ds_read(f"ds_read_b64_tr_b16 {vr(r, 2)}, {vr(DSR)} offset:{DS_BYTES * buf + 16 * DSR_ROW * t}", tag + "slo")
+    e.ds_read(f"ds_read_b64_tr_b16 {vr(r + 2, 2)}, {vr(DSR)} offset:{DS_BYTES * buf + 16 * DSR_ROW * t + 8 * DSR_ROW}", tag + "s")
+
+
+def mfma_dq(e, pool, tag, t):
+    e.need(tag + "k")
+    e.need(tag + "s")
+    a, b = pool.use(tag + "k"), pool.use(tag + "s")
+    e.mfma(vr(ACC_Q, 16), vr(a, 4), vr(b, 4), "0" if t == 0 else vr(ACC_Q, 16))
+
+
+def plan_dq(e, pool, buf, seq):
+    """Reads and MFMAs of a pair by slot: in the block behind its own, and in the one after that (negative slots: the tail of the first)."""
+    parts = [({k: [] for k in range(NSLOT)}, {k: [] for k in range(NSLOT)}), ({k: [] for k in range(-EARLY, NSLOT)}, {k: [] for k in range(NSLOT)})]
+    for t, p in enumerate(DQ_AT):
+        tag = f"{seq}dq{t}_"
+        def rd(tag=tag, t=t): rd_dq(e, pool, tag, t, buf)
+        def mm(tag=tag, t=t): mfma_dq(e, pool, tag, t)
+        second = p >= NSLOT
+        parts[second][0][p - LATQ - NSLOT * second].append(rd)
+        parts[second][1][p - NSLOT * second].append(mm)
+    return parts
+
+
+def plan_reads(e, pool, stage, seq):
+    qt, dot_, stats = QT(stage), DOT(stage), 256 * stage
+    reads = {k: [] for k in range(-EARLY, NSLOT)}
+
+    def plan(first_use, fn):
+        reads[first_use - LAT].append(fn)
+
+    def rd_nat(tag, imm, ks, xbase, uses):
+        def f():
+            r = pool.alloc(tag, uses)
+            e.ds_read(f"ds_read_b128 {vr(r, 4)}, {vr(xbase + ks // 2)} offset:{imm + 32 * (ks % 2)}", tag)
+        return f
+
+    def rd_tr(tag, imm, m, db):
+        def f():
+            r = pool.alloc(tag, NKB)
+            e.ds_read(f"ds_read_b64_tr_b16 {vr(r, 2)}, {vr(TR + db)} offset:{imm + 4 * GRP * m}", tag + "lo")
+            e.ds_read(f"ds_read_b64_tr_b16 {vr(r + 2, 2)}, {vr(TR + db)} offset:{imm + 4 * GRP * m + 2 * GRP}", tag)
+        return f
+
+    def rd_stat(tag, base_reg, imm, js):
+        def f():
+            for j in js:
+                e.ds_read(f"ds_read_b128 {vr(base_reg + 4 * j, 4)}, {vr(G16)} offset:{imm + 32 * j}", f"{tag}{j}")
+        return f
+
+    for ks in range(KS):
+        plan(2 * ks, rd_nat(f"{seq}q{ks}", qt, ks, X, NKB))
+        for nb in range(NKB):
+            plan(2 * ks + nb, rd_nat(f"{seq}K{nb}_{ks}", 8 * GRP * nb, ks, XK, 1))
+        if ks == 0:
+            reads[-EARLY].append(rd_stat(f"{seq}nl", NL, stats, (0, 1)))
+            reads[-EARLY + 1].append(rd_stat(f"{seq}nl", NL, stats, (2, 3)))
+            reads[-EARLY + 4].append(rd_stat(f"{seq}nd", ND, stats + 128, (0, 1)))
+            reads[-EARLY + 5].append(rd_stat(f"{seq}nd", ND, stats + 128, (2, 3)))
+    for ks in range(KS):
+        plan(P2 + 2 * ks, rd_nat(f"{seq}do{ks}", dot_, ks, X, NKB))
+    for ph, tile in (("dV", dot_), ("dK", qt)):
+        for m in range(2):
+            for db in range(DB):
+                plan((P3 if ph == "dV" else P4) + 2 * (DB * m + db), rd_tr(f"{seq}{ph}t{m}_{db}", tile, m, db))
+    return reads
+
+
+def gen_step(e, pool, u, seq, reads, next_reads, dq_behind, dq_next, dq_start, masked):
+    """Block u of the six copies.  dq_behind: the pair two blocks back, finished here; dq_start: the pair of the block before, begun here;
+    dq_next: the same pair's second part, whose first reads are at the tail of this block."""
+    stage, buf = u % NS, u % 2
+    e.comment(f"================ block {u}")
+    slots = [("S", ks, nb) for ks in range(KS) for nb in range(NKB)] + [("dP", ks, nb) for ks in range(KS) for nb in range(NKB)]
+    slots += [(ph, m, db, nb) for ph in ("dV", "dK") for m in range(2) for db in range(DB) for nb in range(NKB)]
+
+    def S(nb, v): return S0 + 16 * nb + v
+    def DP(nb, v): return DP0 + 16 * nb + v
+    valu = []                                          # (earliest slot, text, registers written, issue units, LDS write behind it)
+    for m in range(2):
+        for nb in range(NKB):
+            early = P2 + 1 + nb
+            for grp in range(2):
+                for v in [8 * m + 4 * grp + i for i in range(4)]:
+                    valu.append((early, f"v_exp_f32 {vr(S(nb, v))}, {vr(S(nb, v))}", (), 2, None))
+                if grp == 1:
+                    for i in range(4):
+                        d, a = P16 + 8 * nb + 4 * m + i, S(nb, 8 * m + 2 * i)
+                        valu.append((max(early, P2 + 4), f"v_cvt_pk_bf16_f32 {vr(d)}, {vr(a)}, {vr(a + 1)}", (d,), 1, None))
+    n_first = len(valu)
+    for m in range(2):
+        for nb in range(NKB):
+            early = P3 + 1 + nb
+            for v in range(8 * m, 8 * m + 8):
+                valu.append((early, f"v_mul_f32 {vr(DP(nb, v))}, {vr(S(nb, v))}, {vr(DP(nb, v))}", (), 1, None))
+            for i in range(4):
+                d, a = DP(nb, 4 * m + i), DP(nb, 8 * m + 2 * i)
+                valu.append((early, f"v_cvt_pk_bf16_f32 {vr(d)}, {vr(a)}, {vr(a + 1)}", (d,), 1, None))
+                if i % 2:                              # rows 16 m + 8 (i / 2) + 4 g .. + 3 of the lane's key
+                    off = DS_BYTES * buf + 32 * DSR_ROW * nb + 16 * (2 * m + i // 2)
+                    valu.append((early, f"ds_write_b64 {vr(DSW)}, {vr(d - 1, 2)} offset:{off}", (), 2, f"{seq}ds{m}{nb}{i}"))
+    vi, produced = [0], {}
+
+    def emit_valu(item):
+        _, text, writes, units, tag = item
+        if tag:
+            e.ds_read(text, tag)
+        else:
+            e.valu(text, writes)
+        for r in writes:
+            produced[r] = True
+        return units
+
+    def flush_until(regs):
+        while not all(produced.get(r) for r in regs):
+            assert vi[0] < len(valu), "packed operand never produced"
+            emit_valu(valu[vi[0]])
+            vi[0] += 1
+
+    side = {k: [] for k in range(NSLOT)}               # scalar and memory work behind fixed slots: text, or a function
+    side[2].append(lambda: flag_wait(e, NREQ + 1))     # behind the count's load: the request, a count's store
+    for j in range(4):
+        side[3 + j].append(lambda j=j: old_load(e, j))
+    for j in range(4):
+        side[SUM_SLOT + 1 + j].append(lambda j=j: sum_store(e, j))
+    side[SUM_SLOT + 5] += next_pair()
+    side[SUM_SLOT + 5].append(lambda: flag_load(e))
+    req = request_code((u + PF) % NS, u % 2)
+    for i, grp in enumerate(req):
+        side[SUM_SLOT + 6 + i] += grp
+    assert SUM_SLOT + 5 > SYNC_SLOT
+    adv = kv.advance_code()
+    per = 4
+    for i in range(0, len(adv), per):
+        side[P4 + i // per] += adv[i:i + per]
+    assert P4 + (len(adv) - 1) // per < NSLOT - 3
+    def counted():
+        e.raw(f"s_waitcnt vmcnt({NREQ + 1})")          # behind the stores: the count's load, the request
+        flag_store(e)
+        e.raw(f"s_add_u32 {sr(S_CNT)}, {sr(S_CNT)}, 1")
+    side[NSLOT - 2].append(counted)
+
+    stw = f"{seq}stw"
+
+    def fill(units, budget, k):
+        while vi[0] < len(valu) and valu[vi[0]][0] <= k and units + valu[vi[0]][3] <= budget:
+            units += emit_valu(valu[vi[0]])
+            vi[0] += 1
+
+    for k, sl in enumerate(slots):
+        ph = sl[0]
+        if ph == "S":
+            _, ks, nb = sl
+            tag = f"{seq}q{ks}"
+            e.need(tag)
+            e.need(f"{seq}K{nb}_{ks}")
+            if ks == 0:
+                e.need(f"{seq}nl3")
+            c = vr(NL, 16) if ks == 0 else vr(S0 + 16 * nb, 16)
+            a_reg = pool.use(tag)
+            e.mfma(vr(S0 + 16 * nb, 16), vr(a_reg, 4), vr(pool.use(f"{seq}K{nb}_{ks}"), 4), c)
+        elif ph == "dP":
+            _, ks, nb = sl
+            e.need(f"{seq}do{ks}")
+            if ks == 0:
+                e.need(f"{seq}nd3")
+            c = vr(ND, 16) if ks == 0 else vr(DP0 + 16 * nb, 16)
+            e.mfma(vr(DP0 + 16 * nb, 16), vr(pool.use(f"{seq}do{ks}"), 4), vr(VF(nb, ks), 4), c)
+        else:
+            _, m, db, nb = sl
+            tag = f"{seq}{ph}t{m}_{db}"
+            e.need(tag)
+            b0, acc = (P16 + 8 * nb + 4 * m, ACC_V(db, nb)) if ph == "dV" else (DP0 + 16 * nb + 4 * m, ACC_K(db, nb))
+            flush_until([b0 + i for i in range(4)])
+            e.mfma(ar(acc, 16), vr(pool.use(tag), 4), vr(b0, 4), ar(acc, 16), breads=[b0 + i for i in range(4)])
+        # ---- side work of this slot
+        n0 = len(e.lines)
+        for fn in reads[k] + next_reads.get(k - NSLOT, []) + dq_start[0].get(k, []) + dq_behind[0].get(k, []) + dq_next[0].get(k - NSLOT, []):
+            fn()
+        for x in side[k]:
+            if callable(x):
+                x()
+            else:
+                e.raw(x)
+        units = len(e.lines) - n0
+        if masked and k == P2 + 1:
+            e.raw(f"s_swappc_b64 {sr(T_MRET, 2)}, {sr(T_MASK, 2)}")
+        if k == PUBLISH_SLOT:
+            e.raw("s_waitcnt vmcnt(5)")                # behind the request of the next block: a count's store, what the tile before left
+            kv.stat_publish_to(e, STAT_L, (u + 1) % 2, (u + 1) % NS, stw)
+            units += 8
+        if k == SUM_SLOT:
+            e.raw("s_waitcnt vmcnt(0)")
+            for v in range(16):
+                e.raw(f"v_add_f32 {vr(OLD + v)}, {vr(OLD + v)}, {vr(ACC_Q + v)}")
+            units += 16
+        fill(units, BUDGET, k)
+        for fn in dq_start[1].get(k, []) + dq_behind[1].get(k, []):
+            fn()
+            fill(0, BUDGET_Q, k)
+        if k == SYNC_SLOT:
+            e.need(stw)                                # and with it everything older: dS of the block before
+            e.raw("s_barrier")
+    assert vi[0] == len(valu), f"VALU work left over: {len(valu) - vi[0]}"
+
+
+def pblk_address(e, reg, tmp):
+    """reg = LDS address of this thread's parameters"""
+    e.raw(f"v_mbcnt_lo_u32_b32 {vr(reg)}, -1, 0")
+    e.raw(f"v_mbcnt_hi_u32_b32 {vr(reg)}, -1, {vr(reg)}")
+    e.raw(f"v_lshlrev_b32 {vr(reg)}, 5, {vr(reg)}")
+    e.raw(f"s_lshl_b32 {sr(tmp)}, {sr(S_WAVE)}, 11")
+    e.raw(f"s_add_u32 {sr(tmp)}, {sr(tmp)}, {sr(S_LDS)}")
+    e.raw(f"s_add_u32 {sr(tmp)}, {sr(tmp)}, {PBLK}")
+    e.raw(f"v_add_u32 {vr(reg)}, {sr(tmp)}, {vr(reg)}")
+
+
+def gen_whole_offsets(e, reg, tmp):
+    pblk_address(e, reg, tmp)
+    for i, dst in enumerate((QOFF, QOFF + 1, DOOFF, DOOFF + 1, STAT_G)):
+        e.raw(f"ds_read_b32 {vr(dst)}, {vr(reg)} offset:{8 + 4 * i}")
+    e.raw("s_waitcnt lgkmcnt(0)")
+
+
+def gen_mask_routine(e):
+    """As in gen_bwd_dkv_asm.py, with the parameters of a thread read from LDS."""
+    n4, low, high = TMP, TMP + 1, FLG
+    l_one, l_still = e.label("onehead"), e.label("still")
+    for _ in range(3):
+        e.raw("s_nop 7")
+    e.raw(f"s_sub_u32 {sr(T_MT)}, {sr(S_NSTEPS)}, {sr(T_REM)}")
+    e.raw(f"s_cmp_eq_u32 {sr(S_NIN)}, 1")
+    e.raw(f"s_cbranch_scc1 {l_one}")
+    e.raw(f"s_mul_hi_u32 {sr(T_MT)}, {sr(T_MT)}, {sr(S_GREC)}")
+    e.raw(l_one + ":")
+    e.raw(f"s_lshl_b32 {sr(T_MT)}, {sr(T_MT)}, 5")
+    e.raw(f"s_sub_u32 {sr(S_CI)}, {sr(S_CI0)}, {sr(T_MT)}")
+    e.raw(f"s_sub_u32 {sr(T_MT)}, {sr(S_NSTEPS)}, {sr(S_NRAG)}")
+    e.raw(f"s_add_u32 {sr(T_MT)}, {sr(T_MT)}, 1")
+    e.raw(f"s_cmp_gt_u32 {sr(T_REM)}, {sr(T_MT)}")
+    e.raw(f"s_cselect_b32 {sr(S_EVT)}, -1, {sr(S_DIAG)}")
+    e.raw(f"s_cmp_lt_u32 {sr(T_DSTEP)}, {sr(S_NRAG)}")
+    e.raw(f"s_cbranch_scc1 {l_still}")
+    gen_whole_offsets(e, n4, T_MT)
+    e.raw(l_still + ":")
+    pblk_address(e, n4, T_MT)
+    for nb in range(NKB):
+        e.raw(f"ds_read_b32 {vr(low + nb)}, {vr(n4)} offset:{4 * nb}")
+    e.raw("s_waitcnt lgkmcnt(0)")
+    e.raw(f"v_mbcnt_lo_u32_b32 {vr(n4)}, -1, 0")
+    e.raw(f"v_mbcnt_hi_u32_b32 {vr(n4)}, -1, {vr(n4)}")
+    e.raw(f"v_lshrrev_b32 {vr(n4)}, 5, {vr(n4)}")
+    e.raw(f"v_lshlrev_b32 {vr(n4)}, 2, {vr(n4)}")
+    for nb in range(NKB):
+        e.raw(f"v_subrev_u32 {vr(low + nb)}, {sr(S_CI)}, {vr(low + nb)}")
+        e.raw(f"v_sub_u32 {vr(low + nb)}, {vr(low + nb)}, {vr(n4)}")
+
+    def each(cmp, bound):
+        for nb in range(NKB):
+            for v0 in range(0, 16, 3):
+                vs = range(v0, min(v0 + 3, 16))
+                for v in vs:
+                    e.raw(f"{cmp} {sr(T_CMP[v - v0], 2)}, {vr(bound(nb))}, {8 * (v // 4) + v % 4}")
+                if len(vs) < 3:
+                    e.raw("s_nop 1")
+                for v in vs:
+                    x = vr(S0 + 16 * nb + v)
+                    e.raw(f"v_cndmask_b32_e64 {x}, {vr(NINF)}, {x}, {sr(T_CMP[v - v0], 2)}")
+    each("v_cmp_le_i32_e64", lambda nb: low + nb)
+    l_ret = e.label("mret")
+    e.raw(f"s_add_u32 {sr(T_MT)}, {sr(S_CI)}, 32")
+    e.raw(f"s_cmp_le_u32 {sr(T_MT)}, {sr(S_SQ)}")
+    e.raw(f"s_cbranch_scc1 {l_ret}")
+    e.raw(f"s_sub_u32 {sr(T_MT)}, {sr(S_SQ)}, {sr(S_CI)}")
+    e.raw(f"v_sub_u32 {vr(high)}, {sr(T_MT)}, {vr(n4)}")
+    each("v_cmp_gt_i32_e64", lambda nb: high)
+    e.raw(l_ret + ":")
+    e.raw("s_nop 1")
+    e.raw(f"s_setpc_b64 {sr(T_MRET, 2)}")
+
+
+def gen_tail(e, buf):
+    """Behind the last block: the rest of the pair before the last one (dS in buffer `buf`), then the last one."""
+    pool = Pool()
+
+    def mfmas(ts, b, name):
+        ahead = 3
+        for i in range(min(ahead, len(ts))):
+            rd_dq(e, pool, f"{name}{ts[i]}_", ts[i], b)
+        for i, t in enumerate(ts):
+            if i + ahead < len(ts):
+                rd_dq(e, pool, f"{name}{ts[i + ahead]}_", ts[i + ahead], b)
+            mfma_dq(e, pool, f"{name}{t}_", t)
+
+    def finish():
+        for _ in range(4):
+            e.raw("s_nop 7")
+        e.raw("s_waitcnt vmcnt(0)")
+        for v in range(16):
+            e.raw(f"v_add_f32 {vr(OLD + v)}, {vr(OLD + v)}, {vr(ACC_Q + v)}")
+        for j in range(4):
+            sum_store(e, j)
+        for ln in next_pair():
+            e.raw(ln)
+
+    e.raw("s_waitcnt vmcnt(0) lgkmcnt(0)")             # every wavefront has written its dS of the last block
+    e.ds = []
+    flag_wait(e, 0)
+    for j in range(4):
+        old_load(e, j)
+    e.raw("s_barrier")
+    mfmas(list(range(N_A, 16)), buf, "a")
+    finish()
+    e.raw(f"s_add_u32 {sr(S_CNT)}, {sr(S_CNT)}, 1")
+    mfmas(list(range(16)), 1 - buf, "b")
+    flag_wait(e, None)
+    for j in range(4):
+        old_load(e, j)
+    finish()
+    e.raw("s_waitcnt vmcnt(0)")
+    flag_store(e)
+    e.raw("s_waitcnt vmcnt(0) lgkmcnt(0)")
+
+
+def generate():
+    e = OneEmitter()
+    pool = Pool()
+    l_mask = e.label("mask")
+    e.comment("---- prologue: stream state")
+    for t, s_ in ((T_QPTR, kv.S_QPTR), (T_QHEAD, kv.S_QPTR), (T_DOPTR, kv.S_DOPTR), (T_DOHEAD, kv.S_DOPTR),
+                  (T_LSEPTR, kv.S_LSEPTR), (T_LSEHEAD, kv.S_LSEPTR), (T_DLPTR, kv.S_DLPTR), (T_DLHEAD, kv.S_DLPTR),
+                  (T_VPTR, kv.S_VPTR)):
+        e.raw(f"s_mov_b64 {sr(t, 2)}, {sr(s_, 2)}")
+    for t in (T_DBLK, T_DSTEP):
+        e.raw(f"s_mov_b32 {sr(t)}, 0")
+    e.raw(f"s_mov_b32 {sr(T_REM)}, {sr(S_NSTEPS)}")
+    e.raw(f"s_mov_b32 {sr(S_CNT)}, -1")
+    e.raw(f"s_ashr_i32 {sr(T_OHI)}, {sr(S_QOUT)}, 31")
+    e.raw(f"s_mul_i32 {sr(T_M0)}, {sr(S_WAVE)}, {GRP}")
+    e.raw(f"s_add_u32 {sr(T_M0)}, {sr(T_M0)}, {sr(S_LDS)}")
+    e.raw(f"s_mov_b32 {sr(T_HIMASK)}, 0")
+    e.raw(f"s_mov_b32 {sr(T_HIMASK + 1)}, -1")
+    e.comment("---- resident V fragments (B operands): key row = lane % 32, elements 16 ks + 8 (lane / 32) .. + 7")
+    for nb, row in ((0, kv.I_KROW0), (1, kv.I_KROW1)):
+        for ks in range(KS):
+            e.raw(f"global_load_dwordx4 {vr(VF(nb, ks), 4)}, {vr(row, 2)}, off offset:{32 * ks}")
+    e.comment("---- parameters")
+    e.raw(f"s_add_u32 {sr(T_X)}, {sr(S_LDS)}, {PBLK + 256 * 32}")
+    e.raw(f"v_mov_b32 {vr(TMP)}, {sr(T_X)}")
+    e.raw(f"ds_read_b128 {vr(ST, 4)}, {vr(TMP)}")
+    e.raw(f"ds_read_b64 {vr(TMP, 2)}, {vr(TMP)} offset:16")
+    e.raw("s_waitcnt lgkmcnt(0)")
+    for src, dst in ((ST, S_NRAG), (ST + 1, S_DIAG), (ST + 2, S_GREC), (ST + 3, S_CI0), (TMP, S_SQ), (TMP + 1, S_ROWS)):
+        e.raw(f"v_readfirstlane_b32 {sr(dst)}, {vr(src)}")
+    e.raw(f"s_cmp_lg_u32 {sr(S_NRAG)}, -1")
+    e.raw(f"s_cselect_b32 {sr(S_EVT)}, -1, {sr(S_DIAG)}")
+    e.comment("---- K tile of the workgroup (256 rows) to LDS: instruction 4 j + wave fills group 4 j + wave of four rows")
+    for j in range(16):
+        e.raw(f"v_mul_lo_u32 {vr(TMP)}, {vr(kv.I_SROW)}, {sr(S_VRS)}")
+        e.raw(f"v_add_u32 {vr(TMP)}, {vr(TMP)}, {vr(kv.I_VCOL)}")
+        e.raw(f"s_add_u32 m0, {sr(T_M0)}, {KT + 4 * GRP * j}")
+        e.raw("s_nop 0")
+        e.raw(f"global_load_lds_dwordx4 {vr(TMP)}, {sr(T_VPTR, 2)}")
+        e.raw(f"v_add_u32 {vr(kv.I_SROW)}, 16, {vr(kv.I_SROW)}")
+    l_here = e.label("here")
+    e.raw(f"s_getpc_b64 {sr(T_MASK, 2)}")
+    e.raw(l_here + ":")
+    e.raw(f"s_add_u32 {sr(T_MASK)}, {sr(T_MASK)}, {l_mask}-{l_here}")
+    e.raw(f"s_addc_u32 {sr(T_MASK + 1)}, {sr(T_MASK + 1)}, 0")
+    e.comment("---- per-lane address registers")
+    for dst, src in ((QOFF, kv.I_QOFF0), (QOFF + 1, kv.I_QOFF1), (DOOFF, kv.I_DOOFF0), (DOOFF + 1, kv.I_DOOFF1), (STAT_G, kv.I_STAT_G),
+                     (STAT_L, kv.I_STAT_L)):
+        e.raw(f"v_mov_b32 {vr(dst)}, {vr(src)}")
+    e.raw(f"v_mov_b32 {vr(NINF)}, 0xff800000")
+    L4, LANE, R, G = FLG, TMP, TMP + 1, TMP + 2
+    e.raw(f"v_subrev_u32 {vr(L4)}, {sr(S_LDS)}, {vr(STAT_L)}")           # 4 * lane
+    e.raw(f"v_lshrrev_b32 {vr(LANE)}, 2, {vr(L4)}")
+    e.raw(f"v_lshrrev_b32 {vr(G)}, 5, {vr(LANE)}")                       # half of the wavefront
+    e.raw(f"v_and_b32 {vr(R)}, 31, {vr(LANE)}")
+    e.raw(f"v_lshlrev_b32 {vr(G16)}, 4, {vr(G)}")
+    e.raw(f"v_add_u32 {vr(G16)}, {sr(S_LDS)}, {vr(G16)}")
+    # dS, written: key 64 wave + lane % 32, 8 bytes per half
+    e.raw(f"s_lshl_b32 {sr(T_X)}, {sr(S_WAVE)}, 6")
+    e.raw(f"v_add_u32 {vr(DSW)}, {sr(T_X)}, {vr(R)}")
+    e.raw(f"v_mul_u32_u24 {vr(DSW)}, {DSR_ROW}, {vr(DSW)}")
+    e.raw(f"v_lshlrev_b32 {vr(DQO)}, 3, {vr(G)}")
+    e.raw(f"v_add_u32 {vr(DSW)}, {vr(DSW)}, {vr(DQO)}")
+    e.raw(f"s_add_u32 {sr(T_X)}, {sr(S_LDS)}, {DS0}")
+    e.raw(f"v_add_u32 {vr(DSW)}, {sr(T_X)}, {vr(DSW)}")
+    # dS, read transposed: key 4 g + (lane % 16) / 4, rows 16 ((lane / 16) % 2) + 4 (lane % 4) .. + 3
+    e.raw(f"v_and_b32 {vr(DSR)}, 15, {vr(LANE)}")
+    e.raw(f"v_lshrrev_b32 {vr(DSR)}, 2, {vr(DSR)}")
+    e.raw(f"v_lshlrev_b32 {vr(DQO)}, 2, {vr(G)}")
+    e.raw(f"v_add_u32 {vr(DSR)}, {vr(DSR)}, {vr(DQO)}")
+    e.raw(f"v_mul_u32_u24 {vr(DSR)}, {DSR_ROW}, {vr(DSR)}")
+    e.raw(f"v_bfe_u32 {vr(DQO)}, {vr(LANE)}, 4, 1")
+    e.raw(f"v_lshlrev_b32 {vr(DQO)}, 5, {vr(DQO)}")
+    e.raw(f"v_add_u32 {vr(DSR)}, {vr(DSR)}, {vr(DQO)}")
+    e.raw(f"v_and_b32 {vr(DQO)}, 3, {vr(LANE)}")
+    e.raw(f"v_lshlrev_b32 {vr(DQO)}, 3, {vr(DQO)}")
+    e.raw(f"v_add_u32 {vr(DSR)}, {vr(DSR)}, {vr(DQO)}")
+    e.raw(f"v_add_u32 {vr(DSR)}, {sr(T_X)}, {vr(DSR)}")
+    # workspace: 16 lane + SLICE wave
+    e.raw(f"s_mul_i32 {sr(T_X)}, {sr(S_WAVE)}, {SLICE}")
+    e.raw(f"v_lshlrev_b32 {vr(DQO)}, 2, {vr(L4)}")
+    e.raw(f"v_add_u32 {vr(DQO)}, {sr(T_X)}, {vr(DQO)}")
+    # natural reads: x[a] = xbase + (gf16 ^ 64 a), steps 2 a and 2 a + 1; K: the wavefront's 64 rows
+    e.raw(f"s_mul_i32 {sr(T_X)}, {sr(S_WAVE)}, {16 * GRP}")
+    e.raw(f"s_add_u32 {sr(T_X)}, {sr(T_X)}, {KT}")
+    for a in range(KS // 2):
+        e.raw(f"v_xor_b32 {vr(TMP)}, {64 * a}, {vr(kv.I_GF16)}")
+        e.raw(f"v_add_u32 {vr(X + a)}, {vr(kv.I_XBASE)}, {vr(TMP)}")
+        e.raw(f"v_add_u32 {vr(XK + a)}, {sr(T_X)}, {vr(X + a)}")
+    # transpose reads: tr[db] = trbase + (lf16 ^ 64 db); K^T: columns 32 wave .. + 31
+    for db in range(DB):
+        e.raw(f"v_xor_b32 {vr(TMP)}, {64 * db}, {vr(kv.I_LF16)}")
+        e.raw(f"v_add_u32 {vr(TR + db)}, {vr(kv.I_TRBASE)}, {vr(TMP)}")
+    e.raw(f"s_lshl_b32 {sr(T_X)}, {sr(S_WAVE)}, 6")
+    e.raw(f"v_xor_b32 {vr(TMP)}, {sr(T_X)}, {vr(kv.I_LF16)}")
+    e.raw(f"v_add_u32 {vr(KTR)}, {vr(kv.I_TRBASE)}, {vr(TMP)}")
+    e.raw(f"v_add_u32 {vr(KTR)}, {KT}, {vr(KTR)}")
+    e.comment("---- blocks 0 and 1 requested; accumulators to zero meanwhile")
+
+    for blk in range(2):
+        if blk:
+            l_still = e.label("still")
+            e.raw(f"s_cmp_lt_u32 {sr(T_DSTEP)}, {sr(S_NRAG)}")
+            e.raw(f"s_cbranch_scc1 {l_still}")
+            gen_whole_offsets(e, TMP, T_MT)
+            e.raw(l_still + ":")
+            flag_load(e)
+        for grp in request_code(blk, blk):
+            for ln in grp:
+                e.raw(ln)
+        for ln in kv.advance_code():
+            e.raw(ln)
+    flag_store(e)                                      # (as every block does: the waits count it)
+    for i in range(256):
+        e.raw(f"v_accvgpr_write_b32 {ar(i)}, 0")
+    e.comment("statistics of block 0 to LDS stage 0")
+    e.raw(f"s_waitcnt vmcnt({NREQ + 2})")
+    kv.stat_publish_to(e, STAT_L, 0, 0, "stw")
+    e.raw("s_waitcnt lgkmcnt(0)")
+    e.ds = []
+    e.raw("s_barrier")
+
+    plans = [plan_reads(e, pool, u % NS, u) for u in range(COPIES)] + [None]
+    # pair of block u - 2 (u = 0, 1: none) begins in copy u - 1 and ends in copy u
+    dq = [plan_dq(e, pool, u % 2, f"{u}x") for u in range(COPIES + 2)]          # dq[u]: the pair finished in copy u
+    merged = [{k: plans[0][k] + dq[0][1][0][k] for k in range(-EARLY, 0)}]
+    for k in range(-EARLY, 0):
+        for fn in merged[0][k]:
+            fn()
+    e.need("0nd3")
+    l_done = e.label("done")
+    l_tail = [e.label("tail0"), e.label("tail1")]
+    l_whole, l_masked = ([e.label(f"{x}{u}") for u in range(COPIES)] for x in ("whole", "masked"))
+    strip = lambda tags: [t.lstrip("0123456789") for t in tags]
+    entry, entry_pool = list(e.ds), (pool.next, dict(pool.owner), dict(pool.uses_left), dict(pool.reg))
+    at = [(strip(entry), pool.next % kv.NPOOL)]
+    e.raw(f"s_cmp_le_u32 {sr(T_REM)}, {sr(S_EVT)}")
+    e.raw(f"s_cbranch_scc1 {l_masked[0]}")
+    stubs = []
+    for masked in (False, True):
+        if masked:
+            e.ds = list(entry)
+            pool.next, pool.owner, pool.uses_left, pool.reg = entry_pool[0], dict(entry_pool[1]), dict(entry_pool[2]), dict(entry_pool[3])
+        for u in range(COPIES):
+            e.raw((l_masked if masked else l_whole)[u] + ":")
+            assert (strip(e.ds), pool.next % kv.NPOOL) == at[u], (e.ds, at[u])
+            if u == COPIES - 1:
+                plans[COPIES] = plan_reads(e, pool, 0, COPIES)
+            gen_step(e, pool, u, u, plans[u], plans[u + 1], dq[u][1], dq[u + 1][1], dq[u + 1][0], masked)
+            e.raw(f"s_sub_u32 {sr(T_REM)}, {sr(T_REM)}, 1")
+            # in this copy the pair of block u - 1 has begun, whose dS lies in buffer (u + 1) % 2
+            if masked:
+                e.raw(f"s_cmp_eq_u32 {sr(T_REM)}, 0")
+                e.raw(f"s_cbranch_scc1 {l_tail[(u + 1) % 2]}")
+                e.raw(f"s_cmp_gt_u32 {sr(T_REM)}, {sr(S_EVT)}")
+                e.raw(f"s_cbranch_scc1 {l_whole[(u + 1) % COPIES]}")
+            else:
+                l_leave = e.label("leave")
+                stubs.append((l_leave, l_masked[(u + 1) % COPIES], l_tail[(u + 1) % 2]))
+                e.raw(f"s_cmp_le_u32 {sr(T_REM)}, {sr(S_EVT)}")
+                e.raw(f"s_cbranch_scc1 {l_leave}")
+            if not masked and u < COPIES - 1:
+                at.append((strip(e.ds), pool.next % kv.NPOOL))
+        assert (strip(e.ds), pool.next % kv.NPOOL) == at[0], (e.ds, at[0])
+        e.raw(f"s_branch {(l_masked if masked else l_whole)[0]}")
+    for l_leave, l_to, l_end in stubs:
+        e.raw(l_leave + ":")
+        e.raw(f"s_cmp_lg_u32 {sr(T_REM)}, 0")
+        e.raw(f"s_cbranch_scc1 {l_to}")
+        e.raw(f"s_branch {l_end}")
+    e.raw(l_mask + ":")
+    gen_mask_routine(e)
+    for buf in range(2):
+        e.raw(l_tail[buf] + ":")
+        gen_tail(e, buf)
+        if buf == 0:
+            e.raw(f"s_branch {l_done}")
+    e.raw(l_done + ":")
+    e.comment("---- what the epilogue needs, from LDS")
+    e.raw(f"s_add_u32 {sr(T_X)}, {sr(S_LDS)}, {PBLK + 256 * 32}")
+    e.raw(f"v_mov_b32 {vr(TMP)}, {sr(T_X)}")
+    for i in range(3):
+        e.raw(f"ds_read_b128 {vr(160 + 4 * i, 4)}, {vr(TMP)} offset:{32 + 16 * i}")
+    e.raw("s_waitcnt lgkmcnt(0)")
+    for word, dst in ((U_DKPTR, kv.S_DKPTR), (U_DKPTR + 1, kv.S_DKPTR + 1), (U_DVPTR, kv.S_DVPTR), (U_DVPTR + 1, kv.S_DVPTR + 1),
+                      (U_RS32, kv.S_RS32), (U_SCALE, kv.S_SCALE), (U_FLAGS, S_FLAGS), (U_DKLP, kv.S_DKLP), (U_DKLP + 1, kv.S_DKLP + 1),
+                      (U_DVLP, kv.S_DVLP), (U_DVLP + 1, kv.S_DVLP + 1)):
+        e.raw(f"v_readfirstlane_b32 {sr(dst)}, {vr(160 + word - 8)}")
+    kv.epilogue(e, ragged_tiles=False)
+    return e
+
+
+def main():
+    e = generate()
+    clob = [f"v{i}" for i in range(256) if not (kv.IN_V <= i < kv.IN_V + 16)] + [f"a{i}" for i in range(256)]
+    clob += [f"s{i}" for i in range(64, 96)]
+    write_inc(sys.stdout, "gen_bwd_one_asm.py", "ST_ONE_FAST", e, LDS_BYTES, clob)
+
+
+if __name__ == "__main__":
+    main()

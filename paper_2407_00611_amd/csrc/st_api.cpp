@@ -31,9 +31,10 @@ thread_local char g_err[512] = "";
 // once per device with hipGetSymbolAddress (scratch_of_current_device); kernels only ever see that pointer.
 // Partial sums of under-filled launches have an array of their own, as large as a ring backward ever uses (kPartsMost): what a
 // call gets beside it must not depend on how much of the 40 MiB its Delta and Q' leave.
-constexpr size_t kScratchBytes = (size_t)40 << 20, kPartsMost = (size_t)64 << 20;
+constexpr size_t kScratchBytes = (size_t)40 << 20, kPartsMost = (size_t)64 << 20, kOneMost = (size_t)96 << 20;
+constexpr size_t kRoomMost = kOneMost;               // what a ring backward ever uses beside its Delta and Q'
 static __device__ __align__(256) unsigned char scratch[kScratchBytes];
-static __device__ __align__(256) unsigned char scratch_parts[kPartsMost];
+static __device__ __align__(256) unsigned char scratch_parts[kRoomMost];
 constexpr int kScratchDevices = 64;
 std::mutex g_scratch_mu;
 void* g_scratch_ptr[kScratchDevices][2];
@@ -362,6 +363,7 @@ struct BwdSplit {
   st::TileShares dq = {};
   int kv_each = 0, kv_items = 0;
   bool pair = false;
+  int one_heads = 0;
   size_t dq_bytes = 0, bytes = 0;
 };
 // dQ: the forward's model (the launch + the pass that adds up) with the constants of dq_cost.  fp32: the eight (four beyond head size 128) wavefronts of a workgroup take a
@@ -490,13 +492,69 @@ void f32_bwd_split(BwdSplit& r, const st::Shape& s, const QueryWalk& walk, const
     if (split_dq) each_split(walk, kMaxSplits, [&](const Split& q) { look(x, q); });
   }
 }
+// All three gradients in one walk over the key tiles (launch_bwd_one_fast), `batch` KV heads at a time on an XCD.  The XCD with the
+// most batches sets the time: its 32 workgroups take the tiles in order, and a tile starts two blocks behind the one before.
+// Measured (sums of a backward's launches, us; first the two passes, then one walk of batches of 1 / of all the heads of an XCD; last
+// ranks of rings of 8): 8 heads x 1024 rows 129, 143; x 2048 389, 344; x 4096 1346, 1123; 32 heads x 512 158, 144 / 127; x 1024 420, 373 / 348; x
+// 2048 1374, 1183 / 1178; 12 heads x 2048 582, 608; 24 heads x 2048 1072, 896; 8 x 4 heads x 1024 357, 343; x 2048 1300, 1134.  An XCD
+// without a head, or with one less than the others, idles: 4 x 4 heads x 2048 679, 1109.
+double one_walk_us(const st::Shape& s, const KeyWalk& keys, int batch) {
+  const int64_t rounds = (keys.heads / batch + 7) / 8;
+  const double busy = (double)std::min<int64_t>(keys.heads, 8) / 8 * std::min(1.0, (double)keys.seen * rounds * batch / 32);
+  const double step = 1.5 + 0.45 * busy, fixed = 20, unseen = 10;
+  const double around = 10 + (double)s.B * s.Hq * s.Sq * s.D * 12 / 5.5e6;      // the counts' start values, the pass that adds to dq
+  if (rounds * batch * keys.tiles > 512) {             // by the work alone
+    double us = 0;
+    for (int i = 0; i < keys.n; ++i) us += keys.c[i].tiles * (keys.c[i].blocks > 0 ? fixed + keys.c[i].blocks * keys.G * step : unseen);
+    return around + us * rounds * batch / 32 + 31.0 / batch * step;
+  }
+  double free[32] = {}, end = 0;
+  for (int64_t r = 0; r < rounds; ++r) {
+    double before[8] = {};
+    for (int i = 0; i < keys.n; ++i)                    // most blocks first, as the tiles lie
+      for (int t = 0; t < keys.c[i].tiles; ++t)
+        for (int h = 0; h < batch; ++h) {
+          double& at = *std::min_element(free, free + 32);
+          if (keys.c[i].blocks == 0) {
+            at += unseen;
+          } else {
+            const double start = std::max(at + fixed / 2, before[h]);
+            before[h] = start + step;
+            at = start + keys.c[i].blocks * keys.G * step + fixed / 2;
+          }
+          end = std::max(end, at);
+        }
+  }
+  return around + end;
+}
+// heads of a batch, 0: two passes
+int one_walk(const st::Shape& s, const KeyWalk& keys, const int64_t* k_offset, int n, size_t room, double less_us) {
+  if (s.D != 128 || s.Sk % st::kDkvFastKeys != 0 || keys.seen < 1) return 0;
+  if (st::knobs().one_walk != 1) less_us = st::knobs().one_walk ? 1e30 : 0;
+  if (s.causal && k_offset != nullptr)
+    for (int c = 1; c < n; ++c)                        // a tile sees the blocks of the ones behind it
+      if (k_offset[c] < k_offset[c - 1] + s.Sk - st::kDkvFastKeys) return 0;
+  int best = 0;
+  const int64_t per_xcd = (keys.heads + 7) / 8;
+  for (const int batch : {1, keys.heads % per_xcd == 0 && per_xcd <= 8 ? (int)per_xcd : 1}) {
+    if (batch == best || (size_t)st::OneRoom(s, n, batch).bytes > room) continue;
+    const double us = one_walk_us(s, keys, batch);
+    if (us >= less_us) continue;
+    less_us = us;
+    best = batch;
+  }
+  return best;
+}
 // Both passes in one launch: the compute units that have no key tile, or are done with theirs, take shares of the dQ pass
 // meanwhile, and the launch ends with the last of them (jobs_us, key tiles first).  Forward and backward, apart and together:
 // 4 heads x 700 rows x 4 chunks 99 and 77 us, 12 heads of 64 x 800 rows x 4 chunks 96 and 88 us, 6 heads x 1500 rows x 4
 // chunks 146 and 116 us.
 BwdSplit bwd_splits(const st::Shape& s, int dtype, const int64_t* k_offset, int n, size_t room, bool split_dq = true) {
+  const bool ring_call = split_dq;
   BwdSplit r;
   const bool bf16 = dtype == ST_BF16;
+  const size_t one_room = room;
+  room = std::min(room, kPartsMost);
   if ((bf16 && s.D != 128 && s.D != 64) || n < 1 || n > st::kMaxTable || s.B < 1 || s.Sq < 1 || s.Sk < 1 || s.Hq < 1 || s.Hkv < 1) return r;
   int64_t sorted[st::kMaxTable];                       // the plan does not depend on the order of the table
   if (s.causal && k_offset != nullptr) {
@@ -542,8 +600,27 @@ BwdSplit bwd_splits(const st::Shape& s, int dtype, const int64_t* k_offset, int 
   }
   KeyWalk keys;
   key_walk(keys, s, k_offset, n);
-  if (keys.seen < 1 || keys.heads * keys.seen >= 512 || keys.tiles > 32767) return r;
   const Cost kv_cost = dkv_cost(s.D);
+  // the one walk instead, if it is faster than the two passes: over 108 shares its model is right to 6 % on average, that of the passes
+  // says 0.87 of what they take (a walk of some hundred blocks on a full chip runs at the power limit)
+  auto or_one = [&](const BwdSplit& two, double us) {
+    const int heads = ring_call ? one_walk(s, keys, k_offset, n, one_room, 1.07 * us) : 0;
+    if (heads == 0) return two;
+    BwdSplit one;
+    one.one_heads = heads;
+    one.bytes = (size_t)st::OneRoom(s, n, heads).bytes;
+    return one;
+  };
+  if (keys.seen < 1 || keys.tiles > 32767) return r;
+  if (keys.heads * keys.seen >= 512) {
+    double us = 0;                                     // through the queue, and dQ in many workgroups: by the work alone
+    for (int i = 0; i < keys.n; ++i) us += keys.heads * keys.c[i].tiles * (keys.c[i].blocks > 0 ? kv_cost.us(keys.c[i].blocks * keys.G, kPlanCus) : 8) / kPlanCus;
+    if (!plan_dq) {
+      walk = query_walk(s, dtype, k_offset, n);
+      for (int i = 0; i < walk.n; ++i) dq_us += cost.us(walk.units[i], kPlanCus) * walk.heads * (walk.n == 1 ? walk.tiles : 1) / kPlanCus;
+    }
+    return or_one(r, us + dq_us);
+  }
   auto slot_bytes = [&](const KeySplit& x) { return (size_t)(keys.heads * x.slots * st::kv_slot_floats(s)) * sizeof(float); };
   // the adding pass reads the sums and reads and writes the gradients; only the keys a tile has are there, of the last tile of a
   // chunk often few.  What fits the L2 caches comes at some 16 TB/s, the rest at 5.
@@ -576,12 +653,13 @@ BwdSplit bwd_splits(const st::Shape& s, int dtype, const int64_t* k_offset, int 
     }
   }
   size_t dq_bytes = r.bytes;
+  double two_us = kv_us + 4 + dq_us;
   if (plan_dq && !st::dq_few(s, n)) {
     // Whole key tiles and the split that is best by itself first; any other one has to be better by 10 %, as the model does not know
     // that a share with the blocks of the diagonal takes longer (12/3 heads x 1408 rows: shares of 9 blocks a few per cent
     // better than of 4 in the model, 81 and 74 us).  Where the one that is best by itself fills the chip, few workgroups beside
     // dQ's may be far better: 2 x 8/4 heads x 1728 rows x 573 keys, three blocks 172 us and 224 in launches of their own.
-    double least = kv_us + 4 + dq_us, dq_work = 0, kv_work = 0;
+    double &least = two_us, dq_work = 0, kv_work = 0;
     for (int i = 0; i < walk.n; ++i) dq_work += (double)walk.heads * (walk.n == 1 ? walk.tiles : 1) * walk.units[i];
     for (int i = 0; i < keys.n; ++i) kv_work += (double)keys.heads * keys.G * keys.c[i].tiles * keys.c[i].blocks;
     const int by_itself = kv.each;
@@ -617,13 +695,14 @@ BwdSplit bwd_splits(const st::Shape& s, int dtype, const int64_t* k_offset, int 
   r.kv_items = (int)kv.items;
   r.dq_bytes = dq_bytes;                               // whole rows of 64 or 128 floats: kv_parts stays on its boundary
   r.bytes = r.pair ? dq_bytes + slot_bytes(kv) : std::max(dq_bytes, slot_bytes(kv));
-  return r;
+  return or_one(r, two_us);
 }
 void set_splits(st::BwdArgs& a, const BwdSplit& x, void* parts) {
   a.shares = x.dq;
   a.kv_each = x.kv_each;
   a.kv_items = x.kv_items;
   a.pair = x.pair;
+  a.one_heads = x.one_heads;
   a.parts = (float*)parts;
   a.kv_parts = (float*)((char*)parts + (x.pair ? x.dq_bytes : 0));
 }
@@ -1059,7 +1138,7 @@ static size_t bwd_base_bytes(const st_ring_desc* d) {
 // What a workspace has beyond the rest, for the partial sums of a ring backward
 static size_t ring_room(const st_ring_desc* d, size_t workspace_bytes) {
   const size_t base = bwd_base_bytes(d);
-  return workspace_bytes > base ? std::min(workspace_bytes - base, kPartsMost) : 0;
+  return workspace_bytes > base ? std::min(workspace_bytes - base, kRoomMost) : 0;
 }
 
 // Partial sums to provide for.  Under a causal mask the plan depends on where the chunks lie: as a caller visits them who lists
@@ -1070,7 +1149,7 @@ static size_t ring_parts_bytes(const st_ring_desc* d, int mode) {
   const bool fused = mode == ST_RING_FUSED;
   const int n_chunks = std::min(d->n_chunks, ST_MAX_CHUNKS), per_launch = std::min(n_chunks, fused ? st::kMaxTable : 1);
   size_t most = 0;
-  auto look = [&](const int64_t* k_offset, int n) { most = std::max(most, bwd_splits(s, d->dtype, k_offset, n, kPartsMost).bytes); };
+  auto look = [&](const int64_t* k_offset, int n) { most = std::max(most, bwd_splits(s, d->dtype, k_offset, n, kRoomMost).bytes); };
   if (!d->causal || d->k_offset == nullptr) {
     for (int n = 1; n <= per_launch; ++n) look(nullptr, n);
     return most;
@@ -1117,7 +1196,7 @@ struct RingVisit {
 // st_ring_bwd with that much and st_ring_bwd_noalloc compute the same sums; with less it is the best one that fits.
 static BwdSplit ring_plan(const st_ring_desc* d, int mode, const int64_t* k_offset, int n, bool provided, size_t room) {
   const st::Shape s = shape_of(d);
-  BwdSplit r = bwd_splits(s, d->dtype, k_offset, n, kPartsMost);
+  BwdSplit r = bwd_splits(s, d->dtype, k_offset, n, kRoomMost);
   if (!provided && r.bytes > 0) room = std::min(room, ring_parts_bytes(d, mode));
   return r.bytes <= room ? r : bwd_splits(s, d->dtype, k_offset, n, room);
 }
@@ -1297,7 +1376,7 @@ st_status st_ring_bwd_noalloc(const st_ring_desc* d, const st_tensor* q, const s
   void *ws = nullptr, *parts = nullptr;
   ST_TRY(scratch_of_current_device(&ws, &parts));
   return ring_bwd(d, q, d_o, o, o_dtype, lse_final, order, n_visit, mode, dq_acc, dk_acc, dv_acc, 0, nullptr, nullptr, ws, kScratchBytes,
-                  parts, kPartsMost, hip_stream);
+                  parts, kRoomMost, hip_stream);
 }
 
 size_t st_ring_bwd_noalloc_max_bytes(void) { return kScratchBytes; }
@@ -1388,16 +1467,9 @@ static st_status ring_bwd(const st_ring_desc* d, const st_tensor* q, const st_te
   set_table_strides(a.t, d);
   a.lse = lse_final; a.delta = delta; a.dq = dq_acc;
   a.queue = (int32_t*)((char*)workspace + align_up((size_t)d->B * d->Sq * d->Hq * sizeof(float), 256));
-  if (d->dtype == ST_BF16) {
-    void* qs = (char*)a.queue + align_up(st::kQueueInts * sizeof(int32_t), 256);
-    ST_HIP(st::launch_bwd_prep(a.d_o, view_of(o), o_dtype, a.q, delta, qs, a.queue, d->B, d->Sq, d->Hq, d->D, d->scale, stream), "backward preparation launch");
-    a.qs = qs;
-  } else {
-    ST_HIP(st::launch_delta(a.d_o, d->dtype, view_of(o), o_dtype, delta, d->B, d->Sq, d->Hq, d->D, stream), "delta launch");
-  }
   const int per_launch = mode == ST_RING_FUSED ? st::kMaxTable : 1;
   const bool provided = vis.provided(d, mode);
-  for (int x0 = 0; x0 < vis.n; x0 += per_launch) {
+  for (int x0 = 0; x0 == 0 || x0 < vis.n; x0 += per_launch) {
     const int cnt = std::min(vis.n - x0, per_launch);
     a.t.n = cnt;
     a.queue_clean = d->dtype == ST_BF16 && x0 == 0;
@@ -1408,7 +1480,18 @@ static st_status ring_bwd(const st_ring_desc* d, const st_tensor* q, const st_te
       a.dk_lowp[x] = dk_lowp ? dk_lowp[j] : nullptr;
       a.dv_lowp[x] = dk_lowp ? dv_lowp[j] : nullptr;
     }
-    set_splits(a, ring_plan(d, mode, a.t.k_offset, cnt, provided, parts_bytes), parts);
+    if (cnt > 0) set_splits(a, ring_plan(d, mode, a.t.k_offset, cnt, provided, parts_bytes), parts);
+    if (x0 == 0) {
+      if (d->dtype == ST_BF16) {
+        void* qs = (char*)a.queue + align_up(st::kQueueInts * sizeof(int32_t), 256);
+        const st::OneReset reset = a.one_heads > 0 ? st::one_reset(a.parts, a.s, cnt, a.one_heads) : st::OneReset();
+        ST_HIP(st::launch_bwd_prep(a.d_o, view_of(o), o_dtype, a.q, delta, qs, a.queue, reset, d->B, d->Sq, d->Hq, d->D, d->scale, stream), "backward preparation launch");
+        a.qs = qs;
+      } else {
+        ST_HIP(st::launch_delta(a.d_o, d->dtype, view_of(o), o_dtype, delta, d->B, d->Sq, d->Hq, d->D, stream), "delta launch");
+      }
+      if (cnt <= 0) break;
+    }
     a.kv_assign = assign ? ~0ull : 0ull;
     if (d->dtype != ST_BF16 && assign)              // the fp32 kernels only add
       for (int x = 0; x < cnt; ++x) {
@@ -1427,7 +1510,7 @@ extern "C" int st_testing_bwd_plan(const st_ring_desc* d, const int32_t* order, 
   for (int x = 0; x < n_visit; ++x)
     if (!chunk_invisible(d, order[x]) || (assign && mode == ST_RING_FUSED && d->dtype == ST_BF16)) vis.add(d, order[x]);
   const size_t base = mode < 0 ? align_up((size_t)d->B * d->Sq * d->Hq * d->D * 2, 256) : bwd_base_bytes(d);
-  const size_t room = workspace_bytes < 0 ? kPartsMost : (size_t)workspace_bytes > base ? std::min((size_t)workspace_bytes - base, kPartsMost) : 0;
+  const size_t room = workspace_bytes < 0 ? kRoomMost : (size_t)workspace_bytes > base ? std::min((size_t)workspace_bytes - base, kRoomMost) : 0;
   const int per_launch = mode == ST_RING_FUSED ? st::kMaxTable : 1;
   int written = 0;
   for (int x0 = 0; x0 < vis.n; x0 += per_launch) {
@@ -1436,7 +1519,7 @@ extern "C" int st_testing_bwd_plan(const st_ring_desc* d, const int32_t* order, 
     for (int x = 0; x < cnt; ++x) k_offset[x] = d->k_offset[vis.chunk[x0 + x]];
     const BwdSplit p = mode < 0 ? block_plan(shape_of(d), d->dtype, k_offset[0], room) : ring_plan(d, mode, k_offset, cnt, vis.provided(d, mode), room);
     const int64_t v[] = {cnt, p.dq.n, p.dq.total, p.dq.own0, (int64_t)p.dq.less1[0], (int64_t)p.dq.less1[1], (int64_t)p.dq.less1[2],
-                         (int64_t)p.dq.less1[3], p.kv_each, p.kv_items, p.pair, (int64_t)p.bytes};
+                         (int64_t)p.dq.less1[3], p.kv_each, p.one_heads > 0 ? -p.one_heads : p.kv_items, p.pair, (int64_t)p.bytes};
     for (int64_t y : v) {
       if (written >= max_out) return -1;
       out[written++] = y;

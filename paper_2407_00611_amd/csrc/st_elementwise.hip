@@ -261,10 +261,16 @@ __global__ __launch_bounds__(256) void delta_kernel(View d_o, View o, float* __r
 // ---- backward preparation of a bf16 share in one pass: Delta, Q' = bf16(Q c), the tile counters of the dK/dV launch to zero.
 // Lanes per row = D / 8, one 16-byte vector of each of dO, O (two of an fp32 O), Q per thread.  Bytes only; as three
 // launches these were 4.5 (counters), 10 and 9 us for 2048 rows of 32 heads of 128, each with a gap to the next.
+__device__ __forceinline__ void do_reset(const OneReset& r) {
+  for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < r.n; i += (int64_t)gridDim.x * 256) r.zero[i] = make_uint4(i == r.plenty ? 0x7fffffffu : 0u, 0u, 0u, 0u);
+}
+__global__ __launch_bounds__(256) void one_reset_kernel(OneReset r) { do_reset(r); }
+
 template <bool kOBf16, int LPR>
 __global__ __launch_bounds__(256) void bwd_prep_kernel(View d_o, View o, View q, float* __restrict__ delta, u32x4* __restrict__ qs,
-                                                       int32_t* __restrict__ queue, int32_t B, int32_t Sq, int32_t Hq, float c) {
+                                                       int32_t* __restrict__ queue, OneReset reset, int32_t B, int32_t Sq, int32_t Hq, float c) {
   if (blockIdx.x == 0 && threadIdx.x < kQueueInts) queue[threadIdx.x] = 0;
+  do_reset(reset);
   const int64_t v = (int64_t)blockIdx.x * 256 + threadIdx.x;
   const int64_t row = v / LPR;
   const int d = (int)(v % LPR) * 8;
@@ -571,15 +577,25 @@ hipError_t launch_delta(const View& d_o, int d_o_dtype, const View& o, int o_dty
   return hipGetLastError();
 }
 
+OneReset one_reset(void* room, const Shape& s, int n_chunks, int heads) {
+  const OneRoom r(s, n_chunks, heads);
+  return OneReset{(uint4*)room, (int32_t)(r.pairs / 16), (int32_t)(r.plenty / 16)};
+}
+hipError_t launch_one_reset(const OneReset& r, hipStream_t s) {
+  ProfScope prof("one_reset", s);
+  hipLaunchKernelGGL(one_reset_kernel, dim3((unsigned)((r.n + 255) / 256)), dim3(256), 0, s, r);
+  return hipGetLastError();
+}
+
 hipError_t launch_bwd_prep(const View& d_o, const View& o, int o_dtype, const View& q, float* delta, void* qs, int32_t* queue,
-                           int32_t B, int32_t Sq, int32_t Hq, int32_t D, float scale, hipStream_t s) {
+                           const OneReset& reset, int32_t B, int32_t Sq, int32_t Hq, int32_t D, float scale, hipStream_t s) {
   const int64_t n_vec = (int64_t)B * Sq * Hq * (D / 8);
   if (n_vec == 0) return hipSuccess;
   const dim3 grid(blocks_for(n_vec)), block(256);
   const float c = scale * 1.4426950408889634f;
   ProfScope prof("bwd_prep", s);
 #define ST_LAUNCH_PREP(OB, LPR) \
-  hipLaunchKernelGGL((bwd_prep_kernel<OB, LPR>), grid, block, 0, s, d_o, o, q, delta, (u32x4*)qs, queue, B, Sq, Hq, c)
+  hipLaunchKernelGGL((bwd_prep_kernel<OB, LPR>), grid, block, 0, s, d_o, o, q, delta, (u32x4*)qs, queue, reset, B, Sq, Hq, c)
   if (D == 128) {
     if (o_dtype == ST_BF16) ST_LAUNCH_PREP(true, 16);
     else ST_LAUNCH_PREP(false, 16);

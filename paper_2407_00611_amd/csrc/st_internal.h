@@ -171,6 +171,7 @@ struct BwdArgs {
   KvSection kv_sec[kKvSections];
   int32_t kv_same;     // shares of every tile where all have the same number (then nothing is looked up), else 0; set by the launcher
   int32_t pair;        // 1: both passes in one launch, where the hand-scheduled kernels take both
+  int32_t one_heads;   // > 0: all gradients in one walk (see OneRoom), batches of so many KV heads; parts is its room
   float *parts, *kv_parts;   // of launches that run one after the other they may be the same memory
   // dK / dV work of a chunk's last visit folded into the launch (bf16 path): the hand-scheduled kernel's epilogue does it,
   // beside the general kernel the launcher runs fill and cast launches
@@ -179,7 +180,7 @@ struct BwdArgs {
   void* dv_lowp[kMaxTable];
   int32_t* queue;      // nullable, kQueueInts ints of device memory: the fast dK/dV kernel hands its key tiles out
                        // through it (one counter per XCD), so that XCDs that run faster take more of them
-  int16_t queue_clean; // 1: the counters are zero already (the first launch behind launch_bwd_prep)
+  int16_t queue_clean; // 1: the counters are zero already, and the room of a walk of one is reset (the first launch behind launch_bwd_prep)
   int16_t queue_xcds;  // counters in use (the device's XCD count, 1 .. 8); set by the launcher
 };
 // Partial sum y of query tile qt of batch entry b: [row, head, element] floats from here on.  The sums of a batch entry lie one
@@ -208,6 +209,26 @@ __host__ __device__ inline float* f32_kv_part(float* parts, const Shape& s, int 
 // bf16: a slot of a key tile's sums, dk behind dv (not a multiple of a large power of two: workgroups in step would write to the
 // same memory channels)
 __host__ __device__ inline int64_t kv_slot_floats(const Shape& s) { return (int64_t)2 * kDkvFastKeys * s.D + 17 * 64; }
+// Room of a backward in one walk (gen_bwd_one_asm.py), byte offsets: what hands out the tiles (tickets of 16 XCDs and the next batch, 128
+// bytes apart, claims), a count that is never too low, the tiles' counts (one per wavefront), a pair of zeros, and the pairs of each
+// (KV head, batch entry) in the order of the walk behind two that do not exist.
+constexpr int kOnePairBytes = 16384;
+struct OneRoom {
+  int64_t plenty, claims, counts, zeros, pairs, group_bytes, bytes;
+  int32_t claims_each, tiles;
+  __host__ __device__ OneRoom(const Shape& s, int n_chunks, int heads) {
+    const int64_t groups = (int64_t)s.B * s.Hkv, blocks = (s.Sq + 31) / 32;
+    tiles = (s.Sk + kDkvFastKeys - 1) / kDkvFastKeys * n_chunks;
+    plenty = 17 * 128;
+    claims = 18 * 128;
+    claims_each = (int32_t)((groups / heads + 256 + 31) / 32 * 32);      // (a workgroup that finds no batch left has taken a ticket too)
+    counts = claims + (int64_t)16 * claims_each * 4;
+    zeros = counts + (groups * tiles * 4 * 4 + 255) / 256 * 256;
+    pairs = zeros + kOnePairBytes;
+    group_bytes = (s.Hq / s.Hkv * blocks + 2) * kOnePairBytes;
+    bytes = pairs + groups * group_bytes;
+  }
+};
 constexpr int kQueueInts = 8 * 32;   // at most 8 counters, 128 bytes apart
 // passed by value: a kernel takes 4096 bytes of arguments
 static_assert(sizeof(BwdArgs) <= 4096 - 64 && sizeof(FwdArgs) <= 4096 - 64, "argument structs must fit the kernel arguments");
@@ -229,7 +250,7 @@ struct CombineArgs {
 };
 
 // Tuning and testing switches of the launchers.  The defaults are the product.  They are read from the
-// environment ONCE, when the library is loaded (ST_FWD_FAST, ST_DQ_FAST, ST_DKV_FAST, ST_DKV_QUEUE, ST_FWD_WQ,
+// environment ONCE, when the library is loaded (ST_FWD_FAST, ST_DQ_FAST, ST_DKV_FAST, ST_DKV_QUEUE, ST_ONE_WALK, ST_FWD_WQ,
 // ST_FWD_PIPE, ST_FWD_GAP); afterwards only st_testing_set() changes them, an exported entry point for the
 // library's own tests that the public header does not declare.  No launcher reads the environment.
 struct Knobs {
@@ -237,6 +258,7 @@ struct Knobs {
   int dq_fast = 1;     // 0: the dQ pass stays in the general kernel
   int dkv_fast = 1;    // 0: the dK/dV pass stays in the general kernel
   int dkv_queue = 1;   // 0: every dK/dV key tile is a workgroup of its own (no tile queue)
+  int one_walk = 1;    // ring backward, all gradients in one walk: 0 never, 1 where it is the faster plan, 2 wherever the kernel takes it
   int fwd_wq = 32;     // general forward without the fast path: queries per wavefront (32 or 64)
   int fwd_pipe = 1;    // general forward without the fast path, head size 128: the pipelined variant
   float fwd_gap = 8.f; // fast forward: log2 units every block maximum may exceed the lazy exponent reference by (0 .. 64)
@@ -282,6 +304,7 @@ bool dkv_fast_usable(const BwdArgs& a);
 void kv_sections(BwdArgs& a);    // sets kv_items and kv_sec from the table and kv_each
 hipError_t launch_bwd_dkv_fast(const BwdArgs& a, hipStream_t s);
 hipError_t launch_bwd_pair_fast(const BwdArgs& a, hipStream_t s);   // both
+hipError_t launch_bwd_one_fast(const BwdArgs& a, hipStream_t s);    // all three gradients in one walk
 bool dq_fast_usable(const BwdArgs& a);
 hipError_t launch_bwd_dq_fast(const BwdArgs& a, hipStream_t s);
 
@@ -291,9 +314,18 @@ hipError_t launch_merge(float* o_acc, float* lse_acc, const float* o_part, const
 hipError_t launch_combine(const CombineArgs& a, int lowp_dtype, hipStream_t s);
 hipError_t launch_delta(const View& d_o, int d_o_dtype, const View& o, int o_dtype, float* delta,
                         int32_t B, int32_t Sq, int32_t Hq, int32_t D, hipStream_t s);
-// bf16 backward, head size 64 or 128: delta = rowsum(dO o O), qs as launch_scale_q, queue (kQueueInts ints) to zero
+// What a walk of one finds in its room when it starts (OneRoom): zeros up to the pairs, and the count that is never too low
+struct OneReset {
+  uint4* zero = nullptr;
+  int32_t n = 0;             // 16-byte units
+  int32_t plenty = 0;        // the unit whose first word is that count
+};
+OneReset one_reset(void* room, const Shape& s, int n_chunks, int heads);
+hipError_t launch_one_reset(const OneReset& r, hipStream_t s);
+bool one_fast_usable(const BwdArgs& a);
+// bf16 backward, head size 64 or 128: delta = rowsum(dO o O), qs as launch_scale_q, queue (kQueueInts ints) to zero, reset done
 hipError_t launch_bwd_prep(const View& d_o, const View& o, int o_dtype, const View& q, float* delta, void* qs, int32_t* queue,
-                           int32_t B, int32_t Sq, int32_t Hq, int32_t D, float scale, hipStream_t s);
+                           const OneReset& reset, int32_t B, int32_t Sq, int32_t Hq, int32_t D, float scale, hipStream_t s);
 hipError_t launch_cast(const float* src, void* dst, int64_t n, int dst_dtype, hipStream_t s);
 // dst (dense bf16 [B,Sq,Hq,D]) = bf16(q * scale * log2 e) of a bf16 view q
 hipError_t launch_scale_q(const View& q, void* dst, int32_t B, int32_t Sq, int32_t Hq, int32_t D, float scale, hipStream_t s);

@@ -25,6 +25,7 @@ Knobs knobs_from_env() {
   k.dq_fast = env_int("ST_DQ_FAST", k.dq_fast);
   k.dkv_fast = env_int("ST_DKV_FAST", k.dkv_fast);
   k.dkv_queue = env_int("ST_DKV_QUEUE", k.dkv_queue);
+  k.one_walk = env_int("ST_ONE_WALK", k.one_walk);
   k.fwd_wq = env_int("ST_FWD_WQ", k.fwd_wq);
   k.fwd_pipe = env_int("ST_FWD_PIPE", k.fwd_pipe);
   if (const char* e = getenv("ST_FWD_GAP")) {
@@ -106,6 +107,7 @@ extern "C" int st_testing_set(const char* name, double value) {
   else if (!strcmp(name, "dq_fast")) k.dq_fast = v;
   else if (!strcmp(name, "dkv_fast")) k.dkv_fast = v;
   else if (!strcmp(name, "dkv_queue")) k.dkv_queue = v;
+  else if (!strcmp(name, "one_walk")) k.one_walk = v;
   else if (!strcmp(name, "fwd_wq") && (v == 32 || v == 64)) k.fwd_wq = v;
   else if (!strcmp(name, "fwd_pipe")) k.fwd_pipe = v;
   else if (!strcmp(name, "fwd_gap") && value >= 0.0 && value <= 64.0) k.fwd_gap = (float)value;
