@@ -23,7 +23,7 @@ SOURCES = ["st_api.cpp", "st_runtime.cpp", "st_f32.hip", "st_elementwise.hip", "
 GENERATED = [("gen_bwd_dkv_asm.py", "st_bwd_dkv_asm.inc"), ("gen_bwd_dq_asm.py", "st_bwd_dq_asm.inc"),
              ("gen_fwd_asm.py", "st_fwd_asm.inc"), ("gen_fwd_asm.py 64", "st_fwd64_asm.inc"),
              ("gen_bwd_dq_asm.py 64", "st_bwd_dq64_asm.inc"), ("gen_bwd_dkv_asm.py 64", "st_bwd_dkv64_asm.inc"),
-             ("gen_bwd_one_asm.py", "st_bwd_one_asm.inc"),
+             ("gen_bwd_one_asm.py", "st_bwd_one_asm.inc"), ("gen_bwd_one_asm.py 64", "st_bwd_one64_asm.inc"),
              ("gen_probe_asm.py", "st_probe_asm.inc")]
 
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")

@@ -1,13 +1,14 @@
 #!/usr/bin/env python3
-"""Generates the gfx950 assembly of the loop that makes dK, dV and dQ in one walk (head_dim 128) as a C string literal.
+"""Generates the gfx950 assembly of the loop that makes dK, dV and dQ in one walk (head_dim 128, or 64) as a C string literal.
 
     python gen_bwd_one_asm.py > st_bwd_one_asm.inc          (build.py does this before compiling)
+    python gen_bwd_one_asm.py 64 > st_bwd_one64_asm.inc     (head_dim 64)
 
 The walk, the masks, the statistics and the epilogue are those of gen_bwd_dkv_asm.py; what is said there holds here.  Five contractions
 a pair in place of the seven that the loop there and the one of gen_bwd_dq_asm.py execute: S and dP are not made again for dQ.
 
-  * The packed dS of a block goes to LDS as [key][row] (two buffers; rows padded to 72 bytes, so that the 8-byte writes and the
-    transposing reads meet few bank conflicts).  From the barrier of the next block on, wavefront w contracts all 256 keys of it with
+  * Head size 128: the packed dS of a block goes to LDS as [key][row] (two buffers; rows padded to 72 bytes, so that the 8-byte writes
+    and the transposing reads meet few bank conflicts).  From the barrier of the next block on, wavefront w contracts all 256 keys of it with
     columns 32 w .. 32 w + 31 of K: dQ^T[32 x 32] += K^T dS^T, sixteen MFMAs spread to the barrier after that.  K lies in LDS for
     this, as the tile that S reads; V is resident instead.
   * dQ of a (head, block) pair, 16 KiB, travels from key tile to key tile of its KV head through a workspace in the order of the walk
@@ -30,6 +31,16 @@ block and wavefront) takes 2085 ns on random data, those of the two loops 1547 +
 20.0 -> 16.8 ms, 32 heads x 2048 rows x 16 chunks 2.75 -> 2.39 (64 blocks a tile: 25 us of its 150 are before and behind the loop).
 Where the MFMAs of a pair lie in the block, how far ahead their operands are read and how much side work a slot gets moved that by less than
 1 % each; half of them under the first phase, whose reads are the densest, cost 3 %.
+
+Head size 64 differs where half as many MFMAs leave less time to hide the rest in, and half as many registers are taken:
+  * K is resident too, as the fragments of S and, in accumulator registers, as those of K^T; so are the fragments of dS^T.  Four stages
+    of tiles, three blocks ahead.
+  * A wavefront makes 16 columns of dQ from all keys (MFMAs of 16 x 16 x 32), so that a pair is 8 KiB.  With 32 columns from half the
+    keys it reads half as much of dS, but the exchange is of two halves: 30.6 instead of 33.3 ms below; without any exchange 27.5.
+  * What the tile before left is loaded into the accumulators themselves, a block ahead, and nothing is added up.  Two sets of sums.
+  * All MFMAs of a pair behind the barrier, two a slot, every second slot (three slots apart 30.9 ms, in one block of eight slots 29.9);
+    eleven units of side work a slot (nine and ten 2 to 3 % slower).
+Backward of 24 heads x 16384 rows x 8 chunks, no mask: 34.6 -> 29.6 ms.
 """
 import os
 import sys
@@ -37,55 +48,88 @@ import sys
 import gen_bwd_dkv_asm as kv
 from gen_bwd_dkv_asm import (ACC_K, ACC_V, DB, DP0, KS, ND, NDQ, NINF, NKB, NL, NSLOT, P16, P2, P3, P4, POOL0, S0, ST, TMP,
                              S_CI, S_CI0, S_DIAG, S_EVT, S_FLAGS, S_GREC, S_LDS, S_NIN, S_NRAG, S_NSTEPS, S_QOUT, S_ROWS, S_SQ, S_VRS, S_WAVE, T_CMP,
-                             T_DBLK, T_DLHEAD, T_DLPTR, T_DOHEAD, T_DOPTR, T_DSTEP, T_HIMASK, T_LSEHEAD, T_LSEPTR, T_M0, T_MASK, T_MRET, T_MT,
+                             T_DBLK, T_DLHEAD, T_INC, T_DLPTR, T_DOHEAD, T_DOPTR, T_DSTEP, T_HIMASK, T_LSEHEAD, T_LSEPTR, T_M0, T_MASK, T_MRET, T_MT,
                              T_OHI, T_QHEAD, T_QPTR, T_REM, T_VPTR, T_X)
 from st_asmgen import Emitter, ar, sr, vr, write_inc
 
-assert kv.D == 128
-NS, PF, COPIES = 3, 2, 6
-GRP = 1024 + 16                                      # bytes from one group of four rows to the next
-TQ = 8 * GRP                                         # a 32-row tile
+D = kv.D
+NS, PF, COPIES = (3, 2, 6) if D == 128 else (4, 3, 4)
+GRP = 1024 + 16                                      # bytes from one group of rows (four, or eight of head size 64) to the next
+def rows(n): return n * 2 * D // 1024 * GRP          # bytes of n rows, whole groups
+TQ = rows(32)
 def QT(s): return 1024 + 2 * TQ * s
 def DOT(s): return 1024 + 2 * TQ * s + TQ
-KT = 1024 + 2 * TQ * NS                              # K tile: 256 rows
+TILES = 1024 + 2 * TQ * NS
 DSR_ROW = 72                                         # bytes of a key's 32 dS
 DS_BYTES = 256 * DSR_ROW
-DS0 = KT + 64 * GRP
+KT = TILES                                           # K tile; head size 64 has it in fragments, and only at the start in the place of dS
+DS0 = KT + (rows(256) if D == 128 else 0)
+assert D == 128 or rows(256) <= 2 * DS_BYTES
 PBLK = DS0 + 2 * DS_BYTES                            # as in gen_bwd_dkv_asm.py; it stays, the mask routine reads it
 NUNI = 20                                            # words of the uniform block behind it
 LDS_BYTES = PBLK + 256 * 32 + 4 * NUNI
-assert LDS_BYTES <= 163840 and PBLK >= 4 * 2 * 32 * (4 * 128 + 16)
+assert LDS_BYTES <= 163840 and PBLK >= 4 * 2 * 32 * (4 * D + 16)
 # words of the uniform block behind the six of gen_bwd_dkv_asm.py: what only the epilogue needs
 U_DKPTR, U_DVPTR, U_RS32, U_SCALE, U_FLAGS, U_DKLP, U_DVLP = 8, 10, 12, 13, 14, 16, 18
-SLICE = 4096                                         # a wavefront's part of a pair in the workspace
+NP = D // 32                                         # accesses of 1 KiB that a wavefront's part of a pair takes
+SLICE = 1024 * NP                                    # the part in the workspace
 PAIR = 4 * SLICE
 
 # registers
 VF = kv.KF                                           # resident V fragments
+def KR(nb, ks): return 32 + VF(nb, ks)               # head size 64: resident K fragments of S
+def KTF(t): return 64 + 4 * t                        # and of K^T, in accumulator registers that dK and dV leave
+def DSF(t): return 192 + 4 * (t % 8)                 # of dS^T
+def ACC64(x): return 96 + 4 * NP * (x % 2)           # as the sums of a pair are
 X, XK, TR, KTR, DSW, DSR, DQO, FLG = 216, 220, 224, 228, 229, 230, 231, 232
 QOFF, DOOFF, STAT_G, STAT_L, G16, ACC_Q = 233, 235, 237, 238, 239, 240
 OLD = NL                                             # what the tile before left, from slot 3 to the stores
+MASK_HIGH = FLG if D == 128 else XK                  # a register that is free when the masks are made
 # scalars in the places of the epilogue's inputs
 S_DQL, S_DQW, S_DQINC, S_CNT, S_PRED, S_OWN = 52, 54, 57, 59, 60, 62
 SPINS = int(os.environ.get("ST_GEN_ONE_SPINS", 1 << 21))     # most polls of a wait: seconds; then it goes on, so that every launch ends
 
 LAT = int(os.environ.get("ST_GEN_ONE_LAT", 3))
 LATQ = int(os.environ.get("ST_GEN_ONE_LATQ", 3))
-BUDGET = int(os.environ.get("ST_GEN_ONE_BUDGET", 6))
+BUDGET = int(os.environ.get("ST_GEN_ONE_BUDGET", 6 if D == 128 else 11))
 BUDGET_Q = int(os.environ.get("ST_GEN_ONE_BUDGETQ", 4))
 EARLY = 12
 SYNC_SLOT, PUBLISH_SLOT = P3 - 1, P3 - 6
 # slots behind which the MFMAs of a pair are issued, from the barrier of one block (slot 32 on) to that of the next (64 + 26)
-DQ_AT = [int(x) for x in os.environ.get("ST_GEN_ONE_AT", "35,37,39,41,43,45,47,49,52,55,58,61,80,82,84,86").split(",")]
-assert len(DQ_AT) == 16 and DQ_AT == sorted(DQ_AT) and DQ_AT[0] - LATQ > SYNC_SLOT and DQ_AT[-1] <= NSLOT + P3 - 6
+DQ_AT = [int(x) for x in os.environ.get("ST_GEN_ONE_AT", "35,37,39,41,43,45,47,49,52,55,58,61,80,82,84,86" if D == 128 else
+                                        "19,19,21,21,23,23,25,25,27,27,29,29,31,31,33,33").split(",")]
+N_DQ = 16                                            # head size 64: of 16 columns, 32 keys and 16 rows
+assert len(DQ_AT) == N_DQ and DQ_AT == sorted(DQ_AT) and DQ_AT[0] - LATQ > SYNC_SLOT and DQ_AT[-1] <= NSLOT + P3 - (6 if D == 128 else 8)
 N_A = sum(1 for p in DQ_AT if p < NSLOT)             # of them in the block behind the pair's own
 SUM_SLOT = P3 - 3                                    # the sums behind this slot, the stores behind the next
 NREQ = 2 + 2 * NDQ
-assert NREQ == 6
+
+
+if D == 64:
+    kv.NPOOL = 8                                     # divides the sixteen fragments of a block that lie there
 
 
 class Pool(kv.Pool):
-    pass
+    """Head size 64 has the fragments of dS^T in accumulator registers."""
+
+    def __init__(self):
+        super().__init__()
+        self.ds = {}
+
+    def alloc_ds(self, tag, t):
+        assert t % 8 not in self.ds, f"fragment {self.ds[t % 8]} overwritten by {tag} before its use"
+        self.ds[t % 8] = tag
+        return DSF(t)
+
+    def use_ds(self, tag, t):
+        assert self.ds.pop(t % 8) == tag
+        return DSF(t)
+
+    def state(self):
+        return self.next, dict(self.owner), dict(self.uses_left), dict(self.reg), dict(self.ds)
+
+    def restore(self, state):
+        self.next, self.owner, self.uses_left, self.reg, self.ds = state[0], *(dict(x) for x in state[1:])
 
 
 class OneEmitter(Emitter):
@@ -110,20 +154,25 @@ def flag_load(e):
     e.raw(f"global_load_dword {vr(FLG)}, {vr(TMP + 2)}, {sr(S_PRED, 2)} sc1")
 
 
-def flag_wait(e, newer):
-    """Until the tile before has counted the pair; `newer` memory operations were issued behind the load of its count."""
+def flag_wait(e, newer, ahead=0):
+    """Until the tile before has counted the pair (`ahead` pairs behind this tile's own count); `newer` memory operations were issued
+    behind the load of its count."""
     l_spin, l_ok = e.label("spin"), e.label("counted")
+    need = S_CNT
+    if ahead:
+        need = T_INC
+        e.raw(f"s_add_u32 {sr(T_INC)}, {sr(S_CNT)}, {ahead}")
     if newer is not None:
         e.raw(f"s_waitcnt vmcnt({newer})")
         e.raw(f"v_readfirstlane_b32 {sr(T_MT)}, {vr(FLG)}")
-        e.raw(f"s_cmp_ge_i32 {sr(T_MT)}, {sr(S_CNT)}")
+        e.raw(f"s_cmp_ge_i32 {sr(T_MT)}, {sr(need)}")
         e.raw(f"s_cbranch_scc1 {l_ok}")
     e.raw(f"s_mov_b32 {sr(T_X)}, {SPINS}")
     e.raw(l_spin + ":")
     flag_load(e)
     e.raw("s_waitcnt vmcnt(0)")
     e.raw(f"v_readfirstlane_b32 {sr(T_MT)}, {vr(FLG)}")
-    e.raw(f"s_cmp_ge_i32 {sr(T_MT)}, {sr(S_CNT)}")
+    e.raw(f"s_cmp_ge_i32 {sr(T_MT)}, {sr(need)}")
     e.raw(f"s_cbranch_scc1 {l_ok}")
     e.raw("s_sleep 1")
     e.raw(f"s_sub_u32 {sr(T_X)}, {sr(T_X)}, 1")
@@ -140,30 +189,44 @@ def flag_store(e):
     e.raw("s_mov_b64 exec, -1")
 
 
-def old_load(e, j):
-    e.raw(f"global_load_dwordx4 {vr(OLD + 4 * j, 4)}, {vr(DQO)}, {sr(S_DQL, 2)} offset:{1024 * j} sc1")
+def old_load(e, j, x=0):
+    to = vr(OLD + 4 * j, 4) if D == 128 else ar(ACC64(x) + 4 * j, 4)
+    e.raw(f"global_load_dwordx4 {to}, {vr(DQO)}, {sr(S_DQL, 2)} offset:{1024 * j} sc1")
 
 
-def sum_store(e, j):
-    e.raw(f"global_store_dwordx4 {vr(DQO)}, {vr(OLD + 4 * j, 4)}, {sr(S_DQW, 2)} offset:{1024 * j}")
+def sum_store(e, j, x=0):
+    what = vr(OLD + 4 * j, 4) if D == 128 else ar(ACC64(x) + 4 * j, 4)
+    e.raw(f"global_store_dwordx4 {vr(DQO)}, {what}, {sr(S_DQW, 2)} offset:{1024 * j}")
 
 
-def next_pair():
-    return [f"s_add_u32 {sr(S_DQL)}, {sr(S_DQL)}, {sr(S_DQINC)}", f"s_addc_u32 {sr(S_DQL + 1)}, {sr(S_DQL + 1)}, 0",
-            f"s_add_u32 {sr(S_DQW)}, {sr(S_DQW)}, {PAIR}", f"s_addc_u32 {sr(S_DQW + 1)}, {sr(S_DQW + 1)}, 0"]
+def next_old():
+    return [f"s_add_u32 {sr(S_DQL)}, {sr(S_DQL)}, {sr(S_DQINC)}", f"s_addc_u32 {sr(S_DQL + 1)}, {sr(S_DQL + 1)}, 0"]
+
+
+def next_sum():
+    return [f"s_add_u32 {sr(S_DQW)}, {sr(S_DQW)}, {PAIR}", f"s_addc_u32 {sr(S_DQW + 1)}, {sr(S_DQW + 1)}, 0"]
 
 
 def rd_dq(e, pool, tag, t, buf):
-    """The two operands of MFMA t of a pair: keys 16 t .. + 15 of K^T and of dS^T."""
-    r = pool.alloc(tag + "k", 1)
-    e.ds_read(f"ds_read_b64_tr_b16 {vr(r, 2)}, {vr(KTR)} offset:{4 * GRP * t}", tag + "klo")
-    e.ds_read(f"ds_read_b64_tr_b16 {vr(r + 2, 2)}, {vr(KTR)} offset:{4 * GRP * t + 2 * GRP}", tag + "k")
-    r = pool.alloc(tag + "s", 1)
-    e.ds_read(f"ds_read_b64_tr_b16 {vr(r, 2)}, {vr(DSR)} offset:{DS_BYTES * buf + 16 * DSR_ROW * t}", tag + "slo")
-    e.ds_read(f"ds_read_b64_tr_b16 {vr(r + 2, 2)}, {vr(DSR)} offset:{DS_BYTES * buf + 16 * DSR_ROW * t + 8 * DSR_ROW}", tag + "s")
+    """The two operands of MFMA t of a pair: 16 keys of K^T and of dS^T.  Head size 64: 32 keys, rows 16 (t % 2) .. + 15 of dS^T."""
+    if D == 128:
+        r = pool.alloc(tag + "k", 1)
+        e.ds_read(f"ds_read_b64_tr_b16 {vr(r, 2)}, {vr(KTR)} offset:{rows(16) * t}", tag + "klo")
+        e.ds_read(f"ds_read_b64_tr_b16 {vr(r + 2, 2)}, {vr(KTR)} offset:{rows(16) * t + rows(8)}", tag + "k")
+    r = pool.alloc(tag + "s", 1) if D == 128 else pool.alloc_ds(tag, t)
+    reg = vr if D == 128 else ar
+    at, half = (16 * DSR_ROW * t, 8 * DSR_ROW) if D == 128 else (32 * DSR_ROW * (t // 2) + 32 * (t % 2), 16 * DSR_ROW)
+    e.ds_read(f"ds_read_b64_tr_b16 {reg(r, 2)}, {vr(DSR)} offset:{DS_BYTES * buf + at}", tag + "slo")
+    e.ds_read(f"ds_read_b64_tr_b16 {reg(r + 2, 2)}, {vr(DSR)} offset:{DS_BYTES * buf + at + half}", tag + "s")
 
 
-def mfma_dq(e, pool, tag, t):
+def mfma_dq(e, pool, tag, t, buf):
+    """(the pairs' sums alternate between two sets of registers as their dS do between buffers)"""
+    if D == 64:
+        e.need(tag + "s")
+        acc = ar(ACC64(buf) + 4 * (t % 2), 4)
+        e.mfma(acc, ar(KTF(t // 2), 4), ar(pool.use_ds(tag, t), 4), acc, shape="16x16x32")
+        return
     e.need(tag + "k")
     e.need(tag + "s")
     a, b = pool.use(tag + "k"), pool.use(tag + "s")
@@ -176,7 +239,7 @@ def plan_dq(e, pool, buf, seq):
     for t, p in enumerate(DQ_AT):
         tag = f"{seq}dq{t}_"
         def rd(tag=tag, t=t): rd_dq(e, pool, tag, t, buf)
-        def mm(tag=tag, t=t): mfma_dq(e, pool, tag, t)
+        def mm(tag=tag, t=t): mfma_dq(e, pool, tag, t, buf)
         second = p >= NSLOT
         parts[second][0][p - LATQ - NSLOT * second].append(rd)
         parts[second][1][p - NSLOT * second].append(mm)
@@ -193,14 +256,15 @@ def plan_reads(e, pool, stage, seq):
     def rd_nat(tag, imm, ks, xbase, uses):
         def f():
             r = pool.alloc(tag, uses)
-            e.ds_read(f"ds_read_b128 {vr(r, 4)}, {vr(xbase + ks // 2)} offset:{imm + 32 * (ks % 2)}", tag)
+            x, off = (xbase + ks // 2, 32 * (ks % 2)) if D == 128 else (xbase + ks, 0)
+            e.ds_read(f"ds_read_b128 {vr(r, 4)}, {vr(x)} offset:{imm + off}", tag)
         return f
 
     def rd_tr(tag, imm, m, db):
         def f():
             r = pool.alloc(tag, NKB)
-            e.ds_read(f"ds_read_b64_tr_b16 {vr(r, 2)}, {vr(TR + db)} offset:{imm + 4 * GRP * m}", tag + "lo")
-            e.ds_read(f"ds_read_b64_tr_b16 {vr(r + 2, 2)}, {vr(TR + db)} offset:{imm + 4 * GRP * m + 2 * GRP}", tag)
+            e.ds_read(f"ds_read_b64_tr_b16 {vr(r, 2)}, {vr(TR + db)} offset:{imm + rows(16) * m}", tag + "lo")
+            e.ds_read(f"ds_read_b64_tr_b16 {vr(r + 2, 2)}, {vr(TR + db)} offset:{imm + rows(16) * m + rows(8)}", tag)
         return f
 
     def rd_stat(tag, base_reg, imm, js):
@@ -211,8 +275,8 @@ def plan_reads(e, pool, stage, seq):
 
     for ks in range(KS):
         plan(2 * ks, rd_nat(f"{seq}q{ks}", qt, ks, X, NKB))
-        for nb in range(NKB):
-            plan(2 * ks + nb, rd_nat(f"{seq}K{nb}_{ks}", 8 * GRP * nb, ks, XK, 1))
+        for nb in range(NKB if D == 128 else 0):
+            plan(2 * ks + nb, rd_nat(f"{seq}K{nb}_{ks}", rows(32) * nb, ks, XK, 1))
         if ks == 0:
             reads[-EARLY].append(rd_stat(f"{seq}nl", NL, stats, (0, 1)))
             reads[-EARLY + 1].append(rd_stat(f"{seq}nl", NL, stats, (2, 3)))
@@ -228,7 +292,7 @@ def plan_reads(e, pool, stage, seq):
 
 
 def gen_step(e, pool, u, seq, reads, next_reads, dq_behind, dq_next, dq_start, masked):
-    """Block u of the six copies.  dq_behind: the pair two blocks back, finished here; dq_start: the pair of the block before, begun here;
+    """Block u of the copies.  dq_behind: the pair two blocks back, finished here; dq_start: the pair of the block before, begun here;
     dq_next: the same pair's second part, whose first reads are at the tail of this block."""
     stage, buf = u % NS, u % 2
     e.comment(f"================ block {u}")
@@ -248,7 +312,6 @@ def gen_step(e, pool, u, seq, reads, next_reads, dq_behind, dq_next, dq_start, m
                     for i in range(4):
                         d, a = P16 + 8 * nb + 4 * m + i, S(nb, 8 * m + 2 * i)
                         valu.append((max(early, P2 + 4), f"v_cvt_pk_bf16_f32 {vr(d)}, {vr(a)}, {vr(a + 1)}", (d,), 1, None))
-    n_first = len(valu)
     for m in range(2):
         for nb in range(NKB):
             early = P3 + 1 + nb
@@ -279,28 +342,44 @@ def gen_step(e, pool, u, seq, reads, next_reads, dq_behind, dq_next, dq_start, m
             vi[0] += 1
 
     side = {k: [] for k in range(NSLOT)}               # scalar and memory work behind fixed slots: text, or a function
-    side[2].append(lambda: flag_wait(e, NREQ + 1))     # behind the count's load: the request, a count's store
-    for j in range(4):
-        side[3 + j].append(lambda j=j: old_load(e, j))
-    for j in range(4):
-        side[SUM_SLOT + 1 + j].append(lambda j=j: sum_store(e, j))
-    side[SUM_SLOT + 5] += next_pair()
-    side[SUM_SLOT + 5].append(lambda: flag_load(e))
-    req = request_code((u + PF) % NS, u % 2)
-    for i, grp in enumerate(req):
-        side[SUM_SLOT + 6 + i] += grp
-    assert SUM_SLOT + 5 > SYNC_SLOT
-    adv = kv.advance_code()
-    per = 4
-    for i in range(0, len(adv), per):
-        side[P4 + i // per] += adv[i:i + per]
-    assert P4 + (len(adv) - 1) // per < NSLOT - 3
-    def counted():
-        e.raw(f"s_waitcnt vmcnt({NREQ + 1})")          # behind the stores: the count's load, the request
+    req = request_code((u + PF) % NS, (u + PF) % 2)
+
+    def counted(newer):
+        e.raw(f"s_waitcnt vmcnt({newer})")             # operations behind the stores
         flag_store(e)
         e.raw(f"s_add_u32 {sr(S_CNT)}, {sr(S_CNT)}, 1")
-    side[NSLOT - 2].append(counted)
-
+    if D == 128:
+        # pair s - 2 of block s: what the tile before left is read, added to and stored in this block
+        side[2].append(lambda: flag_wait(e, NREQ + 1))             # behind the count's load: the request, a count's store
+        for j in range(4):
+            side[3 + j].append(lambda j=j: old_load(e, j))
+            side[SUM_SLOT + 1 + j].append(lambda j=j: sum_store(e, j))
+        side[SUM_SLOT + 5] += next_old() + next_sum()
+        side[SUM_SLOT + 5].append(lambda: flag_load(e))
+        for i, grp in enumerate(req):
+            side[SUM_SLOT + 6 + i] += grp
+        assert SUM_SLOT + 5 > SYNC_SLOT and SUM_SLOT < DQ_AT[0] and SUM_SLOT + 6 + len(req) <= P4
+        side[NSLOT - 2].append(lambda: counted(NREQ + 1))          # behind the stores: the count's load, the request
+    else:
+        # pair s - 3 is counted, pair s - 2 stored, pair s read into the registers that leaves.  (Read behind the barrier instead,
+        # ahead of the request, and the tile waits for less: 3 % slower, the next tile runs further behind)
+        side[0].append(lambda: counted(NREQ + NP))                 # behind the stores: the request, what the tile before left
+        side[2].append(lambda: flag_load(e))
+        for j in range(NP):
+            side[SYNC_SLOT - 3 + j].append(lambda j=j: sum_store(e, j, u))
+        side[SYNC_SLOT + 1] += next_sum()
+        side[SYNC_SLOT + 1].append(f"s_waitcnt vmcnt({2 + NP})")         # pair s - 1 is there; behind it: a count's store, a count, the stores
+        for i, grp in enumerate(req):
+            side[SYNC_SLOT + 2 + i] += grp
+        side[NSLOT - 2].append(lambda: flag_wait(e, NREQ + NP, 2))
+        for j in range(NP):
+            side[NSLOT - 2].append(lambda j=j: old_load(e, j, u))
+        side[NSLOT - 1] += next_old()
+    adv = kv.advance_code()
+    per = 4 if D == 128 else 8
+    for i in range(0, len(adv), per):
+        side[P4 + i // per] += adv[i:i + per]
+    assert P4 + (len(adv) - 1) // per < NSLOT - 3      # a wait that looks ahead uses the same scalar
     stw = f"{seq}stw"
 
     def fill(units, budget, k):
@@ -314,12 +393,13 @@ def gen_step(e, pool, u, seq, reads, next_reads, dq_behind, dq_next, dq_start, m
             _, ks, nb = sl
             tag = f"{seq}q{ks}"
             e.need(tag)
-            e.need(f"{seq}K{nb}_{ks}")
+            if D == 128:
+                e.need(f"{seq}K{nb}_{ks}")
             if ks == 0:
                 e.need(f"{seq}nl3")
             c = vr(NL, 16) if ks == 0 else vr(S0 + 16 * nb, 16)
             a_reg = pool.use(tag)
-            e.mfma(vr(S0 + 16 * nb, 16), vr(a_reg, 4), vr(pool.use(f"{seq}K{nb}_{ks}"), 4), c)
+            e.mfma(vr(S0 + 16 * nb, 16), vr(a_reg, 4), vr(pool.use(f"{seq}K{nb}_{ks}") if D == 128 else KR(nb, ks), 4), c)
         elif ph == "dP":
             _, ks, nb = sl
             e.need(f"{seq}do{ks}")
@@ -347,10 +427,12 @@ def gen_step(e, pool, u, seq, reads, next_reads, dq_behind, dq_next, dq_start, m
         if masked and k == P2 + 1:
             e.raw(f"s_swappc_b64 {sr(T_MRET, 2)}, {sr(T_MASK, 2)}")
         if k == PUBLISH_SLOT:
-            e.raw("s_waitcnt vmcnt(5)")                # behind the request of the next block: a count's store, what the tile before left
+            # behind the request of the next block: a count's store, what the tile before left; head size 64: all of a block's and a
+            # count's store
+            e.raw(f"s_waitcnt vmcnt({5 if D == 128 else NREQ + 2})")
             kv.stat_publish_to(e, STAT_L, (u + 1) % 2, (u + 1) % NS, stw)
             units += 8
-        if k == SUM_SLOT:
+        if D == 128 and k == SUM_SLOT:
             e.raw("s_waitcnt vmcnt(0)")
             for v in range(16):
                 e.raw(f"v_add_f32 {vr(OLD + v)}, {vr(OLD + v)}, {vr(ACC_Q + v)}")
@@ -385,7 +467,7 @@ def gen_whole_offsets(e, reg, tmp):
 
 def gen_mask_routine(e):
     """As in gen_bwd_dkv_asm.py, with the parameters of a thread read from LDS."""
-    n4, low, high = TMP, TMP + 1, FLG
+    n4, low, high = TMP, TMP + 1, MASK_HIGH
     l_one, l_still = e.label("onehead"), e.label("still")
     for _ in range(3):
         e.raw("s_nop 7")
@@ -451,7 +533,7 @@ def gen_tail(e, buf):
         for i, t in enumerate(ts):
             if i + ahead < len(ts):
                 rd_dq(e, pool, f"{name}{ts[i + ahead]}_", ts[i + ahead], b)
-            mfma_dq(e, pool, f"{name}{t}_", t)
+            mfma_dq(e, pool, f"{name}{t}_", t, b)
 
     def finish():
         for _ in range(4):
@@ -461,9 +543,27 @@ def gen_tail(e, buf):
             e.raw(f"v_add_f32 {vr(OLD + v)}, {vr(OLD + v)}, {vr(ACC_Q + v)}")
         for j in range(4):
             sum_store(e, j)
-        for ln in next_pair():
+        for ln in next_old() + next_sum():
             e.raw(ln)
 
+    if D == 64:                                        # both pairs have been read
+        e.raw("s_waitcnt vmcnt(0) lgkmcnt(0)")
+        e.ds = []
+        e.raw("s_barrier")
+        mfmas(list(range(N_A, N_DQ)), buf, "a")
+        mfmas(list(range(N_DQ)), 1 - buf, "b")
+        for _ in range(4):
+            e.raw("s_nop 7")
+        for x in (buf, 1 - buf):
+            for j in range(NP):
+                sum_store(e, j, x)
+            for ln in next_sum():
+                e.raw(ln)
+        e.raw(f"s_add_u32 {sr(S_CNT)}, {sr(S_CNT)}, 2")
+        e.raw("s_waitcnt vmcnt(0)")
+        flag_store(e)
+        e.raw("s_waitcnt vmcnt(0) lgkmcnt(0)")
+        return
     e.raw("s_waitcnt vmcnt(0) lgkmcnt(0)")             # every wavefront has written its dS of the last block
     e.ds = []
     flag_wait(e, 0)
@@ -495,7 +595,7 @@ def generate():
     for t in (T_DBLK, T_DSTEP):
         e.raw(f"s_mov_b32 {sr(t)}, 0")
     e.raw(f"s_mov_b32 {sr(T_REM)}, {sr(S_NSTEPS)}")
-    e.raw(f"s_mov_b32 {sr(S_CNT)}, -1")
+    e.raw(f"s_mov_b32 {sr(S_CNT)}, {-1 if D == 128 else -2}")
     e.raw(f"s_ashr_i32 {sr(T_OHI)}, {sr(S_QOUT)}, 31")
     e.raw(f"s_mul_i32 {sr(T_M0)}, {sr(S_WAVE)}, {GRP}")
     e.raw(f"s_add_u32 {sr(T_M0)}, {sr(T_M0)}, {sr(S_LDS)}")
@@ -515,14 +615,30 @@ def generate():
         e.raw(f"v_readfirstlane_b32 {sr(dst)}, {vr(src)}")
     e.raw(f"s_cmp_lg_u32 {sr(S_NRAG)}, -1")
     e.raw(f"s_cselect_b32 {sr(S_EVT)}, -1, {sr(S_DIAG)}")
-    e.comment("---- K tile of the workgroup (256 rows) to LDS: instruction 4 j + wave fills group 4 j + wave of four rows")
-    for j in range(16):
+    e.comment("---- K tile of the workgroup (256 rows) to LDS: instruction 4 j + wave fills group 4 j + wave")
+    per_load = 4 * 1024 // (2 * D)                     # rows
+    for j in range(256 // per_load):
         e.raw(f"v_mul_lo_u32 {vr(TMP)}, {vr(kv.I_SROW)}, {sr(S_VRS)}")
         e.raw(f"v_add_u32 {vr(TMP)}, {vr(TMP)}, {vr(kv.I_VCOL)}")
         e.raw(f"s_add_u32 m0, {sr(T_M0)}, {KT + 4 * GRP * j}")
         e.raw("s_nop 0")
         e.raw(f"global_load_lds_dwordx4 {vr(TMP)}, {sr(T_VPTR, 2)}")
-        e.raw(f"v_add_u32 {vr(kv.I_SROW)}, 16, {vr(kv.I_SROW)}")
+        e.raw(f"v_add_u32 {vr(kv.I_SROW)}, {per_load}, {vr(kv.I_SROW)}")
+    if D == 64:
+        e.comment("---- resident K fragments likewise, from the tile's first row on")
+        e.raw(f"v_mbcnt_lo_u32_b32 {vr(TMP)}, -1, 0")
+        e.raw(f"v_mbcnt_hi_u32_b32 {vr(TMP)}, -1, {vr(TMP)}")
+        e.raw(f"v_and_b32 {vr(TMP + 1)}, 31, {vr(TMP)}")
+        e.raw(f"v_lshrrev_b32 {vr(TMP)}, 5, {vr(TMP)}")
+        e.raw(f"v_lshlrev_b32 {vr(TMP)}, 4, {vr(TMP)}")
+        e.raw(f"s_lshl_b32 {sr(T_X)}, {sr(S_WAVE)}, 6")
+        e.raw(f"v_add_u32 {vr(TMP + 1)}, {sr(T_X)}, {vr(TMP + 1)}")
+        for nb in range(NKB):
+            e.raw(f"v_mul_lo_u32 {vr(TMP + 2)}, {vr(TMP + 1)}, {sr(S_VRS)}")
+            e.raw(f"v_add_u32 {vr(TMP + 2)}, {vr(TMP + 2)}, {vr(TMP)}")
+            for ks in range(KS):
+                e.raw(f"global_load_dwordx4 {vr(KR(nb, ks), 4)}, {vr(TMP + 2)}, {sr(T_VPTR, 2)} offset:{32 * ks}")
+            e.raw(f"v_add_u32 {vr(TMP + 1)}, 32, {vr(TMP + 1)}")
     l_here = e.label("here")
     e.raw(f"s_getpc_b64 {sr(T_MASK, 2)}")
     e.raw(l_here + ":")
@@ -548,61 +664,107 @@ def generate():
     e.raw(f"v_add_u32 {vr(DSW)}, {vr(DSW)}, {vr(DQO)}")
     e.raw(f"s_add_u32 {sr(T_X)}, {sr(S_LDS)}, {DS0}")
     e.raw(f"v_add_u32 {vr(DSW)}, {sr(T_X)}, {vr(DSW)}")
-    # dS, read transposed: key 4 g + (lane % 16) / 4, rows 16 ((lane / 16) % 2) + 4 (lane % 4) .. + 3
-    e.raw(f"v_and_b32 {vr(DSR)}, 15, {vr(LANE)}")
-    e.raw(f"v_lshrrev_b32 {vr(DSR)}, 2, {vr(DSR)}")
-    e.raw(f"v_lshlrev_b32 {vr(DQO)}, 2, {vr(G)}")
-    e.raw(f"v_add_u32 {vr(DSR)}, {vr(DSR)}, {vr(DQO)}")
-    e.raw(f"v_mul_u32_u24 {vr(DSR)}, {DSR_ROW}, {vr(DSR)}")
-    e.raw(f"v_bfe_u32 {vr(DQO)}, {vr(LANE)}, 4, 1")
-    e.raw(f"v_lshlrev_b32 {vr(DQO)}, 5, {vr(DQO)}")
-    e.raw(f"v_add_u32 {vr(DSR)}, {vr(DSR)}, {vr(DQO)}")
+    # dS, read transposed: key 4 g + (lane % 16) / 4, rows 16 ((lane / 16) % 2) + 4 (lane % 4) .. + 3; head size 64: key lane / 4, rows
+    # 4 (lane % 4) .. + 3
+    if D == 128:
+        e.raw(f"v_and_b32 {vr(DSR)}, 15, {vr(LANE)}")
+        e.raw(f"v_lshrrev_b32 {vr(DSR)}, 2, {vr(DSR)}")
+        e.raw(f"v_lshlrev_b32 {vr(DQO)}, 2, {vr(G)}")
+        e.raw(f"v_add_u32 {vr(DSR)}, {vr(DSR)}, {vr(DQO)}")
+        e.raw(f"v_mul_u32_u24 {vr(DSR)}, {DSR_ROW}, {vr(DSR)}")
+        e.raw(f"v_bfe_u32 {vr(DQO)}, {vr(LANE)}, 4, 1")
+        e.raw(f"v_lshlrev_b32 {vr(DQO)}, 5, {vr(DQO)}")
+        e.raw(f"v_add_u32 {vr(DSR)}, {vr(DSR)}, {vr(DQO)}")
+    else:
+        e.raw(f"v_lshrrev_b32 {vr(DSR)}, 2, {vr(LANE)}")
+        e.raw(f"v_mul_u32_u24 {vr(DSR)}, {DSR_ROW}, {vr(DSR)}")
     e.raw(f"v_and_b32 {vr(DQO)}, 3, {vr(LANE)}")
     e.raw(f"v_lshlrev_b32 {vr(DQO)}, 3, {vr(DQO)}")
     e.raw(f"v_add_u32 {vr(DSR)}, {vr(DSR)}, {vr(DQO)}")
     e.raw(f"v_add_u32 {vr(DSR)}, {sr(T_X)}, {vr(DSR)}")
+    if D == 64:
+        # K^T, read transposed: key lane / 4 (groups of eight rows; chunk c of row r lies at c ^ (4 (r / 2 % 2) + 2 (r / 4 % 2))),
+        # columns 16 wave + 4 (lane % 4) .. + 3
+        e.raw(f"v_bfe_u32 {vr(KTR)}, {vr(LANE)}, 1, 1")                  # chunk 2 wave + (lane % 4) / 2, in 16 bytes
+        e.raw(f"s_lshl_b32 {sr(T_X)}, {sr(S_WAVE)}, 1")
+        e.raw(f"v_add_u32 {vr(KTR)}, {sr(T_X)}, {vr(KTR)}")
+        e.raw(f"v_bfe_u32 {vr(DQO)}, {vr(LANE)}, 3, 1")                  # bit 1 of the row
+        e.raw(f"v_lshlrev_b32 {vr(DQO)}, 2, {vr(DQO)}")
+        e.raw(f"v_xor_b32 {vr(KTR)}, {vr(DQO)}, {vr(KTR)}")
+        e.raw(f"v_bfe_u32 {vr(DQO)}, {vr(LANE)}, 4, 1")                  # bit 2
+        e.raw(f"v_lshlrev_b32 {vr(DQO)}, 1, {vr(DQO)}")
+        e.raw(f"v_xor_b32 {vr(KTR)}, {vr(DQO)}, {vr(KTR)}")
+        e.raw(f"v_lshlrev_b32 {vr(KTR)}, 4, {vr(KTR)}")
+        e.raw(f"v_and_b32 {vr(DQO)}, 1, {vr(LANE)}")
+        e.raw(f"v_lshlrev_b32 {vr(DQO)}, 3, {vr(DQO)}")
+        e.raw(f"v_add_u32 {vr(KTR)}, {vr(KTR)}, {vr(DQO)}")
+        e.raw(f"v_bfe_u32 {vr(DQO)}, {vr(LANE)}, 2, 3")                  # row of its group
+        e.raw(f"v_lshlrev_b32 {vr(DQO)}, 7, {vr(DQO)}")
+        e.raw(f"v_add_u32 {vr(KTR)}, {vr(KTR)}, {vr(DQO)}")
+        e.raw(f"v_mul_u32_u24 {vr(DQO)}, {GRP}, {vr(G)}")                # group lane / 32
+        e.raw(f"v_add_u32 {vr(KTR)}, {vr(KTR)}, {vr(DQO)}")
+        e.raw(f"s_add_u32 {sr(T_X)}, {sr(S_LDS)}, {KT}")
+        e.raw(f"v_add_u32 {vr(KTR)}, {sr(T_X)}, {vr(KTR)}")
     # workspace: 16 lane + SLICE wave
     e.raw(f"s_mul_i32 {sr(T_X)}, {sr(S_WAVE)}, {SLICE}")
     e.raw(f"v_lshlrev_b32 {vr(DQO)}, 2, {vr(L4)}")
     e.raw(f"v_add_u32 {vr(DQO)}, {sr(T_X)}, {vr(DQO)}")
-    # natural reads: x[a] = xbase + (gf16 ^ 64 a), steps 2 a and 2 a + 1; K: the wavefront's 64 rows
-    e.raw(f"s_mul_i32 {sr(T_X)}, {sr(S_WAVE)}, {16 * GRP}")
-    e.raw(f"s_add_u32 {sr(T_X)}, {sr(T_X)}, {KT}")
-    for a in range(KS // 2):
-        e.raw(f"v_xor_b32 {vr(TMP)}, {64 * a}, {vr(kv.I_GF16)}")
+    # natural reads: x[a] = xbase + (gf16 ^ 64 a), steps 2 a and 2 a + 1; K: the wavefront's 64 rows.  Head size 64: x[ks] = xbase + (gf16 ^ 32 ks)
+    if D == 128:
+        e.raw(f"s_mul_i32 {sr(T_X)}, {sr(S_WAVE)}, {rows(64)}")
+        e.raw(f"s_add_u32 {sr(T_X)}, {sr(T_X)}, {KT}")
+    for a in range(4):
+        e.raw(f"v_xor_b32 {vr(TMP)}, {(64 if D == 128 else 32) * a}, {vr(kv.I_GF16)}")
         e.raw(f"v_add_u32 {vr(X + a)}, {vr(kv.I_XBASE)}, {vr(TMP)}")
-        e.raw(f"v_add_u32 {vr(XK + a)}, {sr(T_X)}, {vr(X + a)}")
-    # transpose reads: tr[db] = trbase + (lf16 ^ 64 db); K^T: columns 32 wave .. + 31
+        if D == 128:
+            e.raw(f"v_add_u32 {vr(XK + a)}, {sr(T_X)}, {vr(X + a)}")
+    # transpose reads: tr[db] = trbase + (lf16 ^ 64 db); K^T: the wavefront's 32 columns
     for db in range(DB):
         e.raw(f"v_xor_b32 {vr(TMP)}, {64 * db}, {vr(kv.I_LF16)}")
         e.raw(f"v_add_u32 {vr(TR + db)}, {vr(kv.I_TRBASE)}, {vr(TMP)}")
-    e.raw(f"s_lshl_b32 {sr(T_X)}, {sr(S_WAVE)}, 6")
-    e.raw(f"v_xor_b32 {vr(TMP)}, {sr(T_X)}, {vr(kv.I_LF16)}")
-    e.raw(f"v_add_u32 {vr(KTR)}, {vr(kv.I_TRBASE)}, {vr(TMP)}")
-    e.raw(f"v_add_u32 {vr(KTR)}, {KT}, {vr(KTR)}")
-    e.comment("---- blocks 0 and 1 requested; accumulators to zero meanwhile")
+    if D == 128:
+        e.raw(f"s_lshl_b32 {sr(T_X)}, {sr(S_WAVE)}, 6")
+        e.raw(f"v_xor_b32 {vr(TMP)}, {sr(T_X)}, {vr(kv.I_LF16)}")
+        e.raw(f"v_add_u32 {vr(KTR)}, {vr(kv.I_TRBASE)}, {vr(TMP)}")
+        e.raw(f"v_add_u32 {vr(KTR)}, {KT}, {vr(KTR)}")
+    e.comment("---- the first blocks requested; accumulators to zero meanwhile")
 
-    for blk in range(2):
+    def request(blk):
         if blk:
             l_still = e.label("still")
             e.raw(f"s_cmp_lt_u32 {sr(T_DSTEP)}, {sr(S_NRAG)}")
             e.raw(f"s_cbranch_scc1 {l_still}")
             gen_whole_offsets(e, TMP, T_MT)
             e.raw(l_still + ":")
-            flag_load(e)
-        for grp in request_code(blk, blk):
+        for grp in request_code(blk % NS, blk % 2):
             for ln in grp:
                 e.raw(ln)
         for ln in kv.advance_code():
             e.raw(ln)
-    flag_store(e)                                      # (as every block does: the waits count it)
+
+    request(0)
+    if D == 128:
+        flag_load(e)
+    request(1)
+    if D == 128:
+        flag_store(e)                                  # (as every block does: the waits count it)
     for i in range(256):
         e.raw(f"v_accvgpr_write_b32 {ar(i)}, 0")
     e.comment("statistics of block 0 to LDS stage 0")
-    e.raw(f"s_waitcnt vmcnt({NREQ + 2})")
+    e.raw(f"s_waitcnt vmcnt({NREQ + (2 if D == 128 else 0)})")
     kv.stat_publish_to(e, STAT_L, 0, 0, "stw")
     e.raw("s_waitcnt lgkmcnt(0)")
     e.ds = []
+    if D == 64:
+        request(2)
+        e.comment("K^T fragments")
+        e.raw("s_barrier")
+        for t in range(N_DQ // 2):
+            for half in range(2):
+                e.raw(f"ds_read_b64_tr_b16 {vr(POOL0 + 4 * t + 2 * half, 2)}, {vr(KTR)} offset:{rows(32) * t + rows(16) * half}")
+        e.raw("s_waitcnt lgkmcnt(0)")
+        for i in range(2 * N_DQ):
+            e.raw(f"v_accvgpr_write_b32 {ar(KTF(0) + i)}, {vr(POOL0 + i)}")
     e.raw("s_barrier")
 
     plans = [plan_reads(e, pool, u % NS, u) for u in range(COPIES)] + [None]
@@ -617,7 +779,7 @@ def generate():
     l_tail = [e.label("tail0"), e.label("tail1")]
     l_whole, l_masked = ([e.label(f"{x}{u}") for u in range(COPIES)] for x in ("whole", "masked"))
     strip = lambda tags: [t.lstrip("0123456789") for t in tags]
-    entry, entry_pool = list(e.ds), (pool.next, dict(pool.owner), dict(pool.uses_left), dict(pool.reg))
+    entry, entry_pool = list(e.ds), pool.state()
     at = [(strip(entry), pool.next % kv.NPOOL)]
     e.raw(f"s_cmp_le_u32 {sr(T_REM)}, {sr(S_EVT)}")
     e.raw(f"s_cbranch_scc1 {l_masked[0]}")
@@ -625,7 +787,7 @@ def generate():
     for masked in (False, True):
         if masked:
             e.ds = list(entry)
-            pool.next, pool.owner, pool.uses_left, pool.reg = entry_pool[0], dict(entry_pool[1]), dict(entry_pool[2]), dict(entry_pool[3])
+            pool.restore(entry_pool)
         for u in range(COPIES):
             e.raw((l_masked if masked else l_whole)[u] + ":")
             assert (strip(e.ds), pool.next % kv.NPOOL) == at[u], (e.ds, at[u])
@@ -646,7 +808,8 @@ def generate():
                 e.raw(f"s_cbranch_scc1 {l_leave}")
             if not masked and u < COPIES - 1:
                 at.append((strip(e.ds), pool.next % kv.NPOOL))
-        assert (strip(e.ds), pool.next % kv.NPOOL) == at[0], (e.ds, at[0])
+        # writes of dS may be under way here that are not behind the prologue: waits made without them wait for more
+        assert ([t for t in strip(e.ds) if not t.startswith("ds")], pool.next % kv.NPOOL) == at[0], (e.ds, at[0])
         e.raw(f"s_branch {(l_masked if masked else l_whole)[0]}")
     for l_leave, l_to, l_end in stubs:
         e.raw(l_leave + ":")
@@ -679,7 +842,7 @@ def main():
     e = generate()
     clob = [f"v{i}" for i in range(256) if not (kv.IN_V <= i < kv.IN_V + 16)] + [f"a{i}" for i in range(256)]
     clob += [f"s{i}" for i in range(64, 96)]
-    write_inc(sys.stdout, "gen_bwd_one_asm.py", "ST_ONE_FAST", e, LDS_BYTES, clob)
+    write_inc(sys.stdout, "gen_bwd_one_asm.py" + (" 64" if D == 64 else ""), "ST_ONE_FAST" + ("64" if D == 64 else ""), e, LDS_BYTES, clob)
 
 
 if __name__ == "__main__":

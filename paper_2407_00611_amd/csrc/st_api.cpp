@@ -29,10 +29,13 @@ thread_local char g_err[512] = "";
 // ---- scratch of st_ring_bwd_noalloc: device memory every loaded GPU holds until the process ends ----
 // In host code the array's name is only a handle: its device address differs from GPU to GPU and is looked up
 // once per device with hipGetSymbolAddress (scratch_of_current_device); kernels only ever see that pointer.
-// Partial sums of under-filled launches have an array of their own, as large as a ring backward ever uses (kPartsMost): what a
+// Partial sums of under-filled launches have an array of their own, as large as such a backward ever uses (kRoomMost): what a
 // call gets beside it must not depend on how much of the 40 MiB its Delta and Q' leave.
-constexpr size_t kScratchBytes = (size_t)40 << 20, kPartsMost = (size_t)64 << 20, kOneMost = (size_t)96 << 20;
-constexpr size_t kRoomMost = kOneMost;               // what a ring backward ever uses beside its Delta and Q'
+constexpr size_t kScratchBytes = (size_t)40 << 20, kPartsMost = (size_t)64 << 20;
+// What a ring backward ever uses beside its Delta and Q' (the sums of a walk of one, OneRoom, or partial sums, at most kPartsMost):
+// shares that st_ring_bwd_noalloc takes, and larger ones (see room_most): backward of 32/8 heads x 16384 rows x 3 chunks in one walk 22.7
+// ms, in two passes 26.4; 8 heads x 32768 x 2 14.1, 15.7.
+constexpr size_t kRoomMost = (size_t)96 << 20, kRoomMostLarge = (size_t)320 << 20;
 static __device__ __align__(256) unsigned char scratch[kScratchBytes];
 static __device__ __align__(256) unsigned char scratch_parts[kRoomMost];
 constexpr int kScratchDevices = 64;
@@ -497,16 +500,19 @@ void f32_bwd_split(BwdSplit& r, const st::Shape& s, const QueryWalk& walk, const
 // Measured (sums of a backward's launches, us; first the two passes, then one walk of batches of 1 / of all the heads of an XCD; last
 // ranks of rings of 8): 8 heads x 1024 rows 129, 143; x 2048 389, 344; x 4096 1346, 1123; 32 heads x 512 158, 144 / 127; x 1024 420, 373 / 348; x
 // 2048 1374, 1183 / 1178; 12 heads x 2048 582, 608; 24 heads x 2048 1072, 896; 8 x 4 heads x 1024 357, 343; x 2048 1300, 1134.  An XCD
-// without a head, or with one less than the others, idles: 4 x 4 heads x 2048 679, 1109.
+// without a head, or with one less than the others, idles: 4 x 4 heads x 2048 679, 1109.  Head size 64, where a tile runs three blocks
+// behind the one before: 8 heads x 1024 80, 134; x 2048 230, 251; x 4096 790, 650; 32 heads x 512 96, 83; x 1024 243, 198; x 4096 2867,
+// 2506; 24 heads x 2048 625, 495; 12 heads x 2048 331, 341; 8 x 4 heads x 1024 208, 235; x 2048 751, 664; 4 x 4 heads x 2048 381, 576.
 double one_walk_us(const st::Shape& s, const KeyWalk& keys, int batch) {
   const int64_t rounds = (keys.heads / batch + 7) / 8;
   const double busy = (double)std::min<int64_t>(keys.heads, 8) / 8 * std::min(1.0, (double)keys.seen * rounds * batch / 32);
-  const double step = 1.5 + 0.45 * busy, fixed = 20, unseen = 10;
+  const bool wide = s.D == 128;
+  const double step = wide ? 1.5 + 0.45 * busy : 0.9 + 0.1 * busy, fixed = wide ? 20 : 12, unseen = 10, behind = wide ? step : 3 * step;
   const double around = 10 + (double)s.B * s.Hq * s.Sq * s.D * 12 / 5.5e6;      // the counts' start values, the pass that adds to dq
   if (rounds * batch * keys.tiles > 512) {             // by the work alone
     double us = 0;
     for (int i = 0; i < keys.n; ++i) us += keys.c[i].tiles * (keys.c[i].blocks > 0 ? fixed + keys.c[i].blocks * keys.G * step : unseen);
-    return around + us * rounds * batch / 32 + 31.0 / batch * step;
+    return around + us * rounds * batch / 32 + 31.0 / batch * behind;
   }
   double free[32] = {}, end = 0;
   for (int64_t r = 0; r < rounds; ++r) {
@@ -519,7 +525,7 @@ double one_walk_us(const st::Shape& s, const KeyWalk& keys, int batch) {
             at += unseen;
           } else {
             const double start = std::max(at + fixed / 2, before[h]);
-            before[h] = start + step;
+            before[h] = start + behind;
             at = start + keys.c[i].blocks * keys.G * step + fixed / 2;
           }
           end = std::max(end, at);
@@ -529,7 +535,7 @@ double one_walk_us(const st::Shape& s, const KeyWalk& keys, int batch) {
 }
 // heads of a batch, 0: two passes
 int one_walk(const st::Shape& s, const KeyWalk& keys, const int64_t* k_offset, int n, size_t room, double less_us) {
-  if (s.D != 128 || s.Sk % st::kDkvFastKeys != 0 || keys.seen < 1) return 0;
+  if (s.Sk % st::kDkvFastKeys != 0 || keys.seen < 1) return 0;
   if (st::knobs().one_walk != 1) less_us = st::knobs().one_walk ? 1e30 : 0;
   if (s.causal && k_offset != nullptr)
     for (int c = 1; c < n; ++c)                        // a tile sees the blocks of the ones behind it
@@ -602,9 +608,10 @@ BwdSplit bwd_splits(const st::Shape& s, int dtype, const int64_t* k_offset, int 
   key_walk(keys, s, k_offset, n);
   const Cost kv_cost = dkv_cost(s.D);
   // the one walk instead, if it is faster than the two passes: over 108 shares its model is right to 6 % on average, that of the passes
-  // says 0.87 of what they take (a walk of some hundred blocks on a full chip runs at the power limit)
+  // says 0.87 of what they take (a walk of some hundred blocks on a full chip runs at the power limit).  Head size 64, 81 shares: right to
+  // 8 %, the passes' 1.1 of what short ones take; at this bar none of them lost, and three that would have gained 3 to 8 % stay with them
   auto or_one = [&](const BwdSplit& two, double us) {
-    const int heads = ring_call ? one_walk(s, keys, k_offset, n, one_room, 1.07 * us) : 0;
+    const int heads = ring_call ? one_walk(s, keys, k_offset, n, one_room, (s.D == 128 ? 1.07 : 0.87) * us) : 0;
     if (heads == 0) return two;
     BwdSplit one;
     one.one_heads = heads;
@@ -1135,10 +1142,11 @@ static size_t bwd_base_bytes(const st_ring_desc* d) {
          (d->dtype == ST_BF16 ? align_up(n_o / 2, 256) : 0);
 }
 
-// What a workspace has beyond the rest, for the partial sums of a ring backward
+// What a workspace has beyond the rest, for the sums of a ring backward, and the most of it that is ever used
+static size_t room_most(const st_ring_desc* d) { return bwd_base_bytes(d) > kScratchBytes ? kRoomMostLarge : kRoomMost; }
 static size_t ring_room(const st_ring_desc* d, size_t workspace_bytes) {
   const size_t base = bwd_base_bytes(d);
-  return workspace_bytes > base ? std::min(workspace_bytes - base, kRoomMost) : 0;
+  return workspace_bytes > base ? std::min(workspace_bytes - base, room_most(d)) : 0;
 }
 
 // Partial sums to provide for.  Under a causal mask the plan depends on where the chunks lie: as a caller visits them who lists
@@ -1149,7 +1157,7 @@ static size_t ring_parts_bytes(const st_ring_desc* d, int mode) {
   const bool fused = mode == ST_RING_FUSED;
   const int n_chunks = std::min(d->n_chunks, ST_MAX_CHUNKS), per_launch = std::min(n_chunks, fused ? st::kMaxTable : 1);
   size_t most = 0;
-  auto look = [&](const int64_t* k_offset, int n) { most = std::max(most, bwd_splits(s, d->dtype, k_offset, n, kRoomMost).bytes); };
+  auto look = [&](const int64_t* k_offset, int n) { most = std::max(most, bwd_splits(s, d->dtype, k_offset, n, room_most(d)).bytes); };
   if (!d->causal || d->k_offset == nullptr) {
     for (int n = 1; n <= per_launch; ++n) look(nullptr, n);
     return most;
@@ -1196,7 +1204,7 @@ struct RingVisit {
 // st_ring_bwd with that much and st_ring_bwd_noalloc compute the same sums; with less it is the best one that fits.
 static BwdSplit ring_plan(const st_ring_desc* d, int mode, const int64_t* k_offset, int n, bool provided, size_t room) {
   const st::Shape s = shape_of(d);
-  BwdSplit r = bwd_splits(s, d->dtype, k_offset, n, kRoomMost);
+  BwdSplit r = bwd_splits(s, d->dtype, k_offset, n, room_most(d));
   if (!provided && r.bytes > 0) room = std::min(room, ring_parts_bytes(d, mode));
   return r.bytes <= room ? r : bwd_splits(s, d->dtype, k_offset, n, room);
 }
@@ -1510,7 +1518,7 @@ extern "C" int st_testing_bwd_plan(const st_ring_desc* d, const int32_t* order, 
   for (int x = 0; x < n_visit; ++x)
     if (!chunk_invisible(d, order[x]) || (assign && mode == ST_RING_FUSED && d->dtype == ST_BF16)) vis.add(d, order[x]);
   const size_t base = mode < 0 ? align_up((size_t)d->B * d->Sq * d->Hq * d->D * 2, 256) : bwd_base_bytes(d);
-  const size_t room = workspace_bytes < 0 ? kRoomMost : (size_t)workspace_bytes > base ? std::min((size_t)workspace_bytes - base, kRoomMost) : 0;
+  const size_t most = mode < 0 ? kPartsMost : room_most(d), room = workspace_bytes < 0 ? most : (size_t)workspace_bytes > base ? std::min((size_t)workspace_bytes - base, most) : 0;
   const int per_launch = mode == ST_RING_FUSED ? st::kMaxTable : 1;
   int written = 0;
   for (int x0 = 0; x0 < vis.n; x0 += per_launch) {

@@ -212,7 +212,7 @@ __host__ __device__ inline int64_t kv_slot_floats(const Shape& s) { return (int6
 // Room of a backward in one walk (gen_bwd_one_asm.py), byte offsets: what hands out the tiles (tickets of 16 XCDs and the next batch, 128
 // bytes apart, claims), a count that is never too low, the tiles' counts (one per wavefront), a pair of zeros, and the pairs of each
 // (KV head, batch entry) in the order of the walk behind two that do not exist.
-constexpr int kOnePairBytes = 16384;
+__host__ __device__ constexpr int one_pair_bytes(int d) { return 32 * d * 4; }
 struct OneRoom {
   int64_t plenty, claims, counts, zeros, pairs, group_bytes, bytes;
   int32_t claims_each, tiles;
@@ -224,8 +224,8 @@ struct OneRoom {
     claims_each = (int32_t)((groups / heads + 256 + 31) / 32 * 32);      // (a workgroup that finds no batch left has taken a ticket too)
     counts = claims + (int64_t)16 * claims_each * 4;
     zeros = counts + (groups * tiles * 4 * 4 + 255) / 256 * 256;
-    pairs = zeros + kOnePairBytes;
-    group_bytes = (s.Hq / s.Hkv * blocks + 2) * kOnePairBytes;
+    pairs = zeros + one_pair_bytes(s.D);
+    group_bytes = (s.Hq / s.Hkv * blocks + 2) * one_pair_bytes(s.D);
     bytes = pairs + groups * group_bytes;
   }
 };
