@@ -262,8 +262,8 @@ st_status st_ring_bwd(const st_ring_desc* desc, const st_tensor* q, const st_ten
  * every GPU the library runs on holds until the process ends.  The call allocates and frees nothing (no hipMalloc /
  * hipFree, no allocating library routine); the array's device address is looked up once per device, on the first call.
  * A share whose Delta, counters and copy of Q exceed the array returns ST_ERR_WORKSPACE and enqueues nothing;
- * partial sums of launches that are split over more workgroups have a second static array of 64 MiB, which is also the most
- * that st_ring_bwd uses of its workspace for them.  Every call on a GPU uses
+ * partial sums of launches that are split over more workgroups, or of one that makes all three gradients, have a second static array of
+ * 96 MiB, which is also the most that st_ring_bwd uses of its workspace for them (320 MiB for shares that this call refuses).  Every call on a GPU uses
  * that GPU's one array (what must start at zero is cleared by the call itself): calls that overlap on one GPU, on different streams or from different threads, race; order them. */
 st_status st_ring_bwd_noalloc(const st_ring_desc* desc, const st_tensor* q, const st_tensor* d_o,
                               const st_tensor* o, int32_t o_dtype, const float* lse_final,
