@@ -71,6 +71,8 @@ LDS_BYTES = PBLK + 256 * 32 + 4 * NUNI
 assert LDS_BYTES <= 163840 and PBLK >= 4 * 2 * 32 * (4 * D + 16)
 # words of the uniform block behind the six of gen_bwd_dkv_asm.py: what only the epilogue needs
 U_DKPTR, U_DVPTR, U_RS32, U_SCALE, U_FLAGS, U_DKLP, U_DVLP = 8, 10, 12, 13, 14, 16, 18
+U_PLENTY = 6                                         # address of the count that is never too low, which a wait that gives up goes over to
+GAVE_UP = 64                                         # from there to the word that says so (OneRoom::gave_up)
 NP = D // 32                                         # accesses of 1 KiB that a wavefront's part of a pair takes
 SLICE = 1024 * NP                                    # the part in the workspace
 PAIR = 4 * SLICE
@@ -86,8 +88,7 @@ QOFF, DOOFF, STAT_G, STAT_L, G16, ACC_Q = 233, 235, 237, 238, 239, 240
 OLD = NL                                             # what the tile before left, from slot 3 to the stores
 MASK_HIGH = FLG if D == 128 else XK                  # a register that is free when the masks are made
 # scalars in the places of the epilogue's inputs
-S_DQL, S_DQW, S_DQINC, S_CNT, S_PRED, S_OWN = 52, 54, 57, 59, 60, 62
-SPINS = int(os.environ.get("ST_GEN_ONE_SPINS", 1 << 21))     # most polls of a wait: seconds; then it goes on, so that every launch ends
+S_DQL, S_DQW, S_DQINC, S_POLLS, S_CNT, S_PRED, S_OWN = 52, 54, 57, 58, 59, 60, 62
 
 LAT = int(os.environ.get("ST_GEN_ONE_LAT", 3))
 LATQ = int(os.environ.get("ST_GEN_ONE_LATQ", 3))
@@ -133,6 +134,10 @@ class Pool(kv.Pool):
 
 
 class OneEmitter(Emitter):
+    def __init__(self):
+        super().__init__()
+        self.give_ups = []                              # (label, where it goes back to) of every wait
+
     def ds_read(self, text, tag):
         if len(self.ds) >= 15:                          # the counter has four bits
             self.need(self.ds[2])
@@ -156,8 +161,10 @@ def flag_load(e):
 
 def flag_wait(e, newer, ahead=0):
     """Until the tile before has counted the pair (`ahead` pairs behind this tile's own count); `newer` memory operations were issued
-    behind the load of its count."""
-    l_spin, l_ok = e.label("spin"), e.label("counted")
+    behind the load of its count.  At most S_POLLS polls (seconds): a tile waits for running workgroups only and never needs so many, but a
+    launch has to end whatever happens, and not with wrong sums unnoticed (gen_give_up)."""
+    l_spin, l_ok, l_give_up = e.label("spin"), e.label("counted"), e.label("giveup")
+    e.give_ups.append((l_give_up, l_ok))
     need = S_CNT
     if ahead:
         need = T_INC
@@ -167,7 +174,7 @@ def flag_wait(e, newer, ahead=0):
         e.raw(f"v_readfirstlane_b32 {sr(T_MT)}, {vr(FLG)}")
         e.raw(f"s_cmp_ge_i32 {sr(T_MT)}, {sr(need)}")
         e.raw(f"s_cbranch_scc1 {l_ok}")
-    e.raw(f"s_mov_b32 {sr(T_X)}, {SPINS}")
+    e.raw(f"s_mov_b32 {sr(T_X)}, {sr(S_POLLS)}")
     e.raw(l_spin + ":")
     flag_load(e)
     e.raw("s_waitcnt vmcnt(0)")
@@ -178,7 +185,29 @@ def flag_wait(e, newer, ahead=0):
     e.raw(f"s_sub_u32 {sr(T_X)}, {sr(T_X)}, 1")
     e.raw(f"s_cmp_lg_u32 {sr(T_X)}, 0")
     e.raw(f"s_cbranch_scc1 {l_spin}")
+    e.raw(f"s_branch {l_give_up}")
     e.raw(l_ok + ":")
+
+
+def gen_give_up(e, label, l_back):
+    """A wait that has used up its polls, out of line: from here on this wavefront takes every pair for counted, and the launch is marked
+    as one without gradients (add_pairs_kernel writes NaN).  So a launch waits that long once a wavefront, not once a pair.  Leaves
+    no memory operation under way, as the last poll does; the waits behind it count later ones only."""
+    e.raw(label + ":")
+    e.raw(f"s_add_u32 {sr(T_X)}, {sr(S_LDS)}, {PBLK + 256 * 32}")
+    e.raw(f"v_mov_b32 {vr(TMP)}, {sr(T_X)}")
+    e.raw(f"ds_read_b64 {vr(TMP, 2)}, {vr(TMP)} offset:{4 * U_PLENTY}")
+    e.raw("s_waitcnt lgkmcnt(0)")
+    for i in range(2):
+        e.raw(f"v_readfirstlane_b32 {sr(S_PRED + i)}, {vr(TMP + i)}")
+    e.raw(f"v_mov_b32 {vr(TMP + 1)}, 1")
+    e.raw(f"v_mov_b32 {vr(TMP + 2)}, 0")
+    e.raw("s_nop 4")                                   # a scalar written by a vector instruction, as the address of a store
+    e.raw("s_mov_b64 exec, 1")
+    e.raw(f"global_store_dword {vr(TMP + 2)}, {vr(TMP + 1)}, {sr(S_PRED, 2)} offset:{GAVE_UP}")
+    e.raw("s_mov_b64 exec, -1")
+    e.raw("s_waitcnt vmcnt(0)")
+    e.raw(f"s_branch {l_back}")
 
 
 def flag_store(e):
@@ -821,8 +850,9 @@ def generate():
     for buf in range(2):
         e.raw(l_tail[buf] + ":")
         gen_tail(e, buf)
-        if buf == 0:
-            e.raw(f"s_branch {l_done}")
+        e.raw(f"s_branch {l_done}")
+    for l_give_up, l_back in e.give_ups:
+        gen_give_up(e, l_give_up, l_back)
     e.raw(l_done + ":")
     e.comment("---- what the epilogue needs, from LDS")
     e.raw(f"s_add_u32 {sr(T_X)}, {sr(S_LDS)}, {PBLK + 256 * 32}")

@@ -172,6 +172,7 @@ struct BwdArgs {
   int32_t kv_same;     // shares of every tile where all have the same number (then nothing is looked up), else 0; set by the launcher
   int32_t pair;        // 1: both passes in one launch, where the hand-scheduled kernels take both
   int32_t one_heads;   // > 0: all gradients in one walk (see OneRoom), batches of so many KV heads; parts is its room
+  int32_t one_polls;   // most polls of a wait there; set by the launcher
   float *parts, *kv_parts;   // of launches that run one after the other they may be the same memory
   // dK / dV work of a chunk's last visit folded into the launch (bf16 path): the hand-scheduled kernel's epilogue does it,
   // beside the general kernel the launcher runs fill and cast launches
@@ -210,16 +211,17 @@ __host__ __device__ inline float* f32_kv_part(float* parts, const Shape& s, int 
 // same memory channels)
 __host__ __device__ inline int64_t kv_slot_floats(const Shape& s) { return (int64_t)2 * kDkvFastKeys * s.D + 17 * 64; }
 // Room of a backward in one walk (gen_bwd_one_asm.py), byte offsets: what hands out the tiles (tickets of 16 XCDs and the next batch, 128
-// bytes apart, claims), a count that is never too low, the tiles' counts (one per wavefront), a pair of zeros, and the pairs of each
-// (KV head, batch entry) in the order of the walk behind two that do not exist.
+// bytes apart, claims), a count that is never too low, a word that is set when a wait gives up, the tiles' counts (one per wavefront), a
+// pair of zeros, and the pairs of each (KV head, batch entry) in the order of the walk behind two that do not exist.
 __host__ __device__ constexpr int one_pair_bytes(int d) { return 32 * d * 4; }
 struct OneRoom {
-  int64_t plenty, claims, counts, zeros, pairs, group_bytes, bytes;
+  int64_t plenty, gave_up, claims, counts, zeros, pairs, group_bytes, bytes;
   int32_t claims_each, tiles;
   __host__ __device__ OneRoom(const Shape& s, int n_chunks, int heads) {
     const int64_t groups = (int64_t)s.B * s.Hkv, blocks = (s.Sq + 31) / 32;
     tiles = (s.Sk + kDkvFastKeys - 1) / kDkvFastKeys * n_chunks;
     plenty = 17 * 128;
+    gave_up = plenty + 64;                             // (GAVE_UP in gen_bwd_one_asm.py)
     claims = 18 * 128;
     claims_each = (int32_t)((groups / heads + 256 + 31) / 32 * 32);      // (a workgroup that finds no batch left has taken a ticket too)
     counts = claims + (int64_t)16 * claims_each * 4;
@@ -258,6 +260,7 @@ struct Knobs {
   int dq_fast = 1;     // 0: the dQ pass stays in the general kernel
   int dkv_fast = 1;    // 0: the dK/dV pass stays in the general kernel
   int dkv_queue = 1;   // 0: every dK/dV key tile is a workgroup of its own (no tile queue)
+  int one_polls = 1 << 21;   // ring backward in one walk: most polls of a wait (about a microsecond each)
   int one_walk = 1;    // ring backward, all gradients in one walk: 0 never, 1 where it is the faster plan, 2 wherever the kernel takes it
   int fwd_wq = 32;     // general forward without the fast path: queries per wavefront (32 or 64)
   int fwd_pipe = 1;    // general forward without the fast path, head size 128: the pipelined variant

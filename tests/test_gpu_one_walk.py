@@ -124,6 +124,32 @@ def test_one_walk_in_a_graph(D):
             step()
 
 
+@pytest.mark.gpu
+@pytest.mark.parametrize("D", [128, 64])
+def test_a_wait_that_gives_up_is_not_silent(D):
+    """With a single poll a wait, tiles go on before the one ahead of them has counted a pair.  The launch ends, its gradients are NaN, all
+    of them, and the next one in the same workspace is right."""
+    print(f"[one walk] waits of one poll, D={D}", flush=True)
+    w, inp, koffs = _share((1, 8, 8, 256, 256, 8, 2048, (0, 0), True), D)
+    q, ks, vs, d_o = upload(inp)
+    args, order = (w.q_where, koffs, True, w.scale), list(range(8))
+    with launcher_switch("one_walk", 2, 1):
+        o, lse, low = st.st_ring_fwd(q, ks, vs, *args, order)
+        ws = torch.empty(st.st_ring_workspace_bytes(q, ks, vs, *args, st.ST_RING_FUSED, True) + 256, dtype=torch.uint8, device="cuda")
+
+        def step():
+            dq, dk, dv = torch.zeros_like(o), [torch.zeros(k.shape, device="cuda") for k in ks], [torch.zeros(k.shape, device="cuda") for k in ks]
+            dkl, dvl = ([torch.zeros_like(k) for k in ks] for _ in range(2))
+            st.st_ring_bwd_last(q, ks, vs, d_o, low, lse, *args, order, dq, dk, dv, assign=True, dk_lowp=dkl, dv_lowp=dvl, workspace=ws)
+            torch.cuda.synchronize()
+            return [dq, *dk, *dv, *dkl, *dvl]
+
+        want = step()
+        with launcher_switch("one_polls", 1, 1 << 21):
+            assert all(x.isnan().all() for x in step())
+        assert not any(x.isnan().any() for x in want) and all(torch.equal(x, y) for x, y in zip(step(), want))
+
+
 def test_where_one_walk_is_planned():
     """By the work of the longest chain: not where an XCD has no head, nor for few tiles, nor for chunks that overlap, tiles of fewer
     keys than the loop takes, or more sums than there is room for."""
