@@ -503,24 +503,31 @@ void f32_bwd_split(BwdSplit& r, const st::Shape& s, const QueryWalk& walk, const
 // without a head, or with one less than the others, idles: 4 x 4 heads x 2048 679, 1109.  Head size 64, where a tile runs three blocks
 // behind the one before: 8 heads x 1024 80, 134; x 2048 230, 251; x 4096 790, 650; 32 heads x 512 96, 83; x 1024 243, 198; x 4096 2867,
 // 2506; 24 heads x 2048 625, 495; 12 heads x 2048 331, 341; 8 x 4 heads x 1024 208, 235; x 2048 751, 664; 4 x 4 heads x 2048 381, 576.
-double one_walk_us(const st::Shape& s, const KeyWalk& keys, int batch) {
+// What cannot come to less than less_us is given up as soon as that shows.  Every call of a ring backward plans, and it may have 50 us of
+// work: the 512 jobs of 32 heads x 2048 rows x 16 chunks took 45 us as a search over 32 slots each, twice; so 2.
+double one_walk_us(const st::Shape& s, const KeyWalk& keys, int batch, double less_us) {
   const int64_t rounds = (keys.heads / batch + 7) / 8;
   const double busy = (double)std::min<int64_t>(keys.heads, 8) / 8 * std::min(1.0, (double)keys.seen * rounds * batch / 32);
   const bool wide = s.D == 128;
   const double step = wide ? 1.5 + 0.45 * busy : 0.9 + 0.1 * busy, fixed = wide ? 20 : 12, unseen = 10, behind = wide ? step : 3 * step;
   const double around = 10 + (double)s.B * s.Hq * s.Sq * s.D * 12 / 5.5e6;      // the counts' start values, the pass that adds to dq
-  if (rounds * batch * keys.tiles > 512) {             // by the work alone
-    double us = 0;
-    for (int i = 0; i < keys.n; ++i) us += keys.c[i].tiles * (keys.c[i].blocks > 0 ? fixed + keys.c[i].blocks * keys.G * step : unseen);
-    return around + us * rounds * batch / 32 + 31.0 / batch * behind;
-  }
+  double us = 0;
+  for (int i = 0; i < keys.n; ++i) us += keys.c[i].tiles * (keys.c[i].blocks > 0 ? fixed + keys.c[i].blocks * keys.G * step : unseen);
+  const double even = around + us * rounds * batch / 32;
+  if (rounds * batch * keys.tiles > 512) return even + 31.0 / batch * behind;   // by the work alone
+  if (even >= less_us) return even;
+  // when the workgroups are free, rising, in a ring; the one that is free first takes a tile and falls back to where it ends.  A batch
+  // that divides them moves in step: one of its heads stands for all.
+  const bool in_step = 32 % batch == 0;
+  const int m = in_step ? 32 / batch : 32, heads = in_step ? 1 : batch;
   double free[32] = {}, end = 0;
+  int first = 0;
   for (int64_t r = 0; r < rounds; ++r) {
     double before[8] = {};
     for (int i = 0; i < keys.n; ++i)                    // most blocks first, as the tiles lie
       for (int t = 0; t < keys.c[i].tiles; ++t)
-        for (int h = 0; h < batch; ++h) {
-          double& at = *std::min_element(free, free + 32);
+        for (int h = 0; h < heads; ++h) {
+          double at = free[first];
           if (keys.c[i].blocks == 0) {
             at += unseen;
           } else {
@@ -529,14 +536,19 @@ double one_walk_us(const st::Shape& s, const KeyWalk& keys, int batch) {
             at = start + keys.c[i].blocks * keys.G * step + fixed / 2;
           }
           end = std::max(end, at);
+          int slot = first;
+          first = first + 1 < m ? first + 1 : 0;
+          for (int ahead; slot != first && free[ahead = slot > 0 ? slot - 1 : m - 1] > at; slot = ahead) free[slot] = free[ahead];
+          free[slot] = at;
         }
+    if (around + end >= less_us) break;
   }
   return around + end;
 }
 // heads of a batch, 0: two passes
 int one_walk(const st::Shape& s, const KeyWalk& keys, const int64_t* k_offset, int n, size_t room, double less_us) {
-  if (s.Sk % st::kDkvFastKeys != 0 || keys.seen < 1) return 0;
-  if (st::knobs().one_walk != 1) less_us = st::knobs().one_walk ? 1e30 : 0;
+  if (s.Sk % st::kDkvFastKeys != 0 || keys.seen < 1 || st::knobs().one_walk == 0) return 0;
+  if (st::knobs().one_walk != 1) less_us = 1e30;
   if (s.causal && k_offset != nullptr)
     for (int c = 1; c < n; ++c)                        // a tile sees the blocks of the ones behind it
       if (k_offset[c] < k_offset[c - 1] + s.Sk - st::kDkvFastKeys) return 0;
@@ -544,7 +556,7 @@ int one_walk(const st::Shape& s, const KeyWalk& keys, const int64_t* k_offset, i
   const int64_t per_xcd = (keys.heads + 7) / 8;
   for (const int batch : {1, keys.heads % per_xcd == 0 && per_xcd <= 8 ? (int)per_xcd : 1}) {
     if (batch == best || (size_t)st::OneRoom(s, n, batch).bytes > room) continue;
-    const double us = one_walk_us(s, keys, batch);
+    const double us = one_walk_us(s, keys, batch, less_us);
     if (us >= less_us) continue;
     less_us = us;
     best = batch;
@@ -555,7 +567,8 @@ int one_walk(const st::Shape& s, const KeyWalk& keys, const int64_t* k_offset, i
 // meanwhile, and the launch ends with the last of them (jobs_us, key tiles first).  Forward and backward, apart and together:
 // 4 heads x 700 rows x 4 chunks 99 and 77 us, 12 heads of 64 x 800 rows x 4 chunks 96 and 88 us, 6 heads x 1500 rows x 4
 // chunks 146 and 116 us.
-BwdSplit bwd_splits(const st::Shape& s, int dtype, const int64_t* k_offset, int n, size_t room, bool split_dq = true) {
+// `known`: for a caller who asks for the bytes only and has as many already (a plan with no more is any that has no more).
+BwdSplit bwd_splits(const st::Shape& s, int dtype, const int64_t* k_offset, int n, size_t room, bool split_dq = true, size_t known = 0) {
   const bool ring_call = split_dq;
   BwdSplit r;
   const bool bf16 = dtype == ST_BF16;
@@ -611,6 +624,7 @@ BwdSplit bwd_splits(const st::Shape& s, int dtype, const int64_t* k_offset, int 
   // says 0.87 of what they take (a walk of some hundred blocks on a full chip runs at the power limit).  Head size 64, 81 shares: right to
   // 8 %, the passes' 1.1 of what short ones take; at this bar none of them lost, and three that would have gained 3 to 8 % stay with them
   auto or_one = [&](const BwdSplit& two, double us) {
+    if (two.bytes <= known && (size_t)st::OneRoom(s, n, 1).bytes <= known) return two;      // (larger batches need less)
     const int heads = ring_call ? one_walk(s, keys, k_offset, n, one_room, (s.D == 128 ? 1.07 : 0.87) * us) : 0;
     if (heads == 0) return two;
     BwdSplit one;
@@ -1152,14 +1166,18 @@ static size_t ring_room(const st_ring_desc* d, size_t workspace_bytes) {
 // Partial sums to provide for.  Under a causal mask the plan depends on where the chunks lie: as a caller visits them who lists
 // all of them, in one launch or a launch each, and where every row sees them, so that what was sized for one shard does for
 // its neighbours.  Without one it depends on their number, and any subset may be visited.
-static size_t ring_parts_bytes(const st_ring_desc* d, int mode) {
+// `enough`: what more than that is not of interest.
+static size_t ring_parts_bytes(const st_ring_desc* d, int mode, size_t enough = SIZE_MAX) {
   const st::Shape s = shape_of(d);
   const bool fused = mode == ST_RING_FUSED;
   const int n_chunks = std::min(d->n_chunks, ST_MAX_CHUNKS), per_launch = std::min(n_chunks, fused ? st::kMaxTable : 1);
   size_t most = 0;
-  auto look = [&](const int64_t* k_offset, int n) { most = std::max(most, bwd_splits(s, d->dtype, k_offset, n, room_most(d)).bytes); };
+  auto look = [&](const int64_t* k_offset, int n) {
+    if (most < enough) most = std::max(most, bwd_splits(s, d->dtype, k_offset, n, room_most(d), true, most).bytes);
+  };
   if (!d->causal || d->k_offset == nullptr) {
-    for (int n = 1; n <= per_launch; ++n) look(nullptr, n);
+    look(nullptr, per_launch);                         // the sums of one walk grow with the chunks; the plans of few are made quickly
+    for (int n = 1; n < per_launch; ++n) look(nullptr, n);
     return most;
   }
   look(nullptr, per_launch);
@@ -1205,7 +1223,7 @@ struct RingVisit {
 static BwdSplit ring_plan(const st_ring_desc* d, int mode, const int64_t* k_offset, int n, bool provided, size_t room) {
   const st::Shape s = shape_of(d);
   BwdSplit r = bwd_splits(s, d->dtype, k_offset, n, room_most(d));
-  if (!provided && r.bytes > 0) room = std::min(room, ring_parts_bytes(d, mode));
+  if (!provided && r.bytes > 0) room = std::min(room, ring_parts_bytes(d, mode, r.bytes));
   return r.bytes <= room ? r : bwd_splits(s, d->dtype, k_offset, n, room);
 }
 

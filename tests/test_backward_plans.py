@@ -3,6 +3,7 @@ st_ring_bwd_noalloc promise the same bits, so both have to make the same plan, f
 and what the plan stores has to fit what was asked for, which is no more than some plan of the share can use."""
 import ctypes as C
 import random
+import time
 
 import pytest
 
@@ -151,3 +152,23 @@ def test_block_backwards():
             assert causal or size - base == max(x[-1] for x in best), share.text
     assert _block_size(_ring(BF16, 1, 2, 2, 128, 320, 2, 1), 0) <= 8 << 20
     assert _block_size(_ring(BF16, 2, 16, 16, 64, 512, 8, 5), 0) <= 4 << 20
+
+
+def test_what_a_plan_costs():
+    """Every call plans, and the backwards below are some 80 to 625 us of GPU work.  Sizing them took 0.7 to 1.7 ms, planning two chunks of
+    a causal ring 0.15 ms, while the model of the one walk was simulated job by job for every number of chunks; now 40 to 110 us
+    and 10.  The bounds lie between, for the best of several runs."""
+    def best(f):
+        times = []
+        for _ in range(12):
+            start = time.perf_counter()
+            f()
+            times.append(time.perf_counter() - start)
+        return min(times) * 1e6
+
+    for heads, D, S in ((32, 128, 512), (32, 64, 256), (64, 128, 256), (24, 64, 512)):
+        share = _ring(BF16, 1, heads, heads, D, S, 64, 3, False)
+        assert best(lambda: share.size(FUSED)) < 400, share.text
+    for share in (_ring(BF16, 1, 32, 32, 128, 1024, 32, 31), _ring(BF16, 1, 32, 32, 128, 2048, 16, 15)):
+        assert best(lambda: share.plan([3, 7], FUSED, True, -1)) < 60, share.text
+        assert best(lambda: share.size(FUSED)) < 70, share.text
