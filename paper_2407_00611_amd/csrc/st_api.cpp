@@ -567,9 +567,9 @@ int one_walk(const st::Shape& s, const KeyWalk& keys, const int64_t* k_offset, i
 // meanwhile, and the launch ends with the last of them (jobs_us, key tiles first).  Forward and backward, apart and together:
 // 4 heads x 700 rows x 4 chunks 99 and 77 us, 12 heads of 64 x 800 rows x 4 chunks 96 and 88 us, 6 heads x 1500 rows x 4
 // chunks 146 and 116 us.
-// `known`: for a caller who asks for the bytes only and has as many already (a plan with no more is any that has no more).
-BwdSplit bwd_splits(const st::Shape& s, int dtype, const int64_t* k_offset, int n, size_t room, bool split_dq = true, size_t known = 0) {
-  const bool ring_call = split_dq;
+// `one`: the one walk may be taken.  `known`: for a caller who asks for the bytes only and has as many already (a plan with no more is
+// any that has no more).
+BwdSplit bwd_splits(const st::Shape& s, int dtype, const int64_t* k_offset, int n, size_t room, bool split_dq, bool one = false, size_t known = 0) {
   BwdSplit r;
   const bool bf16 = dtype == ST_BF16;
   const size_t one_room = room;
@@ -625,7 +625,7 @@ BwdSplit bwd_splits(const st::Shape& s, int dtype, const int64_t* k_offset, int 
   // 8 %, the passes' 1.1 of what short ones take; at this bar none of them lost, and three that would have gained 3 to 8 % stay with them
   auto or_one = [&](const BwdSplit& two, double us) {
     if (two.bytes <= known && (size_t)st::OneRoom(s, n, 1).bytes <= known) return two;      // (larger batches need less)
-    const int heads = ring_call ? one_walk(s, keys, k_offset, n, one_room, (s.D == 128 ? 1.07 : 0.87) * us) : 0;
+    const int heads = one ? one_walk(s, keys, k_offset, n, one_room, (s.D == 128 ? 1.07 : 0.87) * us) : 0;
     if (heads == 0) return two;
     BwdSplit one;
     one.one_heads = heads;
@@ -1163,6 +1163,11 @@ static size_t ring_room(const st_ring_desc* d, size_t workspace_bytes) {
   return workspace_bytes > base ? std::min(workspace_bytes - base, room_most(d)) : 0;
 }
 
+// Whether the one walk takes this share's K and V rows: as far as the descriptor tells (the launcher has the last word, one_fast_usable)
+static bool one_strides(const st_ring_desc* d) {
+  return std::max(d->k_stride_s, d->v_stride_s) < ((int64_t)1 << 30) / (2 * st::kDkvFastKeys);
+}
+
 // Partial sums to provide for.  Under a causal mask the plan depends on where the chunks lie: as a caller visits them who lists
 // all of them, in one launch or a launch each, and where every row sees them, so that what was sized for one shard does for
 // its neighbours.  Without one it depends on their number, and any subset may be visited.
@@ -1173,7 +1178,7 @@ static size_t ring_parts_bytes(const st_ring_desc* d, int mode, size_t enough = 
   const int n_chunks = std::min(d->n_chunks, ST_MAX_CHUNKS), per_launch = std::min(n_chunks, fused ? st::kMaxTable : 1);
   size_t most = 0;
   auto look = [&](const int64_t* k_offset, int n) {
-    if (most < enough) most = std::max(most, bwd_splits(s, d->dtype, k_offset, n, room_most(d), true, most).bytes);
+    if (most < enough) most = std::max(most, bwd_splits(s, d->dtype, k_offset, n, room_most(d), true, one_strides(d), most).bytes);
   };
   if (!d->causal || d->k_offset == nullptr) {
     look(nullptr, per_launch);                         // the sums of one walk grow with the chunks; the plans of few are made quickly
@@ -1219,12 +1224,14 @@ struct RingVisit {
 };
 
 // The plan of a launch over n chunks.  It does not depend on the room beyond what st_ring_workspace_bytes provides for, so that
-// st_ring_bwd with that much and st_ring_bwd_noalloc compute the same sums; with less it is the best one that fits.
-static BwdSplit ring_plan(const st_ring_desc* d, int mode, const int64_t* k_offset, int n, bool provided, size_t room) {
+// st_ring_bwd with that much and st_ring_bwd_noalloc compute the same sums; with less it is the best one that fits.  `one`: the one walk
+// takes these tensors.
+static BwdSplit ring_plan(const st_ring_desc* d, int mode, const int64_t* k_offset, int n, bool provided, size_t room, bool one) {
   const st::Shape s = shape_of(d);
-  BwdSplit r = bwd_splits(s, d->dtype, k_offset, n, room_most(d));
+  BwdSplit r = bwd_splits(s, d->dtype, k_offset, n, room_most(d), true, one);
+  provided = provided && one == one_strides(d);
   if (!provided && r.bytes > 0) room = std::min(room, ring_parts_bytes(d, mode, r.bytes));
-  return r.bytes <= room ? r : bwd_splits(s, d->dtype, k_offset, n, room);
+  return r.bytes <= room ? r : bwd_splits(s, d->dtype, k_offset, n, room, true, one);
 }
 
 size_t st_ring_workspace_bytes(const st_ring_desc* d, int32_t mode, int32_t backward) {
@@ -1495,6 +1502,9 @@ static st_status ring_bwd(const st_ring_desc* d, const st_tensor* q, const st_te
   a.queue = (int32_t*)((char*)workspace + align_up((size_t)d->B * d->Sq * d->Hq * sizeof(float), 256));
   const int per_launch = mode == ST_RING_FUSED ? st::kMaxTable : 1;
   const bool provided = vis.provided(d, mode);
+  void* const qs = (char*)a.queue + align_up(st::kQueueInts * sizeof(int32_t), 256);
+  a.qs = d->dtype == ST_BF16 ? qs : nullptr;
+  const bool one = d->dtype == ST_BF16 && one_strides(d) && st::one_fast_usable(a);
   for (int x0 = 0; x0 == 0 || x0 < vis.n; x0 += per_launch) {
     const int cnt = std::min(vis.n - x0, per_launch);
     a.t.n = cnt;
@@ -1506,13 +1516,11 @@ static st_status ring_bwd(const st_ring_desc* d, const st_tensor* q, const st_te
       a.dk_lowp[x] = dk_lowp ? dk_lowp[j] : nullptr;
       a.dv_lowp[x] = dk_lowp ? dv_lowp[j] : nullptr;
     }
-    if (cnt > 0) set_splits(a, ring_plan(d, mode, a.t.k_offset, cnt, provided, parts_bytes), parts);
+    if (cnt > 0) set_splits(a, ring_plan(d, mode, a.t.k_offset, cnt, provided, parts_bytes, one), parts);
     if (x0 == 0) {
       if (d->dtype == ST_BF16) {
-        void* qs = (char*)a.queue + align_up(st::kQueueInts * sizeof(int32_t), 256);
         const st::OneReset reset = a.one_heads > 0 ? st::one_reset(a.parts, a.s, cnt, a.one_heads) : st::OneReset();
         ST_HIP(st::launch_bwd_prep(a.d_o, view_of(o), o_dtype, a.q, delta, qs, a.queue, reset, d->B, d->Sq, d->Hq, d->D, d->scale, stream), "backward preparation launch");
-        a.qs = qs;
       } else {
         ST_HIP(st::launch_delta(a.d_o, d->dtype, view_of(o), o_dtype, delta, d->B, d->Sq, d->Hq, d->D, stream), "delta launch");
       }
@@ -1543,7 +1551,7 @@ extern "C" int st_testing_bwd_plan(const st_ring_desc* d, const int32_t* order, 
     int64_t k_offset[st::kMaxTable];
     const int cnt = std::min(vis.n - x0, per_launch);
     for (int x = 0; x < cnt; ++x) k_offset[x] = d->k_offset[vis.chunk[x0 + x]];
-    const BwdSplit p = mode < 0 ? block_plan(shape_of(d), d->dtype, k_offset[0], room) : ring_plan(d, mode, k_offset, cnt, vis.provided(d, mode), room);
+    const BwdSplit p = mode < 0 ? block_plan(shape_of(d), d->dtype, k_offset[0], room) : ring_plan(d, mode, k_offset, cnt, vis.provided(d, mode), room, one_strides(d));
     const int64_t v[] = {cnt, p.dq.n, p.dq.total, p.dq.own0, (int64_t)p.dq.less1[0], (int64_t)p.dq.less1[1], (int64_t)p.dq.less1[2],
                          (int64_t)p.dq.less1[3], p.kv_each, p.one_heads > 0 ? -p.one_heads : p.kv_items, p.pair, (int64_t)p.bytes};
     for (int64_t y : v) {

@@ -469,7 +469,7 @@ hipError_t launch_bwd_bf16(const BwdArgs& a_in, hipStream_t stream) {
         a.kv_assign = (a.kv_assign & ~((1ull << j) | (1ull << (j - 1)))) | (bi << j) | (bj << (j - 1));
       }
   }
-  if (a.one_heads > 0 && dkv_fast && knobs().dq_fast && one_fast_usable(a)) return launch_bwd_one_fast(a, stream);
+  if (a.one_heads > 0 && one_fast_usable(a)) return launch_bwd_one_fast(a, stream);
   // the dK/dV loop is the faster one from the first block on
   const bool few = a.shares.n <= 1 && dq_few(a.s, a.t.n);
   const bool dq_fast = knobs().dq_fast && !few && dq_fast_usable(a), pair = a.pair && dkv_fast && dq_fast;

@@ -8,6 +8,7 @@ import time
 import pytest
 
 from paper_2407_00611_amd import api
+from util import launcher_switch
 
 F32, BF16, STEPWISE, FUSED = 0, 1, 0, 1
 I64, I32 = C.c_int64, C.c_int32
@@ -172,3 +173,20 @@ def test_what_a_plan_costs():
     for share in (_ring(BF16, 1, 32, 32, 128, 1024, 32, 31), _ring(BF16, 1, 32, 32, 128, 2048, 16, 15)):
         assert best(lambda: share.plan([3, 7], FUSED, True, -1)) < 60, share.text
         assert best(lambda: share.size(FUSED)) < 70, share.text
+
+
+def test_shares_whose_rows_the_one_walk_does_not_take():
+    """Its loop keeps the bytes of 256 rows of K in 32 bits.  Rows further apart are planned in two passes, as well as if there were no
+    other way: split, and in a workspace of that size.  (2 x 16 heads of 64 x 512 rows x 8 chunks, batches of 4 heads otherwise.)"""
+    def share(stride):
+        s = _ring(BF16, 2, 16, 16, 64, 512, 8, 5)
+        s.d.k_stride_s = stride
+        return s
+    order = list(range(8))
+    near, far = share((1 << 21) - 1), share(1 << 21)
+    assert all(x[9] < 0 for x in near.plan(order, FUSED, True, -1))
+    with launcher_switch("one_walk", 0, 1):
+        two, size = far.plan(order, FUSED, True, -1), near.size(FUSED)
+        assert two == near.plan(order, FUSED, True, -1) and any(x[10] or x[8] > 0 for x in two)
+    assert far.plan(order, FUSED, True, -1) == two and far.size(FUSED) == size
+    _check(far, random.Random(5))
