@@ -644,10 +644,14 @@ def generate():
         e.raw(f"v_readfirstlane_b32 {sr(dst)}, {vr(src)}")
     e.raw(f"s_cmp_lg_u32 {sr(S_NRAG)}, -1")
     e.raw(f"s_cselect_b32 {sr(S_EVT)}, -1, {sr(S_DIAG)}")
+    # (keys that no row sees are copies of the last one that some row does, here and in V: P is 0 there, but 0 times what lies in memory
+    # that nobody has to have written need not be)
     e.comment("---- K tile of the workgroup (256 rows) to LDS: instruction 4 j + wave fills group 4 j + wave")
     per_load = 4 * 1024 // (2 * D)                     # rows
+    e.raw(f"s_sub_u32 {sr(T_X)}, {sr(S_ROWS)}, 1")
     for j in range(256 // per_load):
-        e.raw(f"v_mul_lo_u32 {vr(TMP)}, {vr(kv.I_SROW)}, {sr(S_VRS)}")
+        e.raw(f"v_min_u32 {vr(TMP)}, {sr(T_X)}, {vr(kv.I_SROW)}")
+        e.raw(f"v_mul_lo_u32 {vr(TMP)}, {vr(TMP)}, {sr(S_VRS)}")
         e.raw(f"v_add_u32 {vr(TMP)}, {vr(TMP)}, {vr(kv.I_VCOL)}")
         e.raw(f"s_add_u32 m0, {sr(T_M0)}, {KT + 4 * GRP * j}")
         e.raw("s_nop 0")
@@ -662,8 +666,10 @@ def generate():
         e.raw(f"v_lshlrev_b32 {vr(TMP)}, 4, {vr(TMP)}")
         e.raw(f"s_lshl_b32 {sr(T_X)}, {sr(S_WAVE)}, 6")
         e.raw(f"v_add_u32 {vr(TMP + 1)}, {sr(T_X)}, {vr(TMP + 1)}")
+        e.raw(f"s_sub_u32 {sr(T_X)}, {sr(S_ROWS)}, 1")
         for nb in range(NKB):
-            e.raw(f"v_mul_lo_u32 {vr(TMP + 2)}, {vr(TMP + 1)}, {sr(S_VRS)}")
+            e.raw(f"v_min_u32 {vr(TMP + 2)}, {sr(T_X)}, {vr(TMP + 1)}")
+            e.raw(f"v_mul_lo_u32 {vr(TMP + 2)}, {vr(TMP + 2)}, {sr(S_VRS)}")
             e.raw(f"v_add_u32 {vr(TMP + 2)}, {vr(TMP + 2)}, {vr(TMP)}")
             for ks in range(KS):
                 e.raw(f"global_load_dwordx4 {vr(KR(nb, ks), 4)}, {vr(TMP + 2)}, {sr(T_VPTR, 2)} offset:{32 * ks}")

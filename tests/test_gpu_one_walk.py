@@ -150,6 +150,39 @@ def test_a_wait_that_gives_up_is_not_silent(D):
         assert not any(x.isnan().any() for x in want) and all(torch.equal(x, y) for x, y in zip(step(), want))
 
 
+@pytest.mark.gpu
+@pytest.mark.parametrize("D", [128, 64])
+@pytest.mark.parametrize("Sq,q0,n", [(64, 0, 1), (128, 256, 3), (192, 256, 2)])
+def test_keys_that_no_row_sees_may_hold_anything(Sq, q0, n, D):
+    """A key tile meets 256 keys, seen or not, and 0 times a NaN is one: what lies behind the last key that a row sees (here at the
+    end of a 64-key tile, where the forward ends) must not reach dQ, as it does not in two passes.  Bit for bit what finite keys give."""
+    print(f"[one walk] keys nobody sees, {Sq} rows at {q0}, {n} chunks, D={D}", flush=True)
+    w, inp, koffs = _share((1, 4, 2, Sq, 256, n, q0, (0, 0), True), D)
+    q, ks, vs, d_o = upload(inp)
+    args, order = (w.q_where, koffs, True, w.scale), list(range(n))
+    o, lse, low = st.st_ring_fwd(q, ks, vs, *args, order)
+
+    def grads(ks, vs):
+        dq, dk, dv = torch.zeros_like(o), [torch.zeros(k.shape, device="cuda") for k in ks], [torch.zeros(k.shape, device="cuda") for k in ks]
+        st.st_profile_begin()
+        try:
+            st.st_ring_bwd(q, ks, vs, d_o, low, lse, *args, order, dq, dk, dv)
+        finally:
+            ran = st.st_profile_end()
+        assert "bwd_one_bf16" in ran
+        return [dq, *dk, *dv]
+
+    with launcher_switch("one_walk", 2, 1):
+        want = grads(ks, vs)
+        for bad in (float("nan"), float("inf")):
+            other = [[x.clone() for x in xs] for xs in (ks, vs)]
+            for xs in other:
+                for j, x in enumerate(xs):
+                    x[:, max(q0 + Sq - koffs[j], 0):] = bad
+            assert any((x != y).any() for x, y in zip(other[0], ks))
+            assert all(torch.equal(x, y) for x, y in zip(grads(*other), want))
+
+
 def test_where_one_walk_is_planned():
     """By the work of the longest chain: not where an XCD has no head, nor for few tiles, nor for chunks that overlap, tiles of fewer
     keys than the loop takes, or more sums than there is room for."""
