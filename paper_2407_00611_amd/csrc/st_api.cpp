@@ -554,7 +554,9 @@ int one_walk(const st::Shape& s, const KeyWalk& keys, const int64_t* k_offset, i
       if (k_offset[c] < k_offset[c - 1] + s.Sk - st::kDkvFastKeys) return 0;
   int best = 0;
   const int64_t per_xcd = (keys.heads + 7) / 8;
-  for (const int batch : {1, keys.heads % per_xcd == 0 && per_xcd <= 8 ? (int)per_xcd : 1}) {
+  const int all = keys.heads % per_xcd == 0 && per_xcd <= 8 ? (int)per_xcd : 1, set = st::knobs().one_heads;
+  const bool forced = set > 0 && keys.heads % set == 0;
+  for (const int batch : {forced ? set : 1, forced ? set : all}) {
     if (batch == best || (size_t)st::OneRoom(s, n, batch).bytes > room) continue;
     const double us = one_walk_us(s, keys, batch, less_us);
     if (us >= less_us) continue;

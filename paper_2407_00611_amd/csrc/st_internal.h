@@ -262,6 +262,7 @@ struct Knobs {
   int dkv_queue = 1;   // 0: every dK/dV key tile is a workgroup of its own (no tile queue)
   int one_polls = 1 << 21;   // ring backward in one walk: most polls of a wait (about a microsecond each)
   int one_walk = 1;    // ring backward, all gradients in one walk: 0 never, 1 where it is the faster plan, 2 wherever the kernel takes it
+  int one_heads = 0;   // KV heads of its batches: 0 as planned, 1 .. 8 so many where they divide the heads
   int fwd_wq = 32;     // general forward without the fast path: queries per wavefront (32 or 64)
   int fwd_pipe = 1;    // general forward without the fast path, head size 128: the pipelined variant
   float fwd_gap = 8.f; // fast forward: log2 units every block maximum may exceed the lazy exponent reference by (0 .. 64)

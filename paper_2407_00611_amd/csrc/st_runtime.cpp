@@ -108,6 +108,7 @@ extern "C" int st_testing_set(const char* name, double value) {
   else if (!strcmp(name, "dkv_fast")) k.dkv_fast = v;
   else if (!strcmp(name, "dkv_queue")) k.dkv_queue = v;
   else if (!strcmp(name, "one_walk")) k.one_walk = v;
+  else if (!strcmp(name, "one_heads") && v >= 0 && v <= 8) k.one_heads = v;
   else if (!strcmp(name, "one_polls") && v >= 1) k.one_polls = v;
   else if (!strcmp(name, "fwd_wq") && (v == 32 || v == 64)) k.fwd_wq = v;
   else if (!strcmp(name, "fwd_pipe")) k.fwd_pipe = v;

@@ -12,6 +12,7 @@ extern "C" {
  *   "fwd_fast", "dq_fast", "dkv_fast"   0 keeps that pass entirely in the general kernels
  *   "dkv_queue"                         0 gives every dK/dV key tile a workgroup of its own
  *   "one_walk"                          0 keeps every ring backward in its two passes, 2 takes the one walk wherever it can
+ *   "one_heads" (0 .. 8)                KV heads of a batch of the one walk, where they divide the heads (0: as planned)
  *   "one_polls" (1 ..)                  polls after which a wait of the one walk gives up (then every gradient is NaN)
  *   "fwd_wq" (32 | 64), "fwd_pipe"      variant of the general forward kernel
  *   "fwd_gap" (0 .. 64)                 log2 units a block maximum may exceed the lazy exponent reference by

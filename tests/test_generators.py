@@ -15,6 +15,7 @@ GENERATORS = [
     ("gen_fwd_asm.py", "ST_FWD_FAST", range(224, 240), range(32, 47)),
     ("gen_bwd_dq_asm.py", "ST_DQ_FAST", range(160, 180), range(32, 44)),
     ("gen_bwd_dkv_asm.py", "ST_DKV_FAST", range(176, 192), list(range(32, 64))),
+    ("gen_bwd_one_asm.py", "ST_ONE_FAST", range(176, 192), list(range(32, 64))),
 ]
 CASES = [(g, d) for g in GENERATORS for d in (128, 64)]
 
@@ -77,4 +78,6 @@ def test_head_sizes_differ_where_they_should():
         big, small = _run(script, 128), _run(script, 64)
         n = lambda t: t.count("v_mfma_f32_32x32x16_bf16")
         assert n(big) > n(small) > 0
+        # in one walk head size 64 makes dQ in 16 columns a wavefront; nothing else uses that shape
+        assert big.count("v_mfma_f32_16x16x32_bf16") == 0 and (small.count("v_mfma_f32_16x16x32_bf16") > 0) == (script == "gen_bwd_one_asm.py")
         assert "_FAST64_" in small and "_FAST64_" not in big

@@ -89,6 +89,98 @@ def test_all_gradients_in_one_walk(c, D):
         check(*less, "two passes")
 
 
+#          heads of a batch; B, Hq, Hkv, Sq, Sk, n, q_offset, (q_seg, q_offset2), causal
+BATCHES = [(2, (1, 16, 16, 96, 256, 3, 672, (0, 0), True)),
+           (3, (2, 12, 12, 70, 256, 12, 3002, (0, 0), True)),      # 36 tiles a batch: more than an XCD has workgroups
+           (3, (1, 48, 24, 64, 512, 2, 0, (0, 0), False)),
+           (4, (2, 32, 16, 100, 256, 9, 1000, (50, 2254), True)),  # the last chunks are seen by one run, or by nobody
+           (5, (1, 5, 5, 128, 256, 2, 384, (0, 0), True)),         # one batch: seven XCDs have none
+           (8, (2, 32, 32, 64, 256, 5, 1216, (0, 0), True)),
+           (8, (1, 24, 24, 160, 256, 4, 0, (0, 0), False))]
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("D", [128, 64])
+@pytest.mark.parametrize("heads,c", BATCHES, ids=[f"{b}_of_{c[0]}x{c[2]}_n{c[5]}" for b, c in BATCHES])
+def test_batches_of_heads(heads, c, D):
+    """A ticket of an XCD is a tile of one of the heads of its batch, the heads in turn.  Which ones are walked together changes no bit;
+    the planner takes one head or all of an XCD's (3, 4 and 8 for 24, 32 and 64)."""
+    B, Hq, Hkv, Sq, Sk, n, q0, (seg, q2), causal = c
+    print(f"[one walk] batches of {heads}: {c} D={D}", flush=True)
+    w, inp, koffs = _share(c, D)
+    q, ks, vs, d_o = upload(inp)
+    order, args = list(range(n)), (w.q_where, koffs, causal, w.scale)
+    o, lse, low = st.st_ring_fwd(q, ks, vs, *args, order)
+    share = Share(BF16, B, Hq, Hkv, D, Sq, Sk, koffs, q0, causal, seg, q2)
+
+    def run():
+        dq, dk, dv = torch.zeros_like(o), [torch.empty(k.shape, device="cuda") for k in ks], [torch.empty(k.shape, device="cuda") for k in ks]
+        st.st_ring_bwd_last(q, ks, vs, d_o, low, lse, *args, order, dq, dk, dv, assign=True)
+        return dq, dk, dv
+
+    with launcher_switch("one_walk", 2, 1):
+        got = []
+        for batch in (heads, 1):
+            with launcher_switch("one_heads", batch, 0):
+                assert [x[9] for x in share.plan(order, FUSED, True, -1)] == [-batch]
+                got.append(run())
+    for a, b in zip(*[[x[0], *x[1], *x[2]] for x in got]):
+        assert torch.equal(a, b)
+    dq_r, dk_r, dv_r = oa.attention_backward(inp.q, inp.k, inp.v, inp.d_o, *positions(w), causal, w.scale)
+    assert_close_wide(host(got[0][0]), dq_r, "dq")
+    for j in range(n):
+        for name, x, ref in (("dk", got[0][1][j], dk_r[j]), ("dv", got[0][2][j], dv_r[j])):
+            if ref.any():
+                assert_close_wide(host(x), ref, f"{name}[{j}]")
+            else:
+                assert not x.any(), f"{name}[{j}]"
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("D", [128, 64])
+@pytest.mark.parametrize("causal", [True, False])
+@pytest.mark.parametrize("layout", ["k_heads_first", "v_heads_first", "k_packed", "all_heads_first"])
+def test_any_memory_layout(layout, causal, D):
+    """K lies in LDS here and V in registers, the other way round than in the dK/dV loop, and head size 64 reads K a second time: with
+    strides of K and V unlike each other, batch 2, grouped heads and (causal) the chunks in another order, the same bits as dense."""
+    print(f"[one walk] {layout}, causal {causal}, D={D}", flush=True)
+    n = 3
+    w, inp, koffs = _share((2, 6, 3, 200, 512, n, 3 * 512 - 200 if causal else 0, (0, 0), causal), D)
+    q, ks, vs, d_o = upload(inp)
+    args = (w.q_where, koffs, causal, w.scale)
+    heads_first = lambda t: t.permute(0, 2, 1, 3).contiguous().permute(0, 2, 1, 3)
+
+    def packed(t):                                                  # beside other data: rows four heads further apart
+        wide = torch.full((*t.shape[:2], t.shape[2] + 4, D), float("nan"), dtype=t.dtype, device="cuda")
+        wide[:, :, 2:-2] = t
+        return wide[:, :, 2:-2]
+
+    same = lambda t: t
+    how_q, how_k, how_v, how_do = {"k_heads_first": (same, heads_first, same, packed), "v_heads_first": (packed, same, heads_first, same),
+                                   "k_packed": (heads_first, packed, heads_first, same), "all_heads_first": (heads_first,) * 4}[layout]
+    o, lse, low = st.st_ring_fwd(q, ks, vs, *args, list(range(n)))
+
+    def run(q, ks, vs, d_o, low, order):
+        dq, dk, dv = torch.zeros_like(o), [torch.zeros(k.shape, device="cuda") for k in ks], [torch.zeros(k.shape, device="cuda") for k in ks]
+        st.st_profile_begin()
+        try:
+            st.st_ring_bwd(q, ks, vs, d_o, low, lse, *args, order, dq, dk, dv)
+        finally:
+            ran = st.st_profile_end()
+        assert "bwd_one_bf16" in ran
+        return [dq, *dk, *dv]
+
+    with launcher_switch("one_walk", 2, 1):
+        want = run(q, ks, vs, d_o, low, [0, 1, 2])
+        got = run(how_q(q), [how_k(x) for x in ks], [how_v(x) for x in vs], how_do(d_o), how_do(low), [2, 0, 1] if causal else [0, 1, 2])
+    assert all(torch.equal(x, y) for x, y in zip(got, want))
+    dq_r, dk_r, dv_r = oa.attention_backward(inp.q, inp.k, inp.v, inp.d_o, *positions(w), causal, w.scale)
+    assert_close_wide(host(want[0]), dq_r, "dq")
+    for j in range(n):
+        assert_close_wide(host(want[1 + j]), dk_r[j], f"dk[{j}]")
+        assert_close_wide(host(want[1 + n + j]), dv_r[j], f"dv[{j}]")
+
+
 @pytest.mark.gpu
 @pytest.mark.parametrize("D", [128, 64])
 def test_one_walk_in_a_graph(D):
@@ -202,3 +294,11 @@ def test_where_one_walk_is_planned():
     heads, size = batch(_ring(BF16, 1, 32, 8, 128, 4096, 32, 31))
     # 16 KiB a pair of head and block, two more a KV head, and less than 1 MiB of counts
     assert 0 <= size - 16384 * (32 * 128 + 2 * 8) < 1 << 20
+
+
+@pytest.mark.parametrize("share,heads", [(_ring(BF16, 1, 16, 16, 128, 1024, 8, 7), 2), (_ring(BF16, 1, 24, 24, 64, 16384, 8, 3, False), 3),
+                                         (_ring(BF16, 2, 16, 16, 64, 512, 8, 5), 4), (_ring(BF16, 1, 48, 48, 128, 512, 8, 7), 6),
+                                         (_ring(BF16, 1, 64, 64, 64, 512, 8, 7), 8)], ids=lambda x: x.text if isinstance(x, Share) else str(x))
+def test_batches_that_are_planned(share, heads):
+    """All heads of an XCD at once where chains are short (the others run one head's tiles behind each other: the case above)."""
+    assert share.plan(list(range(len(share.offsets))), FUSED, True, -1)[0][9] == -heads
