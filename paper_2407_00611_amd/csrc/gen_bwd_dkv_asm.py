@@ -253,13 +253,14 @@ def stat_publish(e, st_set, stage, tag):
 
 
 class Pool:
-    """Round-robin fragment registers; NPOOL divides the 48 fragments of a block, so every block sees the same map."""
+    """Round-robin fragment registers; their number divides the 48 fragments of a block, so every block sees the same map."""
+    size = NPOOL
 
     def __init__(self):
         self.next, self.owner, self.uses_left, self.reg = 0, {}, {}, {}
 
     def alloc(self, tag, uses):
-        i = self.next % NPOOL
+        i = self.next % self.size
         self.next += 1
         old = self.owner.get(i)
         assert old is None or self.uses_left[old] == 0, f"fragment {old} overwritten by {tag} before its last use"

@@ -91,14 +91,13 @@ MASK_HIGH = FLG if D == 128 else XK                  # a register that is free w
 S_DQL, S_DQW, S_DQINC, S_POLLS, S_CNT, S_PRED, S_OWN = 52, 54, 57, 58, 59, 60, 62
 
 LAT = int(os.environ.get("ST_GEN_ONE_LAT", 3))
-LATQ = int(os.environ.get("ST_GEN_ONE_LATQ", 3))
+LATQ = 3                                             # the same for the operands of a pair
 BUDGET = int(os.environ.get("ST_GEN_ONE_BUDGET", 6 if D == 128 else 11))
-BUDGET_Q = int(os.environ.get("ST_GEN_ONE_BUDGETQ", 4))
+BUDGET_Q = 4                                         # issue units behind an MFMA of a pair
 EARLY = 12
 SYNC_SLOT, PUBLISH_SLOT = P3 - 1, P3 - 6
 # slots behind which the MFMAs of a pair are issued, from the barrier of one block (slot 32 on) to that of the next (64 + 26)
-DQ_AT = [int(x) for x in os.environ.get("ST_GEN_ONE_AT", "35,37,39,41,43,45,47,49,52,55,58,61,80,82,84,86" if D == 128 else
-                                        "19,19,21,21,23,23,25,25,27,27,29,29,31,31,33,33").split(",")]
+DQ_AT = [35, 37, 39, 41, 43, 45, 47, 49, 52, 55, 58, 61, 80, 82, 84, 86] if D == 128 else [19 + 2 * (t // 2) for t in range(16)]
 N_DQ = 16                                            # head size 64: of 16 columns, 32 keys and 16 rows
 assert len(DQ_AT) == N_DQ and DQ_AT == sorted(DQ_AT) and DQ_AT[0] - LATQ > SYNC_SLOT and DQ_AT[-1] <= NSLOT + P3 - (6 if D == 128 else 8)
 N_A = sum(1 for p in DQ_AT if p < NSLOT)             # of them in the block behind the pair's own
@@ -106,12 +105,9 @@ SUM_SLOT = P3 - 3                                    # the sums behind this slot
 NREQ = 2 + 2 * NDQ
 
 
-if D == 64:
-    kv.NPOOL = 8                                     # divides the sixteen fragments of a block that lie there
-
-
 class Pool(kv.Pool):
-    """Head size 64 has the fragments of dS^T in accumulator registers."""
+    """Head size 64 has the fragments of dS^T in accumulator registers, and eight here, which divides the sixteen a block has left."""
+    size = kv.Pool.size if D == 128 else 8
 
     def __init__(self):
         super().__init__()
@@ -815,7 +811,7 @@ def generate():
     l_whole, l_masked = ([e.label(f"{x}{u}") for u in range(COPIES)] for x in ("whole", "masked"))
     strip = lambda tags: [t.lstrip("0123456789") for t in tags]
     entry, entry_pool = list(e.ds), pool.state()
-    at = [(strip(entry), pool.next % kv.NPOOL)]
+    at = [(strip(entry), pool.next % pool.size)]
     e.raw(f"s_cmp_le_u32 {sr(T_REM)}, {sr(S_EVT)}")
     e.raw(f"s_cbranch_scc1 {l_masked[0]}")
     stubs = []
@@ -825,7 +821,7 @@ def generate():
             pool.restore(entry_pool)
         for u in range(COPIES):
             e.raw((l_masked if masked else l_whole)[u] + ":")
-            assert (strip(e.ds), pool.next % kv.NPOOL) == at[u], (e.ds, at[u])
+            assert (strip(e.ds), pool.next % pool.size) == at[u], (e.ds, at[u])
             if u == COPIES - 1:
                 plans[COPIES] = plan_reads(e, pool, 0, COPIES)
             gen_step(e, pool, u, u, plans[u], plans[u + 1], dq[u][1], dq[u + 1][1], dq[u + 1][0], masked)
@@ -842,9 +838,9 @@ def generate():
                 e.raw(f"s_cmp_le_u32 {sr(T_REM)}, {sr(S_EVT)}")
                 e.raw(f"s_cbranch_scc1 {l_leave}")
             if not masked and u < COPIES - 1:
-                at.append((strip(e.ds), pool.next % kv.NPOOL))
+                at.append((strip(e.ds), pool.next % pool.size))
         # writes of dS may be under way here that are not behind the prologue: waits made without them wait for more
-        assert ([t for t in strip(e.ds) if not t.startswith("ds")], pool.next % kv.NPOOL) == at[0], (e.ds, at[0])
+        assert ([t for t in strip(e.ds) if not t.startswith("ds")], pool.next % pool.size) == at[0], (e.ds, at[0])
         e.raw(f"s_branch {(l_masked if masked else l_whole)[0]}")
     for l_leave, l_to, l_end in stubs:
         e.raw(l_leave + ":")
