@@ -352,7 +352,7 @@ def main() -> int:
         # executed MFMA work of each hand-scheduled loop (the dQ loop recomputes S and dP: 6 D per pair for the 2 D it
         # is credited with) against what its instruction mix alone reaches on the workload's data
         mixes = ceiling["workload_q_with_side_instructions"]
-        for name, mix, executed_per_credited in (("fwd_bf16", "fwd", 1), ("bwd_dkv_bf16", "dkv", 1), ("bwd_dq_bf16", "dq", 3)):
+        for name, mix, executed_per_credited in (("fwd_bf16", "fwd", 1), ("bwd_dkv_bf16", "dkv", 1), ("bwd_dq_bf16", "dq", 3), ("bwd_one_bf16", "one", 1)):
             if name in per_kernel and "algorithmic_tflops" in per_kernel[name]:
                 ex = per_kernel[name]["algorithmic_tflops"] * executed_per_credited
                 per_kernel[name]["executed_tflops"] = round(ex, 1)

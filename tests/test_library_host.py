@@ -197,6 +197,7 @@ def test_mfma_probe_mixes_and_validation():
     names = [api.st_mfma_probe_mix_name(m) for m in range(n + 1)]
     assert names[0] == "none" and len(set(names)) == n + 1 and all(names)
     assert {"fwd", "dq", "dkv", "fwd64", "dq64", "dkv64"} <= set(names)
+    assert {"one", "one64"} <= set(names)
     assert api.st_mfma_probe_mix_name(n + 1) == "" and api.st_mfma_probe_mix_name(-1) == ""
     flop = C.c_double(-1.0)
 
