@@ -248,7 +248,9 @@ st_status st_ring_fwd(const st_ring_desc* desc, const st_tensor* q, const int32_
 
 /* Backward outputs (all ACCUMULATED, caller zeroes once): dq_acc fp32 [B,Sq,Hq,D];
  * dk_acc, dv_acc host arrays [n_chunks] of device fp32 [B,Sk,Hkv,D] buffers (entries of chunks
- * that are not visited may be NULL).  o: final O in o_dtype; lse_final from st_ring_fwd. */
+ * that are not visited may be NULL).  o: final O in o_dtype; lse_final from st_ring_fwd.
+ * Workgroups of a launch may pass sums on to one another; should one be kept waiting for seconds, which no schedule of them
+ * does, all gradients of the launch are NaN. */
 st_status st_ring_bwd(const st_ring_desc* desc, const st_tensor* q, const st_tensor* d_o,
                       const st_tensor* o, int32_t o_dtype, const float* lse_final,
                       const int32_t* order, int32_t n_visit, int32_t mode,

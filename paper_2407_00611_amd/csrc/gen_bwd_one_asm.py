@@ -25,10 +25,11 @@ a pair in place of the seven that the loop there and the one of gen_bwd_dq_asm.p
     offset are immediates, which leaves the sixteen registers that dQ's accumulator takes.
   * Three stages of tiles, two blocks ahead; with the two buffers of dS six copies of the block make the loop.
 
-What bounds it: the matrix cores at the chip's power limit, as with the two loops it replaces.  A loop of this instruction mix
-without dependences (80 MFMAs, 44 16-byte and 96 transposing LDS reads, 96 VALU instructions, the exchange of a pair and the tile loads per
-block and wavefront) takes 2085 ns on random data, those of the two loops 1547 + 1115.  Backward of 32/8 heads x 4096 rows x 32 chunks
-20.0 -> 16.8 ms, 32 heads x 2048 rows x 16 chunks 2.75 -> 2.39 (64 blocks a tile: 25 us of its 150 are before and behind the loop).
+What bounds it: the matrix cores at the chip's power limit, as with the two loops it replaces.  Its instruction mix without dependences and
+global memory operations (gen_probe_asm.py, "one": 80 MFMAs, 40 16-byte and 96 transposing LDS reads, 8 writes, 112 VALU instructions per block
+and wavefront) reaches 1451 TFLOP/s on normal values, the walk of 32/8 heads x 4096 rows x 32 chunks 1294 on that card, and the two
+passes, each within 1 % of its mix, execute 14/10 of the work at 1495 and 1569.  The rest is the exchange of sums, waits of the chain and, of the 150 us of a
+tile of 64 blocks, 25 before and behind the loop.  Backward of that share 20.0 -> 16.8 ms, 32 heads x 2048 rows x 16 chunks 2.75 -> 2.39.
 Where the MFMAs of a pair lie in the block, how far ahead their operands are read and how much side work a slot gets moved that by less than
 1 % each; half of them under the first phase, whose reads are the densest, cost 3 %.
 
