@@ -133,7 +133,7 @@ class Pool(kv.Pool):
 class OneEmitter(Emitter):
     def __init__(self):
         super().__init__()
-        self.give_ups = []                              # (label, where it goes back to) of every wait
+        self.waits = []                                 # (label, where it goes back to, the count's scalar) of the polls
 
     def ds_read(self, text, tag):
         if len(self.ds) >= 15:                          # the counter has four bits
@@ -158,10 +158,8 @@ def flag_load(e):
 
 def flag_wait(e, newer, ahead=0):
     """Until the tile before has counted the pair (`ahead` pairs behind this tile's own count); `newer` memory operations were issued
-    behind the load of its count.  At most S_POLLS polls (seconds): a tile waits for running workgroups only and never needs so many, but a
-    launch has to end whatever happens, and not with wrong sums unnoticed (gen_give_up)."""
-    l_spin, l_ok, l_give_up = e.label("spin"), e.label("counted"), e.label("giveup")
-    e.give_ups.append((l_give_up, l_ok))
+    behind the load of its count (None: ask again).  What is not there yet is waited for out of line (gen_polls)."""
+    l_polls, l_ok = e.label("polls"), e.label("counted")
     need = S_CNT
     if ahead:
         need = T_INC
@@ -170,27 +168,31 @@ def flag_wait(e, newer, ahead=0):
         e.raw(f"s_waitcnt vmcnt({newer})")
         e.raw(f"v_readfirstlane_b32 {sr(T_MT)}, {vr(FLG)}")
         e.raw(f"s_cmp_ge_i32 {sr(T_MT)}, {sr(need)}")
-        e.raw(f"s_cbranch_scc1 {l_ok}")
+        e.raw(f"s_cbranch_scc0 {l_polls}")
+    else:
+        e.raw(f"s_branch {l_polls}")
+    e.raw(l_ok + ":")
+    e.waits.append((l_polls, l_ok, need))
+
+
+def gen_polls(e, label, l_back, need):
+    """At most S_POLLS polls (seconds): a tile waits for running workgroups only and never needs so many, but a launch has to end
+    whatever happens, and not with wrong sums unnoticed.  A wavefront that has used them up takes every pair from here on for counted, so
+    that a launch waits that long once a wavefront and not once a pair, and marks the launch as one without gradients (add_pairs_kernel
+    writes NaN).  Leaves no memory operation under way; the waits behind it count later ones only."""
+    l_spin = e.label("spin")
+    e.raw(label + ":")
     e.raw(f"s_mov_b32 {sr(T_X)}, {sr(S_POLLS)}")
     e.raw(l_spin + ":")
     flag_load(e)
     e.raw("s_waitcnt vmcnt(0)")
     e.raw(f"v_readfirstlane_b32 {sr(T_MT)}, {vr(FLG)}")
     e.raw(f"s_cmp_ge_i32 {sr(T_MT)}, {sr(need)}")
-    e.raw(f"s_cbranch_scc1 {l_ok}")
+    e.raw(f"s_cbranch_scc1 {l_back}")
     e.raw("s_sleep 1")
     e.raw(f"s_sub_u32 {sr(T_X)}, {sr(T_X)}, 1")
     e.raw(f"s_cmp_lg_u32 {sr(T_X)}, 0")
     e.raw(f"s_cbranch_scc1 {l_spin}")
-    e.raw(f"s_branch {l_give_up}")
-    e.raw(l_ok + ":")
-
-
-def gen_give_up(e, label, l_back):
-    """A wait that has used up its polls, out of line: from here on this wavefront takes every pair for counted, and the launch is marked
-    as one without gradients (add_pairs_kernel writes NaN).  So a launch waits that long once a wavefront, not once a pair.  Leaves
-    no memory operation under way, as the last poll does; the waits behind it count later ones only."""
-    e.raw(label + ":")
     e.raw(f"s_add_u32 {sr(T_X)}, {sr(S_LDS)}, {PBLK + 256 * 32}")
     e.raw(f"v_mov_b32 {vr(TMP)}, {sr(T_X)}")
     e.raw(f"ds_read_b64 {vr(TMP, 2)}, {vr(TMP)} offset:{4 * U_PLENTY}")
@@ -854,8 +856,8 @@ def generate():
         e.raw(l_tail[buf] + ":")
         gen_tail(e, buf)
         e.raw(f"s_branch {l_done}")
-    for l_give_up, l_back in e.give_ups:
-        gen_give_up(e, l_give_up, l_back)
+    for wait in e.waits:
+        gen_polls(e, *wait)
     e.raw(l_done + ":")
     e.comment("---- what the epilogue needs, from LDS")
     e.raw(f"s_add_u32 {sr(T_X)}, {sr(S_LDS)}, {PBLK + 256 * 32}")
